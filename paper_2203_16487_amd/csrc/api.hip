@@ -27,7 +27,7 @@ struct DecLayer {
 };
 
 // LayerNorm folded into the projections that read its output: ln3 of the layer below -> wqkv
-// (unused in layer 0), ln1 -> cwq, ln2 -> w1.
+// (layer 0: none), ln1 -> cwq, ln2 -> w1.
 struct LnFolds {
   sd::LnFold qkv, cq, w1;
   const float *vo, *vco, *v2;   // column vectors of the three residual sums (wo, cwo, w2), [3][d] each
@@ -68,7 +68,7 @@ struct Model {
   int rs_parity = 0;
   int rs_seq = 0;
   bf16* xb = nullptr;        // [Rmax][d]
-  float* lnp[2] = {nullptr, nullptr};   // [rows][d/64 rounded up to even][2] chunk pairs of the two latest residual sums
+  float* lnp[2] = {nullptr, nullptr};   // [rows][d/32 at most][2] chunk pairs of the two latest residual sums
   float* fold = nullptr;     // per decoder layer: cs and bf vectors of wqkv, cwq, w1 (LayerNorm folded)
   std::vector<LnFolds> folds;
   bf16* q = nullptr;         // [Rmax][d]
@@ -267,8 +267,8 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     t.w8s = cv.take<float>((size_t)d->dec_layers * (7 * D + F) + (size_t)d->vocab);
   }
   t.xb = cv.take<bf16>(Rmax * D);
-  t.lnp[0] = cv.take<float>(Rmax * (D / 64 + 1) * 2);
-  t.lnp[1] = cv.take<float>(Rmax * (D / 64 + 1) * 2);
+  t.lnp[0] = cv.take<float>(Rmax * (D / 32) * 2);
+  t.lnp[1] = cv.take<float>(Rmax * (D / 32) * 2);
   t.fold = cv.take<float>((size_t)d->dec_layers * (2 * (3 * D + D + F) + 9 * D));
   t.q = cv.take<bf16>((Rmax > 32 ? Rmax : 32) * D);
   t.att = cv.take<bf16>(Rmax * D);
@@ -340,13 +340,12 @@ int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool 
   // LayerNorm folded into the GEMMs on both sides of it: m.x holds the un-normalised sum, m.xb
   // that sum times the gain, `pend` the LayerNorm still to be applied to them.
   const bool fold = !c->no_ln_fold;
-  const float* pend = nullptr;   // chunk pairs of the sum in m.x (null: m.x is the residual itself)
-  int flip = 0;
+  sd::LnPairs pend{m.lnp[0], 0};   // chunk pairs of the sum in m.x (0 chunks: m.x is the residual itself)
+  int flip = 1;
   auto sum = [&](const bf16* A, int K, const bf16* W, const float* vecs) {
     float* out = m.lnp[flip];
-    hipError_t e = sd::gemm_ln_sum(st, A, K, W, R, D, K, vecs, pend ? pend : m.lnp[flip ^ 1], pend != nullptr, m.x, m.xb, out,
-                                   m_real);
-    pend = out;
+    hipError_t e = sd::gemm_ln_sum(st, A, K, W, R, D, K, vecs, pend, m.x, m.xb, out, m_real);
+    pend = sd::LnPairs{out, sd::ln_sum_chunks(R, D)};
     flip ^= 1;
     return e;
   };
@@ -354,9 +353,8 @@ int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool 
     const DecLayer& L = m.dec[l];
     bf16* kc = m.kc + m.kv_layer * l;
     bf16* vc = m.vc + m.kv_layer * l;
-    if (fold && l > 0) {
-      LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_ln_qkv_append(st, m.xb, L.wqkv, R, D, m.folds[l].qkv, pend, m.q, kc,
-                                       vc, m.rm.row_b, m.rm.row_pos, H, Lcap, m_real));
+    if (fold) {
+      LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_ln_qkv_append(st, m.xb, L.wqkv, R, D, m.folds[l].qkv, pend, m.q, kc, vc, m.rm.row_b, m.rm.row_pos, H, Lcap, m_real));
     } else {
       LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_qkv_append(st, m.xb, L.wqkv, R, D, D, L.bqkv, m.q, kc, vc, m.rm.row_b,
                                     m.rm.row_pos, H, Lcap, m_real));
@@ -683,7 +681,7 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
       HIPCHK(c, sd::ln_sum_vecs(S(stream), L.bo, g0, b0, L.ln1g, D, v));
       HIPCHK(c, sd::ln_sum_vecs(S(stream), L.cbo, L.ln1g, L.ln1b, L.ln2g, D, v + 3 * D));
       HIPCHK(c, sd::ln_sum_vecs(S(stream), L.b2, L.ln2g, L.ln2b, L.ln3g, D, v + 6 * D));
-      if (l > 0) HIPCHK(c, sd::ln_fold(S(stream), L.wqkv, m.dec[l - 1].ln3g, m.dec[l - 1].ln3b, L.bqkv, 3 * D, D, o.qkv));
+      HIPCHK(c, sd::ln_fold(S(stream), L.wqkv, g0, b0, L.bqkv, 3 * D, D, o.qkv));
       HIPCHK(c, sd::ln_fold(S(stream), L.cwq, L.ln1g, L.ln1b, L.cbq, D, D, o.cq));
       HIPCHK(c, sd::ln_fold(S(stream), L.w1, L.ln2g, L.ln2b, L.b1, F, D, o.w1));
     }

@@ -292,7 +292,7 @@ hipError_t gemm_enc_qkv(hipStream_t st, const bf16* A, const bf16* W, int M, int
 // ----------------------------------------------------------------------------- LayerNorm folded into the GEMMs
 // Post-LN blocks: x' = LN(y), y = x + sublayer(x).  Instead of a pass of its own over y, the
 // normalisation is split between the GEMM that produces y and the GEMMs that consume x':
-//   producer (EpiLnSum)   writes y (fp32), bf16(y * g) and, for every 64-column chunk of every row,
+//   producer (EpiLnSum)   writes y (fp32), bf16(y * g) and, for every 64- (or 32-) column chunk of every row,
 //                         the pair {sum, sum of squared deviations from the chunk mean};
 //   consumer (EpiLn*)     multiplies bf16(y * g) by the unchanged weights and finishes
 //                         LN(y) W^T + b = rstd * (acc - mean * cs) + bf,
@@ -308,61 +308,80 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // Sums over aligned groups of 2, 4 or 8 neighbouring lanes with DPP moves (no LDS round trip).
 template <int LANES>
 __device__ __forceinline__ float group_sum(float v) {
-  static_assert(LANES == 2 || LANES == 4 || LANES == 8, "group size");
+  static_assert(LANES == 2 || LANES == 4 || LANES == 8 || LANES == 16 || LANES == 32, "group size");
   v += dpp_f<kDppSwap1>(v);
   if (LANES >= 4) v += dpp_f<kDppSwap2>(v);
   if (LANES >= 8) v += dpp_f<kDppHalfMirror>(v);
+  if (LANES >= 16) v += dpp_f<kDppMirror>(v);
+  if (LANES >= 32) v += __shfl_xor(v, 16, 64);
   return v;
 }
 
-// Chunk pairs of a row lie together, [M][pitch] pairs with pitch = chunks rounded up to even, so a
-// thread fetches two pairs per 16-byte load.
+// V consecutive columns (V = 2, 4 or 8; addresses aligned to V elements) as whole words
+template <int V>
+__device__ __forceinline__ void load_cols(const float* p, float (&o)[V]) { __builtin_memcpy(o, __builtin_assume_aligned(p, V == 2 ? 8 : 16), V * 4); }
+template <int V>
+__device__ __forceinline__ void store_cols(float* p, const float (&v)[V]) { __builtin_memcpy(__builtin_assume_aligned(p, V == 2 ? 8 : 16), v, V * 4); }
+template <int V>
+__device__ __forceinline__ void store_cols(bf16* p, const bf16 (&v)[V]) { __builtin_memcpy(__builtin_assume_aligned(p, V * 2), v, V * 2); }
+
+// Chunk pairs of a row lie together, [M][pitch] pairs with pitch = chunks rounded up to even, so a thread fetches two
+// pairs per 16-byte load.  A chunk is 64 columns, or 32 where the kernel that formed the sums has tiles of 32 columns
+// (few rows): wider chunks are fewer bytes for every consumer (256 rows x 32 pairs are 64 KB per 256 x 128 tile).
 __host__ __device__ __forceinline__ int ln_pitch(int chunks) { return (chunks + 1) & ~1; }
+
+// Mean and rstd of one row from its chunk pairs (the parallel-variance formula): TPR neighbouring threads hold pairs
+// 2q, 2q+1 for q = j + i * TPR in p; the first of them writes {rstd, -mean * rstd} ({1, 0} for identity: nothing to
+// normalise).
+template <int TPR, int NL>
+__device__ __forceinline__ void ln_row_stats(const f32x4 (&p)[NL], int j, int d, int chunks, bool identity, bool writer,
+                                             float* out) {
+  const float inv_d = __builtin_amdgcn_rcpf((float)d);   // exact for powers of two
+  const float cw = d == 32 * chunks ? 32.f : 64.f, inv_cw = d == 32 * chunks ? 1.f / 32 : 1.f / 64;   // chunk width
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    if (2 * i * TPR >= chunks) continue;
+    const int c = 2 * (j + i * TPR);
+    s += (c < chunks ? p[i][0] : 0.f) + (c + 1 < chunks ? p[i][2] : 0.f);
+  }
+  s = group_sum<TPR>(s);
+  const float mean = s * inv_d;
+  float q = 0.f;
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    if (2 * i * TPR >= chunks) continue;
+    const int c = 2 * (j + i * TPR);
+    const float d0 = p[i][0] * inv_cw - mean, d1 = p[i][2] * inv_cw - mean;
+    q += (c < chunks ? p[i][1] + cw * d0 * d0 : 0.f) + (c + 1 < chunks ? p[i][3] + cw * d1 * d1 : 0.f);
+  }
+  q = group_sum<TPR>(q);
+  if (writer && j == 0) {
+    const float rstd = identity ? 1.f : fast_rsqrt(q * inv_d + 1e-5f);
+    out[0] = rstd;
+    out[1] = identity ? 0.f : -mean * rstd;
+  }
+}
 
 template <class Cfg>
 struct LnRows {
   static constexpr int TPR = Cfg::kThreads / Cfg::kBM;   // threads that share one tile row
-  static constexpr int NL = 16 / TPR;                    // 16-byte loads per thread (d <= 2048)
+  static constexpr int NL = 32 / TPR;                    // 16-byte loads per thread (d <= 2048)
   static_assert(TPR == 2 || TPR == 4, "threads per row");
   f32x4 p[NL];                                           // pairs 2q, 2q+1 for q = j + i * TPR
   // Loads sit behind conditions on kernel arguments only (no lane takes a branch of its own).
   __device__ __forceinline__ void request(const f32x2* part, int chunks, int m0, int M) {
     const int r = threadIdx.x / TPR, j = threadIdx.x % TPR;
-    const int pitch = ln_pitch(chunks);
-    const f32x4* src = reinterpret_cast<const f32x4*>(part + (size_t)min(m0 + r, M - 1) * pitch);
+    const f32x4* src = reinterpret_cast<const f32x4*>(part + (size_t)min(m0 + r, M - 1) * ln_pitch(chunks));
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       p[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (2 * i * TPR < chunks) p[i] = src[min(j + i * TPR, pitch / 2 - 1)];
+      if (2 * i * TPR < chunks) p[i] = src[min(j + i * TPR, ln_pitch(chunks) / 2 - 1)];
     }
   }
-  // rowstat [BM][2] in LDS: {rstd, -mean * rstd}; {1, 0} when there is nothing to normalise
-  __device__ __forceinline__ void finish(int chunks, bool identity, float* rowstat) const {
-    const int r = threadIdx.x / TPR, j = threadIdx.x % TPR;
-    const float inv_d = __builtin_amdgcn_rcpf((float)(64 * chunks));   // d = 2^6 * chunks: exact for powers of two
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      if (2 * i * TPR >= chunks) continue;
-      const int c = 2 * (j + i * TPR);
-      s += (c < chunks ? p[i][0] : 0.f) + (c + 1 < chunks ? p[i][2] : 0.f);
-    }
-    s = group_sum<TPR>(s);
-    const float mean = s * inv_d;
-    float q = 0.f;
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      if (2 * i * TPR >= chunks) continue;
-      const int c = 2 * (j + i * TPR);
-      const float d0 = p[i][0] * (1.0f / 64.0f) - mean, d1 = p[i][2] * (1.0f / 64.0f) - mean;
-      q += (c < chunks ? p[i][1] + 64.0f * d0 * d0 : 0.f) + (c + 1 < chunks ? p[i][3] + 64.0f * d1 * d1 : 0.f);
-    }
-    q = group_sum<TPR>(q);
-    if (j == 0) {
-      const float rstd = identity ? 1.f : fast_rsqrt(q * inv_d + 1e-5f);
-      rowstat[2 * r] = rstd;
-      rowstat[2 * r + 1] = identity ? 0.f : -mean * rstd;
-    }
+  // rowstat [BM][2] in LDS
+  __device__ __forceinline__ void finish(int d, int chunks, bool identity, float* rowstat) const {
+    ln_row_stats<TPR, NL>(p, threadIdx.x % TPR, d, chunks, identity, true, rowstat + 2 * (threadIdx.x / TPR));
   }
 };
 
@@ -371,6 +390,7 @@ struct LnRows {
 //   0: gain of the LayerNorm pending on x (1 without one)
 //   1: its shift (0 without one) + this GEMM's bias
 //   2: gain of the LayerNorm that follows
+// An epilogue handles V consecutive columns of one row; CW / V neighbouring lanes hold one chunk of CW columns.
 struct EpiLnSum {
   static constexpr int kVec = 3;
   const float* __restrict__ vecs;
@@ -378,52 +398,49 @@ struct EpiLnSum {
   f32x2* ln_out;                   // chunk pairs of the new sum
   float* x;
   bf16* __restrict__ xg;           // bf16(y * next gain)
-  int ld, chunks;
+  int ld, chunks;                  // d; chunks of y_prev
   int has_prev;                    // 0: x is the residual itself
+  __device__ __forceinline__ int d_ln() const { return ld; }
   __device__ __forceinline__ const float* vec(int i) const { return vecs + i * ld; }
   __device__ __forceinline__ bool identity() const { return has_prev == 0; }
-  struct Pre { f32x4 r0, r1; };
-  __device__ __forceinline__ Pre fetch(int m, int n) const {
-    const size_t o = (size_t)m * ld + n;
-    return Pre{*reinterpret_cast<const f32x4*>(x + o), *reinterpret_cast<const f32x4*>(x + o + 4)};
-  }
+  template <int V> struct Pre { float r[V]; };
+  template <int V>
+  __device__ __forceinline__ void fetch(int m, int n, Pre<V>& p) const { load_cols<V>(x + (size_t)m * ld + n, p.r); }
   // called by every lane (live = inside the matrix): the chunk sums cross lanes
-  __device__ __forceinline__ void store(int m, int n, bool live, const float (&v)[8], const Pre& p,
-                                        float rstd, float nmr, const float (&cv)[kVec][8]) const {
-    float y[8], s = 0.f, ss = 0.f;
+  template <int V, int CW>
+  __device__ __forceinline__ void store(int m, int n, bool live, const float (&v)[V], const Pre<V>& p,
+                                        float rstd, float nmr, const float (&cv)[kVec][V]) const {
+    float y[V], s = 0.f, ss = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float r = i < 4 ? p.r0[i] : p.r1[i - 4];
-      y[i] = v[i] + __builtin_fmaf(__builtin_fmaf(r, rstd, nmr), cv[0][i], cv[1][i]);
+    for (int i = 0; i < V; ++i) {
+      y[i] = v[i] + __builtin_fmaf(__builtin_fmaf(p.r[i], rstd, nmr), cv[0][i], cv[1][i]);
       s += y[i];
       ss = __builtin_fmaf(y[i], y[i], ss);
     }
-    s = group_sum<8>(s);     // 8 lanes = one 64-column chunk
-    ss = group_sum<8>(ss);
+    s = group_sum<CW / V>(s);
+    ss = group_sum<CW / V>(ss);
     if (!live) return;
     const size_t o = (size_t)m * ld + n;
-    *reinterpret_cast<f32x4*>(x + o) = f32x4{y[0], y[1], y[2], y[3]};
-    *reinterpret_cast<f32x4*>(x + o + 4) = f32x4{y[4], y[5], y[6], y[7]};
-    bf16x8 g;
+    store_cols<V>(x + o, y);
+    bf16 g[V];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) g[i] = (bf16)(y[i] * cv[2][i]);
-    *reinterpret_cast<bf16x8*>(xg + o) = g;
-    // squared deviations from the chunk mean = sum y^2 - (sum y)^2 / 64, never below 0
-    if ((n & 63) == 0) ln_out[(size_t)m * ln_pitch(chunks) + (n >> 6)] = f32x2{s, fmaxf(ss - s * s * (1.0f / 64.0f), 0.f)};
+    for (int i = 0; i < V; ++i) g[i] = (bf16)(y[i] * cv[2][i]);
+    store_cols<V>(xg + o, g);
+    // squared deviations from the chunk mean = sum y^2 - (sum y)^2 / CW, never below 0
+    if (n % CW == 0) ln_out[(size_t)m * ln_pitch(ld / CW) + n / CW] = f32x2{s, fmaxf(ss - s * s * (1.0f / CW), 0.f)};
   }
 };
 
-// rstd * (acc - mean * cs) + bf on 8 columns: cv[0] = cs, cv[1] = bf
-__device__ __forceinline__ bf16x8 ln_finish(const float (&v)[8], float rstd, float nmr, const float (&cv)[2][8],
-                                            bool relu) {
-  bf16x8 o;
+// rstd * (acc - mean * cs) + bf on V columns: cv[0] = cs, cv[1] = bf
+template <int V>
+__device__ __forceinline__ void ln_finish(const float (&v)[V], float rstd, float nmr, const float (&cv)[2][V],
+                                          bool relu, bf16 (&o)[V]) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < V; ++i) {
     float t = __builtin_fmaf(v[i], rstd, __builtin_fmaf(nmr, cv[0][i], cv[1][i]));
     if (relu) t = fmaxf(t, 0.f);
     o[i] = (bf16)t;
   }
-  return o;
 }
 
 struct EpiLnBf16 {
@@ -432,46 +449,60 @@ struct EpiLnBf16 {
   const float* __restrict__ bf;
   const f32x2* ln_in;
   bf16* __restrict__ out;
-  int ldo, chunks, relu;
+  int ldo, d, chunks, relu;
+  int has_prev;                    // 0: A holds the input itself, no LayerNorm pending on it
+  __device__ __forceinline__ int d_ln() const { return d; }
   __device__ __forceinline__ const float* vec(int i) const { return i == 0 ? cs : bf; }
-  __device__ __forceinline__ bool identity() const { return false; }
-  struct Pre {};
-  __device__ __forceinline__ Pre fetch(int, int) const { return Pre{}; }
-  __device__ __forceinline__ void store(int m, int n, bool live, const float (&v)[8], const Pre&,
-                                        float rstd, float nmr, const float (&cv)[kVec][8]) const {
-    if (live) *reinterpret_cast<bf16x8*>(out + (size_t)m * ldo + n) = ln_finish(v, rstd, nmr, cv, relu != 0);
+  __device__ __forceinline__ bool identity() const { return has_prev == 0; }
+  template <int V> struct Pre {};
+  template <int V>
+  __device__ __forceinline__ void fetch(int, int, Pre<V>&) const {}
+  template <int V, int CW>
+  __device__ __forceinline__ void store(int m, int n, bool live, const float (&v)[V], const Pre<V>&,
+                                        float rstd, float nmr, const float (&cv)[kVec][V]) const {
+    bf16 o[V];
+    ln_finish<V>(v, rstd, nmr, cv, relu != 0, o);
+    if (live) store_cols<V>(out + (size_t)m * ldo + n, o);
   }
 };
 
+// Decoder self-attention projection: columns [0,d) are queries, [d,2d) keys, [2d,3d) values.
+// Keys and values go straight into the cache rows of the token they belong to: this is the
+// "append" of the KV cache, fused into the projection.  Both caches are [B][H][Lcap][64].
 struct EpiLnQkvAppend {
   static constexpr int kVec = 2;
   const float* __restrict__ cs;
   const float* __restrict__ bf;
   const f32x2* ln_in;
   int chunks;
+  int has_prev;                    // 0: A holds the input itself (embeddings), no LayerNorm pending on it
   bf16* __restrict__ q;
   bf16* __restrict__ kc;
   bf16* __restrict__ vc;
   const int* __restrict__ row_b;
   const int* __restrict__ row_pos;
   int d, H, Lcap;
+  __device__ __forceinline__ int d_ln() const { return d; }
   __device__ __forceinline__ const float* vec(int i) const { return i == 0 ? cs : bf; }
-  __device__ __forceinline__ bool identity() const { return false; }
-  struct Pre { int sb, pos; };
-  __device__ __forceinline__ Pre fetch(int m, int) const { return Pre{row_b[m], row_pos[m]}; }
-  __device__ __forceinline__ void store(int m, int n, bool live, const float (&v)[8], const Pre& p,
-                                        float rstd, float nmr, const float (&cv)[kVec][8]) const {
+  __device__ __forceinline__ bool identity() const { return has_prev == 0; }
+  template <int V> struct Pre { int sb, pos; };
+  template <int V>
+  __device__ __forceinline__ void fetch(int m, int, Pre<V>& p) const { p.sb = row_b[m]; p.pos = row_pos[m]; }
+  template <int V, int CW>
+  __device__ __forceinline__ void store(int m, int n, bool live, const float (&v)[V], const Pre<V>& p,
+                                        float rstd, float nmr, const float (&cv)[kVec][V]) const {
     if (!live) return;
-    const bf16x8 o = ln_finish(v, rstd, nmr, cv, false);
+    bf16 o[V];
+    ln_finish<V>(v, rstd, nmr, cv, false, o);
     const int part = n / d, cc = n - part * d;
     if (part == 0) {
-      *reinterpret_cast<bf16x8*>(q + (size_t)m * d + cc) = o;
+      store_cols<V>(q + (size_t)m * d + cc, o);
       return;
     }
     if (p.sb < 0) return;
     const int h = cc >> 6, e = cc & 63;
     bf16* cache = (part == 1) ? kc : vc;
-    *reinterpret_cast<bf16x8*>(cache + (((size_t)p.sb * H + h) * Lcap + p.pos) * kHeadDim + e) = o;
+    store_cols<V>(cache + (((size_t)p.sb * H + h) * Lcap + p.pos) * kHeadDim + e, o);
   }
 };
 
@@ -509,14 +540,14 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ln_kernel(const bf16* __re
   const bool vec_thread = threadIdx.x < Epi::kVec * QPV;
   f32x4 cvec = {0.f, 0.f, 0.f, 0.f};
   if (vec_thread) cvec = *reinterpret_cast<const f32x4*>(epi.vec(threadIdx.x / QPV) + min(n0 + (int)(threadIdx.x % QPV) * 4, N - 4));
-  typename Epi::Pre pre[ITER];
+  typename Epi::template Pre<8> pre[ITER];
 #pragma unroll
-  for (int it = 0; it < ITER; ++it) pre[it] = epi.fetch(min(m0 + it * RPI + tr, M - 1), min(n, N - 8));
+  for (int it = 0; it < ITER; ++it) epi.template fetch<8>(min(m0 + it * RPI + tr, M - 1), min(n, N - 8), pre[it]);
   GemmAcc<Cfg> acc;
   gemm_mainloop<Cfg>(A, lda, W, ldw, M, N, 0, K / Cfg::GK, m0, n0, smem, acc);
   float* cs = reinterpret_cast<float*>(smem);
   gemm_foreach<Cfg>(acc, 0, 0, [&](int r, int c, float v) { cs[cs_off<Cfg::kBN>(r, c)] = v; });
-  rows.finish(epi.chunks, epi.identity(), rowstat);
+  rows.finish(epi.d_ln(), epi.chunks, epi.identity(), rowstat);
   if (vec_thread) *reinterpret_cast<f32x4*>(colv + threadIdx.x * 4) = cvec;
   __syncthreads();
   float cv[Epi::kVec][8];
@@ -534,7 +565,7 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ln_kernel(const bf16* __re
     const f32x4 a = *reinterpret_cast<const f32x4*>(src), b = *reinterpret_cast<const f32x4*>(src + 4);
     const f32x2 st = *reinterpret_cast<const f32x2*>(rowstat + 2 * r);
     const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    epi.store(m, n, m < M && n < N, v, pre[it], st[0], st[1], cv);
+    epi.template store<8, 64>(m, n, m < M && n < N, v, pre[it], st[0], st[1], cv);
   }
 }
 
@@ -550,10 +581,187 @@ static hipError_t launch_ln_cfg(hipStream_t st, const bf16* A, int lda, const bf
                      A, lda, W, K, M, N, K, MT, NT, epi, m_real);
   return hipGetLastError();
 }
+// ----------------------------------------------------------------------------- K split inside the block
+// With a few hundred rows or fewer, 64 x 64 tiles whose four waves share one ring leave most CUs without a block and
+// make the others walk K alone, one barrier per 64 columns.  Here the waves of a block split K: each takes every
+// NW-th 64-column slab, moves its slab of the whole tile's rows into an LDS ring of its own (whole 128-byte lines,
+// global -> LDS) and multiplies it without ever meeting the other waves, so that a block keeps all of its LDS in
+// flight and no wave waits for another's requests.  The NW partial tiles are summed through LDS in wave order
+// (bit-reproducible); LPR neighbouring lanes finish one row, V columns each, and reduce its LayerNorm statistics.
+template <int BM, int BN, int NW, int STAGES>
+struct KsplitCfg {
+  static constexpr int kBM = BM, kBN = BN, kWaves = NW, kThreads = 64 * NW, kStages = STAGES;
+  static constexpr int kStageElems = (BM + BN) * 64;
+  static constexpr int kIPW = (BM + BN) / 8;                       // requests per wave and stage
+  static constexpr int kRingBytes = NW * STAGES * kStageElems * 2;
+  static constexpr int kSmemBytes = kRingBytes + BM * 8;           // + rowstat
+  static constexpr int kV = BN / 16, kLPR = 16;                    // columns per lane, lanes per row in the epilogue
+  static constexpr int kRowsPerPass = kThreads / kLPR < BM ? kThreads / kLPR : BM;
+  static constexpr int kIter = BM / kRowsPerPass;
+  static constexpr int kTPR = kThreads / BM >= 16 ? 16 : kThreads / BM >= 8 ? 8 : kThreads / BM >= 4 ? 4 : 2;   // statistics: threads per row
+  static_assert(BM * BN * 4 <= STAGES * kStageElems * 2, "a wave's partial tile fits its ring");
+  static_assert((BN == 32 || BN == 64) && BM % 16 == 0 && BM % kRowsPerPass == 0, "tile shape");
+  static_assert(kSmemBytes <= 160 * 1024, "LDS of a CU");
+  // partial tile in LDS: [BM][BN] floats, 16-byte chunk c of row r at chunk c ^ (r mod chunks)
+  __device__ __forceinline__ static int red_off(int r, int c) { return r * BN + ((((c >> 2) ^ r) & (BN / 4 - 1)) << 2) + (c & 3); }
+};
+
+template <class Cfg, class Epi>
+__global__ __launch_bounds__(Cfg::kThreads) void gemm_ksplit_kernel(const bf16* __restrict__ A, int lda,
+                                                                    const bf16* __restrict__ W, int ldw, int M, int N,
+                                                                    int K, int MT, int NT, Epi epi,
+                                                                    const int* __restrict__ m_real) {
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+  constexpr int BM = Cfg::kBM, BN = Cfg::kBN, NW = Cfg::kWaves, S = Cfg::kStages, IPW = Cfg::kIPW;
+  constexpr int FA = BM / 16, FB = BN / 16, V = Cfg::kV, LPR = Cfg::kLPR, ITER = Cfg::kIter, RPP = Cfg::kRowsPerPass;
+  float* rowstat = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Cfg::kRingBytes);   // [BM][2]
+  int mt, nt;
+  if (!xcd_tile(MT, NT, mt, nt)) return;
+  const int m0 = mt * BM, n0 = nt * BN;
+  const int mr = m_real ? *m_real : M;   // arrives with the first operands (rows below M may all be read)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lq = lane & 15, g = lane >> 4;
+  const int slabs = K >> 6, cnt = (slabs - wave + NW - 1) / NW;   // this wave's slabs: wave, wave + NW, ...
+  // request i of a stage moves tile rows 8i .. 8i + 7 (A rows, then W rows), lane -> row 8i + lane/8; the swizzled
+  // chunk depends on i by its parity alone
+  unsigned voff[IPW];
+#pragma unroll
+  for (int i = 0; i < IPW; ++i) {
+    const int row = i * 8 + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
+    voff[i] = i * 8 < BM ? (unsigned)min(row, M - 1 - m0) * (unsigned)(lda * 2) + chunk * 16
+                         : (unsigned)min(row - BM, N - 1 - n0) * (unsigned)(ldw * 2) + chunk * 16;
+  }
+  const bf16 *abase = A + (size_t)m0 * lda + wave * 64, *wbase = W + (size_t)n0 * ldw + wave * 64;
+  const bf16* ring = smem + wave * (S * Cfg::kStageElems);
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)SD_LDS_PTR(const_cast<bf16*>(ring)));
+  auto request = [&](int t, int slot) {
+    const bf16 *as = abase + t * (NW * 64), *ws = wbase + t * (NW * 64);
+    const unsigned l = lds0 + slot * (Cfg::kStageElems * 2);
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) dma16(i * 8 < BM ? as : ws, voff[i], l + i * 1024);
+  };
+#pragma unroll
+  for (int t = 0; t < S; ++t)
+    if (t < cnt) request(t, t);
+  // what the epilogue reads travels behind the first operands
+  constexpr int TPR = Cfg::kTPR, NL = 32 / TPR;   // 16-byte loads of two chunk pairs per thread (d <= 2048)
+  const int sr = min(tid / TPR, BM - 1), sj = tid % TPR;
+  f32x4 pr[NL];
+  {
+    const f32x4* src = reinterpret_cast<const f32x4*>(epi.ln_in + (size_t)min(m0 + sr, M - 1) * ln_pitch(epi.chunks));
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      pr[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (2 * i * TPR < epi.chunks) pr[i] = src[min(sj + i * TPR, ln_pitch(epi.chunks) / 2 - 1)];
+    }
+  }
+  const int r0 = (tid / LPR) % RPP, j0 = tid % LPR, n = n0 + j0 * V;
+  const int nc = min(n, N - V);
+  typename Epi::template Pre<V> pre[ITER];
+#pragma unroll
+  for (int it = 0; it < ITER; ++it) epi.template fetch<V>(min(m0 + it * RPP + r0, M - 1), nc, pre[it]);
+  float cv[Epi::kVec][V];
+#pragma unroll
+  for (int i = 0; i < Epi::kVec; ++i) load_cols<V>(epi.vec(i) + nc, cv[i]);
+  __builtin_amdgcn_sched_barrier(0);
+  f32x4 acc[FA][FB];
+#pragma unroll
+  for (int i = 0; i < FA; ++i)
+#pragma unroll
+    for (int j = 0; j < FB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int slot = 0;
+  for (int t = 0; t < cnt; ++t) {
+    wait_vm_stages<IPW, S - 1>(min(cnt - 1 - t, S - 1));   // (the younger epilogue requests only make this stricter)
+    asm volatile("" ::: "memory");
+    const bf16* st = ring + slot * Cfg::kStageElems;
+    bf16x8 fa[2][FA], fb[2][FB];
+#pragma unroll
+    for (int ss = 0; ss < 2; ++ss) {
+#pragma unroll
+      for (int j = 0; j < FB; ++j) fb[ss][j] = *reinterpret_cast<const bf16x8*>(st + lds_off<64>(BM + j * 16 + lq, ss * 4 + g));
+#pragma unroll
+      for (int i = 0; i < FA; ++i) fa[ss][i] = *reinterpret_cast<const bf16x8*>(st + lds_off<64>(i * 16 + lq, ss * 4 + g));
+    }
+    auto mma = [&](int ss) {
+#pragma unroll
+      for (int i = 0; i < FA; ++i)
+#pragma unroll
+        for (int j = 0; j < FB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ss][j], fa[ss][i], acc[i][j], 0, 0, 0);
+    };
+    mma(0);
+    if (t + S < cnt) {   // once the slot's rows are in registers it may be filled again
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      request(t + S, slot);
+    }
+    mma(1);
+    slot = slot + 1 == S ? 0 : slot + 1;
+  }
+#pragma unroll
+  for (int i = 0; i < FA; ++i)
+#pragma unroll
+    for (int j = 0; j < FB; j += 2) mfma_settle(acc[i][j], acc[i][j + 1]);
+  if (m0 >= mr) return;                  // (same for the whole block)
+  M = min(M, mr);
+  // D[n][m]: this lane holds row i*16 + lq, columns j*16 + 4g .. + 3; the wave's own ring takes its partial tile
+  float* red = reinterpret_cast<float*>(smem);
+  constexpr int kWaveF = S * Cfg::kStageElems / 2;
+#pragma unroll
+  for (int i = 0; i < FA; ++i)
+#pragma unroll
+    for (int j = 0; j < FB; ++j)
+      *reinterpret_cast<f32x4*>(red + wave * kWaveF + Cfg::red_off(i * 16 + lq, j * 16 + 4 * g)) = acc[i][j];
+  ln_row_stats<TPR, NL>(pr, sj, epi.d_ln(), epi.chunks, epi.identity(), tid < BM * TPR, rowstat + 2 * sr);
+  lds_barrier();
+  if (RPP * LPR < Cfg::kThreads && tid >= RPP * LPR) return;
+#pragma unroll
+  for (int it = 0; it < ITER; ++it) {
+    const int r = it * RPP + r0, m = m0 + r;
+    float v[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      float t[V];
+      load_cols<V>(red + w * kWaveF + Cfg::red_off(r, j0 * V), t);
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[e] += t[e];
+    }
+    const f32x2 rs = *reinterpret_cast<const f32x2*>(rowstat + 2 * r);
+    epi.template store<V, BN>(m, n, m < M && n < N, v, pre[it], rs[0], rs[1], cv);
+  }
+}
+
+template <class Cfg, class Epi>
+static hipError_t launch_ksplit(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K,
+                                const Epi& epi, const int* m_real) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ksplit_kernel<Cfg, Epi>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kSmemBytes);
+  if (attr != hipSuccess) return attr;
+  const int MT = (M + Cfg::kBM - 1) / Cfg::kBM, NT = (N + Cfg::kBN - 1) / Cfg::kBN;
+  SD_LAUNCH_TIMED((gemm_ksplit_kernel<Cfg, Epi>), dim3(xcd_grid(MT, NT)), dim3(Cfg::kThreads), Cfg::kSmemBytes, st, A, lda,
+                  W, K, M, N, K, MT, NT, epi, m_real);
+  return hipGetLastError();
+}
+
+static bool one_round(int M, int N, int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) <= 256; }
+
 template <class Epi>
 static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K,
                             const Epi& epi, const int* m_real) {
   if (M <= 0 || N <= 0) return hipSuccess;
+  // K split inside the block wherever its tiles give every CU at most one block (a second round costs more than it
+  // saves): the smallest tile that does.  Chained launches, 64 x 64 ring -> K split, us: N = K = 512, M = 77: 5.6 -> 3.3;
+  // N = 1024, M = 128: K = 1024 7.7 -> 3.9, K = 4096 19.0 -> 7.2; M = 352: K = 1024 8.0 -> 5.4, K = 4096 19.6 -> 11.0;
+  // N = 4096, K = 1024, M = 128: 7.4 -> 5.6.
+  if (one_round(M, N, 16, 32)) return launch_ksplit<KsplitCfg<16, 32, 8, 3>>(st, A, lda, W, M, N, K, epi, m_real);
+  if (one_round(M, N, 32, 32)) return launch_ksplit<KsplitCfg<32, 32, 8, 2>>(st, A, lda, W, M, N, K, epi, m_real);
+  if (one_round(M, N, 32, 64)) return launch_ksplit<KsplitCfg<32, 64, 8, 1>>(st, A, lda, W, M, N, K, epi, m_real);
+  if (one_round(M, N, 48, 64)) return launch_ksplit<KsplitCfg<48, 64, 4, 2>>(st, A, lda, W, M, N, K, epi, m_real);
+  // a long K pays for a larger tile (FFN2 of the big model at 1408 rows: 28.4 -> 23.7 us); at K <= 2048 the ring is level
+  // or better, and so it is where M is only a bound on the rows in use
+  if constexpr (Epi::kVec == 3) {
+    if (K >= 4096 && !m_real && one_round(M, N, 96, 64)) return launch_ksplit<KsplitCfg<96, 64, 3, 2>>(st, A, lda, W, M, N, K, epi, m_real);
+  }
   const long wide_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
   // the widest outputs (QKV and FFN1 of the big model) run on 256x128 tiles, eight waves, three-deep
   // ring: 9-15 % faster than 128x128 on weights streamed from HBM, a few % inside the decoder pass
@@ -564,24 +772,26 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const bf16* 
   return launch_ln_cfg<CfgSmall>(st, A, lda, W, M, N, K, epi, m_real);
 }
 
+int ln_sum_chunks(int M, int d) { return one_round(M, d, 32, 32) ? d / 32 : d / 64; }
 hipError_t gemm_ln_sum(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int d, int K,
-                       const float* vecs, const float* ln_in, bool has_prev, float* x, bf16* xg, float* ln_out,
-                       const int* m_real) {
+                       const float* vecs, LnPairs ln_in, float* x, bf16* xg, float* ln_out, const int* m_real) {
   return launch_ln(st, A, lda, W, M, d, K,
-                   EpiLnSum{vecs, reinterpret_cast<const f32x2*>(ln_in), reinterpret_cast<f32x2*>(ln_out), x, xg, d,
-                            d / 64, has_prev ? 1 : 0}, m_real);
+                   EpiLnSum{vecs, reinterpret_cast<const f32x2*>(ln_in.p), reinterpret_cast<f32x2*>(ln_out), x, xg, d,
+                            ln_in.chunks > 0 ? ln_in.chunks : d / 64, ln_in.chunks > 0}, m_real);
 }
 hipError_t gemm_ln_bf16(hipStream_t st, const bf16* A, const bf16* W, int M, int N, int d, const LnFold& f,
-                        const float* ln_in, bf16* out, int ldo, bool relu, const int* m_real) {
+                        LnPairs ln_in, bf16* out, int ldo, bool relu, const int* m_real) {
   return launch_ln(st, A, d, W, M, N, d,
-                   EpiLnBf16{f.cs, f.bf, reinterpret_cast<const f32x2*>(ln_in), out, ldo, d / 64, relu ? 1 : 0}, m_real);
+                   EpiLnBf16{f.cs, f.bf, reinterpret_cast<const f32x2*>(ln_in.p), out, ldo, d,
+                             ln_in.chunks > 0 ? ln_in.chunks : d / 64, relu ? 1 : 0, ln_in.chunks > 0}, m_real);
 }
 hipError_t gemm_ln_qkv_append(hipStream_t st, const bf16* A, const bf16* W, int M, int d, const LnFold& f,
-                              const float* ln_in, bf16* q_out, bf16* kc, bf16* vc, const int* row_b,
+                              LnPairs ln_in, bf16* q_out, bf16* kc, bf16* vc, const int* row_b,
                               const int* row_pos, int H, int Lcap, const int* m_real) {
   return launch_ln(st, A, d, W, M, 3 * d, d,
-                   EpiLnQkvAppend{f.cs, f.bf, reinterpret_cast<const f32x2*>(ln_in), d / 64, q_out, kc, vc, row_b,
-                                  row_pos, d, H, Lcap}, m_real);
+                   EpiLnQkvAppend{f.cs, f.bf, reinterpret_cast<const f32x2*>(ln_in.p),
+                                  ln_in.chunks > 0 ? ln_in.chunks : d / 64, ln_in.chunks > 0, q_out,
+                                  kc, vc, row_b, row_pos, d, H, Lcap}, m_real);
 }
 
 // cs[n] = sum_k g[k] W[n][k],  bf[n] = b[n] + sum_k beta[k] W[n][k]; one wave per column n
@@ -591,6 +801,10 @@ __global__ __launch_bounds__(256) void ln_fold_kernel(const bf16* __restrict__ W
   const int n = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (n >= N) return;
   const bf16* w = W + (size_t)n * K;
+  if (!g) {   // no LayerNorm in front: the plain bias
+    if (lane == 0) { cs[n] = 0.f; bf[n] = (float)b[n]; }
+    return;
+  }
   float s = 0.f, t = 0.f;
   for (int k = lane; k < K; k += 64) {
     const float wk = (float)w[k];

@@ -67,6 +67,12 @@ __device__ __forceinline__ void dma16(const bf16* g, bf16* lds_dst) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(l), "v"(g));
 }
 
+// The same with the address split into a wave-uniform base (scalar registers) and a byte offset per lane: moving on to
+// the next stage is then scalar arithmetic, and a request's offset costs one multiply-add.
+__device__ __forceinline__ void dma16(const bf16* base, unsigned voff, unsigned lds_dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_dst), "v"(voff), "s"(base));
+}
+
 // wait until at most allow * IPW of this wave's requests are outstanding (allow in [0, MAXA])
 template <int IPW, int MAXA>
 __device__ __forceinline__ void wait_vm_stages(int allow) {

@@ -55,13 +55,14 @@ hipError_t gemm_enc_qkv(hipStream_t st, const bf16* A, const bf16* W, int M, int
 
 // ---- LayerNorm folded into the GEMM around it (post-LN blocks) ----
 // y = residual sum of a sub-layer, LN(y) = (y - mean) * rstd * g + beta.  The GEMM that forms y
-// also writes bf16(y * g) and, per row and 64-column chunk, the pair {sum, squared deviations
-// from the chunk mean} ("chunk pairs", fp32 [M][pitch][2], pitch = d/64 rounded up to even); the GEMMs that consume LN(y) multiply
+// also writes bf16(y * g) and, per row and chunk of columns, the pair {sum, squared deviations from the
+// chunk mean} ("chunk pairs", fp32 [M][pitch][2], pitch = chunks rounded up to even); the GEMMs that consume LN(y) multiply
 // bf16(y * g) and finish with rstd * (acc - mean * cs) + bf.
 struct LnFold {          // per consuming weight matrix W [N,d] with bias b, for one LayerNorm (g, beta)
   const float* cs;       // [N]  sum_k g[k] W[n][k]
   const float* bf;       // [N]  b[n] + sum_k beta[k] W[n][k]
 };
+// (g, beta null: no LayerNorm in front of W, cs = 0 and bf = b)
 hipError_t ln_fold(hipStream_t st, const bf16* W, const bf16* g, const bf16* beta, const bf16* b, int N, int K,
                    const LnFold& out);
 // The column vectors of one producing GEMM, fp32 [3][d] in one piece: gain of the LayerNorm
@@ -69,21 +70,28 @@ hipError_t ln_fold(hipStream_t st, const bf16* W, const bf16* g, const bf16* bet
 // gain of the LayerNorm that follows.
 hipError_t ln_sum_vecs(hipStream_t st, const bf16* bias, const bf16* g_prev, const bf16* b_prev, const bf16* g_next,
                        int d, float* out);
-// x [M,d] += A W^T + bias, where the residual already in x is LN_prev(x) if has_prev (chunk pairs of
-// x in ln_in; without has_prev ln_in is still read, and ignored: pass any chunk-pair buffer);
-// also xg = bf16(x_new * g_next) and the chunk pairs of x_new -> ln_out (a buffer other than ln_in).
+// Chunk pairs of a residual sum: chunks per row = d / 64, or d / 32 where the kernel that formed them has tiles of 32
+// columns (ln_sum_chunks); chunks = 0: no LayerNorm is pending (p is still read, and ignored: any chunk-pair buffer).
+struct LnPairs {
+  const float* p;
+  int chunks;
+};
+int ln_sum_chunks(int M, int d);   // of what gemm_ln_sum writes for M rows
+// x [M,d] += A W^T + bias, where the residual already in x is LN_prev(x) if ln_in says so; also
+// xg = bf16(x_new * g_next) and the chunk pairs of x_new -> ln_out (a buffer other than ln_in.p).
 // m_real (all three; device, nullable): number of leading rows that hold data; row tiles at or
 // beyond it are skipped and rows beyond it are neither computed on nor stored (M stays the
 // upper bound the grid is sized for).
 hipError_t gemm_ln_sum(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int d, int K,
-                       const float* vecs, const float* ln_in, bool has_prev, float* x, bf16* xg, float* ln_out,
+                       const float* vecs, LnPairs ln_in, float* x, bf16* xg, float* ln_out,
                        const int* m_real = nullptr);
-// out bf16 [M,ldo] = act(LN(y) W^T + b) from A = bf16(y * g) [M,d] and the chunk pairs of y
+// out bf16 [M,ldo] = act(LN(y) W^T + b) from A = bf16(y * g) [M,d] and the chunk pairs of y; without a pending
+// LayerNorm act(A W^T + b) with f = {0, b}
 hipError_t gemm_ln_bf16(hipStream_t st, const bf16* A, const bf16* W, int M, int N, int d, const LnFold& f,
-                        const float* ln_in, bf16* out, int ldo, bool relu, const int* m_real = nullptr);
-// gemm_qkv_append on LN(y)
+                        LnPairs ln_in, bf16* out, int ldo, bool relu, const int* m_real = nullptr);
+// gemm_qkv_append on the same
 hipError_t gemm_ln_qkv_append(hipStream_t st, const bf16* A, const bf16* W, int M, int d, const LnFold& f,
-                              const float* ln_in, bf16* q_out, bf16* kc, bf16* vc, const int* row_b,
+                              LnPairs ln_in, bf16* q_out, bf16* kc, bf16* vc, const int* row_b,
                               const int* row_pos, int H, int Lcap, const int* m_real = nullptr);
 
 // Vocabulary projection fused with per-row statistics.  zd_row [M] receives the logit of the

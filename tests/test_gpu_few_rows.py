@@ -1,0 +1,38 @@
+"""Passes of 33 to some 1500 rows: every tile shape of the projections whose blocks split K, at remainders of the row
+tiles, K extents that do not divide among the waves and odd numbers of statistics chunks, against the oracle and against
+the path with a separate LayerNorm."""
+import numpy as np
+import pytest
+
+import cases
+import gpu_harness as gh
+from paper_2203_16487_amd import binding as sd
+from paper_2203_16487_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+# d, heads, F, B, k: rows B*(k+1); the widest projection decides which tiles its rows get
+@pytest.mark.parametrize("d,H,F,B,k", [
+    (192, 3, 320, 3, 10),      # 33 rows, 3 and 5 slabs of K for 8 waves, 3 (or 6) chunks
+    (128, 2, 512, 23, 10),     # 253 rows: 16 x 32
+    (128, 2, 512, 27, 10),     # 297 rows: FFN1 on 32 x 32
+    (128, 2, 512, 55, 10),     # 605 rows: FFN1 on 32 x 64
+    (320, 5, 576, 97, 10),     # 1067 rows: QKV and FFN1 on 48 x 64, sums on 32 x 32 / 32 x 64 (5 chunks)
+    (128, 2, 1024, 129, 10),   # 1419 rows: FFN1 beyond one round of blocks
+])
+def test_rows_against_oracle(d, H, F, B, k):
+    desc = synth.ModelDesc(0, 2, d, H, F, 1000, 16, 64).resolved()
+    case = cases.make_verify_case(desc, seed=d + B, B=B, S=9, k=k, beta=3, tau=1.0, len_lo=0, len_hi=13, drafts="random",
+                                  ragged_src=True, std=0.05)
+    cases.run_oracle(case)
+    out = {}
+    for fold in (1, 0):
+        ses = gh.open_verifier(case, options={sd.SPECDEC_OPT_LN_FOLD: fold}, fill=0xFF)
+        out[fold] = gh.gpu_verify(ses, case)
+        ses.close()
+        err = float(np.abs(out[fold]["logits"] - case.logits).max())
+        exact, excused, bad = cases.compare_decisions(case, out[fold]["accept"], out[fold]["next"])
+        print(f"rows {B * (k + 1)} fold {fold}: err {err:.2e} exact {exact} excused {excused}")
+        assert err <= max(2e-2, 0.04 * float(case.logits.std())), err
+        assert not bad, bad
