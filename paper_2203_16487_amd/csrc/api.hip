@@ -50,7 +50,7 @@ struct Model {
   float* pe = nullptr;       // [n_pos][d]
   bf16 *kc = nullptr, *vc = nullptr;   // [Ld][Bmax][H][Lcap][64]
   bf16 *xk = nullptr, *xv = nullptr;   // [Ld][Bmax][H][Scap][64]
-  float* x = nullptr;        // [Rmax][d] residual stream
+  float* x = nullptr;        // [Rpass][d] residual stream
   float* x2 = nullptr;       // [32][d] second residual buffer of the fused small-batch path
   float* skp = nullptr;      // [2][kSk2MaxParts][32][d] partial results of the sliced small-batch kernels
   unsigned char* w8 = nullptr;   // E4M3 codes of every decoder layer's six matrices, then the embedding (or null)
@@ -67,13 +67,13 @@ struct Model {
   unsigned* rs_bar = nullptr;         // barrier counters + error flag of the resident kernel
   int rs_parity = 0;
   int rs_seq = 0;
-  bf16* xb = nullptr;        // [Rmax][d]
+  bf16* xb = nullptr;        // [Rpass][d]
   float* lnp[2] = {nullptr, nullptr};   // [rows][d/32 at most][2] chunk pairs of the two latest residual sums
   float* fold = nullptr;     // per decoder layer: cs and bf vectors of wqkv, cwq, w1 (LayerNorm folded)
   std::vector<LnFolds> folds;
-  bf16* q = nullptr;         // [Rmax][d]
-  bf16* att = nullptr;       // [Rmax][d]
-  bf16* hid = nullptr;       // [Rmax][F]
+  bf16* q = nullptr;         // [Rpass][d]
+  bf16* att = nullptr;       // [Rpass][d]
+  bf16* hid = nullptr;       // [Rpass][F]
   float* part = nullptr;     // [Rmax][n_tiles][kPartF]
   float* row_stats = nullptr;  // [Rmax][kRowStats]
   float* zd = nullptr;       // [Rmax] logit of the draft each row scores
@@ -93,6 +93,7 @@ struct Model {
 struct specdec_ctx {
   specdec_limits lim{};
   int Lcap = 0, Scap = 0, Tmax = 0, n_pos = 0;
+  long pass_rows = 0;   // rows the activation buffers of a decoder pass hold
   bool state_bound = false;
   sd::SeqState st{};
   Model m[2];
@@ -179,6 +180,7 @@ bool desc_ok(const specdec_model_desc* d) {
          d->eos_id >= 0 && d->eos_id < d->vocab && d->pad_id >= 0 && d->pad_id < d->vocab &&
          d->mask_id >= 0 && d->mask_id < d->vocab;
 }
+constexpr long kPrefillRows = 8192;
 constexpr int kEncT = 12, kDecT = 20;
 int n_weights(const specdec_model_desc* d) { return 1 + kEncT * d->enc_layers + kDecT * d->dec_layers; }
 
@@ -242,7 +244,7 @@ size_t carve_state(const specdec_ctx* c, void* base, sd::SeqState* out) {
 size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base, Model* m) {
   Carver cv(base);
   const size_t Bm = c->lim.max_batch, D = d->d_model, F = d->d_ffn, H = d->n_heads;
-  const size_t Rmax = Bm * c->Tmax;
+  const size_t Rmax = Bm * c->Tmax, Rpass = (size_t)c->pass_rows;   // rows of a verify / draft pass, of any pass
   const size_t n_tiles = (d->vocab + 63) / 64;   // the small-batch path uses 64-column tiles
   Model t;
   t.kv_layer = Bm * H * c->Lcap * 64;
@@ -252,7 +254,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   t.vc = cv.take<bf16>(t.kv_layer * d->dec_layers);
   t.xk = cv.take<bf16>(t.xkv_layer * d->dec_layers);
   t.xv = cv.take<bf16>(t.xkv_layer * d->dec_layers);
-  t.x = cv.take<float>(Rmax * D);
+  t.x = cv.take<float>(Rpass * D);
   t.x2 = cv.take<float>(32 * D);
   t.skp = cv.take<float>((size_t)2 * sd::kSk2MaxParts * 32 * D);
   t.hx = cv.take<float>(Bm * (size_t)c->lim.k_max * D);
@@ -266,21 +268,21 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     t.w8 = cv.take<unsigned char>((size_t)d->dec_layers * (6 * D * D + 2 * D * F) + (size_t)d->vocab * D);
     t.w8s = cv.take<float>((size_t)d->dec_layers * (7 * D + F) + (size_t)d->vocab);
   }
-  t.xb = cv.take<bf16>(Rmax * D);
-  t.lnp[0] = cv.take<float>(Rmax * (D / 32) * 2);
-  t.lnp[1] = cv.take<float>(Rmax * (D / 32) * 2);
+  t.xb = cv.take<bf16>(Rpass * D);
+  t.lnp[0] = cv.take<float>(Rpass * (D / 32) * 2);
+  t.lnp[1] = cv.take<float>(Rpass * (D / 32) * 2);
   t.fold = cv.take<float>((size_t)d->dec_layers * (2 * (3 * D + D + F) + 9 * D));
-  t.q = cv.take<bf16>((Rmax > 32 ? Rmax : 32) * D);
-  t.att = cv.take<bf16>(Rmax * D);
-  t.hid = cv.take<bf16>((Rmax > 32 ? Rmax : 32) * F);
+  t.q = cv.take<bf16>((Rpass > 32 ? Rpass : 32) * D);
+  t.att = cv.take<bf16>(Rpass * D);
+  t.hid = cv.take<bf16>((Rpass > 32 ? Rpass : 32) * F);
   t.part = cv.take<float>(Rmax * n_tiles * sd::kPartF);
   t.row_stats = cv.take<float>(Rmax * sd::kRowStats);
   t.zd = cv.take<float>(Rmax);
-  t.rm.row_b = cv.take<int>(Rmax);
-  t.rm.row_pos = cv.take<int>(Rmax);
-  t.rm.row_tok = cv.take<int>(Rmax);
-  t.rm.row_lim = cv.take<int>(Rmax);
-  t.rm.row_draft = cv.take<int>(Rmax);
+  t.rm.row_b = cv.take<int>(Rpass);
+  t.rm.row_pos = cv.take<int>(Rpass);
+  t.rm.row_tok = cv.take<int>(Rpass);
+  t.rm.row_lim = cv.take<int>(Rpass);
+  t.rm.row_draft = cv.take<int>(Rpass);
   t.rm.seq_rows = cv.take<int>(Bm);
   t.rm.row_start = cv.take<int>(Bm + 1);
   t.slots = cv.take<bf16>(Bm * (size_t)c->lim.k_max * D);
@@ -329,8 +331,9 @@ inline void cross_fp8(const Model& m, int l, sd::AttnArgs& a) {
 // rows per sequence are needed, and they go to m.slots [B*slot_k][d] (bf16) instead.
 // packed: the rows of the pass were assembled without padding (m.rm.row_start); R = B*T is then
 // only the bound the grids are sized for, and tiles beyond the rows in use return at once.
+// kv_only (prefill): the pass is wanted for the keys / values it appends; it ends where the last layer's are stored.
 int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool embedded = false, int slot_k = 0,
-                   bool packed = false) {
+                   bool packed = false, bool kv_only = false) {
   const int R = B * T, D = m.d.d_model, F = m.d.d_ffn, H = m.d.n_heads;
   const int Lcap = c->Lcap, Scap = c->Scap;
   const int* m_real = packed ? m.rm.row_start + B : nullptr;
@@ -359,6 +362,7 @@ int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool 
       LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_qkv_append(st, m.xb, L.wqkv, R, D, D, L.bqkv, m.q, kc, vc, m.rm.row_b,
                                     m.rm.row_pos, H, Lcap, m_real));
     }
+    if (kv_only && l + 1 == m.d.dec_layers) return SPECDEC_OK;
     sd::AttnArgs a{};
     a.q = m.q; a.q_b = (long)T * D; a.q_row = D;
     a.k = kc; a.k_b = (long)H * Lcap * 64; a.k_h = (long)Lcap * 64; a.k_row = 64;
@@ -564,6 +568,11 @@ int specdec_create(specdec_ctx** out, const specdec_limits* lim) {
   c->Lcap = (lim->max_tgt + lim->k_max + 1 + 31) & ~31;   // rows of the KV arenas (32-key chunks)
   c->Scap = (lim->max_src + 31) & ~31;
   c->n_pos = c->Lcap > c->Scap ? c->Lcap : c->Scap;
+  // A prefill pass takes as many rows as make its products large (8192 rows: 150 MB of activations for the big model),
+  // never more than the streams can hold and never fewer than a verify / draft pass needs.
+  const long pre = lim->max_batch * (long)(lim->max_tgt + 1), most = pre < kPrefillRows ? pre : kPrefillRows;
+  const long least = (long)lim->max_batch * c->Tmax;
+  c->pass_rows = most > least ? most : least;
   *out = c;
   return SPECDEC_OK;
 }
@@ -872,11 +881,16 @@ int specdec_prefill(specdec_ctx* c, specdec_role role, void* stream) {
   if (rc) return rc;
   Model& m = c->m[role];
   hipStream_t st = S(stream);
-  const int T = c->Tmax;
+  // As few passes as the activation buffers allow, all of the same size: a pass of a few rows per sequence is a chain of
+  // small launches that reads every weight again (32 sequences of up to 224 tokens, big model: 11 passes of 21 positions
+  // 6.9 ms, TIMEms in one).  Rows are packed: short streams bring no padding.
+  const bool packed = !c->no_ln_fold;
+  const int most = (int)(c->pass_rows / c->B), passes = (c->uncached_ub[role] + most - 1) / most;
+  const int T = passes > 0 ? (c->uncached_ub[role] + passes - 1) / passes : 0;
   while (c->uncached_ub[role] > 0) {
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_stream(st, c->st, m.rm, role, c->B, T, 0, m.d.mask_id, m.d.pad_id, m.d.vocab,
-                                        m.new_rows, m.embed, m.pe, m.x, m.xb, m.d.d_model, false));
-    rc = decoder_layers(c, m, c->B, T, st, true);
+                                        m.new_rows, m.embed, m.pe, m.x, m.xb, m.d.d_model, packed));
+    rc = decoder_layers(c, m, c->B, T, st, true, 0, packed, true);
     if (rc) return rc;
     HIPCHK(c, sd::advance_cached(st, c->st, role, m.new_rows, c->B));
     c->uncached_ub[role] -= T;
