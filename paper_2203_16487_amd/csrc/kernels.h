@@ -155,6 +155,8 @@ struct AttnArgs {
   // key's row) / 64 of k_scale (keys) / v_scale (values): [b][h][cap] with the arena strides above
   const float* k_scale = nullptr;
   const float* v_scale = nullptr;
+  // [B] first key / value row of sequence b (more than 32 queries, rows only; null: k_b / v_b): rows packed like the queries
+  const int* kv_off = nullptr;
 };
 hipError_t attention(hipStream_t st, const AttnArgs& a);
 
