@@ -33,6 +33,11 @@ struct LnFolds {
   const float *vo, *vco, *v2;   // column vectors of the three residual sums (wo, cwo, w2), [3][d] each
 };
 
+struct EncFolds {
+  sd::LnFold qkv, w1;       // ln2 of the layer below -> wqkv (layer 0: none), ln1 -> w1
+  const float *vo, *v2;     // column vectors of the two residual sums (wo, w2)
+};
+
 // FP8 copies of the matrices the small-batch kernels stream (codes + per-row scales)
 struct Fp8Layer {
   sd::SkWeight wqkv, wo, cwq, cwo, w1, w2;
@@ -71,6 +76,8 @@ struct Model {
   float* lnp[2] = {nullptr, nullptr};   // [rows][d/32 at most][2] chunk pairs of the two latest residual sums
   float* fold = nullptr;     // per decoder layer: cs and bf vectors of wqkv, cwq, w1 (LayerNorm folded)
   std::vector<LnFolds> folds;
+  float* efold = nullptr;    // per encoder layer: those of wqkv, w1
+  std::vector<EncFolds> efolds;
   bf16* q = nullptr;         // [Rpass][d]
   bf16* att = nullptr;       // [Rpass][d]
   bf16* hid = nullptr;       // [Rpass][F]
@@ -82,7 +89,8 @@ struct Model {
   // encoder activations, rows = Bmax * Scap
   float* ex = nullptr;
   bf16 *exb = nullptr, *eqkv = nullptr, *eatt = nullptr, *ehid = nullptr;
-  int *etok = nullptr, *epos = nullptr;
+  float* elnp[2] = {nullptr, nullptr};   // chunk pairs of the encoder's two latest residual sums
+  int* epos = nullptr;
   int *erow_b = nullptr, *erow_start = nullptr, *en_rows = nullptr;   // packed encoder rows: owner, first row per sequence, count
   sd::RowMap rm{};
   size_t kv_layer = 0, xkv_layer = 0;  // elements per layer of the arenas
@@ -296,7 +304,9 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     t.eqkv = cv.take<bf16>(Re * 3 * D);
     t.eatt = cv.take<bf16>(Re * D);
     t.ehid = cv.take<bf16>(Re * F);
-    t.etok = cv.take<int>(Re);
+    t.elnp[0] = cv.take<float>(Re * (D / 32) * 2);
+    t.elnp[1] = cv.take<float>(Re * (D / 32) * 2);
+    t.efold = cv.take<float>((size_t)d->enc_layers * (2 * (3 * D + F) + 6 * D));
     t.epos = cv.take<int>(Re);
     t.erow_b = cv.take<int>(Re);
     t.erow_start = cv.take<int>(Bm + 1);
@@ -310,7 +320,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     m->part = t.part; m->row_stats = t.row_stats; m->zd = t.zd; m->rm = t.rm;
     m->slots = t.slots; m->new_rows = t.new_rows; m->rs_layers = t.rs_layers; m->rs_bar = t.rs_bar;
     m->ex = t.ex; m->exb = t.exb; m->eqkv = t.eqkv; m->eatt = t.eatt; m->ehid = t.ehid;
-    m->etok = t.etok; m->epos = t.epos; m->erow_b = t.erow_b; m->erow_start = t.erow_start; m->en_rows = t.en_rows;
+    m->elnp[0] = t.elnp[0]; m->elnp[1] = t.elnp[1]; m->efold = t.efold; m->epos = t.epos; m->erow_b = t.erow_b; m->erow_start = t.erow_start; m->en_rows = t.en_rows;
   }
   return (cv.off + 255) & ~size_t(255);
 }
@@ -528,11 +538,15 @@ int decoder_layers_sliced(specdec_ctx* c, Model& m, int B, int T, hipStream_t st
 // memory: [B][S_max][d] padded, or (packed) the model's own packed encoder rows (erow_b / epos / en_rows)
 int cross_kv_from(specdec_ctx* c, Model& m, const bf16* memory, int B, int S_max, hipStream_t st, bool packed) {
   const int D = m.d.d_model;
-  for (int l = 0; l < m.d.dec_layers; ++l)
-    HIPCHK(c, sd::gemm_cross_kv(st, memory, m.dec[l].cwkv, B * S_max, D, D, m.dec[l].cbkv,
-                                m.xk + m.xkv_layer * l, m.xv + m.xkv_layer * l, S_max, m.d.n_heads,
-                                c->Scap, packed ? m.erow_b : nullptr, packed ? m.epos : nullptr,
-                                packed ? m.en_rows : nullptr));
+  for (int l = 0; l < m.d.dec_layers; l += sd::kCrossLayers) {
+    sd::CrossKvArgs a{};
+    a.layers = m.d.dec_layers - l < sd::kCrossLayers ? m.d.dec_layers - l : sd::kCrossLayers;
+    for (int i = 0; i < a.layers; ++i) { a.w[i] = m.dec[l + i].cwkv; a.b[i] = m.dec[l + i].cbkv; }
+    a.xk = m.xk + m.xkv_layer * l; a.xv = m.xv + m.xkv_layer * l; a.layer_stride = m.xkv_layer;
+    a.Scap = c->Scap;
+    a.rows = sd::SrcRows{packed ? m.erow_b : nullptr, packed ? m.epos : nullptr, S_max};
+    HIPCHK(c, sd::gemm_cross_kv(st, memory, a, B * S_max, D, packed ? m.en_rows : nullptr));
+  }
   if (m.kv8)   // whole arenas: every (layer, sequence of the batch limit, head, key row)
     HIPCHK(c, sd::quantize_cross_kv(st, m.xk, m.xv, (long)(m.xkv_layer / 64) * m.d.dec_layers, m.xk8, m.xv8, m.xks, m.xvs));
   m.has_memory = true;
@@ -695,6 +709,26 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
       HIPCHK(c, sd::ln_fold(S(stream), L.w1, L.ln2g, L.ln2b, L.b1, F, D, o.w1));
     }
   }
+  {
+    const int D = d->d_model, F = d->d_ffn;
+    float* f = m.efold;
+    auto vec2 = [&](int n) { sd::LnFold o{f, f + n}; f += 2 * n; return o; };
+    m.efolds.resize(d->enc_layers);
+    for (int l = 0; l < d->enc_layers; ++l) {
+      const EncLayer& L = m.enc[l];
+      EncFolds& o = m.efolds[l];
+      o.qkv = vec2(3 * D); o.w1 = vec2(F);
+      float* v = f;
+      f += 6 * D;
+      o.vo = v; o.v2 = v + 3 * D;
+      const bf16* g0 = l > 0 ? m.enc[l - 1].ln2g : nullptr;
+      const bf16* b0 = l > 0 ? m.enc[l - 1].ln2b : nullptr;
+      HIPCHK(c, sd::ln_sum_vecs(S(stream), L.bo, g0, b0, L.ln1g, D, v));
+      HIPCHK(c, sd::ln_sum_vecs(S(stream), L.b2, L.ln1g, L.ln1b, L.ln2g, D, v + 3 * D));
+      HIPCHK(c, sd::ln_fold(S(stream), L.wqkv, g0, b0, L.bqkv, 3 * D, D, o.qkv));
+      HIPCHK(c, sd::ln_fold(S(stream), L.w1, L.ln1g, L.ln1b, L.b1, F, D, o.w1));
+    }
+  }
   m.kv8 = c->fp8_kv;
   m.fp8 = c->fp8;
   if (m.fp8) {
@@ -776,34 +810,38 @@ int specdec_set_memory(specdec_ctx* c, specdec_role role, const void* memory, co
 // + src_len[b] - 1; grids are sized for B*S_max rows, row tiles beyond the real count return at once);
 // leaves the memory (bf16, packed) in m.exb.
 static int encoder_pass(specdec_ctx* c, Model& m, const int32_t* src, int B, int S_max, hipStream_t st) {
-  const int R = B * S_max, D = m.d.d_model, F = m.d.d_ffn, H = m.d.n_heads, Scap = c->Scap;
-  const size_t Re = (size_t)c->lim.max_batch * Scap;
-  bf16* eq = m.eqkv;                 // [R][d]
-  bf16* ek = m.eqkv + Re * D;        // [B][H][Scap][64]
-  bf16* ev = m.eqkv + 2 * Re * D;    // [B][H][Scap/8][64][8]
+  const int R = B * S_max, D = m.d.d_model, F = m.d.d_ffn, H = m.d.n_heads;
   const int* nr = m.en_rows;
-  HIPCHK(c, sd::encoder_rows_packed(st, src, c->st.src_len, m.etok, m.epos, m.erow_b, m.erow_start, m.en_rows, B, S_max,
-                                    m.d.vocab));
-  LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::embed_rows(st, m.etok, m.epos, m.embed, m.pe, m.ex, m.exb, R, D));
+  LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::encoder_rows_embed(st, src, c->st.src_len, m.epos, m.erow_b, m.erow_start, m.en_rows, B,
+                                                           S_max, m.d.vocab, m.embed, m.pe, m.ex, m.exb, D));
+  // LayerNorm folded into the projections, as in decoder_layers: m.ex holds un-normalised sums, m.exb them times the gain
+  sd::LnPairs pend{m.elnp[0], 0};
+  int flip = 1;
+  auto sum = [&](const bf16* A, int K, const bf16* W, const float* vecs) {
+    float* out = m.elnp[flip];
+    hipError_t e = sd::gemm_ln_sum(st, A, K, W, R, D, K, vecs, pend, m.ex, m.exb, out, nr);
+    pend = sd::LnPairs{out, sd::ln_sum_chunks(R, D)};
+    flip ^= 1;
+    return e;
+  };
   for (int l = 0; l < m.d.enc_layers; ++l) {
     const EncLayer& L = m.enc[l];
-    LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_enc_qkv(st, m.exb, L.wqkv, R, D, D, L.bqkv, eq, ek, ev, S_max, H, Scap,
-                                                          m.erow_b, m.epos, nr));
+    const EncFolds& f = m.efolds[l];
+    LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_ln_bf16(st, m.exb, L.wqkv, R, 3 * D, D, f.qkv, pend, m.eqkv, 3 * D, false, nr));
     sd::AttnArgs a{};
-    a.q = eq; a.q_b = (long)S_max * D; a.q_row = D;
-    a.k = ek; a.k_b = (long)H * Scap * 64; a.k_h = (long)Scap * 64; a.k_row = 64;
-    a.v = ev; a.v_b = (long)H * Scap * 64; a.v_h = (long)Scap * 64; a.v_row = 64; a.v_blocked = 1;
-    a.o = m.eatt; a.o_b = (long)S_max * D; a.o_row = D;
-    a.q_count = c->st.src_len; a.q_off = m.erow_start; a.lim_row = nullptr; a.lim_seq = c->st.src_len;
-    a.T = S_max; a.H = H; a.B = B;
-    a.key_split = S_max > 256; a.cap = Scap;
+    a.q = m.eqkv; a.q_row = 3 * D;
+    a.k = m.eqkv + D; a.k_h = 64; a.k_row = 3 * D;
+    a.v = m.eqkv + 2 * D; a.v_h = 64; a.v_row = 3 * D; a.v_blocked = 0;
+    a.o = m.eatt; a.o_row = D;
+    a.q_count = c->st.src_len; a.q_off = m.erow_start; a.kv_off = m.erow_start; a.lim_row = nullptr; a.lim_seq = c->st.src_len;
+    a.T = S_max; a.H = H; a.B = B; a.cap = c->Scap;
     LAUNCH(c, SPECDEC_KIND_ATTN, st, sd::attention(st, a));
-    LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sd::gemm_f32(st, m.eatt, D, L.wo, R, D, D, L.bo, m.ex, m.ex, D, nr));
-    LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, L.ln1g, L.ln1b, m.exb, R, D, nr));
-    LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_bf16(st, m.exb, D, L.w1, R, F, D, L.b1, m.ehid, F, true, nr));
-    LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sd::gemm_f32(st, m.ehid, F, L.w2, R, D, F, L.b2, m.ex, m.ex, D, nr));
-    LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, L.ln2g, L.ln2b, m.exb, R, D, nr));
+    LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.eatt, D, L.wo, f.vo));
+    LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_ln_bf16(st, m.exb, L.w1, R, F, D, f.w1, pend, m.ehid, F, true, nr));
+    LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.ehid, F, L.w2, f.v2));
   }
+  const EncLayer& last = m.enc[m.d.enc_layers - 1];
+  LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, last.ln2g, last.ln2b, m.exb, R, D, nr, false));
   m.enc_packed = true;
   return SPECDEC_OK;
 }

@@ -114,21 +114,6 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(AttnArgs a) {
 // maximum moved.
 // 32 x 16 heads, 1024 queries on 1024 keys: 775 -> 186 us (735 TFLOP/s) against the kernel above, whose waves fetch keys
 // and values one by one.
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ s16x4 lds_tr16(const bf16* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)SD_LDS_PTR(p));
-}
-__device__ __forceinline__ float half_max(float v) {   // over lanes l, l ^ 32
-  const unsigned u = __builtin_bit_cast(unsigned, v);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
-}
-__device__ __forceinline__ float half_add(float v) {
-  const unsigned u = __builtin_bit_cast(unsigned, v);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
-}
-
 constexpr int kTileQ = 128, kTileK = 64;
 
 template <bool VBLK>
@@ -281,20 +266,13 @@ __global__ __launch_bounds__(256, 3) void attn_tile_kernel(AttnArgs a, int qgrou
   for (int et = 0; et < 2; ++et)
 #pragma unroll
     for (int q = 0; q < 4; q += 2) {
-      unsigned w[2][2];
+      bf16x4 w[2];
 #pragma unroll
       for (int g = 0; g < 2; ++g)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          bf16x2 t;
-          t[0] = (bf16)(oacc[et][(q + g) * 4 + 2 * i] * inv);
-          t[1] = (bf16)(oacc[et][(q + g) * 4 + 2 * i + 1] * inv);
-          w[g][i] = __builtin_bit_cast(unsigned, t);
-        }
-      const auto x0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
-      const auto x1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
-      const uint4 v = make_uint4(x0[0], x1[0], x0[1], x1[1]);
-      if (qi < nq) *reinterpret_cast<uint4*>(op + et * 32 + 8 * (q + half)) = v;
+        for (int i = 0; i < 4; ++i) w[g][i] = (bf16)(oacc[et][(q + g) * 4 + i] * inv);
+      const bf16x8 v = join_halves(w[0], w[1]);
+      if (qi < nq) *reinterpret_cast<bf16x8*>(op + et * 32 + 8 * (q + half)) = v;
     }
 }
 
@@ -324,7 +302,7 @@ hipError_t attention(hipStream_t st, const AttnArgs& a) {
     if (!a.k_scale || !a.v_scale || !a.v_blocked) return hipErrorInvalidValue;
     return attention_launch<true, true>(st, a);
   }
-  if (a.T > 32) return a.v_blocked ? attention_tile_launch<true>(st, a) : attention_tile_launch<false>(st, a);
+  if (a.T > 32 || a.kv_off) return a.v_blocked ? attention_tile_launch<true>(st, a) : attention_tile_launch<false>(st, a);
   return a.v_blocked ? attention_launch<true, false>(st, a) : attention_launch<false, false>(st, a);
 }
 

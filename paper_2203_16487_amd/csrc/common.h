@@ -70,6 +70,35 @@ __device__ __forceinline__ int wave_max_i(int v) {
              max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
+// Over lanes l and l ^ 32 (one exchange of the two wave halves, no LDS round trip).
+__device__ __forceinline__ float half_max(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+__device__ __forceinline__ float half_add(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+// Lanes l and l + 32 hold the columns 4 (l / 32) .. + 3 of two groups of eight columns (a, b); afterwards the lower lane
+// has all eight of the first group, the upper lane all eight of the second.
+__device__ __forceinline__ bf16x8 join_halves(const bf16x4& a, const bf16x4& b) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  const u32x2 x = __builtin_bit_cast(u32x2, a), y = __builtin_bit_cast(u32x2, b);
+  const auto r0 = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false);
+  const auto r1 = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+  const u32x4 o = {(unsigned)r0[0], (unsigned)r1[0], (unsigned)r0[1], (unsigned)r1[1]};
+  return __builtin_bit_cast(bf16x8, o);
+}
+// Transposing LDS read: the 16 lanes of a group point at four rows of 16 values (lane t: row t / 4, values 4 (t % 4) ..
+// + 3) and lane t receives value t of the four rows.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ s16x4 lds_tr16(const bf16* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)SD_LDS_PTR(p));
+}
+
 // 1 / sqrt(x) for a LayerNorm on a kernel's critical path: the hardware's reciprocal square root
 // (1 ulp) with one Newton step, instead of the correctly rounded square root and division (several
 // dozen instructions).

@@ -22,6 +22,20 @@ __device__ __forceinline__ bool xcd_tile(int MT, int NT, int& mt, int& nt) {
   mt = t - nt * MT;
   return true;
 }
+// The same for many row tiles: groups of 8 row tiles, inside a group n-major, so that what runs together on an XCD shares
+// both a few weight panels and a few row panels (one long n-major run streams all rows past each weight panel: 32768 x 3072
+// x 1024 on 128 x 128 tiles 331 us, grouped 278).
+__device__ __forceinline__ bool xcd_tile_grouped(int MT, int NT, int& mt, int& nt) {
+  constexpr int G = 8;
+  const int nb = MT * NT, id = blockIdx.x;
+  const int per = (nb + 7) >> 3;
+  const int t = (id & 7) * per + (id >> 3);
+  if ((id >> 3) >= per || t >= nb) return false;
+  const int g = t / (G * NT), r = t - g * G * NT, rows = min(G, MT - g * G);
+  nt = r / rows;
+  mt = g * G + r - nt * rows;
+  return true;
+}
 static inline int xcd_grid(int MT, int NT) { return 8 * ((MT * NT + 7) / 8); }
 
 // fp32 staging tile in LDS, [BM][BN]; rows r and r+4 come from the two lane halves of one
@@ -117,81 +131,6 @@ struct EpiQkvAppend {
   }
 };
 
-// Cross-attention keys/values of the encoder memory: row m = b*S + s.
-//   xk [B][H][Scap][64]     xv [B][H][Scap/8][64][8] (blocked like the value cache)
-// Row m of the source side belongs to sequence b at source position s: m = b * S + s for padded
-// rows, or (row_b[m], row_s[m]) for packed rows (row_b < 0: a row no sequence owns).
-struct SrcRows {
-  const int* __restrict__ row_b;   // null: padded rows
-  const int* __restrict__ row_s;
-  int S;
-  struct At { int b, s; };
-  __device__ __forceinline__ At at(int m) const {
-    if (row_b) return At{row_b[m], row_s[m]};
-    const int b = m / S;
-    return At{b, m - b * S};
-  }
-};
-
-struct EpiCrossKv {
-  const bf16* __restrict__ bias;
-  bf16* __restrict__ xk;
-  bf16* __restrict__ xv;
-  int d, H, Scap;
-  SrcRows rows;
-  struct Pre { bf16x8 b; SrcRows::At at; };
-  __device__ __forceinline__ Pre fetch(int m, int n) const {
-    return Pre{*reinterpret_cast<const bf16x8*>(bias + n), rows.at(m)};
-  }
-  __device__ __forceinline__ void store(int m, int n, const float (&v)[8], const Pre& p) const {
-    const bf16x8 o = pack_bias(v, p.b, false);
-    const int part = n / d, c = n - part * d;
-    const int b = p.at.b, s = p.at.s;
-    if (b < 0) return;
-    const int h = c >> 6, e = c & 63;
-    if (part == 0) {
-      *reinterpret_cast<bf16x8*>(xk + (((size_t)b * H + h) * Scap + s) * kHeadDim + e) = o;
-    } else {
-      bf16* dst = xv + ((size_t)b * H + h) * Scap * kHeadDim + vt_off(s, e);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) dst[i * 8] = o[i];
-    }
-  }
-};
-
-// Encoder self-attention projection, N = 3d, row m = b*S + s: queries -> q [M,d]; keys and
-// values of the source go into the same layouts as the cross-attention K/V.
-struct EpiEncQkv {
-  const bf16* __restrict__ bias;
-  bf16* __restrict__ q;
-  bf16* __restrict__ xk;
-  bf16* __restrict__ xv;
-  int d, H, Scap;
-  SrcRows rows;
-  struct Pre { bf16x8 b; SrcRows::At at; };
-  __device__ __forceinline__ Pre fetch(int m, int n) const {
-    return Pre{*reinterpret_cast<const bf16x8*>(bias + n), rows.at(m)};
-  }
-  __device__ __forceinline__ void store(int m, int n, const float (&v)[8], const Pre& p) const {
-    const bf16x8 o = pack_bias(v, p.b, false);
-    const int part = n / d, c = n - part * d;
-    if (part == 0) {
-      *reinterpret_cast<bf16x8*>(q + (size_t)m * d + c) = o;
-      return;
-    }
-    const int b = p.at.b, s = p.at.s;
-    if (b < 0) return;
-    const int h = c >> 6, e = c & 63;
-    if (part == 1) {
-      *reinterpret_cast<bf16x8*>(xk + (((size_t)b * H + h) * Scap + s) * kHeadDim + e) = o;
-    } else {
-      bf16* dst = xv + ((size_t)b * H + h) * Scap * kHeadDim + vt_off(s, e);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) dst[i * 8] = o[i];
-    }
-  }
-};
-
 template <class Cfg, class Epi>
 __global__ __launch_bounds__(Cfg::kThreads) void gemm_kernel(const bf16* __restrict__ A, int lda,
                                                              const bf16* __restrict__ W, int ldw,
@@ -277,18 +216,6 @@ hipError_t gemm_qkv_append(hipStream_t st, const bf16* A, const bf16* W, int M, 
                            const int* row_pos, int H, int Lcap, const int* m_real) {
   return launch(st, A, K, W, M, 3 * d, K, EpiQkvAppend{bias, q_out, kc, vc, row_b, row_pos, d, H, Lcap}, m_real);
 }
-hipError_t gemm_cross_kv(hipStream_t st, const bf16* A, const bf16* W, int M, int d, int K,
-                         const bf16* bias, bf16* xk, bf16* xv, int S, int H, int Scap, const int* row_b,
-                         const int* row_s, const int* m_real) {
-  return launch(st, A, K, W, M, 2 * d, K, EpiCrossKv{bias, xk, xv, d, H, Scap, SrcRows{row_b, row_s, S}}, m_real);
-}
-
-hipError_t gemm_enc_qkv(hipStream_t st, const bf16* A, const bf16* W, int M, int d, int K,
-                        const bf16* bias, bf16* q_out, bf16* ek, bf16* ev, int S, int H, int Scap, const int* row_b,
-                        const int* row_s, const int* m_real) {
-  return launch(st, A, K, W, M, 3 * d, K, EpiEncQkv{bias, q_out, ek, ev, d, H, Scap, SrcRows{row_b, row_s, S}}, m_real);
-}
-
 // ----------------------------------------------------------------------------- LayerNorm folded into the GEMMs
 // Post-LN blocks: x' = LN(y), y = x + sublayer(x).  Instead of a pass of its own over y, the
 // normalisation is split between the GEMM that produces y and the GEMMs that consume x':
@@ -429,6 +356,40 @@ struct EpiLnSum {
     // squared deviations from the chunk mean = sum y^2 - (sum y)^2 / CW, never below 0
     if (n % CW == 0) ln_out[(size_t)m * ln_pitch(ld / CW) + n / CW] = f32x2{s, fmaxf(ss - s * s * (1.0f / CW), 0.f)};
   }
+  // gemm_tile_kernel: the row's running chunk sums, the residual of a 32-column block, its sum, the chunk's pair
+  struct TileRow { float s, ss; };
+  __device__ __forceinline__ void tile_row(int, TileRow& t) const { t.s = t.ss = 0.f; }
+  __device__ __forceinline__ void tile_fetch(int m, int n, f32x4 (&p)[4]) const {
+    const float* src = x + (size_t)m * ld + n;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) p[q] = *reinterpret_cast<const f32x4*>(src + 8 * q);
+  }
+  __device__ __forceinline__ void tile_block(int m, int nb, int half, bool live, const f32x16& a, const f32x4 (&cv)[kVec][4],
+                                             const f32x4 (&p)[4], float rstd, float nmr, TileRow& t) const {
+    bf16x4 g[4];
+    f32x4 y[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        y[q][e] = a[4 * q + e] + __builtin_fmaf(__builtin_fmaf(p[q][e], rstd, nmr), cv[0][q][e], cv[1][q][e]);
+        t.s += y[q][e];
+        t.ss = __builtin_fmaf(y[q][e], y[q][e], t.ss);
+        g[q][e] = (bf16)(y[q][e] * cv[2][q][e]);
+      }
+    const bf16x8 g01 = join_halves(g[0], g[1]), g23 = join_halves(g[2], g[3]);
+    if (!live) return;
+    float* dst = x + (size_t)m * ld + nb + 4 * half;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(dst + 8 * q) = y[q];
+    bf16* dg = xg + (size_t)m * ld + nb + 8 * half;
+    *reinterpret_cast<bf16x8*>(dg) = g01;
+    *reinterpret_cast<bf16x8*>(dg + 16) = g23;
+  }
+  __device__ __forceinline__ void tile_end(int m, int n, int half, bool live, const TileRow& t) const {
+    const float s = half_add(t.s), ss = half_add(t.ss);
+    if (live && half == 0) ln_out[(size_t)m * ln_pitch(ld / 64) + n / 64] = f32x2{s, fmaxf(ss - s * s * (1.0f / 64), 0.f)};
+  }
 };
 
 // rstd * (acc - mean * cs) + bf on V columns: cv[0] = cs, cv[1] = bf
@@ -441,6 +402,22 @@ __device__ __forceinline__ void ln_finish(const float (&v)[V], float rstd, float
     if (relu) t = fmaxf(t, 0.f);
     o[i] = (bf16)t;
   }
+}
+
+// The same on a lane's 16 columns of a 32-column block: columns 8 half .. + 7 and 16 + 8 half .. + 7 of the block.
+__device__ __forceinline__ void ln_finish_block(const f32x16& a, float rstd, float nmr, const f32x4 (&cv)[2][4], bool relu,
+                                                bf16x8 (&o)[2]) {
+  bf16x4 g[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float t = __builtin_fmaf(a[4 * q + e], rstd, __builtin_fmaf(nmr, cv[0][q][e], cv[1][q][e]));
+      if (relu) t = fmaxf(t, 0.f);
+      g[q][e] = (bf16)t;
+    }
+  o[0] = join_halves(g[0], g[1]);
+  o[1] = join_halves(g[2], g[3]);
 }
 
 struct EpiLnBf16 {
@@ -464,6 +441,19 @@ struct EpiLnBf16 {
     ln_finish<V>(v, rstd, nmr, cv, relu != 0, o);
     if (live) store_cols<V>(out + (size_t)m * ldo + n, o);
   }
+  struct TileRow {};
+  __device__ __forceinline__ void tile_row(int, TileRow&) const {}
+  __device__ __forceinline__ void tile_fetch(int, int, f32x4 (&)[4]) const {}
+  __device__ __forceinline__ void tile_block(int m, int nb, int half, bool live, const f32x16& a, const f32x4 (&cv)[kVec][4],
+                                             const f32x4 (&)[4], float rstd, float nmr, TileRow&) const {
+    bf16x8 o[2];
+    ln_finish_block(a, rstd, nmr, cv, relu != 0, o);
+    if (!live) return;
+    bf16* dst = out + (size_t)m * ldo + nb + 8 * half;
+    *reinterpret_cast<bf16x8*>(dst) = o[0];
+    *reinterpret_cast<bf16x8*>(dst + 16) = o[1];
+  }
+  __device__ __forceinline__ void tile_end(int, int, int, bool, const TileRow&) const {}
 };
 
 // Decoder self-attention projection: columns [0,d) are queries, [d,2d) keys, [2d,3d) values.
@@ -504,6 +494,21 @@ struct EpiLnQkvAppend {
     bf16* cache = (part == 1) ? kc : vc;
     store_cols<V>(cache + (((size_t)p.sb * H + h) * Lcap + p.pos) * kHeadDim + e, o);
   }
+  typedef Pre<8> TileRow;
+  __device__ __forceinline__ void tile_row(int m, TileRow& t) const { fetch<8>(m, 0, t); }
+  __device__ __forceinline__ void tile_fetch(int, int, f32x4 (&)[4]) const {}
+  __device__ __forceinline__ void tile_block(int m, int nb, int half, bool live, const f32x16& a, const f32x4 (&cv)[kVec][4],
+                                             const f32x4 (&)[4], float rstd, float nmr, TileRow& t) const {
+    bf16x8 o[2];
+    ln_finish_block(a, rstd, nmr, cv, false, o);
+    const int part = nb / d, c = nb - part * d + 8 * half;   // (the block lies inside one part and one head)
+    if (!live || (part != 0 && t.sb < 0)) return;
+    bf16* dst = part == 0 ? q + (size_t)m * d + c
+                          : (part == 1 ? kc : vc) + (((size_t)t.sb * H + (c >> 6)) * Lcap + t.pos) * kHeadDim + (c & 63);
+    *reinterpret_cast<bf16x8*>(dst) = o[0];
+    *reinterpret_cast<bf16x8*>(dst + 16) = o[1];
+  }
+  __device__ __forceinline__ void tile_end(int, int, int, bool, const TileRow&) const {}
 };
 
 template <class Cfg, int VEC>
@@ -581,6 +586,208 @@ static hipError_t launch_ln_cfg(hipStream_t st, const bf16* A, int lda, const bf
                      A, lda, W, K, M, N, K, MT, NT, epi, m_real);
   return hipGetLastError();
 }
+
+// ----------------------------------------------------------------------------- large tiles, epilogue from registers
+// Many rows (encoder, prefill, full batches).  The product is formed transposed (gemm_mainloop<.., SWAP>), so a lane owns 16
+// columns of one row per 32-column block: four groups of four (8 q + 4 (lane / 32) .. + 3).  LayerNorm statistics of a row's
+// 64-column chunk are then sums over a lane's own values and one exchange with the other half; bf16 results are joined to
+// 16-byte stores by the same exchange; nothing is staged through LDS.
+//   256 x 256 (8 waves, one block per CU): a third fewer LDS reads and half the L2 traffic per product of
+//   128 x 128 (4 waves, two blocks per CU: one block's epilogue runs under the other's products).
+typedef GemmCfg<256, 256, 2, 2, 4> CfgSquare;
+
+template <class Cfg, int VEC>
+constexpr int tile_smem_bytes() { return Cfg::kSmemBytes + (2 * Cfg::kBM + VEC * Cfg::kBN) * 4; }
+
+template <class Cfg, class Epi>
+__global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16* __restrict__ A, int lda,
+                                                                     const bf16* __restrict__ W, int ldw, int M, int N, int K,
+                                                                     int NT, Epi epi, const int* __restrict__ m_real) {
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+  static_assert(Cfg::kWN == 64, "a wave's columns are one statistics chunk");
+  static_assert(Cfg::kThreads >= Epi::kVec * Cfg::kBN / 4, "one thread per 4 entries of the column vectors");
+  constexpr int TM = Cfg::kTM, TN = Cfg::kTN, BN = Cfg::kBN;
+  float* rowstat = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Cfg::kSmemBytes);   // [BM][2]
+  float* colv = rowstat + 2 * Cfg::kBM;                                                          // [kVec][BN]
+  if (m_real) M = min(M, *m_real);   // only the leading *m_real rows hold data (same value for the whole grid)
+  int mt, nt;
+  if (!xcd_tile_grouped((M + Cfg::kBM - 1) / Cfg::kBM, NT, mt, nt)) return;
+  const int m0 = mt * Cfg::kBM, n0 = nt * BN;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lrow = lane & 31, half = lane >> 5;
+  const int wm = (wave / Cfg::kWavesN) * Cfg::kWM, wn = (wave % Cfg::kWavesN) * Cfg::kWN;
+  GemmAcc<Cfg> acc;
+  gemm_mainloop<Cfg, true>(A, lda, W, ldw, M, N, 0, K / Cfg::GK, m0, n0, smem, acc, [&] {
+    constexpr int QPV = BN / 4;   // 16-byte pieces per column vector of the tile
+    const int t = threadIdx.x;
+    LnRows<Cfg> rows;
+    rows.request(epi.ln_in, epi.chunks, m0, M);
+    if (t < Epi::kVec * QPV)
+      *reinterpret_cast<f32x4*>(colv + t * 4) = *reinterpret_cast<const f32x4*>(epi.vec(t / QPV) + min(n0 + (t % QPV) * 4, N - 4));
+    rows.finish(epi.d_ln(), epi.chunks, epi.identity(), rowstat);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // visible after the main loop's first barrier
+  });
+  typename Epi::TileRow tr[TM];
+  f32x2 st[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int r = wm + i * 32 + lrow;
+    epi.tile_row(min(m0 + r, M - 1), tr[i]);
+    st[i] = *reinterpret_cast<const f32x2*>(rowstat + 2 * r);
+  }
+  // blocks of 32 rows x 32 columns in column-major order; the next one's reads are requested before this one's stores
+  f32x4 pre[2][4];
+  auto fetch = [&](int j, int i, f32x4 (&p)[4]) {
+    epi.tile_fetch(min(m0 + wm + i * 32 + lrow, M - 1), min(n0 + wn + j * 32, N - 32) + 4 * half, p);
+  };
+  fetch(0, 0, pre[0]);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int nb = n0 + wn + j * 32;
+    f32x4 cv[Epi::kVec][4];
+#pragma unroll
+    for (int v = 0; v < Epi::kVec; ++v)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) cv[v][q] = *reinterpret_cast<const f32x4*>(colv + v * BN + wn + j * 32 + 8 * q + 4 * half);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int m = m0 + wm + i * 32 + lrow, step = j * TM + i;
+      if (step + 1 < TM * TN) fetch(i + 1 < TM ? j : j + 1, i + 1 < TM ? i + 1 : 0, pre[(step + 1) & 1]);
+      epi.tile_block(m, nb, half, m < M && nb < N, acc.c[i][j], cv, pre[step & 1], st[i][0], st[i][1], tr[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = m0 + wm + i * 32 + lrow;
+    epi.tile_end(m, n0 + wn, half, m < M && n0 + wn < N, tr[i]);
+  }
+}
+
+template <class Cfg, class Epi>
+static hipError_t launch_tile(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K, const Epi& epi,
+                              const int* m_real) {
+  constexpr int kBytes = tile_smem_bytes<Cfg, Epi::kVec>();
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tile_kernel<Cfg, Epi>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
+  if (attr != hipSuccess) return attr;
+  const int MT = (M + Cfg::kBM - 1) / Cfg::kBM, NT = (N + Cfg::kBN - 1) / Cfg::kBN;
+  SD_LAUNCH_TIMED((gemm_tile_kernel<Cfg, Epi>), dim3(xcd_grid(MT, NT)), dim3(Cfg::kThreads), kBytes, st, A, lda, W, K, M, N, K,
+                  NT, epi, m_real);
+  return hipGetLastError();
+}
+
+// 256 x 256 tiles or 128 x 128 ones?  Time of a full round of blocks (256 and 512) as measured over K = 512 .. 4096, us:
+// 9.6 + 1.73 and 3.6 + 1.12 per 64 columns of K; a last round costs nearly a full one on one block per CU, and on two the
+// better part of one as soon as some CU has a second block.
+static bool square_tiles(int M, int N, int K) {
+  const float kt = K / 64.f;
+  const long sq = (long)((M + 255) / 256) * ((N + 255) / 256), wd = (long)((M + 127) / 128) * ((N + 127) / 128);
+  const float t_sq = (float)((sq + 255) / 256) * (sq < 256 ? 0.8f : 1.f) * (9.6f + 1.73f * kt);
+  const long rem = wd % 512;
+  const float t_wd = ((float)(wd / 512) + (rem == 0 ? 0.f : rem <= 256 ? 0.6f : 1.f)) * (3.6f + 1.12f * kt);
+  return t_sq < t_wd;
+}
+
+// ----------------------------------------------------------------------------- cross-attention keys / values
+// Keys and values of the encoder memory for up to kCrossLayers decoder layers in one launch (the layers share the memory's
+// rows): xk [layer][B][H][Scap][64], xv [layer][B][H][Scap/8][64][8].  The finished tile passes through LDS as bf16.  Keys
+// leave as whole rows of a head.  A block of 8 keys of the values is 1 KB of memory: a wave turns 8 tile rows x 64 columns
+// with two transposing reads and stores it at once, wherever in the tile the sequence's blocks begin (single values, as
+// before, only for blocks cut by the tile's edge).
+// 32768 rows, d = 1024: 288 us a layer with values stored one by one, 144 us.
+template <class Cfg>
+__global__ __launch_bounds__(Cfg::kThreads, 2) void cross_kv_kernel(const bf16* __restrict__ A, CrossKvArgs a, int M, int d,
+                                                                    int NT, const int* __restrict__ m_real) {
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+  constexpr int BM = Cfg::kBM, BN = Cfg::kBN, TM = Cfg::kTM, TN = Cfg::kTN, P = BN + 8;
+  static_assert(BM * P * 2 <= Cfg::kSmemBytes + Cfg::kTailBytes, "bf16 tile in the ring");
+  if (m_real) M = min(M, *m_real);
+  int mt, ntl;
+  if (!xcd_tile_grouped((M + BM - 1) / BM, NT * a.layers, mt, ntl)) return;
+  const int layer = ntl / NT, nt = ntl - layer * NT, m0 = mt * BM, n0 = nt * BN, N = 2 * d;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lrow = lane & 31, half = lane >> 5;
+  const int wm = (wave / Cfg::kWavesN) * Cfg::kWM, wn = (wave % Cfg::kWavesN) * Cfg::kWN;
+  const bf16* bias = a.b[layer];
+  GemmAcc<Cfg> acc;
+  gemm_mainloop<Cfg, true>(A, d, a.w[layer], d, M, N, 0, d / Cfg::GK, m0, n0, smem, acc);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    bf16x4 bv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bv[q] = *reinterpret_cast<const bf16x4*>(bias + min(n0 + wn + j * 32, N - 32) + 8 * q + 4 * half);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      bf16x4 g[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[q][e] = (bf16)(acc.c[i][j][4 * q + e] + (float)bv[q][e]);
+      bf16* dst = smem + (wm + i * 32 + lrow) * P + wn + j * 32 + 8 * half;
+      *reinterpret_cast<bf16x8*>(dst) = join_halves(g[0], g[1]);
+      *reinterpret_cast<bf16x8*>(dst + 16) = join_halves(g[2], g[3]);
+    }
+  }
+  __syncthreads();
+  // a wave takes RPW rows of one 64-column strip (one head's keys or values)
+  constexpr int STRIPS = BN / 64, RW = Cfg::kWaves / STRIPS, RPW = BM / RW, STEP = RPW < 64 ? RPW : 64;
+  const int c0 = (wave % STRIPS) * 64, r0 = (wave / STRIPS) * RPW;
+  const int part = (n0 + c0) / d, h = (n0 + c0 - part * d) >> 6, H = d >> 6;
+  if (n0 + c0 >= N) return;
+  bf16* out = (part == 0 ? a.xk : a.xv) + a.layer_stride * layer;
+  for (int base = r0; base < r0 + RPW; base += STEP) {
+    SrcRows::At at{-1, 0};   // of row base + lane
+    if (lane < STEP && m0 + base + lane < M) at = a.rows.at(m0 + base + lane);
+    if (part == 0) {
+#pragma unroll
+      for (int it = 0; it < STEP / 8; ++it) {
+        const int r = it * 8 + (lane >> 3), b = __shfl(at.b, r, 64), s = __shfl(at.s, r, 64);
+        const bf16x8 v = *reinterpret_cast<const bf16x8*>(smem + (base + r) * P + c0 + (lane & 7) * 8);
+        if (b >= 0) *reinterpret_cast<bf16x8*>(out + (((size_t)b * H + h) * a.Scap + s) * kHeadDim + (lane & 7) * 8) = v;
+      }
+      continue;
+    }
+    const bool head = at.b >= 0 && ((at.s & 7) == 0 || base + lane == 0);
+    unsigned long long heads = __builtin_amdgcn_ballot_w64(head);
+    while (heads) {
+      const int l = __builtin_ctzll(heads), r = base + l;
+      heads &= heads - 1;
+      const int b = __builtin_amdgcn_readlane(at.b, l), s = __builtin_amdgcn_readlane(at.s, l), o = s & 7;
+      bf16* dst = out + ((size_t)b * H + h) * a.Scap * kHeadDim + vt_off(s & ~7, lane);
+      if (o == 0 && r + 8 <= BM) {   // whole (rows beyond the sequence's end fill key slots nobody reads)
+        const bf16* src = smem + (r + ((lane >> 2) & 3)) * P + c0 + 16 * (lane >> 4) + 4 * (lane & 3);
+        s16x4 v[2] = {lds_tr16(src), lds_tr16(src + 4 * P)};
+        bf16x8 w;
+        __builtin_memcpy(&w, v, 16);
+        *reinterpret_cast<bf16x8*>(dst) = w;
+      } else {
+        for (int i = 0; i < 8 - o && r + i < BM && m0 + r + i < M; ++i) {
+          if (a.rows.at(m0 + r + i).b != b) break;
+          dst[o + i] = smem[(r + i) * P + c0 + lane];
+        }
+      }
+    }
+  }
+}
+
+template <class Cfg>
+static hipError_t launch_cross_kv(hipStream_t st, const bf16* A, const CrossKvArgs& a, int M, int d, const int* m_real) {
+  constexpr int kBytes = Cfg::kSmemBytes + Cfg::kTailBytes;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(cross_kv_kernel<Cfg>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
+  if (attr != hipSuccess) return attr;
+  const int MT = (M + Cfg::kBM - 1) / Cfg::kBM, NT = (2 * d + Cfg::kBN - 1) / Cfg::kBN;
+  SD_LAUNCH_TIMED((cross_kv_kernel<Cfg>), dim3(xcd_grid(MT, NT * a.layers)), dim3(Cfg::kThreads), kBytes, st, A, a, M, d, NT,
+                  m_real);
+  return hipGetLastError();
+}
+
+hipError_t gemm_cross_kv(hipStream_t st, const bf16* A, const CrossKvArgs& a, int M, int d, const int* m_real) {
+  if (M <= 0 || a.layers <= 0) return hipSuccess;
+  const long wide = (long)((M + 127) / 128) * ((2 * d + 127) / 128) * a.layers;
+  if (wide < 200) return launch_cross_kv<CfgSmall>(st, A, a, M, d, m_real);
+  if (wide >= 512 && square_tiles(M, 2 * d * a.layers, d)) return launch_cross_kv<CfgSquare>(st, A, a, M, d, m_real);
+  return launch_cross_kv<CfgWide>(st, A, a, M, d, m_real);
+}
+
 // ----------------------------------------------------------------------------- K split inside the block
 // With a few hundred rows or fewer, 64 x 64 tiles whose four waves share one ring leave most CUs without a block and
 // make the others walk K alone, one barrier per 64 columns.  Here the waves of a block split K: each takes every
@@ -763,6 +970,10 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const bf16* 
     if (K >= 4096 && !m_real && one_round(M, N, 96, 64)) return launch_ksplit<KsplitCfg<96, 64, 3, 2>>(st, A, lda, W, M, N, K, epi, m_real);
   }
   const long wide_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
+  if (wide_tiles >= 512) {   // two blocks of 128 x 128 for every CU, or larger tiles still
+    if (square_tiles(M, N, K)) return launch_tile<CfgSquare>(st, A, lda, W, M, N, K, epi, m_real);
+    return launch_tile<CfgWide>(st, A, lda, W, M, N, K, epi, m_real);
+  }
   // the widest outputs (QKV and FFN1 of the big model) run on 256x128 tiles, eight waves, three-deep
   // ring: 9-15 % faster than 128x128 on weights streamed from HBM, a few % inside the decoder pass
   if constexpr (Epi::kVec == 2) {

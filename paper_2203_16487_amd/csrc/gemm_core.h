@@ -45,6 +45,8 @@ struct GemmCfg {
   static constexpr int kIPW = kRows / kRowsPerLoad / kWaves;   // global_load_lds per wave per stage
   static constexpr int kStageElems = kRows * GK;
   static constexpr int kSmemBytes = STAGES * kStageElems * 2;
+  // LDS beyond the ring that a bf16 copy of the tile (rows padded by 16 bytes) needs
+  static constexpr int kTailBytes = BM * (BN + 8) * 2 > kSmemBytes ? BM * (BN + 8) * 2 - kSmemBytes : 0;
   static constexpr int kWM = BM / WAVES_M, kWN = BN / WAVES_N;   // wave tile
   static constexpr int kTM = kWM / 32, kTN = kWN / 32;           // MFMA tiles per wave
   static_assert(kRows % (kRowsPerLoad * kWaves) == 0 && BM % kRowsPerLoad == 0 && kWM % 32 == 0 && kWN % 32 == 0,
@@ -101,11 +103,15 @@ __device__ __forceinline__ void wait_vm_stages(int allow) {
 // SWAP: W rows take the MFMA's row operand and A rows its column operand: register r of lane l of
 // tile (i, j) then holds row m = 32 i + l%32, column n = 32 j + 8*(r/4) + 4*(l/32) + r%4 (relative to
 // the wave tile), i.e. a lane owns 16 columns of ONE row per tile instead of 16 rows of one column.
-template <class Cfg, bool SWAP = false>
+// hook() runs once the first stages are requested (its own loads then travel behind them).
+struct NoHook {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <class Cfg, bool SWAP = false, class Hook = NoHook>
 __device__ __forceinline__ void gemm_mainloop(const bf16* __restrict__ A, int lda,
                                               const bf16* __restrict__ W, int ldw, int M, int N,
                                               int k_begin, int KT, int m0, int n0, bf16* smem,
-                                              GemmAcc<Cfg>& acc) {
+                                              GemmAcc<Cfg>& acc, Hook hook = Hook()) {
   constexpr int IPW = Cfg::kIPW, S = Cfg::kStages, GK = Cfg::GK, RPL = Cfg::kRowsPerLoad, CPR = GK / 8;
   constexpr int TM = Cfg::kTM, TN = Cfg::kTN, NS = GK / 16, TMIN = TM < TN ? TM : TN;
   static_assert(S >= 2 && NS % 2 == 0, "ring depth / fragment buffer parity");
@@ -138,6 +144,7 @@ __device__ __forceinline__ void gemm_mainloop(const bf16* __restrict__ A, int ld
 #pragma unroll
       for (int i = 0; i < IPW; ++i) dma16(gptr[i] + s * GK, wslot + s * Cfg::kStageElems + i * 512);
     }
+  hook();
   const int lrow = lane & 31, lhalf = lane >> 5;
   int offA[TM][NS], offB[TN][NS];   // fragment offsets inside a stage
 #pragma unroll

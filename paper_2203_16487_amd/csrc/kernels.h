@@ -40,18 +40,30 @@ hipError_t gemm_bf16(hipStream_t st, const bf16* A, int lda, const bf16* W, int 
 hipError_t gemm_qkv_append(hipStream_t st, const bf16* A, const bf16* W, int M, int d, int K,
                            const bf16* bias, bf16* q_out, bf16* kc, bf16* vc, const int* row_b,
                            const int* row_pos, int H, int Lcap, const int* m_real = nullptr);
-// Cross-attention keys/values of the encoder memory, N = 2d: memory row m -> sequence b, source position s ->
-// xk [B][H][Scap][64], xv key-blocked [B][H][Scap/8][64][8].  Padded rows (row_b null): m = b*S + s; packed
-// rows: b = row_b[m] (negative: a row no sequence owns, dropped), s = row_s[m].
-hipError_t gemm_cross_kv(hipStream_t st, const bf16* A, const bf16* W, int M, int d, int K,
-                         const bf16* bias, bf16* xk, bf16* xv, int S, int H, int Scap, const int* row_b = nullptr,
-                         const int* row_s = nullptr, const int* m_real = nullptr);
-
-// Encoder self-attention projection, N = 3d, rows as above: q -> q_out [M,d] (row m), keys ->
-// ek [B][H][Scap][64], values -> ev key-blocked [B][H][Scap/8][64][8].
-hipError_t gemm_enc_qkv(hipStream_t st, const bf16* A, const bf16* W, int M, int d, int K,
-                        const bf16* bias, bf16* q_out, bf16* ek, bf16* ev, int S, int H, int Scap,
-                        const int* row_b = nullptr, const int* row_s = nullptr, const int* m_real = nullptr);
+// Cross-attention keys/values of the encoder memory [M,d] (N = 2d) for a.layers decoder layers: memory row m -> sequence b,
+// source position s -> xk [layer][B][H][Scap][64], xv key-blocked [layer][B][H][Scap/8][64][8].
+// Row m of the source side belongs to sequence b at source position s: m = b * S + s for padded
+// rows, or (row_b[m], row_s[m]) for packed rows (row_b < 0: a row no sequence owns).
+struct SrcRows {
+  const int* __restrict__ row_b;   // null: padded rows
+  const int* __restrict__ row_s;
+  int S;
+  struct At { int b, s; };
+  __device__ __forceinline__ At at(int m) const {
+    if (row_b) return At{row_b[m], row_s[m]};
+    const int b = m / S;
+    return At{b, m - b * S};
+  }
+};
+constexpr int kCrossLayers = 8;   // layers of one launch
+struct CrossKvArgs {
+  const bf16 *w[kCrossLayers], *b[kCrossLayers];   // [2d,d], [2d]
+  bf16 *xk, *xv;                                   // of the first layer
+  size_t layer_stride;                             // elements between two layers' arenas
+  int layers, Scap;
+  SrcRows rows;
+};
+hipError_t gemm_cross_kv(hipStream_t st, const bf16* A, const CrossKvArgs& a, int M, int d, const int* m_real = nullptr);
 
 // ---- LayerNorm folded into the GEMM around it (post-LN blocks) ----
 // y = residual sum of a sub-layer, LN(y) = (y - mean) * rstd * g + beta.  The GEMM that forms y
@@ -155,7 +167,7 @@ struct AttnArgs {
   // key's row) / 64 of k_scale (keys) / v_scale (values): [b][h][cap] with the arena strides above
   const float* k_scale = nullptr;
   const float* v_scale = nullptr;
-  // [B] first key / value row of sequence b (more than 32 queries, rows only; null: k_b / v_b): rows packed like the queries
+  // [B] first key / value row of sequence b (values in rows only; null: k_b / v_b): rows packed like the queries
   const int* kv_off = nullptr;
 };
 hipError_t attention(hipStream_t st, const AttnArgs& a);
@@ -258,8 +270,9 @@ hipError_t build_pos_table(hipStream_t st, float* pe, int n_pos, int d);
 hipError_t embed_rows(hipStream_t st, const int* tok, const int* pos, const bf16* E,
                       const float* pe, float* x, bf16* xb, int R, int d);
 // x <- LayerNorm(x) * g + b in place (fp32), xb <- bf16(x)
+// (keep_x = false: x stays as it is)
 hipError_t layer_norm(hipStream_t st, float* x, const bf16* g, const bf16* b, bf16* xb, int R,
-                      int d, const int* m_real = nullptr);
+                      int d, const int* m_real = nullptr, bool keep_x = true);
 // dst [B*k][d] bf16 <- LayerNorm of the mask-slot rows first(b) + new_rows[b] + s of x (x unchanged),
 // first(b) = row_start[b], or b*T when row_start is null
 hipError_t layer_norm_slots(hipStream_t st, const float* x, const bf16* g, const bf16* b, bf16* dst,
@@ -293,12 +306,11 @@ hipError_t assemble_embed_stream(hipStream_t st, const SeqState& s, const RowMap
 hipError_t advance_cached(hipStream_t st, const SeqState& s, int role, const int* new_rows, int B);
 hipError_t gather_slots(hipStream_t st, const bf16* xb, bf16* dst, const int* new_rows, const int* row_start, int B,
                         int T, int k, int d);
-hipError_t encoder_rows(hipStream_t st, const int* src, int* tok, int* pos, int B, int S, int V);
-// Encoder rows without padding: sequence b owns rows row_start[b] .. + src_len[b] - 1 (running sum, batch
-// order; row_start [B+1]), n_rows[0] = their number; tok / pos / row_b [B*S]: rows beyond n_rows get token 0,
-// position 0, sequence -1.
-hipError_t encoder_rows_packed(hipStream_t st, const int* src, const int* src_len, int* tok, int* pos, int* row_b,
-                               int* row_start, int* n_rows, int B, int S, int V);
+// Encoder rows without padding: sequence b owns rows row_start[b] .. + src_len[b] - 1 (running sum, batch order; row_start
+// [B+1]), n_rows[0] = their number; their positions pos / owners row_b [B*S], embedded (x fp32, xb bf16) in the same launch.
+// Rows at and beyond n_rows are not written.
+hipError_t encoder_rows_embed(hipStream_t st, const int* src, const int* src_len, int* pos, int* row_b, int* row_start,
+                              int* n_rows, int B, int S, int V, const bf16* E, const float* pe, float* x, bf16* xb, int d);
 // dst [B][S][d] <- packed rows (zeros beyond a sequence's length)
 hipError_t unpack_rows(hipStream_t st, const bf16* src, const int* row_start, const int* src_len, bf16* dst, int B,
                        int S, int d);

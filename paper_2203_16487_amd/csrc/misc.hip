@@ -25,10 +25,11 @@ hipError_t build_pos_table(hipStream_t st, float* pe, int n_pos, int d) {
 
 // ----------------------------------------------------------------------------- embedding
 // x[r] = E[tok[r]] * sqrt(d) + PE[pos[r]]  (fp32) and its bf16 copy
-// One block per row, 8 columns per thread and step (d % 64 == 0).
+// `threads` threads per row (this one is number t), 8 columns per thread and step (d % 64 == 0).
 __device__ __forceinline__ void embed_row(const bf16* __restrict__ e, const float* __restrict__ p,
-                                          float* __restrict__ xr, bf16* __restrict__ xbr, int d, float scale) {
-  for (int c = threadIdx.x * 8; c < d; c += blockDim.x * 8) {
+                                          float* __restrict__ xr, bf16* __restrict__ xbr, int d, float scale,
+                                          int t, int threads) {
+  for (int c = t * 8; c < d; c += threads * 8) {
     const bf16x8 ev = *reinterpret_cast<const bf16x8*>(e + c);
     const f32x4 p0 = *reinterpret_cast<const f32x4*>(p + c), p1 = *reinterpret_cast<const f32x4*>(p + c + 4);
     f32x4 v0, v1;
@@ -51,7 +52,7 @@ __global__ __launch_bounds__(128) void embed_kernel(const int* __restrict__ tok,
                                                     float scale) {
   const int r = blockIdx.x;
   if (r >= R) return;
-  embed_row(E + (size_t)tok[r] * d, pe + (size_t)pos[r] * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale);
+  embed_row(E + (size_t)tok[r] * d, pe + (size_t)pos[r] * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale, threadIdx.x, 128);
 }
 hipError_t embed_rows(hipStream_t st, const int* tok, const int* pos, const bf16* E,
                       const float* pe, float* x, bf16* xb, int R, int d) {
@@ -68,7 +69,7 @@ hipError_t embed_rows(hipStream_t st, const int* tok, const int* pos, const bf16
 template <int PER>   // d = 64 * PER
 __global__ __launch_bounds__(256) void ln_kernel(float* __restrict__ x, const bf16* __restrict__ g,
                                                  const bf16* __restrict__ bta, bf16* __restrict__ xb,
-                                                 int R, const int* __restrict__ m_real) {
+                                                 int R, const int* __restrict__ m_real, int keep_x) {
   constexpr int d = 64 * PER;
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(256) void ln_kernel(float* __restrict__ x, const bf
   for (int i = 0; i < PER; ++i) {
     const int c = i * 64 + lane;
     const float y = (v[i] - mean) * rstd * gg[i] + bb[i];
-    xr[c] = y;
+    if (keep_x) xr[c] = y;
     xb[(size_t)r * d + c] = (bf16)y;
   }
 }
@@ -149,14 +150,16 @@ hipError_t layer_norm_slots(hipStream_t st, const float* x, const bf16* g, const
 }
 
 template <int PER>
-static hipError_t ln_launch(hipStream_t st, float* x, const bf16* g, const bf16* b, bf16* xb, int R, const int* m_real) {
-  hipLaunchKernelGGL(ln_kernel<PER>, dim3((R + 3) / 4), dim3(256), 0, st, x, g, b, xb, R, m_real);
+static hipError_t ln_launch(hipStream_t st, float* x, const bf16* g, const bf16* b, bf16* xb, int R, const int* m_real,
+                            bool keep_x) {
+  hipLaunchKernelGGL(ln_kernel<PER>, dim3((R + 3) / 4), dim3(256), 0, st, x, g, b, xb, R, m_real, keep_x ? 1 : 0);
   return hipGetLastError();
 }
-hipError_t layer_norm(hipStream_t st, float* x, const bf16* g, const bf16* b, bf16* xb, int R, int d, const int* m_real) {
+hipError_t layer_norm(hipStream_t st, float* x, const bf16* g, const bf16* b, bf16* xb, int R, int d, const int* m_real,
+                      bool keep_x) {
   if (R <= 0) return hipSuccess;
   switch (d / 64) {   // d = 64 * heads, heads <= 32
-#define SD_LN_CASE(P) case P: return ln_launch<P>(st, x, g, b, xb, R, m_real);
+#define SD_LN_CASE(P) case P: return ln_launch<P>(st, x, g, b, xb, R, m_real, keep_x);
     SD_LN_CASE(1) SD_LN_CASE(2) SD_LN_CASE(3) SD_LN_CASE(4) SD_LN_CASE(5) SD_LN_CASE(6) SD_LN_CASE(7) SD_LN_CASE(8)
     SD_LN_CASE(9) SD_LN_CASE(10) SD_LN_CASE(11) SD_LN_CASE(12) SD_LN_CASE(13) SD_LN_CASE(14) SD_LN_CASE(15)
     SD_LN_CASE(16) SD_LN_CASE(17) SD_LN_CASE(18) SD_LN_CASE(19) SD_LN_CASE(20) SD_LN_CASE(21) SD_LN_CASE(22)
@@ -220,7 +223,7 @@ __global__ __launch_bounds__(128) void assemble_embed_verify_kernel(SeqState s, 
     if (i < k) s.last_draft[b * s.k_max + i] = draft[b * k + i];
     if (i == 0) rm.seq_rows[b] = T;
   }
-  embed_row(E + (size_t)tok * d, pe + (size_t)(j + i) * d, x + (size_t)idx * d, xb + (size_t)idx * d, d, scale);
+  embed_row(E + (size_t)tok * d, pe + (size_t)(j + i) * d, x + (size_t)idx * d, xb + (size_t)idx * d, d, scale, threadIdx.x, 128);
 }
 hipError_t assemble_embed_verify(hipStream_t st, const SeqState& s, const RowMap& rm, const int* draft, int B, int k,
                                  int V, const bf16* E, const float* pe, float* x, bf16* xb, int d) {
@@ -294,7 +297,7 @@ __global__ __launch_bounds__(128) void assemble_embed_stream_kernel(SeqState s, 
   if (threadIdx.x == 0) {
     rm.row_b[r] = rb; rm.row_pos[r] = pos; rm.row_tok[r] = tok; rm.row_lim[r] = lim; rm.row_draft[r] = -1;
   }
-  embed_row(E + (size_t)tok * d, pe + (size_t)pos * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale);
+  embed_row(E + (size_t)tok * d, pe + (size_t)pos * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale, threadIdx.x, 128);
 }
 hipError_t assemble_embed_stream(hipStream_t st, const SeqState& s, const RowMap& rm, int role, int B, int T,
                                  int n_mask, int mask_id, int pad_id, int V, int* new_rows, const bf16* E,
@@ -335,63 +338,44 @@ hipError_t gather_slots(hipStream_t st, const bf16* xb, bf16* dst, const int* ne
   return hipGetLastError();
 }
 
-// encoder rows: row b*S + s feeds src[b][s] (clamped into the vocabulary) at position s
-__global__ void encoder_rows_kernel(const int* __restrict__ src, int* __restrict__ tok, int* __restrict__ pos,
-                                    long n, int S, int V) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  tok[i] = min(max(src[i], 0), V - 1);
-  pos[i] = (int)(i % S);
-}
-hipError_t encoder_rows(hipStream_t st, const int* src, int* tok, int* pos, int B, int S, int V) {
-  const long n = (long)B * S;
-  hipLaunchKernelGGL(encoder_rows_kernel, blocks_for(n, 256), dim3(256), 0, st, src, tok, pos, n, S, V);
-  return hipGetLastError();
-}
-
-// The same without the padding: sequence b owns rows row_start[b] .. row_start[b] + src_len[b] - 1 (a
-// running sum, sources in batch order), n_rows[0] = their number.  Rows beyond it (up to B * S) get a
-// valid token, position 0 and sequence -1: whatever is computed on them is never stored anywhere else.
-__global__ __launch_bounds__(1024) void encoder_pack_scan_kernel(const int* __restrict__ src_len, int B, int S,
-                                                                 int* __restrict__ row_start, int* __restrict__ n_rows) {
-  __shared__ int part[1024];
-  const int per = (B + 1023) / 1024, b0 = threadIdx.x * per;
-  int sum = 0;
-  for (int i = 0; i < per; ++i)
-    if (b0 + i < B) sum += min(max(src_len[b0 + i], 0), S);
-  part[threadIdx.x] = sum;
+// Encoder rows without padding: sequence b owns rows row_start[b] .. row_start[b] + src_len[b] - 1 (a running sum, sources
+// in batch order), n_rows[0] = their number.  A block embeds kEncRows rows of one sequence; it finds the sequence's first
+// row as the sum of the lengths before it (B loads spread over its threads).
+constexpr int kEncRows = 8;
+__global__ __launch_bounds__(256) void encoder_rows_embed_kernel(const int* __restrict__ src, const int* __restrict__ src_len,
+                                                                 int* __restrict__ pos, int* __restrict__ row_b,
+                                                                 int* __restrict__ row_start, int* __restrict__ n_rows, int B,
+                                                                 int S, int V, const bf16* __restrict__ E,
+                                                                 const float* __restrict__ pe, float* __restrict__ x,
+                                                                 bf16* __restrict__ xb, int d, float scale) {
+  __shared__ int wsum[4];
+  const int per = (S + kEncRows - 1) / kEncRows, b = blockIdx.x / per, s0 = (blockIdx.x - b * per) * kEncRows;
+  const int len = min(max(src_len[b], 0), S);
+  if (s0 >= len && s0 > 0) return;
+  int part = 0;
+  for (int o = threadIdx.x; o < b; o += 256) part += min(max(src_len[o], 0), S);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = part;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int t = 0; t < 1024; ++t) { const int v = part[t]; part[t] = run; run += v; }
-    row_start[B] = run;
-    n_rows[0] = run;
+  const int first = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  if (s0 == 0 && threadIdx.x == 0) {
+    row_start[b] = first;
+    if (b == B - 1) { row_start[B] = first + len; n_rows[0] = first + len; }
   }
-  __syncthreads();
-  int run = part[threadIdx.x];
-  for (int i = 0; i < per; ++i)
-    if (b0 + i < B) { row_start[b0 + i] = run; run += min(max(src_len[b0 + i], 0), S); }
-}
-__global__ void encoder_pack_rows_kernel(const int* __restrict__ src, const int* __restrict__ src_len,
-                                         const int* __restrict__ row_start, int* __restrict__ tok,
-                                         int* __restrict__ pos, int* __restrict__ row_b, long n, int B, int S, int V) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int b = (int)(i / S), s = (int)(i - (long)b * S);
-  if (s < min(max(src_len[b], 0), S)) {
-    const int r = row_start[b] + s;
-    tok[r] = min(max(src[i], 0), V - 1);
-    pos[r] = s;
-    row_b[r] = b;
+  // half a wave-quad per row: two rows at a time
+  const int lo = threadIdx.x >> 7, t = threadIdx.x & 127;
+  for (int i = lo; i < kEncRows && s0 + i < len; i += 2) {
+    const int s = s0 + i, r = first + s, tok = min(max(src[(size_t)b * S + s], 0), V - 1);
+    if (t == 0) { pos[r] = s; row_b[r] = b; }
+    embed_row(E + (size_t)tok * d, pe + (size_t)s * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale, t, 128);
   }
-  if (i >= row_start[B]) { tok[i] = 0; pos[i] = 0; row_b[i] = -1; }   // (the rows no sequence owns)
 }
-hipError_t encoder_rows_packed(hipStream_t st, const int* src, const int* src_len, int* tok, int* pos, int* row_b,
-                               int* row_start, int* n_rows, int B, int S, int V) {
-  const long n = (long)B * S;
-  hipLaunchKernelGGL(encoder_pack_scan_kernel, dim3(1), dim3(1024), 0, st, src_len, B, S, row_start, n_rows);
-  hipLaunchKernelGGL(encoder_pack_rows_kernel, blocks_for(n, 256), dim3(256), 0, st, src, src_len, row_start, tok, pos,
-                     row_b, n, B, S, V);
+hipError_t encoder_rows_embed(hipStream_t st, const int* src, const int* src_len, int* pos, int* row_b, int* row_start,
+                              int* n_rows, int B, int S, int V, const bf16* E, const float* pe, float* x, bf16* xb, int d) {
+  if (B <= 0 || S <= 0) return hipSuccess;
+  hipLaunchKernelGGL(encoder_rows_embed_kernel, dim3(B * ((S + kEncRows - 1) / kEncRows)), dim3(256), 0, st, src, src_len, pos,
+                     row_b, row_start, n_rows, B, S, V, E, pe, x, xb, d, sqrtf((float)d));
   return hipGetLastError();
 }
 
