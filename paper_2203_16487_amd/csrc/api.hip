@@ -65,6 +65,8 @@ struct Model {
   unsigned char *xk8 = nullptr, *xv8 = nullptr;   // E4M3 codes of xk / xv, same layouts
   float *xks = nullptr, *xvs = nullptr;           // one scale per (layer, sequence, head, key)
   std::vector<Fp8Layer> dec8;
+  float* fold8 = nullptr;        // cs and bf vectors as in fold, of the codes
+  std::vector<LnFolds> folds8;
   sd::SkWeight embed8;
   float* hx = nullptr;       // [Bmax*k_max][d] head-based drafting: the hidden state each head adds to, then its output
   bool skinny_ready = false;
@@ -275,6 +277,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   if (c->fp8) {
     t.w8 = cv.take<unsigned char>((size_t)d->dec_layers * (6 * D * D + 2 * D * F) + (size_t)d->vocab * D);
     t.w8s = cv.take<float>((size_t)d->dec_layers * (7 * D + F) + (size_t)d->vocab);
+    t.fold8 = cv.take<float>((size_t)d->dec_layers * 2 * (4 * D + F));
   }
   t.xb = cv.take<bf16>(Rpass * D);
   t.lnp[0] = cv.take<float>(Rpass * (D / 32) * 2);
@@ -316,7 +319,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     m->kv_layer = t.kv_layer; m->xkv_layer = t.xkv_layer;
     m->pe = t.pe; m->kc = t.kc; m->vc = t.vc; m->xk = t.xk; m->xv = t.xv;
     m->lnp[0] = t.lnp[0]; m->lnp[1] = t.lnp[1]; m->fold = t.fold;
-    m->x = t.x; m->x2 = t.x2; m->skp = t.skp; m->hx = t.hx; m->w8 = t.w8; m->w8s = t.w8s; m->xk8 = t.xk8; m->xv8 = t.xv8; m->xks = t.xks; m->xvs = t.xvs; m->xb = t.xb; m->q = t.q; m->att = t.att; m->hid = t.hid;
+    m->x = t.x; m->x2 = t.x2; m->skp = t.skp; m->hx = t.hx; m->w8 = t.w8; m->w8s = t.w8s; m->fold8 = t.fold8; m->xk8 = t.xk8; m->xv8 = t.xv8; m->xks = t.xks; m->xvs = t.xvs; m->xb = t.xb; m->q = t.q; m->att = t.att; m->hid = t.hid;
     m->part = t.part; m->row_stats = t.row_stats; m->zd = t.zd; m->rm = t.rm;
     m->slots = t.slots; m->new_rows = t.new_rows; m->rs_layers = t.rs_layers; m->rs_bar = t.rs_bar;
     m->ex = t.ex; m->exb = t.exb; m->eqkv = t.eqkv; m->eatt = t.eatt; m->ehid = t.ehid;
@@ -342,8 +345,10 @@ inline void cross_fp8(const Model& m, int l, sd::AttnArgs& a) {
 // packed: the rows of the pass were assembled without padding (m.rm.row_start); R = B*T is then
 // only the bound the grids are sized for, and tiles beyond the rows in use return at once.
 // kv_only (prefill): the pass is wanted for the keys / values it appends; it ends where the last layer's are stored.
+// few (verify passes of at most 32 rows, LayerNorm folded): the projections stream the E4M3 copies if the model has them, and
+// the last sum stays un-normalised in m.x (the small-batch vocabulary kernel normalises it itself).
 int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool embedded = false, int slot_k = 0,
-                   bool packed = false, bool kv_only = false) {
+                   bool packed = false, bool kv_only = false, bool few = false) {
   const int R = B * T, D = m.d.d_model, F = m.d.d_ffn, H = m.d.n_heads;
   const int Lcap = c->Lcap, Scap = c->Scap;
   const int* m_real = packed ? m.rm.row_start + B : nullptr;
@@ -355,7 +360,7 @@ int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool 
   const bool fold = !c->no_ln_fold;
   sd::LnPairs pend{m.lnp[0], 0};   // chunk pairs of the sum in m.x (0 chunks: m.x is the residual itself)
   int flip = 1;
-  auto sum = [&](const bf16* A, int K, const bf16* W, const float* vecs) {
+  auto sum = [&](const bf16* A, int K, const sd::SkWeight& W, const float* vecs) {
     float* out = m.lnp[flip];
     hipError_t e = sd::gemm_ln_sum(st, A, K, W, R, D, K, vecs, pend, m.x, m.xb, out, m_real);
     pend = sd::LnPairs{out, sd::ln_sum_chunks(R, D)};
@@ -364,10 +369,12 @@ int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool 
   };
   for (int l = 0; l < m.d.dec_layers; ++l) {
     const DecLayer& L = m.dec[l];
+    const Fp8Layer W = few && m.fp8 ? m.dec8[l] : Fp8Layer{L.wqkv, L.wo, L.cwq, L.cwo, L.w1, L.w2};
+    const LnFolds& fd = few && m.fp8 ? m.folds8[l] : m.folds[l];
     bf16* kc = m.kc + m.kv_layer * l;
     bf16* vc = m.vc + m.kv_layer * l;
     if (fold) {
-      LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_ln_qkv_append(st, m.xb, L.wqkv, R, D, m.folds[l].qkv, pend, m.q, kc, vc, m.rm.row_b, m.rm.row_pos, H, Lcap, m_real));
+      LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_ln_qkv_append(st, m.xb, W.wqkv, R, D, fd.qkv, pend, m.q, kc, vc, m.rm.row_b, m.rm.row_pos, H, Lcap, m_real));
     } else {
       LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_qkv_append(st, m.xb, L.wqkv, R, D, D, L.bqkv, m.q, kc, vc, m.rm.row_b,
                                     m.rm.row_pos, H, Lcap, m_real));
@@ -383,8 +390,8 @@ int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool 
     a.key_split = Lcap > 256; a.cap = Lcap;
     LAUNCH(c, SPECDEC_KIND_ATTN, st, sd::attention(st, a));
     if (fold) {
-      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.att, D, L.wo, m.folds[l].vo));
-      LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_ln_bf16(st, m.xb, L.cwq, R, D, D, m.folds[l].cq, pend, m.q, D, false, m_real));
+      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.att, D, W.wo, fd.vo));
+      LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_ln_bf16(st, m.xb, W.cwq, R, D, D, fd.cq, pend, m.q, D, false, m_real));
     } else {
       LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sd::gemm_f32(st, m.att, D, L.wo, R, D, D, L.bo, m.x, m.x, D));
       LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.x, L.ln1g, L.ln1b, m.xb, R, D));
@@ -397,10 +404,10 @@ int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool 
     if (m.kv8) cross_fp8(m, l, a);
     LAUNCH(c, SPECDEC_KIND_ATTN, st, sd::attention(st, a));
     if (fold) {
-      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.att, D, L.cwo, m.folds[l].vco));
-      LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_ln_bf16(st, m.xb, L.w1, R, F, D, m.folds[l].w1, pend, m.hid, F, true, m_real));
-      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.hid, F, L.w2, m.folds[l].v2));
-      if (l + 1 == m.d.dec_layers) {   // the vocabulary projection reads the normalised rows themselves
+      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.att, D, W.cwo, fd.vco));
+      LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_ln_bf16(st, m.xb, W.w1, R, F, D, fd.w1, pend, m.hid, F, true, m_real));
+      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.hid, F, W.w2, fd.v2));
+      if (l + 1 == m.d.dec_layers && !few) {   // the vocabulary projection reads the normalised rows themselves
         if (slot_k > 0)
           LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm_slots(st, m.x, L.ln3g, L.ln3b, m.slots, m.new_rows, row_start, B, T, slot_k, D));
         else
@@ -428,10 +435,6 @@ bool skinny_ok(const specdec_ctx* c, const Model& m, int R, int T) {
 int decoder_layers_skinny(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, sd::SkSrc* out) {
   const int R = B * T, D = m.d.d_model, F = m.d.d_ffn, H = m.d.n_heads;
   const int Lcap = c->Lcap, Scap = c->Scap;
-  if (!m.skinny_ready) {
-    HIPCHK(c, sd::skinny_init(D));
-    m.skinny_ready = true;
-  }
   sd::SkSrc cur{0, nullptr, nullptr, nullptr, m.rm.row_tok, m.rm.row_pos, m.embed, m.pe};
   float* freeb = m.x;       // residual-sum buffer not read by the kernel being launched
   float* other = m.x2;
@@ -479,10 +482,6 @@ int decoder_layers_skinny(specdec_ctx* c, Model& m, int B, int T, hipStream_t st
 int decoder_layers_sliced(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, sd::SkSrc* out) {
   const int R = B * T, D = m.d.d_model, F = m.d.d_ffn, H = m.d.n_heads;
   const int Lcap = c->Lcap, Scap = c->Scap;
-  if (!m.skinny_ready) {
-    HIPCHK(c, sd::skinny_init(D));
-    m.skinny_ready = true;
-  }
   float* S[2] = {m.x, m.x2};
   float* P[2] = {m.skp, m.skp + (size_t)sd::kSk2MaxParts * 32 * D};
   const size_t pstride = (size_t)32 * D;
@@ -752,6 +751,18 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
       o.w1 = quant(L.w1, F, D); o.w2 = quant(L.w2, D, F);
     }
     m.embed8 = quant(m.embed, d->vocab, D);
+    float* f = m.fold8;
+    auto vec2 = [&](int n) { sd::LnFold o{f, f + n}; f += 2 * n; return o; };
+    m.folds8 = m.folds;
+    for (int l = 0; l < d->dec_layers; ++l) {
+      const DecLayer& L = m.dec[l];
+      LnFolds& o = m.folds8[l];
+      o.qkv = vec2(3 * D); o.cq = vec2(D); o.w1 = vec2(F);
+      HIPCHK(c, sd::ln_fold8(S(stream), m.dec8[l].wqkv, l > 0 ? m.dec[l - 1].ln3g : nullptr, l > 0 ? m.dec[l - 1].ln3b : nullptr,
+                             L.bqkv, 3 * D, D, o.qkv));
+      HIPCHK(c, sd::ln_fold8(S(stream), m.dec8[l].cwq, L.ln1g, L.ln1b, L.cbq, D, D, o.cq));
+      HIPCHK(c, sd::ln_fold8(S(stream), m.dec8[l].w1, L.ln2g, L.ln2b, L.b1, F, D, o.w1));
+    }
     if (rcq != SPECDEC_OK) return fail(c, rcq, "FP8 weight quantisation failed: %s", hipGetErrorString(hipGetLastError()));
   }
   {
@@ -1005,7 +1016,11 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   if (c->uncached_ub[0] > 0 && !c->trusted[0]) return fail(c, SPECDEC_ERR_BAD_STATE, "verifier cache does not cover the stream: call specdec_prefill or specdec_load_cache");
   hipStream_t st = S(stream);
   const int B = c->B, T = k + 1, R = B * T;
-  const bool small = skinny_ok(c, m, R, T);   // the small-batch kernels embed the rows themselves
+  const bool small = skinny_ok(c, m, R, T);
+  // The fused small-batch decoder kernels, whose every block redoes what precedes its product and which embed the rows
+  // themselves, where that is little: one sequence of few rows, d = 512 (3 rows 184 against 205 us, 11: 210 / 214, 16: 220 /
+  // 218; two sequences of 6 235 / 214; d = 1024: 6 rows 285 / 268, 26 521 / 302).  Otherwise the general ones.
+  const bool fused = small && (c->no_ln_fold || c->sliced || (B == 1 && R <= 12 && m.d.d_model <= 512));
   VerifyScratch vs{m.part, m.zd, m.row_stats};
   if (ext) {
     const size_t tiles = small ? (m.d.vocab + 63) / 64 : (m.d.vocab + sd::vocab_tile_cols(R) - 1) / sd::vocab_tile_cols(R);
@@ -1014,7 +1029,11 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
                   "(%zu rows, %zu floats of records)", R, tiles, kStaticRows, kStaticPartFloats);
     vs = *ext;
   }
-  if (small)
+  if (small && !m.skinny_ready) {
+    HIPCHK(c, sd::skinny_init(m.d.d_model));
+    m.skinny_ready = true;
+  }
+  if (fused)
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_verify(st, c->st, m.rm, draft, B, k, m.d.vocab));
   else
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_verify(st, c->st, m.rm, draft, B, k, m.d.vocab, m.embed, m.pe, m.x, m.xb,
@@ -1023,7 +1042,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   int n_tiles = (m.d.vocab + 63) / 64;   // per-row partial records of the vocabulary kernel that ran
   if (small && (m.fp8 || m.kv8) && (c->resident || c->sliced))
     return fail(c, SPECDEC_ERR_BAD_STATE, "a model bound with FP8 weights or FP8 cross keys/values runs small passes on the default kernels only");
-  if (small && c->resident) {
+  if (fused && c->resident && !c->sliced) {
     sd::RsArgs a{};
     a.R = R; a.T = T; a.B = B; a.H = m.d.n_heads; a.V = m.d.vocab; a.Lcap = c->Lcap; a.Scap = c->Scap;
     a.n_layers = m.d.dec_layers; a.layers = m.rs_layers;
@@ -1041,7 +1060,10 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     c->fin_x = nullptr;   // (the resident kernel keeps its last sum to itself)
   } else if (small) {
     sd::SkSrc fin{};
-    if (c->sliced && sd::sk2_supported(m.d.d_model, m.d.d_ffn) && m.d.n_heads <= sd::kSk2MaxParts)
+    if (!fused) {
+      rc = decoder_layers(c, m, B, T, st, true, 0, false, false, true);
+      fin = sd::SkSrc{2, m.x, m.dec.back().ln3g, m.dec.back().ln3b, nullptr, nullptr, nullptr, nullptr};
+    } else if (c->sliced && sd::sk2_supported(m.d.d_model, m.d.d_ffn) && m.d.n_heads <= sd::kSk2MaxParts)
       rc = decoder_layers_sliced(c, m, B, T, st, &fin);
     else
       rc = decoder_layers_skinny(c, m, B, T, st, &fin);

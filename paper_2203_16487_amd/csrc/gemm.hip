@@ -635,11 +635,12 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16*
     st[i] = *reinterpret_cast<const f32x2*>(rowstat + 2 * r);
   }
   // blocks of 32 rows x 32 columns in column-major order; the next one's reads are requested before this one's stores
-  f32x4 pre[2][4];
+  f32x4 pre[3][4];
   auto fetch = [&](int j, int i, f32x4 (&p)[4]) {
     epi.tile_fetch(min(m0 + wm + i * 32 + lrow, M - 1), min(n0 + wn + j * 32, N - 32) + 4 * half, p);
   };
   fetch(0, 0, pre[0]);
+  fetch(0, 1, pre[1]);
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int nb = n0 + wn + j * 32;
@@ -651,8 +652,8 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16*
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int m = m0 + wm + i * 32 + lrow, step = j * TM + i;
-      if (step + 1 < TM * TN) fetch(i + 1 < TM ? j : j + 1, i + 1 < TM ? i + 1 : 0, pre[(step + 1) & 1]);
-      epi.tile_block(m, nb, half, m < M && nb < N, acc.c[i][j], cv, pre[step & 1], st[i][0], st[i][1], tr[i]);
+      if (step + 2 < TM * TN) fetch((step + 2) / TM, (step + 2) % TM, pre[(step + 2) % 3]);
+      epi.tile_block(m, nb, half, m < M && nb < N, acc.c[i][j], cv, pre[step % 3], st[i][0], st[i][1], tr[i]);
     }
   }
 #pragma unroll
@@ -676,15 +677,21 @@ static hipError_t launch_tile(hipStream_t st, const bf16* A, int lda, const bf16
 }
 
 // 256 x 256 tiles or 128 x 128 ones?  Time of a full round of blocks (256 and 512) as measured over K = 512 .. 4096, us:
-// 9.6 + 1.73 and 3.6 + 1.12 per 64 columns of K; a last round costs nearly a full one on one block per CU, and on two the
-// better part of one as soon as some CU has a second block.
-static bool square_tiles(int M, int N, int K) {
+// 10.5 + 1.73 and 3.6 + 1.12 per 64 columns of K; a last round costs nearly a full one on one block per CU, and on two the
+// better part of one as soon as some CU has a second block.  Where M only bounds the rows in use (bound), the sum over half,
+// three quarters and all of it decides.
+static float square_minus_wide(int M, int N, int K) {
   const float kt = K / 64.f;
   const long sq = (long)((M + 255) / 256) * ((N + 255) / 256), wd = (long)((M + 127) / 128) * ((N + 127) / 128);
-  const float t_sq = (float)((sq + 255) / 256) * (sq < 256 ? 0.8f : 1.f) * (9.6f + 1.73f * kt);
+  const float t_sq = (float)((sq + 255) / 256) * (sq < 256 ? 0.8f : 1.f) * (10.5f + 1.73f * kt);
   const long rem = wd % 512;
   const float t_wd = ((float)(wd / 512) + (rem == 0 ? 0.f : rem <= 256 ? 0.6f : 1.f)) * (3.6f + 1.12f * kt);
-  return t_sq < t_wd;
+  return t_sq - t_wd;
+}
+static bool square_tiles(int M, int N, int K, bool bound) {
+  float t = square_minus_wide(M, N, K);
+  if (bound) t += square_minus_wide(M / 2, N, K) + square_minus_wide((int)(M * 3L / 4), N, K);
+  return t < 0.f;
 }
 
 // ----------------------------------------------------------------------------- cross-attention keys / values
@@ -784,7 +791,7 @@ hipError_t gemm_cross_kv(hipStream_t st, const bf16* A, const CrossKvArgs& a, in
   if (M <= 0 || a.layers <= 0) return hipSuccess;
   const long wide = (long)((M + 127) / 128) * ((2 * d + 127) / 128) * a.layers;
   if (wide < 200) return launch_cross_kv<CfgSmall>(st, A, a, M, d, m_real);
-  if (wide >= 512 && square_tiles(M, 2 * d * a.layers, d)) return launch_cross_kv<CfgSquare>(st, A, a, M, d, m_real);
+  if (wide >= 512 && square_tiles(M, 2 * d * a.layers, d, m_real != nullptr)) return launch_cross_kv<CfgSquare>(st, A, a, M, d, m_real);
   return launch_cross_kv<CfgWide>(st, A, a, M, d, m_real);
 }
 
@@ -795,6 +802,8 @@ hipError_t gemm_cross_kv(hipStream_t st, const bf16* A, const CrossKvArgs& a, in
 // global -> LDS) and multiplies it without ever meeting the other waves, so that a block keeps all of its LDS in
 // flight and no wave waits for another's requests.  The NW partial tiles are summed through LDS in wave order
 // (bit-reproducible); LPR neighbouring lanes finish one row, V columns each, and reduce its LayerNorm statistics.
+// W8: W holds E4M3 codes, one byte each, with a scale per output column (applied to the finished sum): a slab of a W row is 64
+// bytes, and a fragment becomes a bf16 operand in registers.
 template <int BM, int BN, int NW, int STAGES>
 struct KsplitCfg {
   static constexpr int kBM = BM, kBN = BN, kWaves = NW, kThreads = 64 * NW, kStages = STAGES;
@@ -813,13 +822,16 @@ struct KsplitCfg {
   __device__ __forceinline__ static int red_off(int r, int c) { return r * BN + ((((c >> 2) ^ r) & (BN / 4 - 1)) << 2) + (c & 3); }
 };
 
-template <class Cfg, class Epi>
+template <class Cfg, class Epi, bool W8>
 __global__ __launch_bounds__(Cfg::kThreads) void gemm_ksplit_kernel(const bf16* __restrict__ A, int lda,
-                                                                    const bf16* __restrict__ W, int ldw, int M, int N,
+                                                                    const void* __restrict__ Wv, int ldw, int M, int N,
                                                                     int K, int MT, int NT, Epi epi,
-                                                                    const int* __restrict__ m_real) {
+                                                                    const int* __restrict__ m_real,
+                                                                    const float* __restrict__ wscale) {
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
-  constexpr int BM = Cfg::kBM, BN = Cfg::kBN, NW = Cfg::kWaves, S = Cfg::kStages, IPW = Cfg::kIPW;
+  // (offsets into W are in bf16 units throughout: half as many for codes)
+  const bf16* __restrict__ W = static_cast<const bf16*>(Wv);
+  constexpr int BM = Cfg::kBM, BN = Cfg::kBN, NW = Cfg::kWaves, S = Cfg::kStages, IPW = W8 ? BM / 8 + BN / 16 : Cfg::kIPW;
   constexpr int FA = BM / 16, FB = BN / 16, V = Cfg::kV, LPR = Cfg::kLPR, ITER = Cfg::kIter, RPP = Cfg::kRowsPerPass;
   float* rowstat = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Cfg::kRingBytes);   // [BM][2]
   int mt, nt;
@@ -834,15 +846,21 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ksplit_kernel(const bf16* 
   unsigned voff[IPW];
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {
+    if (W8 && i * 8 >= BM) {   // 16 rows of 64 codes
+      const int row = (i - BM / 8) * 16 + (lane >> 2), chunk = (lane & 3) ^ ((row >> 2) & 3);
+      voff[i] = (unsigned)min(row, N - 1 - n0) * (unsigned)ldw + chunk * 16;
+      continue;
+    }
     const int row = i * 8 + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
     voff[i] = i * 8 < BM ? (unsigned)min(row, M - 1 - m0) * (unsigned)(lda * 2) + chunk * 16
                          : (unsigned)min(row - BM, N - 1 - n0) * (unsigned)(ldw * 2) + chunk * 16;
   }
-  const bf16 *abase = A + (size_t)m0 * lda + wave * 64, *wbase = W + (size_t)n0 * ldw + wave * 64;
+  constexpr int WS = W8 ? 32 : 64;   // a slab of a W row
+  const bf16 *abase = A + (size_t)m0 * lda + wave * 64, *wbase = W + (size_t)n0 * ldw / (64 / WS) + wave * WS;
   const bf16* ring = smem + wave * (S * Cfg::kStageElems);
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)SD_LDS_PTR(const_cast<bf16*>(ring)));
   auto request = [&](int t, int slot) {
-    const bf16 *as = abase + t * (NW * 64), *ws = wbase + t * (NW * 64);
+    const bf16 *as = abase + t * (NW * 64), *ws = wbase + t * (NW * WS);
     const unsigned l = lds0 + slot * (Cfg::kStageElems * 2);
 #pragma unroll
     for (int i = 0; i < IPW; ++i) dma16(i * 8 < BM ? as : ws, voff[i], l + i * 1024);
@@ -870,6 +888,8 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ksplit_kernel(const bf16* 
   float cv[Epi::kVec][V];
 #pragma unroll
   for (int i = 0; i < Epi::kVec; ++i) load_cols<V>(epi.vec(i) + nc, cv[i]);
+  float wsc[V];
+  if constexpr (W8) load_cols<V>(wscale + nc, wsc);
   __builtin_amdgcn_sched_barrier(0);
   f32x4 acc[FA][FB];
 #pragma unroll
@@ -885,7 +905,12 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ksplit_kernel(const bf16* 
 #pragma unroll
     for (int ss = 0; ss < 2; ++ss) {
 #pragma unroll
-      for (int j = 0; j < FB; ++j) fb[ss][j] = *reinterpret_cast<const bf16x8*>(st + lds_off<64>(BM + j * 16 + lq, ss * 4 + g));
+      for (int j = 0; j < FB; ++j) {
+        if constexpr (W8)
+          fb[ss][j] = e4m3x8_to_bf16(*reinterpret_cast<const fp8x8*>(st + BM * 64 + lds_off<32>(j * 16 + lq, ss * 2 + (g >> 1)) + (g & 1) * 4));
+        else
+          fb[ss][j] = *reinterpret_cast<const bf16x8*>(st + lds_off<64>(BM + j * 16 + lq, ss * 4 + g));
+      }
 #pragma unroll
       for (int i = 0; i < FA; ++i) fa[ss][i] = *reinterpret_cast<const bf16x8*>(st + lds_off<64>(i * 16 + lq, ss * 4 + g));
     }
@@ -933,29 +958,38 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ksplit_kernel(const bf16* 
 #pragma unroll
       for (int e = 0; e < V; ++e) v[e] += t[e];
     }
+    if constexpr (W8) {
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[e] *= wsc[e];
+    }
     const f32x2 rs = *reinterpret_cast<const f32x2*>(rowstat + 2 * r);
     epi.template store<V, BN>(m, n, m < M && n < N, v, pre[it], rs[0], rs[1], cv);
   }
 }
 
-template <class Cfg, class Epi>
-static hipError_t launch_ksplit(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K,
-                                const Epi& epi, const int* m_real) {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ksplit_kernel<Cfg, Epi>),
+template <class Cfg, class Epi, bool W8 = false>
+static hipError_t launch_ksplit(hipStream_t st, const bf16* A, int lda, const void* W, int M, int N, int K,
+                                const Epi& epi, const int* m_real, const float* wscale = nullptr) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ksplit_kernel<Cfg, Epi, W8>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kSmemBytes);
   if (attr != hipSuccess) return attr;
   const int MT = (M + Cfg::kBM - 1) / Cfg::kBM, NT = (N + Cfg::kBN - 1) / Cfg::kBN;
-  SD_LAUNCH_TIMED((gemm_ksplit_kernel<Cfg, Epi>), dim3(xcd_grid(MT, NT)), dim3(Cfg::kThreads), Cfg::kSmemBytes, st, A, lda,
-                  W, K, M, N, K, MT, NT, epi, m_real);
+  SD_LAUNCH_TIMED((gemm_ksplit_kernel<Cfg, Epi, W8>), dim3(xcd_grid(MT, NT)), dim3(Cfg::kThreads), Cfg::kSmemBytes, st, A, lda,
+                  W, K, M, N, K, MT, NT, epi, m_real, wscale);
   return hipGetLastError();
 }
 
 static bool one_round(int M, int N, int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) <= 256; }
 
 template <class Epi>
-static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K,
+static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeight& w, int M, int N, int K,
                             const Epi& epi, const int* m_real) {
   if (M <= 0 || N <= 0) return hipSuccess;
+  if (w.scale) {   // codes: passes of a few rows only
+    if (!one_round(M, N, 16, 32)) return hipErrorInvalidValue;
+    return launch_ksplit<KsplitCfg<16, 32, 8, 3>, Epi, true>(st, A, lda, w.p, M, N, K, epi, m_real, w.scale);
+  }
+  const bf16* W = static_cast<const bf16*>(w.p);
   // K split inside the block wherever its tiles give every CU at most one block (a second round costs more than it
   // saves): the smallest tile that does.  Chained launches, 64 x 64 ring -> K split, us: N = K = 512, M = 77: 5.6 -> 3.3;
   // N = 1024, M = 128: K = 1024 7.7 -> 3.9, K = 4096 19.0 -> 7.2; M = 352: K = 1024 8.0 -> 5.4, K = 4096 19.6 -> 11.0;
@@ -971,7 +1005,7 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const bf16* 
   }
   const long wide_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
   if (wide_tiles >= 512) {   // two blocks of 128 x 128 for every CU, or larger tiles still
-    if (square_tiles(M, N, K)) return launch_tile<CfgSquare>(st, A, lda, W, M, N, K, epi, m_real);
+    if (square_tiles(M, N, K, m_real != nullptr)) return launch_tile<CfgSquare>(st, A, lda, W, M, N, K, epi, m_real);
     return launch_tile<CfgWide>(st, A, lda, W, M, N, K, epi, m_real);
   }
   // the widest outputs (QKV and FFN1 of the big model) run on 256x128 tiles, eight waves, three-deep
@@ -984,19 +1018,19 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const bf16* 
 }
 
 int ln_sum_chunks(int M, int d) { return one_round(M, d, 32, 32) ? d / 32 : d / 64; }
-hipError_t gemm_ln_sum(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int d, int K,
+hipError_t gemm_ln_sum(hipStream_t st, const bf16* A, int lda, const SkWeight& W, int M, int d, int K,
                        const float* vecs, LnPairs ln_in, float* x, bf16* xg, float* ln_out, const int* m_real) {
   return launch_ln(st, A, lda, W, M, d, K,
                    EpiLnSum{vecs, reinterpret_cast<const f32x2*>(ln_in.p), reinterpret_cast<f32x2*>(ln_out), x, xg, d,
                             ln_in.chunks > 0 ? ln_in.chunks : d / 64, ln_in.chunks > 0}, m_real);
 }
-hipError_t gemm_ln_bf16(hipStream_t st, const bf16* A, const bf16* W, int M, int N, int d, const LnFold& f,
+hipError_t gemm_ln_bf16(hipStream_t st, const bf16* A, const SkWeight& W, int M, int N, int d, const LnFold& f,
                         LnPairs ln_in, bf16* out, int ldo, bool relu, const int* m_real) {
   return launch_ln(st, A, d, W, M, N, d,
                    EpiLnBf16{f.cs, f.bf, reinterpret_cast<const f32x2*>(ln_in.p), out, ldo, d,
                              ln_in.chunks > 0 ? ln_in.chunks : d / 64, relu ? 1 : 0, ln_in.chunks > 0}, m_real);
 }
-hipError_t gemm_ln_qkv_append(hipStream_t st, const bf16* A, const bf16* W, int M, int d, const LnFold& f,
+hipError_t gemm_ln_qkv_append(hipStream_t st, const bf16* A, const SkWeight& W, int M, int d, const LnFold& f,
                               LnPairs ln_in, bf16* q_out, bf16* kc, bf16* vc, const int* row_b,
                               const int* row_pos, int H, int Lcap, const int* m_real) {
   return launch_ln(st, A, d, W, M, 3 * d, d,
@@ -1030,6 +1064,34 @@ hipError_t ln_fold(hipStream_t st, const bf16* W, const bf16* g, const bf16* bet
                    const LnFold& out) {
   hipLaunchKernelGGL(ln_fold_kernel, dim3((N + 3) / 4), dim3(256), 0, st, W, g, beta, b, N, K,
                      const_cast<float*>(out.cs), const_cast<float*>(out.bf));
+  return hipGetLastError();
+}
+
+// The same for a matrix stored as codes: value = scale[n] * decode(code[n][k]).
+__global__ __launch_bounds__(256) void ln_fold8_kernel(const fp8* __restrict__ W, const float* __restrict__ scale,
+                                                       const bf16* __restrict__ g, const bf16* __restrict__ beta,
+                                                       const bf16* __restrict__ b, int N, int K, float* __restrict__ cs,
+                                                       float* __restrict__ bf) {
+  const int n = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (n >= N) return;
+  float s = 0.f, t = 0.f;
+  if (g)
+    for (int k = lane * 8; k < K; k += 512) {
+      const bf16x8 w = e4m3x8_to_bf16(*reinterpret_cast<const fp8x8*>(W + (size_t)n * K + k));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        s += (float)g[k + i] * (float)w[i];
+        t += (float)beta[k + i] * (float)w[i];
+      }
+    }
+  s = wave_sum(s) * scale[n];
+  t = wave_sum(t) * scale[n];
+  if (lane == 0) { cs[n] = s; bf[n] = (float)b[n] + t; }
+}
+hipError_t ln_fold8(hipStream_t st, const SkWeight& W, const bf16* g, const bf16* beta, const bf16* b, int N, int K,
+                    const LnFold& out) {
+  hipLaunchKernelGGL(ln_fold8_kernel, dim3((N + 3) / 4), dim3(256), 0, st, static_cast<const fp8*>(W.p), W.scale, g, beta, b, N,
+                     K, const_cast<float*>(out.cs), const_cast<float*>(out.bf));
   return hipGetLastError();
 }
 

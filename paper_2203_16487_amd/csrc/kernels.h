@@ -26,6 +26,16 @@ struct RowMap {
   int* row_start;   // [B + 1]
 };
 
+// A weight matrix [N][K] row-major: bf16 values (scale == nullptr), or FP8 E4M3 codes (one byte each)
+// with one fp32 scale per row, value = scale[n] * decode(code[n][k]).
+struct SkWeight {
+  const void* p = nullptr;
+  const float* scale = nullptr;
+  SkWeight() {}
+  SkWeight(const bf16* w) : p(w) {}
+  SkWeight(const unsigned char* codes, const float* s) : p(codes), scale(s) {}
+};
+
 // ---- gemm.hip: C = A W^T (+bias) with different epilogues; A [M,K] bf16, W [N,K] bf16 ----
 // m_real (device, nullable, here and below): number of leading rows that hold data; row tiles at or beyond it
 // are skipped, rows beyond it neither read nor stored (M stays the upper bound the grid is sized for).
@@ -77,6 +87,9 @@ struct LnFold {          // per consuming weight matrix W [N,d] with bias b, for
 // (g, beta null: no LayerNorm in front of W, cs = 0 and bf = b)
 hipError_t ln_fold(hipStream_t st, const bf16* W, const bf16* g, const bf16* beta, const bf16* b, int N, int K,
                    const LnFold& out);
+// (W as codes + scales)
+hipError_t ln_fold8(hipStream_t st, const SkWeight& W, const bf16* g, const bf16* beta, const bf16* b, int N, int K,
+                    const LnFold& out);
 // The column vectors of one producing GEMM, fp32 [3][d] in one piece: gain of the LayerNorm
 // pending on the residual (1 when g_prev is null), its shift (0 when null) + the GEMM's bias,
 // gain of the LayerNorm that follows.
@@ -94,15 +107,16 @@ int ln_sum_chunks(int M, int d);   // of what gemm_ln_sum writes for M rows
 // m_real (all three; device, nullable): number of leading rows that hold data; row tiles at or
 // beyond it are skipped and rows beyond it are neither computed on nor stored (M stays the
 // upper bound the grid is sized for).
-hipError_t gemm_ln_sum(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int d, int K,
+// W as codes (all three): at most 32 rows.
+hipError_t gemm_ln_sum(hipStream_t st, const bf16* A, int lda, const SkWeight& W, int M, int d, int K,
                        const float* vecs, LnPairs ln_in, float* x, bf16* xg, float* ln_out,
                        const int* m_real = nullptr);
 // out bf16 [M,ldo] = act(LN(y) W^T + b) from A = bf16(y * g) [M,d] and the chunk pairs of y; without a pending
 // LayerNorm act(A W^T + b) with f = {0, b}
-hipError_t gemm_ln_bf16(hipStream_t st, const bf16* A, const bf16* W, int M, int N, int d, const LnFold& f,
+hipError_t gemm_ln_bf16(hipStream_t st, const bf16* A, const SkWeight& W, int M, int N, int d, const LnFold& f,
                         LnPairs ln_in, bf16* out, int ldo, bool relu, const int* m_real = nullptr);
 // gemm_qkv_append on the same
-hipError_t gemm_ln_qkv_append(hipStream_t st, const bf16* A, const bf16* W, int M, int d, const LnFold& f,
+hipError_t gemm_ln_qkv_append(hipStream_t st, const bf16* A, const SkWeight& W, int M, int d, const LnFold& f,
                               LnPairs ln_in, bf16* q_out, bf16* kc, bf16* vc, const int* row_b,
                               const int* row_pos, int H, int Lcap, const int* m_real = nullptr);
 
@@ -196,15 +210,6 @@ struct SkSrc {
   float* xs_out = nullptr;
 };
 bool skinny_supported(int d, int F);
-// A weight matrix [N][K] row-major: bf16 values (scale == nullptr), or FP8 E4M3 codes (one byte each)
-// with one fp32 scale per row, value = scale[n] * decode(code[n][k]).
-struct SkWeight {
-  const void* p = nullptr;
-  const float* scale = nullptr;
-  SkWeight() {}
-  SkWeight(const bf16* w) : p(w) {}
-  SkWeight(const unsigned char* codes, const float* s) : p(codes), scale(s) {}
-};
 // codes, scale <- per-row E4M3 quantisation of w [N][K]: scale = max|row| / 448 (1 for a zero row),
 // code = nearest-even E4M3 of w / scale.  K % 8 == 0.
 hipError_t quantize_rows_e4m3(hipStream_t st, const bf16* w, int N, int K, unsigned char* codes, float* scale);
