@@ -74,7 +74,9 @@ typedef enum {
                                           kernels where they are the faster ones (one sequence of at most 12 rows,
                                           d_model <= 512), else the general ones; the small-batch vocabulary kernel   */
   SPECDEC_OPT_LN_FOLD = 1,             /* default 1: decoder LayerNorms folded into the projections around them  */
-  SPECDEC_OPT_RESIDENT = 2,            /* default 0.  1: where the fused decoder kernels would run, ONE resident kernel */
+  SPECDEC_OPT_RESIDENT = 2,            /* the decoder layers of a pass of few rows run as ONE kernel wherever that kernel
+                                          applies (d_model 512 / 1024), whether this is set or not; setting it refuses
+                                          models bound with FP8 storage in passes of at most 32 rows                  */
   SPECDEC_OPT_SLICED_SUBLAYERS = 3,    /* default 0: the small-batch kernels own sub-layers by output column (six
                                           kernels per layer); 1: by head / FFN slice (three per layer; measured
                                           slower: 8-16 workgroups cannot pull a layer's weights fast enough)      */

@@ -2,11 +2,19 @@
 // of every entry point declared in include/specdec.h.
 #include <hip/hip_runtime.h>
 
+#include <sys/socket.h>
+#include <sys/un.h>
+#include <unistd.h>
+
+#include <atomic>
+#include <cerrno>
 #include <cmath>
 #include <cstdarg>
+#include <cstddef>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -70,10 +78,10 @@ struct Model {
   sd::SkWeight embed8;
   float* hx = nullptr;       // [Bmax*k_max][d] head-based drafting: the hidden state each head adds to, then its output
   bool skinny_ready = false;
-  sd::RsLayer* rs_layers = nullptr;   // device copy of the decoder layers' pointers (resident kernel)
-  unsigned* rs_bar = nullptr;         // barrier counters + error flag of the resident kernel
-  int rs_parity = 0;
-  int rs_seq = 0;
+  sd::PlLayer* pl_layers = nullptr;   // device copy of the decoder layers' pointers (one-kernel decoder, persist.hip)
+  int* pl_err = nullptr;              // its error flag
+  char* pl_exch = nullptr;            // its exchange buffers (null: dimensions it does not support)
+  int pl_rows = 0;                    // rows they are sized for
   bf16* xb = nullptr;        // [Rpass][d]
   float* lnp[2] = {nullptr, nullptr};   // [rows][d/32 at most][2] chunk pairs of the two latest residual sums
   float* fold = nullptr;     // per decoder layer: cs and bf vectors of wqkv, cwq, w1 (LayerNorm folded)
@@ -129,6 +137,7 @@ struct specdec_ctx {
   bool no_skinny = false;   // SPECDEC_OPT_SMALL_BATCH_KERNELS = 0: always take the general kernels
   bool no_ln_fold = false;  // SPECDEC_OPT_LN_FOLD = 0: LayerNorm as a pass of its own between the GEMMs
   bool resident = false;    // SPECDEC_OPT_RESIDENT = 1: small batches run the decoder pass as one resident kernel
+  int persist_dev = -1;     // GPU on which this context is among the users of the one-kernel decoder
   bool sliced = false;      // SPECDEC_OPT_SLICED_SUBLAYERS = 1: small-batch sub-layers owned by head / FFN slice
   bool fp8 = false;         // SPECDEC_OPT_FP8_WEIGHTS = 1: models bound from now on keep E4M3 copies for small batches
   bool fp8_kv = false;      // SPECDEC_OPT_FP8_CROSS_KV = 1: models bound from now on keep E4M3 cross keys / values
@@ -191,6 +200,9 @@ bool desc_ok(const specdec_model_desc* d) {
          d->mask_id >= 0 && d->mask_id < d->vocab;
 }
 constexpr long kPrefillRows = 8192;
+// Most rows of a pass the one-kernel decoder is asked for: with more, launches cost less than what its workgroups, that see
+// 16 rows each, read more (d = 512: 121 rows 171 against 231 us; d = 1024: 44 rows 231 / 292, 77 323 / 313).
+constexpr size_t persist_rows(int d) { return d <= 512 ? 128 : 64; }
 constexpr int kEncT = 12, kDecT = 20;
 int n_weights(const specdec_model_desc* d) { return 1 + kEncT * d->enc_layers + kDecT * d->dec_layers; }
 
@@ -274,10 +286,10 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     t.xks = cv.take<float>(t.xkv_layer / 64 * d->dec_layers);
     t.xvs = cv.take<float>(t.xkv_layer / 64 * d->dec_layers);
   }
+  t.fold8 = cv.take<float>((size_t)d->dec_layers * 2 * (4 * D + F));   // (in every workspace: FP8 adds codes and scales alone)
   if (c->fp8) {
     t.w8 = cv.take<unsigned char>((size_t)d->dec_layers * (6 * D * D + 2 * D * F) + (size_t)d->vocab * D);
     t.w8s = cv.take<float>((size_t)d->dec_layers * (7 * D + F) + (size_t)d->vocab);
-    t.fold8 = cv.take<float>((size_t)d->dec_layers * 2 * (4 * D + F));
   }
   t.xb = cv.take<bf16>(Rpass * D);
   t.lnp[0] = cv.take<float>(Rpass * (D / 32) * 2);
@@ -298,8 +310,13 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   t.rm.row_start = cv.take<int>(Bm + 1);
   t.slots = cv.take<bf16>(Bm * (size_t)c->lim.k_max * D);
   t.new_rows = cv.take<int>(Bm);
-  t.rs_layers = cv.take<sd::RsLayer>(d->dec_layers);
-  t.rs_bar = cv.take<unsigned>(sd::kRsBarWords);
+  t.pl_err = cv.take<int>(64);
+  t.pl_layers = cv.take<sd::PlLayer>((size_t)d->dec_layers * (c->fp8 ? 2 : 1));
+  if (sd::persist_supported(d->dec_layers, (int)D, (int)F)) {
+    const size_t most = Bm * (c->lim.k_max + 1);
+    t.pl_rows = (int)(most < persist_rows((int)D) ? most : persist_rows((int)D));
+    t.pl_exch = cv.take<char>(sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F));
+  }
   if (d->enc_layers > 0) {
     const size_t Re = Bm * (size_t)c->Scap;
     t.ex = cv.take<float>(Re * D);
@@ -321,7 +338,8 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     m->lnp[0] = t.lnp[0]; m->lnp[1] = t.lnp[1]; m->fold = t.fold;
     m->x = t.x; m->x2 = t.x2; m->skp = t.skp; m->hx = t.hx; m->w8 = t.w8; m->w8s = t.w8s; m->fold8 = t.fold8; m->xk8 = t.xk8; m->xv8 = t.xv8; m->xks = t.xks; m->xvs = t.xvs; m->xb = t.xb; m->q = t.q; m->att = t.att; m->hid = t.hid;
     m->part = t.part; m->row_stats = t.row_stats; m->zd = t.zd; m->rm = t.rm;
-    m->slots = t.slots; m->new_rows = t.new_rows; m->rs_layers = t.rs_layers; m->rs_bar = t.rs_bar;
+    m->slots = t.slots; m->new_rows = t.new_rows; m->pl_err = t.pl_err;
+    m->pl_layers = t.pl_layers; m->pl_exch = t.pl_exch; m->pl_rows = t.pl_rows;
     m->ex = t.ex; m->exb = t.exb; m->eqkv = t.eqkv; m->eatt = t.eatt; m->ehid = t.ehid;
     m->elnp[0] = t.elnp[0]; m->elnp[1] = t.elnp[1]; m->efold = t.efold; m->epos = t.epos; m->erow_b = t.erow_b; m->erow_start = t.erow_start; m->en_rows = t.en_rows;
   }
@@ -534,6 +552,93 @@ int decoder_layers_sliced(specdec_ctx* c, Model& m, int B, int T, hipStream_t st
   return SPECDEC_OK;
 }
 
+// The one-kernel decoder keeps its workgroups waiting for each other, so no two such passes may share a GPU's compute units
+// half-started.  Contexts whose passes go to one stream take turns there; the first to ask names the stream, and while it
+// lives, a pass of another context on another stream takes the kernel-per-stage path.  A captured pass may be replayed on any
+// stream, so a context that captures one is alone with its GPU until it is destroyed (or, where it is not alone, captures the
+// kernel-per-stage path).  Among processes the user is the one that could bind a socket named after the GPU's PCI address,
+// which the system gives back when the process ends, however it ends.
+constexpr int kMaxDevices = 64;
+struct PersistGpu {
+  hipStream_t stream = nullptr;
+  int users = 0;             // contexts
+  bool captured = false;     // by the only one
+  int lock = -1, cus = 0;
+};
+PersistGpu persist_gpu[kMaxDevices];
+std::mutex persist_mutex;
+
+bool persist_open(PersistGpu& o, int dev) {
+  sockaddr_un name{};
+  name.sun_family = AF_UNIX;
+  char bus[32];
+  if (hipDeviceGetAttribute(&o.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipDeviceGetPCIBusId(bus, sizeof bus, dev) != hipSuccess)
+    return false;
+  const int n = snprintf(name.sun_path + 1, sizeof name.sun_path - 1, "specdec-%s", bus);
+  const int fd = socket(AF_UNIX, SOCK_DGRAM | SOCK_CLOEXEC, 0);
+  if (fd >= 0 && bind(fd, reinterpret_cast<sockaddr*>(&name), (socklen_t)(offsetof(sockaddr_un, sun_path) + 1 + n)) != 0 &&
+      errno == EADDRINUSE) {
+    close(fd);
+    return false;
+  }
+  o.lock = fd;
+  return true;
+}
+void persist_release(specdec_ctx* c) {
+  if (c->persist_dev < 0) return;
+  std::lock_guard<std::mutex> guard(persist_mutex);
+  PersistGpu& o = persist_gpu[c->persist_dev];
+  if (--o.users) return;
+  o.captured = false;
+  if (o.lock >= 0) close(o.lock);
+  o.lock = -1;
+}
+
+bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
+  const int R = B * T;
+  if (!m.pl_exch || R > m.pl_rows || T > 32 || c->no_skinny || c->no_ln_fold || c->sliced) return false;
+  sd::PlArgs a{};
+  a.R = R; a.T = T; a.B = B; a.H = m.d.n_heads;
+  const int blocks = sd::persist_plan(a, m.d.d_model, m.d.d_ffn);
+  int dev = -1;
+  if (blocks < 1 || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+  if (c->persist_dev >= 0 && c->persist_dev != dev) return false;
+  bool capturing = false;
+  if (st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) return false;
+    capturing = status != hipStreamCaptureStatusNone;
+  }
+  std::lock_guard<std::mutex> guard(persist_mutex);
+  PersistGpu& o = persist_gpu[dev];
+  const bool user = c->persist_dev == dev;
+  if (o.users > (user ? 1 : 0) && (o.captured || capturing || st != o.stream || st == hipStreamPerThread)) return false;
+  if (!o.users && !persist_open(o, dev)) return false;
+  if (!user) {
+    ++o.users;
+    c->persist_dev = dev;
+  }
+  o.stream = st;
+  o.captured |= capturing;
+  return o.cus >= blocks;
+}
+
+// few: as in decoder_layers (the E4M3 copies of the weights, if the model has them)
+int decoder_layers_persist(specdec_ctx* c, Model& m, int B, int T, bool few, hipStream_t st) {
+  sd::PlArgs a{};
+  a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads; a.Lcap = c->Lcap; a.Scap = c->Scap; a.n_layers = m.d.dec_layers;
+  a.fp8 = few && m.fp8;
+  a.layers = m.pl_layers + (a.fp8 ? m.d.dec_layers : 0);
+  a.row_b = m.rm.row_b; a.row_pos = m.rm.row_pos; a.src_len = c->st.src_len;
+  a.x = m.x; a.xb = m.xb; a.y = m.x;
+  a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
+  if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
+  a.exch = m.pl_exch; a.err = reinterpret_cast<unsigned*>(m.pl_err);
+  LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::persist_decoder(st, a, m.d.d_model, m.d.d_ffn));
+  return SPECDEC_OK;
+}
+
 // memory: [B][S_max][d] padded, or (packed) the model's own packed encoder rows (erow_b / epos / en_rows)
 int cross_kv_from(specdec_ctx* c, Model& m, const bf16* memory, int B, int S_max, hipStream_t st, bool packed) {
   const int D = m.d.d_model;
@@ -593,6 +698,7 @@ int specdec_create(specdec_ctx** out, const specdec_limits* lim) {
 void specdec_destroy(specdec_ctx* c) {
   if (!c) return;
   for (hipEvent_t e : c->prof_ev) (void)hipEventDestroy(e);
+  persist_release(c);
   delete c;
 }
 
@@ -766,15 +872,19 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
     if (rcq != SPECDEC_OK) return fail(c, rcq, "FP8 weight quantisation failed: %s", hipGetErrorString(hipGetLastError()));
   }
   {
-    std::vector<sd::RsLayer> rl(d->dec_layers);
-    for (int l = 0; l < d->dec_layers; ++l) {
-      const DecLayer& L = m.dec[l];
-      rl[l] = sd::RsLayer{L.wqkv, L.bqkv, L.wo, L.bo, L.ln1g, L.ln1b, L.cwq, L.cbq, L.cwo, L.cbo, L.ln2g, L.ln2b,
-                          L.w1, L.b1, L.w2, L.b2, L.ln3g, L.ln3b};
-    }
-    HIPCHK(c, hipMemcpy(m.rs_layers, rl.data(), rl.size() * sizeof(sd::RsLayer), hipMemcpyHostToDevice));
-    HIPCHK(c, sd::fill_i32(S(stream), reinterpret_cast<int*>(m.rs_bar), 0, sd::kRsBarWords));
-    m.rs_parity = 0;
+    HIPCHK(c, sd::fill_i32(S(stream), m.pl_err, 0, 1));
+    // for the one-kernel decoder: the bf16 matrices, then (FP8 weights) their codes
+    std::vector<sd::PlLayer> pl;
+    for (int set = 0; set < (m.fp8 ? 2 : 1); ++set)
+      for (int l = 0; l < d->dec_layers; ++l) {
+        const DecLayer& L = m.dec[l];
+        const LnFolds& f = set ? m.folds8[l] : m.folds[l];
+        const Fp8Layer w = set ? m.dec8[l] : Fp8Layer{L.wqkv, L.wo, L.cwq, L.cwo, L.w1, L.w2};
+        auto pw = [](const sd::SkWeight& x) { return sd::PlWeight{x.p, x.scale}; };
+        pl.push_back(sd::PlLayer{pw(w.wqkv), pw(w.wo), pw(w.cwq), pw(w.cwo), pw(w.w1), pw(w.w2), f.qkv.cs, f.qkv.bf, f.cq.cs,
+                                 f.cq.bf, f.w1.cs, f.w1.bf, f.vo, f.vco, f.v2});
+      }
+    HIPCHK(c, hipMemcpy(m.pl_layers, pl.data(), pl.size() * sizeof(sd::PlLayer), hipMemcpyHostToDevice));
   }
   m.bound = true;
   return SPECDEC_OK;
@@ -789,10 +899,7 @@ int specdec_begin(specdec_ctx* c, int32_t B, int32_t max_new, void* stream) {
   const Model& any = c->m[0].bound ? c->m[0] : c->m[1];
   if (max_new > c->lim.max_tgt) max_new = c->lim.max_tgt;   // no stream grows beyond the arena
   HIPCHK(c, sd::begin_state(S(stream), c->st, B, max_new, c->lim.max_tgt, any.d.bos_id));
-  if (c->m[0].bound) {   // a new run clears the resident kernel's counters and error flag
-    HIPCHK(c, sd::fill_i32(S(stream), reinterpret_cast<int*>(c->m[0].rs_bar), 0, sd::kRsBarWords));
-    c->m[0].rs_parity = 0;
-  }
+  if (c->m[0].bound) HIPCHK(c, sd::fill_i32(S(stream), c->m[0].pl_err, 0, 1));   // a new run clears the one-kernel decoder's error flag
   c->B = B;
   c->max_new = max_new;
   c->last_T = 0;
@@ -1000,7 +1107,6 @@ namespace {
 struct VerifyScratch {
   float *part, *zd, *row_stats;
 };
-constexpr int kMaxDevices = 64;
 float* scratch_ptr[kMaxDevices] = {nullptr};                  // device address of `scratch` on each GPU
 
 int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, float tau, int32_t* accept_len,
@@ -1020,7 +1126,8 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   // The fused small-batch decoder kernels, whose every block redoes what precedes its product and which embed the rows
   // themselves, where that is little: one sequence of few rows, d = 512 (3 rows 184 against 205 us, 11: 210 / 214, 16: 220 /
   // 218; two sequences of 6 235 / 214; d = 1024: 6 rows 285 / 268, 26 521 / 302).  Otherwise the general ones.
-  const bool fused = small && (c->no_ln_fold || c->sliced || (B == 1 && R <= 12 && m.d.d_model <= 512));
+  const bool one = persist_ok(c, m, B, T, st);
+  const bool fused = small && !one && (c->no_ln_fold || c->sliced || (B == 1 && R <= 12 && m.d.d_model <= 512));
   VerifyScratch vs{m.part, m.zd, m.row_stats};
   if (ext) {
     const size_t tiles = small ? (m.d.vocab + 63) / 64 : (m.d.vocab + sd::vocab_tile_cols(R) - 1) / sd::vocab_tile_cols(R);
@@ -1037,31 +1144,16 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_verify(st, c->st, m.rm, draft, B, k, m.d.vocab));
   else
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_verify(st, c->st, m.rm, draft, B, k, m.d.vocab, m.embed, m.pe, m.x, m.xb,
-                                        m.d.d_model));
-  const unsigned* failed = nullptr;
+                                        m.d.d_model, one ? m.pl_exch : nullptr,
+                                        one ? sd::persist_exch_bytes(R, m.d.dec_layers, m.d.d_model, m.d.d_ffn) : 0));
+  const unsigned* failed = one ? reinterpret_cast<const unsigned*>(m.pl_err) : nullptr;
   int n_tiles = (m.d.vocab + 63) / 64;   // per-row partial records of the vocabulary kernel that ran
   if (small && (m.fp8 || m.kv8) && (c->resident || c->sliced))
     return fail(c, SPECDEC_ERR_BAD_STATE, "a model bound with FP8 weights or FP8 cross keys/values runs small passes on the default kernels only");
-  if (fused && c->resident && !c->sliced) {
-    sd::RsArgs a{};
-    a.R = R; a.T = T; a.B = B; a.H = m.d.n_heads; a.V = m.d.vocab; a.Lcap = c->Lcap; a.Scap = c->Scap;
-    a.n_layers = m.d.dec_layers; a.layers = m.rs_layers;
-    a.row_tok = m.rm.row_tok; a.row_pos = m.rm.row_pos; a.row_b = m.rm.row_b; a.row_lim = m.rm.row_lim;
-    a.row_draft = m.rm.row_draft; a.seq_rows = m.rm.seq_rows; a.src_len = c->st.src_len;
-    a.E = m.embed; a.pe = m.pe; a.xs0 = m.x; a.xs1 = m.x2; a.q = m.q; a.hid = m.hid;
-    a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
-    a.zd = vs.zd; a.part = vs.part; a.logits = logits;
-    a.bar = m.rs_bar; a.parity = m.rs_parity;
-    m.rs_seq = m.rs_seq >= 0x3fffffff ? 1 : m.rs_seq + 1;
-    a.seq = m.rs_seq;
-    m.rs_parity ^= 1;
-    LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::resident_verify(st, a, m.d.d_model, m.d.d_ffn));
-    failed = m.rs_bar + 16;
-    c->fin_x = nullptr;   // (the resident kernel keeps its last sum to itself)
-  } else if (small) {
+  if (small) {
     sd::SkSrc fin{};
     if (!fused) {
-      rc = decoder_layers(c, m, B, T, st, true, 0, false, false, true);
+      rc = one ? decoder_layers_persist(c, m, B, T, true, st) : decoder_layers(c, m, B, T, st, true, 0, false, false, true);
       fin = sd::SkSrc{2, m.x, m.dec.back().ln3g, m.dec.back().ln3b, nullptr, nullptr, nullptr, nullptr};
     } else if (c->sliced && sd::sk2_supported(m.d.d_model, m.d.d_ffn) && m.d.n_heads <= sd::kSk2MaxParts)
       rc = decoder_layers_sliced(c, m, B, T, st, &fin);
@@ -1071,8 +1163,14 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     LAUNCH(c, SPECDEC_KIND_VOCAB, st, sd::skinny_vocab(st, fin, R, m.d.d_model, m.fp8 ? m.embed8 : sd::SkWeight(m.embed), m.d.vocab, m.rm.row_draft, vs.zd, vs.part, logits));
     c->fin_x = fin.xs; c->fin_g = fin.g; c->fin_b = fin.b;
   } else {
-    rc = decoder_layers(c, m, B, T, st, true);
-    if (rc) return rc;
+    if (one) {
+      rc = decoder_layers_persist(c, m, B, T, false, st);
+      if (rc) return rc;
+      LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.x, m.dec.back().ln3g, m.dec.back().ln3b, m.xb, R, m.d.d_model));
+    } else {
+      rc = decoder_layers(c, m, B, T, st, true);
+      if (rc) return rc;
+    }
     c->fin_x = m.x; c->fin_g = nullptr; c->fin_b = nullptr;   // normalised in place by the last LayerNorm
     n_tiles = (m.d.vocab + sd::vocab_tile_cols(R) - 1) / sd::vocab_tile_cols(R);
     LAUNCH(c, SPECDEC_KIND_VOCAB, st, sd::vocab_stats(st, m.xb, m.embed, R, m.d.vocab, m.d.d_model, m.rm.row_draft, vs.zd, vs.part, logits, c->wide_vocab));
@@ -1137,7 +1235,6 @@ int specdec_draft_heads(specdec_ctx* c, const int32_t* accept_len, int32_t k, in
   if (k > c->n_draft_heads) return fail(c, SPECDEC_ERR_TOO_LARGE, "k = %d exceeds the %d heads bound", k, c->n_draft_heads);
   if (c->last_T <= 0) return fail(c, SPECDEC_ERR_BAD_STATE, "specdec_draft_heads needs the hidden states of a specdec_verify "
                                   "(call it after specdec_verify, before specdec_commit)");
-  if (!c->fin_x) return fail(c, SPECDEC_ERR_BAD_STATE, "the latest verification pass (resident kernel) kept no hidden states");
   Model& m = c->m[SPECDEC_VERIFIER];
   hipStream_t st = S(stream);
   const int B = c->B, D = m.d.d_model, F = m.d.d_ffn, nh = c->n_draft_heads, R = B * k;

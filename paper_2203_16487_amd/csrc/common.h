@@ -130,12 +130,6 @@ __device__ __forceinline__ void mfma_settle(f32x16& a) { asm volatile("s_nop 15\
 // device scope go to the coherence point instead of the issuing CU's L1 / XCD's L2, so a
 // value stored this way and acknowledged (s_waitcnt vmcnt(0)) is what a later load of this
 // kind returns, on whichever XCD the two workgroups run.
-__device__ __forceinline__ float ld_coh(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ int ld_coh(const int* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ bf16x8 ld_coh16(const bf16* p) {   // 16 bytes, 8-byte aligned halves
   const unsigned long long* q = reinterpret_cast<const unsigned long long*>(p);
   unsigned long long u[2];
@@ -144,14 +138,6 @@ __device__ __forceinline__ bf16x8 ld_coh16(const bf16* p) {   // 16 bytes, 8-byt
   bf16x8 v;
   __builtin_memcpy(&v, u, 16);
   return v;
-}
-__device__ __forceinline__ void st_coh(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_coh(bf16* p, bf16 v) {
-  unsigned short bits;
-  __builtin_memcpy(&bits, &v, 2);
-  __hip_atomic_store(reinterpret_cast<unsigned short*>(p), bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // FP8 E4M3 codes (OCP 8-bit float: 1-4-3, bias 7, largest value 448, no infinities) as stored
 // weights / keys / values: eight codes are one operand fragment's worth.

@@ -219,32 +219,6 @@ hipError_t quantize_rows_e4m3(hipStream_t st, const bf16* w, int N, int K, unsig
 hipError_t quantize_cross_kv(hipStream_t st, const bf16* xk, const bf16* xv, long rows, unsigned char* k8,
                              unsigned char* v8, float* ksc, float* vsc);
 
-// ---- resident.hip: the whole verification pass of at most 32 rows as one resident kernel ----
-struct RsLayer {
-  const bf16 *wqkv, *bqkv, *wo, *bo, *ln1g, *ln1b;
-  const bf16 *cwq, *cbq, *cwo, *cbo, *ln2g, *ln2b;
-  const bf16 *w1, *b1, *w2, *b2, *ln3g, *ln3b;
-};
-struct RsArgs {
-  int R, T, B, H, V, Lcap, Scap, n_layers;
-  const RsLayer* layers;              // device array [n_layers]
-  const int *row_tok, *row_pos, *row_b, *row_lim, *row_draft, *seq_rows, *src_len;
-  const bf16* E;                      // tied embedding / output matrix [V][d]
-  const float* pe;
-  float *xs0, *xs1;                   // residual-sum buffers [32][d]
-  bf16 *q, *hid;                      // [32][d], [32][F]
-  bf16 *kc, *vc;                      // self K/V arenas, layer stride kv_layer
-  const bf16 *xk, *xv;                // cross K/V arenas, layer stride xkv_layer
-  size_t kv_layer, xkv_layer;
-  float *zd, *part, *logits;          // outputs: draft logits [R], tile records, optional logits
-  unsigned* bar;                      // kRsBarWords words: [0],[1] arrival counters (alternating
-                                      // launches), [16] error flag, [64*(1+h)] wake-up word of helper h
-  int parity;                         // which counter this launch uses (the other one is cleared)
-  int seq;                            // launch number, never 0
-};
-constexpr int kRsWorkers = 32;        // workgroups of the resident kernel that run the decoder phases
-constexpr int kRsBarWords = 64 * 226;
-hipError_t resident_verify(hipStream_t st, const RsArgs& a, int d, int F);
 hipError_t skinny_init(int d);
 hipError_t skinny_qkv(hipStream_t st, const SkSrc& src, int R, int d, SkWeight W, const bf16* bias, bf16* q,
                       bf16* kc, bf16* vc, const int* row_b, const int* row_pos, int H, int Lcap);
@@ -255,6 +229,34 @@ hipError_t skinny_proj(hipStream_t st, const SkSrc& src, int R, int d, SkWeight 
                        bf16* out, bool relu);
 hipError_t skinny_ffn2(hipStream_t st, const SkSrc& resid, int R, int d, const bf16* hid, int F, SkWeight W,
                        const bf16* bias, float* xs_out);
+// ---- persist.hip: the decoder layers of a pass of few rows as one kernel ----
+struct PlWeight { const void* p; const float* scale; };   // as SkWeight
+struct PlLayer {
+  PlWeight wqkv, wo, cwq, cwo, w1, w2;
+  const float *qkv_cs, *qkv_bf, *cq_cs, *cq_bf, *w1_cs, *w1_bf;   // LnFold of the projections
+  const float *vo, *vco, *v2;                                     // column vectors of the residual sums
+};
+struct PlArgs {
+  int R, T, B, H, Lcap, Scap, n_layers;   // rows b*T .. b*T + T - 1 of sequence b, at consecutive positions
+  const PlLayer* layers;                  // device array [n_layers]
+  const int *row_b, *row_pos, *src_len;
+  const float* x;                         // embedded rows, fp32 and bf16 [R][d]
+  const bf16* xb;
+  float* y;                               // last residual sum, un-normalised [R][d] (may be x)
+  bf16 *kc, *vc;                          // self K/V arenas, layer stride kv_layer
+  const void *xk, *xv;                    // cross K/V arenas, layer stride xkv_layer elements: bf16, or (scales not null) codes
+  const float *xk_scale, *xv_scale;
+  size_t kv_layer, xkv_layer;
+  int fp8;                                // the layers' weights are codes
+  char* exch;                             // persist_exch_bytes, every byte 0xff when the kernel starts
+  unsigned* err;                          // sticky error flag
+  int RP, RT, d, fbw, att0;               // filled by the launcher
+};
+constexpr int kPlBlocks = 256;            // most workgroups of a pass
+bool persist_supported(int layers, int d, int F);
+size_t persist_exch_bytes(int rows, int layers, int d, int F);
+int persist_plan(PlArgs& a, int d, int F);   // workgroups of a pass of a.R rows, a.B sequences, a.H heads (0: too many rows)
+hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F);
 // ---- skinny2.hip: the same passes with sub-layers owned by head / by FFN slice (three kernels per layer) ----
 bool sk2_supported(int d, int F);
 int sk2_ffn_slices(int F);             // partial results the FFN kernel leaves (at most 16)
@@ -300,8 +302,10 @@ struct SeqState {       // device arrays of the bound state buffer, all [max_bat
 hipError_t assemble_verify(hipStream_t st, const SeqState& s, const RowMap& rm, const int* draft,
                            int B, int k, int V);
 // assemble_verify and embed_rows of the same rows in one launch
+// (clear, clear_bytes: a buffer the same launch fills with 0xff; multiple of 16)
 hipError_t assemble_embed_verify(hipStream_t st, const SeqState& s, const RowMap& rm, const int* draft, int B, int k,
-                                 int V, const bf16* E, const float* pe, float* x, bf16* xb, int d);
+                                 int V, const bf16* E, const float* pe, float* x, bf16* xb, int d, void* clear = nullptr,
+                                 size_t clear_bytes = 0);
 // rows of a prefill pass (n_mask = 0) or of a drafter pass (stream rows + n_mask [MASK] slots),
 // embedded in the same launch; new_rows[b] = stream rows of sequence b in this pass;
 // packed: rows of the sequences follow each other without padding (RowMap::row_start is written)

@@ -208,8 +208,13 @@ __global__ __launch_bounds__(128) void assemble_embed_verify_kernel(SeqState s, 
                                                                     const bf16* __restrict__ E,
                                                                     const float* __restrict__ pe,
                                                                     float* __restrict__ x, bf16* __restrict__ xb, int d,
-                                                                    float scale) {
+                                                                    float scale, uint4* __restrict__ clear, long n16) {
   const int idx = blockIdx.x, T = k + 1;
+  if (idx >= B * T) {   // the blocks beyond the rows clear
+    for (long i = (long)(idx - B * T) * 128 + threadIdx.x; i < n16; i += (long)(gridDim.x - B * T) * 128)
+      clear[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    return;
+  }
   const int b = idx / T, i = idx - b * T;
   const int j = s.len[b];
   int tok = (i == 0) ? s.tokens[(size_t)b * s.tok_pitch + j] : draft[b * k + i - 1];
@@ -226,10 +231,12 @@ __global__ __launch_bounds__(128) void assemble_embed_verify_kernel(SeqState s, 
   embed_row(E + (size_t)tok * d, pe + (size_t)(j + i) * d, x + (size_t)idx * d, xb + (size_t)idx * d, d, scale, threadIdx.x, 128);
 }
 hipError_t assemble_embed_verify(hipStream_t st, const SeqState& s, const RowMap& rm, const int* draft, int B, int k,
-                                 int V, const bf16* E, const float* pe, float* x, bf16* xb, int d) {
+                                 int V, const bf16* E, const float* pe, float* x, bf16* xb, int d, void* clear,
+                                 size_t clear_bytes) {
   if (B <= 0) return hipSuccess;
-  hipLaunchKernelGGL(assemble_embed_verify_kernel, dim3(B * (k + 1)), dim3(128), 0, st, s, rm, draft, B, k, V, E, pe,
-                     x, xb, d, sqrtf((float)d));
+  const long n16 = (long)(clear_bytes / 16), more = (n16 + 511) / 512;   // four pieces per thread
+  hipLaunchKernelGGL(assemble_embed_verify_kernel, dim3((unsigned)(B * (k + 1) + (more < 1024 ? more : 1024))), dim3(128), 0, st,
+                     s, rm, draft, B, k, V, E, pe, x, xb, d, sqrtf((float)d), static_cast<uint4*>(clear), n16);
   return hipGetLastError();
 }
 

@@ -1,0 +1,747 @@
+// The decoder layers of a pass of few rows as ONE kernel whose workgroups hand over through memory.
+//
+// With few rows a decoder layer is eight dependent products and attentions of a microsecond each, and as separate kernels
+// every hand-over costs a launch (about 4 us from one kernel's operands to the next one's).  Here up to kPlBlocks workgroups
+// of four (d = 512) or eight (1024) waves stay resident for all layers, with seven hand-overs in each: queries / keys / values,
+// self-attention, its output product, cross-attention (whose units form their queries themselves), its output product, and
+// the two FFN matrices.  What one workgroup produces for another goes to an exchange buffer that holds kPoison in
+// every 32-bit word beforehand (the pass's first kernel writes it); the consumers load the words they need, coherently and
+// straight into MFMA operand registers, until none of them is kPoison any more.  The value is its own flag: a hand-over is
+// one store and one load through memory, 1.0 - 1.4 us, plus 0.6 - 1.1 us of work, with no barrier, no counter and no fence.
+// No word of a result is ever stored as kPoison (not_poison).
+//
+// Work items of a stage are dealt to the workgroups round robin; the three residual-sum products of a layer give a workgroup
+// the same tile each time, so that the fp32 residual stays in its LDS.  A projection item is 16 rows x 16 FB columns: the
+// waves split K, each lane requests its weight fragments before it waits for the rows (they arrive meanwhile), the
+// partial tiles are summed through LDS in wave order, and wave f < FB finishes columns 16 f .. + 15.  LayerNorm is folded into
+// the products as in the general kernels (gemm.hip), with statistics per 16 columns.
+//
+// What bounds it: the chain of 7 hand-overs a layer.  A whole verify pass, separate
+// kernels -> this one: d = 512, 6 layers, 11 rows 196 -> 124 us; 77 rows 241 -> 161; d = 1024, 26 rows of E4M3 weights
+// 303 -> 224.
+//
+// Waits are bounded: after kPlSpinMax polls, or once another workgroup has raised the error flag, a wave raises it and ends;
+// the host reports accept_len = -1.  All workgroups are co-resident by construction (there are no more than CUs and
+// the host has one such pass at a time on a GPU).
+#include "attn_core.h"
+
+namespace sd {
+
+constexpr unsigned kPoison = 0xffffffffu;
+constexpr unsigned kPlSpinMax = 1u << 21;
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// Coherent 16-byte load (device scope: past the L1 and this XCD's L2): the buffer form with sc1.  (An inline-asm load would
+// leave the compiler free to copy its result before it has arrived.)
+typedef __amdgpu_buffer_rsrc_t PlBuf;
+__device__ __forceinline__ PlBuf pl_buf(const void* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffff, 0x00027000); }
+constexpr int kPlSc1 = 16;
+__device__ __forceinline__ u32x4 pl_request(PlBuf b, int voff, int soff) { return __builtin_amdgcn_raw_buffer_load_b128(b, voff, soff, kPlSc1); }
+__device__ __forceinline__ bool pl_missing(const u32x4& v) {
+  return v[0] == kPoison || v[1] == kPoison || v[2] == kPoison || v[3] == kPoison;
+}
+__device__ __forceinline__ unsigned not_poison(unsigned u) { return u == kPoison ? 0x7fc07fc0u : u; }   // (a NaN for a NaN)
+__device__ __forceinline__ void pl_store8(void* p, unsigned a, unsigned b) {
+  u32x2 v = {not_poison(a), not_poison(b)};
+  asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory");
+}
+__device__ __forceinline__ u32x2 pl_pack4(const float (&v)[4]) {
+  bf16x4 t;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) t[i] = (bf16)v[i];
+  return __builtin_bit_cast(u32x2, t);
+}
+
+// One more round of a wait: false once the pass is to be abandoned.
+__device__ __forceinline__ bool pl_again(unsigned& spins, unsigned* err) {
+  ++spins;
+  if ((spins & 63) == 0) {
+    const bool raised = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+    if (raised || spins > kPlSpinMax) {
+      __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return false;
+    }
+  }
+  __builtin_amdgcn_s_sleep(1);
+  return true;
+}
+
+// N requests at off + i * stride (bytes from A), repeated until they hold no kPoison; lanes with on = false read along and are
+// not waited for (their addresses are valid).  M of 8 bytes (M = 0: none) at qoff + i * qstride from Q in the same rounds.
+template <int N, int M>
+__device__ __forceinline__ bool pl_poll(u32x4 (&f)[N], PlBuf A, int off, int stride, bool on, u32x2* s, PlBuf Q, int qoff,
+                                        int qstride, unsigned* err) {
+  unsigned spins = 0;
+  while (true) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i] = pl_request(A, off, i * stride);
+#pragma unroll
+    for (int i = 0; i < M; ++i) s[i] = __builtin_amdgcn_raw_buffer_load_b64(Q, qoff, i * qstride, kPlSc1);
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) bad |= pl_missing(f[i]);
+#pragma unroll
+    for (int i = 0; i < M; ++i) bad |= s[i][0] == kPoison || s[i][1] == kPoison;
+    if (!__builtin_amdgcn_ballot_w64(bad && on)) return true;
+    if (!pl_again(spins, err)) return false;
+    asm volatile("" ::: "memory");
+  }
+}
+
+// sums over the four 16-lane rows (lanes lq + 16 g), result in all of them
+__device__ __forceinline__ float pl_row_sum(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return half_add(__builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]));
+}
+
+struct PlStat { float rstd, nmr; };
+// mean and rstd of row lq from its chunk pairs of 16 columns; this lane holds NS of them
+template <int NS>
+__device__ __forceinline__ PlStat pl_stat(const u32x2 (&pairs)[NS], int d) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  f32x2 p[NS];
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    p[i] = __builtin_bit_cast(f32x2, pairs[i]);
+    s += p[i][0];
+  }
+  const float inv_d = __builtin_amdgcn_rcpf((float)d), mean = pl_row_sum(s) * inv_d;
+  float q = 0.f;
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const float dv = p[i][0] * (1.f / 16) - mean;
+    q += p[i][1] + 16.f * dv * dv;
+  }
+  const float rstd = fast_rsqrt(pl_row_sum(q) * inv_d + 1e-5f);
+  return PlStat{rstd, -mean * rstd};
+}
+
+// The lane, as a value the compiler cannot carry over from an earlier stage: otherwise every stage's addresses are computed
+// ahead of the layer loop and held (or spilled) throughout.
+__device__ __forceinline__ int pl_lane() {
+  int t = threadIdx.x & 63;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+__device__ __forceinline__ int pl_opaque(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
+constexpr int kPlLayers = 32;
+constexpr int kPlQPitch = 72;   // (16 rows of 144 bytes: a 16-byte read of every row meets all banks once)
+constexpr int kPlRounds = 4;   // residual tiles a workgroup can hold
+
+template <int NW>
+struct PlLds {
+  f32x4 red[2][NW * 4 * 64];                // partial tiles, two in turn
+  float resid[kPlRounds][16 * 16];
+  float stat[2][32];                              // {rstd, -mean rstd} of the 16 rows, beside red
+  bf16 q[16 * kPlQPitch];                         // queries of the workgroup's unit (cross-attention)
+  unsigned long long layers[kPlLayers * sizeof(PlLayer) / 8];   // every stage's pointers
+  // attention: the value tiles of the waves ([32 keys][64], swizzled like the tile kernel's) in red[1], partial results in red[0]
+  __device__ __forceinline__ bf16* vs(int wave) { return reinterpret_cast<bf16*>(red[1]) + wave * (32 * 64); }
+};
+
+// Exchange buffers of one layer, all in tiles of 16 columns, [column / 16][RP][16]: what one item produces lies together and
+// shares no line with another workgroup's stores (with rows of all columns side by side the 8- and 32-byte pieces of up to 16
+// workgroups met in every line, and a residual sum took 3 us to become visible instead of 1).  Statistics likewise
+// [chunk][RP] pairs.
+__host__ __device__ inline size_t pl_layer_bytes(int RP, int d, int F) {
+  return (size_t)RP * (3 * (2 * d + d / 2) + 6 * 2 * d + 2 * F);
+}
+struct PlExch {   // (only the layer's base stays in registers)
+  char* base;
+  int row;        // bytes of a buffer of RP rows of d
+  __device__ __forceinline__ PlExch(char* exch, int l, int RP, int d, int F)
+      : base(exch + (size_t)l * pl_layer_bytes(RP, d, F)), row(RP * 2 * d) {}
+  __device__ __forceinline__ char* xg(int i) const { return base + i * row; }
+  __device__ __forceinline__ char* q(int i) const { return base + (3 + i) * row; }
+  __device__ __forceinline__ char* kx() const { return base + 5 * row; }
+  __device__ __forceinline__ char* vx() const { return base + 6 * row; }
+  __device__ __forceinline__ char* att(int i) const { return base + (7 + i) * row; }
+  __device__ __forceinline__ char* st(int i) const { return base + 9 * row + i * (row >> 2); }
+  __device__ __forceinline__ char* hid() const { return base + 9 * row + 3 * (row >> 2); }
+};
+// element (row, k) of a buffer, bytes
+__device__ __forceinline__ int pl_at(int RP, int row, int k) { return ((k >> 4) * RP + row) * 32 + (k & 15) * 2; }
+
+// Product of one item: rows row0 .. row0 + 15 below rlim of A (exchange buffer, or plain rows), columns n0 .. n0 + 16 FB - 1 of
+// W [N][32 * 8 * KS].  Returns in v the finished sums of this lane, row row0 + lane % 16, columns n0 + 16 wave + 4 (lane / 16)
+// .. + 3, for waves < FB, and in ps the statistics of that row (stats null: {1, 0}), which the last wave waits for and reduces.
+// WT: bf16 values, or E4M3 codes that become bf16 operands as they arrive (the caller applies the columns' scales).
+template <class WT> struct PlFrag { typedef bf16x8 type; };
+template <> struct PlFrag<fp8> { typedef fp8x8 type; };
+__device__ __forceinline__ bf16x8 pl_operand(const bf16x8& f) { return f; }
+__device__ __forceinline__ bf16x8 pl_operand(const fp8x8& f) { return e4m3x8_to_bf16(f); }
+template <class WT, int NW, int KS, int FB, int NS>
+__device__ __forceinline__ bool pl_product(const PlArgs& a, PlLds<NW>& L, int flip, const void* Wv, const char* A, bool plain, int row0,
+                                           int rlim, int n0, const char* stats, f32x4& v, PlStat& ps) {
+  constexpr int K = 32 * NW * KS;
+  const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
+  f32x4* red = L.red[flip];
+  const WT* W = static_cast<const WT*>(Wv);
+  typename PlFrag<WT>::type wf[FB][KS];
+#pragma unroll
+  for (int f = 0; f < FB; ++f)
+#pragma unroll
+    for (int u = 0; u < KS; ++u)
+      wf[f][u] = *reinterpret_cast<const typename PlFrag<WT>::type*>(W + (size_t)(n0 + 16 * f + lq) * K + (wave * KS + u) * 32 + 8 * g);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  const int row = min(row0 + lq, rlim - 1);
+  const bool on = row0 + lq < rlim;
+  f32x4 acc[FB];
+#pragma unroll
+  for (int f = 0; f < FB; ++f) acc[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr int AC = KS > 16 ? 16 : KS;   // fragments waited for together
+  const PlBuf buf = pl_buf(A);
+  const int stride = a.RP * 64;
+#pragma unroll
+  for (int u0 = 0; u0 < KS; u0 += AC) {
+    u32x4 af[AC];
+    const int k = (wave * KS + u0) * 32 + 8 * g;
+    if (plain) {   // rows another kernel wrote, [R][K]
+#pragma unroll
+      for (int u = 0; u < AC; ++u) af[u] = *reinterpret_cast<const u32x4*>(A + ((size_t)row * K + k + u * 32) * 2);
+    } else if (u0 == 0 && wave == NW - 1 && stats) {   // chunks g * NS .. of the row
+      u32x2 st[NS];
+      if (!pl_poll<AC, NS>(af, buf, pl_at(a.RP, row, k), stride, on, st, pl_buf(stats), (g * NS * a.RP + row) * 8, a.RP * 8, a.err)) return false;
+      const PlStat s = pl_stat<NS>(st, a.d);
+      if (g == 0) { L.stat[flip][2 * lq] = s.rstd; L.stat[flip][2 * lq + 1] = s.nmr; }
+    } else {
+      if (!pl_poll<AC, 0>(af, buf, pl_at(a.RP, row, k), stride, on, nullptr, buf, 0, 0, a.err)) return false;
+    }
+#pragma unroll
+    for (int f = 0; f < FB; ++f)
+#pragma unroll
+      for (int u = 0; u < AC; ++u)
+        acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl_operand(wf[f][u0 + u]), __builtin_bit_cast(bf16x8, af[u]), acc[f], 0, 0, 0);
+  }
+#pragma unroll
+  for (int f = 0; f < FB; ++f) {
+    mfma_settle(acc[f]);
+    red[(wave * FB + f) * 64 + lane] = acc[f];
+  }
+  lds_barrier();
+  v = f32x4{0.f, 0.f, 0.f, 0.f};
+  ps = PlStat{1.f, 0.f};
+  if (wave < FB) {
+    f32x4 t[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t[w] = red[(w * FB + wave) * 64 + lane];
+    if (stats) ps = PlStat{L.stat[flip][2 * lq], L.stat[flip][2 * lq + 1]};
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += t[w][e];
+  }
+  return true;
+}
+
+// hidden(LayerNorm folded) W^T + b of one item; epi(row, n, float[4]) on live rows
+template <class WT, int NW, int KS, int FB, int NS, class Epi>
+__device__ __forceinline__ bool pl_project(const PlArgs& a, PlLds<NW>& L, int flip, const PlWeight& W, const float* cs, const float* bf,
+                                           const char* A, bool plain, const char* stats, int row0, int rlim, int n0, Epi&& epi) {
+  const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
+  const int n = n0 + 16 * min(wave, FB - 1) + 4 * g;
+  const f32x4 c4 = *reinterpret_cast<const f32x4*>(cs + n), b4 = *reinterpret_cast<const f32x4*>(bf + n);
+  f32x4 w4 = {1.f, 1.f, 1.f, 1.f};
+  if constexpr (sizeof(WT) == 1) w4 = *reinterpret_cast<const f32x4*>(W.scale + n);
+  f32x4 v;
+  PlStat s;
+  if (!pl_product<WT, NW, KS, FB, NS>(a, L, flip, W.p, A, plain, row0, rlim, n0, stats, v, s)) return false;
+  if (wave < FB) {
+    float o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(sizeof(WT) == 1 ? v[e] * w4[e] : v[e], s.rstd, __builtin_fmaf(s.nmr, c4[e], b4[e]));
+    const int row = row0 + lq;
+    if (row < rlim) epi(row, n, o);
+  }
+  return true;
+}
+
+// residual sum of one item (FB = 1): y = LN_prev(x) + A W^T + b; xg, statistics and the workgroup's copy of y
+template <class WT, int NW, int KS, int NS>
+__device__ __forceinline__ bool pl_sum(const PlArgs& a, PlLds<NW>& L, int flip, float* resid, const PlWeight& W, const float* vecs,
+                                       const char* A, const char* stats_prev, bool first, bool last, char* xg, char* st_out,
+                                       int row0, int n0) {
+  const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
+  const int n = n0 + 4 * g, row = min(row0 + lq, a.R - 1);
+  f32x4 cv[3], x, w4 = {1.f, 1.f, 1.f, 1.f};
+  if constexpr (sizeof(WT) == 1) w4 = *reinterpret_cast<const f32x4*>(W.scale + n);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) cv[i] = *reinterpret_cast<const f32x4*>(vecs + i * a.d + n);
+  if (first) x = *reinterpret_cast<const f32x4*>(a.x + (size_t)row * a.d + n);
+  else x = *reinterpret_cast<const f32x4*>(resid + lq * 16 + 4 * g);
+  f32x4 v;
+  PlStat s;
+  if (!pl_product<WT, NW, KS, 1, NS>(a, L, flip, W.p, A, false, row0, a.R, n0, stats_prev, v, s)) return false;
+  if (wave != 0) return true;
+  float y[4], gx[4], sum = 0.f, ss = 0.f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    y[e] = (sizeof(WT) == 1 ? v[e] * w4[e] : v[e]) + __builtin_fmaf(__builtin_fmaf(x[e], s.rstd, s.nmr), cv[0][e], cv[1][e]);
+    gx[e] = y[e] * cv[2][e];
+  }
+  const bool live = row0 + lq < a.R;
+  if (last) {
+    if (live) *reinterpret_cast<f32x4*>(a.y + (size_t)row * a.d + n) = f32x4{y[0], y[1], y[2], y[3]};
+    return true;
+  }
+  const u32x2 w = pl_pack4(gx);
+  if (live) pl_store8(xg + pl_at(a.RP, row, n), w[0], w[1]);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { sum += y[e]; ss = __builtin_fmaf(y[e], y[e], ss); }
+  sum = pl_row_sum(sum);
+  ss = pl_row_sum(ss);
+  if (live && g == 0)
+    pl_store8(st_out + ((n0 >> 4) * a.RP + row) * 8, __builtin_bit_cast(unsigned, sum),
+              __builtin_bit_cast(unsigned, fmaxf(ss - sum * sum * (1.0f / 16), 0.f)));
+  *reinterpret_cast<f32x4*>(resid + lq * 16 + 4 * g) = f32x4{y[0], y[1], y[2], y[3]};
+  return true;
+}
+
+// Attention of one unit: 16 queries (the last ones of a sequence: fewer) of one (sequence, head) pair.  at: the keys its
+// queries see.
+struct PlUnit {
+  int b, h, q0, j, nkey;   // sequence, head, first query; keys cached before the pass (self-attention), all keys
+};
+template <bool SELF>
+__device__ __forceinline__ PlUnit pl_unit(const PlArgs& a, int u) {
+  const int tiles = (a.T + 15) >> 4, pair = u / tiles;
+  PlUnit t;
+  t.b = pair / a.H; t.h = pair - t.b * a.H; t.q0 = (u - pair * tiles) * 16;
+  t.j = SELF ? a.row_pos[t.b * a.T] : 0;
+  t.nkey = SELF ? t.j + min(a.T, t.q0 + 16) : a.src_len[t.b];
+  return t;
+}
+// 1 / sqrt(64) and log2(e) meet the scores in the exponent.
+constexpr float kCexp = 0.125f * 1.44269504088896341f;
+
+// Key chunks kw, kw + kstep, ... of 32 on this wave (see attn_core.h for the operand layouts).  SELF: keys / values below the
+// pass's first row come from the cache, the pass's own from the exchange buffers (waited for); else the cross-attention arenas.
+// QLDS: the queries are in LDS (q_lds) once form_q() has returned; it runs behind the first keys' and values' requests.
+// KV8 (cross): codes with one fp32 scale per key and per value, as in attn_core.h.
+template <bool SELF, bool QLDS, bool KV8, class FormQ>
+__device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, int l, const PlUnit& t, int kw, int kstep,
+                                             const bf16* q_lds, FormQ&& form_q, bf16* Vs, float& mrun, float& lrun,
+                                             f32x4 (&oacc)[4]) {
+  const int lane = pl_lane(), lq = lane & 15, g = lane >> 4;
+  const int r0 = t.b * a.T;                                // first row of the sequence
+  const int j = t.j, nkey = t.nkey;
+  const int cap = SELF ? a.Lcap : a.Scap;
+  const size_t arena = ((size_t)t.b * a.H + t.h) * cap * kHeadDim;
+  constexpr int EB = KV8 ? 1 : 2;   // bytes of an element
+  const char* kb = (SELF ? reinterpret_cast<const char*>(a.kc + a.kv_layer * l) : static_cast<const char*>(a.xk) + a.xkv_layer * l * EB) + arena * EB;
+  const char* vb = (SELF ? reinterpret_cast<const char*>(a.vc + a.kv_layer * l) : static_cast<const char*>(a.xv) + a.xkv_layer * l * EB) + arena * EB;
+  const size_t sc0 = KV8 ? (a.xkv_layer * l + arena) / kHeadDim : 0;
+  mrun = kNegInf;
+  lrun = 0.f;
+#pragma unroll
+  for (int et = 0; et < 4; ++et) oacc[et] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // K operands: tile i, row lq  <->  key c0 + 8*(lq/4) + 4*i + lq%4; values as whole rows (lane -> row 8*i + lane/8, dims
+  // 8*(lane%8) .. + 7) or, key-blocked, as operands.  What the cache holds is requested once, the pass's own rows until they
+  // are there.
+  u32x4 kf[4], vf[4], f[2];
+  fp8x8 kf8[4], vf8[4];
+  f32x4 sck[2], scv[2];
+  auto key_k = [&](int c0, int i) { return c0 + 8 * (lq >> 2) + 4 * i + (lq & 3); };
+  auto key_v = [&](int c0, int i) { return c0 + 8 * i + (lane >> 3); };
+  auto fetch = [&](int c0) {
+    const int last = (SELF ? j : nkey) - 1;
+    if (SELF && c0 > last) return;
+    if constexpr (KV8) {
+      const int k8 = min(c0 + 8 * g, cap - 8);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const char* p = kb + max(min(key_k(c0, i), last), 0) * 64 + g * 8;
+        kf8[2 * i] = *reinterpret_cast<const fp8x8*>(p);
+        kf8[2 * i + 1] = *reinterpret_cast<const fp8x8*>(p + 32);
+        sck[i] = *reinterpret_cast<const f32x4*>(a.xk_scale + sc0 + k8 + 4 * i);
+        scv[i] = *reinterpret_cast<const f32x4*>(a.xv_scale + sc0 + k8 + 4 * i);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) vf8[i] = *reinterpret_cast<const fp8x8*>(vb + vt_off(k8, i * 16 + lq));
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const char* p = kb + max(min(key_k(c0, i), last), 0) * 128 + g * 16;
+      kf[2 * i] = *reinterpret_cast<const u32x4*>(p);
+      kf[2 * i + 1] = *reinterpret_cast<const u32x4*>(p + 64);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      vf[i] = *reinterpret_cast<const u32x4*>(SELF ? vb + min(key_v(c0, i), last) * 128 + (lane & 7) * 16
+                                                   : vb + vt_off(min(c0 + 8 * g, cap - 8), i * 16 + lq) * 2);
+  };
+  // the chunk's own rows (SELF) and, with_q, the queries
+  auto await = [&](int c0, bool with_q) {
+    const bool own = SELF && c0 + 32 > j;
+    if (!own && !with_q) return true;
+    const PlBuf kxb = pl_buf(ex.kx()), vxb = pl_buf(ex.vx()), qb = pl_buf(ex.q(SELF ? 0 : 1));
+    const int off = pl_at(a.RP, r0, t.h * kHeadDim), xtile = a.RP * 32;
+    const int offk = off + pl_at(a.RP, 0, 8 * g), offv = off + pl_at(a.RP, 0, 8 * (lane & 7));
+    unsigned spins = 0;
+    while (true) {
+      u32x4 kn[4], vn[4];
+      bool bad = false;
+      if (own) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) kn[i] = pl_request(kxb, offk + min(max(key_k(c0, i >> 1) - j, 0), a.T - 1) * 32, (i & 1) * 2 * xtile);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) vn[i] = pl_request(vxb, offv + min(max(key_v(c0, i) - j, 0), a.T - 1) * 32, 0);
+      }
+      if (with_q) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) f[i] = pl_request(qb, offk + min(t.q0 + lq, a.T - 1) * 32, i * 2 * xtile);
+      }
+      if (own) {   // (keys at and beyond nkey are masked later: not waited for)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bad |= key_k(c0, i >> 1) >= j && key_k(c0, i >> 1) < nkey && pl_missing(kn[i]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bad |= key_v(c0, i) >= j && key_v(c0, i) < nkey && pl_missing(vn[i]);
+      }
+      if (with_q) bad |= pl_missing(f[0]) || pl_missing(f[1]);
+      if (!__builtin_amdgcn_ballot_w64(bad)) {
+        if (own) {
+          // (values beyond nkey meet a probability of zero: they must be finite)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              kf[i][e] = key_k(c0, i >> 1) >= j ? kn[i][e] : kf[i][e];
+              vf[i][e] = key_v(c0, i) >= nkey ? 0u : key_v(c0, i) >= j ? vn[i][e] : vf[i][e];
+            }
+        }
+        return true;
+      }
+      if (!pl_again(spins, a.err)) return false;
+      asm volatile("" ::: "memory");
+    }
+  };
+  const int cfirst = kw * 32;
+  fetch(cfirst);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (QLDS) {   // formed by this workgroup
+    if (!await(cfirst, false)) return false;
+    if (!form_q()) return false;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) f[i] = *reinterpret_cast<const u32x4*>(q_lds + lq * kPlQPitch + i * 32 + 8 * g);
+  } else {
+    if (!await(cfirst, true)) return false;
+  }
+  const bf16x8 q0 = __builtin_bit_cast(bf16x8, f[0]), q1 = __builtin_bit_cast(bf16x8, f[1]);
+  const int lim = t.q0 + lq < a.T ? (SELF ? j + t.q0 + lq + 1 : nkey) : 0;
+  for (int c0 = cfirst; c0 < nkey; c0 += kstep * 32) {
+    if (c0 != cfirst) {
+      fetch(c0);
+      if (!await(c0, false)) return false;
+    }
+    bf16x8 vo[4];
+    if constexpr (KV8) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        kf[i] = __builtin_bit_cast(u32x4, e4m3x8_to_bf16(kf8[i]));
+        vf[i] = __builtin_bit_cast(u32x4, e4m3x8_to_bf16(vf8[i]));
+      }
+    }
+    if constexpr (SELF) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 8 * i + (lane >> 3);
+        *reinterpret_cast<u32x4*>(Vs + r * 64 + (((lane & 7) ^ ((r & 2) << 1)) << 3)) = vf[i];
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int et = 0; et < 4; ++et) {
+        const int r = 8 * g + ((lane >> 2) & 3), c = et * 16 + 4 * (lane & 3);
+        const bf16* src = Vs + r * 64 + (((c >> 3) ^ ((r & 2) << 1)) << 3) + (c & 7);   // (row r + 4 has the same swizzle)
+        s16x4 p[2] = {lds_tr16(src), lds_tr16(src + 4 * 64)};
+        __builtin_memcpy(&vo[et], p, 16);
+      }
+    } else {
+#pragma unroll
+      for (int et = 0; et < 4; ++et) vo[et] = __builtin_bit_cast(bf16x8, vf[et]);
+      if (c0 + 32 > nkey) {
+#pragma unroll
+        for (int et = 0; et < 4; ++et) vo[et] = zero_tail(vo[et], nkey - (c0 + 8 * g));
+      }
+    }
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[0]), q0, s0, 0, 0, 0);
+    s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[2]), q0, s1, 0, 0, 0);
+    s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[1]), q1, s0, 0, 0, 0);
+    s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[3]), q1, s1, 0, 0, 0);
+    mfma_settle(s0, s1);
+    if constexpr (KV8) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) { s0[r] *= sck[0][r]; s1[r] *= sck[1][r]; }
+    }
+    const int left = lim - (c0 + 8 * g);   // this lane: query lq, keys c0 + 8 g .. + 7, of which it sees the first `left`
+    float s[8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[r] = r < left ? s0[r] : kNegInf;
+      s[4 + r] = 4 + r < left ? s1[r] : kNegInf;
+    }
+    float cm = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
+    {
+      const unsigned u = __builtin_bit_cast(unsigned, cm);
+      const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+      cm = half_max(fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])));
+    }
+    const float mnew = fmaxf(mrun, cm);
+    const float nb = mnew > kNegInf ? -mnew * kCexp : 0.f;   // nothing seen yet: every exponential below is of -inf
+    bf16x8 pf;
+    float p[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], kCexp, nb));
+      // (a masked key's scale may be anything, NaN included)
+      if constexpr (KV8) pf[r] = (bf16)(r < left ? p[r] * scv[r >> 2][r & 3] : 0.f);
+      else pf[r] = (bf16)p[r];
+    }
+    const float ps = pl_row_sum(((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])));
+    if (c0 == cfirst) {
+      lrun = ps;
+    } else {
+      const float alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(mrun, kCexp, nb));
+      lrun = lrun * alpha + ps;
+#pragma unroll
+      for (int et = 0; et < 4; ++et)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) oacc[et][r] *= alpha;
+    }
+    mrun = mnew;
+#pragma unroll
+    for (int et = 0; et < 4; ++et) oacc[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vo[et], pf, oacc[et], 0, 0, 0);
+  }
+  mfma_settle(oacc);
+  return true;
+}
+
+// All units of one attention stage.  Few: a workgroup per unit, its waves take chunks of 32 keys in turn and merge through LDS;
+// many: a wave per unit.
+template <int NW, bool SELF, bool QLDS, bool KV8, class FormQ>
+__device__ __forceinline__ bool pl_attention(const PlArgs& a, const PlExch& ex, int l, int w, int units, const PlUnit& mine,
+                                             PlLds<NW>& L, FormQ&& form_q) {
+  const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
+  const int NB = gridDim.x;
+  if (units <= NB && (unsigned)w >= (unsigned)units) return true;   // (w: number among the workgroups that take units)
+  lds_barrier();   // the latest product's partial tiles are done with
+  char* out = ex.att(SELF ? 0 : 1);
+  float mrun, lrun;
+  f32x4 oacc[4];
+  auto store = [&](const PlUnit& t, int et, const f32x4& o, float inv) {
+    float v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = o[r] * inv;
+    const u32x2 p = pl_pack4(v);
+    if (t.q0 + lq < a.T) pl_store8(out + pl_at(a.RP, t.b * a.T + t.q0 + lq, t.h * kHeadDim + et * 16 + 4 * g), p[0], p[1]);
+  };
+  if (units > NB) {
+    for (int u = w * NW + wave; u < units; u += NB * NW) {
+      const PlUnit t = pl_unit<SELF>(a, u);
+      if (!pl_attn_wave<SELF, false, KV8>(a, ex, l, t, 0, 1, nullptr, [] { return true; }, L.vs(wave), mrun, lrun, oacc)) return false;
+      const float inv = lrun > 0.f ? __builtin_amdgcn_rcpf(lrun) : 0.f;
+#pragma unroll
+      for (int et = 0; et < 4; ++et) store(t, et, oacc[et], inv);
+    }
+    lds_barrier();
+    return true;
+  }
+  const int chunks = (mine.nkey + 31) >> 5, used = min(max(chunks, 1), NW);   // waves with keys (one at least)
+  // (every wave takes part in forming the queries; one beyond the keys then finds none)
+  if ((QLDS || wave < used) &&
+      !pl_attn_wave<SELF, QLDS, KV8>(a, ex, l, mine, wave, NW, L.q, form_q, L.vs(wave), mrun, lrun, oacc))
+    return false;
+  if (used == 1) {
+    if (wave == 0) {
+      const float inv = lrun > 0.f ? __builtin_amdgcn_rcpf(lrun) : 0.f;
+#pragma unroll
+      for (int et = 0; et < 4; ++et) store(mine, et, oacc[et], inv);
+    }
+    lds_barrier();
+    return true;
+  }
+  // O of every wave to LDS (the partial-tile buffers); wave et merges dims 16 et .. + 15
+  f32x4* om = L.red[0];                                            // [wave][et][lane]
+  float* ml = reinterpret_cast<float*>(L.red[1]);                  // [wave][max, sum][16]  (the value tiles are done with)
+  lds_barrier();
+  if (wave < used) {
+#pragma unroll
+    for (int et = 0; et < 4; ++et) om[(wave * 4 + et) * 64 + lane] = oacc[et];
+    if (g == 0) { ml[wave * 32 + lq] = mrun; ml[wave * 32 + 16 + lq] = lrun; }
+  }
+  lds_barrier();
+  if (wave < 4) {
+    float M = kNegInf, Ls = 0.f;
+    for (int s = 0; s < used; ++s) M = fmaxf(M, ml[s * 32 + lq]);
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < used; ++s) {
+      const float ms = ml[s * 32 + lq], f = ms > kNegInf ? __builtin_amdgcn_exp2f((ms - M) * kCexp) : 0.f;
+      Ls += ml[s * 32 + 16 + lq] * f;
+      const f32x4 v = om[(s * 4 + wave) * 64 + lane];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[r] += v[r] * f;
+    }
+    store(mine, wave, o, Ls > 0.f ? __builtin_amdgcn_rcpf(Ls) : 0.f);
+  }
+  lds_barrier();
+  return true;
+}
+
+// WT: weights (bf16 or E4M3 codes).  KV8: cross-attention keys / values as E4M3 codes.
+// FBW: column tiles of an item of the wide projections (QKV, first FFN matrix).
+template <class WT, bool KV8, int NW, int KSD, int KSF, int FBW>
+__global__ __launch_bounds__((64 * NW), 2) void pl_decoder_kernel(PlArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char pl_smem[];
+  PlLds<NW>& L = *reinterpret_cast<PlLds<NW>*>(pl_smem);
+  constexpr int d = 32 * NW * KSD, F = 32 * NW * KSF, NS = d / 64;   // statistics: d / 16 pairs over four lanes
+  // wide projections from the top, sums from the bottom, attention units from att0 on: where there is room a workgroup has one
+  // kind of item and its weights are on their way long before the rows are
+  const int NB = gridDim.x, w = blockIdx.x, wr = NB - 1 - w;
+  if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return;   // sticky error: do nothing
+  {
+    const int words = a.n_layers * (int)(sizeof(PlLayer) / 8);
+    for (int i = threadIdx.x; i < words; i += (64 * NW)) L.layers[i] = reinterpret_cast<const unsigned long long*>(a.layers)[i];
+  }
+  const int units = a.B * a.H * ((a.T + 15) >> 4), wa = units <= NB ? w - a.att0 : w;
+  PlUnit self{}, cross{};
+  if ((unsigned)wa < (unsigned)units && units <= NB) {
+    self = pl_unit<true>(a, wa);
+    cross = pl_unit<false>(a, wa);
+  }
+  __syncthreads();
+  int flip = 0;
+  auto turn = [&]() { return flip ^= 1; };
+  // items of a projection with N columns: 16 FB columns each, column tile fastest (tiles of one column range then share an XCD)
+  auto project = [&](auto fbt, int N, const PlWeight& W, const float* cs, const float* bf, const char* A, bool plain,
+                     const char* stats, auto&& epi) -> bool {
+    constexpr int FB = decltype(fbt)::value;
+    const int nt = pl_opaque(N / (16 * FB)), items = nt * a.RT;
+    for (int it = wr; it < items; it += NB) {
+      const int mt = it / nt;
+      if (!pl_project<WT, NW, KSD, FB, NS>(a, L, turn(), W, cs, bf, A, plain, stats, mt * 16, a.R, (it - mt * nt) * 16 * FB, epi)) return false;
+    }
+    return true;
+  };
+  auto sum = [&](auto kst, const PlWeight& W, const float* vecs, const char* A, const char* stats_prev, bool first, bool last,
+                 char* xg, char* st) -> bool {
+    constexpr int KS = decltype(kst)::value, nt = d / 16;
+    int round = 0;
+    for (int it = w; it < nt * a.RT; it += NB, ++round) {
+      const int mt = it / nt;
+      if (!pl_sum<WT, NW, KS, NS>(a, L, turn(), L.resid[round], W, vecs, A, stats_prev, first, last, xg, st, mt * 16, (it - mt * nt) * 16))
+        return false;
+    }
+    return true;
+  };
+  typedef std::integral_constant<int, KSD> CD;
+  typedef std::integral_constant<int, KSF> CF;
+  typedef std::integral_constant<int, FBW> CW;
+  typedef std::integral_constant<int, 1> C1;
+  for (int l = 0; l < a.n_layers; ++l) {
+    const PlLayer& Y = reinterpret_cast<const PlLayer*>(L.layers)[l];
+    const PlExch ex(a.exch, l, a.RP, d, F), before(a.exch, l - 1, a.RP, d, F);
+    const bool top = l == 0;
+    // queries, keys, values (appended to the cache as well)
+    const char* st0 = top ? nullptr : before.st(2);
+    if (!project(CW{}, 3 * d, Y.wqkv, Y.qkv_cs, Y.qkv_bf, top ? reinterpret_cast<const char*>(a.xb) : before.xg(2), top, st0,
+                    [&](int row, int n, const float (&v)[4]) {
+          const int part = n / d, c = n - part * d;
+          const u32x2 p = pl_pack4(v);
+          char* dst = (part == 0 ? ex.q(0) : part == 1 ? ex.kx() : ex.vx()) + pl_at(a.RP, row, c);
+          pl_store8(dst, p[0], p[1]);
+          const int b = a.row_b[row];
+          if (part == 0 || b < 0) return;
+          bf16* cache = (part == 1 ? a.kc : a.vc) + a.kv_layer * l +
+                        (((size_t)b * a.H + (c >> 6)) * a.Lcap + a.row_pos[row]) * kHeadDim + (c & 63);
+          *reinterpret_cast<u32x2*>(cache) = p;
+        })) return;
+    if (!pl_attention<NW, true, false, false>(a, ex, l, wa, units, self, L, [] { return true; })) return;
+    if (!sum(CD{}, Y.wo, Y.vo, ex.att(0), st0, top, false, ex.xg(0), ex.st(0))) return;
+    if (units <= NB) {   // a unit's workgroup forms its queries itself: a product of 64 columns instead of a hand-over
+      if (!pl_attention<NW, false, true, KV8>(a, ex, l, wa, units, cross, L, [&] {
+            const int row0 = cross.b * a.T + cross.q0, n0 = cross.h * kHeadDim;
+            if (!pl_project<WT, NW, KSD, 4, NS>(a, L, turn(), Y.cwq, Y.cq_cs, Y.cq_bf, ex.xg(0), false, ex.st(0), row0, (cross.b + 1) * a.T,
+                                            n0, [&](int row, int n, const float (&v)[4]) {
+                  *reinterpret_cast<u32x2*>(&L.q[(row - row0) * kPlQPitch + n - n0]) = pl_pack4(v);
+                })) return false;
+            lds_barrier();
+            return true;
+          })) return;
+    } else {
+      if (!project(C1{}, d, Y.cwq, Y.cq_cs, Y.cq_bf, ex.xg(0), false, ex.st(0), [&](int row, int n, const float (&v)[4]) {
+            const u32x2 p = pl_pack4(v);
+            pl_store8(ex.q(1) + pl_at(a.RP, row, n), p[0], p[1]);
+          })) return;
+      if (!pl_attention<NW, false, false, KV8>(a, ex, l, wa, units, cross, L, [] { return true; })) return;
+    }
+    if (!sum(CD{}, Y.cwo, Y.vco, ex.att(1), ex.st(0), false, false, ex.xg(1), ex.st(1))) return;
+    if (!project(CW{}, F, Y.w1, Y.w1_cs, Y.w1_bf, ex.xg(1), false, ex.st(1), [&](int row, int n, const float (&v)[4]) {
+          const float r[4] = {fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f)};
+          const u32x2 p = pl_pack4(r);
+          pl_store8(ex.hid() + pl_at(a.RP, row, n), p[0], p[1]);
+        })) return;
+    if (!sum(CF{}, Y.w2, Y.v2, ex.hid(), ex.st(1), false, l + 1 == a.n_layers, ex.xg(2), ex.st(2))) return;
+  }
+}
+
+// ---- launcher ------------------------------------------------------------------------------
+bool persist_supported(int layers, int d, int F) {
+  return layers <= kPlLayers && ((d == 512 && F == 2048) || (d == 1024 && F == 4096));
+}
+size_t persist_exch_bytes(int rows, int layers, int d, int F) { return (size_t)layers * pl_layer_bytes((rows + 15) & ~15, d, F); }
+
+int persist_plan(PlArgs& a, int d, int F) {
+  a.RP = (a.R + 15) & ~15;
+  a.RT = a.RP / 16;
+  a.d = d;
+  // The narrowest items of the wide projections that leave every workgroup one kind of item; failing that, that give every
+  // workgroup at most one of them.
+  const int sums = d / 16 * a.RT, most = 3 * d > F ? 3 * d : F, units = a.B * a.H * ((a.T + 15) >> 4);
+  auto wide = [&](int fb) { const int n = most / (16 * fb) * a.RT; return n > sums ? n : sums; };
+  int fb = 2;
+  while (fb < 4 && sums + units + wide(fb) > kPlBlocks) fb *= 2;
+  if (sums + units + wide(fb) > kPlBlocks) {
+    fb = 2;
+    while (fb < 4 && wide(fb) > kPlBlocks) fb *= 2;
+  }
+  a.fbw = fb;
+  int NB = sums + units + wide(fb);
+  if (NB > kPlBlocks) NB = kPlBlocks;
+  a.att0 = sums + units <= NB ? sums : 0;
+  return (sums + NB - 1) / NB <= kPlRounds ? NB : 0;
+}
+
+template <class WT, bool KV8, int NW, int KSD, int KSF, int FBW>
+static hipError_t pl_launch(hipStream_t st, const PlArgs& a, int NB) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pl_decoder_kernel<WT, KV8, NW, KSD, KSF, FBW>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(PlLds<NW>));
+  if (attr != hipSuccess) return attr;
+  static_assert(sizeof(PlLds<NW>) <= 80 * 1024, "two workgroups per CU");
+  SD_LAUNCH_TIMED((pl_decoder_kernel<WT, KV8, NW, KSD, KSF, FBW>), dim3(NB), dim3((64 * NW)), sizeof(PlLds<NW>), st, a);
+  return hipGetLastError();
+}
+template <class WT, bool KV8>
+static hipError_t pl_launch_dims(hipStream_t st, const PlArgs& a, int d, int NB) {
+  if (d == 512) return a.fbw == 2 ? pl_launch<WT, KV8, 4, 4, 16, 2>(st, a, NB) : pl_launch<WT, KV8, 4, 4, 16, 4>(st, a, NB);
+  return a.fbw == 2 ? pl_launch<WT, KV8, 8, 4, 16, 2>(st, a, NB) : pl_launch<WT, KV8, 8, 4, 16, 4>(st, a, NB);
+}
+
+hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F) {
+  if (a.R < 1 || a.T < 1 || a.T > 32 || a.R != a.B * a.T || !persist_supported(a.n_layers, d, F)) return hipErrorInvalidValue;
+  const int NB = persist_plan(a, d, F);
+  if (NB < 1) return hipErrorInvalidValue;
+  if (a.fp8) return a.xk_scale ? pl_launch_dims<fp8, true>(st, a, d, NB) : pl_launch_dims<fp8, false>(st, a, d, NB);
+  return a.xk_scale ? pl_launch_dims<bf16, true>(st, a, d, NB) : pl_launch_dims<bf16, false>(st, a, d, NB);
+}
+
+}  // namespace sd

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(64 * kSkAttnWaves) void sk_attn_o_kernel(SkSrc resi
   // the block's 16 columns of the sublayer's input (for the residual add) are requested now
   // (rows wave, wave + 8, ... of every wave) and normalised after the attention, whose own
   // requests travel at the same time
-  SkHidden<PER, false, TWO ? 4 : 2, kSkAttnWaves> hs;
+  SkHidden<PER, TWO ? 4 : 2, kSkAttnWaves> hs;
   if (kwave) sk_wload<steps>(W, d, n0, d, k0, wf);
   const bf16 bias_n = bias[n0 + (threadIdx.x & 15)];   // for the epilogue (sk_reduce: column threadIdx % 16)
   const float ws_n = sk_wscale<WT>(wscale, n0 + (threadIdx.x & 15));

@@ -39,12 +39,11 @@ struct SkLds {
 // A wave takes rows base, base + STRIDE, ...; it requests the data of RU of them (and the
 // LayerNorm parameters, once) before it reduces any, so the prologue costs one memory round
 // trip for RU rows per wave.
-// COH: the fp32 rows were written by other workgroups of the running kernel.  n0b: a second
-// 16-column residual slice (slot 1 of hown, [2][32][16]); negative: none.
+// n0b: a second 16-column residual slice (slot 1 of hown, [2][32][16]); negative: none.
 // A lane holds VEC consecutive columns per 64*VEC-column group (VEC = 4 when d % 256 == 0), so a
 // row is fetched with 16-byte loads: the prologue's cost is the number of load instructions
 // the CU has to issue, not their bytes.
-template <int PER, bool COH = false, int RU = 4, int STRIDE = 4>
+template <int PER, int RU = 4, int STRIDE = 4>
 struct SkHidden {
   static constexpr int d = 64 * PER, pitch = d + kSkPad;
   static constexpr int VEC = PER % 4 == 0 ? 4 : (PER % 2 == 0 ? 2 : 1);
@@ -67,30 +66,16 @@ struct SkHidden {
   __device__ __forceinline__ static void load_vec(const T* p, float* out) {   // VEC values -> fp32
     if constexpr (sizeof(T) == 4) {
       if constexpr (VEC == 4) {
-        f32x4 t;
-        if (COH) {
-          const unsigned long long* q = reinterpret_cast<const unsigned long long*>(p);
-          unsigned long long u[2] = {__hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                                     __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
-          __builtin_memcpy(&t, u, 16);
-        } else {
-          t = *reinterpret_cast<const f32x4*>(p);
-        }
+        const f32x4 t = *reinterpret_cast<const f32x4*>(p);
         out[0] = t[0]; out[1] = t[1]; out[2] = t[2]; out[3] = t[3];
       } else if constexpr (VEC == 2) {
         float t[2];
-        if (COH) {
-          unsigned long long u = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-          __builtin_memcpy(t, &u, 8);
-        } else {
-          __builtin_memcpy(t, p, 8);
-        }
+        __builtin_memcpy(t, p, 8);
         out[0] = t[0]; out[1] = t[1];
       } else {
-        out[0] = COH ? ld_coh(p) : p[0];
+        out[0] = p[0];
       }
-    } else {   // bf16 (read-only data: never written by the running kernel)
+    } else {   // bf16
       if constexpr (VEC == 4) {
         const bf16x4 t = *reinterpret_cast<const bf16x4*>(p);
         out[0] = (float)t[0]; out[1] = (float)t[1]; out[2] = (float)t[2]; out[3] = (float)t[3];
@@ -133,7 +118,7 @@ struct SkHidden {
         for (int j = 0; j < NV; ++j) {
           float ev[VEC], pv[VEC];
           load_vec(e + col(j * VEC, lane), ev);
-          SkHidden<PER, false, RU, STRIDE>::load_vec(p + col(j * VEC, lane), pv);
+          SkHidden<PER, RU, STRIDE>::load_vec(p + col(j * VEC, lane), pv);
 #pragma unroll
           for (int i = 0; i < VEC; ++i) v[u][j * VEC + i] = ev[i] * sc + pv[i];
         }
@@ -242,7 +227,7 @@ struct SkHidden {
 template <int PER, int NW, int PREG = 128>
 __device__ __forceinline__ void sk_hidden_sum(const SkSrc& s, int R, int nrows, bf16* hb, float* hown, int n0,
                                               bool want_hb, int n0b) {
-  typedef SkHidden<PER, false, 1, NW> HS;
+  typedef SkHidden<PER, 1, NW> HS;
   constexpr int d = 64 * PER, VEC = HS::VEC, NV = HS::NV;
   constexpr int PB = (PREG / PER) < 1 ? 1 : (PREG / PER);   // partial slices held in registers at a time
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -305,22 +290,22 @@ __device__ __forceinline__ void sk_hidden_sum(const SkSrc& s, int R, int nrows, 
   }
 }
 
-template <int PER, bool COH = false>
+template <int PER>
 __device__ __forceinline__ void sk_hidden(const SkSrc& s, int R, int nrows, bf16* hb, float* hown, int n0,
                                           bool want_hb, int n0b = -64) {
-  if (!COH && s.np > 0) {   // (same for the whole grid)
+  if (s.np > 0) {   // (same for the whole grid)
     sk_hidden_sum<PER, 4>(s, R, nrows, hb, hown, n0, want_hb, n0b);
     return;
   }
   const int wave = (threadIdx.x >> 6) & 3;
   if (PER <= 8 && nrows > 16) {   // eight rows per wave at once: still one round trip for 32 rows
-    SkHidden<PER, COH, 8> hs;
+    SkHidden<PER, 8> hs;
     hs.params(s);
     hs.load(s, R, wave);
     hs.finish(s, R, nrows, wave, hb, hown, n0, want_hb, n0b);
     return;
   }
-  SkHidden<PER, COH> hs;
+  SkHidden<PER> hs;
   hs.params(s);
   for (int base = wave; base < nrows; base += 16) {
     hs.load(s, R, base);

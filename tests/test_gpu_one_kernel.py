@@ -1,0 +1,87 @@
+"""The decoder layers of a pass of few rows as one kernel (d_model 512 / 1024): row tiles and their remainders, queries beyond
+one tile of 16, key chunks split over the waves and not, a unit of attention per workgroup and per wave, E4M3 weights and
+cross keys / values, against the oracle; the path a second context takes; replays of a captured pass."""
+import numpy as np
+import pytest
+import torch
+
+import cases
+import gpu_harness as gh
+from paper_2203_16487_amd import binding as sd
+from paper_2203_16487_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def desc(d, layers=2):
+    return synth.ModelDesc(0, layers, d, d // 64, 4 * d, 1003, 64, 300).resolved()
+
+
+def check(case, out):
+    err = float(np.abs(out["logits"] - case.logits).max())
+    exact, excused, bad = cases.compare_decisions(case, out["accept"], out["next"])
+    assert err <= max(2e-2, 0.04 * float(case.logits.std())), err
+    assert not bad, bad
+
+
+@pytest.mark.parametrize("d,B,k,S,lo,hi,opts", [
+    (512, 1, 1, 5, 0, 0, {}),                # two rows, nothing cached
+    (512, 1, 16, 40, 31, 31, {}),            # 17 rows: a second query tile of one row
+    (512, 7, 10, 40, 0, 75, {}),             # 77 rows, sequences across row tiles
+    (512, 2, 15, 200, 180, 220, {}),         # every wave has key chunks
+    (512, 42, 2, 20, 0, 30, {}),             # 126 rows, a wave per unit of attention
+    (1024, 1, 25, 90, 57, 57, {}),
+    (1024, 16, 3, 30, 0, 40, {}),            # 64 rows, the most
+    (512, 3, 9, 50, 0, 40, {sd.SPECDEC_OPT_FP8_WEIGHTS: 1}),
+    (512, 3, 9, 50, 0, 40, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
+    (1024, 1, 30, 33, 9, 9, {sd.SPECDEC_OPT_FP8_WEIGHTS: 1, sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
+])
+def test_against_oracle(d, B, k, S, lo, hi, opts):
+    case = cases.make_verify_case(desc(d), seed=d + 10 * B + k, B=B, S=S, k=k, beta=3, tau=1.0, len_lo=lo, len_hi=hi, drafts="random",
+                                  ragged_src=True, fp8=sd.SPECDEC_OPT_FP8_WEIGHTS in opts, fp8_kv=sd.SPECDEC_OPT_FP8_CROSS_KV in opts)
+    cases.run_oracle(case)
+    ses = gh.open_verifier(case, options=opts, fill=0xFF)
+    out = gh.gpu_verify(ses, case)
+    again = gh.gpu_verify(ses, case)
+    L = case.L_max + k + 1
+    K, V = gh.gpu_cache(ses, case, L)
+    ses.close()
+    check(case, out)
+    assert np.array_equal(out["logits"], again["logits"])
+    for b, st in enumerate(case.states):
+        j = int(case.lens[b])
+        for l in range(case.desc.dec_layers):
+            assert np.abs(K[l, b, j:j + k + 1] - st.K[l][j:j + k + 1]).max() <= 3e-2, (b, l)
+            assert np.abs(V[l, b, j:j + k + 1] - st.V[l][j:j + k + 1]).max() <= 3e-2, (b, l)
+
+
+def test_two_contexts_and_replays():
+    case = cases.make_verify_case(desc(512), seed=5, B=2, S=30, k=5, beta=3, tau=1.0, len_lo=3, len_hi=20, drafts="greedy",
+                                  ragged_src=True)
+    cases.run_oracle(case)
+    first = gh.open_verifier(case, fill=0xFF)
+    out = gh.gpu_verify(first, case)
+    check(case, out)
+    second = gh.open_verifier(case, fill=0xFF)
+    assert np.array_equal(gh.gpu_verify(second, case)["logits"], out["logits"])
+    other = torch.cuda.Stream()
+    other.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(other):                    # (two streams: other kernels than the first context's)
+        check(case, gh.gpu_verify(second, case))
+    other.synchronize()
+    second.close()
+    d, acc, nxt = first.i32(case.drafts), torch.zeros(2, dtype=torch.int32, device="cuda"), torch.zeros(2, dtype=torch.int32, device="cuda")
+    logits = torch.zeros((2, 6, case.desc.vocab), dtype=torch.float32, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        sd.specdec_verify(first.ctx, d, case.k, case.beta, case.tau, acc, nxt, logits)
+    for _ in range(4):
+        logits.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(logits.cpu().numpy(), out["logits"])
+        assert acc.cpu().tolist() == out["accept"].tolist() and nxt.cpu().tolist() == out["next"].tolist()
+        assert np.array_equal(gh.gpu_verify(first, case)["logits"], out["logits"])
+    first.close()
