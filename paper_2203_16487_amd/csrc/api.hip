@@ -201,8 +201,8 @@ bool desc_ok(const specdec_model_desc* d) {
 }
 constexpr long kPrefillRows = 8192;
 // Most rows of a pass the one-kernel decoder is asked for: with more, launches cost less than what its workgroups, that see
-// 16 rows each, read more (d = 512: 121 rows 171 against 231 us; d = 1024: 44 rows 231 / 292, 77 323 / 313).
-constexpr size_t persist_rows(int d) { return d <= 512 ? 128 : 64; }
+// 32 rows each, read more (d = 512: 253 rows 226 against 258 us, 286 281 / 282; d = 1024: 121 rows 294 / 315, 176 371 / 365).
+constexpr size_t persist_rows(int d) { return d <= 512 ? 256 : 128; }
 constexpr int kEncT = 12, kDecT = 20;
 int n_weights(const specdec_model_desc* d) { return 1 + kEncT * d->enc_layers + kDecT * d->dec_layers; }
 

@@ -250,7 +250,7 @@ struct PlArgs {
   int fp8;                                // the layers' weights are codes
   char* exch;                             // persist_exch_bytes, every byte 0xff when the kernel starts
   unsigned* err;                          // sticky error flag
-  int RP, RT, d, fbw, att0;               // filled by the launcher
+  int RP, d, mr, fbw, att0, wpu;          // filled by the launcher
 };
 constexpr int kPlBlocks = 256;            // most workgroups of a pass
 bool persist_supported(int layers, int d, int F);

@@ -11,14 +11,16 @@
 // No word of a result is ever stored as kPoison (not_poison).
 //
 // Work items of a stage are dealt to the workgroups round robin; the three residual-sum products of a layer give a workgroup
-// the same tile each time, so that the fp32 residual stays in its LDS.  A projection item is 16 rows x 16 FB columns: the
-// waves split K, each lane requests its weight fragments before it waits for the rows (they arrive meanwhile), the
-// partial tiles are summed through LDS in wave order, and wave f < FB finishes columns 16 f .. + 15.  LayerNorm is folded into
-// the products as in the general kernels (gemm.hip), with statistics per 16 columns.
+// the same tile each time, so that the fp32 residual stays in its LDS.  An item is 16 MR rows x 16 FB columns: the
+// waves split K, each lane requests its weight fragments before it waits for the rows (they arrive meanwhile), the partial
+// tiles are summed through LDS in wave order, and the waves divide the 16 x 16 results.  LayerNorm is folded into the products as
+// in the general kernels (gemm.hip), with statistics per 16 columns.
 //
-// What bounds it: the chain of 7 hand-overs a layer.  A whole verify pass, separate
-// kernels -> this one: d = 512, 6 layers, 11 rows 196 -> 124 us; 77 rows 241 -> 161; d = 1024, 26 rows of E4M3 weights
-// 303 -> 224.
+// What bounds it: the chain of 7 hand-overs a layer.  A whole verify pass, separate kernels -> this one: d = 512, 6 layers, 11 rows 196 -> 124 us; 77 rows 241 -> 161; d = 1024, 26 rows of E4M3 weights
+// 303 -> 224.  Beyond 128 rows (d = 1024: 64), items of 32 rows: 176 rows of d = 512 251 -> 221, 121 of d = 1024 315 -> 294.
+// Larger ones were tried (48 x 64, 352 rows) and are level with separate kernels: every item fetches its rows and weights at the
+// 60 - 75 GB/s one CU takes in, whether the rows come through the L2 (counters instead of kPoison) or not, and whether or not
+// the next weights are requested ahead.
 //
 // Waits are bounded: after kPlSpinMax polls, or once another workgroup has raised the error flag, a wave raises it and ends;
 // the host reports accept_len = -1.  All workgroups are co-resident by construction (there are no more than CUs and
@@ -67,28 +69,6 @@ __device__ __forceinline__ bool pl_again(unsigned& spins, unsigned* err) {
   return true;
 }
 
-// N requests at off + i * stride (bytes from A), repeated until they hold no kPoison; lanes with on = false read along and are
-// not waited for (their addresses are valid).  M of 8 bytes (M = 0: none) at qoff + i * qstride from Q in the same rounds.
-template <int N, int M>
-__device__ __forceinline__ bool pl_poll(u32x4 (&f)[N], PlBuf A, int off, int stride, bool on, u32x2* s, PlBuf Q, int qoff,
-                                        int qstride, unsigned* err) {
-  unsigned spins = 0;
-  while (true) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) f[i] = pl_request(A, off, i * stride);
-#pragma unroll
-    for (int i = 0; i < M; ++i) s[i] = __builtin_amdgcn_raw_buffer_load_b64(Q, qoff, i * qstride, kPlSc1);
-    bool bad = false;
-#pragma unroll
-    for (int i = 0; i < N; ++i) bad |= pl_missing(f[i]);
-#pragma unroll
-    for (int i = 0; i < M; ++i) bad |= s[i][0] == kPoison || s[i][1] == kPoison;
-    if (!__builtin_amdgcn_ballot_w64(bad && on)) return true;
-    if (!pl_again(spins, err)) return false;
-    asm volatile("" ::: "memory");
-  }
-}
-
 // sums over the four 16-lane rows (lanes lq + 16 g), result in all of them
 __device__ __forceinline__ float pl_row_sum(float v) {
   const unsigned u = __builtin_bit_cast(unsigned, v);
@@ -133,17 +113,22 @@ __device__ __forceinline__ int pl_opaque(int v) {
 
 constexpr int kPlLayers = 32;
 constexpr int kPlQPitch = 72;   // (16 rows of 144 bytes: a 16-byte read of every row meets all banks once)
-constexpr int kPlRounds = 4;   // residual tiles a workgroup can hold
 
-template <int NW>
+// NP: pairs (row tile, column tile) of the largest item; more than four: one set of partial tiles instead of two in turn
+template <int NW, int NP>
 struct PlLds {
-  f32x4 red[2][NW * 4 * 64];                // partial tiles, two in turn
-  float resid[kPlRounds][16 * 16];
-  float stat[2][32];                              // {rstd, -mean rstd} of the 16 rows, beside red
+  static constexpr int kFlips = NP > 4 ? 1 : 2, kRows = NP > 4 ? 32 : 16;
+  f32x4 red[kFlips][NW * NP * 64];                // partial tiles
+  float resid[kRows * 16];                        // of the workgroup's residual-sum tile
+  float stat[kFlips][2 * kRows];                  // {rstd, -mean rstd} of the rows, beside red
   bf16 q[16 * kPlQPitch];                         // queries of the workgroup's unit (cross-attention)
   unsigned long long layers[kPlLayers * sizeof(PlLayer) / 8];   // every stage's pointers
-  // attention: the value tiles of the waves ([32 keys][64], swizzled like the tile kernel's) in red[1], partial results in red[0]
-  __device__ __forceinline__ bf16* vs(int wave) { return reinterpret_cast<bf16*>(red[1]) + wave * (32 * 64); }
+  // attention: partial results in the first half of red, the value tiles of the waves ([32 keys][64], swizzled like the tile
+  // kernel's) in the second
+  static_assert(kFlips * NP >= 8, "attention's share of red");
+  __device__ __forceinline__ f32x4* om() { return red[0]; }
+  __device__ __forceinline__ float* ml() { return reinterpret_cast<float*>(red[0] + NW * 4 * 64); }
+  __device__ __forceinline__ bf16* vs(int wave) { return reinterpret_cast<bf16*>(red[0] + NW * 4 * 64) + wave * (32 * 64); }
 };
 
 // Exchange buffers of one layer, all in tiles of 16 columns, [column / 16][RP][16]: what one item produces lies together and
@@ -169,20 +154,24 @@ struct PlExch {   // (only the layer's base stays in registers)
 // element (row, k) of a buffer, bytes
 __device__ __forceinline__ int pl_at(int RP, int row, int k) { return ((k >> 4) * RP + row) * 32 + (k & 15) * 2; }
 
-// Product of one item: rows row0 .. row0 + 15 below rlim of A (exchange buffer, or plain rows), columns n0 .. n0 + 16 FB - 1 of
-// W [N][32 * 8 * KS].  Returns in v the finished sums of this lane, row row0 + lane % 16, columns n0 + 16 wave + 4 (lane / 16)
-// .. + 3, for waves < FB, and in ps the statistics of that row (stats null: {1, 0}), which the last wave waits for and reduces.
+// Product of one item: rows row0 .. row0 + 16 MR - 1 below rlim of A (exchange buffer, or plain rows), columns n0 .. n0 +
+// 16 FB - 1 of W [N][32 * NW * KS].  done(mr, f, v, s) receives the finished sums of row row0 + 16 mr + lane % 16, columns
+// n0 + 16 f + 4 (lane / 16) .. + 3 (on the waves these pairs fall to, f = wave % FB), and the statistics of that row (stats
+// null: {1, 0}); wave NW - 1 - mr reduces those of row tile mr.  late: the statistics are as new as the rows and are waited for
+// with them; otherwise they were there long ago and are taken first.
 // WT: bf16 values, or E4M3 codes that become bf16 operands as they arrive (the caller applies the columns' scales).
 template <class WT> struct PlFrag { typedef bf16x8 type; };
 template <> struct PlFrag<fp8> { typedef fp8x8 type; };
 __device__ __forceinline__ bf16x8 pl_operand(const bf16x8& f) { return f; }
 __device__ __forceinline__ bf16x8 pl_operand(const fp8x8& f) { return e4m3x8_to_bf16(f); }
-template <class WT, int NW, int KS, int FB, int NS>
-__device__ __forceinline__ bool pl_product(const PlArgs& a, PlLds<NW>& L, int flip, const void* Wv, const char* A, bool plain, int row0,
-                                           int rlim, int n0, const char* stats, f32x4& v, PlStat& ps) {
+template <class WT, int NW, int KS, int MR, int FB, int NS, bool LATE, class Lds, class Done>
+__device__ __forceinline__ bool pl_product(const PlArgs& a, Lds& L, int flip, const void* Wv, const char* A, bool plain, int row0,
+                                           int rlim, int n0, const char* stats, Done&& done) {
   constexpr int K = 32 * NW * KS;
+  static_assert(MR <= NW && NW % FB == 0, "a wave per row tile's statistics; a wave's column tile");
   const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
   f32x4* red = L.red[flip];
+  float* rstat = L.stat[flip];
   const WT* W = static_cast<const WT*>(Wv);
   typename PlFrag<WT>::type wf[FB][KS];
 #pragma unroll
@@ -192,117 +181,176 @@ __device__ __forceinline__ bool pl_product(const PlArgs& a, PlLds<NW>& L, int fl
       wf[f][u] = *reinterpret_cast<const typename PlFrag<WT>::type*>(W + (size_t)(n0 + 16 * f + lq) * K + (wave * KS + u) * 32 + 8 * g);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
-  const int row = min(row0 + lq, rlim - 1);
-  const bool on = row0 + lq < rlim;
-  f32x4 acc[FB];
+  const int smr = NW - 1 - wave;   // whose statistics this wave reduces
+  const bool has_stat = stats && smr < MR;
+  const int srow = min(row0 + 16 * smr + lq, rlim - 1);
+  const bool s_on = row0 + 16 * smr + lq < rlim;
+  u32x2 st[NS];
+  auto stat_request = [&]() {   // chunks g * NS .. of the row
+    const PlBuf sb = pl_buf(stats);
 #pragma unroll
-  for (int f = 0; f < FB; ++f) acc[f] = f32x4{0.f, 0.f, 0.f, 0.f};
-  constexpr int AC = KS > 16 ? 16 : KS;   // fragments waited for together
+    for (int i = 0; i < NS; ++i) st[i] = __builtin_amdgcn_raw_buffer_load_b64(sb, (g * NS * a.RP + srow) * 8, i * a.RP * 8, kPlSc1);
+  };
+  auto stat_missing = [&]() {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) bad |= st[i][0] == kPoison || st[i][1] == kPoison;
+    return bad && s_on;
+  };
+  unsigned spins = 0;
+  auto stat_reduce = [&]() {
+    const PlStat s = pl_stat<NS>(st, a.d);
+    if (g == 0) { rstat[32 * smr + 2 * lq] = s.rstd; rstat[32 * smr + 2 * lq + 1] = s.nmr; }
+  };
+  if (Lds::kFlips == 1) lds_barrier();   // the partial tiles and statistics of the item before have been read
+  if (!LATE && has_stat) {
+    stat_request();
+    while (__builtin_amdgcn_ballot_w64(stat_missing())) {
+      if (!pl_again(spins, a.err)) return false;
+      asm volatile("" ::: "memory");
+      stat_request();
+    }
+    stat_reduce();
+  }
+  // row fragments in chunks of CH, DEPTH chunks requested ahead; chunk c: k fragments (c / MR) * CH .. of row tile c % MR
+  constexpr int CH = 4, NC = MR * KS / CH, DEPTH = NC < 4 ? NC : 4;
+  static_assert(KS % CH == 0, "whole chunks");
   const PlBuf buf = pl_buf(A);
-  const int stride = a.RP * 64;
-#pragma unroll
-  for (int u0 = 0; u0 < KS; u0 += AC) {
-    u32x4 af[AC];
-    const int k = (wave * KS + u0) * 32 + 8 * g;
+  u32x4 af[DEPTH][CH];
+  auto request = [&](int c) {
+    const int row = min(row0 + 16 * (c % MR) + lq, rlim - 1), k = (wave * KS + c / MR * CH) * 32 + 8 * g;
     if (plain) {   // rows another kernel wrote, [R][K]
 #pragma unroll
-      for (int u = 0; u < AC; ++u) af[u] = *reinterpret_cast<const u32x4*>(A + ((size_t)row * K + k + u * 32) * 2);
-    } else if (u0 == 0 && wave == NW - 1 && stats) {   // chunks g * NS .. of the row
-      u32x2 st[NS];
-      if (!pl_poll<AC, NS>(af, buf, pl_at(a.RP, row, k), stride, on, st, pl_buf(stats), (g * NS * a.RP + row) * 8, a.RP * 8, a.err)) return false;
-      const PlStat s = pl_stat<NS>(st, a.d);
-      if (g == 0) { L.stat[flip][2 * lq] = s.rstd; L.stat[flip][2 * lq + 1] = s.nmr; }
+      for (int u = 0; u < CH; ++u) af[c % DEPTH][u] = *reinterpret_cast<const u32x4*>(A + ((size_t)row * K + k + u * 32) * 2);
     } else {
-      if (!pl_poll<AC, 0>(af, buf, pl_at(a.RP, row, k), stride, on, nullptr, buf, 0, 0, a.err)) return false;
+      const int off = pl_at(a.RP, row, k);
+#pragma unroll
+      for (int u = 0; u < CH; ++u) af[c % DEPTH][u] = pl_request(buf, off, u * a.RP * 64);
     }
+  };
+#pragma unroll
+  for (int c = 0; c < DEPTH; ++c) request(c);
+  if (LATE && has_stat) stat_request();
+  f32x4 acc[MR][FB];
+#pragma unroll
+  for (int mr = 0; mr < MR; ++mr)
+#pragma unroll
+    for (int f = 0; f < FB; ++f) acc[mr][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // waits for chunks c .. : what is in flight behind a missing one was requested as early, so all of it once more
+  auto arrive = [&](int c, int n) {
+    while (true) {
+      bool bad = false;
+#pragma unroll
+      for (int cc = c; cc < c + n; ++cc)
+#pragma unroll
+        for (int u = 0; u < CH; ++u) bad |= pl_missing(af[cc % DEPTH][u]) && row0 + 16 * (cc % MR) + lq < rlim;
+      if (LATE && has_stat && c == 0) bad |= stat_missing();
+      if (!__builtin_amdgcn_ballot_w64(bad)) return true;
+      if (!pl_again(spins, a.err)) return false;
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int cc = c; cc < c + DEPTH && cc < NC; ++cc) request(cc);
+      if (LATE && has_stat && c == 0) stat_request();
+    }
+  };
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    if (!plain && (c == 0 || c >= DEPTH) && !arrive(c, c == 0 ? DEPTH : 1)) return false;
+    if (LATE && c == 0 && has_stat) stat_reduce();
 #pragma unroll
     for (int f = 0; f < FB; ++f)
 #pragma unroll
-      for (int u = 0; u < AC; ++u)
-        acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl_operand(wf[f][u0 + u]), __builtin_bit_cast(bf16x8, af[u]), acc[f], 0, 0, 0);
+      for (int u = 0; u < CH; ++u)
+        acc[c % MR][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl_operand(wf[f][c / MR * CH + u]), __builtin_bit_cast(bf16x8, af[c % DEPTH][u]),
+                                                                 acc[c % MR][f], 0, 0, 0);
+    if (c + DEPTH < NC) request(c + DEPTH);
   }
 #pragma unroll
-  for (int f = 0; f < FB; ++f) {
-    mfma_settle(acc[f]);
-    red[(wave * FB + f) * 64 + lane] = acc[f];
-  }
+  for (int mr = 0; mr < MR; ++mr)
+#pragma unroll
+    for (int f = 0; f < FB; ++f) {
+      mfma_settle(acc[mr][f]);
+      red[((wave * MR + mr) * FB + f) * 64 + lane] = acc[mr][f];
+    }
   lds_barrier();
-  v = f32x4{0.f, 0.f, 0.f, 0.f};
-  ps = PlStat{1.f, 0.f};
-  if (wave < FB) {
-    f32x4 t[NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) t[w] = red[(w * FB + wave) * 64 + lane];
-    if (stats) ps = PlStat{L.stat[flip][2 * lq], L.stat[flip][2 * lq + 1]};
+  for (int p0 = 0; p0 < MR * FB; p0 += NW) {
+    const int p = p0 + wave;
+    if (p >= MR * FB) break;
+    f32x4 t[NW], v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t[w] = red[(w * MR * FB + p) * 64 + lane];
+    PlStat s{1.f, 0.f};
+    const int mr = p / FB;
+    if (stats) s = PlStat{rstat[32 * mr + 2 * lq], rstat[32 * mr + 2 * lq + 1]};
 #pragma unroll
     for (int w = 0; w < NW; ++w)
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] += t[w][e];
+    done(mr, p % FB, v, s);
   }
   return true;
 }
 
 // hidden(LayerNorm folded) W^T + b of one item; epi(row, n, float[4]) on live rows
-template <class WT, int NW, int KS, int FB, int NS, class Epi>
-__device__ __forceinline__ bool pl_project(const PlArgs& a, PlLds<NW>& L, int flip, const PlWeight& W, const float* cs, const float* bf,
+template <class WT, int NW, int KS, int MR, int FB, int NS, class Lds, class Epi>
+__device__ __forceinline__ bool pl_project(const PlArgs& a, Lds& L, int flip, const PlWeight& W, const float* cs, const float* bf,
                                            const char* A, bool plain, const char* stats, int row0, int rlim, int n0, Epi&& epi) {
   const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
-  const int n = n0 + 16 * min(wave, FB - 1) + 4 * g;
+  const int n = n0 + 16 * (wave % FB) + 4 * g;
   const f32x4 c4 = *reinterpret_cast<const f32x4*>(cs + n), b4 = *reinterpret_cast<const f32x4*>(bf + n);
   f32x4 w4 = {1.f, 1.f, 1.f, 1.f};
   if constexpr (sizeof(WT) == 1) w4 = *reinterpret_cast<const f32x4*>(W.scale + n);
-  f32x4 v;
-  PlStat s;
-  if (!pl_product<WT, NW, KS, FB, NS>(a, L, flip, W.p, A, plain, row0, rlim, n0, stats, v, s)) return false;
-  if (wave < FB) {
+  return pl_product<WT, NW, KS, MR, FB, NS, true>(a, L, flip, W.p, A, plain, row0, rlim, n0, stats, [&](int mr, int, const f32x4& v, const PlStat& s) {
     float o[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(sizeof(WT) == 1 ? v[e] * w4[e] : v[e], s.rstd, __builtin_fmaf(s.nmr, c4[e], b4[e]));
-    const int row = row0 + lq;
+    const int row = row0 + 16 * mr + lq;
     if (row < rlim) epi(row, n, o);
-  }
-  return true;
+  });
 }
 
-// residual sum of one item (FB = 1): y = LN_prev(x) + A W^T + b; xg, statistics and the workgroup's copy of y
-template <class WT, int NW, int KS, int NS>
-__device__ __forceinline__ bool pl_sum(const PlArgs& a, PlLds<NW>& L, int flip, float* resid, const PlWeight& W, const float* vecs,
+// residual sum of one item: y = LN_prev(x) + A W^T + b; xg, statistics and the workgroup's copy of y
+template <class WT, int NW, int KS, int MR, int NS, class Lds>
+__device__ __forceinline__ bool pl_sum(const PlArgs& a, Lds& L, int flip, float* resid, const PlWeight& W, const float* vecs,
                                        const char* A, const char* stats_prev, bool first, bool last, char* xg, char* st_out,
                                        int row0, int n0) {
   const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
-  const int n = n0 + 4 * g, row = min(row0 + lq, a.R - 1);
-  f32x4 cv[3], x, w4 = {1.f, 1.f, 1.f, 1.f};
+  const int n = n0 + 4 * g;
+  f32x4 cv[3], w4 = {1.f, 1.f, 1.f, 1.f};
   if constexpr (sizeof(WT) == 1) w4 = *reinterpret_cast<const f32x4*>(W.scale + n);
 #pragma unroll
   for (int i = 0; i < 3; ++i) cv[i] = *reinterpret_cast<const f32x4*>(vecs + i * a.d + n);
-  if (first) x = *reinterpret_cast<const f32x4*>(a.x + (size_t)row * a.d + n);
-  else x = *reinterpret_cast<const f32x4*>(resid + lq * 16 + 4 * g);
-  f32x4 v;
-  PlStat s;
-  if (!pl_product<WT, NW, KS, 1, NS>(a, L, flip, W.p, A, false, row0, a.R, n0, stats_prev, v, s)) return false;
-  if (wave != 0) return true;
-  float y[4], gx[4], sum = 0.f, ss = 0.f;
+  static_assert(MR <= NW, "a pair per wave");
+  const int mine = min(wave, MR - 1);
+  float* own = resid + (mine * 16 + lq) * 16 + 4 * g;
+  f32x4 x;
+  if (first) x = *reinterpret_cast<const f32x4*>(a.x + (size_t)min(row0 + 16 * mine + lq, a.R - 1) * a.d + n);
+  else x = *reinterpret_cast<const f32x4*>(own);
+  return pl_product<WT, NW, KS, MR, 1, NS, false>(a, L, flip, W.p, A, false, row0, a.R, n0, stats_prev, [&](int mr, int, const f32x4& v, const PlStat& s) {
+    const int row = row0 + 16 * mr + lq;
+    float y[4], gx[4], sum = 0.f, ss = 0.f;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    y[e] = (sizeof(WT) == 1 ? v[e] * w4[e] : v[e]) + __builtin_fmaf(__builtin_fmaf(x[e], s.rstd, s.nmr), cv[0][e], cv[1][e]);
-    gx[e] = y[e] * cv[2][e];
-  }
-  const bool live = row0 + lq < a.R;
-  if (last) {
-    if (live) *reinterpret_cast<f32x4*>(a.y + (size_t)row * a.d + n) = f32x4{y[0], y[1], y[2], y[3]};
-    return true;
-  }
-  const u32x2 w = pl_pack4(gx);
-  if (live) pl_store8(xg + pl_at(a.RP, row, n), w[0], w[1]);
+    for (int e = 0; e < 4; ++e) {
+      y[e] = (sizeof(WT) == 1 ? v[e] * w4[e] : v[e]) + __builtin_fmaf(__builtin_fmaf(x[e], s.rstd, s.nmr), cv[0][e], cv[1][e]);
+      gx[e] = y[e] * cv[2][e];
+    }
+    const bool live = row < a.R;
+    if (last) {
+      if (live) *reinterpret_cast<f32x4*>(a.y + (size_t)row * a.d + n) = f32x4{y[0], y[1], y[2], y[3]};
+      return;
+    }
+    const u32x2 w = pl_pack4(gx);
+    if (live) pl_store8(xg + pl_at(a.RP, row, n), w[0], w[1]);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) { sum += y[e]; ss = __builtin_fmaf(y[e], y[e], ss); }
-  sum = pl_row_sum(sum);
-  ss = pl_row_sum(ss);
-  if (live && g == 0)
-    pl_store8(st_out + ((n0 >> 4) * a.RP + row) * 8, __builtin_bit_cast(unsigned, sum),
-              __builtin_bit_cast(unsigned, fmaxf(ss - sum * sum * (1.0f / 16), 0.f)));
-  *reinterpret_cast<f32x4*>(resid + lq * 16 + 4 * g) = f32x4{y[0], y[1], y[2], y[3]};
-  return true;
+    for (int e = 0; e < 4; ++e) { sum += y[e]; ss = __builtin_fmaf(y[e], y[e], ss); }
+    sum = pl_row_sum(sum);
+    ss = pl_row_sum(ss);
+    if (live && g == 0)
+      pl_store8(st_out + ((n0 >> 4) * a.RP + row) * 8, __builtin_bit_cast(unsigned, sum),
+                __builtin_bit_cast(unsigned, fmaxf(ss - sum * sum * (1.0f / 16), 0.f)));
+    *reinterpret_cast<f32x4*>(own) = f32x4{y[0], y[1], y[2], y[3]};
+  });
 }
 
 // Attention of one unit: 16 queries (the last ones of a sequence: fewer) of one (sequence, head) pair.  at: the keys its
@@ -346,12 +394,15 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
   // K operands: tile i, row lq  <->  key c0 + 8*(lq/4) + 4*i + lq%4; values as whole rows (lane -> row 8*i + lane/8, dims
   // 8*(lane%8) .. + 7) or, key-blocked, as operands.  What the cache holds is requested once, the pass's own rows until they
   // are there.
-  u32x4 kf[4], vf[4], f[2];
-  fp8x8 kf8[4], vf8[4];
-  f32x4 sck[2], scv[2];
+  struct Chunk {   // (one of the two forms)
+    u32x4 kf[4], vf[4];
+    fp8x8 kf8[4], vf8[4];
+    f32x4 sck[2], scv[2];
+  } now, next;
+  u32x4 f[2];
   auto key_k = [&](int c0, int i) { return c0 + 8 * (lq >> 2) + 4 * i + (lq & 3); };
   auto key_v = [&](int c0, int i) { return c0 + 8 * i + (lane >> 3); };
-  auto fetch = [&](int c0) {
+  auto fetch = [&](int c0, Chunk& t) {
     const int last = (SELF ? j : nkey) - 1;
     if (SELF && c0 > last) return;
     if constexpr (KV8) {
@@ -359,24 +410,24 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const char* p = kb + max(min(key_k(c0, i), last), 0) * 64 + g * 8;
-        kf8[2 * i] = *reinterpret_cast<const fp8x8*>(p);
-        kf8[2 * i + 1] = *reinterpret_cast<const fp8x8*>(p + 32);
-        sck[i] = *reinterpret_cast<const f32x4*>(a.xk_scale + sc0 + k8 + 4 * i);
-        scv[i] = *reinterpret_cast<const f32x4*>(a.xv_scale + sc0 + k8 + 4 * i);
+        t.kf8[2 * i] = *reinterpret_cast<const fp8x8*>(p);
+        t.kf8[2 * i + 1] = *reinterpret_cast<const fp8x8*>(p + 32);
+        t.sck[i] = *reinterpret_cast<const f32x4*>(a.xk_scale + sc0 + k8 + 4 * i);
+        t.scv[i] = *reinterpret_cast<const f32x4*>(a.xv_scale + sc0 + k8 + 4 * i);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) vf8[i] = *reinterpret_cast<const fp8x8*>(vb + vt_off(k8, i * 16 + lq));
+      for (int i = 0; i < 4; ++i) t.vf8[i] = *reinterpret_cast<const fp8x8*>(vb + vt_off(k8, i * 16 + lq));
       return;
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const char* p = kb + max(min(key_k(c0, i), last), 0) * 128 + g * 16;
-      kf[2 * i] = *reinterpret_cast<const u32x4*>(p);
-      kf[2 * i + 1] = *reinterpret_cast<const u32x4*>(p + 64);
+      t.kf[2 * i] = *reinterpret_cast<const u32x4*>(p);
+      t.kf[2 * i + 1] = *reinterpret_cast<const u32x4*>(p + 64);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      vf[i] = *reinterpret_cast<const u32x4*>(SELF ? vb + min(key_v(c0, i), last) * 128 + (lane & 7) * 16
+      t.vf[i] = *reinterpret_cast<const u32x4*>(SELF ? vb + min(key_v(c0, i), last) * 128 + (lane & 7) * 16
                                                    : vb + vt_off(min(c0 + 8 * g, cap - 8), i * 16 + lq) * 2);
   };
   // the chunk's own rows (SELF) and, with_q, the queries
@@ -414,8 +465,8 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
           for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              kf[i][e] = key_k(c0, i >> 1) >= j ? kn[i][e] : kf[i][e];
-              vf[i][e] = key_v(c0, i) >= nkey ? 0u : key_v(c0, i) >= j ? vn[i][e] : vf[i][e];
+              now.kf[i][e] = key_k(c0, i >> 1) >= j ? kn[i][e] : now.kf[i][e];
+              now.vf[i][e] = key_v(c0, i) >= nkey ? 0u : key_v(c0, i) >= j ? vn[i][e] : now.vf[i][e];
             }
         }
         return true;
@@ -425,7 +476,7 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
     }
   };
   const int cfirst = kw * 32;
-  fetch(cfirst);
+  fetch(cfirst, now);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (QLDS) {   // formed by this workgroup
@@ -439,23 +490,21 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
   const bf16x8 q0 = __builtin_bit_cast(bf16x8, f[0]), q1 = __builtin_bit_cast(bf16x8, f[1]);
   const int lim = t.q0 + lq < a.T ? (SELF ? j + t.q0 + lq + 1 : nkey) : 0;
   for (int c0 = cfirst; c0 < nkey; c0 += kstep * 32) {
-    if (c0 != cfirst) {
-      fetch(c0);
-      if (!await(c0, false)) return false;
-    }
+    const int c1 = c0 + kstep * 32;
+    if (c1 < nkey) fetch(c1, next);
     bf16x8 vo[4];
     if constexpr (KV8) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        kf[i] = __builtin_bit_cast(u32x4, e4m3x8_to_bf16(kf8[i]));
-        vf[i] = __builtin_bit_cast(u32x4, e4m3x8_to_bf16(vf8[i]));
+        now.kf[i] = __builtin_bit_cast(u32x4, e4m3x8_to_bf16(now.kf8[i]));
+        now.vf[i] = __builtin_bit_cast(u32x4, e4m3x8_to_bf16(now.vf8[i]));
       }
     }
     if constexpr (SELF) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = 8 * i + (lane >> 3);
-        *reinterpret_cast<u32x4*>(Vs + r * 64 + (((lane & 7) ^ ((r & 2) << 1)) << 3)) = vf[i];
+        *reinterpret_cast<u32x4*>(Vs + r * 64 + (((lane & 7) ^ ((r & 2) << 1)) << 3)) = now.vf[i];
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
@@ -467,21 +516,21 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
       }
     } else {
 #pragma unroll
-      for (int et = 0; et < 4; ++et) vo[et] = __builtin_bit_cast(bf16x8, vf[et]);
+      for (int et = 0; et < 4; ++et) vo[et] = __builtin_bit_cast(bf16x8, now.vf[et]);
       if (c0 + 32 > nkey) {
 #pragma unroll
         for (int et = 0; et < 4; ++et) vo[et] = zero_tail(vo[et], nkey - (c0 + 8 * g));
       }
     }
     f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-    s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[0]), q0, s0, 0, 0, 0);
-    s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[2]), q0, s1, 0, 0, 0);
-    s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[1]), q1, s0, 0, 0, 0);
-    s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[3]), q1, s1, 0, 0, 0);
+    s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, now.kf[0]), q0, s0, 0, 0, 0);
+    s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, now.kf[2]), q0, s1, 0, 0, 0);
+    s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, now.kf[1]), q1, s0, 0, 0, 0);
+    s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, now.kf[3]), q1, s1, 0, 0, 0);
     mfma_settle(s0, s1);
     if constexpr (KV8) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) { s0[r] *= sck[0][r]; s1[r] *= sck[1][r]; }
+      for (int r = 0; r < 4; ++r) { s0[r] *= now.sck[0][r]; s1[r] *= now.sck[1][r]; }
     }
     const int left = lim - (c0 + 8 * g);   // this lane: query lq, keys c0 + 8 g .. + 7, of which it sees the first `left`
     float s[8];
@@ -504,7 +553,7 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
     for (int r = 0; r < 8; ++r) {
       p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], kCexp, nb));
       // (a masked key's scale may be anything, NaN included)
-      if constexpr (KV8) pf[r] = (bf16)(r < left ? p[r] * scv[r >> 2][r & 3] : 0.f);
+      if constexpr (KV8) pf[r] = (bf16)(r < left ? p[r] * now.scv[r >> 2][r & 3] : 0.f);
       else pf[r] = (bf16)p[r];
     }
     const float ps = pl_row_sum(((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])));
@@ -521,88 +570,95 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
     mrun = mnew;
 #pragma unroll
     for (int et = 0; et < 4; ++et) oacc[et] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vo[et], pf, oacc[et], 0, 0, 0);
+    if (c1 < nkey) {
+      now = next;
+      if (!await(c1, false)) return false;
+    }
   }
   mfma_settle(oacc);
   return true;
 }
 
-// All units of one attention stage.  Few: a workgroup per unit, its waves take chunks of 32 keys in turn and merge through LDS;
-// many: a wave per unit.
-template <int NW, bool SELF, bool QLDS, bool KV8, class FormQ>
-__device__ __forceinline__ bool pl_attention(const PlArgs& a, const PlExch& ex, int l, int w, int units, const PlUnit& mine,
-                                             PlLds<NW>& L, FormQ&& form_q) {
+// All units of one attention stage.  No more units than workgroups: a workgroup each (mine); else as many waves each as there
+// are, a power of two, several units to a workgroup.  The waves of a unit take chunks of 32 keys in turn and merge through LDS.
+template <int NW, bool SELF, bool QLDS, bool KV8, class Lds, class FormQ>
+__device__ __forceinline__ bool pl_attention(const PlArgs& a, const PlExch& ex, int l, int w, int units, const PlUnit& mine, Lds& L,
+                                             FormQ&& form_q) {
   const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
   const int NB = gridDim.x;
   if (units <= NB && (unsigned)w >= (unsigned)units) return true;   // (w: number among the workgroups that take units)
-  lds_barrier();   // the latest product's partial tiles are done with
   char* out = ex.att(SELF ? 0 : 1);
-  float mrun, lrun;
-  f32x4 oacc[4];
-  auto store = [&](const PlUnit& t, int et, const f32x4& o, float inv) {
-    float v[4];
+  const int wpu = QLDS ? NW : a.wpu, per = NW / wpu, kw = wave & (wpu - 1);   // waves of a unit, units at a time
+  for (int u0 = w * per; u0 < units; u0 += NB * per) {
+    const int u = u0 + wave / wpu;
+    const bool any = u < units;
+    PlUnit t = mine;
+    if (!QLDS && units > NB) t = pl_unit<SELF>(a, any ? u : units - 1);
+    const int chunks = (t.nkey + 31) >> 5, used = any ? min(max(chunks, 1), wpu) : 0;   // waves with keys (one at least)
+    float mrun, lrun;
+    f32x4 oacc[4];
+    auto store = [&](int et, const f32x4& o, float inv) {
+      float v[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = o[r] * inv;
-    const u32x2 p = pl_pack4(v);
-    if (t.q0 + lq < a.T) pl_store8(out + pl_at(a.RP, t.b * a.T + t.q0 + lq, t.h * kHeadDim + et * 16 + 4 * g), p[0], p[1]);
-  };
-  if (units > NB) {
-    for (int u = w * NW + wave; u < units; u += NB * NW) {
-      const PlUnit t = pl_unit<SELF>(a, u);
-      if (!pl_attn_wave<SELF, false, KV8>(a, ex, l, t, 0, 1, nullptr, [] { return true; }, L.vs(wave), mrun, lrun, oacc)) return false;
+      for (int r = 0; r < 4; ++r) v[r] = o[r] * inv;
+      const u32x2 p = pl_pack4(v);
+      if (t.q0 + lq < a.T) pl_store8(out + pl_at(a.RP, t.b * a.T + t.q0 + lq, t.h * kHeadDim + et * 16 + 4 * g), p[0], p[1]);
+    };
+    lds_barrier();   // the latest product's partial tiles, or the units' before, are done with
+    // (every wave takes part in forming the queries; one beyond the keys then finds none)
+    if ((QLDS || kw < used) &&
+        !pl_attn_wave<SELF, QLDS, KV8>(a, ex, l, t, kw, wpu, L.q, form_q, L.vs(wave), mrun, lrun, oacc))
+      return false;
+    if (wpu == 1 || (per == 1 && used <= 1)) {   // nothing to merge
       const float inv = lrun > 0.f ? __builtin_amdgcn_rcpf(lrun) : 0.f;
+      if (any && kw == 0)
 #pragma unroll
-      for (int et = 0; et < 4; ++et) store(t, et, oacc[et], inv);
+        for (int et = 0; et < 4; ++et) store(et, oacc[et], inv);
+      continue;
+    }
+    // O of every wave to LDS; wave et of the unit (two or more et's where it has few waves) merges dims 16 et .. + 15
+    f32x4* om = L.om();   // [wave][et][lane]
+    float* ml = L.ml();   // [wave][max, sum][16]  (the value tiles are done with)
+    lds_barrier();
+    if (kw < used) {
+#pragma unroll
+      for (int et = 0; et < 4; ++et) om[(wave * 4 + et) * 64 + lane] = oacc[et];
+      if (g == 0) { ml[wave * 32 + lq] = mrun; ml[wave * 32 + 16 + lq] = lrun; }
     }
     lds_barrier();
-    return true;
-  }
-  const int chunks = (mine.nkey + 31) >> 5, used = min(max(chunks, 1), NW);   // waves with keys (one at least)
-  // (every wave takes part in forming the queries; one beyond the keys then finds none)
-  if ((QLDS || wave < used) &&
-      !pl_attn_wave<SELF, QLDS, KV8>(a, ex, l, mine, wave, NW, L.q, form_q, L.vs(wave), mrun, lrun, oacc))
-    return false;
-  if (used == 1) {
-    if (wave == 0) {
-      const float inv = lrun > 0.f ? __builtin_amdgcn_rcpf(lrun) : 0.f;
+    if (any) {
+      const int first = wave - kw;
+      float M = kNegInf, Ls = 0.f;
+      for (int s = first; s < first + used; ++s) M = fmaxf(M, ml[s * 32 + lq]);
+      for (int s = first; s < first + used; ++s) {
+        const float ms = ml[s * 32 + lq];
+        Ls += ml[s * 32 + 16 + lq] * (ms > kNegInf ? __builtin_amdgcn_exp2f((ms - M) * kCexp) : 0.f);
+      }
+      const float inv = Ls > 0.f ? __builtin_amdgcn_rcpf(Ls) : 0.f;
+      for (int et = kw; et < 4; et += wpu) {
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        for (int s = first; s < first + used; ++s) {
+          const float ms = ml[s * 32 + lq], e = ms > kNegInf ? __builtin_amdgcn_exp2f((ms - M) * kCexp) : 0.f;
+          const f32x4 v = om[(s * 4 + et) * 64 + lane];
 #pragma unroll
-      for (int et = 0; et < 4; ++et) store(mine, et, oacc[et], inv);
+          for (int r = 0; r < 4; ++r) o[r] += v[r] * e;
+        }
+        store(et, o, inv);
+      }
     }
-    lds_barrier();
-    return true;
-  }
-  // O of every wave to LDS (the partial-tile buffers); wave et merges dims 16 et .. + 15
-  f32x4* om = L.red[0];                                            // [wave][et][lane]
-  float* ml = reinterpret_cast<float*>(L.red[1]);                  // [wave][max, sum][16]  (the value tiles are done with)
-  lds_barrier();
-  if (wave < used) {
-#pragma unroll
-    for (int et = 0; et < 4; ++et) om[(wave * 4 + et) * 64 + lane] = oacc[et];
-    if (g == 0) { ml[wave * 32 + lq] = mrun; ml[wave * 32 + 16 + lq] = lrun; }
-  }
-  lds_barrier();
-  if (wave < 4) {
-    float M = kNegInf, Ls = 0.f;
-    for (int s = 0; s < used; ++s) M = fmaxf(M, ml[s * 32 + lq]);
-    f32x4 o = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < used; ++s) {
-      const float ms = ml[s * 32 + lq], f = ms > kNegInf ? __builtin_amdgcn_exp2f((ms - M) * kCexp) : 0.f;
-      Ls += ml[s * 32 + 16 + lq] * f;
-      const f32x4 v = om[(s * 4 + wave) * 64 + lane];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) o[r] += v[r] * f;
-    }
-    store(mine, wave, o, Ls > 0.f ? __builtin_amdgcn_rcpf(Ls) : 0.f);
   }
   lds_barrier();
   return true;
 }
 
 // WT: weights (bf16 or E4M3 codes).  KV8: cross-attention keys / values as E4M3 codes.
-// FBW: column tiles of an item of the wide projections (QKV, first FFN matrix).
-template <class WT, bool KV8, int NW, int KSD, int KSF, int FBW>
-__global__ __launch_bounds__((64 * NW), 2) void pl_decoder_kernel(PlArgs a) {
+// MR: row tiles of an item.  FBW: column tiles of an item of the wide projections (QKV, first FFN matrix).
+template <class WT, bool KV8, int NW, int KSD, int KSF, int MR, int FBW>
+__global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decoder_kernel(PlArgs a) {
   extern __shared__ __attribute__((aligned(16))) char pl_smem[];
-  PlLds<NW>& L = *reinterpret_cast<PlLds<NW>*>(pl_smem);
+  typedef PlLds<NW, (MR > 1 ? MR * FBW : 4)> Lds;
+  static_assert(Lds::kRows == 16 * MR, "residual tile");
+  Lds& L = *reinterpret_cast<Lds*>(pl_smem);
   constexpr int d = 32 * NW * KSD, F = 32 * NW * KSF, NS = d / 64;   // statistics: d / 16 pairs over four lanes
   // wide projections from the top, sums from the bottom, attention units from att0 on: where there is room a workgroup has one
   // kind of item and its weights are on their way long before the rows are
@@ -620,28 +676,25 @@ __global__ __launch_bounds__((64 * NW), 2) void pl_decoder_kernel(PlArgs a) {
   }
   __syncthreads();
   int flip = 0;
-  auto turn = [&]() { return flip ^= 1; };
-  // items of a projection with N columns: 16 FB columns each, column tile fastest (tiles of one column range then share an XCD)
+  auto turn = [&]() { return Lds::kFlips == 1 ? 0 : flip ^= 1; };
+  const int RT = (a.R + 16 * MR - 1) / (16 * MR);
+  // items of a projection with N columns: 16 MR rows x 16 FB columns each, column tile fastest (tiles of one column range then share an XCD)
   auto project = [&](auto fbt, int N, const PlWeight& W, const float* cs, const float* bf, const char* A, bool plain,
                      const char* stats, auto&& epi) -> bool {
     constexpr int FB = decltype(fbt)::value;
-    const int nt = pl_opaque(N / (16 * FB)), items = nt * a.RT;
+    const int nt = pl_opaque(N / (16 * FB)), items = nt * RT;
     for (int it = wr; it < items; it += NB) {
       const int mt = it / nt;
-      if (!pl_project<WT, NW, KSD, FB, NS>(a, L, turn(), W, cs, bf, A, plain, stats, mt * 16, a.R, (it - mt * nt) * 16 * FB, epi)) return false;
+      if (!pl_project<WT, NW, KSD, MR, FB, NS>(a, L, turn(), W, cs, bf, A, plain, stats, mt * 16 * MR, a.R, (it - mt * nt) * 16 * FB, epi)) return false;
     }
     return true;
   };
   auto sum = [&](auto kst, const PlWeight& W, const float* vecs, const char* A, const char* stats_prev, bool first, bool last,
                  char* xg, char* st) -> bool {
     constexpr int KS = decltype(kst)::value, nt = d / 16;
-    int round = 0;
-    for (int it = w; it < nt * a.RT; it += NB, ++round) {
-      const int mt = it / nt;
-      if (!pl_sum<WT, NW, KS, NS>(a, L, turn(), L.resid[round], W, vecs, A, stats_prev, first, last, xg, st, mt * 16, (it - mt * nt) * 16))
-        return false;
-    }
-    return true;
+    if (w >= nt * RT) return true;
+    const int mt = w / nt;
+    return pl_sum<WT, NW, KS, MR, NS>(a, L, turn(), L.resid, W, vecs, A, stats_prev, first, last, xg, st, mt * 16 * MR, (w - mt * nt) * 16);
   };
   typedef std::integral_constant<int, KSD> CD;
   typedef std::integral_constant<int, KSF> CF;
@@ -670,7 +723,7 @@ __global__ __launch_bounds__((64 * NW), 2) void pl_decoder_kernel(PlArgs a) {
     if (units <= NB) {   // a unit's workgroup forms its queries itself: a product of 64 columns instead of a hand-over
       if (!pl_attention<NW, false, true, KV8>(a, ex, l, wa, units, cross, L, [&] {
             const int row0 = cross.b * a.T + cross.q0, n0 = cross.h * kHeadDim;
-            if (!pl_project<WT, NW, KSD, 4, NS>(a, L, turn(), Y.cwq, Y.cq_cs, Y.cq_bf, ex.xg(0), false, ex.st(0), row0, (cross.b + 1) * a.T,
+            if (!pl_project<WT, NW, KSD, 1, 4, NS>(a, L, turn(), Y.cwq, Y.cq_cs, Y.cq_bf, ex.xg(0), false, ex.st(0), row0, (cross.b + 1) * a.T,
                                             n0, [&](int row, int n, const float (&v)[4]) {
                   *reinterpret_cast<u32x2*>(&L.q[(row - row0) * kPlQPitch + n - n0]) = pl_pack4(v);
                 })) return false;
@@ -702,15 +755,18 @@ size_t persist_exch_bytes(int rows, int layers, int d, int F) { return (size_t)l
 
 int persist_plan(PlArgs& a, int d, int F) {
   a.RP = (a.R + 15) & ~15;
-  a.RT = a.RP / 16;
   a.d = d;
+  // Rows of an item: 16 as long as every workgroup has at most one residual sum of 16 x 16, else 32 (weights are read once per
+  // item).
+  const int most = 3 * d > F ? 3 * d : F, units = a.B * a.H * ((a.T + 15) >> 4);
+  a.mr = d / 16 * (a.RP / 16) <= kPlBlocks ? 1 : 2;
+  const int rt = (a.R + 16 * a.mr - 1) / (16 * a.mr), sums = d / 16 * rt;
   // The narrowest items of the wide projections that leave every workgroup one kind of item; failing that, that give every
   // workgroup at most one of them.
-  const int sums = d / 16 * a.RT, most = 3 * d > F ? 3 * d : F, units = a.B * a.H * ((a.T + 15) >> 4);
-  auto wide = [&](int fb) { const int n = most / (16 * fb) * a.RT; return n > sums ? n : sums; };
-  int fb = 2;
+  auto wide = [&](int fb) { const int n = most / (16 * fb) * rt; return n > sums ? n : sums; };
+  int fb = a.mr > 1 ? 4 : 2;
   while (fb < 4 && sums + units + wide(fb) > kPlBlocks) fb *= 2;
-  if (sums + units + wide(fb) > kPlBlocks) {
+  if (a.mr == 1 && sums + units + wide(fb) > kPlBlocks) {
     fb = 2;
     while (fb < 4 && wide(fb) > kPlBlocks) fb *= 2;
   }
@@ -718,22 +774,31 @@ int persist_plan(PlArgs& a, int d, int F) {
   int NB = sums + units + wide(fb);
   if (NB > kPlBlocks) NB = kPlBlocks;
   a.att0 = sums + units <= NB ? sums : 0;
-  return (sums + NB - 1) / NB <= kPlRounds ? NB : 0;
+  const int nw = d == 512 ? 4 : 8;
+  a.wpu = nw;
+  while (a.wpu > 1 && units > NB * (nw / a.wpu)) a.wpu >>= 1;
+  return sums <= NB ? NB : 0;
 }
 
-template <class WT, bool KV8, int NW, int KSD, int KSF, int FBW>
+template <class WT, bool KV8, int NW, int KSD, int KSF, int MR, int FBW>
 static hipError_t pl_launch(hipStream_t st, const PlArgs& a, int NB) {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pl_decoder_kernel<WT, KV8, NW, KSD, KSF, FBW>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(PlLds<NW>));
+  constexpr int kBytes = (int)sizeof(PlLds<NW, (MR > 1 ? MR * FBW : 4)>);
+  static_assert(kBytes <= 160 * 1024, "LDS of a CU");
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pl_decoder_kernel<WT, KV8, NW, KSD, KSF, MR, FBW>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
   if (attr != hipSuccess) return attr;
-  static_assert(sizeof(PlLds<NW>) <= 80 * 1024, "two workgroups per CU");
-  SD_LAUNCH_TIMED((pl_decoder_kernel<WT, KV8, NW, KSD, KSF, FBW>), dim3(NB), dim3((64 * NW)), sizeof(PlLds<NW>), st, a);
+  SD_LAUNCH_TIMED((pl_decoder_kernel<WT, KV8, NW, KSD, KSF, MR, FBW>), dim3(NB), dim3((64 * NW)), kBytes, st, a);
   return hipGetLastError();
+}
+template <class WT, bool KV8, int NW>
+static hipError_t pl_launch_items(hipStream_t st, const PlArgs& a, int NB) {
+  if (a.mr == 1) return a.fbw == 2 ? pl_launch<WT, KV8, NW, 4, 16, 1, 2>(st, a, NB) : pl_launch<WT, KV8, NW, 4, 16, 1, 4>(st, a, NB);
+  if constexpr (sizeof(WT) == 1) return hipErrorInvalidValue;   // codes: passes of a few rows only
+  else return pl_launch<WT, KV8, NW, 4, 16, 2, 4>(st, a, NB);
 }
 template <class WT, bool KV8>
 static hipError_t pl_launch_dims(hipStream_t st, const PlArgs& a, int d, int NB) {
-  if (d == 512) return a.fbw == 2 ? pl_launch<WT, KV8, 4, 4, 16, 2>(st, a, NB) : pl_launch<WT, KV8, 4, 4, 16, 4>(st, a, NB);
-  return a.fbw == 2 ? pl_launch<WT, KV8, 8, 4, 16, 2>(st, a, NB) : pl_launch<WT, KV8, 8, 4, 16, 4>(st, a, NB);
+  return d == 512 ? pl_launch_items<WT, KV8, 4>(st, a, NB) : pl_launch_items<WT, KV8, 8>(st, a, NB);
 }
 
 hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F) {

@@ -31,7 +31,14 @@ def check(case, out):
     (512, 2, 15, 200, 180, 220, {}),         # every wave has key chunks
     (512, 42, 2, 20, 0, 30, {}),             # 126 rows, a wave per unit of attention
     (1024, 1, 25, 90, 57, 57, {}),
-    (1024, 16, 3, 30, 0, 40, {}),            # 64 rows, the most
+    (1024, 16, 3, 30, 0, 40, {}),            # 64 rows, the most on tiles of 16 rows
+    (512, 43, 2, 20, 0, 30, {}),             # 129 rows: tiles of 32, the last of one row
+    (512, 8, 16, 20, 0, 30, {}),             # 136 rows, two query tiles a sequence
+    (512, 32, 7, 20, 60, 90, {}),            # 256 rows, the most; a unit of attention per workgroup
+    (1024, 13, 4, 30, 0, 140, {}),           # 65 rows: tiles of 32
+    (1024, 64, 1, 40, 50, 70, {}),           # 128 rows, the most; two waves per unit
+    (1024, 11, 10, 150, 100, 130, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
+    (1024, 24, 4, 200, 60, 140, {}),         # four waves per unit, several chunks of keys each
     (512, 3, 9, 50, 0, 40, {sd.SPECDEC_OPT_FP8_WEIGHTS: 1}),
     (512, 3, 9, 50, 0, 40, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
     (1024, 1, 30, 33, 9, 9, {sd.SPECDEC_OPT_FP8_WEIGHTS: 1, sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
