@@ -104,10 +104,13 @@ typedef enum {
                                           drafting) then reads the codes: score = k_scale * (codes . q),
                                           out += (p * v_scale) * codes.  Changes the model like FP8_WEIGHTS does;
                                           the two options are independent.  Refused by RESIDENT / SLICED_SUBLAYERS. */
-  SPECDEC_OPT_WIDE_VOCAB_TILES = 6     /* default 0: the vocabulary projection of a pass of more than 32 rows takes
+  SPECDEC_OPT_WIDE_VOCAB_TILES = 6,    /* default 0: the vocabulary projection of a pass of more than 32 rows takes
                                           its 256 x 256 tiles only where they give every compute unit two or more
                                           (the batched passes), else 128 x 128 tiles.  1: 256 x 256 tiles in every
                                           such pass (so that the wide kernel can be checked on small shapes).     */
+  SPECDEC_OPT_GIVE_UP_WAITS = 7        /* default 0.  1: every wait of the one-kernel decoder that does not end at once is
+                                          given up, and the pass completed by the kernel behind it (specdec_verify),
+                                          so that this way of completing a pass can be checked.                   */
 } specdec_option;
 
 /* ---- life cycle -------------------------------------------------------------------- */
@@ -224,11 +227,12 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * Finished sequences report accept_len 0 and next_token pad_id.
  * k = 0 (draft may be null) is one plain autoregressive step: accept_len = 0 and next_token is
  * the verifier's greedy token (the baseline of Sec. 2 on the same kernels).
- * With SPECDEC_OPT_RESIDENT set (specdec_configure), passes of at most 32
- * rows run as one resident kernel whose workgroups meet at bounded grid barriers; should a
- * barrier time out (never expected), every sequence reports accept_len -1 and next_token
- * pad_id, specdec_commit then changes nothing, and the condition lasts until the next
- * specdec_begin.
+ * Passes of few rows (at most 256 with d_model 512 / d_ffn 2048, 128 with 1024 / 4096, 32 layers)
+ * run their decoder layers as one kernel of up to 256 workgroups that wait for each other; where a
+ * kernel of another stream or process keeps some of them from starting for 0.1 s or more, the waits
+ * are given up and a second kernel, which needs no more than one free compute unit, computes
+ * the pass instead (same bits, 0.5 - 3 ms); the run's later passes then go to that kernel
+ * directly, until the next specdec_begin.
  * logits_or_null: optional device fp32 [B, k+1, V] receiving every row's logits (parity
  * mode; slow).  Does not change any length: calling it twice gives the same result. */
 int specdec_verify(specdec_ctx* ctx, const int32_t* draft, int32_t k, int32_t beta, float tau,

@@ -79,7 +79,7 @@ struct Model {
   float* hx = nullptr;       // [Bmax*k_max][d] head-based drafting: the hidden state each head adds to, then its output
   bool skinny_ready = false;
   sd::PlLayer* pl_layers = nullptr;   // device copy of the decoder layers' pointers (one-kernel decoder, persist.hip)
-  int* pl_err = nullptr;              // its error flag
+  int* pl_err = nullptr;              // its two flags (PlArgs::err)
   char* pl_exch = nullptr;            // its exchange buffers (null: dimensions it does not support)
   int pl_rows = 0;                    // rows they are sized for
   bf16* xb = nullptr;        // [Rpass][d]
@@ -138,6 +138,7 @@ struct specdec_ctx {
   bool no_ln_fold = false;  // SPECDEC_OPT_LN_FOLD = 0: LayerNorm as a pass of its own between the GEMMs
   bool resident = false;    // SPECDEC_OPT_RESIDENT = 1: small batches run the decoder pass as one resident kernel
   int persist_dev = -1;     // GPU on which this context is among the users of the one-kernel decoder
+  bool give_up = false;     // SPECDEC_OPT_GIVE_UP_WAITS = 1: the one-kernel decoder's waits are given up at once
   bool sliced = false;      // SPECDEC_OPT_SLICED_SUBLAYERS = 1: small-batch sub-layers owned by head / FFN slice
   bool fp8 = false;         // SPECDEC_OPT_FP8_WEIGHTS = 1: models bound from now on keep E4M3 copies for small batches
   bool fp8_kv = false;      // SPECDEC_OPT_FP8_CROSS_KV = 1: models bound from now on keep E4M3 cross keys / values
@@ -278,7 +279,8 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   t.xv = cv.take<bf16>(t.xkv_layer * d->dec_layers);
   t.x = cv.take<float>(Rpass * D);
   t.x2 = cv.take<float>(32 * D);
-  t.skp = cv.take<float>((size_t)2 * sd::kSk2MaxParts * 32 * D);
+  t.skp = cv.take<float>((size_t)2 * sd::kSk2MaxParts * 32 * D);   // (or the one-kernel decoder's sum and its residual)
+  static_assert(2 * persist_rows(512) <= 2 * sd::kSk2MaxParts * 32, "both fit");
   t.hx = cv.take<float>(Bm * (size_t)c->lim.k_max * D);
   if (c->fp8_kv) {
     t.xk8 = cv.take<unsigned char>(t.xkv_layer * d->dec_layers);
@@ -552,8 +554,8 @@ int decoder_layers_sliced(specdec_ctx* c, Model& m, int B, int T, hipStream_t st
   return SPECDEC_OK;
 }
 
-// The one-kernel decoder keeps its workgroups waiting for each other, so no two such passes may share a GPU's compute units
-// half-started.  Contexts whose passes go to one stream take turns there; the first to ask names the stream, and while it
+// The one-kernel decoder keeps its workgroups waiting for each other, and two such passes that share a GPU's compute units
+// half-started wait in vain until their bound (persist.hip completes them another way then).  So contexts whose passes go to one stream take turns there; the first to ask names the stream, and while it
 // lives, a pass of another context on another stream takes the kernel-per-stage path.  A captured pass may be replayed on any
 // stream, so a context that captures one is alone with its GPU until it is destroyed (or, where it is not alone, captures the
 // kernel-per-stage path).  Among processes the user is the one that could bind a socket named after the GPU's PCI address,
@@ -631,11 +633,11 @@ int decoder_layers_persist(specdec_ctx* c, Model& m, int B, int T, bool few, hip
   a.fp8 = few && m.fp8;
   a.layers = m.pl_layers + (a.fp8 ? m.d.dec_layers : 0);
   a.row_b = m.rm.row_b; a.row_pos = m.rm.row_pos; a.src_len = c->st.src_len;
-  a.x = m.x; a.xb = m.xb; a.y = m.x;
+  a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + persist_rows(m.d.d_model) * m.d.d_model;
   a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
   if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
   a.exch = m.pl_exch; a.err = reinterpret_cast<unsigned*>(m.pl_err);
-  LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::persist_decoder(st, a, m.d.d_model, m.d.d_ffn));
+  LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::persist_decoder(st, a, m.d.d_model, m.d.d_ffn, c->give_up));
   return SPECDEC_OK;
 }
 
@@ -715,6 +717,7 @@ int specdec_configure(specdec_ctx* c, int32_t option, int32_t value) {
     case SPECDEC_OPT_FP8_WEIGHTS: c->fp8 = (value == 1); break;
     case SPECDEC_OPT_FP8_CROSS_KV: c->fp8_kv = (value == 1); break;
     case SPECDEC_OPT_WIDE_VOCAB_TILES: c->wide_vocab = (value == 1); break;
+    case SPECDEC_OPT_GIVE_UP_WAITS: c->give_up = (value == 1); break;
     default: return fail(c, SPECDEC_ERR_INVALID_ARG, "unknown option %d", option);
   }
   return SPECDEC_OK;
@@ -872,7 +875,7 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
     if (rcq != SPECDEC_OK) return fail(c, rcq, "FP8 weight quantisation failed: %s", hipGetErrorString(hipGetLastError()));
   }
   {
-    HIPCHK(c, sd::fill_i32(S(stream), m.pl_err, 0, 1));
+    HIPCHK(c, sd::fill_i32(S(stream), m.pl_err, 0, 2));
     // for the one-kernel decoder: the bf16 matrices, then (FP8 weights) their codes
     std::vector<sd::PlLayer> pl;
     for (int set = 0; set < (m.fp8 ? 2 : 1); ++set)
@@ -899,7 +902,7 @@ int specdec_begin(specdec_ctx* c, int32_t B, int32_t max_new, void* stream) {
   const Model& any = c->m[0].bound ? c->m[0] : c->m[1];
   if (max_new > c->lim.max_tgt) max_new = c->lim.max_tgt;   // no stream grows beyond the arena
   HIPCHK(c, sd::begin_state(S(stream), c->st, B, max_new, c->lim.max_tgt, any.d.bos_id));
-  if (c->m[0].bound) HIPCHK(c, sd::fill_i32(S(stream), c->m[0].pl_err, 0, 1));   // a new run clears the one-kernel decoder's error flag
+  if (c->m[0].bound) HIPCHK(c, sd::fill_i32(S(stream), c->m[0].pl_err, 0, 2));   // a new run clears the one-kernel decoder's flags
   c->B = B;
   c->max_new = max_new;
   c->last_T = 0;
@@ -1146,7 +1149,8 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_verify(st, c->st, m.rm, draft, B, k, m.d.vocab, m.embed, m.pe, m.x, m.xb,
                                         m.d.d_model, one ? m.pl_exch : nullptr,
                                         one ? sd::persist_exch_bytes(R, m.d.dec_layers, m.d.d_model, m.d.d_ffn) : 0));
-  const unsigned* failed = one ? reinterpret_cast<const unsigned*>(m.pl_err) : nullptr;
+  const unsigned* failed = one ? reinterpret_cast<const unsigned*>(m.pl_err) + 1 : nullptr;
+  float* sums = one ? m.skp : m.x;   // the last residual sums (the one-kernel decoder keeps its input rows)
   int n_tiles = (m.d.vocab + 63) / 64;   // per-row partial records of the vocabulary kernel that ran
   if (small && (m.fp8 || m.kv8) && (c->resident || c->sliced))
     return fail(c, SPECDEC_ERR_BAD_STATE, "a model bound with FP8 weights or FP8 cross keys/values runs small passes on the default kernels only");
@@ -1154,7 +1158,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     sd::SkSrc fin{};
     if (!fused) {
       rc = one ? decoder_layers_persist(c, m, B, T, true, st) : decoder_layers(c, m, B, T, st, true, 0, false, false, true);
-      fin = sd::SkSrc{2, m.x, m.dec.back().ln3g, m.dec.back().ln3b, nullptr, nullptr, nullptr, nullptr};
+      fin = sd::SkSrc{2, sums, m.dec.back().ln3g, m.dec.back().ln3b, nullptr, nullptr, nullptr, nullptr};
     } else if (c->sliced && sd::sk2_supported(m.d.d_model, m.d.d_ffn) && m.d.n_heads <= sd::kSk2MaxParts)
       rc = decoder_layers_sliced(c, m, B, T, st, &fin);
     else
@@ -1166,12 +1170,12 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     if (one) {
       rc = decoder_layers_persist(c, m, B, T, false, st);
       if (rc) return rc;
-      LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.x, m.dec.back().ln3g, m.dec.back().ln3b, m.xb, R, m.d.d_model));
+      LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, sums, m.dec.back().ln3g, m.dec.back().ln3b, m.xb, R, m.d.d_model));
     } else {
       rc = decoder_layers(c, m, B, T, st, true);
       if (rc) return rc;
     }
-    c->fin_x = m.x; c->fin_g = nullptr; c->fin_b = nullptr;   // normalised in place by the last LayerNorm
+    c->fin_x = sums; c->fin_g = nullptr; c->fin_b = nullptr;   // normalised in place by the last LayerNorm
     n_tiles = (m.d.vocab + sd::vocab_tile_cols(R) - 1) / sd::vocab_tile_cols(R);
     LAUNCH(c, SPECDEC_KIND_VOCAB, st, sd::vocab_stats(st, m.xb, m.embed, R, m.d.vocab, m.d.d_model, m.rm.row_draft, vs.zd, vs.part, logits, c->wide_vocab));
   }

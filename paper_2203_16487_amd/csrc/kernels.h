@@ -242,21 +242,27 @@ struct PlArgs {
   const int *row_b, *row_pos, *src_len;
   const float* x;                         // embedded rows, fp32 and bf16 [R][d]
   const bf16* xb;
-  float* y;                               // last residual sum, un-normalised [R][d] (may be x)
+  float* y;                               // last residual sum, un-normalised [R][d] (not x)
+  float* resid;                           // [R rounded up to 16][d], scratch
   bf16 *kc, *vc;                          // self K/V arenas, layer stride kv_layer
   const void *xk, *xv;                    // cross K/V arenas, layer stride xkv_layer elements: bf16, or (scales not null) codes
   const float *xk_scale, *xv_scale;
   size_t kv_layer, xkv_layer;
   int fp8;                                // the layers' weights are codes
   char* exch;                             // persist_exch_bytes, every byte 0xff when the kernel starts
-  unsigned* err;                          // sticky error flag
-  int RP, d, mr, fbw, att0, wpu;          // filled by the launcher
+  unsigned* err;                          // [2] flags, zero at first and kept from pass to pass: waits of the pass were given
+                                          // up (and it is finished another way), those of that way too (results are void)
+  int RP, d, mr, fbw, att0, wpu, NB;      // filled by the launcher, as what follows
+  const unsigned* raised;
+  unsigned poll_mask, spin_max;
+  struct PlTickets* tickets;
 };
 constexpr int kPlBlocks = 256;            // most workgroups of a pass
 bool persist_supported(int layers, int d, int F);
 size_t persist_exch_bytes(int rows, int layers, int d, int F);
 int persist_plan(PlArgs& a, int d, int F);   // workgroups of a pass of a.R rows, a.B sequences, a.H heads (0: too many rows)
-hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F);
+// give_up: every wait that does not end at once is given up
+hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F, bool give_up);
 // ---- skinny2.hip: the same passes with sub-layers owned by head / by FFN slice (three kernels per layer) ----
 bool sk2_supported(int d, int F);
 int sk2_ffn_slices(int F);             // partial results the FFN kernel leaves (at most 16)

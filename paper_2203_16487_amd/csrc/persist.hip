@@ -22,15 +22,23 @@
 // 60 - 75 GB/s one CU takes in, whether the rows come through the L2 (counters instead of kPoison) or not, and whether or not
 // the next weights are requested ahead.
 //
-// Waits are bounded: after kPlSpinMax polls, or once another workgroup has raised the error flag, a wave raises it and ends;
-// the host reports accept_len = -1.  All workgroups are co-resident by construction (there are no more than CUs and
-// the host has one such pass at a time on a GPU).
+// The workgroups wait for each other, so all of them have to be running.  There are no more of them than the stream has CUs and
+// the host lets one such pass at a time onto a GPU, but a kernel of another stream or process may hold some of the CUs.  Waits
+// are therefore bounded: after kPlSpinMax polls, or once another workgroup has raised the error flag, a wave raises it and ends,
+// and the same stages are run again by the kernel launched behind this one (TICKETS), which returns at once where the flag is
+// not raised.  Its workgroups draw (stage, virtual workgroup) tickets in the order of the stages and wait only for
+// stages whose tickets have all been drawn, that is for workgroups that are running: it needs no more than one CU.  It computes
+// the same bits.  The flag stays raised until specdec_begin: later passes of that run do not wait in vain again.
+// A whole verify pass with the second launch returning at once and without it: 125.3 / 124.8 us (d = 512, 6 rows), 168.4 / 166.3
+// (77 rows), 380.2 / 378.0 (d = 1024, 128 rows); by tickets 0.51, 1.13 and 2.7 ms.
 #include "attn_core.h"
 
 namespace sd {
 
 constexpr unsigned kPoison = 0xffffffffu;
-constexpr unsigned kPlSpinMax = 1u << 21;
+constexpr unsigned kPlSpinMax = 1u << 17;   // (0.1 - 0.2 s)
+constexpr unsigned kPlTicketSpinMax = 1u << 24;
+constexpr int kPlTicketBlocks = 64;
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
@@ -56,12 +64,12 @@ __device__ __forceinline__ u32x2 pl_pack4(const float (&v)[4]) {
 }
 
 // One more round of a wait: false once the pass is to be abandoned.
-__device__ __forceinline__ bool pl_again(unsigned& spins, unsigned* err) {
+__device__ __forceinline__ bool pl_again(unsigned& spins, const PlArgs& a) {
   ++spins;
-  if ((spins & 63) == 0) {
-    const bool raised = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
-    if (raised || spins > kPlSpinMax) {
-      __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((spins & a.poll_mask) == 0) {
+    const bool raised = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+    if (raised || spins > a.spin_max) {
+      __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return false;
     }
   }
@@ -206,7 +214,7 @@ __device__ __forceinline__ bool pl_product(const PlArgs& a, Lds& L, int flip, co
   if (!LATE && has_stat) {
     stat_request();
     while (__builtin_amdgcn_ballot_w64(stat_missing())) {
-      if (!pl_again(spins, a.err)) return false;
+      if (!pl_again(spins, a)) return false;
       asm volatile("" ::: "memory");
       stat_request();
     }
@@ -246,7 +254,7 @@ __device__ __forceinline__ bool pl_product(const PlArgs& a, Lds& L, int flip, co
         for (int u = 0; u < CH; ++u) bad |= pl_missing(af[cc % DEPTH][u]) && row0 + 16 * (cc % MR) + lq < rlim;
       if (LATE && has_stat && c == 0) bad |= stat_missing();
       if (!__builtin_amdgcn_ballot_w64(bad)) return true;
-      if (!pl_again(spins, a.err)) return false;
+      if (!pl_again(spins, a)) return false;
       asm volatile("" ::: "memory");
 #pragma unroll
       for (int cc = c; cc < c + DEPTH && cc < NC; ++cc) request(cc);
@@ -471,7 +479,7 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
         }
         return true;
       }
-      if (!pl_again(spins, a.err)) return false;
+      if (!pl_again(spins, a)) return false;
       asm volatile("" ::: "memory");
     }
   };
@@ -582,10 +590,9 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
 // All units of one attention stage.  No more units than workgroups: a workgroup each (mine); else as many waves each as there
 // are, a power of two, several units to a workgroup.  The waves of a unit take chunks of 32 keys in turn and merge through LDS.
 template <int NW, bool SELF, bool QLDS, bool KV8, class Lds, class FormQ>
-__device__ __forceinline__ bool pl_attention(const PlArgs& a, const PlExch& ex, int l, int w, int units, const PlUnit& mine, Lds& L,
+__device__ __forceinline__ bool pl_attention(const PlArgs& a, const PlExch& ex, int l, int w, int NB, int units, const PlUnit& mine, Lds& L,
                                              FormQ&& form_q) {
   const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
-  const int NB = gridDim.x;
   if (units <= NB && (unsigned)w >= (unsigned)units) return true;   // (w: number among the workgroups that take units)
   char* out = ex.att(SELF ? 0 : 1);
   const int wpu = QLDS ? NW : a.wpu, per = NW / wpu, kw = wave & (wpu - 1);   // waves of a unit, units at a time
@@ -651,9 +658,16 @@ __device__ __forceinline__ bool pl_attention(const PlArgs& a, const PlExch& ex, 
   return true;
 }
 
+// What the ticket kernel counts with, ahead of the exchange buffers (all words ~0 when a pass starts): tickets drawn, and per
+// stage the virtual workgroups that have finished it.
+constexpr int kPlStages = 8;
+struct PlTickets { unsigned drawn, done[kPlStages * kPlLayers]; };
+constexpr size_t kPlTicketBytes = (sizeof(PlTickets) + 255) & ~size_t(255);
+
 // WT: weights (bf16 or E4M3 codes).  KV8: cross-attention keys / values as E4M3 codes.
 // MR: row tiles of an item.  FBW: column tiles of an item of the wide projections (QKV, first FFN matrix).
-template <class WT, bool KV8, int NW, int KSD, int KSF, int MR, int FBW>
+// TICKETS: see the head of this file; a.NB virtual workgroups, the residual in memory instead of LDS (MR = 1).
+template <class WT, bool KV8, int NW, int KSD, int KSF, int MR, int FBW, bool TICKETS>
 __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decoder_kernel(PlArgs a) {
   extern __shared__ __attribute__((aligned(16))) char pl_smem[];
   typedef PlLds<NW, (MR > 1 ? MR * FBW : 4)> Lds;
@@ -662,18 +676,23 @@ __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decod
   constexpr int d = 32 * NW * KSD, F = 32 * NW * KSF, NS = d / 64;   // statistics: d / 16 pairs over four lanes
   // wide projections from the top, sums from the bottom, attention units from att0 on: where there is room a workgroup has one
   // kind of item and its weights are on their way long before the rows are
-  const int NB = gridDim.x, w = blockIdx.x, wr = NB - 1 - w;
-  if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return;   // sticky error: do nothing
+  const int NB = TICKETS ? a.NB : gridDim.x;
+  int w = blockIdx.x;
+  if ((__hip_atomic_load(a.raised, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) != TICKETS) return;
   {
     const int words = a.n_layers * (int)(sizeof(PlLayer) / 8);
     for (int i = threadIdx.x; i < words; i += (64 * NW)) L.layers[i] = reinterpret_cast<const unsigned long long*>(a.layers)[i];
   }
-  const int units = a.B * a.H * ((a.T + 15) >> 4), wa = units <= NB ? w - a.att0 : w;
+  const int units = a.B * a.H * ((a.T + 15) >> 4);
   PlUnit self{}, cross{};
-  if ((unsigned)wa < (unsigned)units && units <= NB) {
-    self = pl_unit<true>(a, wa);
-    cross = pl_unit<false>(a, wa);
-  }
+  auto take_units = [&]() {
+    const int wa = w - a.att0;
+    if ((unsigned)wa < (unsigned)units && units <= NB) {
+      self = pl_unit<true>(a, wa);
+      cross = pl_unit<false>(a, wa);
+    }
+  };
+  if (!TICKETS) take_units();
   __syncthreads();
   int flip = 0;
   auto turn = [&]() { return Lds::kFlips == 1 ? 0 : flip ^= 1; };
@@ -683,7 +702,7 @@ __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decod
                      const char* stats, auto&& epi) -> bool {
     constexpr int FB = decltype(fbt)::value;
     const int nt = pl_opaque(N / (16 * FB)), items = nt * RT;
-    for (int it = wr; it < items; it += NB) {
+    for (int it = NB - 1 - w; it < items; it += NB) {
       const int mt = it / nt;
       if (!pl_project<WT, NW, KSD, MR, FB, NS>(a, L, turn(), W, cs, bf, A, plain, stats, mt * 16 * MR, a.R, (it - mt * nt) * 16 * FB, epi)) return false;
     }
@@ -692,22 +711,29 @@ __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decod
   auto sum = [&](auto kst, const PlWeight& W, const float* vecs, const char* A, const char* stats_prev, bool first, bool last,
                  char* xg, char* st) -> bool {
     constexpr int KS = decltype(kst)::value, nt = d / 16;
-    if (w >= nt * RT) return true;
-    const int mt = w / nt;
-    return pl_sum<WT, NW, KS, MR, NS>(a, L, turn(), L.resid, W, vecs, A, stats_prev, first, last, xg, st, mt * 16 * MR, (w - mt * nt) * 16);
+    for (int it = w; it < nt * RT; it += NB) {
+      const int mt = it / nt;
+      if (!pl_sum<WT, NW, KS, MR, NS>(a, L, turn(), TICKETS ? a.resid + it * (256 * MR) : L.resid, W, vecs, A, stats_prev, first, last,
+                                      xg, st, mt * 16 * MR, (it - mt * nt) * 16)) return false;
+      if (!TICKETS) break;   // (the plan gives a workgroup at most one)
+    }
+    return true;
   };
   typedef std::integral_constant<int, KSD> CD;
   typedef std::integral_constant<int, KSF> CF;
   typedef std::integral_constant<int, FBW> CW;
   typedef std::integral_constant<int, 1> C1;
-  for (int l = 0; l < a.n_layers; ++l) {
+  // stage s of layer l, of workgroup w
+  auto stage = [&](int s, int l) __attribute__((always_inline)) -> bool {
+    const int wa = units <= NB ? w - a.att0 : w;
     const PlLayer& Y = reinterpret_cast<const PlLayer*>(L.layers)[l];
     const PlExch ex(a.exch, l, a.RP, d, F), before(a.exch, l - 1, a.RP, d, F);
     const bool top = l == 0;
-    // queries, keys, values (appended to the cache as well)
     const char* st0 = top ? nullptr : before.st(2);
-    if (!project(CW{}, 3 * d, Y.wqkv, Y.qkv_cs, Y.qkv_bf, top ? reinterpret_cast<const char*>(a.xb) : before.xg(2), top, st0,
-                    [&](int row, int n, const float (&v)[4]) {
+    switch (s) {
+      case 0:   // queries, keys, values (appended to the cache as well)
+        return project(CW{}, 3 * d, Y.wqkv, Y.qkv_cs, Y.qkv_bf, top ? reinterpret_cast<const char*>(a.xb) : before.xg(2), top, st0,
+                       [&](int row, int n, const float (&v)[4]) {
           const int part = n / d, c = n - part * d;
           const u32x2 p = pl_pack4(v);
           char* dst = (part == 0 ? ex.q(0) : part == 1 ? ex.kx() : ex.vx()) + pl_at(a.RP, row, c);
@@ -717,33 +743,58 @@ __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decod
           bf16* cache = (part == 1 ? a.kc : a.vc) + a.kv_layer * l +
                         (((size_t)b * a.H + (c >> 6)) * a.Lcap + a.row_pos[row]) * kHeadDim + (c & 63);
           *reinterpret_cast<u32x2*>(cache) = p;
-        })) return;
-    if (!pl_attention<NW, true, false, false>(a, ex, l, wa, units, self, L, [] { return true; })) return;
-    if (!sum(CD{}, Y.wo, Y.vo, ex.att(0), st0, top, false, ex.xg(0), ex.st(0))) return;
-    if (units <= NB) {   // a unit's workgroup forms its queries itself: a product of 64 columns instead of a hand-over
-      if (!pl_attention<NW, false, true, KV8>(a, ex, l, wa, units, cross, L, [&] {
-            const int row0 = cross.b * a.T + cross.q0, n0 = cross.h * kHeadDim;
-            if (!pl_project<WT, NW, KSD, 1, 4, NS>(a, L, turn(), Y.cwq, Y.cq_cs, Y.cq_bf, ex.xg(0), false, ex.st(0), row0, (cross.b + 1) * a.T,
-                                            n0, [&](int row, int n, const float (&v)[4]) {
-                  *reinterpret_cast<u32x2*>(&L.q[(row - row0) * kPlQPitch + n - n0]) = pl_pack4(v);
-                })) return false;
-            lds_barrier();
-            return true;
-          })) return;
-    } else {
-      if (!project(C1{}, d, Y.cwq, Y.cq_cs, Y.cq_bf, ex.xg(0), false, ex.st(0), [&](int row, int n, const float (&v)[4]) {
-            const u32x2 p = pl_pack4(v);
-            pl_store8(ex.q(1) + pl_at(a.RP, row, n), p[0], p[1]);
-          })) return;
-      if (!pl_attention<NW, false, false, KV8>(a, ex, l, wa, units, cross, L, [] { return true; })) return;
-    }
-    if (!sum(CD{}, Y.cwo, Y.vco, ex.att(1), ex.st(0), false, false, ex.xg(1), ex.st(1))) return;
-    if (!project(CW{}, F, Y.w1, Y.w1_cs, Y.w1_bf, ex.xg(1), false, ex.st(1), [&](int row, int n, const float (&v)[4]) {
+        });
+      case 1: return pl_attention<NW, true, false, false>(a, ex, l, wa, NB, units, self, L, [] { return true; });
+      case 2: return sum(CD{}, Y.wo, Y.vo, ex.att(0), st0, top, false, ex.xg(0), ex.st(0));
+      case 3:
+        return units <= NB || project(C1{}, d, Y.cwq, Y.cq_cs, Y.cq_bf, ex.xg(0), false, ex.st(0), [&](int row, int n, const float (&v)[4]) {
+          const u32x2 p = pl_pack4(v);
+          pl_store8(ex.q(1) + pl_at(a.RP, row, n), p[0], p[1]);
+        });
+      case 4:
+        if (units > NB) return pl_attention<NW, false, false, KV8>(a, ex, l, wa, NB, units, cross, L, [] { return true; });
+        // a unit's workgroup forms its queries itself: a product of 64 columns instead of a hand-over
+        return pl_attention<NW, false, true, KV8>(a, ex, l, wa, NB, units, cross, L, [&] {
+          const int row0 = cross.b * a.T + cross.q0, n0 = cross.h * kHeadDim;
+          if (!pl_project<WT, NW, KSD, 1, 4, NS>(a, L, turn(), Y.cwq, Y.cq_cs, Y.cq_bf, ex.xg(0), false, ex.st(0), row0, (cross.b + 1) * a.T,
+                                          n0, [&](int row, int n, const float (&v)[4]) {
+                *reinterpret_cast<u32x2*>(&L.q[(row - row0) * kPlQPitch + n - n0]) = pl_pack4(v);
+              })) return false;
+          lds_barrier();
+          return true;
+        });
+      case 5: return sum(CD{}, Y.cwo, Y.vco, ex.att(1), ex.st(0), false, false, ex.xg(1), ex.st(1));
+      case 6:
+        return project(CW{}, F, Y.w1, Y.w1_cs, Y.w1_bf, ex.xg(1), false, ex.st(1), [&](int row, int n, const float (&v)[4]) {
           const float r[4] = {fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f)};
           const u32x2 p = pl_pack4(r);
           pl_store8(ex.hid() + pl_at(a.RP, row, n), p[0], p[1]);
-        })) return;
-    if (!sum(CF{}, Y.w2, Y.v2, ex.hid(), ex.st(1), false, l + 1 == a.n_layers, ex.xg(2), ex.st(2))) return;
+        });
+      default: return sum(CF{}, Y.w2, Y.v2, ex.hid(), ex.st(1), false, l + 1 == a.n_layers, ex.xg(2), ex.st(2));
+    }
+  };
+  if constexpr (!TICKETS) {
+    for (int l = 0; l < a.n_layers; ++l) {
+      if (!stage(0, l) || !stage(1, l) || !stage(2, l) || !stage(3, l) || !stage(4, l) || !stage(5, l) || !stage(6, l) || !stage(7, l)) return;
+    }
+  } else {
+    __shared__ int drawn;
+    const int total = a.n_layers * kPlStages * NB;   // (ids of a pass: below 2^24)
+    while (true) {
+      if (threadIdx.x == 0) drawn = (int)(__hip_atomic_fetch_add(&a.tickets->drawn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u);
+      __syncthreads();
+      const int t = __builtin_amdgcn_readfirstlane(drawn), st = t / NB, l = st / kPlStages;
+      if (t >= total) return;
+      w = t - st * NB;
+      // everything before this stage: its tickets are out, so whoever holds them is running
+      unsigned spins = 0;
+      while (st > 0 && __hip_atomic_load(&a.tickets->done[st - 1], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) + 1u != (unsigned)NB)
+        if (!pl_again(spins, a)) return;
+      take_units();
+      if (!stage(st - l * kPlStages, l)) return;
+      __syncthreads();   // all stores of the workgroup are out (and the ticket has been read)
+      if (threadIdx.x == 0) __hip_atomic_fetch_add(&a.tickets->done[st], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
 }
 
@@ -751,7 +802,9 @@ __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decod
 bool persist_supported(int layers, int d, int F) {
   return layers <= kPlLayers && ((d == 512 && F == 2048) || (d == 1024 && F == 4096));
 }
-size_t persist_exch_bytes(int rows, int layers, int d, int F) { return (size_t)layers * pl_layer_bytes((rows + 15) & ~15, d, F); }
+size_t persist_exch_bytes(int rows, int layers, int d, int F) {
+  return kPlTicketBytes + (size_t)layers * pl_layer_bytes((rows + 15) & ~15, d, F);
+}
 
 int persist_plan(PlArgs& a, int d, int F) {
   a.RP = (a.R + 15) & ~15;
@@ -780,33 +833,48 @@ int persist_plan(PlArgs& a, int d, int F) {
   return sums <= NB ? NB : 0;
 }
 
-template <class WT, bool KV8, int NW, int KSD, int KSF, int MR, int FBW>
-static hipError_t pl_launch(hipStream_t st, const PlArgs& a, int NB) {
+template <class WT, bool KV8, int NW, int KSD, int KSF, int MR, int FBW, bool TICKETS>
+static hipError_t pl_launch(hipStream_t st, const PlArgs& a, int blocks) {
   constexpr int kBytes = (int)sizeof(PlLds<NW, (MR > 1 ? MR * FBW : 4)>);
   static_assert(kBytes <= 160 * 1024, "LDS of a CU");
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pl_decoder_kernel<WT, KV8, NW, KSD, KSF, MR, FBW>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pl_decoder_kernel<WT, KV8, NW, KSD, KSF, MR, FBW, TICKETS>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
   if (attr != hipSuccess) return attr;
-  SD_LAUNCH_TIMED((pl_decoder_kernel<WT, KV8, NW, KSD, KSF, MR, FBW>), dim3(NB), dim3((64 * NW)), kBytes, st, a);
+  SD_LAUNCH_TIMED((pl_decoder_kernel<WT, KV8, NW, KSD, KSF, MR, FBW, TICKETS>), dim3(blocks), dim3((64 * NW)), kBytes, st, a);
   return hipGetLastError();
 }
 template <class WT, bool KV8, int NW>
-static hipError_t pl_launch_items(hipStream_t st, const PlArgs& a, int NB) {
-  if (a.mr == 1) return a.fbw == 2 ? pl_launch<WT, KV8, NW, 4, 16, 1, 2>(st, a, NB) : pl_launch<WT, KV8, NW, 4, 16, 1, 4>(st, a, NB);
+static hipError_t pl_launch_items(hipStream_t st, const PlArgs& a) {
+  if (a.mr == 1) return a.fbw == 2 ? pl_launch<WT, KV8, NW, 4, 16, 1, 2, false>(st, a, a.NB) : pl_launch<WT, KV8, NW, 4, 16, 1, 4, false>(st, a, a.NB);
   if constexpr (sizeof(WT) == 1) return hipErrorInvalidValue;   // codes: passes of a few rows only
-  else return pl_launch<WT, KV8, NW, 4, 16, 2, 4>(st, a, NB);
+  else return pl_launch<WT, KV8, NW, 4, 16, 2, 4, false>(st, a, a.NB);
+}
+// the pass, and its second run by tickets (kPlTicketBlocks workgroups: a fraction of the chip, so that it costs little to start)
+template <class WT, bool KV8, int NW>
+static hipError_t pl_launch_both(hipStream_t st, PlArgs a) {
+  const hipError_t e = pl_launch_items<WT, KV8, NW>(st, a);
+  if (e != hipSuccess) return e;
+  a.err += 1;
+  a.poll_mask = 63;
+  a.spin_max = kPlTicketSpinMax;
+  return pl_launch<WT, KV8, NW, 4, 16, 1, 2, true>(st, a, kPlTicketBlocks);
 }
 template <class WT, bool KV8>
-static hipError_t pl_launch_dims(hipStream_t st, const PlArgs& a, int d, int NB) {
-  return d == 512 ? pl_launch_items<WT, KV8, 4>(st, a, NB) : pl_launch_items<WT, KV8, 8>(st, a, NB);
+static hipError_t pl_launch_dims(hipStream_t st, const PlArgs& a, int d) {
+  return d == 512 ? pl_launch_both<WT, KV8, 4>(st, a) : pl_launch_both<WT, KV8, 8>(st, a);
 }
 
-hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F) {
+hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F, bool give_up) {
   if (a.R < 1 || a.T < 1 || a.T > 32 || a.R != a.B * a.T || !persist_supported(a.n_layers, d, F)) return hipErrorInvalidValue;
-  const int NB = persist_plan(a, d, F);
-  if (NB < 1) return hipErrorInvalidValue;
-  if (a.fp8) return a.xk_scale ? pl_launch_dims<fp8, true>(st, a, d, NB) : pl_launch_dims<fp8, false>(st, a, d, NB);
-  return a.xk_scale ? pl_launch_dims<bf16, true>(st, a, d, NB) : pl_launch_dims<bf16, false>(st, a, d, NB);
+  a.NB = persist_plan(a, d, F);
+  if (a.NB < 1) return hipErrorInvalidValue;
+  a.tickets = reinterpret_cast<PlTickets*>(a.exch);
+  a.exch += kPlTicketBytes;
+  a.raised = a.err;
+  a.poll_mask = give_up ? 0 : 63;
+  a.spin_max = give_up ? 0 : kPlSpinMax;
+  if (a.fp8) return a.xk_scale ? pl_launch_dims<fp8, true>(st, a, d) : pl_launch_dims<fp8, false>(st, a, d);
+  return a.xk_scale ? pl_launch_dims<bf16, true>(st, a, d) : pl_launch_dims<bf16, false>(st, a, d);
 }
 
 }  // namespace sd

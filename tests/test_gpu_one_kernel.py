@@ -92,3 +92,37 @@ def test_two_contexts_and_replays():
         assert acc.cpu().tolist() == out["accept"].tolist() and nxt.cpu().tolist() == out["next"].tolist()
         assert np.array_equal(gh.gpu_verify(first, case)["logits"], out["logits"])
     first.close()
+
+
+@pytest.mark.parametrize("d,B,k,S,lo,hi,opts", [
+    (512, 1, 5, 32, 16, 16, {}),
+    (512, 2, 15, 200, 180, 220, {}),         # a unit of attention per workgroup, every wave with key chunks
+    (512, 42, 2, 20, 0, 30, {}),             # more units than workgroups
+    (512, 32, 7, 20, 60, 90, {}),            # 256 rows, items of 32: more items of 16 than workgroups
+    (1024, 64, 1, 40, 50, 70, {}),
+    (1024, 11, 10, 150, 100, 130, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
+    (1024, 1, 30, 33, 9, 9, {sd.SPECDEC_OPT_FP8_WEIGHTS: 1, sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
+])
+def test_waits_given_up(d, B, k, S, lo, hi, opts):
+    """Waits of the kernel given up at once (it ends, half of its results missing): the kernel behind it computes the pass,
+    to the last bit as the waiting one; so do the passes after it, which find the flag raised, until a new run begins."""
+    case = cases.make_verify_case(desc(d), seed=d + B, B=B, S=S, k=k, beta=3, tau=1.0, len_lo=lo, len_hi=hi, drafts="random",
+                                  ragged_src=True, fp8=sd.SPECDEC_OPT_FP8_WEIGHTS in opts, fp8_kv=sd.SPECDEC_OPT_FP8_CROSS_KV in opts)
+    cases.run_oracle(case)
+    ses = gh.open_verifier(case, options=opts, fill=0xFF)
+    L = case.L_max + k + 1
+    want, cache = gh.gpu_verify(ses, case), gh.gpu_cache(ses, case, L)
+    check(case, want)
+    sd.specdec_profile_select(ses.ctx, sd.KIND["resident"])
+    times = []
+    for give_up in (0, 1, 0):
+        sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_GIVE_UP_WAITS, give_up)
+        got = gh.gpu_verify(ses, case)
+        times.append(sd.specdec_profile_read(ses.ctx)[0])
+        for key in ("logits", "accept", "next", "stats"):
+            assert np.array_equal(got[key], want[key]), (give_up, key)
+        for x, y in zip(gh.gpu_cache(ses, case, L), cache):
+            for b, j in enumerate(case.lens):
+                assert np.array_equal(x[:, b, :j + k + 1], y[:, b, :j + k + 1])
+    print(f"one-kernel decoder {times[0]:.3f} ms, given up {times[1]:.3f} ms, flag raised {times[2]:.3f} ms")
+    ses.close()
