@@ -2,12 +2,6 @@
 // of every entry point declared in include/specdec.h.
 #include <hip/hip_runtime.h>
 
-#include <sys/socket.h>
-#include <sys/un.h>
-#include <unistd.h>
-
-#include <atomic>
-#include <cerrno>
 #include <cmath>
 #include <cstdarg>
 #include <cstddef>
@@ -20,6 +14,7 @@
 
 #include "../../include/specdec.h"
 #include "kernels.h"
+#include "process_lock.h"
 
 using sd::bf16;
 
@@ -555,37 +550,26 @@ int decoder_layers_sliced(specdec_ctx* c, Model& m, int B, int T, hipStream_t st
 }
 
 // The one-kernel decoder keeps its workgroups waiting for each other, and two such passes that share a GPU's compute units
-// half-started wait in vain until their bound (persist.hip completes them another way then).  So contexts whose passes go to one stream take turns there; the first to ask names the stream, and while it
-// lives, a pass of another context on another stream takes the kernel-per-stage path.  A captured pass may be replayed on any
-// stream, so a context that captures one is alone with its GPU until it is destroyed (or, where it is not alone, captures the
-// kernel-per-stage path).  Among processes the user is the one that could bind a socket named after the GPU's PCI address,
-// which the system gives back when the process ends, however it ends.
+// half-started wait in vain until their bound (persist.hip completes them another way then).  So contexts whose passes go to
+// one stream take turns there; the first to ask names the stream, and while it lives, a pass of another context on another
+// stream takes the kernel-per-stage path.  A captured pass may be replayed on any stream, so a context that captures one
+// is alone with its GPU until it is destroyed (or, where it is not alone, captures the kernel-per-stage path).  Among processes
+// the user is the one that holds the lock named after the GPU's PCI address.
 constexpr int kMaxDevices = 64;
 struct PersistGpu {
   hipStream_t stream = nullptr;
   int users = 0;             // contexts
   bool captured = false;     // by the only one
-  int lock = -1, cus = 0;
+  sd::ProcessLock lock;
 };
 PersistGpu persist_gpu[kMaxDevices];
 std::mutex persist_mutex;
 
 bool persist_open(PersistGpu& o, int dev) {
-  sockaddr_un name{};
-  name.sun_family = AF_UNIX;
-  char bus[32];
-  if (hipDeviceGetAttribute(&o.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipDeviceGetPCIBusId(bus, sizeof bus, dev) != hipSuccess)
-    return false;
-  const int n = snprintf(name.sun_path + 1, sizeof name.sun_path - 1, "specdec-%s", bus);
-  const int fd = socket(AF_UNIX, SOCK_DGRAM | SOCK_CLOEXEC, 0);
-  if (fd >= 0 && bind(fd, reinterpret_cast<sockaddr*>(&name), (socklen_t)(offsetof(sockaddr_un, sun_path) + 1 + n)) != 0 &&
-      errno == EADDRINUSE) {
-    close(fd);
-    return false;
-  }
-  o.lock = fd;
-  return true;
+  char bus[32], name[64];
+  if (hipDeviceGetPCIBusId(bus, sizeof bus, dev) != hipSuccess) return false;
+  snprintf(name, sizeof name, "specdec-%s", bus);
+  return o.lock.take(name);
 }
 void persist_release(specdec_ctx* c) {
   if (c->persist_dev < 0) return;
@@ -593,8 +577,7 @@ void persist_release(specdec_ctx* c) {
   PersistGpu& o = persist_gpu[c->persist_dev];
   if (--o.users) return;
   o.captured = false;
-  if (o.lock >= 0) close(o.lock);
-  o.lock = -1;
+  o.lock.drop();
 }
 
 bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
@@ -603,8 +586,10 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
   sd::PlArgs a{};
   a.R = R; a.T = T; a.B = B; a.H = m.d.n_heads;
   const int blocks = sd::persist_plan(a, m.d.d_model, m.d.d_ffn);
-  int dev = -1;
-  if (blocks < 1 || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+  int dev = -1, cus = 0;
+  if (blocks < 1 || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < blocks)
+    return false;
   if (c->persist_dev >= 0 && c->persist_dev != dev) return false;
   bool capturing = false;
   if (st) {
@@ -623,7 +608,7 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
   }
   o.stream = st;
   o.captured |= capturing;
-  return o.cus >= blocks;
+  return true;
 }
 
 // few: as in decoder_layers (the E4M3 copies of the weights, if the model has them)
