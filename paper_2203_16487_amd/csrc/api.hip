@@ -580,6 +580,16 @@ void persist_release(specdec_ctx* c) {
   o.lock.drop();
 }
 
+// Compute units a kernel on this stream may use: a stream can be made with a mask of them, and the environment can set one for
+// the process (one that the HIP runtime does not report is taken for none at all).
+int stream_cus(hipStream_t st) {
+  uint32_t mask[32] = {};
+  if (getenv("HSA_CU_MASK") || hipExtStreamGetCUMask(st, 32, mask) != hipSuccess) return 0;
+  int n = 0;
+  for (uint32_t word : mask) n += __builtin_popcount(word);
+  return n;
+}
+
 bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
   const int R = B * T;
   if (!m.pl_exch || R > m.pl_rows || T > 32 || c->no_skinny || c->no_ln_fold || c->sliced) return false;
@@ -588,7 +598,8 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
   const int blocks = sd::persist_plan(a, m.d.d_model, m.d.d_ffn);
   int dev = -1, cus = 0;
   if (blocks < 1 || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < blocks)
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < blocks ||
+      stream_cus(st) < blocks)
     return false;
   if (c->persist_dev >= 0 && c->persist_dev != dev) return false;
   bool capturing = false;

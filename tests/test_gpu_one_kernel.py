@@ -1,6 +1,8 @@
 """The decoder layers of a pass of few rows as one kernel (d_model 512 / 1024): row tiles and their remainders, queries beyond
 one tile of 16, key chunks split over the waves and not, a unit of attention per workgroup and per wave, E4M3 weights and
 cross keys / values, against the oracle; the path a second context takes; replays of a captured pass."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -125,4 +127,38 @@ def test_waits_given_up(d, B, k, S, lo, hi, opts):
             for b, j in enumerate(case.lens):
                 assert np.array_equal(x[:, b, :j + k + 1], y[:, b, :j + k + 1])
     print(f"one-kernel decoder {times[0]:.3f} ms, given up {times[1]:.3f} ms, flag raised {times[2]:.3f} ms")
+    ses.close()
+
+
+def resident_launches(ses, run):
+    """How often the one-kernel decoder was launched by run(), and run()'s result."""
+    sd.specdec_profile_select(ses.ctx, sd.KIND["resident"])
+    out = run()
+    n = sd.specdec_profile_read(ses.ctx)[1]
+    sd.specdec_profile_select(ses.ctx, sd.KIND["none"])
+    return n, out
+
+
+def masked_stream(words):
+    """A stream whose kernels may use the compute units of this mask only."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    hip, handle = C.CDLL(path), C.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(C.byref(handle), C.c_uint32(len(words)), (C.c_uint32 * len(words))(*words)) == 0
+    return torch.cuda.ExternalStream(handle.value)
+
+
+def test_stream_with_few_compute_units():
+    """The kernel's workgroups wait for each other: a stream that may not use as many compute units as there are workgroups
+    takes separate launches."""
+    case = cases.make_verify_case(desc(512), seed=42, B=42, S=20, k=2, beta=3, tau=1.0, len_lo=0, len_hi=30, drafts="random", ragged_src=True)
+    cases.run_oracle(case)
+    ses = gh.open_verifier(case, fill=0xFF)
+    assert resident_launches(ses, lambda: gh.gpu_verify(ses, case))[0] == 1
+    torch.cuda.synchronize()
+    half = masked_stream([0xffffffff] * 4 + [0] * 4)
+    with torch.cuda.stream(half):
+        n, out = resident_launches(ses, lambda: gh.gpu_verify(ses, case))
+    half.synchronize()
+    assert n == 0
+    check(case, out)
     ses.close()
