@@ -232,9 +232,17 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * kernel of another stream or process keeps some of them from starting for 0.1 s or more, the waits
  * are given up and a second kernel, which needs no more than one free compute unit, computes
  * the pass instead (same bits, 0.5 - 3 ms); the run's later passes then go to that kernel
- * directly, until the next specdec_begin.
+ * directly, until the next specdec_begin.  One stream of one process at a time runs such passes on a
+ * GPU: that of the first context to ask, until it and the others on its stream are destroyed (a
+ * context that captures one: until it is destroyed, whatever the stream).  A context on another
+ * stream or in another process runs its passes as separate launches, from the first pass refused to its
+ * next specdec_begin.  So does a stream with fewer compute units than the pass has workgroups.  The
+ * two ways add in different orders: their logits differ in the last bits.  Processes in different
+ * network name spaces (containers) do not see each other: their passes may meet, and are then completed
+ * as above.
  * logits_or_null: optional device fp32 [B, k+1, V] receiving every row's logits (parity
- * mode; slow).  Does not change any length: calling it twice gives the same result. */
+ * mode; slow).  Does not change any length: calling it twice, on the same stream and within one run
+ * (not captured in between), gives the same result. */
 int specdec_verify(specdec_ctx* ctx, const int32_t* draft, int32_t k, int32_t beta, float tau,
                    int32_t* accept_len, int32_t* next_token, float* logits_or_null, void* stream);
 

@@ -133,6 +133,7 @@ struct specdec_ctx {
   bool no_ln_fold = false;  // SPECDEC_OPT_LN_FOLD = 0: LayerNorm as a pass of its own between the GEMMs
   bool resident = false;    // SPECDEC_OPT_RESIDENT = 1: small batches run the decoder pass as one resident kernel
   int persist_dev = -1;     // GPU on which this context is among the users of the one-kernel decoder
+  bool persist_refused = false;   // another user was found on it in this run: separate launches until the next specdec_begin
   bool give_up = false;     // SPECDEC_OPT_GIVE_UP_WAITS = 1: the one-kernel decoder's waits are given up at once
   bool sliced = false;      // SPECDEC_OPT_SLICED_SUBLAYERS = 1: small-batch sub-layers owned by head / FFN slice
   bool fp8 = false;         // SPECDEC_OPT_FP8_WEIGHTS = 1: models bound from now on keep E4M3 copies for small batches
@@ -601,7 +602,7 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < blocks ||
       stream_cus(st) < blocks)
     return false;
-  if (c->persist_dev >= 0 && c->persist_dev != dev) return false;
+  if (c->persist_refused || (c->persist_dev >= 0 && c->persist_dev != dev)) return false;
   bool capturing = false;
   if (st) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -611,8 +612,10 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
   std::lock_guard<std::mutex> guard(persist_mutex);
   PersistGpu& o = persist_gpu[dev];
   const bool user = c->persist_dev == dev;
-  if (o.users > (user ? 1 : 0) && (o.captured || capturing || st != o.stream || st == hipStreamPerThread)) return false;
-  if (!o.users && !persist_open(o, dev)) return false;
+  // (for the whole run: the two ways add in different orders, and which one a pass takes is not to change with the life of others)
+  c->persist_refused = (o.users > (user ? 1 : 0) && (o.captured || capturing || st != o.stream || st == hipStreamPerThread)) ||
+                       (!o.users && !persist_open(o, dev));
+  if (c->persist_refused) return false;
   if (!user) {
     ++o.users;
     c->persist_dev = dev;
@@ -906,6 +909,7 @@ int specdec_begin(specdec_ctx* c, int32_t B, int32_t max_new, void* stream) {
   c->uncached_ub[0] = 0;
   c->uncached_ub[1] = 1;
   c->trusted[0] = c->trusted[1] = false;
+  c->persist_refused = false;
   c->m[0].has_memory = c->m[1].has_memory = false;
   return SPECDEC_OK;
 }

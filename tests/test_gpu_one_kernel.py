@@ -162,3 +162,40 @@ def test_stream_with_few_compute_units():
     assert n == 0
     check(case, out)
     ses.close()
+
+
+def restart(ses, case):
+    """A new run on the case's streams, memory and cache."""
+    sd.specdec_begin(ses.ctx, case.B, 10 ** 6)
+    sd.specdec_set_memory(ses.ctx, sd.SPECDEC_VERIFIER, ses.bf16(case.memory), ses.i32(case.src_len))
+    sd.specdec_set_stream(ses.ctx, ses.i32(case.tokens), ses.i32(case.lens))
+    K, V = cases.oracle_flat_cache(case, max(case.L_max, 1))
+    sd.specdec_load_cache(ses.ctx, sd.SPECDEC_VERIFIER, ses.bf16(K), ses.bf16(V), ses.i32(case.lens))
+
+
+@pytest.mark.parametrize("B,k", [(1, 5), (1, 11), (1, 12), (2, 5), (7, 10)])   # the fused small-batch kernels up to 12 rows, the general ones
+def test_way_of_a_run_does_not_change(B, k):
+    """A context refused the one-kernel decoder, because another one on another stream has it, keeps its separate launches when
+    that one is gone, until its next run: a pass repeated gives the same bits."""
+    case = cases.make_verify_case(desc(512), seed=50 + 10 * B + k, B=B, S=30, k=k, beta=3, tau=1.0, len_lo=3, len_hi=20,
+                                  drafts="greedy", ragged_src=True)
+    cases.run_oracle(case)
+    first = gh.open_verifier(case, fill=0xFF)
+    n, out = resident_launches(first, lambda: gh.gpu_verify(first, case))
+    assert n == 1
+    second = gh.open_verifier(case, fill=0xFF)
+    other = torch.cuda.Stream()
+    other.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(other):
+        n, apart = resident_launches(second, lambda: gh.gpu_verify(second, case))
+        assert n == 0
+        check(case, apart)
+        other.synchronize()
+        first.close()
+        n, again = resident_launches(second, lambda: gh.gpu_verify(second, case))
+        assert n == 0 and np.array_equal(again["logits"], apart["logits"])
+        restart(second, case)
+        n, alone = resident_launches(second, lambda: gh.gpu_verify(second, case))
+        assert n == 1 and np.array_equal(alone["logits"], out["logits"])
+        other.synchronize()
+        second.close()
