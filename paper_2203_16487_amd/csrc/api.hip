@@ -561,6 +561,7 @@ struct PersistGpu {
   hipStream_t stream = nullptr;
   int users = 0;             // contexts
   bool captured = false;     // by the only one
+  bool draining = false;     // the last user is gone, a pass of its may still run on `stream`
   sd::ProcessLock lock;
 };
 PersistGpu persist_gpu[kMaxDevices];
@@ -572,12 +573,26 @@ bool persist_open(PersistGpu& o, int dev) {
   snprintf(name, sizeof name, "specdec-%s", bus);
   return o.lock.take(name);
 }
+// Nothing of the users before is left on their stream.  (Not asked during a capture on this stream, and so that one on another
+// thread's does not end by it.)
+bool persist_free(PersistGpu& o, hipStream_t st, bool capturing) {
+  if (o.draining && o.stream != st) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (capturing || hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+    const bool busy = hipStreamQuery(o.stream) == hipErrorNotReady;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (busy) return false;
+  }
+  o.draining = false;
+  return true;
+}
 void persist_release(specdec_ctx* c) {
   if (c->persist_dev < 0) return;
   std::lock_guard<std::mutex> guard(persist_mutex);
   PersistGpu& o = persist_gpu[c->persist_dev];
   if (--o.users) return;
   o.captured = false;
+  o.draining = true;
   o.lock.drop();
 }
 
@@ -614,7 +629,7 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
   const bool user = c->persist_dev == dev;
   // (for the whole run: the two ways add in different orders, and which one a pass takes is not to change with the life of others)
   c->persist_refused = (o.users > (user ? 1 : 0) && (o.captured || capturing || st != o.stream || st == hipStreamPerThread)) ||
-                       (!o.users && !persist_open(o, dev));
+                       (!o.users && !persist_free(o, st, capturing)) || (!o.users && !persist_open(o, dev));
   if (c->persist_refused) return false;
   if (!user) {
     ++o.users;

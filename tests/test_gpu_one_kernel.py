@@ -199,3 +199,31 @@ def test_way_of_a_run_does_not_change(B, k):
         assert n == 1 and np.array_equal(alone["logits"], out["logits"])
         other.synchronize()
         second.close()
+
+
+def test_pass_in_flight_when_its_context_ends():
+    """A context destroyed before its latest pass has run: a context on another stream does not start one beside it."""
+    case = cases.make_verify_case(desc(512), seed=60, B=7, S=30, k=10, beta=3, tau=1.0, len_lo=3, len_hi=20, drafts="greedy", ragged_src=True)
+    cases.run_oracle(case)
+    first, second = gh.open_verifier(case, fill=0xFF), gh.open_verifier(case, fill=0xFF)
+    acc, nxt, d = first.i32(np.zeros(7)), first.i32(np.zeros(7)), first.i32(case.drafts)
+    one, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    busy = torch.empty(1 << 28, dtype=torch.float32, device="cuda")
+    with torch.cuda.stream(one):
+        for _ in range(200):                           # some tens of milliseconds ahead of the pass
+            busy.add_(1.0)
+        sd.specdec_verify(first.ctx, d, case.k, case.beta, case.tau, acc, nxt)
+    sd.specdec_destroy(first.ctx)                      # (what it points to stays)
+    first.ctx = None
+    with torch.cuda.stream(other):
+        n, out = resident_launches(second, lambda: gh.gpu_verify(second, case))   # (waits for both)
+    torch.cuda.synchronize()
+    assert n == 0
+    check(case, out)
+    assert acc.cpu().tolist() == out["accept"].tolist()
+    restart(second, case)
+    with torch.cuda.stream(other):
+        assert resident_launches(second, lambda: gh.gpu_verify(second, case))[0] == 1
+        other.synchronize()
+    second.close()
