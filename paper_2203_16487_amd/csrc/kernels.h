@@ -91,8 +91,8 @@ hipError_t ln_fold(hipStream_t st, const bf16* W, const bf16* g, const bf16* bet
 hipError_t ln_fold8(hipStream_t st, const SkWeight& W, const bf16* g, const bf16* beta, const bf16* b, int N, int K,
                     const LnFold& out);
 // The column vectors of one producing GEMM, fp32 [3][d] in one piece: gain of the LayerNorm
-// pending on the residual (1 when g_prev is null), its shift (0 when null) + the GEMM's bias,
-// gain of the LayerNorm that follows.
+// pending on the residual (1 when g_prev is null), its shift (0 when null) + the GEMM's bias less the mean of both (the
+// sums are followed by a LayerNorm, which does not see it), gain of the LayerNorm that follows.
 hipError_t ln_sum_vecs(hipStream_t st, const bf16* bias, const bf16* g_prev, const bf16* b_prev, const bf16* g_next,
                        int d, float* out);
 // Chunk pairs of a residual sum: chunks per row = d / 64, or d / 32 where the kernel that formed them has tiles of 32

@@ -24,35 +24,57 @@ hipError_t build_pos_table(hipStream_t st, float* pe, int n_pos, int d) {
 }
 
 // ----------------------------------------------------------------------------- embedding
-// x[r] = E[tok[r]] * sqrt(d) + PE[pos[r]]  (fp32) and its bf16 copy
-// `threads` threads per row (this one is number t), 8 columns per thread and step (d % 64 == 0).
+// xb[r] = E[tok[r]] * sqrt(d) + PE[pos[r]] in bf16, and x[r] the same in fp32 less the row's mean: x only ever enters residual
+// sums that a LayerNorm follows, and sums that lie about zero lose nothing when they are rounded before it (LnFold, gemm.hip).
+// (The positions alone would put a row off by half its standard deviation.)
+// 128 threads per row (this one is number t), 8 columns per thread and step (d % 64 == 0, d <= 2048); red: two floats of LDS.
+// Meets a barrier: every thread of the block calls it, `live` or not.
 __device__ __forceinline__ void embed_row(const bf16* __restrict__ e, const float* __restrict__ p,
                                           float* __restrict__ xr, bf16* __restrict__ xbr, int d, float scale,
-                                          int t, int threads) {
-  for (int c = t * 8; c < d; c += threads * 8) {
+                                          int t, float* red, bool live = true) {
+  f32x4 v[2][2];
+  float s = 0.f;
+#pragma unroll
+  for (int st = 0; st < 2; ++st) {
+    const int c = t * 8 + st * 1024;
+    if (!live || c >= d) continue;
     const bf16x8 ev = *reinterpret_cast<const bf16x8*>(e + c);
     const f32x4 p0 = *reinterpret_cast<const f32x4*>(p + c), p1 = *reinterpret_cast<const f32x4*>(p + c + 4);
-    f32x4 v0, v1;
     bf16x8 o;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      v0[i] = (float)ev[i] * scale + p0[i];
-      v1[i] = (float)ev[4 + i] * scale + p1[i];
-      o[i] = (bf16)v0[i];
-      o[4 + i] = (bf16)v1[i];
+      v[st][0][i] = (float)ev[i] * scale + p0[i];
+      v[st][1][i] = (float)ev[4 + i] * scale + p1[i];
+      o[i] = (bf16)v[st][0][i];
+      o[4 + i] = (bf16)v[st][1][i];
+      s += v[st][0][i] + v[st][1][i];
     }
-    *reinterpret_cast<f32x4*>(xr + c) = v0;
-    *reinterpret_cast<f32x4*>(xr + c + 4) = v1;
     *reinterpret_cast<bf16x8*>(xbr + c) = o;
+  }
+  s = wave_sum(s);
+  if ((t & 63) == 0) red[t >> 6] = s;
+  __syncthreads();
+  const float mean = (red[0] + red[1]) / (float)d;
+#pragma unroll
+  for (int st = 0; st < 2; ++st) {
+    const int c = t * 8 + st * 1024;
+    if (!live || c >= d) continue;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[st][h][i] -= mean;
+      *reinterpret_cast<f32x4*>(xr + c + 4 * h) = v[st][h];
+    }
   }
 }
 __global__ __launch_bounds__(128) void embed_kernel(const int* __restrict__ tok, const int* __restrict__ pos,
                                                     const bf16* __restrict__ E, const float* __restrict__ pe,
                                                     float* __restrict__ x, bf16* __restrict__ xb, int R, int d,
                                                     float scale) {
+  __shared__ float red[2];
   const int r = blockIdx.x;
   if (r >= R) return;
-  embed_row(E + (size_t)tok[r] * d, pe + (size_t)pos[r] * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale, threadIdx.x, 128);
+  embed_row(E + (size_t)tok[r] * d, pe + (size_t)pos[r] * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale, threadIdx.x, red);
 }
 hipError_t embed_rows(hipStream_t st, const int* tok, const int* pos, const bf16* E,
                       const float* pe, float* x, bf16* xb, int R, int d) {
@@ -209,6 +231,7 @@ __global__ __launch_bounds__(128) void assemble_embed_verify_kernel(SeqState s, 
                                                                     const float* __restrict__ pe,
                                                                     float* __restrict__ x, bf16* __restrict__ xb, int d,
                                                                     float scale, uint4* __restrict__ clear, long n16) {
+  __shared__ float red[2];
   const int idx = blockIdx.x, T = k + 1;
   if (idx >= B * T) {   // the blocks beyond the rows clear
     for (long i = (long)(idx - B * T) * 128 + threadIdx.x; i < n16; i += (long)(gridDim.x - B * T) * 128)
@@ -228,7 +251,7 @@ __global__ __launch_bounds__(128) void assemble_embed_verify_kernel(SeqState s, 
     if (i < k) s.last_draft[b * s.k_max + i] = draft[b * k + i];
     if (i == 0) rm.seq_rows[b] = T;
   }
-  embed_row(E + (size_t)tok * d, pe + (size_t)(j + i) * d, x + (size_t)idx * d, xb + (size_t)idx * d, d, scale, threadIdx.x, 128);
+  embed_row(E + (size_t)tok * d, pe + (size_t)(j + i) * d, x + (size_t)idx * d, xb + (size_t)idx * d, d, scale, threadIdx.x, red);
 }
 hipError_t assemble_embed_verify(hipStream_t st, const SeqState& s, const RowMap& rm, const int* draft, int B, int k,
                                  int V, const bf16* E, const float* pe, float* x, bf16* xb, int d, void* clear,
@@ -273,6 +296,7 @@ __global__ __launch_bounds__(128) void assemble_embed_stream_kernel(SeqState s, 
                                                                     float* __restrict__ x, bf16* __restrict__ xb, int d,
                                                                     float scale) {
   __shared__ int wsum[2];
+  __shared__ float red[2];
   const int b = blockIdx.x / T, i = blockIdx.x - b * T;
   const StreamRows me = stream_rows(s, role, b, T, n_mask);
   int first = b * T;
@@ -304,7 +328,7 @@ __global__ __launch_bounds__(128) void assemble_embed_stream_kernel(SeqState s, 
   if (threadIdx.x == 0) {
     rm.row_b[r] = rb; rm.row_pos[r] = pos; rm.row_tok[r] = tok; rm.row_lim[r] = lim; rm.row_draft[r] = -1;
   }
-  embed_row(E + (size_t)tok * d, pe + (size_t)pos * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale, threadIdx.x, 128);
+  embed_row(E + (size_t)tok * d, pe + (size_t)pos * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale, threadIdx.x, red);
 }
 hipError_t assemble_embed_stream(hipStream_t st, const SeqState& s, const RowMap& rm, int role, int B, int T,
                                  int n_mask, int mask_id, int pad_id, int V, int* new_rows, const bf16* E,
@@ -356,6 +380,7 @@ __global__ __launch_bounds__(256) void encoder_rows_embed_kernel(const int* __re
                                                                  const float* __restrict__ pe, float* __restrict__ x,
                                                                  bf16* __restrict__ xb, int d, float scale) {
   __shared__ int wsum[4];
+  __shared__ float red[2][4];   // (rows take turns)
   const int per = (S + kEncRows - 1) / kEncRows, b = blockIdx.x / per, s0 = (blockIdx.x - b * per) * kEncRows;
   const int len = min(max(src_len[b], 0), S);
   if (s0 >= len && s0 > 0) return;
@@ -372,10 +397,11 @@ __global__ __launch_bounds__(256) void encoder_rows_embed_kernel(const int* __re
   }
   // half a wave-quad per row: two rows at a time
   const int lo = threadIdx.x >> 7, t = threadIdx.x & 127;
-  for (int i = lo; i < kEncRows && s0 + i < len; i += 2) {
-    const int s = s0 + i, r = first + s, tok = min(max(src[(size_t)b * S + s], 0), V - 1);
-    if (t == 0) { pos[r] = s; row_b[r] = b; }
-    embed_row(E + (size_t)tok * d, pe + (size_t)s * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale, t, 128);
+  for (int i = 0; i < kEncRows && s0 + i < len; i += 2) {
+    const bool live = s0 + i + lo < len;
+    const int s = min(s0 + i + lo, len - 1), r = first + s, tok = min(max(src[(size_t)b * S + s], 0), V - 1);
+    if (t == 0 && live) { pos[r] = s; row_b[r] = b; }
+    embed_row(E + (size_t)tok * d, pe + (size_t)s * d, x + (size_t)r * d, xb + (size_t)r * d, d, scale, t, red[(i >> 1) & 1] + 2 * lo, live);
   }
 }
 hipError_t encoder_rows_embed(hipStream_t st, const int* src, const int* src_len, int* pos, int* row_b, int* row_start,
