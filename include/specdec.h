@@ -73,7 +73,8 @@ typedef enum {
   SPECDEC_OPT_SMALL_BATCH_KERNELS = 0, /* default 1: passes of at most 32 rows use the small-batch kernels: the fused decoder
                                           kernels where they are the faster ones (one sequence of at most 12 rows,
                                           d_model <= 512), else the general ones; the small-batch vocabulary kernel   */
-  SPECDEC_OPT_LN_FOLD = 1,             /* default 1: decoder LayerNorms folded into the projections around them  */
+  SPECDEC_OPT_LN_FOLD = 1,             /* default 1: LayerNorms folded into the projections around them; 0: a pass of their own
+                                          between them, encoder (from the next specdec_encode) and decoder        */
   SPECDEC_OPT_RESIDENT = 2,            /* the decoder layers of a pass of few rows run as ONE kernel wherever that kernel
                                           applies (d_model 512 / 1024), whether this is set or not; setting it refuses
                                           models bound with FP8 storage in passes of at most 32 rows                  */
@@ -118,7 +119,7 @@ int specdec_create(specdec_ctx** out, const specdec_limits* limits); /* host onl
 void specdec_destroy(specdec_ctx* ctx);
 const char* specdec_last_error(const specdec_ctx* ctx); /* (host) valid until the next call */
 /* Chooses between kernel paths that compute the same pass (all are parity-tested against each other);
- * takes effect from the next specdec_verify / specdec_draft / specdec_prefill.  SPECDEC_OPT_FP8_WEIGHTS and
+ * takes effect from the next specdec_verify / specdec_draft / specdec_prefill / specdec_encode.  SPECDEC_OPT_FP8_WEIGHTS and
  * SPECDEC_OPT_FP8_CROSS_KV are the exception on both counts: they select a storage format, and are read by
  * specdec_workspace_bytes and specdec_bind_model.  Host only. */
 int specdec_configure(specdec_ctx* ctx, int32_t option, int32_t value);

@@ -951,6 +951,7 @@ static int encoder_pass(specdec_ctx* c, Model& m, const int32_t* src, int B, int
   LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::encoder_rows_embed(st, src, c->st.src_len, m.epos, m.erow_b, m.erow_start, m.en_rows, B,
                                                            S_max, m.d.vocab, m.embed, m.pe, m.ex, m.exb, D));
   // LayerNorm folded into the projections, as in decoder_layers: m.ex holds un-normalised sums, m.exb them times the gain
+  const bool fold = !c->no_ln_fold;
   sd::LnPairs pend{m.elnp[0], 0};
   int flip = 1;
   auto sum = [&](const bf16* A, int K, const bf16* W, const float* vecs) {
@@ -963,7 +964,8 @@ static int encoder_pass(specdec_ctx* c, Model& m, const int32_t* src, int B, int
   for (int l = 0; l < m.d.enc_layers; ++l) {
     const EncLayer& L = m.enc[l];
     const EncFolds& f = m.efolds[l];
-    LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_ln_bf16(st, m.exb, L.wqkv, R, 3 * D, D, f.qkv, pend, m.eqkv, 3 * D, false, nr));
+    if (fold) LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_ln_bf16(st, m.exb, L.wqkv, R, 3 * D, D, f.qkv, pend, m.eqkv, 3 * D, false, nr));
+    else LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_bf16(st, m.exb, D, L.wqkv, R, 3 * D, D, L.bqkv, m.eqkv, 3 * D, false, nr));
     sd::AttnArgs a{};
     a.q = m.eqkv; a.q_row = 3 * D;
     a.k = m.eqkv + D; a.k_h = 64; a.k_row = 3 * D;
@@ -972,9 +974,17 @@ static int encoder_pass(specdec_ctx* c, Model& m, const int32_t* src, int B, int
     a.q_count = c->st.src_len; a.q_off = m.erow_start; a.kv_off = m.erow_start; a.lim_row = nullptr; a.lim_seq = c->st.src_len;
     a.T = S_max; a.H = H; a.B = B; a.cap = c->Scap;
     LAUNCH(c, SPECDEC_KIND_ATTN, st, sd::attention(st, a));
-    LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.eatt, D, L.wo, f.vo));
-    LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_ln_bf16(st, m.exb, L.w1, R, F, D, f.w1, pend, m.ehid, F, true, nr));
-    LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.ehid, F, L.w2, f.v2));
+    if (fold) {
+      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.eatt, D, L.wo, f.vo));
+      LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_ln_bf16(st, m.exb, L.w1, R, F, D, f.w1, pend, m.ehid, F, true, nr));
+      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.ehid, F, L.w2, f.v2));
+    } else {
+      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sd::gemm_f32(st, m.eatt, D, L.wo, R, D, D, L.bo, m.ex, m.ex, D, nr));
+      LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, L.ln1g, L.ln1b, m.exb, R, D, nr));
+      LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_bf16(st, m.exb, D, L.w1, R, F, D, L.b1, m.ehid, F, true, nr));
+      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sd::gemm_f32(st, m.ehid, F, L.w2, R, D, F, L.b2, m.ex, m.ex, D, nr));
+      if (l + 1 < m.d.enc_layers) LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, L.ln2g, L.ln2b, m.exb, R, D, nr));
+    }
   }
   const EncLayer& last = m.enc[m.d.enc_layers - 1];
   LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, last.ln2g, last.ln2b, m.exb, R, D, nr, false));

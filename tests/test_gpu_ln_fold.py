@@ -25,6 +25,12 @@ def rel(got, want):
     return float(np.linalg.norm(got - want) / np.linalg.norm(want))
 
 
+def ses_launches(ses, run):
+    sd.specdec_profile_select(ses.ctx, sd.KIND["ln"])
+    run()
+    return sd.specdec_profile_read(ses.ctx)[1]
+
+
 # Operands are rounded to bf16: with the mean left in, the error of every folded LayerNorm is sqrt(1 + shift^2 / variance) times as
 # large, 4 times at shift 4 (sums have standard deviations of 1 .. 1.1).  1.1: errors of two samples of this size.
 SHIFT, BOUND = 4.0, 1.1
@@ -51,17 +57,19 @@ def test_verify_of_rows_off_zero(d, B, k):
 def test_encoder_rows_off_zero(d, S):
     desc = synth.ModelDesc(3, 1, d, d // 64, 4 * d, 1003, S, 16).resolved()
     src, err = synth.random_tokens(5, "src", (2, S), desc), []
-    for shift in (0.0, SHIFT):
+    for shift, fold in ((0.0, 0), (0.0, 1), (SHIFT, 1)):
         bits = shifted(desc, 5, shift)
         model = orc.Model(desc, synth.weights_f32(bits))
-        ses = sd.Session(2, 4, S, 16)
+        ses = sd.Session(2, 4, S, 16, fill=0xFF)
+        sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_LN_FOLD, fold)
         ses.bind_model(sd.SPECDEC_VERIFIER, desc, ses.upload_weights(bits))
         sd.specdec_begin(ses.ctx, 2, 8)
-        sd.specdec_encode(ses.ctx, ses.i32(src), ses.i32(np.full(2, S)))
+        launches = ses_launches(ses, lambda: sd.specdec_encode(ses.ctx, ses.i32(src), ses.i32(np.full(2, S))))
+        assert launches == (1 if fold else 2 * desc.enc_layers)        # LayerNorms as launches of their own
         mem = torch.zeros((2, S, d), dtype=torch.bfloat16, device=ses.device)
         sd.specdec_get_memory(ses.ctx, sd.SPECDEC_VERIFIER, mem)
         torch.cuda.synchronize()
         err.append(rel(mem.float().cpu().numpy(), np.stack([orc.encode(model, [int(t) for t in s]) for s in src])))
         ses.close()
-    print(f"encoder {d}: {err[0]:.2e}, off zero {err[1]:.2e}")
-    assert err[1] <= BOUND * err[0]
+    print(f"encoder {d}: not folded {err[0]:.2e}, folded {err[1]:.2e}, off zero {err[2]:.2e}")
+    assert max(err[1:]) <= BOUND * err[0]
