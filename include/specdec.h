@@ -75,9 +75,11 @@ typedef enum {
                                           d_model <= 512), else the general ones; the small-batch vocabulary kernel   */
   SPECDEC_OPT_LN_FOLD = 1,             /* default 1: LayerNorms folded into the projections around them; 0: a pass of their own
                                           between them, encoder (from the next specdec_encode) and decoder        */
-  SPECDEC_OPT_RESIDENT = 2,            /* the decoder layers of a pass of few rows run as ONE kernel wherever that kernel
-                                          applies (d_model 512 / 1024), whether this is set or not; setting it refuses
-                                          models bound with FP8 storage in passes of at most 32 rows                  */
+  SPECDEC_OPT_RESIDENT = 2,            /* default 0.  It once selected a kernel of its own for passes of at most 32 rows;
+                                          the one-kernel decoder (specdec_verify) that took its place runs wherever it
+                                          applies, whether this is set or not.  1 chooses no kernel: it keeps the
+                                          limits of that kernel, for callers that rely on them: passes of at most 32 rows
+                                          refuse models bound with FP8 storage and leave nothing to specdec_draft_heads  */
   SPECDEC_OPT_SLICED_SUBLAYERS = 3,    /* default 0: the small-batch kernels own sub-layers by output column (six
                                           kernels per layer); 1: by head / FFN slice (three per layer; measured
                                           slower: 8-16 workgroups cannot pull a layer's weights fast enough)      */

@@ -131,7 +131,7 @@ struct specdec_ctx {
   int prof_used = 0;
   bool no_skinny = false;   // SPECDEC_OPT_SMALL_BATCH_KERNELS = 0: always take the general kernels
   bool no_ln_fold = false;  // SPECDEC_OPT_LN_FOLD = 0: LayerNorm as a pass of its own between the GEMMs
-  bool resident = false;    // SPECDEC_OPT_RESIDENT = 1: small batches run the decoder pass as one resident kernel
+  bool resident = false;    // SPECDEC_OPT_RESIDENT = 1: refuses what a pass of at most 32 rows as one kernel once did not support
   int persist_dev = -1;     // GPU on which this context is among the users of the one-kernel decoder
   bool persist_refused = false;   // another user was found on it in this run: separate launches until the next specdec_begin
   bool give_up = false;     // SPECDEC_OPT_GIVE_UP_WAITS = 1: the one-kernel decoder's waits are given up at once
@@ -313,6 +313,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   if (sd::persist_supported(d->dec_layers, (int)D, (int)F)) {
     const size_t most = Bm * (c->lim.k_max + 1);
     t.pl_rows = (int)(most < persist_rows((int)D) ? most : persist_rows((int)D));
+    // (in a drafter's workspace too, which never uses it: the size is asked for without a role)
     t.pl_exch = cv.take<char>(sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F));
   }
   if (d->enc_layers > 0) {
@@ -1190,7 +1191,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
       rc = decoder_layers_skinny(c, m, B, T, st, &fin);
     if (rc) return rc;
     LAUNCH(c, SPECDEC_KIND_VOCAB, st, sd::skinny_vocab(st, fin, R, m.d.d_model, m.fp8 ? m.embed8 : sd::SkWeight(m.embed), m.d.vocab, m.rm.row_draft, vs.zd, vs.part, logits));
-    c->fin_x = fin.xs; c->fin_g = fin.g; c->fin_b = fin.b;
+    c->fin_x = c->resident ? nullptr : fin.xs; c->fin_g = fin.g; c->fin_b = fin.b;
   } else {
     if (one) {
       rc = decoder_layers_persist(c, m, B, T, false, st);
@@ -1264,6 +1265,7 @@ int specdec_draft_heads(specdec_ctx* c, const int32_t* accept_len, int32_t k, in
   if (k > c->n_draft_heads) return fail(c, SPECDEC_ERR_TOO_LARGE, "k = %d exceeds the %d heads bound", k, c->n_draft_heads);
   if (c->last_T <= 0) return fail(c, SPECDEC_ERR_BAD_STATE, "specdec_draft_heads needs the hidden states of a specdec_verify "
                                   "(call it after specdec_verify, before specdec_commit)");
+  if (!c->fin_x) return fail(c, SPECDEC_ERR_BAD_STATE, "the latest verification pass (SPECDEC_OPT_RESIDENT) kept no hidden states");
   Model& m = c->m[SPECDEC_VERIFIER];
   hipStream_t st = S(stream);
   const int B = c->B, D = m.d.d_model, F = m.d.d_ffn, nh = c->n_draft_heads, R = B * k;

@@ -11,6 +11,7 @@ import cases
 import gpu_harness as gh
 from paper_2203_16487_amd import binding as sd
 from paper_2203_16487_amd import synth
+import specdec_oracle as orc
 
 pytestmark = pytest.mark.gpu
 
@@ -227,3 +228,38 @@ def test_pass_in_flight_when_its_context_ends():
         assert resident_launches(second, lambda: gh.gpu_verify(second, case))[0] == 1
         other.synchronize()
     second.close()
+
+
+@pytest.mark.parametrize("B,k", [(2, 5), (7, 10)])     # last sums left un-normalised (at most 32 rows) and not
+def test_head_drafts_after_it(B, k):
+    """The hidden states the kernel leaves to specdec_draft_heads, also where its waits were given up; SPECDEC_OPT_RESIDENT keeps
+    refusing them after passes of at most 32 rows."""
+    case = cases.make_verify_case(desc(512), seed=70 + B, B=B, S=30, k=k, beta=3, tau=1.0, len_lo=3, len_hi=20, drafts="greedy", ragged_src=True)
+    cases.run_oracle(case)
+    hb = synth.make_head_weights(case.desc, 3, 70, std=0.02)
+    heads = [synth.weights_f32(h) for h in hb]
+    ses = gh.open_verifier(case, fill=0xFF)
+    stacked = ses.upload_weights({n: np.concatenate([h[n] for h in hb]) for n in ("w1", "b1", "w2", "b2")})   # (used in place)
+    sd.specdec_bind_draft_heads(ses.ctx, 3, *stacked)
+    z = torch.zeros((B, 3, case.desc.vocab), dtype=torch.float32, device=ses.device)
+    drafts = ses.i32(np.zeros((B, 3)))
+    for give_up in (0, 1):
+        sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_GIVE_UP_WAITS, give_up)
+        n, out = resident_launches(ses, lambda: gh.gpu_verify(ses, case))
+        assert n == 1
+        check(case, out)
+        sd.specdec_draft_heads(ses.ctx, out["accept_t"], 3, drafts, z)
+        torch.cuda.synchronize()
+        for b in range(B):
+            hidden = orc.verify_onepass(case.model, case.states[b], int(case.tokens[b, case.lens[b]]), list(case.drafts[b]), return_hidden=True)[1]
+            want = orc.head_draft(case.model, heads, hidden[int(out["accept"][b])], return_logits=True)[1]
+            assert float(np.abs(z[b].cpu().numpy() - want).max()) <= max(2e-2, 0.04 * float(want.std())), (give_up, b)
+    sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_RESIDENT, 1)
+    gh.gpu_verify(ses, case)
+    if B * (k + 1) <= 32:
+        with pytest.raises(sd.SpecDecError) as e:
+            sd.specdec_draft_heads(ses.ctx, out["accept_t"], 3, drafts)
+        assert e.value.code == sd.SPECDEC_ERR_BAD_STATE
+    else:
+        sd.specdec_draft_heads(ses.ctx, out["accept_t"], 3, drafts)
+    ses.close()
