@@ -297,10 +297,11 @@ __device__ __forceinline__ void ln_row_stats(const f32x4 (&p)[NL], int j, int d,
   }
 }
 
-template <class Cfg>
+// PAIRS: most chunks of a row.
+template <class Cfg, int PAIRS>
 struct LnRows {
   static constexpr int TPR = Cfg::kThreads / Cfg::kBM;   // threads that share one tile row
-  static constexpr int NL = 32 / TPR;                    // 16-byte loads per thread (d <= 2048)
+  static constexpr int NL = PAIRS / 2 / TPR;             // 16-byte loads per thread
   static_assert(TPR == 2 || TPR == 4, "threads per row");
   f32x4 p[NL];                                           // pairs 2q, 2q+1 for q = j + i * TPR
   // Loads sit behind conditions on kernel arguments only (no lane takes a branch of its own).
@@ -521,7 +522,11 @@ struct EpiLnQkvAppend {
 template <class Cfg, int VEC>
 constexpr int ln_smem_bytes() { return Cfg::kSmemBytes + (2 * Cfg::kBM + VEC * Cfg::kBN) * 4; }
 
-template <class Cfg, class Epi>
+// PAIRS: 32 chunks of 64 columns are the most there can be (d <= 2048); with 32 columns, for d > 1024, up to 64.  They are held in
+// registers through the main loop, so the kernel that has room for 64 is for those rows only: with room for 64 everywhere the
+// residual sums of 7168 x 1024 x 1024 and x 4096 on 128 x 128 tiles ran one block a CU instead of two and took 69 us on average,
+// now 47.5; 1408 x 4096 x 1024 on 256 x 128 tiles 20.1, now 19.7.
+template <class Cfg, class Epi, int PAIRS>
 __global__ __launch_bounds__(Cfg::kThreads) void gemm_ln_kernel(const bf16* __restrict__ A, int lda,
                                                                 const bf16* __restrict__ W, int ldw,
                                                                 int M, int N, int K, int MT, int NT,
@@ -546,7 +551,7 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ln_kernel(const bf16* __re
   const int tr = threadIdx.x / CPR, tc = (threadIdx.x % CPR) * 8;
   const int n = n0 + tc;
   // everything the epilogue reads is requested here and arrives under the K loop
-  LnRows<Cfg> rows;
+  LnRows<Cfg, PAIRS> rows;
   rows.request(epi.ln_in, epi.chunks, m0, M);
   constexpr int QPV = Cfg::kBN / 4;   // 16-byte pieces per column vector of the tile
   const bool vec_thread = threadIdx.x < Epi::kVec * QPV;
@@ -581,15 +586,18 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ln_kernel(const bf16* __re
   }
 }
 
-template <class Cfg, class Epi>
+template <class Cfg, int PAIRS = 32, class Epi>
 static hipError_t launch_ln_cfg(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K,
                                 const Epi& epi, const int* m_real) {
+  if constexpr (PAIRS < 64) {
+    if (epi.chunks > PAIRS) return launch_ln_cfg<Cfg, 64>(st, A, lda, W, M, N, K, epi, m_real);
+  }
   constexpr int kBytes = ln_smem_bytes<Cfg, Epi::kVec>();
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ln_kernel<Cfg, Epi>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ln_kernel<Cfg, Epi, PAIRS>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
   if (attr != hipSuccess) return attr;
   const int MT = (M + Cfg::kBM - 1) / Cfg::kBM, NT = (N + Cfg::kBN - 1) / Cfg::kBN;
-  SD_LAUNCH_TIMED((gemm_ln_kernel<Cfg, Epi>), dim3(xcd_grid(MT, NT)), dim3(Cfg::kThreads), kBytes, st,
+  SD_LAUNCH_TIMED((gemm_ln_kernel<Cfg, Epi, PAIRS>), dim3(xcd_grid(MT, NT)), dim3(Cfg::kThreads), kBytes, st,
                      A, lda, W, K, M, N, K, MT, NT, epi, m_real);
   return hipGetLastError();
 }
@@ -626,7 +634,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16*
   gemm_mainloop<Cfg, true>(A, lda, W, ldw, M, N, 0, K / Cfg::GK, m0, n0, smem, acc, [&] {
     constexpr int QPV = BN / 4;   // 16-byte pieces per column vector of the tile
     const int t = threadIdx.x;
-    LnRows<Cfg> rows;
+    LnRows<Cfg, 64> rows;
     rows.request(epi.ln_in, epi.chunks, m0, M);
     if (t < Epi::kVec * QPV)
       *reinterpret_cast<f32x4*>(colv + t * 4) = *reinterpret_cast<const f32x4*>(epi.vec(t / QPV) + min(n0 + (t % QPV) * 4, N - 4));
