@@ -256,8 +256,16 @@ template <int V>
 __device__ __forceinline__ void load_cols(const float* p, float (&o)[V]) { __builtin_memcpy(o, __builtin_assume_aligned(p, V == 2 ? 8 : 16), V * 4); }
 template <int V>
 __device__ __forceinline__ void store_cols(float* p, const float (&v)[V]) { __builtin_memcpy(__builtin_assume_aligned(p, V == 2 ? 8 : 16), v, V * 4); }
+// (As a vector from the start: a copy of the array may be stored in pieces, as it was in the QKV projection, in 8, 4 and 2 bytes:
+// 1408 x 3072 x 1024 on 256 x 128 tiles 21.8 us, now 20.6.)
 template <int V>
-__device__ __forceinline__ void store_cols(bf16* p, const bf16 (&v)[V]) { __builtin_memcpy(__builtin_assume_aligned(p, V * 2), v, V * 2); }
+__device__ __forceinline__ void store_cols(bf16* p, const bf16 (&v)[V]) {
+  typedef bf16 vec __attribute__((ext_vector_type(V)));
+  vec t;
+#pragma unroll
+  for (int i = 0; i < V; ++i) t[i] = v[i];
+  *reinterpret_cast<vec*>(p) = t;
+}
 
 // Chunk pairs of a row lie together, [M][pitch] pairs with pitch = chunks rounded up to even, so a thread fetches two
 // pairs per 16-byte load.  A chunk is 64 columns, or 32 where the kernel that formed the sums has tiles of 32 columns
