@@ -198,7 +198,8 @@ bool desc_ok(const specdec_model_desc* d) {
 }
 constexpr long kPrefillRows = 8192;
 // Most rows of a pass the one-kernel decoder is asked for: with more, launches cost less than what its workgroups, that see
-// 32 rows each, read more (d = 512: 253 rows 226 against 258 us, 286 281 / 282; d = 1024: 121 rows 294 / 315, 176 371 / 365).
+// 32 rows each, read more (whole passes; d = 512: 253 rows 227 against 272 us, level at 286; d = 1024: 121 rows 304 / 338, level at
+// 176).
 constexpr size_t persist_rows(int d) { return d <= 512 ? 256 : 128; }
 constexpr int kEncT = 12, kDecT = 20;
 int n_weights(const specdec_model_desc* d) { return 1 + kEncT * d->enc_layers + kDecT * d->dec_layers; }
@@ -1068,7 +1069,7 @@ int specdec_prefill(specdec_ctx* c, specdec_role role, void* stream) {
   hipStream_t st = S(stream);
   // As few passes as the activation buffers allow, all of the same size: a pass of a few rows per sequence is a chain of
   // small launches that reads every weight again (32 sequences of up to 224 tokens, big model: 11 passes of 21 positions
-  // 6.9 ms, TIMEms in one).  Rows are packed: short streams bring no padding.
+  // 7.4 ms, 1.8 ms in one).  Rows are packed: short streams bring no padding.
   const bool packed = !c->no_ln_fold;
   const int most = (int)(c->pass_rows / c->B), passes = (c->uncached_ub[role] + most - 1) / most;
   const int T = passes > 0 ? (c->uncached_ub[role] + passes - 1) / passes : 0;

@@ -24,7 +24,7 @@ __device__ __forceinline__ bool xcd_tile(int MT, int NT, int& mt, int& nt) {
 }
 // The same for many row tiles: groups of 8 row tiles, inside a group n-major, so that what runs together on an XCD shares
 // both a few weight panels and a few row panels (one long n-major run streams all rows past each weight panel: 32768 x 3072
-// x 1024 on 128 x 128 tiles 331 us, grouped 278).
+// x 1024 on 128 x 128 tiles 276 us, grouped 247; on 256 x 256 231, grouped 212).
 __device__ __forceinline__ bool xcd_tile_grouped(int MT, int NT, int& mt, int& nt) {
   constexpr int G = 8;
   const int nb = MT * NT, id = blockIdx.x;
@@ -701,8 +701,9 @@ static hipError_t launch_tile(hipStream_t st, const bf16* A, int lda, const bf16
 
 // 256 x 256 tiles or 128 x 128 ones?  Time of a full round of blocks (256 and 512) as measured over K = 512 .. 4096, us:
 // 10.5 + 1.73 and 3.6 + 1.12 per 64 columns of K; a last round costs nearly a full one on one block per CU, and on two the
-// better part of one as soon as some CU has a second block.  Where M only bounds the rows in use (bound), the sum over half,
-// three quarters and all of it decides.
+// better part of one as soon as some CU has a second block.  (Sums of K = 512 take twice as long on both.)  Of twelve row counts from
+// 352 to 32768 and nine (N, K) of the two models, the choice was at most 3 % slower than the better of the two wherever it is
+// made.  Where M only bounds the rows in use (bound), the sum over half, three quarters and all of it decides.
 static float square_minus_wide(int M, int N, int K) {
   const float kt = K / 64.f;
   const long sq = (long)((M + 255) / 256) * ((N + 255) / 256), wd = (long)((M + 127) / 128) * ((N + 127) / 128);
@@ -723,7 +724,7 @@ static bool square_tiles(int M, int N, int K, bool bound) {
 // leave as whole rows of a head.  A block of 8 keys of the values is 1 KB of memory: a wave turns 8 tile rows x 64 columns
 // with two transposing reads and stores it at once, wherever in the tile the sequence's blocks begin (single values, as
 // before, only for blocks cut by the tile's edge).
-// 32768 rows, d = 1024: 288 us a layer with values stored one by one, 144 us.
+// 32768 rows, d = 1024: 288 us a layer with values stored one by one; six layers now 815 us, 136 a layer.
 template <class Cfg>
 __global__ __launch_bounds__(Cfg::kThreads, 2) void cross_kv_kernel(const bf16* __restrict__ A, CrossKvArgs a, int M, int d,
                                                                     int NT, const int* __restrict__ m_real) {
@@ -1014,28 +1015,35 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeig
   }
   const bf16* W = static_cast<const bf16*>(w.p);
   // K split inside the block wherever its tiles give every CU at most one block (a second round costs more than it
-  // saves): the smallest tile that does.  Chained launches, 64 x 64 ring -> K split, us: N = K = 512, M = 77: 5.6 -> 3.3;
-  // N = 1024, M = 128: K = 1024 7.7 -> 3.9, K = 4096 19.0 -> 7.2; M = 352: K = 1024 8.0 -> 5.4, K = 4096 19.6 -> 11.0;
-  // N = 4096, K = 1024, M = 128: 7.4 -> 5.6.
+  // saves): the smallest tile that does.  Launches back to back, 64 x 64 ring -> K split, us: sums of N = K = 512, M = 77: 5.6 ->
+  // 5.2; N = 1024, M = 128: K = 1024 7.0 -> 5.2, K = 4096 15.9 -> 7.2; M = 352: K = 1024 7.3 -> 5.9, K = 4096 16.2 -> 11.2;
+  // output N = 4096, K = 1024, M = 128: 6.7 -> 5.9.
   if (one_round(M, N, 16, 32)) return launch_ksplit<KsplitCfg<16, 32, 8, 3>>(st, A, lda, W, M, N, K, epi, m_real);
   if (one_round(M, N, 32, 32)) return launch_ksplit<KsplitCfg<32, 32, 8, 2>>(st, A, lda, W, M, N, K, epi, m_real);
   if (one_round(M, N, 32, 64)) return launch_ksplit<KsplitCfg<32, 64, 8, 1>>(st, A, lda, W, M, N, K, epi, m_real);
   if (one_round(M, N, 48, 64)) return launch_ksplit<KsplitCfg<48, 64, 4, 2>>(st, A, lda, W, M, N, K, epi, m_real);
-  // a long K pays for a larger tile (FFN2 of the big model at 1408 rows: 28.4 -> 23.7 us); at K <= 2048 the ring is level
-  // or better, and so it is where M is only a bound on the rows in use
+  // a long K pays for a larger tile (FFN2 of the big model at 1408 rows: 64 x 64 ring 28.0 us, 24.2; but at 1024 rows, where the ring's
+  // tiles are one to a CU, 19.2 and 22.9); at K <= 2048 the ring is level or better, and so it is where M is only a bound on
+  // the rows in use
   if constexpr (Epi::kVec == 3) {
     if (K >= 4096 && !m_real && one_round(M, N, 96, 64)) return launch_ksplit<KsplitCfg<96, 64, 3, 2>>(st, A, lda, W, M, N, K, epi, m_real);
   }
   const long wide_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
-  if (wide_tiles >= 512) {   // two blocks of 128 x 128 for every CU, or larger tiles still
+  // Two blocks of 128 x 128 for every CU, or larger tiles still.  (Below that the register epilogue would be the faster one for outputs,
+  // 7168 x 1024 x 1024 21.2 us against 24.8, and for long sums, x 4096 71.6 / 78.9; not for sums of d = 512, 9216 x 512 x 2048 38.9
+  // / 35.7.)
+  if (wide_tiles >= 512) {
     if (square_tiles(M, N, K, m_real != nullptr)) return launch_tile<CfgSquare>(st, A, lda, W, M, N, K, epi, m_real);
     return launch_tile<CfgWide>(st, A, lda, W, M, N, K, epi, m_real);
   }
-  // the widest outputs (QKV and FFN1 of the big model) run on 256x128 tiles, eight waves, three-deep
-  // ring: 9-15 % faster than 128x128 on weights streamed from HBM, a few % inside the decoder pass
+  // the widest outputs (QKV and FFN1 of the big model) run on 256 x 128 tiles, eight waves, three-deep ring.  K = 1024, us on 256 x 128 /
+  // 128 x 128 / 64 x 64 tiles: 1408 rows x 3072 16.3 / 18.0 / 19.9, x 4096 18.0 / 19.4 / 22.7; 2048 rows 18.8 / 20.0 / 26.9 and 21.7 /
+  // 22.9 / 34.1; at the line, 1024 rows, 15.5 / 15.3 / 13.5 and 16.1 / 15.6 / 16.3.
   if constexpr (Epi::kVec == 2) {
     if (N >= 3072 && M >= 1024) return launch_ln_cfg<CfgTall>(st, A, lda, W, M, N, K, epi, m_real);
   }
+  // (K = 512: up to some 2000 rows the small tiles, whose fixed costs are smaller: 1408 x 2048 x 512 9.7 us against 10.1; beyond, the wide
+  // ones would be faster, 2816 rows 15.3 / 13.4, but most rows are a bound there: the drafter's 2688 hold some 1500)
   if (wide_tiles >= 200 && K > 512) return launch_ln_cfg<CfgWide>(st, A, lda, W, M, N, K, epi, m_real);
   return launch_ln_cfg<CfgSmall>(st, A, lda, W, M, N, K, epi, m_real);
 }
@@ -1412,7 +1420,9 @@ hipError_t vocab_stats(hipStream_t st, const bf16* A, const bf16* E, int M, int 
   const bool stats = row_draft || logits;
   const int MT = (M + 127) / 128, NT = (V + 127) / 128;
   // 256 x 256 tiles once they give every CU two or more (the batched passes); their product is formed with
-  // the operand roles swapped, and the draft logits follow suit
+  // the operand roles swapped, and the draft logits follow suit.  V = 32768, d = 1024, a launch on 128 x 128 / 256 x 256 tiles: 132 rows
+  // (128 of the larger tiles) 25.6 / 32.3 us, 352 (256) 44.8 / 34.7, 704 (384) 68.6 / 62.9, 1023 (512) - / 68.6: one tile per CU
+  // would already do
   const int MT256 = (M + 255) / 256, NT256 = (V + 255) / 256;
   const bool big = force_wide || (long)MT256 * NT256 >= 512;
   // without row_draft no row scores a draft (drafter pass): every count is taken against -inf, unused

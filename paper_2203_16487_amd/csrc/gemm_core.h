@@ -130,8 +130,9 @@ __device__ __forceinline__ void gemm_mainloop(const bf16* __restrict__ A, int ld
   // One request moves 64 lanes x 16 B = RPL tile rows; lane l lands at row l/CPR, physical chunk
   // l%CPR, so it fetches the logical chunk that the swizzle maps there.  A lane keeps its byte offsets from the tile's first
   // row; what moves on with the stages is wave-uniform (scalar registers), and so is the place in LDS: per request one scalar
-  // move and the load itself (with full addresses per lane and LDS pointers made uniform at every request, ten instructions
-  // more: 3072 x 4096 x 4096 on 256 x 256 tiles 105.7 us, now 96.3; 1024 x 4096 x 4096 on 128 x 128, four-deep ring 47.8, now 35.2).
+  // move and the load itself.  With full addresses per lane and LDS pointers made uniform at every request, ten instructions
+  // more, launches of the encoder and the batch-128 loop took, us: 32768 x 4096 x 1024 on 256 x 256 tiles 276.9, now 266.8; 9216 x
+  // 3072 x 1024 on 128 x 128 77.2, now 73.0; 1408 x 4096 x 1024 on 256 x 128 21.0, now 20.2; 64 x 64 tiles 0 - 3 % more.
   unsigned voff[IPW];
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {

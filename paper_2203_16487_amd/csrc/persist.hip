@@ -16,11 +16,11 @@
 // tiles are summed through LDS in wave order, and the waves divide the 16 x 16 results.  LayerNorm is folded into the products as
 // in the general kernels (gemm.hip), with statistics per 16 columns.
 //
-// What bounds it: the chain of 7 hand-overs a layer.  A whole verify pass, separate kernels -> this one: d = 512, 6 layers, 11 rows 196 -> 124 us; 77 rows 241 -> 161; d = 1024, 26 rows of E4M3 weights
-// 303 -> 224.  Beyond 128 rows (d = 1024: 64), items of 32 rows: 176 rows of d = 512 251 -> 221, 121 of d = 1024 315 -> 294.
-// Larger ones were tried (48 x 64, 352 rows) and are level with separate kernels: every item fetches its rows and weights at the
-// 60 - 75 GB/s one CU takes in, whether the rows come through the L2 (counters instead of kPoison) or not, and whether or not
-// the next weights are requested ahead.
+// What bounds it: the chain of 7 hand-overs a layer.  A whole verify pass of 6 layers, separate launches -> this kernel: d = 512, 6 rows
+// 199 -> 125 us, 77 243 -> 166; d = 1024, 6 rows 250 -> 171, 26 312 -> 218, with E4M3 weights 303 -> 224.  Beyond 128 rows
+// (d = 1024: 64), items of 32 rows: 176 rows of d = 512 265 -> 219, 121 of d = 1024 338 -> 304.  Larger ones were tried (48 x 64,
+// 352 rows) and are level with separate launches: every item fetches its rows and weights at the 60 - 75 GB/s one CU takes in,
+// whether the rows come through the L2 (counters instead of kPoison) or not, and whether or not the next weights are requested ahead.
 //
 // The workgroups wait for each other, so all of them have to be running.  There are no more of them than the stream has CUs and
 // the host lets one such pass at a time onto a GPU, but a kernel of another stream or process may hold some of the CUs.  Waits
