@@ -70,11 +70,14 @@ enum { SPECDEC_COUNTERS = 8 };  /* int32 words reported by specdec_get_counters 
 
 /* Kernel-path switches of a context (specdec_configure), value 0 or 1. */
 typedef enum {
-  SPECDEC_OPT_SMALL_BATCH_KERNELS = 0, /* default 1: passes of at most 32 rows use the small-batch kernels: the fused decoder
-                                          kernels where they are the faster ones (one sequence of at most 12 rows,
-                                          d_model <= 512), else the general ones; the small-batch vocabulary kernel   */
+  SPECDEC_OPT_SMALL_BATCH_KERNELS = 0, /* default 1: passes of few rows run their decoder layers as one kernel where that applies
+                                          (specdec_verify); else, of at most 32 rows, one sequence of at most 12 rows with
+                                          d_model <= 512 (and every such pass with LN_FOLD = 0) on the fused small-batch
+                                          kernels, others on the general ones; at most 32 rows: the small-batch
+                                          vocabulary kernel.  0: none of these                                       */
   SPECDEC_OPT_LN_FOLD = 1,             /* default 1: LayerNorms folded into the projections around them; 0: a pass of their own
-                                          between them, encoder (from the next specdec_encode) and decoder        */
+                                          between them, encoder (from the next specdec_encode) and decoder (which then
+                                          does not run as one kernel)                                              */
   SPECDEC_OPT_RESIDENT = 2,            /* default 0.  It once selected a kernel of its own for passes of at most 32 rows;
                                           the one-kernel decoder (specdec_verify) that took its place runs wherever it
                                           applies, whether this is set or not.  1 chooses no kernel: it keeps the
@@ -188,8 +191,8 @@ int specdec_set_prefix(specdec_ctx* ctx, specdec_role role, const int32_t* token
                        int32_t L_max, const void* k_cache, const void* v_cache, void* stream);
 
 /* Cache the keys/values of every stream token a model has not cached yet (u_0..u_{j-1} for
- * the verifier, u_0..u_j for the drafter) with causal decoder passes of up to k_max+1 rows
- * per sequence.  Needed after specdec_set_stream unless a cache is loaded. */
+ * the verifier, u_0..u_j for the drafter) with causal decoder passes, as few as the workspace's
+ * activation buffers allow.  Needed after specdec_set_stream unless a cache is loaded. */
 int specdec_prefill(specdec_ctx* ctx, specdec_role role, void* stream);
 
 /* ---- the hot path -------------------------------------------------------------------- */
@@ -313,9 +316,9 @@ int specdec_quantize_rows(specdec_ctx* ctx, const void* w, int64_t N, int64_t K,
 
 /* ---- timing of one kernel kind ----------------------------------------------------------- */
 /* While a kind is selected every launch of that kernel is timed by a pair of HIP events on the launch
- * stream (up to 4096 launches between two reads; later ones are not recorded): for the GEMM, attention and
- * vocabulary kernels of passes of more than 32 rows the pair holds the kernel's own begin and end, for the
- * other kernels the moments the stream reaches a marker before and after the launch (the hand-over from the
+ * stream (up to 4096 launches between two reads; later ones are not recorded): for the GEMM and attention
+ * kernels, the vocabulary kernels of passes of more than 32 rows and the one-kernel decoder the pair holds the kernel's own
+ * begin and end, for the other kernels the moments the stream reaches a marker before and after the launch (the hand-over from the
  * launch before is then inside).
  * specdec_profile_read waits for the recorded events (it synchronises on them), returns their
  * summed duration in milliseconds and their number, and clears the record. */
@@ -329,7 +332,8 @@ typedef enum {
   SPECDEC_KIND_LN = 5,
   SPECDEC_KIND_ACCEPT = 6,
   SPECDEC_KIND_OTHER = 7,
-  SPECDEC_KIND_RESIDENT = 8,   /* whole decoder pass + vocabulary tiles of a small batch, one kernel */
+  SPECDEC_KIND_RESIDENT = 8,   /* the decoder layers of a pass of few rows, one kernel (a pass is one launch of this
+                                  kind; the kernel that completes a pass given up is not counted)  */
   SPECDEC_KIND_COUNT = 9
 } specdec_kernel_kind;
 int specdec_profile_select(specdec_ctx* ctx, int32_t kind);

@@ -228,7 +228,7 @@ def test_autoregressive_baseline_k0():
     """k = 0: verification degenerates to one plain autoregressive step per call (Sec. 2, the
     baseline SpecDec is measured against).  The oracle follows in lock step with dec_step; the
     whole output must equal the oracle's greedy decoding unless a near-tie was excused.  B = 40
-    takes the general kernels, B = 5 the fused small-batch ones."""
+    takes the 128 x 128 vocabulary tiles, B = 5 the small-batch ones."""
     compared = 0
     for B in (5, 40):
         (vd, vb, vm), _ = make_models(seed=31)

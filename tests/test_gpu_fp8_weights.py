@@ -47,8 +47,9 @@ def test_quantiser_matches_the_oracle_bit_for_bit():
     ses.close()
 
 
+@pytest.mark.parametrize("fold", [1, 0])   # 0: the fused small-batch kernels
 @pytest.mark.parametrize("shape", ["toy", "base_b1", "base_b3", "big_b1"])
-def test_fp8_small_batch_pass_matches_the_quantised_oracle(shape):
+def test_fp8_small_batch_pass_matches_the_quantised_oracle(shape, fold):
     if shape == "toy":
         desc = synth.ModelDesc(0, 2, 128, 2, 256, 1000, 16, 64).resolved()
         args = dict(seed=81, B=5, S=9, k=4, len_lo=0, len_hi=14, std=0.08)
@@ -63,7 +64,7 @@ def test_fp8_small_batch_pass_matches_the_quantised_oracle(shape):
         args = dict(seed=84, B=1, S=20, k=30, len_lo=11, len_hi=11, std=0.02)
     case = cases.make_verify_case(desc, beta=3, tau=1.0, drafts="greedy", ragged_src=True, fp8=True, **args)
     cases.run_oracle(case)
-    ses = gh.open_verifier(case, options=FP8)
+    ses = gh.open_verifier(case, options={**FP8, sd.SPECDEC_OPT_LN_FOLD: fold})
     out = gh.gpu_verify(ses, case)
     L = case.L_max + case.k + 1
     Kg, Vg = gh.gpu_cache(ses, case, L)
@@ -137,8 +138,8 @@ def test_fp8_cross_kv_matches_the_quantised_oracle(shape):
     """Cross keys / values stored as E4M3 with one scale per (key, head) vector, against the oracle whose
     state holds the same stored values.  The library converts from its bf16 arenas, the oracle from
     unrounded values: a code may differ by one step where bf16 rounding crosses an E4M3 boundary, which
-    stays far inside the logit tolerance.  Cases: the fused small-batch kernels, the general kernels
-    (40 rows), a source longer than 256 (4-way key split), the base verifier, both FP8 options at once,
+    stays far inside the logit tolerance.  Every case with LayerNorm folded (few rows: the general kernels or, at d = 512,
+    the one-kernel decoder) and not (few rows: the fused small-batch kernels).  Cases: few rows, 40 rows, a source longer than 256 (4-way key split), the base verifier, both FP8 options at once,
     and buffers filled with 0xFF (dead keys then carry NaN codes AND NaN scales)."""
     toy = synth.ModelDesc(0, 2, 128, 2, 256, 1000, 16, 64).resolved()
     opts, fill, fp8w = dict(KV8), 0, False
@@ -161,15 +162,16 @@ def test_fp8_cross_kv_matches_the_quantised_oracle(shape):
         desc, args, fill = toy, dict(seed=96, B=5, S=9, k=4, len_lo=0, len_hi=14, std=0.08), 0xFF
     case = cases.make_verify_case(desc, beta=3, tau=1.0, drafts="greedy", ragged_src=True, fp8=fp8w, fp8_kv=True, **args)
     cases.run_oracle(case)
-    ses = gh.open_verifier(case, options=opts, fill=fill)
-    out = gh.gpu_verify(ses, case)
-    ses.close()
-    assert np.isfinite(out["logits"]).all()
-    err = float(np.abs(out["logits"] - case.logits).max())
-    zstd = float(case.logits.std())
-    print(f"[fp8 cross-kv {shape}] logit std {zstd:.3f}, max-abs err vs the quantised oracle {err:.3e}")
-    assert err <= max(LOGIT_TOL, REL_TOL * zstd)
-    assert not cases.compare_decisions(case, out["accept"], out["next"])[2]
+    for fold in (1, 0):
+        ses = gh.open_verifier(case, options={**opts, sd.SPECDEC_OPT_LN_FOLD: fold}, fill=fill)
+        out = gh.gpu_verify(ses, case)
+        ses.close()
+        assert np.isfinite(out["logits"]).all()
+        err = float(np.abs(out["logits"] - case.logits).max())
+        zstd = float(case.logits.std())
+        print(f"[fp8 cross-kv {shape} fold {fold}] logit std {zstd:.3f}, max-abs err vs the quantised oracle {err:.3e}")
+        assert err <= max(LOGIT_TOL, REL_TOL * zstd)
+        assert not cases.compare_decisions(case, out["accept"], out["next"])[2]
 
 
 def test_fp8_cross_kv_format_error_is_reported():

@@ -379,9 +379,9 @@ def test_large_drafter_shape_24_plus_6():
 
 def test_random_small_shapes_against_oracle_and_across_paths():
     """Sixteen seeded random small cases (batch 1-8, block size 1-15, prefixes 0-40, ragged sources, a
-    pass of at most 32 rows): the fused small-batch kernels and the general kernels both against the
-    oracle, and against each other (same tolerance: different kernels, same arithmetic up to
-    rounding order)."""
+    pass of at most 32 rows): the default kernels, the fused small-batch kernels (which take every such pass where
+    LayerNorm is not folded) and the general kernels, against the oracle, and against each other (same
+    tolerance: different kernels, same arithmetic up to rounding order)."""
     desc = synth.ModelDesc(0, 2, 128, 2, 256, 1000, 24, 64).resolved()
     rng = np.random.default_rng(2024)
     worst = 0.0
@@ -395,7 +395,8 @@ def test_random_small_shapes_against_oracle_and_across_paths():
         cases.run_oracle(case)
         tol = max(LOGIT_TOL, REL_TOL * float(case.logits.std()))
         outs = {}
-        for name, opt in (("fused", None), ("general", {sd.SPECDEC_OPT_SMALL_BATCH_KERNELS: 0})):
+        for name, opt in (("default", None), ("fused", {sd.SPECDEC_OPT_LN_FOLD: 0}),
+                          ("general", {sd.SPECDEC_OPT_SMALL_BATCH_KERNELS: 0})):
             ses = gh.open_verifier(case, options=opt)
             outs[name] = gh.gpu_verify(ses, case)
             ses.close()
@@ -403,8 +404,9 @@ def test_random_small_shapes_against_oracle_and_across_paths():
             worst = max(worst, err)
             assert err <= tol, (case_no, name, B, k, hi, S, err)
             assert not cases.compare_decisions(case, outs[name]["accept"], outs[name]["next"])[2], (case_no, name, B, k)
-        assert np.abs(outs["fused"]["logits"] - outs["general"]["logits"]).max() <= tol, (case_no, B, k)
-    print(f"[random shapes] 16 cases x 2 paths, worst max-abs logit err {worst:.3e}")
+        for name in ("default", "fused"):
+            assert np.abs(outs[name]["logits"] - outs["general"]["logits"]).max() <= tol, (case_no, name, B, k)
+    print(f"[random shapes] 16 cases x 3 paths, worst max-abs logit err {worst:.3e}")
 
 
 def test_wide_vocabulary_tiles_on_small_shapes():
@@ -487,8 +489,8 @@ def test_kernel_kind_timing_counts_and_leaves_results_alone():
     """specdec_profile_select / specdec_profile_read: the number of timed launches per kind is the number the
     pass makes (3 residual-sum projections, 2 attentions, 1 QKV projection per layer, one vocabulary kernel),
     every duration is positive and small, for the kernels timed by their own begin / end (general kernels) and
-    for those bracketed on the stream (small-batch kernels), and timing changes no result."""
-    for B, k in ((40, 4), (5, 4)):                      # general kernels / fused small-batch kernels
+    for the one bracketed on the stream (small-batch vocabulary kernel), and timing changes no result."""
+    for B, k in ((40, 4), (5, 4)):                      # general kernels / the same with the small-batch vocabulary kernel
         case = small_case(seed=61, B=B, k=k)
         ses = gh.open_verifier(case)
         ref = gh.gpu_verify(ses, case)
@@ -500,7 +502,7 @@ def test_kernel_kind_timing_counts_and_leaves_results_alone():
             ms, n = sd.specdec_profile_read(ses.ctx)
             if B * (k + 1) > 32:
                 assert n == per_pass, (B, kind, n, per_pass)
-            elif kind in (0, 4):                         # the fused kernels: attention runs inside kind 0
+            elif kind in (0, 4):
                 assert n >= 1, (B, kind, n)
             assert n == 0 or 0.0 < ms < 5.0 * n, (B, kind, ms, n)
             assert np.array_equal(out["logits"], ref["logits"]) and np.array_equal(out["accept"], ref["accept"])

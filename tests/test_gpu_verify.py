@@ -251,10 +251,10 @@ def test_argument_errors_on_device():
 def test_small_batch_paths_agree():
     """The implementations of a pass of at most 32 rows -- general kernels with LayerNorm folded
     into the GEMMs around it (what larger batches run), general kernels with LayerNorm as a
-    pass of its own, fused per-projection kernels (the default at this size), kernels that own
-    sub-layers by head / FFN slice (opt-in) and the single resident kernel (opt-in) -- all match the oracle,
-    every one gives the same bits when run twice, and the per-projection and resident paths give
-    the same logits to the last bit; the cases cover d = 128, d = 512 with two 16-row tiles (B = 2,
+    pass of its own, fused per-projection kernels (with LayerNorm not folded, and one sequence of few rows
+    at d <= 512), kernels that own sub-layers by head / FFN slice (opt-in) and the one-kernel decoder (the default
+    at the paper's dimensions) -- all match the oracle, every one gives the same bits when run twice, and
+    SPECDEC_OPT_RESIDENT changes none; the cases cover d = 128, d = 512 with two 16-row tiles (B = 2,
     k = 10) and d = 1024 with one and two tiles."""
     import gpu_harness as gh
     case = cases.make_verify_case(small_desc(), seed=21, B=3, S=9, k=4, beta=3, tau=1.0, len_lo=0, len_hi=12,
@@ -264,7 +264,7 @@ def test_small_batch_paths_agree():
     case2 = cases.make_verify_case(desc2, seed=22, B=2, S=24, k=10, beta=3, tau=1.0, len_lo=3, len_hi=20,
                                    drafts="greedy", ragged_src=True)
     cases.run_oracle(case2)
-    # big verifier (d = 1024, F = 4096: two output slices per resident workgroup, long FFN2 k range)
+    # big verifier (d = 1024, F = 4096: long FFN2 k range)
     desc3 = synth.big_verifier(max_src=48, max_tgt=64, enc_layers=0)
     case3 = cases.make_verify_case(desc3, seed=23, B=2, S=40, k=10, beta=3, tau=1.0, len_lo=5, len_hi=30,
                                    drafts="greedy", ragged_src=True)
@@ -275,11 +275,14 @@ def test_small_batch_paths_agree():
         outs = {}
         for tag, opts in (("general", {sd.SPECDEC_OPT_SMALL_BATCH_KERNELS: 0}),
                           ("general, separate LayerNorm", {sd.SPECDEC_OPT_SMALL_BATCH_KERNELS: 0, sd.SPECDEC_OPT_LN_FOLD: 0}),
+                          ("per projection", {sd.SPECDEC_OPT_LN_FOLD: 0}),
                           ("fused", {}), ("sliced", {sd.SPECDEC_OPT_SLICED_SUBLAYERS: 1}),
                           ("resident", {sd.SPECDEC_OPT_RESIDENT: 1})):
             ses = gh.open_verifier(cs, options=opts)
             outs[tag] = gh.gpu_verify(ses, cs)
+            sd.specdec_profile_select(ses.ctx, sd.KIND["resident"])
             again = gh.gpu_verify(ses, cs)          # every path gives the same bits when run twice
+            assert sd.specdec_profile_read(ses.ctx)[1] == (1 if tag in ("fused", "resident") and cs is not case else 0), tag
             assert np.array_equal(outs[tag]["logits"], again["logits"]), tag
             ses.close()
             err = np.abs(outs[tag]["logits"] - cs.logits).max()

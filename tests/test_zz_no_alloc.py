@@ -32,7 +32,7 @@ def run_both(ses, case, drafts, k):
 
 def test_verify_static_matches_verify():
     desc = synth.ModelDesc(0, 2, 128, 2, 256, 1000, 16, 64).resolved()
-    # general kernels (B * (k + 1) = 264 rows), then a smaller pass on the fused small-batch kernels
+    # general kernels (B * (k + 1) = 264 rows), then a smaller pass with the small-batch vocabulary kernel
     big = cases.make_verify_case(desc, seed=71, B=24, S=12, k=10, beta=3, tau=1.0, len_lo=0, len_hi=30,
                                  drafts="greedy", ragged_src=True, std=0.08)
     small = cases.make_verify_case(desc, seed=72, B=3, S=9, k=4, beta=2, tau=0.5, len_lo=1, len_hi=12,
