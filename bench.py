@@ -45,7 +45,7 @@ SEED = 0
 # reads 0.5 per KiB copied, WRITE_SIZE 1.0.  Summary and commands: profiles/hbm_traffic.md.
 # Offline measurements, not taken in this run.
 MEASURED_TRAFFIC_BYTES = {
-    "gemm_f32": {"fetch": 1.9998 * 26694.0 * 1024, "write": 1.0 * 8465.9 * 1024},
+    "gemm_f32": {"fetch": 1.9998 * 25336.8 * 1024, "write": 1.0 * 8427.9 * 1024},
 }
 
 
