@@ -237,8 +237,8 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * run their decoder layers as one kernel of up to 256 workgroups that wait for each other; where a
  * kernel of another stream or process keeps some of them from starting for 0.1 s or more, the waits
  * are given up and a second kernel, which needs no more than one free compute unit, computes
- * the pass instead (same bits, 0.5 - 3 ms); the run's later passes then go to that kernel
- * directly, until the next specdec_begin.  One stream of one process at a time runs such passes on a
+ * the pass instead (same bits, 0.5 - 3 ms); so it does the run's next 63 passes without
+ * waiting first.  One stream of one process at a time runs such passes on a
  * GPU: that of the first context to ask, until it and the others on its stream are destroyed (a
  * context that captures one: until it is destroyed, whatever the stream).  A context on another
  * stream or in another process runs its passes as separate launches, from the first pass refused to its

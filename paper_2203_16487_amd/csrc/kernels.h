@@ -250,10 +250,10 @@ struct PlArgs {
   size_t kv_layer, xkv_layer;
   int fp8;                                // the layers' weights are codes
   char* exch;                             // persist_exch_bytes, every byte 0xff when the kernel starts
-  unsigned* err;                          // [2] flags, zero at first and kept from pass to pass: waits of the pass were given
-                                          // up (and it is finished another way), those of that way too (results are void)
+  unsigned* err;                          // [2] flags, zero at first and kept from pass to pass: waits were given up (passes yet to
+                                          // be computed another way), those of that way too (results are void)
   int RP, d, mr, fbw, att0, wpu, NB;      // filled by the launcher, as what follows
-  const unsigned* raised;
+  unsigned* raised;
   unsigned poll_mask, spin_max;
   struct PlTickets* tickets;
 };

@@ -28,7 +28,7 @@
 // and the same stages are run again by the kernel launched behind this one (TICKETS), which returns at once where the flag is
 // not raised.  Its workgroups draw (stage, virtual workgroup) tickets in the order of the stages and wait only for
 // stages whose tickets have all been drawn, that is for workgroups that are running: it needs no more than one CU.  It computes
-// the same bits.  The flag stays raised until specdec_begin: later passes of that run do not wait in vain again.
+// the same bits.  The flag counts the passes that go to it directly (kPlTicketPasses, this one included) before one waits again.
 // A whole verify pass with the second launch returning at once and without it: 125.3 / 124.8 us (d = 512, 6 rows), 168.4 / 166.3
 // (77 rows), 380.2 / 378.0 (d = 1024, 128 rows); by tickets 0.51, 1.13 and 2.7 ms.
 #include "attn_core.h"
@@ -39,6 +39,7 @@ constexpr unsigned kPoison = 0xffffffffu;
 constexpr unsigned kPlSpinMax = 1u << 17;   // (0.1 - 0.2 s)
 constexpr unsigned kPlTicketSpinMax = 1u << 24;
 constexpr int kPlTicketBlocks = 64;
+constexpr unsigned kPlTicketPasses = 64;    // (a wait in vain then costs 2 - 3 ms a pass)
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
@@ -69,7 +70,7 @@ __device__ __forceinline__ bool pl_again(unsigned& spins, const PlArgs& a) {
   if ((spins & a.poll_mask) == 0) {
     const bool raised = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
     if (raised || spins > a.spin_max) {
-      __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(a.err, kPlTicketPasses, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return false;
     }
   }
@@ -784,7 +785,10 @@ __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decod
       if (threadIdx.x == 0) drawn = (int)(__hip_atomic_fetch_add(&a.tickets->drawn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u);
       __syncthreads();
       const int t = __builtin_amdgcn_readfirstlane(drawn), st = t / NB, l = st / kPlStages;
-      if (t >= total) return;
+      if (t >= total) {   // (the last workgroup to find none left: every one has read the flag, and nothing else writes it now)
+        if (t == total + (int)gridDim.x - 1 && threadIdx.x == 0) *a.raised -= 1;
+        return;
+      }
       w = t - st * NB;
       // everything before this stage: its tickets are out, so whoever holds them is running
       unsigned spins = 0;

@@ -108,7 +108,7 @@ def test_two_contexts_and_replays():
 ])
 def test_waits_given_up(d, B, k, S, lo, hi, opts):
     """Waits of the kernel given up at once (it ends, half of its results missing): the kernel behind it computes the pass,
-    to the last bit as the waiting one; so do the passes after it, which find the flag raised, until a new run begins."""
+    to the last bit as the waiting one; so do the next 63, which find the flag raised; then one waits again."""
     case = cases.make_verify_case(desc(d), seed=d + B, B=B, S=S, k=k, beta=3, tau=1.0, len_lo=lo, len_hi=hi, drafts="random",
                                   ragged_src=True, fp8=sd.SPECDEC_OPT_FP8_WEIGHTS in opts, fp8_kv=sd.SPECDEC_OPT_FP8_CROSS_KV in opts)
     cases.run_oracle(case)
@@ -127,7 +127,11 @@ def test_waits_given_up(d, B, k, S, lo, hi, opts):
         for x, y in zip(gh.gpu_cache(ses, case, L), cache):
             for b, j in enumerate(case.lens):
                 assert np.array_equal(x[:, b, :j + k + 1], y[:, b, :j + k + 1])
-    print(f"one-kernel decoder {times[0]:.3f} ms, given up {times[1]:.3f} ms, flag raised {times[2]:.3f} ms")
+    for _ in range(65):
+        got = gh.gpu_verify(ses, case, want_logits=False)
+        assert np.array_equal(got["stats"], want["stats"])
+    times.append(sd.specdec_profile_read(ses.ctx)[0] / 65)
+    print(f"one-kernel decoder {times[0]:.3f} ms, given up {times[1]:.3f} ms, flag raised {times[2]:.3f} ms, mean of the next 65 {times[3]:.3f} ms")
     ses.close()
 
 
