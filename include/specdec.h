@@ -244,8 +244,8 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * stream or in another process runs its passes as separate launches, from the first pass refused to its
  * next specdec_begin.  So does a stream with fewer compute units than the pass has workgroups.  The
  * two ways add in different orders: their logits differ in the last bits.  Processes in different
- * network name spaces (containers) do not see each other: their passes may meet, and are then completed
- * as above.
+ * network name spaces (containers) do not see each other, nor is a pass seen that a destroyed context
+ * has left in flight: such passes may meet, and are then completed as above.
  * logits_or_null: optional device fp32 [B, k+1, V] receiving every row's logits (parity
  * mode; slow).  Does not change any length: calling it twice, on the same stream and within one run
  * (not captured in between), gives the same result. */

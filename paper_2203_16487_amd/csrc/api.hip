@@ -557,13 +557,13 @@ int decoder_layers_sliced(specdec_ctx* c, Model& m, int B, int T, hipStream_t st
 // one stream take turns there; the first to ask names the stream, and while it lives, a pass of another context on another
 // stream takes the kernel-per-stage path.  A captured pass may be replayed on any stream, so a context that captures one
 // is alone with its GPU until it is destroyed (or, where it is not alone, captures the kernel-per-stage path).  Among processes
-// the user is the one that holds the lock named after the GPU's PCI address.
+// the user is the one that holds the lock named after the GPU's PCI address.  (`stream` is compared, never used: it may be gone.  So a
+// pass of a destroyed context that is still in flight is not seen, and one of the next context on another stream may meet it.)
 constexpr int kMaxDevices = 64;
 struct PersistGpu {
   hipStream_t stream = nullptr;
   int users = 0;             // contexts
   bool captured = false;     // by the only one
-  bool draining = false;     // the last user is gone, a pass of its may still run on `stream`
   sd::ProcessLock lock;
 };
 PersistGpu persist_gpu[kMaxDevices];
@@ -575,26 +575,12 @@ bool persist_open(PersistGpu& o, int dev) {
   snprintf(name, sizeof name, "specdec-%s", bus);
   return o.lock.take(name);
 }
-// Nothing of the users before is left on their stream.  (Not asked during a capture on this stream, and so that one on another
-// thread's does not end by it.)
-bool persist_free(PersistGpu& o, hipStream_t st, bool capturing) {
-  if (o.draining && o.stream != st) {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (capturing || hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
-    const bool busy = hipStreamQuery(o.stream) == hipErrorNotReady;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (busy) return false;
-  }
-  o.draining = false;
-  return true;
-}
 void persist_release(specdec_ctx* c) {
   if (c->persist_dev < 0) return;
   std::lock_guard<std::mutex> guard(persist_mutex);
   PersistGpu& o = persist_gpu[c->persist_dev];
   if (--o.users) return;
   o.captured = false;
-  o.draining = true;
   o.lock.drop();
 }
 
@@ -602,6 +588,7 @@ void persist_release(specdec_ctx* c) {
 // the process (one that the HIP runtime does not report is taken for none at all).
 int stream_cus(hipStream_t st) {
   uint32_t mask[32] = {};
+  if (st == hipStreamPerThread || st == hipStreamLegacy) st = nullptr;   // (names of default streams, not streams)
   if (getenv("HSA_CU_MASK") || hipExtStreamGetCUMask(st, 32, mask) != hipSuccess) return 0;
   int n = 0;
   for (uint32_t word : mask) n += __builtin_popcount(word);
@@ -621,7 +608,7 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
     return false;
   if (c->persist_refused || (c->persist_dev >= 0 && c->persist_dev != dev)) return false;
   bool capturing = false;
-  if (st) {
+  if (st && st != hipStreamLegacy) {   // (which cannot be captured)
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &status) != hipSuccess) return false;
     capturing = status != hipStreamCaptureStatusNone;
@@ -631,7 +618,7 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
   const bool user = c->persist_dev == dev;
   // (for the whole run: the two ways add in different orders, and which one a pass takes is not to change with the life of others)
   c->persist_refused = (o.users > (user ? 1 : 0) && (o.captured || capturing || st != o.stream || st == hipStreamPerThread)) ||
-                       (!o.users && !persist_free(o, st, capturing)) || (!o.users && !persist_open(o, dev));
+                       (!o.users && !persist_open(o, dev));
   if (c->persist_refused) return false;
   if (!user) {
     ++o.users;

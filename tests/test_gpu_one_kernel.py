@@ -207,7 +207,8 @@ def test_way_of_a_run_does_not_change(B, k):
 
 
 def test_pass_in_flight_when_its_context_ends():
-    """A context destroyed before its latest pass has run: a context on another stream does not start one beside it."""
+    """A context destroyed before its latest pass has run, and a pass of another context on another stream that may meet it:
+    whichever way the two are completed, both are right."""
     case = cases.make_verify_case(desc(512), seed=60, B=7, S=30, k=10, beta=3, tau=1.0, len_lo=3, len_hi=20, drafts="greedy", ragged_src=True)
     cases.run_oracle(case)
     first, second = gh.open_verifier(case, fill=0xFF), gh.open_verifier(case, fill=0xFF)
@@ -222,15 +223,10 @@ def test_pass_in_flight_when_its_context_ends():
     sd.specdec_destroy(first.ctx)                      # (what it points to stays)
     first.ctx = None
     with torch.cuda.stream(other):
-        n, out = resident_launches(second, lambda: gh.gpu_verify(second, case))   # (waits for both)
+        out = gh.gpu_verify(second, case)              # (waits for both)
     torch.cuda.synchronize()
-    assert n == 0
     check(case, out)
     assert acc.cpu().tolist() == out["accept"].tolist()
-    restart(second, case)
-    with torch.cuda.stream(other):
-        assert resident_launches(second, lambda: gh.gpu_verify(second, case))[0] == 1
-        other.synchronize()
     second.close()
 
 
@@ -266,4 +262,21 @@ def test_head_drafts_after_it(B, k):
         assert e.value.code == sd.SPECDEC_ERR_BAD_STATE
     else:
         sd.specdec_draft_heads(ses.ctx, out["accept_t"], 3, drafts)
+    ses.close()
+
+
+@pytest.mark.parametrize("name", [1, 2])               # hipStreamLegacy, hipStreamPerThread
+def test_default_streams_by_name(name):
+    case = cases.make_verify_case(desc(512), seed=80, B=2, S=30, k=5, beta=3, tau=1.0, len_lo=3, len_hi=20, drafts="greedy", ragged_src=True)
+    cases.run_oracle(case)
+    ses = gh.open_verifier(case, fill=0xFF)
+    out = gh.gpu_verify(ses, case)
+    check(case, out)
+    d, acc, nxt = ses.i32(case.drafts), ses.i32(np.zeros(2)), ses.i32(np.zeros(2))
+    z = torch.zeros((2, 6, case.desc.vocab), dtype=torch.float32, device=ses.device)
+    torch.cuda.synchronize()
+    rc = sd.lib().specdec_verify(ses.ctx, d.data_ptr(), case.k, case.beta, C.c_float(case.tau), acc.data_ptr(), nxt.data_ptr(), z.data_ptr(), name)
+    torch.cuda.synchronize()
+    assert rc == sd.SPECDEC_OK
+    assert np.array_equal(z.cpu().numpy(), out["logits"]) and acc.cpu().tolist() == out["accept"].tolist()
     ses.close()
