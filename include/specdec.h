@@ -115,8 +115,9 @@ typedef enum {
                                           (the batched passes), else 128 x 128 tiles.  1: 256 x 256 tiles in every
                                           such pass (so that the wide kernel can be checked on small shapes).     */
   SPECDEC_OPT_GIVE_UP_WAITS = 7        /* default 0.  1: every wait of the one-kernel decoder that does not end at once is
-                                          given up, and the pass completed by the kernel behind it (specdec_verify),
-                                          so that this way of completing a pass can be checked.                   */
+                                          given up (in groups: taken as given up), and the pass completed by the kernel
+                                          behind it (specdec_verify), so that this way of completing a pass can be
+                                          checked.                                                                */
 } specdec_option;
 
 /* ---- life cycle -------------------------------------------------------------------- */
@@ -233,11 +234,12 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * Finished sequences report accept_len 0 and next_token pad_id.
  * k = 0 (draft may be null) is one plain autoregressive step: accept_len = 0 and next_token is
  * the verifier's greedy token (the baseline of Sec. 2 on the same kernels).
- * Passes of few rows (at most 256 with d_model 512 / d_ffn 2048, 128 with 1024 / 4096, 32 layers)
- * run their decoder layers as one kernel of up to 256 workgroups that wait for each other; where a
+ * Passes of few rows (d_model 512 / d_ffn 2048 or 1024 / 4096, 32 layers; at most 512 rows, and at most
+ * 64 to each of eight groups that the sequences are dealt to evenly; of those beyond 63 (1024: 128) rows every XCD
+ * takes one group) run their decoder layers as one kernel of up to 256 workgroups that wait for each other; where a
  * kernel of another stream or process keeps some of them from starting for 0.1 s or more, the waits
  * are given up and a second kernel, which needs no more than one free compute unit, computes
- * the pass instead (same bits, 0.5 - 3 ms); so it does the run's next 63 passes without
+ * the pass instead (same bits, 0.5 - 3 ms; in groups 7 - 14); so it does the run's next 63 (15) passes without
  * waiting first.  One stream of one process at a time runs such passes on a
  * GPU: that of the first context to ask, until it and the others on its stream are destroyed (a
  * context that captures one: until it is destroyed, whatever the stream).  A context on another

@@ -74,9 +74,11 @@ struct Model {
   float* hx = nullptr;       // [Bmax*k_max][d] head-based drafting: the hidden state each head adds to, then its output
   bool skinny_ready = false;
   sd::PlLayer* pl_layers = nullptr;   // device copy of the decoder layers' pointers (one-kernel decoder, persist.hip)
-  int* pl_err = nullptr;              // its two flags (PlArgs::err)
-  char* pl_exch = nullptr;            // its exchange buffers (null: dimensions it does not support)
-  int pl_rows = 0;                    // rows they are sized for
+  int* pl_err = nullptr;              // its flags (PlArgs::err, XcdArgs::err)
+  char* pl_exch = nullptr;            // exchange buffers, its or the per-XCD one's (xcd.hip); null: dimensions they do not support
+  int pl_rows = 0;                    // rows they are sized for, its
+  char* xcd_stream = nullptr;         // the layers' weights as the per-XCD decoder streams them
+  float* xcd_vecs = nullptr;          // and their column vectors
   bf16* xb = nullptr;        // [Rpass][d]
   float* lnp[2] = {nullptr, nullptr};   // [rows][d/32 at most][2] chunk pairs of the two latest residual sums
   float* fold = nullptr;     // per decoder layer: cs and bf vectors of wqkv, cwq, w1 (LayerNorm folded)
@@ -197,10 +199,12 @@ bool desc_ok(const specdec_model_desc* d) {
          d->mask_id >= 0 && d->mask_id < d->vocab;
 }
 constexpr long kPrefillRows = 8192;
-// Most rows of a pass the one-kernel decoder is asked for: with more, launches cost less than what its workgroups, that see
-// 32 rows each, read more (whole passes; d = 512: 253 rows 227 against 272 us, level at 286; d = 1024: 121 rows 304 / 338, level at
-// 176).
-constexpr size_t persist_rows(int d) { return d <= 512 ? 256 : 128; }
+// Most rows of a pass the one-kernel decoder over the whole GPU is asked for: beyond, its workgroups read more than the per-XCD one's
+// do.  Whole passes, launches / whole GPU / per XCD, us: d = 512: 6 rows 234 / 136 / 144, 48 rows 246 / 147 / 155, 64 (one a sequence)
+// 256 / 186 / 175, 77 251 / 167 / 154, 176 271 / 217 / 185, 352 315 / - / 212, 480 327 / - / 255; d = 1024 (whose weights every XCD
+// reads: 176 MB): 6 rows 266 / 177 / 253, 77 341 / 289 / 305, 96 354 / 306 / 314, 128 407 / 374 / 392, 176 391 / - / 345, 352
+// 497 / - / 409, 480 539 / - / 482.
+constexpr size_t persist_rows(int d) { return d <= 512 ? 63 : 128; }
 constexpr int kEncT = 12, kDecT = 20;
 int n_weights(const specdec_model_desc* d) { return 1 + kEncT * d->enc_layers + kDecT * d->dec_layers; }
 
@@ -277,7 +281,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   t.x = cv.take<float>(Rpass * D);
   t.x2 = cv.take<float>(32 * D);
   t.skp = cv.take<float>((size_t)2 * sd::kSk2MaxParts * 32 * D);   // (or the one-kernel decoder's sum and its residual)
-  static_assert(2 * persist_rows(512) <= 2 * sd::kSk2MaxParts * 32, "both fit");
+  static_assert(2 * persist_rows(512) <= 2 * sd::kSk2MaxParts * 32 && 2 * sd::kXcdMostRows <= 2 * sd::kSk2MaxParts * 32, "both fit");
   t.hx = cv.take<float>(Bm * (size_t)c->lim.k_max * D);
   if (c->fp8_kv) {
     t.xk8 = cv.take<unsigned char>(t.xkv_layer * d->dec_layers);
@@ -315,7 +319,10 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     const size_t most = Bm * (c->lim.k_max + 1);
     t.pl_rows = (int)(most < persist_rows((int)D) ? most : persist_rows((int)D));
     // (in a drafter's workspace too, which never uses it: the size is asked for without a role)
-    t.pl_exch = cv.take<char>(sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F));
+    const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F), xcd = sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F);
+    t.pl_exch = cv.take<char>(one > xcd ? one : xcd);
+    t.xcd_stream = cv.take<char>(sd::xcd_stream_bytes(d->dec_layers, (int)D, (int)F));
+    t.xcd_vecs = cv.take<float>(sd::xcd_vec_bytes(d->dec_layers, (int)D) / sizeof(float));
   }
   if (d->enc_layers > 0) {
     const size_t Re = Bm * (size_t)c->Scap;
@@ -340,6 +347,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     m->part = t.part; m->row_stats = t.row_stats; m->zd = t.zd; m->rm = t.rm;
     m->slots = t.slots; m->new_rows = t.new_rows; m->pl_err = t.pl_err;
     m->pl_layers = t.pl_layers; m->pl_exch = t.pl_exch; m->pl_rows = t.pl_rows;
+    m->xcd_stream = t.xcd_stream; m->xcd_vecs = t.xcd_vecs;
     m->ex = t.ex; m->exb = t.exb; m->eqkv = t.eqkv; m->eatt = t.eatt; m->ehid = t.ehid;
     m->elnp[0] = t.elnp[0]; m->elnp[1] = t.elnp[1]; m->efold = t.efold; m->epos = t.epos; m->erow_b = t.erow_b; m->erow_start = t.erow_start; m->en_rows = t.en_rows;
   }
@@ -595,14 +603,29 @@ int stream_cus(hipStream_t st) {
   return n;
 }
 
+// How the decoder layers of a verify pass run: launches a stage; as one kernel over the whole GPU (persist.hip); as one kernel, each XCD
+// on sequences of its own (xcd.hip).
+enum class Way { launches, gpu, xcd };
+
+Way one_kernel_way(const specdec_ctx* c, const Model& m, int B, int T) {
+  sd::PlArgs p{};
+  p.R = B * T; p.T = T; p.B = B; p.H = m.d.n_heads;
+  sd::XcdArgs x{};
+  x.R = B * T; x.T = T; x.B = B; x.H = m.d.n_heads;
+  const int D = m.d.d_model, F = m.d.d_ffn, R = B * T;
+  const bool gpu = R <= m.pl_rows && sd::persist_plan(p, D, F) > 0, xcd = R <= sd::kXcdMostRows && !(m.fp8 && R <= 32) && sd::xcd_plan(x, D, F) > 0;
+  return gpu ? Way::gpu : xcd ? Way::xcd : Way::launches;
+}
+
 bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
-  const int R = B * T;
-  if (!m.pl_exch || R > m.pl_rows || T > 32 || c->no_skinny || c->no_ln_fold || c->sliced) return false;
+  if (!m.pl_exch || T > 32 || c->no_skinny || c->no_ln_fold || c->sliced) return false;
+  const Way way = one_kernel_way(c, m, B, T);
+  if (way == Way::launches) return false;
   sd::PlArgs a{};
-  a.R = R; a.T = T; a.B = B; a.H = m.d.n_heads;
-  const int blocks = sd::persist_plan(a, m.d.d_model, m.d.d_ffn);
+  a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads;
+  const int blocks = way == Way::xcd ? sd::kPlBlocks : sd::persist_plan(a, m.d.d_model, m.d.d_ffn);   // all of them running at once
   int dev = -1, cus = 0;
-  if (blocks < 1 || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices ||
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < blocks ||
       stream_cus(st) < blocks)
     return false;
@@ -629,8 +652,29 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
   return true;
 }
 
+// Bytes of the exchange buffers that the pass's first kernel fills with 0xff.
+size_t persist_clear(const specdec_ctx* c, const Model& m, int B, int T) {
+  if (one_kernel_way(c, m, B, T) == Way::gpu) return sd::persist_exch_bytes(B * T, m.d.dec_layers, m.d.d_model, m.d.d_ffn);
+  sd::XcdArgs a{};
+  a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads;
+  return sd::xcd_plan(a, m.d.d_model, m.d.d_ffn);
+}
+
 // few: as in decoder_layers (the E4M3 copies of the weights, if the model has them)
 int decoder_layers_persist(specdec_ctx* c, Model& m, int B, int T, bool few, hipStream_t st) {
+  if (one_kernel_way(c, m, B, T) == Way::xcd) {
+    sd::XcdArgs a{};
+    a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads; a.Lcap = c->Lcap; a.Scap = c->Scap; a.n_layers = m.d.dec_layers;
+    a.stream = m.xcd_stream; a.vecs = m.xcd_vecs;
+    a.row_b = m.rm.row_b; a.row_pos = m.rm.row_pos; a.src_len = c->st.src_len;
+    a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + (size_t)sd::kXcdMostRows * m.d.d_model;
+    a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
+    if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
+    a.exch = m.pl_exch; a.err = reinterpret_cast<unsigned*>(m.pl_err);
+    if (c->give_up) HIPCHK(c, sd::fill_i32(st, m.pl_err, (int)sd::kXcdAlonePasses, 1));
+    LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::xcd_decoder(st, a, m.d.d_model, m.d.d_ffn));
+    return SPECDEC_OK;
+  }
   sd::PlArgs a{};
   a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads; a.Lcap = c->Lcap; a.Scap = c->Scap; a.n_layers = m.d.dec_layers;
   a.fp8 = few && m.fp8;
@@ -878,7 +922,7 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
     if (rcq != SPECDEC_OK) return fail(c, rcq, "FP8 weight quantisation failed: %s", hipGetErrorString(hipGetLastError()));
   }
   {
-    HIPCHK(c, sd::fill_i32(S(stream), m.pl_err, 0, 2));
+    HIPCHK(c, sd::fill_i32(S(stream), m.pl_err, 0, 3));
     // for the one-kernel decoder: the bf16 matrices, then (FP8 weights) their codes
     std::vector<sd::PlLayer> pl;
     for (int set = 0; set < (m.fp8 ? 2 : 1); ++set)
@@ -891,6 +935,7 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
                                  f.cq.bf, f.w1.cs, f.w1.bf, f.vo, f.vco, f.v2});
       }
     HIPCHK(c, hipMemcpy(m.pl_layers, pl.data(), pl.size() * sizeof(sd::PlLayer), hipMemcpyHostToDevice));
+    if (m.pl_exch) HIPCHK(c, sd::xcd_pack(S(stream), m.pl_layers, d->dec_layers, d->d_model, m.xcd_stream, m.xcd_vecs));
   }
   m.bound = true;
   return SPECDEC_OK;
@@ -905,7 +950,7 @@ int specdec_begin(specdec_ctx* c, int32_t B, int32_t max_new, void* stream) {
   const Model& any = c->m[0].bound ? c->m[0] : c->m[1];
   if (max_new > c->lim.max_tgt) max_new = c->lim.max_tgt;   // no stream grows beyond the arena
   HIPCHK(c, sd::begin_state(S(stream), c->st, B, max_new, c->lim.max_tgt, any.d.bos_id));
-  if (c->m[0].bound) HIPCHK(c, sd::fill_i32(S(stream), c->m[0].pl_err, 0, 2));   // a new run clears the one-kernel decoder's flags
+  if (c->m[0].bound) HIPCHK(c, sd::fill_i32(S(stream), c->m[0].pl_err, 0, 3));   // a new run clears the one-kernel decoder's flags
   c->B = B;
   c->max_new = max_new;
   c->last_T = 0;
@@ -1162,7 +1207,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   else
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_verify(st, c->st, m.rm, draft, B, k, m.d.vocab, m.embed, m.pe, m.x, m.xb,
                                         m.d.d_model, one ? m.pl_exch : nullptr,
-                                        one ? sd::persist_exch_bytes(R, m.d.dec_layers, m.d.d_model, m.d.d_ffn) : 0));
+                                        one ? persist_clear(c, m, B, T) : 0));
   const unsigned* failed = one ? reinterpret_cast<const unsigned*>(m.pl_err) + 1 : nullptr;
   float* sums = one ? m.skp : m.x;   // the last residual sums (the one-kernel decoder keeps its input rows)
   int n_tiles = (m.d.vocab + 63) / 64;   // per-row partial records of the vocabulary kernel that ran

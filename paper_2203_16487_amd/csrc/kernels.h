@@ -263,6 +263,37 @@ size_t persist_exch_bytes(int rows, int layers, int d, int F);
 int persist_plan(PlArgs& a, int d, int F);   // workgroups of a pass of a.R rows, a.B sequences, a.H heads (0: too many rows)
 // give_up: every wait that does not end at once is given up
 hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F, bool give_up);
+// ---- xcd.hip: the same for more rows, each XCD on sequences of its own ----
+struct XcdArgs {
+  int R, T, B, H, Lcap, Scap, n_layers;   // as PlArgs
+  const char* stream;                     // weights and column vectors as xcd_pack lays them out
+  const float* vecs;
+  const int *row_b, *row_pos, *src_len;
+  const float* x;
+  const bf16* xb;
+  float* y;
+  float* resid;                           // [kXcdMostRows][d], scratch
+  bf16 *kc, *vc;
+  const void *xk, *xv;
+  const float *xk_scale, *xv_scale;
+  size_t kv_layer, xkv_layer;
+  char* exch;                             // xcd_plan bytes of it 0xff when the kernel starts
+  unsigned* err;                          // [3], zero at first and kept from pass to pass: waits were given up (passes yet to
+                                          // be computed another way); those of that way too (results are void); a counter
+  int RP, d, G, wpu;                      // filled by the launcher, as what follows
+  unsigned *raised, *ended;
+};
+constexpr int kXcdMostRows = 512;         // rows of a pass at most: 64 on each of 8 XCDs
+constexpr unsigned kXcdAlonePasses = 16;  // that are computed without waits (7 - 14 ms each) after waits were given up
+// Weights (bf16) of a model's layers (device array) in the order they are used, and their column vectors.
+size_t xcd_stream_bytes(int layers, int d, int F);
+size_t xcd_vec_bytes(int layers, int d);
+hipError_t xcd_pack(hipStream_t st, const PlLayer* layers, int n, int d, char* stream, float* vecs);
+// bytes of exch for passes of up to max_batch sequences of up to max_T rows
+size_t xcd_exch_most(int max_batch, int max_T, int d, int F);
+// bytes of exch that a pass of a.B sequences of a.T rows uses (0: too many rows)
+size_t xcd_plan(XcdArgs& a, int d, int F);
+hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F);
 // ---- skinny2.hip: the same passes with sub-layers owned by head / by FFN slice (three kernels per layer) ----
 bool sk2_supported(int d, int F);
 int sk2_ffn_slices(int F);             // partial results the FFN kernel leaves (at most 16)

@@ -17,9 +17,9 @@
 // in the general kernels (gemm.hip), with statistics per 16 columns.
 //
 // What bounds it: the chain of 7 hand-overs a layer.  A whole verify pass of 6 layers, separate launches -> this kernel: d = 512, 6 rows
-// 199 -> 125 us, 77 243 -> 166; d = 1024, 6 rows 250 -> 171, 26 312 -> 218, with E4M3 weights 303 -> 224.  Beyond 128 rows
-// (d = 1024: 64), items of 32 rows: 176 rows of d = 512 265 -> 219, 121 of d = 1024 338 -> 304.  Larger ones were tried (48 x 64,
-// 352 rows) and are level with separate launches: every item fetches its rows and weights at the 60 - 75 GB/s one CU takes in,
+// 199 -> 125 us, 48 246 -> 147; d = 1024, 6 rows 250 -> 171, 26 312 -> 218, with E4M3 weights 303 -> 224.  Beyond 64 rows
+// of d = 1024, items of 32 rows: 121 rows 338 -> 304.  More rows (from 64 of d = 512, 129 of d = 1024 on) are the per-XCD decoder's
+// (xcd.hip).  Larger items were tried (48 x 64, 352 rows) and are level with separate launches: every item fetches its rows and weights at the 60 - 75 GB/s one CU takes in,
 // whether the rows come through the L2 (counters instead of kPoison) or not, and whether or not the next weights are requested ahead.
 //
 // The workgroups wait for each other, so all of them have to be running.  There are no more of them than the stream has CUs and
@@ -29,8 +29,8 @@
 // not raised.  Its workgroups draw (stage, virtual workgroup) tickets in the order of the stages and wait only for
 // stages whose tickets have all been drawn, that is for workgroups that are running: it needs no more than one CU.  It computes
 // the same bits.  The flag counts the passes that go to it directly (kPlTicketPasses, this one included) before one waits again.
-// A whole verify pass with the second launch returning at once and without it: 125.3 / 124.8 us (d = 512, 6 rows), 168.4 / 166.3
-// (77 rows), 380.2 / 378.0 (d = 1024, 128 rows); by tickets 0.51, 1.13 and 2.7 ms.
+// A whole verify pass with the second launch returning at once and without it: 125.3 / 124.8 us (d = 512, 6 rows),
+// 380.2 / 378.0 (d = 1024, 128 rows); by tickets 0.51 and 2.7 ms.
 #include "attn_core.h"
 
 namespace sd {
@@ -850,7 +850,7 @@ static hipError_t pl_launch(hipStream_t st, const PlArgs& a, int blocks) {
 template <class WT, bool KV8, int NW>
 static hipError_t pl_launch_items(hipStream_t st, const PlArgs& a) {
   if (a.mr == 1) return a.fbw == 2 ? pl_launch<WT, KV8, NW, 4, 16, 1, 2, false>(st, a, a.NB) : pl_launch<WT, KV8, NW, 4, 16, 1, 4, false>(st, a, a.NB);
-  if constexpr (sizeof(WT) == 1) return hipErrorInvalidValue;   // codes: passes of a few rows only
+  if constexpr (sizeof(WT) == 1 || NW == 4) return hipErrorInvalidValue;   // codes, d = 512: passes of fewer rows only
   else return pl_launch<WT, KV8, NW, 4, 16, 2, 4, false>(st, a, a.NB);
 }
 // the pass, and its second run by tickets (kPlTicketBlocks workgroups: a fraction of the chip, so that it costs little to start)

@@ -42,6 +42,12 @@ def check(case, out):
     (1024, 64, 1, 40, 50, 70, {}),           # 128 rows, the most; two waves per unit
     (1024, 11, 10, 150, 100, 130, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
     (1024, 24, 4, 200, 60, 140, {}),         # four waves per unit, several chunks of keys each
+    (512, 32, 10, 64, 0, 64, {}),            # 44 rows an XCD: three row tiles
+    (512, 37, 11, 70, 0, 130, {}),           # 60 and 48 rows an XCD: four row tiles
+    (1024, 9, 10, 300, 0, 140, {}),          # two sequences on one XCD, one on the others
+    (1024, 16, 31, 40, 0, 90, {}),           # 512 rows, the most
+    (1024, 17, 20, 45, 30, 90, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),   # 63 rows, two query tiles a sequence
+    (512, 128, 1, 60, 0, 60, {}),            # two rows a sequence, two waves a unit of attention
     (512, 3, 9, 50, 0, 40, {sd.SPECDEC_OPT_FP8_WEIGHTS: 1}),
     (512, 3, 9, 50, 0, 40, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
     (1024, 1, 30, 33, 9, 9, {sd.SPECDEC_OPT_FP8_WEIGHTS: 1, sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
