@@ -372,9 +372,10 @@ inline void cross_fp8(const Model& m, int l, sd::AttnArgs& a) {
 // only the bound the grids are sized for, and tiles beyond the rows in use return at once.
 // kv_only (prefill): the pass is wanted for the keys / values it appends; it ends where the last layer's are stored.
 // few (verify passes of at most 32 rows, LayerNorm folded): the projections stream the E4M3 copies if the model has them, and
-// the last sum stays un-normalised in m.x (the small-batch vocabulary kernel normalises it itself).
+// the last sum stays un-normalised in m.x (the small-batch vocabulary kernel normalises it itself); so it does with leave_sum (and
+// LayerNorm folded), for vocab_stats.
 int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool embedded = false, int slot_k = 0,
-                   bool packed = false, bool kv_only = false, bool few = false) {
+                   bool packed = false, bool kv_only = false, bool few = false, bool leave_sum = false) {
   const int R = B * T, D = m.d.d_model, F = m.d.d_ffn, H = m.d.n_heads;
   const int Lcap = c->Lcap, Scap = c->Scap;
   const int* m_real = packed ? m.rm.row_start + B : nullptr;
@@ -433,7 +434,7 @@ int decoder_layers(specdec_ctx* c, Model& m, int B, int T, hipStream_t st, bool 
       LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.att, D, W.cwo, fd.vco));
       LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_ln_bf16(st, m.xb, W.w1, R, F, D, fd.w1, pend, m.hid, F, true, m_real));
       LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.hid, F, W.w2, fd.v2));
-      if (l + 1 == m.d.dec_layers && !few) {   // the vocabulary projection reads the normalised rows themselves
+      if (l + 1 == m.d.dec_layers && !few && !leave_sum) {   // the vocabulary projection reads the normalised rows themselves
         if (slot_k > 0)
           LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm_slots(st, m.x, L.ln3g, L.ln3b, m.slots, m.new_rows, row_start, B, T, slot_k, D));
         else
@@ -1229,14 +1230,15 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     if (one) {
       rc = decoder_layers_persist(c, m, B, T, false, st);
       if (rc) return rc;
-      LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, sums, m.dec.back().ln3g, m.dec.back().ln3b, m.xb, R, m.d.d_model));
     } else {
-      rc = decoder_layers(c, m, B, T, st, true);
+      rc = decoder_layers(c, m, B, T, st, true, 0, false, false, false, true);
       if (rc) return rc;
     }
+    const sd::VocabLn ln{sums, m.dec.back().ln3g, m.dec.back().ln3b, m.xb};
     c->fin_x = sums; c->fin_g = nullptr; c->fin_b = nullptr;   // normalised in place by the last LayerNorm
     n_tiles = (m.d.vocab + sd::vocab_tile_cols(R) - 1) / sd::vocab_tile_cols(R);
-    LAUNCH(c, SPECDEC_KIND_VOCAB, st, sd::vocab_stats(st, m.xb, m.embed, R, m.d.vocab, m.d.d_model, m.rm.row_draft, vs.zd, vs.part, logits, c->wide_vocab));
+    LAUNCH(c, SPECDEC_KIND_VOCAB, st, sd::vocab_stats(st, m.xb, m.embed, R, m.d.vocab, m.d.d_model, m.rm.row_draft, vs.zd, vs.part, logits, c->wide_vocab,
+                                                             c->no_ln_fold ? nullptr : &ln));
   }
   LAUNCH(c, SPECDEC_KIND_ACCEPT, st, sd::merge_accept(st, vs.part, vs.zd, n_tiles, vs.row_stats, c->st, B, k, beta, tau, m.d.pad_id,
                                       accept_len, next_token, failed));

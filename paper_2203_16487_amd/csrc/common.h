@@ -107,6 +107,28 @@ __device__ __forceinline__ float fast_rsqrt(float x) {
   return r * __builtin_fmaf(-0.5f * x * r, r, 1.5f);
 }
 
+// LayerNorm of one row of 64 * PER values by one wave: y[i] = column 64 i + lane.  All loads are issued before the first use.
+template <int PER>
+__device__ __forceinline__ void ln_row(const float* __restrict__ xr, const bf16* __restrict__ g, const bf16* __restrict__ bta, int lane,
+                                       float (&y)[PER]) {
+  constexpr int d = 64 * PER;
+  float gg[PER], bb[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) y[i] = xr[i * 64 + lane];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) { gg[i] = (float)g[i * 64 + lane]; bb[i] = (float)bta[i * 64 + lane]; }
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) s += y[i];
+  const float mean = wave_sum(s) / (float)d;
+  float q = 0.f;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) { float t = y[i] - mean; q += t * t; }
+  const float rstd = fast_rsqrt(wave_sum(q) / (float)d + 1e-5f);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) y[i] = (y[i] - mean) * rstd * gg[i] + bb[i];
+}
+
 // Workgroup barrier that orders LDS traffic only: __syncthreads() also waits for every global
 // load in flight (vmcnt(0)), which serialises requests a kernel issued early on purpose.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }

@@ -1210,12 +1210,75 @@ __global__ __launch_bounds__(64) void draft_logit_kernel(const bf16* __restrict_
   }
 }
 
+// The last LayerNorm and the draft logits of 16 rows in one launch: a wave normalises two rows, x in place and bf16 rows to memory and
+// LDS, and the first one forms the products, in the same order and with the same instruction as above.  A chain of a few memory round
+// trips and K / 16 dependent products; all loads are issued ahead of it (with the products' operands read from memory as they go,
+// 14 us at 1024).  In two launches, ln_kernel and the kernel above, 2.7 - 4.8 + 4.2 - 7.2 us; here 4.7 us (352 rows of 512),
+// 7.3 - 8.8 us (352 - 1408 rows of 1024).
+template <int PER, bool SWAP>
+__global__ __launch_bounds__(512) void ln_draft_kernel(float* __restrict__ x, const bf16* __restrict__ g, const bf16* __restrict__ b,
+                                                       bf16* __restrict__ xb, const bf16* __restrict__ E, int M, int V,
+                                                       const int* __restrict__ row_draft, float* __restrict__ zd_out) {
+  constexpr int K = 64 * PER, P = K + 8, PIECES = K / 8, NE = 16 * PIECES / 512;   // (rows padded by 16 bytes: reads of 16 rows meet all banks)
+  __shared__ __attribute__((aligned(16))) bf16 rows[16 * P], emb[16 * P];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lrow = lane & 31, lhalf = lane >> 5;
+  const int r0 = blockIdx.x * 16, r = r0 + (lrow & 15);
+  bf16x8 e[NE];   // the drafts' embedding rows, all at once, under the LayerNorm
+#pragma unroll
+  for (int i = 0; i < NE; ++i) {
+    const int p = threadIdx.x + i * 512, t = row_draft[min(r0 + p / PIECES, M - 1)];
+    e[i] = *reinterpret_cast<const bf16x8*>(E + (size_t)(t >= 0 && t < V ? t : 0) * K + p % PIECES * 8);
+  }
+  float y[2][PER];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) ln_row<PER>(x + (size_t)min(r0 + wave * 2 + i, M - 1) * K, g, b, lane, y[i]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int m = r0 + wave * 2 + i;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if (m < M) {
+        x[(size_t)m * K + j * 64 + lane] = y[i][j];
+        xb[(size_t)m * K + j * 64 + lane] = (bf16)y[i][j];
+      }
+      rows[(wave * 2 + i) * P + j * 64 + lane] = (bf16)y[i][j];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NE; ++i) {
+    const int p = threadIdx.x + i * 512;
+    *reinterpret_cast<bf16x8*>(emb + p / PIECES * P + p % PIECES * 8) = e[i];
+  }
+  lds_barrier();
+  if (wave != 0) return;
+  const int t = row_draft[min(r, M - 1)];
+  const bool has = r < M && t >= 0 && t < V;
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll 8
+  for (int k = 0; k < K / 16; ++k) {
+    const bf16x8 a = *reinterpret_cast<const bf16x8*>(rows + (lrow & 15) * P + k * 16 + lhalf * 8);
+    const bf16x8 c = *reinterpret_cast<const bf16x8*>(emb + (lrow & 15) * P + k * 16 + lhalf * 8);
+    acc = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(c, a, acc, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, c, acc, 0, 0, 0);
+  }
+  mfma_settle(acc);
+  if (lrow < 16 && lhalf == ((lrow >> 2) & 1) && r < M) {   // the diagonal, as above
+    const int reg = 4 * (lrow >> 3) + (lrow & 3);
+    float v = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) if (i == reg) v = acc[i];
+    zd_out[r] = has ? v : kNegInf;
+  }
+}
+
 // One block = 128 rows x 128 vocabulary columns.  After the K loop the fp32 tile goes through
 // LDS so that two threads own one row (64 columns each); each scans its columns once for
 // max / arg-max / number of logits above the draft's and once for the sum of exponentials, the
 // two halves are merged with lane shuffles, and one 16-byte partial record per (row, tile) is
 // written.  Logits never reach memory unless the caller asks for them.
-typedef GemmCfg<128, 128, 2> CfgVocab;
+typedef GemmCfg<128, 128, 2> CfgVocab;       // two blocks per CU
+typedef GemmCfg<128, 128, 4> CfgVocabDeep;   // where there is one to a CU at most, nothing hides its loads but its own ring: 128 KB LDS
 
 // Staging tile of the vocabulary kernel: [128 rows][32 chunks of 4 columns], chunk ch of row r
 // at chunk (ch & 16) + ((ch & 15) ^ (r & 15) ^ ((ch >> 4) << 3)): the 16 lanes that read one
@@ -1226,8 +1289,8 @@ __device__ __forceinline__ int vs_off(int row, int ch) {
 
 // ARGMAX: rows that score no draft and whose log-sum-exp nobody reads (the drafter's slots):
 // only max / arg-max are formed; the record's sum is 0 and its count 0.
-template <bool ARGMAX>
-__global__ __launch_bounds__(CfgVocab::kThreads) void vocab_kernel(const bf16* __restrict__ A,
+template <bool ARGMAX, class Cfg>
+__global__ __launch_bounds__(Cfg::kThreads) void vocab_kernel(const bf16* __restrict__ A,
                                                                    const bf16* __restrict__ E, int M,
                                                                    int V, int K, int MT, int NT,
                                                                    const float* __restrict__ zd_row,
@@ -1237,10 +1300,10 @@ __global__ __launch_bounds__(CfgVocab::kThreads) void vocab_kernel(const bf16* _
   int mt, nt;
   if (!xcd_tile(MT, NT, mt, nt)) return;
   const int m0 = mt * 128, n0 = nt * 128;
-  GemmAcc<CfgVocab> acc;
-  gemm_mainloop<CfgVocab>(A, K, E, K, M, V, 0, K / CfgVocab::GK, m0, n0, smem, acc);
+  GemmAcc<Cfg> acc;
+  gemm_mainloop<Cfg>(A, K, E, K, M, V, 0, K / Cfg::GK, m0, n0, smem, acc);
   float* cs = reinterpret_cast<float*>(smem);  // [128][128] fp32 = 64 KB
-  gemm_foreach<CfgVocab>(acc, 0, 0, [&](int r, int c, float v) { cs[vs_off(r, c >> 2) + (c & 3)] = v; });
+  gemm_foreach<Cfg>(acc, 0, 0, [&](int r, int c, float v) { cs[vs_off(r, c >> 2) + (c & 3)] = v; });
   __syncthreads();
 
   const int tid = threadIdx.x;
@@ -1288,7 +1351,7 @@ __global__ __launch_bounds__(CfgVocab::kThreads) void vocab_kernel(const bf16* _
     *reinterpret_cast<f32x4*>(part + ((size_t)m * NT + nt) * kPartF) = rec;
   }
   if (logits) {
-    for (int idx = tid; idx < 128 * 128; idx += CfgVocab::kThreads) {
+    for (int idx = tid; idx < 128 * 128; idx += Cfg::kThreads) {
       int r = idx >> 7, c = idx & 127;
       if (m0 + r < M && n0 + c < V) logits[(size_t)(m0 + r) * V + n0 + c] = cs[vs_off(r, c >> 2) + (c & 3)];
     }
@@ -1405,31 +1468,49 @@ __global__ __launch_bounds__(CfgVocab256::kThreads) void vocab256_kernel(const b
 
 int vocab_tile_cols(int) { return CfgVocab::kBN; }
 
+template <bool ARGMAX, class Cfg>
+static hipError_t launch_vocab(hipStream_t st, const bf16* A, const bf16* E, int M, int V, int K, int MT, int NT, const float* zd, float* part,
+                               float* logits) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab_kernel<ARGMAX, Cfg>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kSmemBytes);
+  if (attr != hipSuccess) return attr;
+  SD_LAUNCH_TIMED((vocab_kernel<ARGMAX, Cfg>), dim3(xcd_grid(MT, NT)), dim3(Cfg::kThreads), Cfg::kSmemBytes, st, A, E, M, V, K, MT, NT, zd, part,
+                  logits);
+  return hipGetLastError();
+}
+
+template <bool SWAP>
+static hipError_t launch_draft_logits(hipStream_t st, const bf16* A, const bf16* E, int M, int V, int K, const int* row_draft, float* zd_row,
+                                      const VocabLn* ln) {
+  if (ln && row_draft && (K == 512 || K == 1024)) {
+    if (K == 512) hipLaunchKernelGGL((ln_draft_kernel<8, SWAP>), dim3((M + 15) / 16), dim3(512), 0, st, ln->x, ln->g, ln->b, ln->xb, E, M, V, row_draft, zd_row);
+    else hipLaunchKernelGGL((ln_draft_kernel<16, SWAP>), dim3((M + 15) / 16), dim3(512), 0, st, ln->x, ln->g, ln->b, ln->xb, E, M, V, row_draft, zd_row);
+    return hipGetLastError();
+  }
+  if (ln) {
+    const hipError_t e = layer_norm(st, ln->x, ln->g, ln->b, ln->xb, M, K);
+    if (e != hipSuccess) return e;
+  }
+  // without row_draft no row scores a draft (drafter pass): every count is taken against -inf, unused
+  if (row_draft) hipLaunchKernelGGL(draft_logit_kernel<SWAP>, dim3((M + 31) / 32), dim3(64), 0, st, A, E, M, V, K, row_draft, zd_row);
+  return hipGetLastError();
+}
+
 hipError_t vocab_stats(hipStream_t st, const bf16* A, const bf16* E, int M, int V, int K,
-                       const int* row_draft, float* zd_row, float* part, float* logits, bool force_wide) {
+                       const int* row_draft, float* zd_row, float* part, float* logits, bool force_wide, const VocabLn* ln) {
   if (M <= 0) return hipSuccess;
-  static const hipError_t attr128 = [] {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab_kernel<false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, CfgVocab::kSmemBytes);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab_kernel<true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, CfgVocab::kSmemBytes);
-    return e;
-  }();
-  if (attr128 != hipSuccess) return attr128;
   const bool stats = row_draft || logits;
   const int MT = (M + 127) / 128, NT = (V + 127) / 128;
-  // 256 x 256 tiles once they give every CU two or more (the batched passes); their product is formed with
+  // 256 x 256 tiles once they give every CU one (the batched passes); their product is formed with
   // the operand roles swapped, and the draft logits follow suit.  V = 32768, d = 1024, a launch on 128 x 128 / 256 x 256 tiles: 132 rows
-  // (128 of the larger tiles) 25.6 / 32.3 us, 352 (256) 44.8 / 34.7, 704 (384) 68.6 / 62.9, 1023 (512) - / 68.6: one tile per CU
-  // would already do
+  // (128 of the larger tiles) 25.6 / 32.3 us, 352 (256) 44.8 / 34.7 (d = 512
+  // 25.3 / 20.9), 704 (384) 68.6 / 62.9.
   const int MT256 = (M + 255) / 256, NT256 = (V + 255) / 256;
-  const bool big = force_wide || (long)MT256 * NT256 >= 512;
-  // without row_draft no row scores a draft (drafter pass): every count is taken against -inf, unused
-  if (row_draft) {
-    if (big) hipLaunchKernelGGL(draft_logit_kernel<true>, dim3((M + 31) / 32), dim3(64), 0, st, A, E, M, V, K, row_draft, zd_row);
-    else hipLaunchKernelGGL(draft_logit_kernel<false>, dim3((M + 31) / 32), dim3(64), 0, st, A, E, M, V, K, row_draft, zd_row);
-  }
+  const bool big = force_wide || (long)MT256 * NT256 >= 256;
+  const hipError_t e = big ? launch_draft_logits<true>(st, A, E, M, V, K, row_draft, zd_row, ln)
+                           : launch_draft_logits<false>(st, A, E, M, V, K, row_draft, zd_row, ln);
+  if (e != hipSuccess) return e;
+  const float* zd = row_draft ? zd_row : nullptr;
   if (big) {
     constexpr int kSmem256 = CfgVocab256::kSmemBytes;
     static const hipError_t attr256 = [] {
@@ -1442,18 +1523,14 @@ hipError_t vocab_stats(hipStream_t st, const bf16* A, const bf16* E, int M, int 
     }();
     if (attr256 != hipSuccess) return attr256;
     if (stats)
-      SD_LAUNCH_TIMED(vocab256_kernel<false>, dim3(xcd_grid(MT256, NT256)), dim3(CfgVocab256::kThreads), kSmem256, st, A, E, M, V, K, MT256, NT256, NT, row_draft ? zd_row : nullptr, part, logits);
+      SD_LAUNCH_TIMED(vocab256_kernel<false>, dim3(xcd_grid(MT256, NT256)), dim3(CfgVocab256::kThreads), kSmem256, st, A, E, M, V, K, MT256, NT256, NT, zd, part, logits);
     else
       SD_LAUNCH_TIMED(vocab256_kernel<true>, dim3(xcd_grid(MT256, NT256)), dim3(CfgVocab256::kThreads), kSmem256, st, A, E, M, V, K, MT256, NT256, NT, nullptr, part, logits);
     return hipGetLastError();
   }
-  if (stats)
-    SD_LAUNCH_TIMED(vocab_kernel<false>, dim3(xcd_grid(MT, NT)), dim3(CfgVocab::kThreads), CfgVocab::kSmemBytes, st,
-                       A, E, M, V, K, MT, NT, row_draft ? zd_row : nullptr, part, logits);
-  else
-    SD_LAUNCH_TIMED(vocab_kernel<true>, dim3(xcd_grid(MT, NT)), dim3(CfgVocab::kThreads), CfgVocab::kSmemBytes, st,
-                       A, E, M, V, K, MT, NT, nullptr, part, logits);
-  return hipGetLastError();
+  const bool deep = (long)MT * NT <= 256;   // V = 32768, d = 1024, 128 rows (256 blocks): short ring 24.2 us, deep 21.1; more blocks share CUs
+  if (stats) return deep ? launch_vocab<false, CfgVocabDeep>(st, A, E, M, V, K, MT, NT, zd, part, logits) : launch_vocab<false, CfgVocab>(st, A, E, M, V, K, MT, NT, zd, part, logits);
+  return deep ? launch_vocab<true, CfgVocabDeep>(st, A, E, M, V, K, MT, NT, nullptr, part, logits) : launch_vocab<true, CfgVocab>(st, A, E, M, V, K, MT, NT, nullptr, part, logits);
 }
 
 }  // namespace sd

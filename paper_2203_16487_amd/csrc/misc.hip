@@ -86,8 +86,6 @@ hipError_t embed_rows(hipStream_t st, const int* tok, const int* pos, const bf16
 
 // ----------------------------------------------------------------------------- LayerNorm
 // One wave per row; mean and biased variance as two reductions over registers; eps 1e-5.
-// All loads of a row are issued before the first use (PER is a compile-time count), so a
-// row costs one memory round trip, not one per element.
 template <int PER>   // d = 64 * PER
 __global__ __launch_bounds__(256) void ln_kernel(float* __restrict__ x, const bf16* __restrict__ g,
                                                  const bf16* __restrict__ bta, bf16* __restrict__ xb,
@@ -97,25 +95,12 @@ __global__ __launch_bounds__(256) void ln_kernel(float* __restrict__ x, const bf
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= R || (m_real && r >= *m_real)) return;
   float* xr = x + (size_t)r * d;
-  float v[PER], gg[PER], bb[PER];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) v[i] = xr[i * 64 + lane];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) { gg[i] = (float)g[i * 64 + lane]; bb[i] = (float)bta[i * 64 + lane]; }
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) s += v[i];
-  const float mean = wave_sum(s) / (float)d;
-  float q = 0.f;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) { float t = v[i] - mean; q += t * t; }
-  const float rstd = fast_rsqrt(wave_sum(q) / (float)d + 1e-5f);
+  float y[PER];
+  ln_row<PER>(xr, g, bta, lane, y);
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    const int c = i * 64 + lane;
-    const float y = (v[i] - mean) * rstd * gg[i] + bb[i];
-    if (keep_x) xr[c] = y;
-    xb[(size_t)r * d + c] = (bf16)y;
+    if (keep_x) xr[i * 64 + lane] = y[i];
+    xb[(size_t)r * d + i * 64 + lane] = (bf16)y[i];
   }
 }
 // The same on the drafter's mask-slot rows only: output row o = b*k + s is the LayerNorm of row
