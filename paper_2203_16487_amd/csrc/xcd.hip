@@ -468,7 +468,7 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
   typedef PlDim<D> Dim;
   const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
   const PlRows<D, MR> R(a, A, false, rows, lane, wave);
-  constexpr int SETS = MR * Dim::KS * KC <= 16 ? KC : MR * Dim::KS <= 16 ? 2 : 1, TD = Dim::kTD;   // chunks of K of which rows are held
+  constexpr int SETS = MR * Dim::KS * KC <= 32 ? KC : MR * Dim::KS <= 16 ? 2 : 1, TD = Dim::kTD;   // chunks of K of which rows are held
   constexpr int NB = PlLds<D, MR>::kBatch, GT = NB < TD ? NB : TD;        // column tiles summed together
   static_assert(TD % GT == 0 && GT <= 2, "whole batches");
   u32x4 af[SETS][MR][Dim::KS];
@@ -799,20 +799,28 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
     lds_barrier();
     if (used > 1) {
       const int first = wave - kw;
-      float M = kNegInf, Ls = 0.f;
-      for (int s = first; s < first + used; ++s) M = fmaxf(M, ml[s * 32 + lq]);
-      for (int s = first; s < first + used; ++s) {
-        const float ms = ml[s * 32 + lq];
-        Ls += ml[s * 32 + 16 + lq] * (ms > kNegInf ? __builtin_amdgcn_exp2f((ms - M) * kCexp) : 0.f);
+      float ms[kPlWaves], ls[kPlWaves], M = kNegInf, Ls = 0.f;
+#pragma unroll
+      for (int s = 0; s < kPlWaves; ++s) {
+        const int w = first + min(s, used - 1);
+        ms[s] = ml[w * 32 + lq];
+        ls[s] = ml[w * 32 + 16 + lq];
+      }
+#pragma unroll
+      for (int s = 0; s < kPlWaves; ++s) M = fmaxf(M, ms[s]);
+#pragma unroll
+      for (int s = 0; s < kPlWaves; ++s) {
+        ms[s] = s < used && ms[s] > kNegInf ? __builtin_amdgcn_exp2f((ms[s] - M) * kCexp) : 0.f;
+        Ls += ls[s] * ms[s];
       }
       const float inv = Ls > 0.f ? __builtin_amdgcn_rcpf(Ls) : 0.f;
       for (int et = kw; et < 4; et += wpu) {
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
-        for (int s = first; s < first + used; ++s) {
-          const float ms = ml[s * 32 + lq], e = ms > kNegInf ? __builtin_amdgcn_exp2f((ms - M) * kCexp) : 0.f;
-          const f32x4 v = om[(s * 4 + et) * 64 + lane];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) o[i] += v[i] * e;
+        for (int s = 0; s < kPlWaves; ++s) {
+          const f32x4 v = om[((first + min(s, used - 1)) * 4 + et) * 64 + lane];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[i] += v[i] * ms[s];
         }
         store(et, o, inv);
       }
