@@ -372,40 +372,25 @@ struct EpiLnSum {
     // squared deviations from the chunk mean = sum y^2 - (sum y)^2 / CW, never below 0
     if (n % CW == 0) ln_out[(size_t)m * ln_pitch(ld / CW) + n / CW] = f32x2{s, fmaxf(ss - s * s * (1.0f / CW), 0.f)};
   }
-  // gemm_tile_kernel: the row's running chunk sums, the residual of a 32-column block, its sum, the chunk's pair
-  struct TileRow { float s, ss; };
-  __device__ __forceinline__ void tile_row(int, TileRow& t) const { t.s = t.ss = 0.f; }
-  __device__ __forceinline__ void tile_fetch(int m, int n, f32x4 (&p)[4]) const {
-    const float* src = x + (size_t)m * ld + n;
+  // gemm_tile_kernel: four columns of a row, 16 neighbouring lanes the row's chunk of 64; keep: the lane that writes the chunk's pair
+  __device__ __forceinline__ void tile_line(int m, int n, bool live, const f32x4& a, const f32x4& p, const f32x4 (&cv)[kVec], float rstd,
+                                            float nmr, bool keep, f32x2& pair) const {
+    f32x4 y;
+    bf16x4 g;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) p[q] = *reinterpret_cast<const f32x4*>(src + 8 * q);
-  }
-  __device__ __forceinline__ void tile_block(int m, int nb, int half, bool live, const f32x16& a, const f32x4 (&cv)[kVec][4],
-                                             const f32x4 (&p)[4], float rstd, float nmr, TileRow& t) const {
-    bf16x4 g[4];
-    f32x4 y[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        y[q][e] = a[4 * q + e] + __builtin_fmaf(__builtin_fmaf(p[q][e], rstd, nmr), cv[0][q][e], cv[1][q][e]);
-        t.s += y[q][e];
-        t.ss = __builtin_fmaf(y[q][e], y[q][e], t.ss);
-        g[q][e] = (bf16)(y[q][e] * cv[2][q][e]);
-      }
-    const bf16x8 g01 = join_halves(g[0], g[1]), g23 = join_halves(g[2], g[3]);
+    for (int e = 0; e < 4; ++e) {
+      y[e] = a[e] + __builtin_fmaf(__builtin_fmaf(p[e], rstd, nmr), cv[0][e], cv[1][e]);
+      g[e] = (bf16)(y[e] * cv[2][e]);
+    }
+    const float s = group_sum<16>((y[0] + y[1]) + (y[2] + y[3]));
+    const float ss = group_sum<16>(__builtin_fmaf(y[0], y[0], y[1] * y[1]) + __builtin_fmaf(y[2], y[2], y[3] * y[3]));
+    pair = f32x2{keep ? s : pair[0], keep ? fmaxf(ss - s * s * (1.0f / 64), 0.f) : pair[1]};
     if (!live) return;
-    float* dst = x + (size_t)m * ld + nb + 4 * half;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(dst + 8 * q) = y[q];
-    bf16* dg = xg + (size_t)m * ld + nb + 8 * half;
-    *reinterpret_cast<bf16x8*>(dg) = g01;
-    *reinterpret_cast<bf16x8*>(dg + 16) = g23;
+    const size_t o = (size_t)m * ld + n;
+    *reinterpret_cast<f32x4*>(x + o) = y;
+    *reinterpret_cast<bf16x4*>(xg + o) = g;
   }
-  __device__ __forceinline__ void tile_end(int m, int n, int half, bool live, const TileRow& t) const {
-    const float s = half_add(t.s), ss = half_add(t.ss);
-    if (live && half == 0) ln_out[(size_t)m * ln_pitch(ld / 64) + n / 64] = f32x2{s, fmaxf(ss - s * s * (1.0f / 64), 0.f)};
-  }
+  __device__ __forceinline__ void tile_pair(int m, int n, const f32x2& pair) const { ln_out[(size_t)m * ln_pitch(ld / 64) + n / 64] = pair; }
 };
 
 // rstd * (acc - mean * cs) + bf on V columns: cv[0] = cs, cv[1] = bf
@@ -421,16 +406,14 @@ __device__ __forceinline__ void ln_finish(const float (&v)[V], float rstd, float
 }
 
 // The same on a lane's 16 columns of a 32-column block: columns 8 half .. + 7 and 16 + 8 half .. + 7 of the block.
-__device__ __forceinline__ void ln_finish_block(const f32x16& a, float rstd, float nmr, const f32x4 (&cv)[2][4], bool relu,
+__device__ __forceinline__ void ln_finish_block(const f32x16& a, float rstd, float nmr, const f32x4 (&cv)[2][4], float floor,
                                                 bf16x8 (&o)[2]) {
   bf16x4 g[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float t = __builtin_fmaf(a[4 * q + e], rstd, __builtin_fmaf(nmr, cv[0][q][e], cv[1][q][e]));
-      if (relu) t = fmaxf(t, 0.f);
-      g[q][e] = (bf16)t;
+      g[q][e] = (bf16)fmaxf(__builtin_fmaf(a[4 * q + e], rstd, __builtin_fmaf(nmr, cv[0][q][e], cv[1][q][e])), floor);
     }
   o[0] = join_halves(g[0], g[1]);
   o[1] = join_halves(g[2], g[3]);
@@ -457,19 +440,13 @@ struct EpiLnBf16 {
     ln_finish<V>(v, rstd, nmr, cv, relu != 0, o);
     if (live) store_cols<V>(out + (size_t)m * ldo + n, o);
   }
-  struct TileRow {};
+  __device__ __forceinline__ bool tile_relu() const { return relu != 0; }
+  struct TileRow { __device__ __forceinline__ TileRow of(int) const { return {}; } };
   __device__ __forceinline__ void tile_row(int, TileRow&) const {}
-  __device__ __forceinline__ void tile_fetch(int, int, f32x4 (&)[4]) const {}
-  __device__ __forceinline__ void tile_block(int m, int nb, int half, bool live, const f32x16& a, const f32x4 (&cv)[kVec][4],
-                                             const f32x4 (&)[4], float rstd, float nmr, TileRow&) const {
-    bf16x8 o[2];
-    ln_finish_block(a, rstd, nmr, cv, relu != 0, o);
-    if (!live) return;
-    bf16* dst = out + (size_t)m * ldo + nb + 8 * half;
-    *reinterpret_cast<bf16x8*>(dst) = o[0];
-    *reinterpret_cast<bf16x8*>(dst + 16) = o[1];
+  // columns nb + c .. + 7 of row m + r (m, nb: the same for the whole wave)
+  __device__ __forceinline__ void tile_store(int m, int r, int nb, int c, const bf16x8& v, const TileRow&) const {
+    *reinterpret_cast<bf16x8*>(reinterpret_cast<char*>(out + (size_t)m * ldo + nb) + (unsigned)(r * ldo + c) * 2u) = v;
   }
-  __device__ __forceinline__ void tile_end(int, int, int, bool, const TileRow&) const {}
 };
 
 // Decoder self-attention projection: columns [0,d) are queries, [d,2d) keys, [2d,3d) values.
@@ -510,21 +487,23 @@ struct EpiLnQkvAppend {
     bf16* cache = (part == 1) ? kc : vc;
     store_cols<V>(cache + (((size_t)p.sb * H + h) * Lcap + p.pos) * kHeadDim + e, o);
   }
-  typedef Pre<8> TileRow;
+  __device__ __forceinline__ bool tile_relu() const { return false; }
+  struct TileRow : Pre<8> {   // of(l): lane l's
+    __device__ __forceinline__ TileRow of(int l) const {
+      TileRow t;
+      t.sb = __shfl(this->sb, l, 64);
+      t.pos = __shfl(this->pos, l, 64);
+      return t;
+    }
+  };
   __device__ __forceinline__ void tile_row(int m, TileRow& t) const { fetch<8>(m, 0, t); }
-  __device__ __forceinline__ void tile_fetch(int, int, f32x4 (&)[4]) const {}
-  __device__ __forceinline__ void tile_block(int m, int nb, int half, bool live, const f32x16& a, const f32x4 (&cv)[kVec][4],
-                                             const f32x4 (&)[4], float rstd, float nmr, TileRow& t) const {
-    bf16x8 o[2];
-    ln_finish_block(a, rstd, nmr, cv, false, o);
-    const int part = nb / d, c = nb - part * d + 8 * half;   // (the block lies inside one part and one head)
-    if (!live || (part != 0 && t.sb < 0)) return;
-    bf16* dst = part == 0 ? q + (size_t)m * d + c
-                          : (part == 1 ? kc : vc) + (((size_t)t.sb * H + (c >> 6)) * Lcap + t.pos) * kHeadDim + (c & 63);
-    *reinterpret_cast<bf16x8*>(dst) = o[0];
-    *reinterpret_cast<bf16x8*>(dst + 16) = o[1];
+  __device__ __forceinline__ void tile_store(int m, int r, int nb, int c, const bf16x8& v, const TileRow& t) const {
+    const int part = nb / d, h = (nb - part * d) >> 6;   // (a wave's 64 columns are one head's)
+    if (part != 0 && t.sb < 0) return;
+    bf16* dst = part == 0 ? q + (size_t)m * d + h * kHeadDim + (unsigned)(r * d)
+                          : (part == 1 ? kc : vc) + (((size_t)t.sb * H + h) * Lcap + t.pos) * kHeadDim;
+    *reinterpret_cast<bf16x8*>(dst + c) = v;
   }
-  __device__ __forceinline__ void tile_end(int, int, int, bool, const TileRow&) const {}
 };
 
 template <class Cfg, int VEC>
@@ -610,11 +589,14 @@ static hipError_t launch_ln_cfg(hipStream_t st, const bf16* A, int lda, const bf
   return hipGetLastError();
 }
 
-// ----------------------------------------------------------------------------- large tiles, epilogue from registers
+// ----------------------------------------------------------------------------- large tiles
 // Many rows (encoder, prefill, full batches).  The product is formed transposed (gemm_mainloop<.., SWAP>), so a lane owns 16
-// columns of one row per 32-column block: four groups of four (8 q + 4 (lane / 32) .. + 3).  LayerNorm statistics of a row's
-// 64-column chunk are then sums over a lane's own values and one exchange with the other half; bf16 results are joined to
-// 16-byte stores by the same exchange; nothing is staged through LDS.
+// columns of one row per 32-column block, four groups of four (8 q + 4 (lane / 32) .. + 3), and a wave's 64 columns are one chunk
+// of a row's statistics.  The epilogue has the whole ring to itself: a wave turns its row tiles through 16 KB of it, without barriers,
+// into whole lines.  Outputs are finished in the accumulators, then 8 lanes store a row's 128 bytes; sums are finished by 16
+// lanes a row, which read and write its 256 bytes of fp32.  Straight from the accumulators a store touches 32 rows, 32 bytes of each:
+// 32768 x 1024 x 1024 + sum 134.8 us, now 107.5; x 4096 + 280 / 255; outputs 32768 x 4096 x 1024 279 / 265 (of which the stores are some
+// 27 us, 268 MB; without any 197 for the product alone), 16384 x 3072 x 1024 99.0 / 96.5.
 //   256 x 256 (8 waves, one block per CU): a third fewer LDS reads and half the L2 traffic per product of
 //   128 x 128 (4 waves, two blocks per CU: one block's epilogue runs under the other's products).
 typedef GemmCfg<256, 256, 2, 2, 4> CfgSquare;
@@ -636,7 +618,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16*
   int mt, nt;
   if (!xcd_tile_grouped((M + Cfg::kBM - 1) / Cfg::kBM, NT, mt, nt)) return;
   const int m0 = mt * Cfg::kBM, n0 = nt * BN;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lrow = lane & 31, half = lane >> 5;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lrow = lane & 31, half = lane >> 5;
   const int wm = (wave / Cfg::kWavesN) * Cfg::kWM, wn = (wave % Cfg::kWavesN) * Cfg::kWN;
   GemmAcc<Cfg> acc;
   gemm_mainloop<Cfg, true>(A, lda, W, ldw, M, N, 0, K / Cfg::GK, m0, n0, smem, acc, [&] {
@@ -649,40 +631,82 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16*
     rows.finish(epi.d_ln(), epi.chunks, epi.identity(), rowstat);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // visible after the main loop's first barrier
   });
-  typename Epi::TileRow tr[TM];
-  f32x2 st[TM];
+  // Through 16 KB of the ring a wave, a row tile of 32 x 64 at a time, two in turn (LDS accesses of a wave are in order).
+  constexpr int OWN = Cfg::kSmemBytes / Cfg::kWaves;
+  static_assert(OWN >= 16384, "two fp32 row tiles");
+  char* own = reinterpret_cast<char*>(smem) + wave * OWN;
+  const int nb = n0 + wn;
+  if constexpr (Epi::kVec == 3) {
+    // sums: lane l finishes columns 4 (l % 16) .. + 3 of rows 4 p + l / 16, p = 0 .. 7
+    const int r4 = lane >> 4, c4 = lane & 15;
+    f32x4 cv[3], res[TM][8];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int r = wm + i * 32 + lrow;
-    epi.tile_row(min(m0 + r, M - 1), tr[i]);
-    st[i] = *reinterpret_cast<const f32x2*>(rowstat + 2 * r);
-  }
-  // blocks of 32 rows x 32 columns in column-major order; the next one's reads are requested before this one's stores
-  f32x4 pre[3][4];
-  auto fetch = [&](int j, int i, f32x4 (&p)[4]) {
-    epi.tile_fetch(min(m0 + wm + i * 32 + lrow, M - 1), min(n0 + wn + j * 32, N - 32) + 4 * half, p);
-  };
-  fetch(0, 0, pre[0]);
-  fetch(0, 1, pre[1]);
+    for (int v = 0; v < 3; ++v) cv[v] = *reinterpret_cast<const f32x4*>(colv + v * BN + wn + c4 * 4);
+    auto fetch = [&](int i) {
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int nb = n0 + wn + j * 32;
-    f32x4 cv[Epi::kVec][4];
-#pragma unroll
-    for (int v = 0; v < Epi::kVec; ++v)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) cv[v][q] = *reinterpret_cast<const f32x4*>(colv + v * BN + wn + j * 32 + 8 * q + 4 * half);
+      for (int p = 0; p < 8; ++p) {
+        const int r = i * 32 + p * 4;
+        res[i][p] = *reinterpret_cast<const f32x4*>(epi.x + (size_t)min(m0 + wm + r + r4, M - 1) * epi.ld + min(nb + c4 * 4, N - 4));
+      }
+    };
+    fetch(0);
+    fetch(1);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int m = m0 + wm + i * 32 + lrow, step = j * TM + i;
-      if (step + 2 < TM * TN) fetch((step + 2) / TM, (step + 2) % TM, pre[(step + 2) % 3]);
-      epi.tile_block(m, nb, half, m < M && nb < N, acc.c[i][j], cv, pre[step % 3], st[i][0], st[i][1], tr[i]);
-    }
-  }
+      float* buf = reinterpret_cast<float*>(own + (i & 1) * 8192);
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int m = m0 + wm + i * 32 + lrow;
-    epi.tile_end(m, n0 + wn, half, m < M && n0 + wn < N, tr[i]);
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16& a = acc.c[i][j];
+          *reinterpret_cast<f32x4*>(buf + lrow * 64 + (((j * 8 + 2 * q + half) ^ (lrow & 15)) << 2)) = f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+        }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (i + 2 < TM) fetch(i + 2);
+      f32x2 pair = {0.f, 0.f};
+#pragma unroll
+      for (int p = 0; p < 8; ++p) {
+        const int r = i * 32 + p * 4;
+        const f32x4 a = *reinterpret_cast<const f32x4*>(buf + (p * 4 + r4) * 64 + ((c4 ^ (((p & 3) << 2) + r4)) << 2));
+        const f32x2 st = *reinterpret_cast<const f32x2*>(rowstat + 2 * (wm + r + r4));
+        epi.tile_line(m0 + wm + r + r4, nb + c4 * 4, m0 + wm + r + r4 < M && nb < N, a, res[i][p], cv, st[0], st[1], c4 == p, pair);
+      }
+      const int m = m0 + wm + i * 32 + c4 * 4 + r4;
+      if (c4 < 8 && m < M && nb < N) epi.tile_pair(m, nb, pair);
+    }
+  } else {
+    // outputs: a lane finishes its accumulators and stores 8 columns of rows 8 p + l / 8, p = 0 .. 3
+    f32x4 cv[TN][2][4];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cv[j][v][q] = *reinterpret_cast<const f32x4*>(colv + v * BN + wn + j * 32 + 8 * q + 4 * half);
+    typename Epi::TileRow tr[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) epi.tile_row(min(m0 + wm + i * 32 + lrow, M - 1), tr[i]);
+    const float floor = epi.tile_relu() ? 0.f : __builtin_nanf("");   // (fmaxf of a number and NaN is the number)
+    const int r8 = lane >> 3, c8 = (lane & 7) * 8;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      bf16* buf = reinterpret_cast<bf16*>(own + (i & 1) * 4096);
+      const f32x2 st = *reinterpret_cast<const f32x2*>(rowstat + 2 * (wm + i * 32 + lrow));
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        bf16x8 o[2];
+        ln_finish_block(acc.c[i][j], st[0], st[1], cv[j], floor, o);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) *reinterpret_cast<bf16x8*>(buf + lrow * 64 + (((j * 4 + q * 2 + half) ^ (lrow & 7)) << 3)) = o[q];
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const bf16x8 v = *reinterpret_cast<const bf16x8*>(buf + (p * 8 + r8) * 64 + (c8 ^ (r8 << 3)));
+        const typename Epi::TileRow t = tr[i].of(p * 8 + r8);
+        if (m0 + wm + i * 32 + p * 8 + r8 < M && nb + c8 < N) epi.tile_store(m0 + wm + i * 32 + p * 8, r8, nb, c8, v, t);
+      }
+    }
   }
 }
 

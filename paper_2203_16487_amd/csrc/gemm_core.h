@@ -10,6 +10,7 @@
 #pragma once
 #include "common.h"
 #include <stdint.h>
+#include <type_traits>
 
 namespace sd {
 
@@ -107,11 +108,136 @@ __device__ __forceinline__ void wait_vm_stages(int allow) {
 struct NoHook {
   __device__ __forceinline__ void operator()() const {}
 };
+// The loop of the 256 x 256 tiles (2 x 4 waves of 128 x 64, two ring slots, SWAP): same products in the same order, but a stage is
+// walked by A row tile (phase i = row tile i, four steps of k) and not by k.  W's fragments of the whole stage are held (32
+// registers, replaced step by step in the last phase), so that a slot is given back a piece at a time: W and row tile 0 before the
+// stage's first product, then row tile after row tile, and the next occupant's requests go out two a phase instead of sixteen behind
+// one barrier, four to six phases before they are needed.  Barriers stand before phases 0 and 2; what each certifies is what the two
+// phases behind it read:
+//   before phase 0 of stage kt: row tiles 1, 2 of kt      requested in phase 3 of stage kt - 2
+//   before phase 2:             row tile 3 of kt          phase 0 of kt - 1
+//                               row tile 0 of kt + 1      phase 0 of kt - 1
+//                               W of kt + 1               phases 1, 2 of kt - 1
+// Written plainly, 8192^3: 832 us, now 775 (1.42 PFLOP/s; on zeros 710 and 584: the rate of real data is what the card's power
+// allows); 32768 x 1024 x 4096: 217, now 207; at K = 1024 1 - 2 % (a tile's fixed costs are a fifth there).
+template <class Cfg, class Hook = NoHook>
+__device__ __forceinline__ void gemm_mainloop_square(const bf16* __restrict__ A, int lda, const bf16* __restrict__ W, int ldw, int M, int N,
+                                                     int k_begin, int KT, int m0, int n0, bf16* smem, GemmAcc<Cfg>& acc, Hook hook = Hook()) {
+  static_assert(Cfg::kBM == 256 && Cfg::kBN == 256 && Cfg::kWavesM == 2 && Cfg::kWavesN == 4 && Cfg::GK == 64 && Cfg::kStages == 2, "shape");
+  constexpr int TM = 4, TN = 2, NS = 4, E = Cfg::kStageElems;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = (wave >> 2) * 128, wn = (wave & 3) * 64;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc.c[i][j][r] = 0.f;
+  // request q of a stage: 0 .. 3 row tile q of A (32 rows of either half), 4 .. 7 quarter q - 4 of W; a wave moves 8 rows of each
+  unsigned voff[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int row = q < 4 ? wm + q * 32 + (wave & 3) * 8 + (lane >> 3) : (q - 4) * 64 + wave * 8 + (lane >> 3);
+    const int chunk = (lane & 7) ^ ((row >> 1) & 7);
+    voff[q] = (q < 4 ? (unsigned)min(row, M - 1 - m0) * (unsigned)lda : (unsigned)min(row, N - 1 - n0) * (unsigned)ldw) * 2u + chunk * 16;
+  }
+  const bf16 *abase = A + (size_t)m0 * lda + k_begin, *wbase = W + (size_t)n0 * ldw + k_begin;
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)SD_LDS_PTR(smem));
+  const unsigned ldsA = lds0 + (wm + (wave & 3) * 8) * 128, ldsW = lds0 + (256 + wave * 8) * 128;
+  auto request = [&](int q, int kt) {
+    const unsigned s = (kt & 1) * (E * 2);
+    if (q < 4) dma16(abase + kt * 64, voff[q], ldsA + s + q * 32 * 128);
+    else dma16(wbase + kt * 64, voff[q], ldsW + s + (q - 4) * 64 * 128);
+  };
+#pragma unroll
+  for (int q = 4; q < 8; ++q) request(q, 0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) request(q, 0);
+  if (KT > 1) {
+    request(0, 1);
+#pragma unroll
+    for (int q = 4; q < 8; ++q) request(q, 1);
+    request(1, 1);
+    request(2, 1);
+  }
+  hook();
+  const int lrow = lane & 31, lhalf = lane >> 5;
+  int offA[NS], offB[NS];
+#pragma unroll
+  for (int ss = 0; ss < NS; ++ss) {
+    offA[ss] = lds_off<64>(wm + lrow, ss * 2 + lhalf);
+    offB[ss] = 256 * 64 + lds_off<64>(wn + lrow, ss * 2 + lhalf);
+  }
+  bf16x8 fa[2][NS], fb[NS][TN];
+  auto read_a = [&](int kt, int i, int ss) { fa[i & 1][ss] = *reinterpret_cast<const bf16x8*>(smem + (kt & 1) * E + offA[ss] + i * 2048); };
+  auto read_b = [&](int kt, int ss, int j) { fb[ss][j] = *reinterpret_cast<const bf16x8*>(smem + (kt & 1) * E + offB[ss] + j * 2048); };
+  // MODE 0: a stage with two more behind it, 1: one more, 2: the last
+  auto phase = [&](auto I, auto MODE, int kt) {
+    constexpr int i = decltype(I)::value, mode = decltype(MODE)::value;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int ss = s >> 1, j = s & 1;
+      acc.c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ss][j], fa[i & 1][ss], acc.c[i][j], 0, 0, 0);
+      if (i < 3) {
+        if (s < 4) read_a(kt, i + 1, s);
+      } else if (mode < 2) {
+        if (!(s & 1)) read_a(kt + 1, 0, s >> 1);
+        else { read_b(kt + 1, ss, 0); read_b(kt + 1, ss, 1); }
+      }
+      if (s == 3 || s == 5) {
+        const int w = s == 5;
+        if (i == 0) { if (w == 0 && mode < 2) request(3, kt + 1); if (w == 1 && mode < 1) request(0, kt + 2); }
+        if (i == 1 && mode < 1) request(4 + w, kt + 2);
+        if (i == 2 && mode < 1) request(6 + w, kt + 2);
+        if (i == 3 && mode < 1) request(1 + w, kt + 2);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto stage = [&](auto MODE, int kt) {
+    constexpr int mode = decltype(MODE)::value;
+    phase(std::integral_constant<int, 0>{}, MODE, kt);
+    phase(std::integral_constant<int, 1>{}, MODE, kt);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wait_vmcnt<mode == 0 ? 6 : mode == 1 ? 3 : 0>();
+    block_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    phase(std::integral_constant<int, 2>{}, MODE, kt);
+    phase(std::integral_constant<int, 3>{}, MODE, kt);
+    if (mode < 2) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      wait_vmcnt<mode == 0 ? 8 : 1>();
+      block_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if (KT > 1) wait_vmcnt<8>(); else wait_vmcnt<1>();
+  block_barrier();
+#pragma unroll
+  for (int ss = 0; ss < NS; ++ss) {
+    read_a(0, 0, ss);
+    read_b(0, ss, 0);
+    read_b(0, ss, 1);
+  }
+  int kt = 0;
+  for (; kt + 2 < KT; ++kt) stage(std::integral_constant<int, 0>{}, kt);
+  if (kt + 1 < KT) { stage(std::integral_constant<int, 1>{}, kt); ++kt; }
+  stage(std::integral_constant<int, 2>{}, kt);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) mfma_settle(acc.c[i][j]);
+  block_barrier();
+}
 template <class Cfg, bool SWAP = false, class Hook = NoHook>
 __device__ __forceinline__ void gemm_mainloop(const bf16* __restrict__ A, int lda,
                                               const bf16* __restrict__ W, int ldw, int M, int N,
                                               int k_begin, int KT, int m0, int n0, bf16* smem,
                                               GemmAcc<Cfg>& acc, Hook hook = Hook()) {
+  if constexpr (SWAP && Cfg::kBM == 256 && Cfg::kBN == 256 && Cfg::kStages == 2 && Cfg::kWavesM == 2 && Cfg::kWavesN == 4 && Cfg::GK == 64) {
+    gemm_mainloop_square<Cfg>(A, lda, W, ldw, M, N, k_begin, KT, m0, n0, smem, acc, hook);
+    return;
+  }
   constexpr int IPW = Cfg::kIPW, S = Cfg::kStages, GK = Cfg::GK, RPL = Cfg::kRowsPerLoad, CPR = GK / 8;
   constexpr int TM = Cfg::kTM, TN = Cfg::kTN, NS = GK / 16, TMIN = TM < TN ? TM : TN;
   static_assert(S >= 2 && NS % 2 == 0, "ring depth / fragment buffer parity");
