@@ -510,9 +510,7 @@ template <class Cfg, int VEC>
 constexpr int ln_smem_bytes() { return Cfg::kSmemBytes + (2 * Cfg::kBM + VEC * Cfg::kBN) * 4; }
 
 // PAIRS: 32 chunks of 64 columns are the most there can be (d <= 2048); with 32 columns, for d > 1024, up to 64.  They are held in
-// registers through the main loop, so the kernel that has room for 64 is for those rows only: with room for 64 everywhere the
-// residual sums of 7168 x 1024 x 1024 and x 4096 on 128 x 128 tiles ran one block a CU instead of two and took 69 us on average,
-// now 47.5; 1408 x 4096 x 1024 on 256 x 128 tiles 20.1, now 19.7.
+// registers through the main loop, so the kernel that has room for 64 is for those rows only.
 template <class Cfg, class Epi, int PAIRS>
 __global__ __launch_bounds__(Cfg::kThreads) void gemm_ln_kernel(const bf16* __restrict__ A, int lda,
                                                                 const bf16* __restrict__ W, int ldw,
@@ -598,8 +596,10 @@ static hipError_t launch_ln_cfg(hipStream_t st, const bf16* A, int lda, const bf
 // 32768 x 1024 x 1024 + sum 134.8 us, now 107.5; x 4096 + 280 / 255; outputs 32768 x 4096 x 1024 279 / 265 (of which the stores are some
 // 27 us, 268 MB; without any 197 for the product alone), 16384 x 3072 x 1024 99.0 / 96.5.
 //   256 x 256 (8 waves, one block per CU): a third fewer LDS reads and half the L2 traffic per product of
-//   128 x 128 (4 waves, two blocks per CU: one block's epilogue runs under the other's products).
+//   128 x 128 (4 waves, two blocks per CU: one block's epilogue runs under the other's products);
+//   256 x 128 and 128 x 128 with a deep ring, one block per CU, for outputs of one round of them.
 typedef GemmCfg<256, 256, 2, 2, 4> CfgSquare;
+typedef GemmCfg<128, 128, 4> CfgDeep;   // 128 KB LDS: one block per CU
 
 template <class Cfg, int VEC>
 constexpr int tile_smem_bytes() { return Cfg::kSmemBytes + (2 * Cfg::kBM + VEC * Cfg::kBN) * 4; }
@@ -1046,29 +1046,29 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeig
   if (one_round(M, N, 32, 32)) return launch_ksplit<KsplitCfg<32, 32, 8, 2>>(st, A, lda, W, M, N, K, epi, m_real);
   if (one_round(M, N, 32, 64)) return launch_ksplit<KsplitCfg<32, 64, 8, 1>>(st, A, lda, W, M, N, K, epi, m_real);
   if (one_round(M, N, 48, 64)) return launch_ksplit<KsplitCfg<48, 64, 4, 2>>(st, A, lda, W, M, N, K, epi, m_real);
-  // a long K pays for a larger tile (FFN2 of the big model at 1408 rows: 64 x 64 ring 28.0 us, 24.2; but at 1024 rows, where the ring's
-  // tiles are one to a CU, 19.2 and 22.9); at K <= 2048 the ring is level or better, and so it is where M is only a bound on
-  // the rows in use
+  // a long K pays for a larger tile where the ring's tiles are more than one to a CU (FFN2 of the big model at 1408 rows: 64 x 64 ring
+  // 28.0 us, 24.2; but at 1024 rows 19.2 and 22.9); at K <= 2048 the ring is level or better, and so it is where M is only a bound on the
+  // rows in use
   if constexpr (Epi::kVec == 3) {
-    if (K >= 4096 && !m_real && one_round(M, N, 96, 64)) return launch_ksplit<KsplitCfg<96, 64, 3, 2>>(st, A, lda, W, M, N, K, epi, m_real);
+    if (K >= 4096 && !m_real && !one_round(M, N, 64, 64) && one_round(M, N, 96, 64)) return launch_ksplit<KsplitCfg<96, 64, 3, 2>>(st, A, lda, W, M, N, K, epi, m_real);
   }
+  // From 512 tiles of 128 x 128 on: two of them a CU, or 256 x 256.  Below: 256 x 128 while those are at most one to a CU, 128 x 128 with a
+  // ring of four, one to a CU, while these are, and 64 x 64, two to a CU, while those are.  us on 64 x 64 / 128 x 128 ring of four /
+  // 256 x 128 / 128 x 128 two to a CU (x N x K, "+" a sum; of 128 x 128 tiles):
+  //   2048 x 1024 x 1024 (128) 10.8 / 12.7 / 17.1 / 12.5;  1408 x 1536 x 512 (132) 9.7 / 8.7 / 10.5 / 9.1;  1024 x 3072 x 1024 (192)
+  //   14.0 / 12.4 / 15.9 / 13.7;  4096 x 1024 x 1024 (256) 24.0 / 14.0 / 17.3 / 14.0;  2816 x 1024 x 4096 + (176) 56.3 / 35.2 / 48.5 / 49.3
+  //   2816 x 1536 x 512 (264) 13.9 / 16.4 / 11.6 / 12.9;  9216 x 512 x 512 + (288) 24.4 / 22.9 / 17.6 / 18.4;  7168 x 1024 x 4096 + (448)
+  //   147 / 72.2 / 62.5 / 66.0;  16384 x 512 x 512 (512) 26.6 / 20.1 / 16.1 / 15.1
   const long wide_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
-  // Two blocks of 128 x 128 for every CU, or larger tiles still.  (Below that the register epilogue would be the faster one for outputs,
-  // 7168 x 1024 x 1024 21.2 us against 24.8, and for long sums, x 4096 71.6 / 78.9; not for sums of d = 512, 9216 x 512 x 2048 38.9
-  // / 35.7.)
   if (wide_tiles >= 512) {
     if (square_tiles(M, N, K, m_real != nullptr)) return launch_tile<CfgSquare>(st, A, lda, W, M, N, K, epi, m_real);
     return launch_tile<CfgWide>(st, A, lda, W, M, N, K, epi, m_real);
   }
-  // the widest outputs (QKV and FFN1 of the big model) run on 256 x 128 tiles, eight waves, three-deep ring.  K = 1024, us on 256 x 128 /
-  // 128 x 128 / 64 x 64 tiles: 1408 rows x 3072 16.3 / 18.0 / 19.9, x 4096 18.0 / 19.4 / 22.7; 2048 rows 18.8 / 20.0 / 26.9 and 21.7 /
-  // 22.9 / 34.1; at the line, 1024 rows, 15.5 / 15.3 / 13.5 and 16.1 / 15.6 / 16.3.
-  if constexpr (Epi::kVec == 2) {
-    if (N >= 3072 && M >= 1024) return launch_ln_cfg<CfgTall>(st, A, lda, W, M, N, K, epi, m_real);
+  if (wide_tiles > 256) {
+    if (one_round(M, N, 256, 128)) return launch_tile<CfgTall>(st, A, lda, W, M, N, K, epi, m_real);
+    return launch_tile<CfgWide>(st, A, lda, W, M, N, K, epi, m_real);
   }
-  // (K = 512: up to some 2000 rows the small tiles, whose fixed costs are smaller: 1408 x 2048 x 512 9.7 us against 10.1; beyond, the wide
-  // ones would be faster, 2816 rows 15.3 / 13.4, but most rows are a bound there: the drafter's 2688 hold some 1500)
-  if (wide_tiles >= 200 && K > 512) return launch_ln_cfg<CfgWide>(st, A, lda, W, M, N, K, epi, m_real);
+  if (wide_tiles > 128) return launch_tile<CfgDeep>(st, A, lda, W, M, N, K, epi, m_real);
   return launch_ln_cfg<CfgSmall>(st, A, lda, W, M, N, K, epi, m_real);
 }
 
@@ -1302,7 +1302,7 @@ __global__ __launch_bounds__(512) void ln_draft_kernel(float* __restrict__ x, co
 // two halves are merged with lane shuffles, and one 16-byte partial record per (row, tile) is
 // written.  Logits never reach memory unless the caller asks for them.
 typedef GemmCfg<128, 128, 2> CfgVocab;       // two blocks per CU
-typedef GemmCfg<128, 128, 4> CfgVocabDeep;   // where there is one to a CU at most, nothing hides its loads but its own ring: 128 KB LDS
+typedef CfgDeep CfgVocabDeep;                // where there is one to a CU at most, nothing hides its loads but its own ring: 128 KB LDS
 
 // Staging tile of the vocabulary kernel: [128 rows][32 chunks of 4 columns], chunk ch of row r
 // at chunk (ch & 16) + ((ch & 15) ^ (r & 15) ^ ((ch >> 4) << 3)): the 16 lanes that read one
