@@ -25,9 +25,9 @@ __device__ __forceinline__ bool xcd_tile(int MT, int NT, int& mt, int& nt) {
 // The same for many row tiles: groups of 8 row tiles, inside a group n-major, so that what runs together on an XCD shares
 // both a few weight panels and a few row panels (one long n-major run streams all rows past each weight panel: 32768 x 3072
 // x 1024 on 128 x 128 tiles 276 us, grouped 247; on 256 x 256 231, grouped 212).
-__device__ __forceinline__ bool xcd_tile_grouped(int MT, int NT, int& mt, int& nt) {
+__device__ __forceinline__ bool xcd_tile_grouped(int id, int MT, int NT, int& mt, int& nt) {
   constexpr int G = 8;
-  const int nb = MT * NT, id = blockIdx.x;
+  const int nb = MT * NT;
   const int per = (nb + 7) >> 3;
   const int t = (id & 7) * per + (id >> 3);
   if ((id >> 3) >= per || t >= nb) return false;
@@ -441,6 +441,7 @@ struct EpiLnBf16 {
     if (live) store_cols<V>(out + (size_t)m * ldo + n, o);
   }
   __device__ __forceinline__ bool tile_relu() const { return relu != 0; }
+  static constexpr bool kStoresAll = true;   // every row inside the matrix is stored
   struct TileRow { __device__ __forceinline__ TileRow of(int) const { return {}; } };
   __device__ __forceinline__ void tile_row(int, TileRow&) const {}
   // columns nb + c .. + 7 of row m + r (m, nb: the same for the whole wave)
@@ -488,6 +489,7 @@ struct EpiLnQkvAppend {
     store_cols<V>(cache + (((size_t)p.sb * H + h) * Lcap + p.pos) * kHeadDim + e, o);
   }
   __device__ __forceinline__ bool tile_relu() const { return false; }
+  static constexpr bool kStoresAll = false;
   struct TileRow : Pre<8> {   // of(l): lane l's
     __device__ __forceinline__ TileRow of(int l) const {
       TileRow t;
@@ -598,6 +600,7 @@ static hipError_t launch_ln_cfg(hipStream_t st, const bf16* A, int lda, const bf
 //   256 x 256 (8 waves, one block per CU): a third fewer LDS reads and half the L2 traffic per product of
 //   128 x 128 (4 waves, two blocks per CU: one block's epilogue runs under the other's products);
 //   256 x 128 and 128 x 128 with a deep ring, one block per CU, for outputs of one round of them.
+// (Outputs of more than one round of 256 x 256 tiles: gemm_stream_kernel.)
 typedef GemmCfg<256, 256, 2, 2, 4> CfgSquare;
 typedef GemmCfg<128, 128, 4> CfgDeep;   // 128 KB LDS: one block per CU
 
@@ -616,7 +619,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16*
   float* colv = rowstat + 2 * Cfg::kBM;                                                          // [kVec][BN]
   if (m_real) M = min(M, *m_real);   // only the leading *m_real rows hold data (same value for the whole grid)
   int mt, nt;
-  if (!xcd_tile_grouped((M + Cfg::kBM - 1) / Cfg::kBM, NT, mt, nt)) return;
+  if (!xcd_tile_grouped(blockIdx.x, (M + Cfg::kBM - 1) / Cfg::kBM, NT, mt, nt)) return;
   const int m0 = mt * Cfg::kBM, n0 = nt * BN;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lrow = lane & 31, half = lane >> 5;
   const int wm = (wave / Cfg::kWavesN) * Cfg::kWM, wn = (wave % Cfg::kWavesN) * Cfg::kWN;
@@ -723,22 +726,161 @@ static hipError_t launch_tile(hipStream_t st, const bf16* A, int lda, const bf16
   return hipGetLastError();
 }
 
+// Outputs of more than one round of 256 x 256 tiles: a block per CU takes one tile after the other (gemm_mainloop_square).  The ring stays
+// the products': a wave turns 16 rows x 64 columns at a time through 2 KB of its own, and the column vectors (and the rows' statistics, where the
+// row tile changes) of the next tile have a place beside those of this one.
+// As blocks of a tile each, every round began with a memory round trip (operands, the rows' statistics) and ended with the stores of all
+// CUs at once, which a block has to see through before its LDS is free: 34 us a round at K = 1024, 22 at 512; now 30 and 19, of which the
+// products' rate on real data (1.42 PFLOP/s, see gemm_mainloop_square) asks for 24 and 12.  us, launches in place: 32768 x 4096 x 1024 277,
+// now 241; x 3072 205 / 182; 32768 x 2048 x 512 88 / 77; x 1536 (on 128 x 128 tiles before) 79 / 64; 9216 of 16384 rows x 3072 x 1024 75 / 59.
+template <class Epi>
+struct StreamTiles {
+  typedef CfgSquare Cfg;
+  static constexpr bool kStream = true;
+  static constexpr int kStores = Epi::kStoresAll ? 4 * Cfg::kTM : 0;
+  static constexpr int kPairs = 16;   // chunks of a row at most
+  static constexpr int kOwn = 16 * 64 * 2, kVecBytes = Epi::kVec * Cfg::kBN * 4, kStatBytes = 2 * Cfg::kBM * 4;
+  static constexpr int kBytes = Cfg::kSmemBytes + Cfg::kWaves * kOwn + 2 * (kVecBytes + kStatBytes);
+  static_assert(kBytes <= 160 * 1024, "LDS of a CU");
+  const Epi& epi;
+  GemmAcc<Cfg>& acc;
+  char* smem;
+  int M, N, MT, NT;
+  int m0, n0, m1, n1, at, flip, rflip;   // this tile, the next one; which of the XCD's run; halves of vectors and statistics in use
+  bool more;
+  __device__ __forceinline__ float* rowstat(int f) const { return reinterpret_cast<float*>(smem + Cfg::kSmemBytes + Cfg::kWaves * kOwn + f * kStatBytes); }
+  __device__ __forceinline__ float* colv(int f) const { return reinterpret_cast<float*>(smem + Cfg::kSmemBytes + Cfg::kWaves * kOwn + 2 * kStatBytes + f * kVecBytes); }
+  // tile `at` of the XCD's run
+  __device__ __forceinline__ bool tile(int at, int& m, int& n) const {
+    int mt, nt;
+    if (!xcd_tile_grouped((blockIdx.x & 7) + 8 * at, MT, NT, mt, nt)) return false;
+    m = mt * Cfg::kBM;
+    n = nt * Cfg::kBN;
+    return true;
+  }
+  __device__ __forceinline__ bool next(int& m, int& n) {
+    at += gridDim.x >> 3;
+    m1 = m0;
+    n1 = n0;
+    more = tile(at, m1, n1);
+    m = m1;
+    n = n1;
+    return more;
+  }
+  // the first waves' requests of the column vectors, 256 columns each
+  __device__ __forceinline__ void vectors(int wave, int lane, int n, int f) const {
+    if (wave < Epi::kVec)
+      dma16(reinterpret_cast<const bf16*>(epi.vec(wave)), (unsigned)min(n + lane * 4, N - 4) * 4u,
+            __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)SD_LDS_PTR(colv(f) + wave * Cfg::kBN)));
+  }
+  __device__ __forceinline__ void statistics(int m, int f) const {
+    int chunks = epi.chunks;
+    asm volatile("" : "+s"(chunks));   // (as fresh_lane)
+    LnRows<Cfg, kPairs> rows;
+    rows.request(epi.ln_in, chunks, m, M);
+    rows.finish(epi.d_ln(), chunks, epi.identity(), rowstat(f));
+  }
+  __device__ __forceinline__ bool done() {
+    constexpr int TM = Cfg::kTM, TN = Cfg::kTN, BN = Cfg::kBN;
+    const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lrow = lane & 31, half = lane >> 5;
+    const int wm = (wave / Cfg::kWavesN) * Cfg::kWM, wn = (wave % Cfg::kWavesN) * Cfg::kWN, nb = n0 + wn;
+    const float *stat = rowstat(rflip), *cvs = colv(flip);
+    if (more) {   // (ahead of the stores: loads and stores are answered in order)
+      vectors(wave, lane, n1, flip ^ 1);
+      if (m1 != m0) statistics(m1, rflip ^= 1);
+    }
+    bf16* buf = reinterpret_cast<bf16*>(smem + Cfg::kSmemBytes + wave * kOwn);
+    f32x4 cv[TN][2][4];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cv[j][v][q] = *reinterpret_cast<const f32x4*>(cvs + v * BN + wn + j * 32 + 8 * q + 4 * half);
+    typename Epi::TileRow tr[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) epi.tile_row(min(m0 + wm + i * 32 + lrow, M - 1), tr[i]);
+    const float floor = epi.tile_relu() ? 0.f : __builtin_nanf("");   // (fmaxf of a number and NaN is the number)
+    const int r8 = lane >> 3, c8 = (lane & 7) * 8;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const f32x2 st = *reinterpret_cast<const f32x2*>(stat + 2 * (wm + i * 32 + lrow));
+      bf16x8 o[TN][2];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) ln_finish_block(acc.c[i][j], st[0], st[1], cv[j], floor, o[j]);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if ((lrow >> 4) == h) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) *reinterpret_cast<bf16x8*>(buf + (lrow & 15) * 64 + (((j * 4 + q * 2 + half) ^ (lrow & 7)) << 3)) = o[j][q];
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const int r = i * 32 + h * 16 + p * 8;
+          const bf16x8 v = *reinterpret_cast<const bf16x8*>(buf + (p * 8 + r8) * 64 + (c8 ^ (r8 << 3)));
+          const typename Epi::TileRow t = tr[i].of(h * 16 + p * 8 + r8);
+          if (m0 + wm + r + r8 < M && nb + c8 < N) epi.tile_store(m0 + wm + r, r8, nb, c8, v, t);
+        }
+      }
+    }
+    const bool all = Epi::kStoresAll && m0 + Cfg::kBM <= M && n0 + BN <= N;
+    m0 = m1;
+    n0 = n1;
+    flip ^= 1;
+    return all;
+  }
+};
+
+template <class Epi>
+__global__ __launch_bounds__(CfgSquare::kThreads, 2) void gemm_stream_kernel(const bf16* __restrict__ A, int lda,
+                                                                             const bf16* __restrict__ W, int ldw, int M, int N, int K,
+                                                                             int NT, Epi epi, const int* __restrict__ m_real) {
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+  typedef CfgSquare Cfg;
+  if (m_real) M = min(M, *m_real);   // only the leading *m_real rows hold data (same value for the whole grid)
+  GemmAcc<Cfg> acc;
+  StreamTiles<Epi> t{epi, acc, reinterpret_cast<char*>(smem), M, N, (M + Cfg::kBM - 1) / Cfg::kBM, NT, 0, 0, 0, 0, (int)blockIdx.x >> 3, 0, 0, false};
+  if (!t.tile(t.at, t.m0, t.n0)) return;
+  gemm_mainloop_square<Cfg>(A, lda, W, ldw, M, N, 0, K / Cfg::GK, t.m0, t.n0, smem, acc, [&] {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    t.vectors(wave, threadIdx.x & 63, t.n0, 0);
+    t.statistics(t.m0, 0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // visible after the main loop's barriers
+  }, t);
+}
+
+template <class Epi>
+static hipError_t launch_stream(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K, const Epi& epi, const int* m_real) {
+  constexpr int kBytes = StreamTiles<Epi>::kBytes;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_stream_kernel<Epi>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
+  if (attr != hipSuccess) return attr;
+  const int MT = (M + 255) / 256, NT = (N + 255) / 256;
+  SD_LAUNCH_TIMED((gemm_stream_kernel<Epi>), dim3(std::min(xcd_grid(MT, NT), 256)), dim3(CfgSquare::kThreads), kBytes, st, A, lda, W, K, M, N,
+                  K, NT, epi, m_real);
+  return hipGetLastError();
+}
+
 // 256 x 256 tiles or 128 x 128 ones?  Time of a full round of blocks (256 and 512) as measured over K = 512 .. 4096, us:
-// 10.5 + 1.73 and 3.6 + 1.12 per 64 columns of K; a last round costs nearly a full one on one block per CU, and on two the
+// 10.5 + 1.73 and 3.6 + 1.12 per 64 columns of K; 8.2 + 1.38 where a block takes tile after tile (stream); a last round costs nearly a full one on one block per CU, and on two the
 // better part of one as soon as some CU has a second block.  (Sums of K = 512 take twice as long on both.)  Of twelve row counts from
 // 352 to 32768 and nine (N, K) of the two models, the choice was at most 3 % slower than the better of the two wherever it is
 // made.  Where M only bounds the rows in use (bound), the sum over half, three quarters and all of it decides.
-static float square_minus_wide(int M, int N, int K) {
+static float square_minus_wide(int M, int N, int K, bool stream) {
   const float kt = K / 64.f;
   const long sq = (long)((M + 255) / 256) * ((N + 255) / 256), wd = (long)((M + 127) / 128) * ((N + 127) / 128);
-  const float t_sq = (float)((sq + 255) / 256) * (sq < 256 ? 0.8f : 1.f) * (10.5f + 1.73f * kt);
+  const float round = stream && sq > 256 ? 8.2f + 1.38f * kt : 10.5f + 1.73f * kt;
+  const float t_sq = (float)((sq + 255) / 256) * (sq < 256 ? 0.8f : 1.f) * round;
   const long rem = wd % 512;
   const float t_wd = ((float)(wd / 512) + (rem == 0 ? 0.f : rem <= 256 ? 0.6f : 1.f)) * (3.6f + 1.12f * kt);
   return t_sq - t_wd;
 }
-static bool square_tiles(int M, int N, int K, bool bound) {
-  float t = square_minus_wide(M, N, K);
-  if (bound) t += square_minus_wide(M / 2, N, K) + square_minus_wide((int)(M * 3L / 4), N, K);
+static bool square_tiles(int M, int N, int K, bool bound, bool stream = false) {
+  float t = square_minus_wide(M, N, K, stream);
+  if (bound) t += square_minus_wide(M / 2, N, K, stream) + square_minus_wide((int)(M * 3L / 4), N, K, stream);
   return t < 0.f;
 }
 
@@ -757,7 +899,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void cross_kv_kernel(const bf16* 
   static_assert(BM * P * 2 <= Cfg::kSmemBytes + Cfg::kTailBytes, "bf16 tile in the ring");
   if (m_real) M = min(M, *m_real);
   int mt, ntl;
-  if (!xcd_tile_grouped((M + BM - 1) / BM, NT * a.layers, mt, ntl)) return;
+  if (!xcd_tile_grouped(blockIdx.x, (M + BM - 1) / BM, NT * a.layers, mt, ntl)) return;
   const int layer = ntl / NT, nt = ntl - layer * NT, m0 = mt * BM, n0 = nt * BN, N = 2 * d;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lrow = lane & 31, half = lane >> 5;
   const int wm = (wave / Cfg::kWavesN) * Cfg::kWM, wn = (wave % Cfg::kWavesN) * Cfg::kWN;
@@ -1061,7 +1203,14 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeig
   //   147 / 72.2 / 62.5 / 66.0;  16384 x 512 x 512 (512) 26.6 / 20.1 / 16.1 / 15.1
   const long wide_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
   if (wide_tiles >= 512) {
-    if (square_tiles(M, N, K, m_real != nullptr)) return launch_tile<CfgSquare>(st, A, lda, W, M, N, K, epi, m_real);
+    bool stream = false;
+    if constexpr (Epi::kVec == 2) stream = K % 128 == 0 && K >= 256 && epi.chunks <= StreamTiles<Epi>::kPairs && !one_round(M, N, 256, 256);
+    if (square_tiles(M, N, K, m_real != nullptr, stream)) {
+      if constexpr (Epi::kVec == 2) {
+        if (stream) return launch_stream(st, A, lda, W, M, N, K, epi, m_real);
+      }
+      return launch_tile<CfgSquare>(st, A, lda, W, M, N, K, epi, m_real);
+    }
     return launch_tile<CfgWide>(st, A, lda, W, M, N, K, epi, m_real);
   }
   if (wide_tiles > 256) {

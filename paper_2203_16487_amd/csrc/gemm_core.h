@@ -108,6 +108,12 @@ __device__ __forceinline__ void wait_vm_stages(int allow) {
 struct NoHook {
   __device__ __forceinline__ void operator()() const {}
 };
+// The lane, as a value that is not carried over from before: a loop over tiles would hold all addresses that follow from it.
+__device__ __forceinline__ int fresh_lane() {
+  int l = threadIdx.x & 63;
+  asm volatile("" : "+v"(l));
+  return l;
+}
 // The loop of the 256 x 256 tiles (2 x 4 waves of 128 x 64, two ring slots, SWAP): same products in the same order, but a stage is
 // walked by A row tile (phase i = row tile i, four steps of k) and not by k.  W's fragments of the whole stage are held (32
 // registers, replaced step by step in the last phase), so that a slot is given back a piece at a time: W and row tile 0 before the
@@ -120,33 +126,48 @@ struct NoHook {
 //                               W of kt + 1               phases 1, 2 of kt - 1
 // Written plainly, 8192^3: 832 us, now 775 (1.42 PFLOP/s; on zeros 710 and 584: the rate of real data is what the card's power
 // allows); 32768 x 1024 x 4096: 217, now 207; at K = 1024 1 - 2 % (a tile's fixed costs are a fifth there).
-template <class Cfg, class Hook = NoHook>
+//
+// One tile after the other (Tiles): next(m, n) says which follows (false: none; m, n are then the tile's own), done() finishes one and
+// says whether every wave sent off exactly STORES vector stores.  The requests of the next tile's first two stages go out in the last two of the
+// tile before as if they were its own (behind the last tile, once more its own, which nobody reads), so its first products need not wait,
+// and what done() stores is on its way under them: only the waits of the next tile's first stage count the stores among what may
+// still be in flight.  KT even and at least 4 (a slot's number does not depend on the tile); done() keeps out of the ring.
+struct OneTile {
+  static constexpr bool kStream = false;
+  static constexpr int kStores = 0;
+  __device__ __forceinline__ bool next(int&, int&) const { return false; }
+  __device__ __forceinline__ bool done() const { return false; }
+};
+template <class Cfg, class Hook = NoHook, class Tiles = OneTile>
 __device__ __forceinline__ void gemm_mainloop_square(const bf16* __restrict__ A, int lda, const bf16* __restrict__ W, int ldw, int M, int N,
-                                                     int k_begin, int KT, int m0, int n0, bf16* smem, GemmAcc<Cfg>& acc, Hook hook = Hook()) {
+                                                     int k_begin, int KT, int m0, int n0, bf16* smem, GemmAcc<Cfg>& acc, Hook hook = Hook(),
+                                                     Tiles tiles = Tiles()) {
   static_assert(Cfg::kBM == 256 && Cfg::kBN == 256 && Cfg::kWavesM == 2 && Cfg::kWavesN == 4 && Cfg::GK == 64 && Cfg::kStages == 2, "shape");
   constexpr int TM = 4, TN = 2, NS = 4, E = Cfg::kStageElems;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave >> 2) * 128, wn = (wave & 3) * 64;
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc.c[i][j][r] = 0.f;
   // request q of a stage: 0 .. 3 row tile q of A (32 rows of either half), 4 .. 7 quarter q - 4 of W; a wave moves 8 rows of each
-  unsigned voff[8];
+  unsigned voff[8], voff3;   // (3: of the stage after this one, which is the tile's where the others may be the next tile's)
+  const bf16 *abase, *wbase, *abase3;
+  auto place = [&](int tm, int tn) {
+    const int l = Tiles::kStream ? fresh_lane() : lane;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int row = q < 4 ? wm + q * 32 + (wave & 3) * 8 + (lane >> 3) : (q - 4) * 64 + wave * 8 + (lane >> 3);
-    const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-    voff[q] = (q < 4 ? (unsigned)min(row, M - 1 - m0) * (unsigned)lda : (unsigned)min(row, N - 1 - n0) * (unsigned)ldw) * 2u + chunk * 16;
-  }
-  const bf16 *abase = A + (size_t)m0 * lda + k_begin, *wbase = W + (size_t)n0 * ldw + k_begin;
+    for (int q = 0; q < 8; ++q) {
+      const int row = q < 4 ? wm + q * 32 + (wave & 3) * 8 + (l >> 3) : (q - 4) * 64 + wave * 8 + (l >> 3);
+      const int chunk = (l & 7) ^ ((row >> 1) & 7);
+      voff[q] = (q < 4 ? (unsigned)min(row, M - 1 - tm) * (unsigned)lda : (unsigned)min(row, N - 1 - tn) * (unsigned)ldw) * 2u + chunk * 16;
+    }
+    abase = A + (size_t)tm * lda + k_begin;
+    wbase = W + (size_t)tn * ldw + k_begin;
+  };
+  place(m0, n0);
+  abase3 = abase;
+  voff3 = voff[3];
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)SD_LDS_PTR(smem));
   const unsigned ldsA = lds0 + (wm + (wave & 3) * 8) * 128, ldsW = lds0 + (256 + wave * 8) * 128;
   auto request = [&](int q, int kt) {
     const unsigned s = (kt & 1) * (E * 2);
-    if (q < 4) dma16(abase + kt * 64, voff[q], ldsA + s + q * 32 * 128);
+    if (q < 4) dma16((q == 3 ? abase3 : abase) + kt * 64, q == 3 ? voff3 : voff[q], ldsA + s + q * 32 * 128);
     else dma16(wbase + kt * 64, voff[q], ldsW + s + (q - 4) * 64 * 128);
   };
 #pragma unroll
@@ -174,6 +195,7 @@ __device__ __forceinline__ void gemm_mainloop_square(const bf16* __restrict__ A,
   // MODE 0: a stage with two more behind it, 1: one more, 2: the last
   auto phase = [&](auto I, auto MODE, int kt) {
     constexpr int i = decltype(I)::value, mode = decltype(MODE)::value;
+    constexpr bool two = mode == 0;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       const int ss = s >> 1, j = s & 1;
@@ -186,48 +208,97 @@ __device__ __forceinline__ void gemm_mainloop_square(const bf16* __restrict__ A,
       }
       if (s == 3 || s == 5) {
         const int w = s == 5;
-        if (i == 0) { if (w == 0 && mode < 2) request(3, kt + 1); if (w == 1 && mode < 1) request(0, kt + 2); }
-        if (i == 1 && mode < 1) request(4 + w, kt + 2);
-        if (i == 2 && mode < 1) request(6 + w, kt + 2);
-        if (i == 3 && mode < 1) request(1 + w, kt + 2);
+        if (i == 0) { if (w == 0 && mode != 2) request(3, kt + 1); if (w == 1 && two) request(0, kt + 2); }
+        if (i == 1 && two) request(4 + w, kt + 2);
+        if (i == 2 && two) request(6 + w, kt + 2);
+        if (i == 3 && two) request(1 + w, kt + 2);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto stage = [&](auto MODE, int kt) {
-    constexpr int mode = decltype(MODE)::value;
+  // stored: STORES vector stores went out between the requests of this stage's last pieces and those of the next ones'
+  auto stage = [&](auto MODE, int kt, bool stored = false) {
+    constexpr int mode = decltype(MODE)::value, ST = Tiles::kStores;
     phase(std::integral_constant<int, 0>{}, MODE, kt);
     phase(std::integral_constant<int, 1>{}, MODE, kt);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    wait_vmcnt<mode == 0 ? 6 : mode == 1 ? 3 : 0>();
+    if (mode == 0 && ST > 0 && stored) wait_vmcnt<6 + ST>();
+    else wait_vmcnt<mode == 0 ? 6 : mode == 1 ? 3 : 0>();
     block_barrier();
     __builtin_amdgcn_sched_barrier(0);
     phase(std::integral_constant<int, 2>{}, MODE, kt);
     phase(std::integral_constant<int, 3>{}, MODE, kt);
-    if (mode < 2) {
+    if (mode != 2) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      wait_vmcnt<mode == 0 ? 8 : 1>();
+      if (mode == 0 && ST > 0 && stored) wait_vmcnt<8 + ST>();
+      else wait_vmcnt<mode == 0 ? 8 : 1>();
       block_barrier();
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  auto start = [&] {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc.c[i][j][r] = 0.f;
+#pragma unroll
+    for (int ss = 0; ss < NS; ++ss) {
+      read_a(0, 0, ss);
+      read_b(0, ss, 0);
+      read_b(0, ss, 1);
+    }
+    // (the first requests of the stage go to where these lay)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    block_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto settle = [&] {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) mfma_settle(acc.c[i][j]);
+  };
+  constexpr std::integral_constant<int, 0> kGoing{};
   if (KT > 1) wait_vmcnt<8>(); else wait_vmcnt<1>();
   block_barrier();
-#pragma unroll
-  for (int ss = 0; ss < NS; ++ss) {
-    read_a(0, 0, ss);
-    read_b(0, ss, 0);
-    read_b(0, ss, 1);
+  start();
+  if constexpr (Tiles::kStream) {
+    static_assert(8 + Tiles::kStores <= 63, "what a wave counts");
+    bool stored = false, more;
+    do {
+      int m1 = 0, n1 = 0;
+      more = tiles.next(m1, n1);
+      for (int kt = 0; kt < KT; ++kt) {
+        if (kt == KT - 2) {
+          place(m1, n1);
+          abase -= KT * 64;
+          wbase -= KT * 64;
+        }
+        stage(kGoing, kt, stored);
+        abase3 = abase;
+        voff3 = voff[3];
+        stored = false;
+      }
+      settle();
+      stored = tiles.done();
+      abase += KT * 64;
+      wbase += KT * 64;
+      abase3 = abase;
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) start();
+    } while (more);
+    wait_vmcnt<0>();
+  } else {
+    int kt = 0;
+    for (; kt + 2 < KT; ++kt) stage(kGoing, kt);
+    if (kt + 1 < KT) { stage(std::integral_constant<int, 1>{}, kt); ++kt; }
+    stage(std::integral_constant<int, 2>{}, kt);
+    settle();
+    block_barrier();
   }
-  int kt = 0;
-  for (; kt + 2 < KT; ++kt) stage(std::integral_constant<int, 0>{}, kt);
-  if (kt + 1 < KT) { stage(std::integral_constant<int, 1>{}, kt); ++kt; }
-  stage(std::integral_constant<int, 2>{}, kt);
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) mfma_settle(acc.c[i][j]);
-  block_barrier();
 }
 template <class Cfg, bool SWAP = false, class Hook = NoHook>
 __device__ __forceinline__ void gemm_mainloop(const bf16* __restrict__ A, int lda,

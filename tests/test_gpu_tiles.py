@@ -1,5 +1,5 @@
-"""The projections' larger tiles (128 x 128 with a ring of four, 256 x 128, 128 x 128 two to a CU, 256 x 256), each where the rule
-first and last takes it: widths that end inside a tile, rows that end inside one, rows that the call only bounds; outputs, sums
+"""The projections' larger tiles (128 x 128 with a ring of four, 256 x 128, 128 x 128 two to a CU, 256 x 256, one or several of these
+to a block), each where the rule first and last takes it: widths that end inside a tile, rows that end inside one, rows that the call only bounds; outputs, sums
 with their statistics, and keys / values appended to the cache."""
 import numpy as np
 import pytest
@@ -19,7 +19,11 @@ pytestmark = pytest.mark.gpu
     (192, 2112, 131, 64, 40),     # bound 8384 rows: sums of 132, QKV of 330, FFN1 of 1122
     (192, 2112, 257, 65, 1),      # bound 16705 rows: sums of 262
     (512, 2048, 64, 129, 129),    # 8256 rows: sums of 260
-    (512, 2048, 128, 128, 90),    # bound 16384 rows: sums of 512 (two to a CU or 256 x 256)
+    (512, 2048, 128, 128, 90),    # bound 16384 rows: sums of 512 (two to a CU or 256 x 256), FFN1 of 256 x 256, two or three to a block
+    (512, 2112, 129, 128, 100),   # FFN1: the last tile of a row 64 columns wide
+    (256, 2048, 256, 128, 128),   # K = 256, the shortest of them: four whole tiles to a block
+    (512, 2048, 129, 128, 1),     # half the rows that the grid is sized for
+    (1024, 4096, 20, 450, 450),   # 9000 rows, K = 1024: QKV and FFN1
 ])
 def test_encoder_tiles(d, F, B, S, lo):
     desc = synth.ModelDesc(1, 1, d, d // 64, F, 1000, S, 16).resolved()
@@ -61,3 +65,24 @@ def test_decoder_tiles(B, k):
         j = int(case.lens[b])
         assert np.abs(K[0, b, j:j + k + 1] - st.K[0][j:j + k + 1]).max() <= 3e-2, b
         assert np.abs(V[0, b, j:j + k + 1] - st.V[0][j:j + k + 1]).max() <= 3e-2, b
+
+
+def test_prefill_tiles():
+    """5000 - 6560 rows of d = 1024: keys / values of 312 tiles of 256 x 256, some blocks with two."""
+    desc = synth.ModelDesc(0, 1, 1024, 16, 4096, 1000, 16, 64).resolved()
+    case = cases.make_verify_case(desc, seed=3, B=32, S=7, k=4, beta=3, tau=1.0, len_lo=110, len_hi=205, drafts="random", ragged_src=True,
+                                  std=0.015)
+    L = case.L_max
+    K, V = cases.oracle_flat_cache(case, L)
+    ses = gh.open_verifier(case, max_tgt=216, fill=0xFF)
+    sd.specdec_set_stream(ses.ctx, ses.i32(case.tokens), ses.i32(case.lens))   # nothing counts as cached any more
+    zeros = torch.zeros((1, 32, L, 1024), dtype=torch.bfloat16, device=ses.device)
+    sd.specdec_load_cache(ses.ctx, sd.SPECDEC_VERIFIER, zeros, zeros, ses.i32(np.zeros(32, np.int32)))
+    sd.specdec_set_stream(ses.ctx, ses.i32(case.tokens), ses.i32(case.lens))
+    sd.specdec_prefill(ses.ctx, sd.SPECDEC_VERIFIER)
+    gk, gv = gh.gpu_cache(ses, case, L)
+    ses.close()
+    for b in range(32):
+        j = int(case.lens[b])
+        assert np.abs(gk[:, b, :j] - K[:, b, :j]).max() <= 3e-2, b
+        assert np.abs(gv[:, b, :j] - V[:, b, :j]).max() <= 3e-2, b
