@@ -13,8 +13,8 @@ KernelTimer* kernel_timer() { return g_kernel_timer; }
 // numbered n-major (m fastest) and XCD x takes the contiguous run [x*per, (x+1)*per): the
 // tiles that run together on one XCD then share a few weight column-panels and the
 // activation rows, which stay in that XCD's L2.  Returns false for the padding blocks.
-__device__ __forceinline__ bool xcd_tile(int MT, int NT, int& mt, int& nt) {
-  const int nb = MT * NT, id = blockIdx.x;
+__device__ __forceinline__ bool xcd_tile(int id, int MT, int NT, int& mt, int& nt) {
+  const int nb = MT * NT;
   const int per = (nb + 7) >> 3;
   const int t = (id & 7) * per + (id >> 3);
   if ((id >> 3) >= per || t >= nb) return false;
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_kernel(const bf16* __restr
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
   static_assert(Cfg::kSmemBytes >= Cfg::kBM * Cfg::kBN * 4, "staging tile must fit in the ring");
   int mt, nt;
-  if (!xcd_tile(MT, NT, mt, nt)) return;
+  if (!xcd_tile(blockIdx.x, MT, NT, mt, nt)) return;
   const int m0 = mt * Cfg::kBM, n0 = nt * Cfg::kBN;
   if (m_real) {   // only the leading *m_real rows hold data (same value for the whole grid)
     M = min(M, *m_real);
@@ -524,7 +524,7 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ln_kernel(const bf16* __re
   float* rowstat = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Cfg::kSmemBytes);   // [BM][2]
   float* colv = rowstat + 2 * Cfg::kBM;                                                          // [kVec][BN]
   int mt, nt;
-  if (!xcd_tile(MT, NT, mt, nt)) return;
+  if (!xcd_tile(blockIdx.x, MT, NT, mt, nt)) return;
   const int m0 = mt * Cfg::kBM, n0 = nt * Cfg::kBN;
   if (m_real) {   // only the leading *m_real rows hold data (same value for the whole grid)
     M = min(M, *m_real);
@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ksplit_kernel(const bf16* 
   constexpr int FA = BM / 16, FB = BN / 16, V = Cfg::kV, LPR = Cfg::kLPR, ITER = Cfg::kIter, RPP = Cfg::kRowsPerPass;
   float* rowstat = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Cfg::kRingBytes);   // [BM][2]
   int mt, nt;
-  if (!xcd_tile(MT, NT, mt, nt)) return;
+  if (!xcd_tile(blockIdx.x, MT, NT, mt, nt)) return;
   const int m0 = mt * BM, n0 = nt * BN;
   const int mr = m_real ? *m_real : M;   // arrives with the first operands (rows below M may all be read)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1471,7 +1471,7 @@ __global__ __launch_bounds__(Cfg::kThreads) void vocab_kernel(const bf16* __rest
                                                                    float* __restrict__ logits) {
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
   int mt, nt;
-  if (!xcd_tile(MT, NT, mt, nt)) return;
+  if (!xcd_tile(blockIdx.x, MT, NT, mt, nt)) return;
   const int m0 = mt * 128, n0 = nt * 128;
   GemmAcc<Cfg> acc;
   gemm_mainloop<Cfg>(A, K, E, K, M, V, 0, K / Cfg::GK, m0, n0, smem, acc);
@@ -1538,30 +1538,66 @@ __global__ __launch_bounds__(Cfg::kThreads) void vocab_kernel(const bf16* __rest
 // accumulators -- no staging of the fp32 tile through LDS -- followed by one exchange between the lane
 // halves and a merge of the two waves that share a 128-column tile through 16 KB of LDS.  The
 // partial records keep the 128-column granularity of the kernel above.
+// Beyond 256 tiles a block takes one after the other (STREAM, see gemm_mainloop_square): the next one's first operands arrive under the scan.
+// Launches in the translation loop, a block a tile / so: 1408 rows, d = 1024 97.6 / 95.2 us, 1280 rows, d = 512, 50.2 / 47.4 (three rounds
+// each; the scan, a quarter-rate exponential and six instructions per logit, is 4 us of a round, with nothing beside it).
 typedef GemmCfg<256, 256, 2, 2, 4> CfgVocab256;
 
-template <bool ARGMAX>
-__global__ __launch_bounds__(CfgVocab256::kThreads) void vocab256_kernel(const bf16* __restrict__ A,
-                                                                         const bf16* __restrict__ E, int M, int V,
-                                                                         int K, int MT, int NT256, int NT,
-                                                                         const float* __restrict__ zd_row,
-                                                                         float* __restrict__ part,
-                                                                         float* __restrict__ logits) {
-  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
-  int mt, nt;
-  if (!xcd_tile(MT, NT256, mt, nt)) return;
-  const int m0 = mt * 256, n0 = nt * 256;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+template <bool ARGMAX, bool STREAM>
+struct VocabTiles {
+  typedef CfgVocab256 Cfg;
+  static constexpr bool kStream = STREAM;
+  static constexpr int kStores = 0;   // (one record a lane, or logits beside it: not counted on)
+  static constexpr int kBytes = Cfg::kSmemBytes + 4 * 256 * 16 + 2 * 256 * 4;
+  GemmAcc<Cfg>& acc;
+  char* smem;
+  int M, V, MT, NT256, NT;
+  const float* __restrict__ zd_row;
+  float* __restrict__ part;
+  float* __restrict__ logits;
+  int m0, n0, m1, n1, at, flip;   // this tile, the next one; which of the XCD's run; half of zd in use
+  __device__ __forceinline__ float* zd_rows(int f) const { return reinterpret_cast<float*>(smem + Cfg::kSmemBytes + 4 * 256 * 16) + f * 256; }
+  __device__ __forceinline__ bool tile(int at, int& m, int& n) const {
+    int mt, nt;
+    if (!xcd_tile((blockIdx.x & 7) + 8 * at, MT, NT256, mt, nt)) return false;
+    m = mt * 256;
+    n = nt * 256;
+    return true;
+  }
+  // the first wave's request of the drafts' logits of 256 rows (of rows beyond M: not used)
+  __device__ __forceinline__ void drafts(int m, int f) const {
+    if (zd_row && threadIdx.x < 64)
+      dma16(reinterpret_cast<const bf16*>(zd_row), (unsigned)min(m + (int)threadIdx.x * 4, (M - 1) & ~3) * 4u,
+            __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)SD_LDS_PTR(zd_rows(f))));
+  }
+  __device__ __forceinline__ bool next(int& m, int& n) {
+    at += gridDim.x >> 3;
+    m1 = m0;
+    n1 = n0;
+    const bool more = tile(at, m1, n1);
+    if (more) drafts(m1, flip ^ 1);
+    m = m1;
+    n = n1;
+    return more;
+  }
+  __device__ __forceinline__ bool done() {
+    finish();
+    m0 = m1;
+    n0 = n1;
+    flip ^= 1;
+    return false;
+  }
+  __device__ __forceinline__ void finish() const;
+};
+
+template <bool ARGMAX, bool STREAM>
+__device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
+  const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tid = wave * 64 + lane;
   const int wy = wave >> 2, wx = wave & 3, lcol = lane & 31, lhalf = lane >> 5;
   float zd[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + wy * 128 + i * 32 + lcol;
-    zd[i] = (zd_row && m < M) ? zd_row[m] : kNegInf;   // -inf on rows that score no draft: count unused
-  }
-  GemmAcc<CfgVocab256> acc;
-  gemm_mainloop<CfgVocab256, true>(A, K, E, K, M, V, 0, K / CfgVocab256::GK, m0, n0, smem, acc);
-  f32x4* rec = reinterpret_cast<f32x4*>(smem);   // [4 wave columns][256 rows]; the ring is free after the main loop
+  for (int i = 0; i < 4; ++i) zd[i] = zd_row ? zd_rows(flip)[wy * 128 + i * 32 + lcol] : kNegInf;   // -inf on rows that score no draft: count unused
+  f32x4* rec = reinterpret_cast<f32x4*>(smem + Cfg::kSmemBytes);   // [4 wave columns][256 rows]
   const int nw = n0 + wx * 64 + 4 * lhalf;        // first column of this lane
   // column of accumulator (j, r) relative to nw: ascending in (j, r), so ">" keeps the lowest index of a tie
   auto col = [](int j, int r) { return j * 32 + 8 * (r >> 2) + (r & 3); };
@@ -1623,10 +1659,10 @@ __global__ __launch_bounds__(CfgVocab256::kThreads) void vocab256_kernel(const b
         }
     }
   }
-  __syncthreads();
+  lds_barrier();
   // thread (row, 128-column tile): waves 2t and 2t+1 of the row, lower columns first
   const int row = tid & 255, ct = tid >> 8;
-  const int m = m0 + row, nt128 = nt * 2 + ct;
+  const int m = m0 + row, nt128 = n0 / 128 + ct;
   if (m < M && nt128 < NT) {
     const f32x4 a = rec[(2 * ct) * 256 + row], b = rec[(2 * ct + 1) * 256 + row];
     const float nb = fmaxf(a[0], b[0]);
@@ -1637,6 +1673,37 @@ __global__ __launch_bounds__(CfgVocab256::kThreads) void vocab256_kernel(const b
     f32x4 out = {nb, tb ? b[1] : a[1], tot, __int_as_float(__float_as_int(a[3]) + __float_as_int(b[3]))};
     *reinterpret_cast<f32x4*>(part + ((size_t)m * NT + nt128) * kPartF) = out;
   }
+}
+
+template <bool ARGMAX, bool STREAM>
+__global__ __launch_bounds__(CfgVocab256::kThreads, 2) void vocab256_kernel(const bf16* __restrict__ A,
+                                                                            const bf16* __restrict__ E, int M, int V,
+                                                                            int K, int MT, int NT256, int NT,
+                                                                            const float* __restrict__ zd_row,
+                                                                            float* __restrict__ part,
+                                                                            float* __restrict__ logits) {
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+  GemmAcc<CfgVocab256> acc;
+  VocabTiles<ARGMAX, STREAM> t{acc, reinterpret_cast<char*>(smem), M, V, MT, NT256, NT, zd_row, part, logits, 0, 0, 0, 0, (int)blockIdx.x >> 3, 0};
+  if (!t.tile(t.at, t.m0, t.n0)) return;
+  auto hook = [&] { t.drafts(t.m0, 0); };
+  if constexpr (STREAM) {
+    gemm_mainloop_square<CfgVocab256>(A, K, E, K, M, V, 0, K / CfgVocab256::GK, t.m0, t.n0, smem, acc, hook, t);
+  } else {
+    gemm_mainloop_square<CfgVocab256>(A, K, E, K, M, V, 0, K / CfgVocab256::GK, t.m0, t.n0, smem, acc, hook);
+    t.finish();
+  }
+}
+template <bool ARGMAX, bool STREAM>
+static hipError_t launch_vocab256(hipStream_t st, const bf16* A, const bf16* E, int M, int V, int K, const float* zd, float* part, float* logits) {
+  constexpr int kBytes = VocabTiles<ARGMAX, STREAM>::kBytes;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab256_kernel<ARGMAX, STREAM>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
+  if (attr != hipSuccess) return attr;
+  const int MT = (M + 255) / 256, NT = (V + 255) / 256, grid = xcd_grid(MT, NT);
+  SD_LAUNCH_TIMED((vocab256_kernel<ARGMAX, STREAM>), dim3(STREAM ? std::min(grid, 256) : grid), dim3(CfgVocab256::kThreads), kBytes, st, A, E, M, V, K,
+                  MT, NT, (V + 127) / 128, zd, part, logits);
+  return hipGetLastError();
 }
 
 int vocab_tile_cols(int) { return CfgVocab::kBN; }
@@ -1685,21 +1752,9 @@ hipError_t vocab_stats(hipStream_t st, const bf16* A, const bf16* E, int M, int 
   if (e != hipSuccess) return e;
   const float* zd = row_draft ? zd_row : nullptr;
   if (big) {
-    constexpr int kSmem256 = CfgVocab256::kSmemBytes;
-    static const hipError_t attr256 = [] {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab256_kernel<false>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, kSmem256);
-      if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab256_kernel<true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmem256);
-      return e;
-    }();
-    if (attr256 != hipSuccess) return attr256;
-    if (stats)
-      SD_LAUNCH_TIMED(vocab256_kernel<false>, dim3(xcd_grid(MT256, NT256)), dim3(CfgVocab256::kThreads), kSmem256, st, A, E, M, V, K, MT256, NT256, NT, zd, part, logits);
-    else
-      SD_LAUNCH_TIMED(vocab256_kernel<true>, dim3(xcd_grid(MT256, NT256)), dim3(CfgVocab256::kThreads), kSmem256, st, A, E, M, V, K, MT256, NT256, NT, nullptr, part, logits);
-    return hipGetLastError();
+    const bool stream = K % 128 == 0 && K >= 256 && (long)MT256 * NT256 > 256;
+    if (stats) return stream ? launch_vocab256<false, true>(st, A, E, M, V, K, zd, part, logits) : launch_vocab256<false, false>(st, A, E, M, V, K, zd, part, logits);
+    return stream ? launch_vocab256<true, true>(st, A, E, M, V, K, nullptr, part, logits) : launch_vocab256<true, false>(st, A, E, M, V, K, nullptr, part, logits);
   }
   const bool deep = (long)MT * NT <= 256;   // V = 32768, d = 1024, 128 rows (256 blocks): short ring 24.2 us, deep 21.1; more blocks share CUs
   if (stats) return deep ? launch_vocab<false, CfgVocabDeep>(st, A, E, M, V, K, MT, NT, zd, part, logits) : launch_vocab<false, CfgVocab>(st, A, E, M, V, K, MT, NT, zd, part, logits);

@@ -1,6 +1,6 @@
 """The end of a verify pass: the last LayerNorm and the drafts' logits in one launch (d_model 512 / 1024, 16 rows a block), and the
 vocabulary tiles by which they are chosen: 128 x 128 with a deep ring where every block has a CU of its own, with a short one where
-not, 256 x 256 from one to a CU."""
+not, 256 x 256 from one to a CU, several of them to a block beyond (K a multiple of 128)."""
 import numpy as np
 import pytest
 
@@ -21,6 +21,9 @@ pytestmark = pytest.mark.gpu
     (1024, 9, 6, 1003, {}),                                       # 63 rows
     (1024, 13, 4, 300, {sd.SPECDEC_OPT_WIDE_VOCAB_TILES: 1}),     # 65 rows, 256 x 256 tiles
     (512, 43, 5, 32768, {}),                                      # 258 rows, 256 tiles of 256 x 256: the fewest by themselves
+    (512, 65, 7, 32100, {}),                                      # 520 rows, 378 tiles of 256 x 256: two to some blocks, edges cut
+    (256, 65, 7, 33000, {}),                                      # K = 256, the shortest of them
+    (192, 65, 7, 32100, {}),                                      # K = 192: a block a tile
     (128, 11, 2, 1003, {}),                                       # another width: two launches
 ])
 def test_tail_against_oracle(d, B, k, V, opts):
