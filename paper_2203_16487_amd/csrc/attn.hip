@@ -109,10 +109,11 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(AttnArgs a) {
 // eight consecutive keys of its query: already the B operand of the second product.  Values in row layout become V^T
 // operands through the transposing LDS read (a 16-lane group turns 4 keys x 16 dims); key-blocked ones are the operand.
 // Per 64 keys and wave: 16 MFMAs (512 cycles) against about 1100 cycles of softmax (a quarter-rate exponential per
-// score), so the vector pipe bounds it and what matters is instructions per score: row maxima are exchanged once per
-// tile, row sums once per pass, masking happens only on tiles a limit cuts, accumulators are rescaled only when some
-// maximum moved.
-// 32 x 16 heads, 1024 queries on 1024 keys: 166 us (829 TFLOP/s), 775 with the kernel above, whose waves fetch keys and values
+// score), so the vector pipe bounds it (busy 79 % of the time, the matrix pipe 43) and what matters is instructions per score: row maxima
+// are exchanged once per tile, row sums once per pass, masking happens only on tiles a limit cuts, accumulators are rescaled only when some
+// maximum has moved by more than kSlack (at every move, which with 32 rows is nearly every tile: 188 us in place of 177 below).  120 registers,
+// four waves a SIMD; with 140, three of them, 205 us.
+// 32 x 16 heads, 1024 queries on 1024 keys: 177 us in an encoder (776 TFLOP/s), 775 with the kernel above, whose waves fetch keys and values
 // one by one.
 constexpr int kTileQ = 128, kTileK = 64;
 
@@ -170,6 +171,9 @@ __global__ __launch_bounds__(256, 3) void attn_tile_kernel(AttnArgs a, int qgrou
     for (int e = 0; e < 8; ++e) qf[ks][e] = (bf16)((float)qf[ks][e] * 0.125f);   // exact: power of two
 
   constexpr float kLog2e = 1.44269504088896341f;
+  // What the exponentials are relative to (mrun) follows the row's maximum only when some row's has grown by more than this
+  // (then for all): probabilities up to 256 instead of 1 cost no precision, and sums of them no range.
+  constexpr float kSlack = 8.f / kLog2e;
   float mrun = kNegInf, lrun = 0.f;
   f32x16 oacc[2];
 #pragma unroll
@@ -198,8 +202,7 @@ __global__ __launch_bounds__(256, 3) void attn_tile_kernel(AttnArgs a, int qgrou
         s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[t], 0, 0, 0);
       }
     }
-    mfma_settle(s[0]);
-    mfma_settle(s[1]);
+    mfma_settle(s[0], s[1]);
     if (c0 + kTileK > kmin) {   // some query of the wave does not see the whole tile
 #pragma unroll
       for (int t = 0; t < 2; ++t)
@@ -216,8 +219,9 @@ __global__ __launch_bounds__(256, 3) void attn_tile_kernel(AttnArgs a, int qgrou
       for (int r = 0; r < 16; ++r) cm = fmaxf(cm, s[t][r]);
     cm = half_max(cm);
     const float mnew = fmaxf(mrun, cm);
-    const float nb = mnew > kNegInf ? -mnew * kLog2e : 0.f;
-    if (__builtin_amdgcn_ballot_w64(mnew > mrun)) {
+    const bool move = __builtin_amdgcn_ballot_w64(mnew > mrun + kSlack) != 0;
+    const float mref = move ? mnew : mrun, nb = mref > kNegInf ? -mref * kLog2e : 0.f;
+    if (move) {
       const float alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(mrun, kLog2e, nb));   // 0 on first use
       lrun *= alpha;
 #pragma unroll

@@ -146,6 +146,7 @@ __device__ __forceinline__ void mfma_settle(f32x4& a, f32x4& b) {
 __device__ __forceinline__ void mfma_settle(f32x4 (&a)[4]) {
   asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));
 }
+__device__ __forceinline__ void mfma_settle(f32x16& a, f32x16& b) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a), "+v"(b)); }
 __device__ __forceinline__ void mfma_settle(f32x16& a) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a)); }
 
 // Accesses that are coherent among all workgroups of a running kernel: relaxed atomics at
