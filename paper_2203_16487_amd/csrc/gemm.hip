@@ -1201,8 +1201,9 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeig
   //   14.0 / 12.4 / 15.9 / 13.7;  4096 x 1024 x 1024 (256) 24.0 / 14.0 / 17.3 / 14.0;  2816 x 1024 x 4096 + (176) 56.3 / 35.2 / 48.5 / 49.3
   //   2816 x 1536 x 512 (264) 13.9 / 16.4 / 11.6 / 12.9;  9216 x 512 x 512 + (288) 24.4 / 22.9 / 17.6 / 18.4;  7168 x 1024 x 4096 + (448)
   //   147 / 72.2 / 62.5 / 66.0;  16384 x 512 x 512 (512) 26.6 / 20.1 / 16.1 / 15.1
+  // (512 of a sum: 256 x 128, with 9216 of 16384 rows in use x 512 x 2048 37.9 against 43.5, x 512 x 512 19.6 / 20.4)
   const long wide_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
-  if (wide_tiles >= 512) {
+  if (wide_tiles > 512 || (wide_tiles == 512 && !(Epi::kVec == 3 && one_round(M, N, 256, 128)))) {
     bool stream = false;
     if constexpr (Epi::kVec == 2) stream = K % 128 == 0 && K >= 256 && epi.chunks <= StreamTiles<Epi>::kPairs && !one_round(M, N, 256, 256);
     if (square_tiles(M, N, K, m_real != nullptr, stream)) {

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
     (192, 2112, 131, 64, 40),     # bound 8384 rows: sums of 132, QKV of 330, FFN1 of 1122
     (192, 2112, 257, 65, 1),      # bound 16705 rows: sums of 262
     (512, 2048, 64, 129, 129),    # 8256 rows: sums of 260
-    (512, 2048, 128, 128, 90),    # bound 16384 rows: sums of 512 (two to a CU or 256 x 256), FFN1 of 256 x 256, two or three to a block
+    (512, 2048, 128, 128, 90),    # bound 16384 rows: sums of 512 (256 x 128, one to a CU), FFN1 of 256 x 256, two or three to a block
     (512, 2112, 129, 128, 100),   # FFN1: the last tile of a row 64 columns wide
     (256, 2048, 256, 128, 128),   # K = 256, the shortest of them: four whole tiles to a block
     (512, 2048, 129, 128, 1),     # half the rows that the grid is sized for
