@@ -624,16 +624,34 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16*
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lrow = lane & 31, half = lane >> 5;
   const int wm = (wave / Cfg::kWavesN) * Cfg::kWM, wn = (wave % Cfg::kWavesN) * Cfg::kWN;
   GemmAcc<Cfg> acc;
-  gemm_mainloop<Cfg, true>(A, lda, W, ldw, M, N, 0, K / Cfg::GK, m0, n0, smem, acc, [&] {
-    constexpr int QPV = BN / 4;   // 16-byte pieces per column vector of the tile
-    const int t = threadIdx.x;
-    LnRows<Cfg, 64> rows;
+  // The rows' statistics and the column vectors: requested ahead of the operands and finished behind the products where registers can hold
+  // them meanwhile (1408 x 3072 x 1024 on 256 x 128 21.2 us, now 20.7; sums of 7168 x 1024 39.1 / 38.3; with the residual requested there
+  // as well, ahead of the operands, 38.8); by the 256 x 256 tiles ahead of the loop.
+  constexpr bool HELD = Cfg::kBM * BN < 65536;
+  constexpr int QPV = BN / 4;   // 16-byte pieces per column vector of the tile
+  const int t = threadIdx.x;
+  LnRows<Cfg, 32> rows;
+  f32x4 cvec = {0.f, 0.f, 0.f, 0.f};
+  auto request = [&] {
     rows.request(epi.ln_in, epi.chunks, m0, M);
-    if (t < Epi::kVec * QPV)
-      *reinterpret_cast<f32x4*>(colv + t * 4) = *reinterpret_cast<const f32x4*>(epi.vec(t / QPV) + min(n0 + (t % QPV) * 4, N - 4));
+    if (t < Epi::kVec * QPV) cvec = *reinterpret_cast<const f32x4*>(epi.vec(t / QPV) + min(n0 + (t % QPV) * 4, N - 4));
+  };
+  auto finish = [&] {
+    if (t < Epi::kVec * QPV) *reinterpret_cast<f32x4*>(colv + t * 4) = cvec;
     rows.finish(epi.d_ln(), epi.chunks, epi.identity(), rowstat);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // visible after the main loop's first barrier
-  });
+  };
+  if constexpr (HELD) {
+    request();
+    gemm_mainloop<Cfg, true>(A, lda, W, ldw, M, N, 0, K / Cfg::GK, m0, n0, smem, acc);
+    finish();
+    lds_barrier();
+  } else {
+    gemm_mainloop<Cfg, true>(A, lda, W, ldw, M, N, 0, K / Cfg::GK, m0, n0, smem, acc, [&] {
+      request();
+      finish();
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // visible after the main loop's first barrier
+    });
+  }
   // Through 16 KB of the ring a wave, a row tile of 32 x 64 at a time, two in turn (LDS accesses of a wave are in order).
   constexpr int OWN = Cfg::kSmemBytes / Cfg::kWaves;
   static_assert(OWN >= 16384, "two fp32 row tiles");
@@ -1203,6 +1221,7 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeig
   //   147 / 72.2 / 62.5 / 66.0;  16384 x 512 x 512 (512) 26.6 / 20.1 / 16.1 / 15.1
   // (512 of a sum: 256 x 128, with 9216 of 16384 rows in use x 512 x 2048 37.9 against 43.5, x 512 x 512 19.6 / 20.4)
   const long wide_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
+  if (epi.chunks > 32) return launch_ln_cfg<CfgSmall>(st, A, lda, W, M, N, K, epi, m_real);   // (sums of so many rows come in fewer chunks)
   if (wide_tiles > 512 || (wide_tiles == 512 && !(Epi::kVec == 3 && one_round(M, N, 256, 128)))) {
     bool stream = false;
     if constexpr (Epi::kVec == 2) stream = K % 128 == 0 && K >= 256 && epi.chunks <= StreamTiles<Epi>::kPairs && !one_round(M, N, 256, 256);
