@@ -607,20 +607,15 @@ typedef GemmCfg<128, 128, 4> CfgDeep;   // 128 KB LDS: one block per CU
 template <class Cfg, int VEC>
 constexpr int tile_smem_bytes() { return Cfg::kSmemBytes + (2 * Cfg::kBM + VEC * Cfg::kBN) * 4; }
 
+// the tile at (m0, n0); smem: tile_smem_bytes
 template <class Cfg, class Epi>
-__global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16* __restrict__ A, int lda,
-                                                                     const bf16* __restrict__ W, int ldw, int M, int N, int K,
-                                                                     int NT, Epi epi, const int* __restrict__ m_real) {
-  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+__device__ __forceinline__ void gemm_tile(const bf16* __restrict__ A, int lda, const bf16* __restrict__ W, int ldw, int M, int N, int K,
+                                          int m0, int n0, const Epi& epi, bf16* smem) {
   static_assert(Cfg::kWN == 64, "a wave's columns are one statistics chunk");
   static_assert(Cfg::kThreads >= Epi::kVec * Cfg::kBN / 4, "one thread per 4 entries of the column vectors");
   constexpr int TM = Cfg::kTM, TN = Cfg::kTN, BN = Cfg::kBN;
   float* rowstat = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Cfg::kSmemBytes);   // [BM][2]
   float* colv = rowstat + 2 * Cfg::kBM;                                                          // [kVec][BN]
-  if (m_real) M = min(M, *m_real);   // only the leading *m_real rows hold data (same value for the whole grid)
-  int mt, nt;
-  if (!xcd_tile_grouped(blockIdx.x, (M + Cfg::kBM - 1) / Cfg::kBM, NT, mt, nt)) return;
-  const int m0 = mt * Cfg::kBM, n0 = nt * BN;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lrow = lane & 31, half = lane >> 5;
   const int wm = (wave / Cfg::kWavesN) * Cfg::kWM, wn = (wave % Cfg::kWavesN) * Cfg::kWN;
   GemmAcc<Cfg> acc;
@@ -732,6 +727,17 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16*
 }
 
 template <class Cfg, class Epi>
+__global__ __launch_bounds__(Cfg::kThreads, 2) void gemm_tile_kernel(const bf16* __restrict__ A, int lda,
+                                                                     const bf16* __restrict__ W, int ldw, int M, int N, int K,
+                                                                     int NT, Epi epi, const int* __restrict__ m_real) {
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+  if (m_real) M = min(M, *m_real);   // only the leading *m_real rows hold data (same value for the whole grid)
+  int mt, nt;
+  if (!xcd_tile_grouped(blockIdx.x, (M + Cfg::kBM - 1) / Cfg::kBM, NT, mt, nt)) return;
+  gemm_tile<Cfg, Epi>(A, lda, W, ldw, M, N, K, mt * Cfg::kBM, nt * Cfg::kBN, epi, smem);
+}
+
+template <class Cfg, class Epi>
 static hipError_t launch_tile(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K, const Epi& epi,
                               const int* m_real) {
   constexpr int kBytes = tile_smem_bytes<Cfg, Epi::kVec>();
@@ -766,6 +772,7 @@ struct StreamTiles {
   int M, N, MT, NT;
   int m0, n0, m1, n1, at, flip, rflip;   // this tile, the next one; which of the XCD's run; halves of vectors and statistics in use
   bool more;
+  int end;                               // of the XCD's run: where tiles of half the width begin
   __device__ __forceinline__ float* rowstat(int f) const { return reinterpret_cast<float*>(smem + Cfg::kSmemBytes + Cfg::kWaves * kOwn + f * kStatBytes); }
   __device__ __forceinline__ float* colv(int f) const { return reinterpret_cast<float*>(smem + Cfg::kSmemBytes + Cfg::kWaves * kOwn + 2 * kStatBytes + f * kVecBytes); }
   // tile `at` of the XCD's run
@@ -780,7 +787,7 @@ struct StreamTiles {
     at += gridDim.x >> 3;
     m1 = m0;
     n1 = n0;
-    more = tile(at, m1, n1);
+    more = at < end && tile(at, m1, n1);
     m = m1;
     n = n1;
     return more;
@@ -860,19 +867,32 @@ __global__ __launch_bounds__(CfgSquare::kThreads, 2) void gemm_stream_kernel(con
   typedef CfgSquare Cfg;
   if (m_real) M = min(M, *m_real);   // only the leading *m_real rows hold data (same value for the whole grid)
   GemmAcc<Cfg> acc;
-  StreamTiles<Epi> t{epi, acc, reinterpret_cast<char*>(smem), M, N, (M + Cfg::kBM - 1) / Cfg::kBM, NT, 0, 0, 0, 0, (int)blockIdx.x >> 3, 0, 0, false};
+  StreamTiles<Epi> t{epi, acc, reinterpret_cast<char*>(smem), M, N, (M + Cfg::kBM - 1) / Cfg::kBM, NT, 0, 0, 0, 0, (int)blockIdx.x >> 3, 0, 0, false, 0};
   if (!t.tile(t.at, t.m0, t.n0)) return;
+  // the XCD's run: whole rounds, and what is left of it
+  const int nb = t.MT * NT, per = (nb + 7) >> 3, run = min(per, nb - (int)(blockIdx.x & 7) * per), cus = gridDim.x >> 3, left = run % cus;
+  const bool halves = run > cus && left != 0 && 2 * left <= cus;
+  t.end = halves ? run - left : run;
   gemm_mainloop_square<Cfg>(A, lda, W, ldw, M, N, 0, K / Cfg::GK, t.m0, t.n0, smem, acc, [&] {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     t.vectors(wave, threadIdx.x & 63, t.n0, 0);
     t.statistics(t.m0, 0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // visible after the main loop's barriers
   }, t);
+  // a last round at most half full: tiles of 256 x 128, for twice as many CUs (7168 x 3072 x 1024, 336 tiles: 61.7 us, now 56.0; 9216 of 16384
+  // rows x 2048 x 512, 288 tiles, 37.7 / 34.4)
+  const int i = (int)blockIdx.x >> 3;
+  if (!halves || i >= 2 * left) return;
+  if (!t.tile(t.end + (i >> 1), t.m0, t.n0)) return;
+  t.n0 += (i & 1) * 128;
+  if (t.n0 >= N) return;
+  __syncthreads();   // the ring is everybody's again
+  gemm_tile<CfgTall, Epi>(A, lda, W, ldw, M, N, K, t.m0, t.n0, epi, smem);
 }
 
 template <class Epi>
 static hipError_t launch_stream(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K, const Epi& epi, const int* m_real) {
-  constexpr int kBytes = StreamTiles<Epi>::kBytes;
+  constexpr int kBytes = std::max(StreamTiles<Epi>::kBytes, tile_smem_bytes<CfgTall, Epi::kVec>());
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_stream_kernel<Epi>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
   if (attr != hipSuccess) return attr;

@@ -20,10 +20,10 @@ pytestmark = pytest.mark.gpu
     (192, 2112, 257, 65, 1),      # bound 16705 rows: sums of 262
     (512, 2048, 64, 129, 129),    # 8256 rows: sums of 260
     (512, 2048, 128, 128, 90),    # bound 16384 rows: sums of 512 (256 x 128, one to a CU), FFN1 of 256 x 256, two or three to a block
-    (512, 2112, 129, 128, 100),   # FFN1: the last tile of a row 64 columns wide
+    (512, 2112, 129, 128, 100),   # FFN1: the last tile of a row 64 columns wide (half of it empty)
     (256, 2048, 256, 128, 128),   # K = 256, the shortest of them: four whole tiles to a block
-    (512, 2048, 129, 128, 1),     # half the rows that the grid is sized for
-    (1024, 4096, 20, 450, 450),   # 9000 rows, K = 1024: QKV and FFN1
+    (512, 2048, 129, 128, 1),     # half the rows that the grid is sized for: 264 tiles, the last ones in halves
+    (1024, 4096, 20, 450, 450),   # 9000 rows, K = 1024: QKV (22 of an XCD's round left: whole tiles) and FFN1 (8: halves)
 ])
 def test_encoder_tiles(d, F, B, S, lo):
     desc = synth.ModelDesc(1, 1, d, d // 64, F, 1000, S, 16).resolved()
@@ -68,9 +68,9 @@ def test_decoder_tiles(B, k):
 
 
 def test_prefill_tiles():
-    """5000 - 6560 rows of d = 1024: keys / values of 312 tiles of 256 x 256, some blocks with two."""
+    """Some 6300 rows of d = 1024: queries, keys and values of 300 tiles of 256 x 256, six left of every XCD's round, in halves."""
     desc = synth.ModelDesc(0, 1, 1024, 16, 4096, 1000, 16, 64).resolved()
-    case = cases.make_verify_case(desc, seed=3, B=32, S=7, k=4, beta=3, tau=1.0, len_lo=110, len_hi=205, drafts="random", ragged_src=True,
+    case = cases.make_verify_case(desc, seed=3, B=32, S=7, k=4, beta=3, tau=1.0, len_lo=190, len_hi=205, drafts="random", ragged_src=True,
                                   std=0.015)
     L = case.L_max
     K, V = cases.oracle_flat_cache(case, L)
