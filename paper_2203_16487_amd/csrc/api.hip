@@ -318,11 +318,16 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   if (sd::persist_supported(d->dec_layers, (int)D, (int)F)) {
     const size_t most = Bm * (c->lim.k_max + 1);
     t.pl_rows = (int)(most < persist_rows((int)D) ? most : persist_rows((int)D));
-    // (in a drafter's workspace too, which never uses it: the size is asked for without a role)
-    const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F), xcd = sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F);
+    // The per-XCD decoder's share only where a pass within the limits can be its (one_kernel_way).  (In a drafter's workspace too, which
+    // uses neither: the size is asked for without a role.)
+    const bool per_xcd = sd::xcd_rows_most((int)Bm, c->lim.k_max + 1) > t.pl_rows;
+    const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F);
+    const size_t xcd = per_xcd ? sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F) : 0;
     t.pl_exch = cv.take<char>(one > xcd ? one : xcd);
-    t.xcd_stream = cv.take<char>(sd::xcd_stream_bytes(d->dec_layers, (int)D, (int)F));
-    t.xcd_vecs = cv.take<float>(sd::xcd_vec_bytes(d->dec_layers, (int)D) / sizeof(float));
+    if (per_xcd) {
+      t.xcd_stream = cv.take<char>(sd::xcd_stream_bytes(d->dec_layers, (int)D, (int)F));
+      t.xcd_vecs = cv.take<float>(sd::xcd_vec_bytes(d->dec_layers, (int)D) / sizeof(float));
+    }
   }
   if (d->enc_layers > 0) {
     const size_t Re = Bm * (size_t)c->Scap;
@@ -614,7 +619,7 @@ Way one_kernel_way(const specdec_ctx* c, const Model& m, int B, int T) {
   sd::XcdArgs x{};
   x.R = B * T; x.T = T; x.B = B; x.H = m.d.n_heads;
   const int D = m.d.d_model, F = m.d.d_ffn, R = B * T;
-  const bool gpu = R <= m.pl_rows && sd::persist_plan(p, D, F) > 0, xcd = R <= sd::kXcdMostRows && !(m.fp8 && R <= 32) && sd::xcd_plan(x, D, F) > 0;
+  const bool gpu = R <= m.pl_rows && sd::persist_plan(p, D, F) > 0, xcd = m.xcd_stream && R <= sd::kXcdMostRows && !(m.fp8 && R <= 32) && sd::xcd_plan(x, D, F) > 0;
   return gpu ? Way::gpu : xcd ? Way::xcd : Way::launches;
 }
 
@@ -936,7 +941,7 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
                                  f.cq.bf, f.w1.cs, f.w1.bf, f.vo, f.vco, f.v2});
       }
     HIPCHK(c, hipMemcpy(m.pl_layers, pl.data(), pl.size() * sizeof(sd::PlLayer), hipMemcpyHostToDevice));
-    if (m.pl_exch) HIPCHK(c, sd::xcd_pack(S(stream), m.pl_layers, d->dec_layers, d->d_model, m.xcd_stream, m.xcd_vecs));
+    if (m.xcd_stream && role == SPECDEC_VERIFIER) HIPCHK(c, sd::xcd_pack(S(stream), m.pl_layers, d->dec_layers, d->d_model, m.xcd_stream, m.xcd_vecs));
   }
   m.bound = true;
   return SPECDEC_OK;

@@ -291,6 +291,8 @@ constexpr unsigned kXcdAlonePasses = 16;  // that are computed without waits (7 
 size_t xcd_stream_bytes(int layers, int d, int F);
 size_t xcd_vec_bytes(int layers, int d);
 hipError_t xcd_pack(hipStream_t st, const PlLayer* layers, int n, int d, char* stream, float* vecs);
+// rows of the largest pass of up to max_batch sequences of up to max_T rows each that it takes
+int xcd_rows_most(int max_batch, int max_T);
 // bytes of exch for passes of up to max_batch sequences of up to max_T rows
 size_t xcd_exch_most(int max_batch, int max_T, int d, int F);
 // bytes of exch that a pass of a.B sequences of a.T rows uses (0: too many rows)

@@ -39,6 +39,8 @@
 // (A workgroup takes the XCD it finds itself on for its group and the eighth of its number for its place there, as ids are dealt to
 // the XCDs in turn.  Were they dealt otherwise, a place would be missing or taken twice: the same words written twice, or waits
 // given up.)
+#include <algorithm>
+
 #include "attn_core.h"
 #include "gemm_core.h"
 
@@ -1067,6 +1069,14 @@ static hipError_t pl_launch_both(hipStream_t st, XcdArgs a) {
 }
 }  // namespace xcd
 
+int xcd_rows_most(int max_batch, int max_T) {
+  int most = 0;
+  for (int T = 1; T <= max_T && T <= 32; ++T) {
+    const int B = std::min(max_batch, xcd::kPlGroups * (xcd::kPlRows / T));
+    most = std::max(most, B * T);
+  }
+  return most;
+}
 size_t xcd_exch_most(int max_batch, int max_T, int d, int F) {
   const int rows = xcd::pl_group_rows(max_batch, max_T);
   return xcd::pl_exch_bytes(max_batch, rows < xcd::kPlRows ? rows : xcd::kPlRows, d, F);

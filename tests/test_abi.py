@@ -139,3 +139,22 @@ def test_options_and_new_entry_points_validate_their_arguments():
         assert L.specdec_bind_draft_heads(ctx, 3, None, None, None, None) != sd.SPECDEC_OK
     finally:
         sd.specdec_destroy(ctx)
+
+
+@pytest.mark.parametrize("d,batch,k_max,held", [
+    (512, 1, 10, False),
+    (512, 21, 2, False),      # 63 rows: the one-kernel decoder over the whole GPU takes them all
+    (512, 32, 1, True),       # 64 rows
+    (1024, 1, 25, False),
+    (1024, 64, 1, False),     # 128 rows
+    (1024, 43, 2, True),      # 129 rows
+    (1024, 5, 31, True),      # 160 rows, 32 a sequence
+])
+def test_second_copy_of_the_matrices_only_where_a_pass_can_use_it(d, batch, k_max, held):
+    """The per-XCD decoder's copy of the decoder matrices: one model of two layers and one of four differ by the copies of two layers where
+    it is held, and by caches and vectors alone where not."""
+    ctx = sd.specdec_create(batch, k_max, 8, 8)
+    size = {n: sd.specdec_workspace_bytes(ctx, synth.ModelDesc(0, n, d, d // 64, 4 * d, 1000, 8, 8).resolved()) for n in (2, 4)}
+    sd.specdec_destroy(ctx)
+    copy = 2 * 2 * (6 * d * d + 2 * d * 4 * d)
+    assert (size[4] - size[2] >= copy) == held, (size, copy)
