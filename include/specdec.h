@@ -115,9 +115,9 @@ typedef enum {
                                           (the batched passes), else 128 x 128 tiles.  1: 256 x 256 tiles in every
                                           such pass (so that the wide kernel can be checked on small shapes).     */
   SPECDEC_OPT_GIVE_UP_WAITS = 7        /* default 0.  1: every wait of the one-kernel decoder that does not end at once is
-                                          given up (in groups: taken as given up), and the pass completed by the kernel
-                                          behind it (specdec_verify), so that this way of completing a pass can be
-                                          checked.                                                                */
+                                          given up (in groups: one workgroup of each is left out, and waits end at their
+                                          bound), and the pass completed by the kernel behind it
+                                          (specdec_verify), so that this way of completing a pass can be checked. */
 } specdec_option;
 
 /* ---- life cycle -------------------------------------------------------------------- */

@@ -677,8 +677,7 @@ int decoder_layers_persist(specdec_ctx* c, Model& m, int B, int T, bool few, hip
     a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
     if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
     a.exch = m.pl_exch; a.err = reinterpret_cast<unsigned*>(m.pl_err);
-    if (c->give_up) HIPCHK(c, sd::fill_i32(st, m.pl_err, (int)sd::kXcdAlonePasses, 1));
-    LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::xcd_decoder(st, a, m.d.d_model, m.d.d_ffn));
+    LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::xcd_decoder(st, a, m.d.d_model, m.d.d_ffn, c->give_up));
     return SPECDEC_OK;
   }
   sd::PlArgs a{};

@@ -297,7 +297,7 @@ int xcd_rows_most(int max_batch, int max_T);
 size_t xcd_exch_most(int max_batch, int max_T, int d, int F);
 // bytes of exch that a pass of a.B sequences of a.T rows uses (0: too many rows)
 size_t xcd_plan(XcdArgs& a, int d, int F);
-hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F);
+hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F, bool give_up);   // give_up: so that waits have to be given up
 // ---- skinny2.hip: the same passes with sub-layers owned by head / by FFN slice (three kernels per layer) ----
 bool sk2_supported(int d, int F);
 int sk2_ffn_slices(int F);             // partial results the FFN kernel leaves (at most 16)

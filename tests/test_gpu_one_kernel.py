@@ -71,8 +71,9 @@ def test_against_oracle(d, B, k, S, lo, hi, opts):
             assert np.abs(V[l, b, j:j + k + 1] - st.V[l][j:j + k + 1]).max() <= 3e-2, (b, l)
 
 
-def test_two_contexts_and_replays():
-    case = cases.make_verify_case(desc(512), seed=5, B=2, S=30, k=5, beta=3, tau=1.0, len_lo=3, len_hi=20, drafts="greedy",
+@pytest.mark.parametrize("B,k", [(2, 5), (9, 10)])   # over the whole GPU; 99 rows: per XCD
+def test_two_contexts_and_replays(B, k):
+    case = cases.make_verify_case(desc(512), seed=5, B=B, S=30, k=k, beta=3, tau=1.0, len_lo=3, len_hi=20, drafts="greedy",
                                   ragged_src=True)
     cases.run_oracle(case)
     first = gh.open_verifier(case, fill=0xFF)
@@ -86,8 +87,8 @@ def test_two_contexts_and_replays():
         check(case, gh.gpu_verify(second, case))
     other.synchronize()
     second.close()
-    d, acc, nxt = first.i32(case.drafts), torch.zeros(2, dtype=torch.int32, device="cuda"), torch.zeros(2, dtype=torch.int32, device="cuda")
-    logits = torch.zeros((2, 6, case.desc.vocab), dtype=torch.float32, device="cuda")
+    d, acc, nxt = first.i32(case.drafts), torch.zeros(B, dtype=torch.int32, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda")
+    logits = torch.zeros((B, k + 1, case.desc.vocab), dtype=torch.float32, device="cuda")
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     graph = torch.cuda.CUDAGraph()
@@ -111,10 +112,15 @@ def test_two_contexts_and_replays():
     (1024, 64, 1, 40, 50, 70, {}),
     (1024, 11, 10, 150, 100, 130, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
     (1024, 1, 30, 33, 9, 9, {sd.SPECDEC_OPT_FP8_WEIGHTS: 1, sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
+    # per XCD
+    (512, 9, 10, 40, 0, 75, {}),             # 99 rows: one row tile and two
+    (512, 32, 10, 64, 0, 64, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
+    (1024, 32, 10, 60, 0, 100, {}),          # 352 rows
+    (1024, 17, 20, 45, 30, 90, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),   # two query tiles a sequence
 ])
 def test_waits_given_up(d, B, k, S, lo, hi, opts):
     """Waits of the kernel given up at once (it ends, half of its results missing): the kernel behind it computes the pass,
-    to the last bit as the waiting one; so do the next 63, which find the flag raised; then one waits again."""
+    to the last bit as the waiting one; so do the next 63 (per XCD: 15), which find the flag raised; then one waits again."""
     case = cases.make_verify_case(desc(d), seed=d + B, B=B, S=S, k=k, beta=3, tau=1.0, len_lo=lo, len_hi=hi, drafts="random",
                                   ragged_src=True, fp8=sd.SPECDEC_OPT_FP8_WEIGHTS in opts, fp8_kv=sd.SPECDEC_OPT_FP8_CROSS_KV in opts)
     cases.run_oracle(case)
@@ -139,6 +145,36 @@ def test_waits_given_up(d, B, k, S, lo, hi, opts):
     times.append(sd.specdec_profile_read(ses.ctx)[0] / 65)
     print(f"one-kernel decoder {times[0]:.3f} ms, given up {times[1]:.3f} ms, flag raised {times[2]:.3f} ms, mean of the next 65 {times[3]:.3f} ms")
     ses.close()
+
+
+@pytest.mark.parametrize("d,B,k", [(512, 9, 10), (1024, 19, 10)])
+def test_finished_sequences_per_xcd(d, B, k):
+    """A pass after some sequences have ended, whole XCDs of them: theirs are computed and not reported, the others' as if alone; the same
+    where waits are given up."""
+    case = cases.make_verify_case(desc(d), seed=90 + d, B=B, S=30, k=k, beta=3, tau=1.0, len_lo=0, len_hi=20, drafts="random", ragged_src=True,
+                                  cap_extra=1)
+    cases.run_oracle(case)
+    ses = gh.open_verifier(case, max_tgt=case.L_max + 2 * k + 8, fill=0xFF)
+    check(case, gh.gpu_verify(ses, case))
+    done = [b for b in range(B) if b < 2 or b % 3 == 0]
+    nxt = [case.desc.eos_id if b in done else int(case.nxt[b]) for b in range(B)]
+    sd.specdec_commit(ses.ctx, ses.i32(np.zeros(B)), ses.i32(nxt))
+    outs = []
+    for give_up in (0, 1):
+        sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_GIVE_UP_WAITS, give_up)
+        n, out = resident_launches(ses, lambda: gh.gpu_verify(ses, case))
+        assert n == 1
+        outs.append(out)
+    ses.close()
+    for key in ("logits", "accept", "next", "stats"):
+        assert np.array_equal(outs[0][key], outs[1][key]), key
+    for b, st in enumerate(case.states):
+        if b in done:
+            assert outs[0]["accept"][b] == 0 and outs[0]["next"][b] == case.desc.pad_id
+            continue
+        st.len += 1
+        z = orc.verify_onepass(case.model, st, nxt[b], list(case.drafts[b]))
+        assert float(np.abs(outs[0]["logits"][b] - z).max()) <= max(2e-2, 0.04 * float(z.std())), b
 
 
 def resident_launches(ses, run):
