@@ -74,7 +74,7 @@ struct Model {
   float* hx = nullptr;       // [Bmax*k_max][d] head-based drafting: the hidden state each head adds to, then its output
   bool skinny_ready = false;
   sd::PlLayer* pl_layers = nullptr;   // device copy of the decoder layers' pointers (one-kernel decoder, persist.hip)
-  int* pl_err = nullptr;              // its flags (PlArgs::err, XcdArgs::err)
+  int* pl_err = nullptr;              // its flags (PlArgs::err), behind them the per-XCD one's (XcdArgs::err)
   char* pl_exch = nullptr;            // exchange buffers, its or the per-XCD one's (xcd.hip); null: dimensions they do not support
   int pl_rows = 0;                    // rows they are sized for, its
   char* xcd_stream = nullptr;         // the layers' weights as the per-XCD decoder streams them
@@ -658,6 +658,11 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
   return true;
 }
 
+// The flags of the decoder that runs it.
+unsigned* persist_flags(const specdec_ctx* c, const Model& m, int B, int T) {
+  return reinterpret_cast<unsigned*>(m.pl_err) + (one_kernel_way(c, m, B, T) == Way::xcd ? sd::kPlFlags : 0);
+}
+
 // Bytes of the exchange buffers that the pass's first kernel fills with 0xff.
 size_t persist_clear(const specdec_ctx* c, const Model& m, int B, int T) {
   if (one_kernel_way(c, m, B, T) == Way::gpu) return sd::persist_exch_bytes(B * T, m.d.dec_layers, m.d.d_model, m.d.d_ffn);
@@ -676,7 +681,7 @@ int decoder_layers_persist(specdec_ctx* c, Model& m, int B, int T, bool few, hip
     a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + (size_t)sd::kXcdMostRows * m.d.d_model;
     a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
     if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
-    a.exch = m.pl_exch; a.err = reinterpret_cast<unsigned*>(m.pl_err);
+    a.exch = m.pl_exch; a.err = persist_flags(c, m, B, T);
     LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::xcd_decoder(st, a, m.d.d_model, m.d.d_ffn, c->give_up));
     return SPECDEC_OK;
   }
@@ -688,7 +693,7 @@ int decoder_layers_persist(specdec_ctx* c, Model& m, int B, int T, bool few, hip
   a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + persist_rows(m.d.d_model) * m.d.d_model;
   a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
   if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
-  a.exch = m.pl_exch; a.err = reinterpret_cast<unsigned*>(m.pl_err);
+  a.exch = m.pl_exch; a.err = persist_flags(c, m, B, T);
   LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::persist_decoder(st, a, m.d.d_model, m.d.d_ffn, c->give_up));
   return SPECDEC_OK;
 }
@@ -927,7 +932,7 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
     if (rcq != SPECDEC_OK) return fail(c, rcq, "FP8 weight quantisation failed: %s", hipGetErrorString(hipGetLastError()));
   }
   {
-    HIPCHK(c, sd::fill_i32(S(stream), m.pl_err, 0, 3));
+    HIPCHK(c, sd::fill_i32(S(stream), m.pl_err, 0, sd::kPlFlags + sd::kXcdFlags));
     // for the one-kernel decoder: the bf16 matrices, then (FP8 weights) their codes
     std::vector<sd::PlLayer> pl;
     for (int set = 0; set < (m.fp8 ? 2 : 1); ++set)
@@ -955,7 +960,7 @@ int specdec_begin(specdec_ctx* c, int32_t B, int32_t max_new, void* stream) {
   const Model& any = c->m[0].bound ? c->m[0] : c->m[1];
   if (max_new > c->lim.max_tgt) max_new = c->lim.max_tgt;   // no stream grows beyond the arena
   HIPCHK(c, sd::begin_state(S(stream), c->st, B, max_new, c->lim.max_tgt, any.d.bos_id));
-  if (c->m[0].bound) HIPCHK(c, sd::fill_i32(S(stream), c->m[0].pl_err, 0, 3));   // a new run clears the one-kernel decoder's flags
+  if (c->m[0].bound) HIPCHK(c, sd::fill_i32(S(stream), c->m[0].pl_err, 0, sd::kPlFlags + sd::kXcdFlags));   // a new run clears the one-kernel decoder's flags
   c->B = B;
   c->max_new = max_new;
   c->last_T = 0;
@@ -1213,7 +1218,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_verify(st, c->st, m.rm, draft, B, k, m.d.vocab, m.embed, m.pe, m.x, m.xb,
                                         m.d.d_model, one ? m.pl_exch : nullptr,
                                         one ? persist_clear(c, m, B, T) : 0));
-  const unsigned* failed = one ? reinterpret_cast<const unsigned*>(m.pl_err) + 1 : nullptr;
+  const unsigned* failed = one ? persist_flags(c, m, B, T) + 1 : nullptr;
   float* sums = one ? m.skp : m.x;   // the last residual sums (the one-kernel decoder keeps its input rows)
   int n_tiles = (m.d.vocab + 63) / 64;   // per-row partial records of the vocabulary kernel that ran
   if (small && (m.fp8 || m.kv8) && (c->resident || c->sliced))

@@ -260,6 +260,7 @@ struct PlArgs {
   struct PlTickets* tickets;
 };
 constexpr int kPlBlocks = 256;            // most workgroups of a pass
+constexpr int kPlFlags = 2, kXcdFlags = 3;   // words of PlArgs::err, XcdArgs::err: each decoder's passes are counted for themselves
 bool persist_supported(int layers, int d, int F);
 size_t persist_exch_bytes(int rows, int layers, int d, int F);
 int persist_plan(PlArgs& a, int d, int F);   // workgroups of a pass of a.R rows, a.B sequences, a.H heads (0: too many rows)

@@ -179,6 +179,37 @@ def test_finished_sequences_per_xcd(d, B, k):
         assert float(np.abs(outs[0]["logits"][b] - z).max()) <= max(2e-2, 0.04 * float(z.std())), b
 
 
+def test_each_decoder_gives_up_for_itself():
+    """Passes of 9 rows run over the whole GPU, of 99 per XCD: where one kind has given up its waits, the other still waits (its kernel
+    takes some 40 us, 5 where it finds its flag raised)."""
+    case = cases.make_verify_case(desc(512), seed=95, B=9, S=30, k=10, beta=3, tau=1.0, len_lo=0, len_hi=20, drafts="random", ragged_src=True)
+    cases.run_oracle(case)
+    ses = gh.open_verifier(case, fill=0xFF)
+    acc, nxt, z = ses.i32(np.zeros(9)), ses.i32(np.zeros(9)), torch.zeros((9, 1, case.desc.vocab), dtype=torch.float32, device=ses.device)
+
+    def few():
+        sd.specdec_verify(ses.ctx, None, 0, 1, 0.0, acc, nxt, z)
+        return z.cpu().numpy()
+
+    def many():
+        return gh.gpu_verify(ses, case)["logits"]
+
+    want = {f: f() for f in (few, many)}
+    sd.specdec_profile_select(ses.ctx, sd.KIND["resident"])
+    for given_up, other in ((few, many), (many, few)):
+        sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_GIVE_UP_WAITS, 1)
+        assert np.array_equal(given_up(), want[given_up])
+        sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_GIVE_UP_WAITS, 0)
+        sd.specdec_profile_read(ses.ctx)
+        assert np.array_equal(other(), want[other])
+        ms, n = sd.specdec_profile_read(ses.ctx)
+        assert n == 1 and ms > 0.015, (given_up, ms)
+        assert np.array_equal(given_up(), want[given_up])
+        assert sd.specdec_profile_read(ses.ctx)[0] < 0.015
+        restart(ses, case)                     # (a new run: no flag is raised)
+    ses.close()
+
+
 def resident_launches(ses, run):
     """How often the one-kernel decoder was launched by run(), and run()'s result."""
     sd.specdec_profile_select(ses.ctx, sd.KIND["resident"])
