@@ -781,10 +781,24 @@ __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decod
   } else {
     __shared__ int drawn;
     const int total = a.n_layers * kPlStages * NB;   // (ids of a pass: below 2^24)
+    int st = -1;
     while (true) {
-      if (threadIdx.x == 0) drawn = (int)(__hip_atomic_fetch_add(&a.tickets->drawn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u);
+      // (In one block: of one at the loop's end and one at its top the compiler can make one with two ways back, and lanes 1 - 63 then go
+      // round, barriers and all, without lane 0.)
+      if (threadIdx.x == 0) {
+        if (st >= 0) {
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the caches' write-back, which the fence only starts)
+          __hip_atomic_fetch_add(&a.tickets->done[st], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        drawn = (int)(__hip_atomic_fetch_add(&a.tickets->drawn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u);
+      }
       __syncthreads();
-      const int t = __builtin_amdgcn_readfirstlane(drawn), st = t / NB, l = st / kPlStages;
+      // a wave that gives up ends, and what it would have drawn or left the others cannot go on with
+      if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0) return;
+      const int t = __builtin_amdgcn_readfirstlane(drawn);
+      st = t / NB;
+      const int l = st / kPlStages;
       if (t >= total) {   // (the last workgroup to find none left: every one has read the flag, and nothing else writes it now)
         if (t == total + (int)gridDim.x - 1 && threadIdx.x == 0) *a.raised -= 1;
         return;
@@ -797,7 +811,6 @@ __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decod
       take_units();
       if (!stage(st - l * kPlStages, l)) return;
       __syncthreads();   // all stores of the workgroup are out (and the ticket has been read)
-      if (threadIdx.x == 0) __hip_atomic_fetch_add(&a.tickets->done[st], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
