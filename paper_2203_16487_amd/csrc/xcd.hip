@@ -910,14 +910,7 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     }
     auto resid = [&](int mr, int ct) {
       const int lane = pl_lane(), lq = lane & 15, g = lane >> 4;
-      if (ALONE) {   // (rows beyond the group's: read, never used)
-        const size_t o = (size_t)(at.g * kPlRows + 16 * mr + lq) * D + (at.w * Dim::kTD + ct) * 16 + 4 * g;
-        if (s == 2 && l == 0) {
-          const int row = at.row0 + min(16 * mr + lq, at.rows - 1);
-          *reinterpret_cast<f32x4*>(a.resid + o) = *reinterpret_cast<const f32x4*>(a.x + (size_t)row * D + (at.w * Dim::kTD + ct) * 16 + 4 * g);
-        }
-        return a.resid + o;
-      }
+      if (ALONE) return a.resid + (size_t)(at.g * kPlRows + 16 * mr + lq) * D + (at.w * Dim::kTD + ct) * 16 + 4 * g;
       return L.resid + ((ct * MR + mr) * 16 + lq) * 16 + 4 * g;
     };
     auto out = [&](int row, int c, const f32x4& y, const f32x4& gx) {
@@ -965,6 +958,14 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
       for (int s = 0; s < kPlStages; ++s)
         stage(s, l);
   } else {
+    // the residual: embedded rows (those beyond the group's: read, never used).  All of them, and there, ahead of the stages: a wave without
+    // a tile to sum reads another's (pl_reduce), and a copy it made then could overtake that one's result.
+    for (int i = threadIdx.x; i < 16 * MR * (D / 4); i += kPlThreads) {
+      const int row = i / (D / 4), c = i % (D / 4) * 4;
+      *reinterpret_cast<f32x4*>(a.resid + (size_t)(at.g * kPlRows + row) * D + c) =
+          *reinterpret_cast<const f32x4*>(a.x + (size_t)(at.row0 + min(row, at.rows - 1)) * D + c);
+    }
+    wait_vmcnt<0>();
     __syncthreads();
     for (int i = 0; i < a.n_layers * kPlStages * kPlMembers; ++i) {
       const int l = i / (kPlStages * kPlMembers), s = i / kPlMembers % kPlStages;

@@ -115,6 +115,7 @@ def test_two_contexts_and_replays(B, k):
     # per XCD
     (512, 9, 10, 40, 0, 75, {}),             # 99 rows: one row tile and two
     (512, 32, 10, 64, 0, 64, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),
+    (512, 37, 11, 70, 0, 130, {}),           # 60 and 48 rows an XCD: all four row tiles, residual of the fourth
     (1024, 32, 10, 60, 0, 100, {}),          # 352 rows
     (1024, 17, 20, 45, 30, 90, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}),   # two query tiles a sequence
 ])
