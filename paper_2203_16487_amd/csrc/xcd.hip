@@ -786,7 +786,7 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
     lds_barrier();   // the latest product's partial tiles, or the units' before, are done with
     if (kw < used) pl_attn_wave<SELF, KV8>(a, ex, l, at.b0, t, kw, wpu, L.vs(wave), mrun, lrun, oacc);
     if (used == 1 && kw == 0) {   // nothing to merge
-      const float inv = lrun > 0.f ? __builtin_amdgcn_rcpf(lrun) : 0.f;
+      const float inv = lrun > 0.f ? 1.f / lrun : 0.f;
 #pragma unroll
       for (int et = 0; et < 4; ++et) store(et, oacc[et], inv);
     }
@@ -816,7 +816,7 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
         ms[s] = s < used && ms[s] > kNegInf ? __builtin_amdgcn_exp2f((ms[s] - M) * kCexp) : 0.f;
         Ls += ls[s] * ms[s];
       }
-      const float inv = Ls > 0.f ? __builtin_amdgcn_rcpf(Ls) : 0.f;
+      const float inv = Ls > 0.f ? 1.f / Ls : 0.f;
       for (int et = kw; et < 4; et += wpu) {
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
