@@ -48,7 +48,7 @@ namespace sd {
 namespace xcd {
 
 constexpr unsigned kPoison = 0xffffffffu;
-constexpr unsigned kPlSpinMax = 1u << 19;   // (0.1 s: 2^17 polls of the L2 take 25 ms with d = 512, 28 with 1024)
+constexpr unsigned kPlSpinMax = 3u << 18;   // (0.13 - 0.17 s: 2^17 polls of the L2 take 21 - 28 ms)
 constexpr int kPlGroups = 8, kPlMembers = 32;          // XCDs; workgroups of each
 constexpr int kPlWaves = 8, kPlThreads = 64 * kPlWaves;
 static_assert(kPlGroups * kPlMembers == kPlBlocks, "a workgroup per CU");

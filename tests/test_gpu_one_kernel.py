@@ -136,7 +136,7 @@ def test_waits_given_up(d, B, k, S, lo, hi, opts):
         got = gh.gpu_verify(ses, case)
         times.append(sd.specdec_profile_read(ses.ctx)[0])
         if give_up and B * (k + 1) > (63 if d == 512 else 128):
-            assert times[-1] > 50, times       # per XCD: a workgroup is missing, and waits last as long as the header says
+            assert times[-1] > 100, times      # per XCD: a workgroup is missing, and waits last the 0.1 s the header says
         for key in ("logits", "accept", "next", "stats"):
             assert np.array_equal(got[key], want[key]), (give_up, key)
         for x, y in zip(gh.gpu_cache(ses, case, L), cache):
