@@ -132,6 +132,7 @@ struct PlLds {
   float stat[kFlips][2 * kRows];                  // {rstd, -mean rstd} of the rows, beside red
   bf16 q[16 * kPlQPitch];                         // queries of the workgroup's unit (cross-attention)
   unsigned long long layers[kPlLayers * sizeof(PlLayer) / 8];   // every stage's pointers
+  unsigned raised;                                // (of the first wave's look at the flag)
   // attention: partial results in the first half of red, the value tiles of the waves ([32 keys][64], swizzled like the tile
   // kernel's) in the second
   static_assert(kFlips * NP >= 8, "attention's share of red");
@@ -679,7 +680,11 @@ __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decod
   // kind of item and its weights are on their way long before the rows are
   const int NB = TICKETS ? a.NB : gridDim.x;
   int w = blockIdx.x;
-  if ((__hip_atomic_load(a.raised, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) != TICKETS) return;
+  // Without tickets one look for all waves: others may raise the flag meanwhile, and a wave that goes on needs what every other one
+  // has put into L.layers.  (With them nothing else writes it until every workgroup has drawn a ticket.)
+  unsigned raised = 0;
+  if (TICKETS || threadIdx.x == 0) raised = __hip_atomic_load(a.raised, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (TICKETS && raised == 0u) return;
   {
     const int words = a.n_layers * (int)(sizeof(PlLayer) / 8);
     for (int i = threadIdx.x; i < words; i += (64 * NW)) L.layers[i] = reinterpret_cast<const unsigned long long*>(a.layers)[i];
@@ -694,7 +699,9 @@ __global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decod
     }
   };
   if (!TICKETS) take_units();
+  if (!TICKETS && threadIdx.x == 0) L.raised = raised;
   __syncthreads();
+  if (!TICKETS && __builtin_amdgcn_readfirstlane(L.raised) != 0u) return;
   int flip = 0;
   auto turn = [&]() { return Lds::kFlips == 1 ? 0 : flip ^= 1; };
   const int RT = (a.R + 16 * MR - 1) / (16 * MR);
