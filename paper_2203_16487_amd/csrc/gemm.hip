@@ -508,17 +508,18 @@ struct EpiLnQkvAppend {
   }
 };
 
-template <class Cfg, int VEC>
-constexpr int ln_smem_bytes() { return Cfg::kSmemBytes + (2 * Cfg::kBM + VEC * Cfg::kBN) * 4; }
+template <int VEC>
+constexpr int ln_smem_bytes() { return CfgSmall::kSmemBytes + (2 * CfgSmall::kBM + VEC * CfgSmall::kBN) * 4; }
 
 // PAIRS: 32 chunks of 64 columns are the most there can be (d <= 2048); with 32 columns, for d > 1024, up to 64.  They are held in
 // registers through the main loop, so the kernel that has room for 64 is for those rows only.
-template <class Cfg, class Epi, int PAIRS>
-__global__ __launch_bounds__(Cfg::kThreads) void gemm_ln_kernel(const bf16* __restrict__ A, int lda,
+template <class Epi, int PAIRS>
+__global__ __launch_bounds__(CfgSmall::kThreads) void gemm_ln_kernel(const bf16* __restrict__ A, int lda,
                                                                 const bf16* __restrict__ W, int ldw,
                                                                 int M, int N, int K, int MT, int NT,
                                                                 Epi epi, const int* __restrict__ m_real) {
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+  typedef CfgSmall Cfg;
   static_assert(Cfg::kSmemBytes >= Cfg::kBM * Cfg::kBN * 4, "staging tile must fit in the ring");
   static_assert(Cfg::kThreads >= Epi::kVec * Cfg::kBN / 4, "one thread per 4 entries of the column vectors");
   float* rowstat = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Cfg::kSmemBytes);   // [BM][2]
@@ -573,18 +574,19 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ln_kernel(const bf16* __re
   }
 }
 
-template <class Cfg, int PAIRS = 32, class Epi>
-static hipError_t launch_ln_cfg(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K,
+template <int PAIRS = 32, class Epi>
+static hipError_t launch_ln_small(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K,
                                 const Epi& epi, const int* m_real) {
   if constexpr (PAIRS < 64) {
-    if (epi.chunks > PAIRS) return launch_ln_cfg<Cfg, 64>(st, A, lda, W, M, N, K, epi, m_real);
+    if (epi.chunks > PAIRS) return launch_ln_small<64>(st, A, lda, W, M, N, K, epi, m_real);
   }
-  constexpr int kBytes = ln_smem_bytes<Cfg, Epi::kVec>();
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ln_kernel<Cfg, Epi, PAIRS>),
+  typedef CfgSmall Cfg;
+  constexpr int kBytes = ln_smem_bytes<Epi::kVec>();
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ln_kernel<Epi, PAIRS>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
   if (attr != hipSuccess) return attr;
   const int MT = (M + Cfg::kBM - 1) / Cfg::kBM, NT = (N + Cfg::kBN - 1) / Cfg::kBN;
-  SD_LAUNCH_TIMED((gemm_ln_kernel<Cfg, Epi, PAIRS>), dim3(xcd_grid(MT, NT)), dim3(Cfg::kThreads), kBytes, st,
+  SD_LAUNCH_TIMED((gemm_ln_kernel<Epi, PAIRS>), dim3(xcd_grid(MT, NT)), dim3(Cfg::kThreads), kBytes, st,
                      A, lda, W, K, M, N, K, MT, NT, epi, m_real);
   return hipGetLastError();
 }
@@ -1241,7 +1243,7 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeig
   //   147 / 72.2 / 62.5 / 66.0;  16384 x 512 x 512 (512) 26.6 / 20.1 / 16.1 / 15.1
   // (512 of a sum: 256 x 128, with 9216 of 16384 rows in use x 512 x 2048 37.9 against 43.5, x 512 x 512 19.6 / 20.4)
   const long wide_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
-  if (epi.chunks > 32) return launch_ln_cfg<CfgSmall>(st, A, lda, W, M, N, K, epi, m_real);   // (sums of so many rows come in fewer chunks)
+  if (epi.chunks > 32) return launch_ln_small(st, A, lda, W, M, N, K, epi, m_real);   // (sums of so many rows come in fewer chunks)
   if (wide_tiles > 512 || (wide_tiles == 512 && !(Epi::kVec == 3 && one_round(M, N, 256, 128)))) {
     bool stream = false;
     if constexpr (Epi::kVec == 2) stream = K % 128 == 0 && K >= 256 && epi.chunks <= StreamTiles<Epi>::kPairs && !one_round(M, N, 256, 256);
@@ -1258,7 +1260,7 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeig
     return launch_tile<CfgWide>(st, A, lda, W, M, N, K, epi, m_real);
   }
   if (wide_tiles > 128) return launch_tile<CfgDeep>(st, A, lda, W, M, N, K, epi, m_real);
-  return launch_ln_cfg<CfgSmall>(st, A, lda, W, M, N, K, epi, m_real);
+  return launch_ln_small(st, A, lda, W, M, N, K, epi, m_real);
 }
 
 int ln_sum_chunks(int M, int d) { return one_round(M, d, 32, 32) ? d / 32 : d / 64; }

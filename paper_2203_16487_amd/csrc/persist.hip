@@ -670,7 +670,7 @@ constexpr size_t kPlTicketBytes = (sizeof(PlTickets) + 255) & ~size_t(255);
 // MR: row tiles of an item.  FBW: column tiles of an item of the wide projections (QKV, first FFN matrix).
 // TICKETS: see the head of this file; a.NB virtual workgroups, the residual in memory instead of LDS (MR = 1).
 template <class WT, bool KV8, int NW, int KSD, int KSF, int MR, int FBW, bool TICKETS>
-__global__ __launch_bounds__((64 * NW), MR > 1 && NW == 4 ? 1 : 2) void pl_decoder_kernel(PlArgs a) {
+__global__ __launch_bounds__((64 * NW), 2) void pl_decoder_kernel(PlArgs a) {
   extern __shared__ __attribute__((aligned(16))) char pl_smem[];
   typedef PlLds<NW, (MR > 1 ? MR * FBW : 4)> Lds;
   static_assert(Lds::kRows == 16 * MR, "residual tile");

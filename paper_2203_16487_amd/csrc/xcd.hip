@@ -180,7 +180,7 @@ template <class Dim>
 __device__ __forceinline__ int pl_chunks(int s) {
   return s == 0 ? Dim::kTQ : s == 6 ? Dim::kTF : s == 7 ? Dim::kTD * Dim::kKC : s == 1 || s == 4 ? 0 : Dim::kTD;
 }
-// Attention of a group: waves of a unit (PlArgs::wpu), units of a workgroup at a time, rounds.
+// Attention of a group: waves of a unit (XcdArgs::wpu), units of a workgroup at a time, rounds.
 __device__ __forceinline__ int pl_units(const XcdArgs& a, const PlPlace& p) { return p.nb * a.H * ((a.T + 15) >> 4); }
 __device__ __forceinline__ int pl_rounds(const XcdArgs& a, const PlPlace& p) {
   const int per = kPlMembers * (kPlWaves / a.wpu);
@@ -753,7 +753,7 @@ __device__ __forceinline__ void pl_attn_wave(const XcdArgs& a, const PlExch& ex,
   mfma_settle(oacc);
 }
 
-// All units of one attention stage: as many waves to a unit as there are (PlArgs::wpu), a power of two.  The waves of a unit take
+// All units of one attention stage: as many waves to a unit as there are (XcdArgs::wpu), a power of two.  The waves of a unit take
 // chunks of 32 keys in turn and merge through LDS.
 struct PlPair { int b, h, q0; };   // sequence of the group, head, first query
 __device__ __forceinline__ PlPair pl_pair(const XcdArgs& a, const PlPlace& p, int r, int wave) {
@@ -1060,7 +1060,9 @@ template <bool KV8, int D>
 static hipError_t pl_launch_both(hipStream_t st, XcdArgs a, int blocks) {
   hipError_t e = hipErrorInvalidValue;
   switch (a.RP / 16) {
-    case 1: e = pl_launch<KV8, D, 1, false>(st, a, blocks); break;
+    case 1:   // (128 rows at most: with d = 1024 the decoder over the whole GPU takes them)
+      if constexpr (D == 512) e = pl_launch<KV8, D, 1, false>(st, a, blocks);
+      break;
     case 2: e = pl_launch<KV8, D, 2, false>(st, a, blocks); break;
     case 3: e = pl_launch<KV8, D, 3, false>(st, a, blocks); break;
     case 4: e = pl_launch<KV8, D, 4, false>(st, a, blocks); break;
