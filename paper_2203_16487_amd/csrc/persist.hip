@@ -31,37 +31,20 @@
 // the same bits.  The flag counts the passes that go to it directly (kPlTicketPasses, this one included) before one waits again.
 // A whole verify pass with the second launch returning at once and without it: 125.3 / 124.8 us (d = 512, 6 rows),
 // 380.2 / 378.0 (d = 1024, 128 rows); by tickets 0.51 and 2.7 ms.
-#include "attn_core.h"
+#include "resident_core.h"
 
 namespace sd {
 
-constexpr unsigned kPoison = 0xffffffffu;
 constexpr unsigned kPlSpinMax = 1u << 17;   // (0.1 - 0.2 s)
 constexpr unsigned kPlTicketSpinMax = 1u << 24;
 constexpr int kPlTicketBlocks = 64;
 constexpr unsigned kPlTicketPasses = 64;    // (a wait in vain then costs 2 - 3 ms a pass)
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-// Coherent 16-byte load (device scope: past the L1 and this XCD's L2): the buffer form with sc1.  (An inline-asm load would
-// leave the compiler free to copy its result before it has arrived.)
-typedef __amdgpu_buffer_rsrc_t PlBuf;
-__device__ __forceinline__ PlBuf pl_buf(const void* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffff, 0x00027000); }
-constexpr int kPlSc1 = 16;
-__device__ __forceinline__ u32x4 pl_request(PlBuf b, int voff, int soff) { return __builtin_amdgcn_raw_buffer_load_b128(b, voff, soff, kPlSc1); }
 __device__ __forceinline__ bool pl_missing(const u32x4& v) {
   return v[0] == kPoison || v[1] == kPoison || v[2] == kPoison || v[3] == kPoison;
 }
-__device__ __forceinline__ unsigned not_poison(unsigned u) { return u == kPoison ? 0x7fc07fc0u : u; }   // (a NaN for a NaN)
 __device__ __forceinline__ void pl_store8(void* p, unsigned a, unsigned b) {
   u32x2 v = {not_poison(a), not_poison(b)};
   asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory");
-}
-__device__ __forceinline__ u32x2 pl_pack4(const float (&v)[4]) {
-  bf16x4 t;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) t[i] = (bf16)v[i];
-  return __builtin_bit_cast(u32x2, t);
 }
 
 // One more round of a wait: false once the pass is to be abandoned.
@@ -78,18 +61,10 @@ __device__ __forceinline__ bool pl_again(unsigned& spins, const PlArgs& a) {
   return true;
 }
 
-// sums over the four 16-lane rows (lanes lq + 16 g), result in all of them
-__device__ __forceinline__ float pl_row_sum(float v) {
-  const unsigned u = __builtin_bit_cast(unsigned, v);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return half_add(__builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]));
-}
-
 struct PlStat { float rstd, nmr; };
 // mean and rstd of row lq from its chunk pairs of 16 columns; this lane holds NS of them
 template <int NS>
 __device__ __forceinline__ PlStat pl_stat(const u32x2 (&pairs)[NS], int d) {
-  typedef float f32x2 __attribute__((ext_vector_type(2)));
   f32x2 p[NS];
   float s = 0.f;
 #pragma unroll
@@ -108,13 +83,6 @@ __device__ __forceinline__ PlStat pl_stat(const u32x2 (&pairs)[NS], int d) {
   return PlStat{rstd, -mean * rstd};
 }
 
-// The lane, as a value the compiler cannot carry over from an earlier stage: otherwise every stage's addresses are computed
-// ahead of the layer loop and held (or spilled) throughout.
-__device__ __forceinline__ int pl_lane() {
-  int t = threadIdx.x & 63;
-  asm volatile("" : "+v"(t));
-  return t;
-}
 __device__ __forceinline__ int pl_opaque(int v) {
   asm volatile("" : "+s"(v));
   return v;
@@ -140,29 +108,6 @@ struct PlLds {
   __device__ __forceinline__ float* ml() { return reinterpret_cast<float*>(red[0] + NW * 4 * 64); }
   __device__ __forceinline__ bf16* vs(int wave) { return reinterpret_cast<bf16*>(red[0] + NW * 4 * 64) + wave * (32 * 64); }
 };
-
-// Exchange buffers of one layer, all in tiles of 16 columns, [column / 16][RP][16]: what one item produces lies together and
-// shares no line with another workgroup's stores (with rows of all columns side by side the 8- and 32-byte pieces of up to 16
-// workgroups met in every line, and a residual sum took 3 us to become visible instead of 1).  Statistics likewise
-// [chunk][RP] pairs.
-__host__ __device__ inline size_t pl_layer_bytes(int RP, int d, int F) {
-  return (size_t)RP * (3 * (2 * d + d / 2) + 6 * 2 * d + 2 * F);
-}
-struct PlExch {   // (only the layer's base stays in registers)
-  char* base;
-  int row;        // bytes of a buffer of RP rows of d
-  __device__ __forceinline__ PlExch(char* exch, int l, int RP, int d, int F)
-      : base(exch + (size_t)l * pl_layer_bytes(RP, d, F)), row(RP * 2 * d) {}
-  __device__ __forceinline__ char* xg(int i) const { return base + i * row; }
-  __device__ __forceinline__ char* q(int i) const { return base + (3 + i) * row; }
-  __device__ __forceinline__ char* kx() const { return base + 5 * row; }
-  __device__ __forceinline__ char* vx() const { return base + 6 * row; }
-  __device__ __forceinline__ char* att(int i) const { return base + (7 + i) * row; }
-  __device__ __forceinline__ char* st(int i) const { return base + 9 * row + i * (row >> 2); }
-  __device__ __forceinline__ char* hid() const { return base + 9 * row + 3 * (row >> 2); }
-};
-// element (row, k) of a buffer, bytes
-__device__ __forceinline__ int pl_at(int RP, int row, int k) { return ((k >> 4) * RP + row) * 32 + (k & 15) * 2; }
 
 // Product of one item: rows row0 .. row0 + 16 MR - 1 below rlim of A (exchange buffer, or plain rows), columns n0 .. n0 +
 // 16 FB - 1 of W [N][32 * NW * KS].  done(mr, f, v, s) receives the finished sums of row row0 + 16 mr + lane % 16, columns
@@ -363,11 +308,6 @@ __device__ __forceinline__ bool pl_sum(const PlArgs& a, Lds& L, int flip, float*
   });
 }
 
-// Attention of one unit: 16 queries (the last ones of a sequence: fewer) of one (sequence, head) pair.  at: the keys its
-// queries see.
-struct PlUnit {
-  int b, h, q0, j, nkey;   // sequence, head, first query; keys cached before the pass (self-attention), all keys
-};
 template <bool SELF>
 __device__ __forceinline__ PlUnit pl_unit(const PlArgs& a, int u) {
   const int tiles = (a.T + 15) >> 4, pair = u / tiles;
@@ -377,8 +317,6 @@ __device__ __forceinline__ PlUnit pl_unit(const PlArgs& a, int u) {
   t.nkey = SELF ? t.j + min(a.T, t.q0 + 16) : a.src_len[t.b];
   return t;
 }
-// 1 / sqrt(64) and log2(e) meet the scores in the exponent.
-constexpr float kCexp = 0.125f * 1.44269504088896341f;
 
 // Key chunks kw, kw + kstep, ... of 32 on this wave (see attn_core.h for the operand layouts).  SELF: keys / values below the
 // pass's first row come from the cache, the pass's own from the exchange buffers (waited for); else the cross-attention arenas.
@@ -404,15 +342,11 @@ __device__ __forceinline__ bool pl_attn_wave(const PlArgs& a, const PlExch& ex, 
   // K operands: tile i, row lq  <->  key c0 + 8*(lq/4) + 4*i + lq%4; values as whole rows (lane -> row 8*i + lane/8, dims
   // 8*(lane%8) .. + 7) or, key-blocked, as operands.  What the cache holds is requested once, the pass's own rows until they
   // are there.
-  struct Chunk {   // (one of the two forms)
-    u32x4 kf[4], vf[4];
-    fp8x8 kf8[4], vf8[4];
-    f32x4 sck[2], scv[2];
-  } now, next;
+  PlChunk now, next;
   u32x4 f[2];
   auto key_k = [&](int c0, int i) { return c0 + 8 * (lq >> 2) + 4 * i + (lq & 3); };
   auto key_v = [&](int c0, int i) { return c0 + 8 * i + (lane >> 3); };
-  auto fetch = [&](int c0, Chunk& t) {
+  auto fetch = [&](int c0, PlChunk& t) {
     const int last = (SELF ? j : nkey) - 1;
     if (SELF && c0 > last) return;
     if constexpr (KV8) {
@@ -735,7 +669,7 @@ __global__ __launch_bounds__((64 * NW), 2) void pl_decoder_kernel(PlArgs a) {
   auto stage = [&](int s, int l) __attribute__((always_inline)) -> bool {
     const int wa = units <= NB ? w - a.att0 : w;
     const PlLayer& Y = reinterpret_cast<const PlLayer*>(L.layers)[l];
-    const PlExch ex(a.exch, l, a.RP, d, F), before(a.exch, l - 1, a.RP, d, F);
+    const PlExch ex(a.exch + (size_t)l * pl_layer_bytes(a.RP, d, F), a.RP, d), before(a.exch + (size_t)(l - 1) * pl_layer_bytes(a.RP, d, F), a.RP, d);
     const bool top = l == 0;
     const char* st0 = top ? nullptr : before.st(2);
     switch (s) {

@@ -41,41 +41,22 @@
 // given up.)
 #include <algorithm>
 
-#include "attn_core.h"
 #include "gemm_core.h"
+#include "resident_core.h"
 
 namespace sd {
 namespace xcd {
 
-constexpr unsigned kPoison = 0xffffffffu;
 constexpr unsigned kPlSpinMax = 3u << 18;   // (0.13 - 0.17 s: 2^17 polls of the L2 take 21 - 28 ms)
 constexpr int kPlGroups = 8, kPlMembers = 32;          // XCDs; workgroups of each
 constexpr int kPlWaves = 8, kPlThreads = 64 * kPlWaves;
 static_assert(kPlGroups * kPlMembers == kPlBlocks, "a workgroup per CU");
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-// Coherent 16-byte load (past the L1): the buffer form with sc1.  (An inline-asm load would
-// leave the compiler free to copy its result before it has arrived.)
-typedef __amdgpu_buffer_rsrc_t PlBuf;
-__device__ __forceinline__ PlBuf pl_buf(const void* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffff, 0x00027000); }
-constexpr int kPlSc1 = 16;
-__device__ __forceinline__ u32x4 pl_request(PlBuf b, int voff, int soff) { return __builtin_amdgcn_raw_buffer_load_b128(b, voff, soff, kPlSc1); }
 // (a word of each 8 bytes: results are stored 8 bytes at a time)
 __device__ __forceinline__ bool pl_missing(const u32x4& v) { return v[1] == kPoison || v[3] == kPoison; }
-__device__ __forceinline__ unsigned not_poison(unsigned u) { return u == kPoison ? 0x7fc07fc0u : u; }   // (a NaN for a NaN)
 __device__ __forceinline__ void pl_store8(void* p, unsigned a, unsigned b) {
   u32x2 v = {not_poison(a), not_poison(b)};
   asm volatile("global_store_dwordx2 %0, %1, off sc0" ::"v"(p), "v"(v) : "memory");
 }
-__device__ __forceinline__ u32x2 pl_pack4(const float (&v)[4]) {
-  bf16x4 t;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) t[i] = (bf16)v[i];
-  return __builtin_bit_cast(u32x2, t);
-}
-
 // One more round of a wait; ends the wave once the pass is to be abandoned.  (The end of the wave, not a result that every caller
 // hands on: with one, the rows a wave holds were copied at every join of the ways, and spilled.)
 __device__ __forceinline__ void pl_again(unsigned& spins, const XcdArgs& a) {
@@ -91,21 +72,6 @@ __device__ __forceinline__ void pl_again(unsigned& spins, const XcdArgs& a) {
   }
   __builtin_amdgcn_s_sleep(1);
   asm volatile("" ::: "memory");
-}
-
-// sums over the four 16-lane rows (lanes lq + 16 g), result in all of them
-__device__ __forceinline__ float pl_row_sum(float v) {
-  const unsigned u = __builtin_bit_cast(unsigned, v);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return half_add(__builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]));
-}
-
-// The lane, as a value the compiler cannot carry over from an earlier stage: otherwise every stage's addresses are computed
-// ahead of the layer loop and held (or spilled) throughout.
-__device__ __forceinline__ int pl_lane() {
-  int t = threadIdx.x & 63;
-  asm volatile("" : "+v"(t));
-  return t;
 }
 
 constexpr int kPlRows = 64;   // rows of a group
@@ -142,26 +108,6 @@ struct PlLds {
   int row_at[kPlRows], row_pos[kPlRows], src_len[kPlRows];   // row_at: of the row in the self-attention cache of head 0 (< 0: none)
   __device__ __forceinline__ bf16* vs(int wave) { return reinterpret_cast<bf16*>(red + wave * 256); }
 };
-
-// Exchange buffers of one layer and group, all in tiles of 16 columns, [column / 16][RP][16]: what one workgroup produces lies
-// together.  Statistics likewise, [chunk][RP] pairs.
-__host__ __device__ inline size_t pl_layer_bytes(int RP, int d, int F) {
-  return (size_t)RP * (3 * (2 * d + d / 2) + 6 * 2 * d + 2 * F);
-}
-struct PlExch {   // (only the layer's base stays in registers)
-  char* base;
-  int row;        // bytes of a buffer of RP rows of d
-  __device__ __forceinline__ PlExch(char* b, int RP, int d) : base(b), row(RP * 2 * d) {}
-  __device__ __forceinline__ char* xg(int i) const { return base + i * row; }
-  __device__ __forceinline__ char* q(int i) const { return base + (3 + i) * row; }
-  __device__ __forceinline__ char* kx() const { return base + 5 * row; }
-  __device__ __forceinline__ char* vx() const { return base + 6 * row; }
-  __device__ __forceinline__ char* att(int i) const { return base + (7 + i) * row; }
-  __device__ __forceinline__ char* st(int i) const { return base + 9 * row + i * (row >> 2); }
-  __device__ __forceinline__ char* hid() const { return base + 9 * row + 3 * (row >> 2); }
-};
-// element (row, k) of a buffer, bytes
-__device__ __forceinline__ int pl_at(int RP, int row, int k) { return ((k >> 4) * RP + row) * 32 + (k & 15) * 2; }
 
 // A workgroup's place: group g carries sequences b0 .. b0 + nb - 1, rows row0 .. row0 + rows - 1 of the pass.
 struct PlPlace { int g, w, b0, nb, row0, rows; };
@@ -539,13 +485,6 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
   }
 }
 
-// Attention of one unit: 16 queries (the last ones of a sequence: fewer) of one (sequence, head) pair.
-struct PlUnit {
-  int b, h, q0, j, nkey;   // sequence of the group, head, first query; keys cached before the pass (self-attention), all keys
-};
-// 1 / sqrt(64) and log2(e) meet the scores in the exponent.
-constexpr float kCexp = 0.125f * 1.44269504088896341f;
-
 // Key chunks kw, kw + kstep, ... of 32 on this wave (see attn_core.h for the operand layouts).  SELF: keys / values below the
 // pass's first row come from the cache, the pass's own from the exchange buffers (waited for); else the cross-attention arenas.
 // KV8 (cross): codes with one fp32 scale per key and per value, as in attn_core.h.
@@ -567,15 +506,11 @@ __device__ __forceinline__ void pl_attn_wave(const XcdArgs& a, const PlExch& ex,
   for (int et = 0; et < 4; ++et) oacc[et] = f32x4{0.f, 0.f, 0.f, 0.f};
   // K operands: tile i, row lq  <->  key c0 + 8*(lq/4) + 4*i + lq%4; values as whole rows (lane -> row 8*i + lane/8, dims
   // 8*(lane%8) .. + 7) or, key-blocked, as operands.  A chunk without rows of the pass is requested ahead.
-  struct Chunk {   // (one of the two forms)
-    u32x4 kf[4], vf[4];
-    fp8x8 kf8[4], vf8[4];
-    f32x4 sck[2], scv[2];
-  } now, next;
+  PlChunk now, next;
   u32x4 f[2];
   auto key_k = [&](int c0, int i) { return c0 + 8 * (lq >> 2) + 4 * i + (lq & 3); };
   auto key_v = [&](int c0, int i) { return c0 + 8 * i + (lane >> 3); };
-  auto fetch = [&](int c0, Chunk& t) {
+  auto fetch = [&](int c0, PlChunk& t) {
     const int last = (SELF ? j : nkey) - 1;
     if constexpr (KV8) {
       const int k8 = min(c0 + 8 * g, cap - 8);
@@ -607,7 +542,7 @@ __device__ __forceinline__ void pl_attn_wave(const XcdArgs& a, const PlExch& ex,
   unsigned spins = 0;
   // a chunk with rows of the pass: every lane's keys and values from the cache or the exchange buffers, and the queries, until all
   // are there.  (One statement: its results are valid behind its wait.)
-  auto own = [&](int c0, Chunk& t_) {
+  auto own = [&](int c0, PlChunk& t_) {
     const char *pk[4], *pv[4], *pq[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
