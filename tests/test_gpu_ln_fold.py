@@ -36,7 +36,11 @@ def ses_launches(ses, run):
 SHIFT, BOUND = 4.0, 1.1
 
 
-@pytest.mark.parametrize("d,B,k", [(512, 1, 25), (1024, 1, 9), (512, 12, 10), (512, 30, 10)])   # one kernel, 16 and 32 rows an item; launches
+@pytest.mark.parametrize("d,B,k", [
+    (512, 1, 25), (1024, 1, 9), (1024, 9, 8),       # one kernel over the whole GPU; the last on items of 32 rows
+    (512, 12, 10), (512, 30, 10), (1024, 17, 8),    # one kernel, per XCD: two and three row tiles
+    (512, 48, 10),                                  # 528 rows: launches
+])
 def test_verify_of_rows_off_zero(d, B, k):
     desc = synth.ModelDesc(0, 2, d, d // 64, 4 * d, 1003, 64, 64).resolved()
     err = []
