@@ -111,7 +111,7 @@ typedef enum {
                                           out += (p * v_scale) * codes.  Changes the model like FP8_WEIGHTS does;
                                           the two options are independent.  Refused by RESIDENT / SLICED_SUBLAYERS. */
   SPECDEC_OPT_WIDE_VOCAB_TILES = 6,    /* default 0: the vocabulary projection of a pass of more than 32 rows takes
-                                          its 256 x 256 tiles only where they give every compute unit two or more
+                                          its 256 x 256 tiles only where they give every compute unit one or more
                                           (the batched passes), else 128 x 128 tiles.  1: 256 x 256 tiles in every
                                           such pass (so that the wide kernel can be checked on small shapes).     */
   SPECDEC_OPT_GIVE_UP_WAITS = 7        /* default 0.  1: every wait of the one-kernel decoder that does not end at once is
@@ -240,7 +240,8 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * kernel of another stream or process keeps some of them from starting for 0.1 s or more, the waits
  * are given up and a second kernel, which needs no more than one free compute unit, computes
  * the pass instead (same bits, 0.5 - 3 ms; in groups 7 - 14); so it does the run's next 63 (15) passes without
- * waiting first.  One stream of one process at a time runs such passes on a
+ * waiting first.  (SPECDEC_OPT_SMALL_BATCH_KERNELS = 0: separate launches, which share a GPU freely.)
+ * One stream of one process at a time runs such passes on a
  * GPU: that of the first context to ask, until it and the others on its stream are destroyed (a
  * context that captures one: until it is destroyed, whatever the stream).  A context on another
  * stream or in another process runs its passes as separate launches, from the first pass refused to its

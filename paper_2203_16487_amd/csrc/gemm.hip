@@ -905,10 +905,11 @@ static hipError_t launch_stream(hipStream_t st, const bf16* A, int lda, const bf
 }
 
 // 256 x 256 tiles or 128 x 128 ones?  Time of a full round of blocks (256 and 512) as measured over K = 512 .. 4096, us:
-// 10.5 + 1.73 and 3.6 + 1.12 per 64 columns of K; 8.2 + 1.38 where a block takes tile after tile (stream); a last round costs nearly a full one on one block per CU, and on two the
-// better part of one as soon as some CU has a second block.  (Sums of K = 512 take twice as long on both.)  Of twelve row counts from
-// 352 to 32768 and nine (N, K) of the two models, the choice was at most 3 % slower than the better of the two wherever it is
-// made.  Where M only bounds the rows in use (bound), the sum over half, three quarters and all of it decides.
+// 10.5 + 1.73 and 3.6 + 1.12 per 64 columns of K; 8.2 + 1.38 where a block takes tile after tile (stream); a last round costs nearly a full one
+// on one block per CU, and on two the better part of one as soon as some CU has a second block.  (Sums of K = 512 take twice as long on both.
+// A streamed last round that is at most half full is charged in full, too, though gemm_stream_kernel computes it as tiles of half the width:
+// the choices were checked before it did.)  Of twelve row counts from 352 to 32768 and nine (N, K) of the two models, the choice was at most
+// 3 % slower than the better of the two wherever it is made.  Where M only bounds the rows in use (bound), the sum over half, three quarters and all of it decides.
 static float square_minus_wide(int M, int N, int K, bool stream) {
   const float kt = K / 64.f;
   const long sq = (long)((M + 255) / 256) * ((N + 255) / 256), wd = (long)((M + 127) / 128) * ((N + 127) / 128);
@@ -1241,7 +1242,8 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeig
   //   14.0 / 12.4 / 15.9 / 13.7;  4096 x 1024 x 1024 (256) 24.0 / 14.0 / 17.3 / 14.0;  2816 x 1024 x 4096 + (176) 56.3 / 35.2 / 48.5 / 49.3
   //   2816 x 1536 x 512 (264) 13.9 / 16.4 / 11.6 / 12.9;  9216 x 512 x 512 + (288) 24.4 / 22.9 / 17.6 / 18.4;  7168 x 1024 x 4096 + (448)
   //   147 / 72.2 / 62.5 / 66.0;  16384 x 512 x 512 (512) 26.6 / 20.1 / 16.1 / 15.1
-  // (512 of a sum: 256 x 128, with 9216 of 16384 rows in use x 512 x 2048 37.9 against 43.5, x 512 x 512 19.6 / 20.4)
+  // (512 of a sum, where 256 x 128 is exactly one round: that.  x 512 x 2048 and x 512 x 512, mean, against 128 x 128: 9216 of 16384 rows
+  // in use 28.7 / 31.6, all of a bound 35.3 / 36.8, 16384 without one 31.0 / 32.1)
   const long wide_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
   if (epi.chunks > 32) return launch_ln_small(st, A, lda, W, M, N, K, epi, m_real);   // (sums of so many rows come in fewer chunks)
   if (wide_tiles > 512 || (wide_tiles == 512 && !(Epi::kVec == 3 && one_round(M, N, 256, 128)))) {
