@@ -59,7 +59,8 @@ __device__ __forceinline__ void pl_store8(void* p, unsigned a, unsigned b) {
   asm volatile("global_store_dwordx2 %0, %1, off sc0" ::"v"(p), "v"(v) : "memory");
 }
 // One more round of a wait; ends the wave once the pass is to be abandoned.  (The end of the wave, not a result that every caller
-// hands on: with one, the rows a wave holds were copied at every join of the ways, and spilled.)
+// hands on: with one, the rows a wave holds were copied at every join of the ways, and spilled.  And as an instruction like any other: the
+// builtin is an end of the program's ways, and the others then came with a dozen flags at every wait.)
 __device__ __forceinline__ void pl_again(unsigned& spins, const XcdArgs& a) {
   ++spins;
   if ((spins & 63u) == 0) {
@@ -67,8 +68,8 @@ __device__ __forceinline__ void pl_again(unsigned& spins, const XcdArgs& a) {
     const unsigned raised = __builtin_amdgcn_readfirstlane(__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     if (raised != 0u || spins > kPlSpinMax) {
       __hip_atomic_store(a.err, kXcdAlonePasses, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (weights on their way to LDS: it may be another workgroup's next)
-      __builtin_amdgcn_endpgm();
+      // (weights on their way to LDS: it may be another workgroup's next)
+      asm volatile("s_waitcnt vmcnt(0)\n\ts_endpgm" ::: "memory");
     }
   }
   __builtin_amdgcn_s_sleep(1);
@@ -778,6 +779,8 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
   typedef PlDim<D> Dim;
   static_assert(sizeof(Lds) <= 160 * 1024, "LDS of a CU");
   Lds& L = *reinterpret_cast<Lds*>(pl_smem);
+  if (!ALONE) a.RP = 16 * MR;   // known when compiled: every place in the exchange buffers is then a constant away from the layer's
+  a.H = D / kHeadDim;
   // (one look for all waves: others may raise the flag meanwhile, and none of a workgroup's waves is to go on without the rest)
   if (threadIdx.x == 0) L.row_at[0] = (int)__hip_atomic_load(a.raised, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
@@ -800,6 +803,11 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
   PlPair mine = pl_pair(a, at, 0, wave);
   // stage s of layer l
   auto stage = [&](int s, int l) __attribute__((always_inline)) {
+    // What follows from the layer is worked out where it is used.  Ahead of the layer's stages, where the compiler would have it, it does not fit
+    // the scalar registers and goes through lanes of vector ones: with the builtin in pl_again and the row pitch of the buffers as an argument
+    // a wave issued 500 instructions a stage, half of them scalar.  Whole verify passes, us, with all that / without: d = 512, 77 rows
+    // 149.3 / 133.9, 352 rows 198.4 / 188.9; d = 1024, 352 rows of long sources 544 / 530, 209 rows 422 / 408.
+    asm volatile("" : "+s"(l));
     const PlExch ex(a.exch + (at.g * 2 + (l & 1)) * pl_layer_bytes(a.RP, D, 4 * D), a.RP, D);
     const PlExch before(a.exch + (at.g * 2 + (~l & 1)) * pl_layer_bytes(a.RP, D, 4 * D), a.RP, D);
     const float* vec = L.vec[l & 1];
@@ -890,9 +898,9 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     pl_ask<D, MR>(L, turn, wave, Dim::kRing);
     wait_vmcnt<Dim::kRing * Dim::kReq>();   // the vectors
     __syncthreads();
-    for (int l = 0; l < a.n_layers; ++l)
-      for (int s = 0; s < kPlStages; ++s)
-        stage(s, l);
+    for (int l = 0; l < a.n_layers; ++l) {
+      stage(0, l); stage(1, l); stage(2, l); stage(3, l); stage(4, l); stage(5, l); stage(6, l); stage(7, l);
+    }
   } else {
     // the residual: embedded rows (those beyond the group's: read, never used).  All of them, and there, ahead of the stages: a wave without
     // a tile to sum reads another's (pl_reduce), and a copy it made then could overtake that one's result.
