@@ -379,6 +379,8 @@ __device__ __forceinline__ void pl_project(const XcdArgs& a, PlLds<D, MR>& L, Pl
     if constexpr (NT > 3) tile(std::integral_constant<int, (CT + 3 < Dim::kRing ? -1 : R1 > 3 ? R1 - 3 : 0)>{}, 3);
     static_assert(NT <= 4 && NT <= Dim::kRing, "a batch");
     struct Have { f32x4 c, b; };
+    // (ahead of the sum, so that the next stage's rows are waited for behind less of it: 352 rows of d = 512 188.9 -> 186.7 us)
+    pl_ask<D, MR>(L, t, wave, NT);
     pl_reduce<D, MR, NT>(L, t, wave, lane, acc,
       [&](int i, int) {
         const float* v = cs + (CT + i) * 16 + 4 * g;
@@ -398,7 +400,6 @@ __device__ __forceinline__ void pl_project(const XcdArgs& a, PlLds<D, MR>& L, Pl
         for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(v[e], st[0], __builtin_fmaf(st[1], h.c[e], h.b[e]));
         if (row < rows) epi(row, (CT + i) * 16 + 4 * g, o);
       });
-    pl_ask<D, MR>(L, t, wave, NT);
   };
   batch(std::integral_constant<int, 0>{}, std::integral_constant<int, (N < NB ? N : NB)>{});
   if constexpr (N > NB) batch(std::integral_constant<int, NB>{}, std::integral_constant<int, (N - NB < NB ? N - NB : NB)>{});
@@ -457,6 +458,7 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
       }
       if ((ct + 1) % GT != 0) continue;
       struct Have { f32x4 v[3], x; };
+      pl_ask<D, MR>(L, t, wave, KC * TD > Dim::kRing ? GT : ct + 1 == TD ? KC * TD : 0);
       pl_reduce<D, MR, GT>(L, t, wave, lane, acc[ct / GT],
         [&](int i, int mr) {
           const int tile = ct / GT * GT + i;
@@ -476,7 +478,6 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
           *reinterpret_cast<f32x4*>(resid(mr, tile)) = y;
           out(row, tile * 16 + 4 * g, y, gx);
         });
-      pl_ask<D, MR>(L, t, wave, KC * TD > Dim::kRing ? GT : ct + 1 == TD ? KC * TD : 0);
     }
     if (SETS == 1 && kc + 1 < KC) {
       asm volatile("" ::: "memory");   // (not above the products: there is one set of registers)
