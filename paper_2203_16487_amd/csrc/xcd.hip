@@ -219,15 +219,65 @@ struct PlRows {
       for (int u = 0; u < KS; ++u) af[mr][u] = pl_request(buf, off, u * a.RP * 64);
     }
   }
+  // (rows beyond the group's are its last one again)
   __device__ __forceinline__ bool missing(int mr, const u32x4 (&af)[MR][KS]) const {
-    bool bad = false;
+    unsigned m = 0u;
 #pragma unroll
-    for (int u = 0; u < KS; ++u) bad |= pl_missing(af[mr][u]);
-    return __builtin_amdgcn_ballot_w64(bad && 16 * mr + (lane & 15) < rows) != 0;
+    for (int u = 0; u < KS; ++u) m = max(m, max(af[mr][u][1], af[mr][u][3]));
+    return __builtin_amdgcn_ballot_w64(m == kPoison) != 0;
   }
-  // requested before: those that are not there yet, again
-  __device__ __forceinline__ void arrive(int kc, u32x4 (&af)[MR][KS]) const {
-    if (plain) return;
+  struct NoStats {
+    __device__ __forceinline__ void request() const {}
+    __device__ __forceinline__ bool missing() const { return false; }
+  };
+  struct LateStats {   // chunks NS (4 wave + g) .. of the row, as new as the rows
+    const PlRows& R;
+    PlBuf sb;
+    u32x2 (&st)[MR][NS];
+    __device__ __forceinline__ void request() const {
+#pragma unroll
+      for (int mr = 0; mr < MR; ++mr)
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+          st[mr][i] = __builtin_amdgcn_raw_buffer_load_b64(sb, (NS * (4 * R.wave + (R.lane >> 4)) * R.a.RP + min(16 * mr + (R.lane & 15), R.rows - 1)) * 8,
+                                                           i * R.a.RP * 8, kPlSc1);
+    }
+    __device__ __forceinline__ bool missing() const {
+      unsigned m = 0u;
+#pragma unroll
+      for (int mr = 0; mr < MR; ++mr)
+#pragma unroll
+        for (int i = 0; i < NS; ++i) m = max(m, st[mr][i][1]);
+      return __builtin_amdgcn_ballot_w64(m == kPoison) != 0;
+    }
+  };
+  // Requested before: what is not there yet, again, all of it at once.  (A tile after the other, and the statistics behind them, one more round
+  // trip of 0.4 us each: verify pass of 352 rows of d = 512 186.7 us, so 175.0; 209 rows of d = 1024 403 / 393.)
+  template <class Stats = NoStats>
+  __device__ __forceinline__ void arrive(u32x4 (&af)[MR][KS], Stats stats = Stats()) const {
+    if constexpr (MR * KS > 12) {   // (held twice over at the loop's end, such rows do not fit the registers)
+      arrive_later(0, af);
+      for (unsigned spins = 0; stats.missing(); stats.request()) pl_again(spins, a);
+      return;
+    }
+    unsigned spins = 0;
+    while (true) {
+      bool miss[MR], late = stats.missing(), any = late;
+#pragma unroll
+      for (int mr = 0; mr < MR; ++mr) {
+        miss[mr] = missing(mr, af);
+        any |= miss[mr];
+      }
+      if (!any) break;
+      pl_again(spins, a);
+#pragma unroll
+      for (int mr = 0; mr < MR; ++mr)
+        if (miss[mr]) request(mr, 0, af);
+      if (late) stats.request();
+    }
+  }
+  // the same of later columns, a tile after the other (two sets of rows are held)
+  __device__ __forceinline__ void arrive_later(int kc, u32x4 (&af)[MR][KS]) const {
     unsigned spins = 0;
 #pragma unroll
     for (int mr = 0; mr < MR; ++mr)
@@ -241,30 +291,17 @@ struct PlRows {
   __device__ __forceinline__ void first(u32x4 (&af)[MR][KS], const char* stats, float* part) const {
 #pragma unroll
     for (int mr = 0; mr < MR; ++mr) request(mr, 0, af);
+    if (plain) {
+      wait_vmcnt<0>();
+      asm volatile("" ::: "memory");
+      return;
+    }
     if (stats) {
-      const PlBuf sb = pl_buf(stats);
       const int lq = lane & 15, g = lane >> 4;
       u32x2 st[MR][NS];
-      auto stat_request = [&]() {   // chunks NS (4 wave + g) .. of the row
-#pragma unroll
-        for (int mr = 0; mr < MR; ++mr)
-#pragma unroll
-          for (int i = 0; i < NS; ++i)
-            st[mr][i] = __builtin_amdgcn_raw_buffer_load_b64(sb, (NS * (4 * wave + g) * a.RP + min(16 * mr + lq, rows - 1)) * 8, i * a.RP * 8, kPlSc1);
-      };
-      stat_request();
-      arrive(0, af);
-      unsigned spins = 0;
-      while (true) {
-        bool bad = false;
-#pragma unroll
-        for (int mr = 0; mr < MR; ++mr)
-#pragma unroll
-          for (int i = 0; i < NS; ++i) bad |= st[mr][i][1] == kPoison;
-        if (!__builtin_amdgcn_ballot_w64(bad)) break;
-        pl_again(spins, a);
-        stat_request();
-      }
+      const LateStats late{*this, pl_buf(stats), st};
+      late.request();
+      arrive(af, late);
 #pragma unroll
       for (int mr = 0; mr < MR; ++mr) {
         f32x2 p[NS];
@@ -284,11 +321,7 @@ struct PlRows {
         if (g == 0) *reinterpret_cast<f32x2*>(part + 2 * (16 * mr + lq)) = f32x2{s, q};
       }
     } else {
-      arrive(0, af);
-    }
-    if (plain) {
-      wait_vmcnt<0>();
-      asm volatile("" ::: "memory");
+      arrive(af);
     }
   }
 };
@@ -433,7 +466,7 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
   for (int kc = 0; kc < KC; ++kc) {
     u32x4(&now)[MR][Dim::KS] = af[kc % SETS];
     if (kc == 0) R.first(now, nullptr, nullptr);
-    else R.arrive(kc, now);
+    else R.arrive_later(kc, now);
 #pragma unroll
     for (int ahead = 1; ahead < SETS; ++ahead)   // as early as there are registers
       if (kc + ahead < KC && (kc == 0 || ahead + 1 == SETS)) {
