@@ -88,6 +88,11 @@ struct PlDim {
   // columns and column tiles of a workgroup: QKV, the square ones, first FFN matrix; chunks of K of the second; all chunks of a layer
   static constexpr int kNQ = 3 * D / kPlMembers, kND = D / kPlMembers, kNF = 4 * D / kPlMembers;
   static constexpr int kTQ = kNQ / 16, kTD = kND / 16, kTF = kNF / 16, kKC = 4, kPerLayer = kTQ + 3 * kTD + kTF + kKC * kTD;
+  // Chunks requested in stage s.  Rows are waited for behind what a CU has requested before (0.6 us a chunk of d = 512), so where the ring holds
+  // more than a stage's chunks they are spread over the stages, attention among them, as far as the ring goes: with as many requested as a
+  // stage had used, three or four at a time, a verify pass of 77 rows took 130.0 us, so 125.2; 352 rows 175.0 / 173.5.
+  static constexpr int kAsk[8] = {D == 512 ? 2 : kTQ, D == 512 ? 2 : 0, kTD, kTD, D == 512 ? 1 : 0, kTD, D == 512 ? 3 : kTF, D == 512 ? 3 : kTD * kKC};
+  static constexpr int kAskFirst = D == 512 ? kTQ : kRing;   // ahead of the first
   // column vectors of a layer, floats: cs and bf of the three projections, three of each sum
   static constexpr int kVecQ = 0, kVecC = 2 * kNQ, kVecF = kVecC + 2 * kND, kVecS = kVecF + 2 * kNF;
   static constexpr int kVecs = kVecS + 9 * kND, kVecReq = (kVecs / 4 + 63) / 64, kVecPitch = kVecReq * 256;   // requests of 64 x 16 bytes
@@ -382,7 +387,7 @@ __device__ __forceinline__ void pl_reduce(PlLds<D, MR>& L, PlTurn& t, int wave, 
 
 // hidden (LayerNorm folded) W^T + b on N column tiles, the workgroup's; cs: their cs, behind them bf (LDS); epi(row of the group,
 // column of the workgroup, float[4]) on live rows.
-template <int D, int MR, int N, class Epi>
+template <int D, int MR, int S, int N, class Epi>
 __device__ __forceinline__ void pl_project(const XcdArgs& a, PlLds<D, MR>& L, PlTurn& t, const char* A, bool plain, const char* stats,
                                            float* stat, int rows, const float* cs, Epi&& epi) {
   typedef PlDim<D> Dim;
@@ -413,7 +418,7 @@ __device__ __forceinline__ void pl_project(const XcdArgs& a, PlLds<D, MR>& L, Pl
     static_assert(NT <= 4 && NT <= Dim::kRing, "a batch");
     struct Have { f32x4 c, b; };
     // (ahead of the sum, so that the next stage's rows are waited for behind less of it: 352 rows of d = 512 188.9 -> 186.7 us)
-    pl_ask<D, MR>(L, t, wave, NT);
+    pl_ask<D, MR>(L, t, wave, Dim::kAsk[S] * (CT + NT) / N - Dim::kAsk[S] * CT / N);
     pl_reduce<D, MR, NT>(L, t, wave, lane, acc,
       [&](int i, int) {
         const float* v = cs + (CT + i) * 16 + 4 * g;
@@ -491,7 +496,7 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
       }
       if ((ct + 1) % GT != 0) continue;
       struct Have { f32x4 v[3], x; };
-      pl_ask<D, MR>(L, t, wave, KC * TD > Dim::kRing ? GT : ct + 1 == TD ? KC * TD : 0);
+      pl_ask<D, MR>(L, t, wave, KC * TD > Dim::kRing ? GT : ct + 1 == TD ? Dim::kAsk[KC == 1 ? 2 : 7] : 0);
       pl_reduce<D, MR, GT>(L, t, wave, lane, acc[ct / GT],
         [&](int i, int mr) {
           const int tile = ct / GT * GT + i;
@@ -732,8 +737,9 @@ __device__ __forceinline__ PlPair pl_pair(const XcdArgs& a, const PlPlace& p, in
   return PlPair{__builtin_amdgcn_readfirstlane(b), __builtin_amdgcn_readfirstlane(pair - b * a.H), __builtin_amdgcn_readfirstlane((u - pair * tiles) * 16)};
 }
 // mine: the unit of the first round (there is seldom another)
-template <bool SELF, bool KV8, class Lds>
-__device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex, int l, const PlPlace& at, const PlPair& mine, int units, int rounds, Lds& L) {
+template <bool SELF, bool KV8, int D, int MR>
+__device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex, int l, const PlPlace& at, const PlPair& mine, int units, int rounds, PlLds<D, MR>& L,
+                                             PlTurn& turn) {
   const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
   char* out = ex.att(SELF ? 0 : 1);
   const int wpu = a.wpu, per = kPlWaves / wpu, kw = wave & (wpu - 1);   // waves of a unit, units at a time
@@ -771,6 +777,7 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
       if (g == 0) { ml[wave * 32 + lq] = mrun; ml[wave * 32 + 16 + lq] = lrun; }
     }
     lds_barrier();
+    if (r + 1 == rounds) pl_ask<D, MR>(L, turn, wave, PlDim<D>::kAsk[SELF ? 1 : 4]);   // (behind all waves' keys and values)
     if (used > 1) {
       const int first = wave - kw;
       float ms[kPlWaves], ls[kPlWaves], M = kNegInf, Ls = 0.f;
@@ -846,15 +853,15 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     const PlExch before(a.exch + (at.g * 2 + (~l & 1)) * pl_layer_bytes(a.RP, D, 4 * D), a.RP, D);
     const float* vec = L.vec[l & 1];
     float* stat = L.stat[(3 * l + s / 3) & 1];
-    if (s == 1) return pl_attention<true, false>(a, ex, l, at, mine, units, rounds, L);
-    if (s == 4) return pl_attention<false, KV8>(a, ex, l, at, mine, units, rounds, L);
+    if (s == 1) return pl_attention<true, false>(a, ex, l, at, mine, units, rounds, L, turn);
+    if (s == 4) return pl_attention<false, KV8>(a, ex, l, at, mine, units, rounds, L, turn);
     // the statistics of the LayerNorm pending on the residual
     const char* st = s <= 2 ? (l == 0 ? nullptr : before.st(2)) : s <= 5 ? ex.st(0) : ex.st(1);
     if (s == 0 || s == 3 || s == 6) {
       const bool top = s == 0 && l == 0;
       const char* A = top ? reinterpret_cast<const char*>(a.xb + (size_t)at.row0 * D) : s == 0 ? before.xg(2) : s == 3 ? ex.xg(0) : ex.xg(1);
       if (s == 0) {   // queries, keys, values (these appended to the cache as well)
-        pl_project<D, MR, Dim::kTQ>(a, L, turn, A, top, st, stat, at.rows, vec + Dim::kVecQ, [&](int row, int c, const float (&v)[4]) {
+        pl_project<D, MR, 0, Dim::kTQ>(a, L, turn, A, top, st, stat, at.rows, vec + Dim::kVecQ, [&](int row, int c, const float (&v)[4]) {
           const int col = at.w * Dim::kNQ + c, part = col / D, cc = col - part * D;
           const u32x2 p = pl_pack4(v);
           pl_store8((part == 0 ? ex.q(0) : part == 1 ? ex.kx() : ex.vx()) + pl_at(a.RP, row, cc), p[0], p[1]);
@@ -864,12 +871,12 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
           *reinterpret_cast<u32x2*>(cache + (size_t)(to + (cc >> 6) * a.Lcap) * kHeadDim + (cc & 63)) = p;
         });
       } else if (s == 3) {
-        pl_project<D, MR, Dim::kTD>(a, L, turn, A, false, st, stat, at.rows, vec + Dim::kVecC, [&](int row, int c, const float (&v)[4]) {
+        pl_project<D, MR, 3, Dim::kTD>(a, L, turn, A, false, st, stat, at.rows, vec + Dim::kVecC, [&](int row, int c, const float (&v)[4]) {
           const u32x2 p = pl_pack4(v);
           pl_store8(ex.q(1) + pl_at(a.RP, row, at.w * Dim::kND + c), p[0], p[1]);
         });
       } else {
-        pl_project<D, MR, Dim::kTF>(a, L, turn, A, false, st, stat, at.rows, vec + Dim::kVecF, [&](int row, int c, const float (&v)[4]) {
+        pl_project<D, MR, 6, Dim::kTF>(a, L, turn, A, false, st, stat, at.rows, vec + Dim::kVecF, [&](int row, int c, const float (&v)[4]) {
           const float o[4] = {fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f)};
           const u32x2 p = pl_pack4(o);
           pl_store8(ex.hid() + pl_at(a.RP, row, at.w * Dim::kNF + c), p[0], p[1]);
@@ -929,8 +936,8 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     }
     __syncthreads();
     pl_ask_vectors<D, MR>(a, L, 0, at.w, wave);
-    pl_ask<D, MR>(L, turn, wave, Dim::kRing);
-    wait_vmcnt<Dim::kRing * Dim::kReq>();   // the vectors
+    pl_ask<D, MR>(L, turn, wave, Dim::kAskFirst);
+    wait_vmcnt<Dim::kAskFirst * Dim::kReq>();   // the vectors
     __syncthreads();
     for (int l = 0; l < a.n_layers; ++l) {
       stage(0, l); stage(1, l); stage(2, l); stage(3, l); stage(4, l); stage(5, l); stage(6, l); stage(7, l);
