@@ -51,7 +51,7 @@ namespace xcd {
 constexpr unsigned kPlSpinMax = 3u << 18;   // (0.13 - 0.17 s: 2^17 polls of the L2 take 21 - 28 ms)
 constexpr int kPlGroups = 8, kPlMembers = 32;          // XCDs; workgroups of each
 constexpr int kPlWaves = 8, kPlThreads = 64 * kPlWaves;
-static_assert(kPlGroups * kPlMembers == kPlBlocks, "a workgroup per CU");
+static_assert(kPlGroups * kPlMembers == kPlBlocks && kPlWaves == 8, "a workgroup per CU; pairs of a row's four lanes");
 // (a word of each 8 bytes: results are stored 8 bytes at a time)
 __device__ __forceinline__ bool pl_missing(const u32x4& v) { return v[1] == kPoison || v[3] == kPoison; }
 __device__ __forceinline__ void pl_store8(void* p, unsigned a, unsigned b) {
@@ -291,6 +291,33 @@ struct PlRows {
         request(mr, kc, af);
       }
   }
+  // All columns of a few rows, KC sets of them.
+  template <int KC>
+  __device__ __forceinline__ void all(u32x4 (&af)[KC][MR][KS]) const {
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+      for (int mr = 0; mr < MR; ++mr) request(mr, kc, af[kc]);
+    unsigned spins = 0;
+    while (true) {
+      bool miss[KC], any = false;
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc) {
+        miss[kc] = false;
+#pragma unroll
+        for (int mr = 0; mr < MR; ++mr) miss[kc] |= missing(mr, af[kc]);
+        any |= miss[kc];
+      }
+      if (!any) break;
+      pl_again(spins, a);
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc)
+        if (miss[kc]) {
+#pragma unroll
+          for (int mr = 0; mr < MR; ++mr) request(mr, kc, af[kc]);
+        }
+    }
+  }
   // All row tiles of the first D columns; with them (stats not null) the statistics of the same columns, merged into one pair a row
   // (part).  What has been requested of the weights is there, too.
   __device__ __forceinline__ void first(u32x4 (&af)[MR][KS], const char* stats, float* part) const {
@@ -330,23 +357,20 @@ struct PlRows {
     }
   }
 };
-// {rstd, -mean rstd} of a row from the waves' pairs
+// {rstd, -mean rstd} of row 16 mr + lq from the waves' pairs, two of them a lane of the row's four
 template <int D>
-__device__ __forceinline__ f32x2 pl_row_stat(const float* part, int pitch, int row) {
-  f32x2 p[kPlWaves];
-  float s = 0.f, q = 0.f;
+__device__ __forceinline__ f32x2 pl_row_stat(const float* part, int pitch, int row, int g) {
+  f32x2 p[2];
 #pragma unroll
-  for (int w = 0; w < kPlWaves; ++w) {
-    p[w] = *reinterpret_cast<const f32x2*>(part + w * pitch + 2 * row);
-    s += p[w][0];
-  }
-  const float mean = s * (1.f / D);
+  for (int i = 0; i < 2; ++i) p[i] = *reinterpret_cast<const f32x2*>(part + (2 * g + i) * pitch + 2 * row);
+  const float mean = pl_row_sum(p[0][0] + p[1][0]) * (1.f / D);
+  float q = 0.f;
 #pragma unroll
-  for (int w = 0; w < kPlWaves; ++w) {
-    const float dv = p[w][0] * ((float)kPlWaves / D) - mean;
-    q += __builtin_fmaf((float)(D / kPlWaves) * dv, dv, p[w][1]);
+  for (int i = 0; i < 2; ++i) {
+    const float dv = p[i][0] * ((float)kPlWaves / D) - mean;
+    q += __builtin_fmaf((float)(D / kPlWaves) * dv, dv, p[i][1]);
   }
-  const float rstd = fast_rsqrt(q * (1.f / D) + 1e-5f);
+  const float rstd = fast_rsqrt(pl_row_sum(q) * (1.f / D) + 1e-5f);
   return f32x2{rstd, -mean * rstd};
 }
 
@@ -430,7 +454,7 @@ __device__ __forceinline__ void pl_project(const XcdArgs& a, PlLds<D, MR>& L, Pl
         if (CT > 0) {   // (the first batch's waves have left them)
           st = *reinterpret_cast<const f32x2*>(stat + 2 * row);
         } else {
-          if (stats) st = pl_row_stat<D>(&L.part[0][0], 2 * 16 * MR, row);
+          if (stats) st = pl_row_stat<D>(&L.part[0][0], 2 * 16 * MR, row, g);
           if (i == 0) *reinterpret_cast<f32x2*>(stat + 2 * row) = st;
         }
         float o[4];
@@ -470,10 +494,15 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
 #pragma unroll
   for (int kc = 0; kc < KC; ++kc) {
     u32x4(&now)[MR][Dim::KS] = af[kc % SETS];
-    if (kc == 0) R.first(now, nullptr, nullptr);
-    else R.arrive_later(kc, now);
+    constexpr bool ALL = KC > 1 && MR * Dim::KS * KC <= 8;
+    if constexpr (ALL) {
+      if (kc == 0) R.template all<KC>(af);
+    } else {
+      if (kc == 0) R.first(now, nullptr, nullptr);
+      else R.arrive_later(kc, now);
+    }
 #pragma unroll
-    for (int ahead = 1; ahead < SETS; ++ahead)   // as early as there are registers
+    for (int ahead = 1; ahead < (ALL ? 0 : SETS); ++ahead)   // as early as there are registers
       if (kc + ahead < KC && (kc == 0 || ahead + 1 == SETS)) {
 #pragma unroll
         for (int mr = 0; mr < MR; ++mr) R.request(mr, kc + ahead, af[(kc + ahead) % SETS]);
@@ -777,20 +806,25 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
       if (g == 0) { ml[wave * 32 + lq] = mrun; ml[wave * 32 + 16 + lq] = lrun; }
     }
     lds_barrier();
-    if (r + 1 == rounds) pl_ask<D, MR>(L, turn, wave, PlDim<D>::kAsk[SELF ? 1 : 4]);   // (behind all waves' keys and values)
-    if (used > 1) {
+    // what is requested goes behind all waves' keys and values, and behind the merge on the waves that have a share of it
+    auto ask = [&] {
+      if (r + 1 == rounds) pl_ask<D, MR>(L, turn, wave, PlDim<D>::kAsk[SELF ? 1 : 4]);
+    };
+    if (used <= 1 || kw >= 4) ask();
+    auto merge = [&](auto most) {
+      constexpr int W = decltype(most)::value;
       const int first = wave - kw;
-      float ms[kPlWaves], ls[kPlWaves], M = kNegInf, Ls = 0.f;
+      float ms[W], ls[W], M = kNegInf, Ls = 0.f;
 #pragma unroll
-      for (int s = 0; s < kPlWaves; ++s) {
+      for (int s = 0; s < W; ++s) {
         const int w = first + min(s, used - 1);
         ms[s] = ml[w * 32 + lq];
         ls[s] = ml[w * 32 + 16 + lq];
       }
 #pragma unroll
-      for (int s = 0; s < kPlWaves; ++s) M = fmaxf(M, ms[s]);
+      for (int s = 0; s < W; ++s) M = fmaxf(M, ms[s]);
 #pragma unroll
-      for (int s = 0; s < kPlWaves; ++s) {
+      for (int s = 0; s < W; ++s) {
         ms[s] = s < used && ms[s] > kNegInf ? __builtin_amdgcn_exp2f((ms[s] - M) * kCexp) : 0.f;
         Ls += ls[s] * ms[s];
       }
@@ -798,13 +832,18 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
       for (int et = kw; et < 4; et += wpu) {
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < kPlWaves; ++s) {
+        for (int s = 0; s < W; ++s) {
           const f32x4 v = om[((first + min(s, used - 1)) * 4 + et) * 64 + lane];
 #pragma unroll
           for (int i = 0; i < 4; ++i) o[i] += v[i] * ms[s];
         }
         store(et, o, inv);
       }
+    };
+    if (used > 1 && kw < 4) {
+      if (used <= 3) merge(std::integral_constant<int, 3>{});
+      else merge(std::integral_constant<int, kPlWaves>{});
+      ask();
     }
   }
   lds_barrier();
@@ -890,8 +929,10 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
       u32x4 none[MR][Dim::KS];
       PlRows<D, MR>(a, s == 7 ? ex.hid() : ex.att(i), false, at.rows, pl_lane(), wave).first(none, st, L.part[wave]);
       lds_barrier();
-      for (int row = threadIdx.x; row < 16 * MR; row += kPlThreads)
-        *reinterpret_cast<f32x2*>(stat + 2 * row) = st ? pl_row_stat<D>(&L.part[0][0], 2 * 16 * MR, row) : f32x2{1.f, 0.f};
+      if (wave < MR) {
+        const int row = 16 * wave + (pl_lane() & 15);
+        *reinterpret_cast<f32x2*>(stat + 2 * row) = st ? pl_row_stat<D>(&L.part[0][0], 2 * 16 * MR, row, pl_lane() >> 4) : f32x2{1.f, 0.f};
+      }
     }
     auto resid = [&](int mr, int ct) {
       const int lane = pl_lane(), lq = lane & 15, g = lane >> 4;
