@@ -1059,17 +1059,15 @@ int specdec_encode(specdec_ctx* c, const int32_t* src, const int32_t* src_len, i
   return SPECDEC_OK;
 }
 
-int specdec_set_stream(specdec_ctx* c, const int32_t* tokens, const int32_t* len, int32_t L_max, void* stream) {
-  if (!c) return SPECDEC_ERR_INVALID_ARG;
-  if (!c->state_bound || c->B <= 0) return fail(c, SPECDEC_ERR_BAD_STATE, "bind state and call specdec_begin first");
-  if (!tokens || !len) return fail(c, SPECDEC_ERR_INVALID_ARG, "null tokens/len");
-  if (L_max < 0) return fail(c, SPECDEC_ERR_INVALID_ARG, "L_max = %d", L_max);
-  if (L_max > c->lim.max_tgt) return fail(c, SPECDEC_ERR_TOO_LARGE, "L_max = %d exceeds max_tgt = %d", L_max, c->lim.max_tgt);
-  HIPCHK(c, sd::set_stream(S(stream), c->st, tokens, len, c->B, L_max, c->max_new, c->lim.max_tgt));
-  c->uncached_ub[0] = L_max;
-  c->uncached_ub[1] = L_max + 1;
-  c->trusted[0] = c->trusted[1] = false;
-  c->last_T = 0;
+// tokens: set_stream in the same launch (null: not)
+static int load_cache(specdec_ctx* c, specdec_role role, const void* k_cache, const void* v_cache, const int32_t* n, int32_t L_max,
+                      const int32_t* tokens, void* stream) {
+  Model& m = c->m[role];
+  // (a kernel's parameters take no const buffers: this direction only reads them)
+  HIPCHK(c, sd::cache_load(S(stream), c->st, sd::CacheFlat{m.kc, m.vc, static_cast<bf16*>(const_cast<void*>(k_cache)),
+                           static_cast<bf16*>(const_cast<void*>(v_cache)), m.kv_layer, m.d.dec_layers, m.d.n_heads, c->Lcap, L_max, n, role,
+                           tokens, c->max_new, c->lim.max_tgt}, c->B));
+  c->trusted[role] = true;
   return SPECDEC_OK;
 }
 
@@ -1081,15 +1079,29 @@ int specdec_load_cache(specdec_ctx* c, specdec_role role, const void* k_cache, c
   if ((reinterpret_cast<uintptr_t>(k_cache) | reinterpret_cast<uintptr_t>(v_cache)) & 15) return fail(c, SPECDEC_ERR_INVALID_ARG, "cache not 16-byte aligned");
   if (L_max < 0) return fail(c, SPECDEC_ERR_INVALID_ARG, "L_max = %d", L_max);
   if (L_max > c->lim.max_tgt + 1) return fail(c, SPECDEC_ERR_TOO_LARGE, "L_max = %d exceeds max_tgt + 1", L_max);
-  Model& m = c->m[role];
-  const int H = m.d.n_heads;
-  const size_t flat_layer = (size_t)c->B * L_max * m.d.d_model;
-  for (int l = 0; l < m.d.dec_layers; ++l) {
-    HIPCHK(c, sd::cache_from_flat(S(stream), m.kc + m.kv_layer * l, static_cast<const bf16*>(k_cache) + flat_layer * l, c->B, H, c->Lcap, L_max, false));
-    HIPCHK(c, sd::cache_from_flat(S(stream), m.vc + m.kv_layer * l, static_cast<const bf16*>(v_cache) + flat_layer * l, c->B, H, c->Lcap, L_max, false));
-  }
-  HIPCHK(c, sd::set_cached(S(stream), c->st, role, n, c->B, L_max));
-  c->trusted[role] = true;
+  return load_cache(c, role, k_cache, v_cache, n, L_max, nullptr, stream);
+}
+
+static int check_stream(specdec_ctx* c, const int32_t* tokens, const int32_t* len, int32_t L_max) {
+  if (!tokens || !len) return fail(c, SPECDEC_ERR_INVALID_ARG, "null tokens/len");
+  if (L_max < 0) return fail(c, SPECDEC_ERR_INVALID_ARG, "L_max = %d", L_max);
+  if (L_max > c->lim.max_tgt) return fail(c, SPECDEC_ERR_TOO_LARGE, "L_max = %d exceeds max_tgt = %d", L_max, c->lim.max_tgt);
+  return SPECDEC_OK;
+}
+static void stream_replaced(specdec_ctx* c, int32_t L_max) {
+  c->uncached_ub[0] = L_max;
+  c->uncached_ub[1] = L_max + 1;
+  c->trusted[0] = c->trusted[1] = false;
+  c->last_T = 0;
+}
+
+int specdec_set_stream(specdec_ctx* c, const int32_t* tokens, const int32_t* len, int32_t L_max, void* stream) {
+  if (!c) return SPECDEC_ERR_INVALID_ARG;
+  if (!c->state_bound || c->B <= 0) return fail(c, SPECDEC_ERR_BAD_STATE, "bind state and call specdec_begin first");
+  int rc = check_stream(c, tokens, len, L_max);
+  if (rc) return rc;
+  HIPCHK(c, sd::set_stream(S(stream), c->st, tokens, len, c->B, L_max, c->max_new, c->lim.max_tgt));
+  stream_replaced(c, L_max);
   return SPECDEC_OK;
 }
 
@@ -1098,10 +1110,18 @@ int specdec_set_prefix(specdec_ctx* c, specdec_role role, const int32_t* tokens,
   int rc = check_ready(c, role, false);
   if (rc) return rc;
   if (!k_cache || !v_cache) return fail(c, SPECDEC_ERR_INVALID_ARG, "null cache");
-  rc = specdec_set_stream(c, tokens, len, L_max, stream);
+  if ((reinterpret_cast<uintptr_t>(k_cache) | reinterpret_cast<uintptr_t>(v_cache)) & 15) {   // (the stream is replaced, the cache refused)
+    rc = specdec_set_stream(c, tokens, len, L_max, stream);
+    return rc ? rc : specdec_load_cache(c, role, k_cache, v_cache, len, L_max, stream);
+  }
+  rc = check_stream(c, tokens, len, L_max);
   if (rc) return rc;
   // every position below j is cached (the drafter's own count of u_j is left to its next pass)
-  return specdec_load_cache(c, role, k_cache, v_cache, len, L_max, stream);
+  rc = load_cache(c, role, k_cache, v_cache, len, L_max, tokens, stream);
+  if (rc) return rc;
+  stream_replaced(c, L_max);
+  c->trusted[role] = true;
+  return SPECDEC_OK;
 }
 
 int specdec_prefill(specdec_ctx* c, specdec_role role, void* stream) {
@@ -1395,11 +1415,8 @@ int specdec_get_cache(specdec_ctx* c, specdec_role role, void* k_cache, void* v_
   if (!k_cache || !v_cache) return fail(c, SPECDEC_ERR_INVALID_ARG, "null cache");
   if (L < 1 || L > c->Lcap) return fail(c, SPECDEC_ERR_INVALID_ARG, "L = %d outside [1, %d]", L, c->Lcap);
   Model& m = c->m[role];
-  const size_t flat_layer = (size_t)c->B * L * m.d.d_model;
-  for (int l = 0; l < m.d.dec_layers; ++l) {
-    HIPCHK(c, sd::cache_to_flat(S(stream), m.kc + m.kv_layer * l, static_cast<bf16*>(k_cache) + flat_layer * l, c->B, m.d.n_heads, c->Lcap, L, false));
-    HIPCHK(c, sd::cache_to_flat(S(stream), m.vc + m.kv_layer * l, static_cast<bf16*>(v_cache) + flat_layer * l, c->B, m.d.n_heads, c->Lcap, L, false));
-  }
+  HIPCHK(c, sd::cache_read(S(stream), sd::CacheFlat{m.kc, m.vc, static_cast<bf16*>(k_cache), static_cast<bf16*>(v_cache), m.kv_layer, m.d.dec_layers,
+                                                    m.d.n_heads, c->Lcap, L, nullptr, role, nullptr, 0, 0}, c->B));
   return SPECDEC_OK;
 }
 

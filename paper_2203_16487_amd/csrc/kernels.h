@@ -393,13 +393,19 @@ hipError_t set_stream(hipStream_t st, const SeqState& s, const int* tokens, cons
                       int L_max, int max_new, int max_tgt);
 hipError_t rewind_state(hipStream_t st, const SeqState& s, const int* len, int B);
 hipError_t set_src_len(hipStream_t st, const SeqState& s, const int* src_len, int B, int S_max);
-hipError_t set_cached(hipStream_t st, const SeqState& s, int role, const int* n, int B, int hi);
 hipError_t get_output(hipStream_t st, const SeqState& s, int* tokens, int out_cap, int* out_len,
                       int* finished, int B, int pad_id);
-// key cache [B][H][Lcap][64] / key-blocked value cache  <->  flat [B][L][d]
-hipError_t cache_from_flat(hipStream_t st, bf16* cache, const bf16* flat, int B, int H, int Lcap,
-                           int L, bool blocked);
-hipError_t cache_to_flat(hipStream_t st, const bf16* cache, bf16* flat, int B, int H, int Lcap,
-                         int L, bool blocked);
+// Keys / values of every layer of a model [layer][B][H][Lcap][64] and a caller's [layer][B][L][d].
+struct CacheFlat {
+  bf16 *kc, *vc, *k, *v;
+  size_t kv_layer;
+  int layers, H, Lcap, L;
+  const int* n;                          // cache_load: rows of a sequence that count as cached (at most L)
+  int role;
+  const int* tokens;                     // cache_load: its stream as well, as set_stream (null: not)
+  int max_new, max_tgt;
+};
+hipError_t cache_load(hipStream_t st, const SeqState& s, const CacheFlat& a, int B);
+hipError_t cache_read(hipStream_t st, const CacheFlat& a, int B);
 
 }  // namespace sd

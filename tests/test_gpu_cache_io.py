@@ -1,0 +1,45 @@
+"""Stored caches in and out: whatever number of layers, heads and rows, all of them arrive where they belong, and set_prefix is set_stream
+and load_cache in one."""
+import numpy as np
+import pytest
+import torch
+
+import cases
+import gpu_harness as gh
+from paper_2203_16487_amd import binding as sd
+from paper_2203_16487_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,layers,B,L", [(64, 1, 1, 1), (192, 3, 5, 7), (512, 2, 3, 33), (1024, 1, 2, 40)])   # one block a sequence .. several, the last part empty
+def test_round_trip_and_prefix(d, layers, B, L):
+    desc = synth.ModelDesc(0, layers, d, d // 64, 4 * d, 1003, 64, 300).resolved()
+    case = cases.make_verify_case(desc, seed=d + L, B=B, S=9, k=2, beta=3, tau=1.0, len_lo=L, len_hi=L, drafts="random", ragged_src=True)
+    ses = gh.open_verifier(case, fill=0xFF)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    K, V = (torch.randn((layers, B, L, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    n = ses.i32(np.arange(B) % (L + 1))                   # (rows beyond the count are stored all the same)
+    lens = ses.i32(np.full(B, L) - np.arange(B) % 2)
+    got = []
+    for prefix in (False, True):
+        zeros = torch.zeros_like(K)
+        sd.specdec_load_cache(ses.ctx, sd.SPECDEC_VERIFIER, zeros, zeros, n)
+        if prefix:
+            sd.specdec_set_prefix(ses.ctx, sd.SPECDEC_VERIFIER, ses.i32(case.tokens), lens, K, V)
+        else:
+            sd.specdec_set_stream(ses.ctx, ses.i32(case.tokens), lens)
+            sd.specdec_load_cache(ses.ctx, sd.SPECDEC_VERIFIER, K, V, lens)
+        k2, v2 = torch.zeros_like(K), torch.zeros_like(V)
+        sd.specdec_get_cache(ses.ctx, sd.SPECDEC_VERIFIER, k2, v2)
+        assert torch.equal(k2.view(torch.int16), K.view(torch.int16)) and torch.equal(v2.view(torch.int16), V.view(torch.int16))
+        acc, nxt = ses.i32(np.zeros(B)), ses.i32(np.zeros(B))
+        sd.specdec_verify(ses.ctx, ses.i32(case.drafts), case.k, case.beta, case.tau, acc, nxt)
+        got.append((acc.cpu().tolist(), nxt.cpu().tolist()))
+        assert min(got[-1][0]) >= 0                       # every row below its length counts as cached
+    assert got[0] == got[1]
+    sd.specdec_load_cache(ses.ctx, sd.SPECDEC_VERIFIER, K, V, n)
+    sd.specdec_verify(ses.ctx, ses.i32(case.drafts), case.k, case.beta, case.tau, acc, nxt)
+    short = (n < lens).cpu().tolist()
+    assert [a == -1 for a in acc.cpu().tolist()] == short
+    ses.close()
