@@ -116,7 +116,7 @@ typedef enum {
                                           such pass (so that the wide kernel can be checked on small shapes).     */
   SPECDEC_OPT_GIVE_UP_WAITS = 7        /* default 0.  1: every wait of the one-kernel decoder that does not end at once is
                                           given up (in groups: one workgroup of each is left out, and waits end at their
-                                          bound), and the pass completed by the kernel behind it
+                                          bound, of at most 63 rows after 64 polls), and the pass completed by the kernel behind it
                                           (specdec_verify), so that this way of completing a pass can be checked. */
 } specdec_option;
 
@@ -235,8 +235,10 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * k = 0 (draft may be null) is one plain autoregressive step: accept_len = 0 and next_token is
  * the verifier's greedy token (the baseline of Sec. 2 on the same kernels).
  * Passes of few rows (d_model 512 / d_ffn 2048 or 1024 / 4096, 32 layers; at most 512 rows, and at most
- * 64 to each of eight groups that the sequences are dealt to evenly; of those beyond 63 (1024: 128) rows every XCD
- * takes one group) run their decoder layers as one kernel of up to 256 workgroups that wait for each other; where a
+ * 64 to each of eight groups that the sequences are dealt to evenly; of those beyond 128 rows, and at d_model 512 of
+ * all that read bf16 weights, every XCD takes one group; where the stream has fewer than 256 compute units, one of at
+ * most 63 (1024: 128) rows may still run over those it has) run their decoder layers as one kernel of up to 256
+ * workgroups that wait for each other; where a
  * kernel of another stream or process keeps some of them from starting for 0.1 s or more, the waits
  * are given up and a second kernel, which needs no more than one free compute unit, computes
  * the pass instead (same bits, 0.5 - 3 ms; in groups 7 - 14); so it does the run's next 63 (15) passes without

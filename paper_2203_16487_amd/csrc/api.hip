@@ -46,6 +46,10 @@ struct Fp8Layer {
   sd::SkWeight wqkv, wo, cwq, cwo, w1, w2;
 };
 
+// How the decoder layers of a verify pass run: launches a stage; as one kernel over the whole GPU (persist.hip); as one kernel, each XCD
+// on sequences of its own (xcd.hip), from a copy of the weights in order of use or, a few rows, from the weights as bound.
+enum class Way { launches, gpu, xcd, xcd_few };
+
 struct Model {
   bool bound = false;
   bool has_memory = false;
@@ -77,7 +81,7 @@ struct Model {
   int* pl_err = nullptr;              // its flags (PlArgs::err), behind them the per-XCD one's (XcdArgs::err)
   char* pl_exch = nullptr;            // exchange buffers, its or the per-XCD one's (xcd.hip); null: dimensions they do not support
   int pl_rows = 0;                    // rows they are sized for, its
-  char* xcd_stream = nullptr;         // the layers' weights as the per-XCD decoder streams them
+  char* xcd_stream = nullptr;         // the layers' weights as the per-XCD decoder streams them (null: no pass of more than a few rows of 512)
   float* xcd_vecs = nullptr;          // and their column vectors
   bf16* xb = nullptr;        // [Rpass][d]
   float* lnp[2] = {nullptr, nullptr};   // [rows][d/32 at most][2] chunk pairs of the two latest residual sums
@@ -136,6 +140,7 @@ struct specdec_ctx {
   bool resident = false;    // SPECDEC_OPT_RESIDENT = 1: refuses what a pass of at most 32 rows as one kernel once did not support
   int persist_dev = -1;     // GPU on which this context is among the users of the one-kernel decoder
   bool persist_refused = false;   // another user was found on it in this run: separate launches until the next specdec_begin
+  Way way = Way::launches;  // of the latest pass
   bool give_up = false;     // SPECDEC_OPT_GIVE_UP_WAITS = 1: the one-kernel decoder's waits are given up at once
   bool sliced = false;      // SPECDEC_OPT_SLICED_SUBLAYERS = 1: small-batch sub-layers owned by head / FFN slice
   bool fp8 = false;         // SPECDEC_OPT_FP8_WEIGHTS = 1: models bound from now on keep E4M3 copies for small batches
@@ -199,12 +204,13 @@ bool desc_ok(const specdec_model_desc* d) {
          d->mask_id >= 0 && d->mask_id < d->vocab;
 }
 constexpr long kPrefillRows = 8192;
-// Most rows of a pass the one-kernel decoder over the whole GPU is asked for: beyond, its workgroups read more than the per-XCD one's
-// do.  Whole passes, launches / whole GPU / per XCD, us: d = 512: 6 rows 234 / 136 / 144, 48 rows 246 / 147 / 155, 64 (one a sequence)
-// 256 / 186 / 175, 77 251 / 167 / 154, 176 271 / 217 / 185, 352 315 / - / 212, 480 327 / - / 255; d = 1024 (whose weights every XCD
-// reads: 176 MB): 6 rows 266 / 177 / 253, 77 341 / 289 / 305, 96 354 / 306 / 314, 128 407 / 374 / 392, 176 391 / - / 345, 352
-// 497 / - / 409, 480 539 / - / 482.
+// Most rows of a pass the one-kernel decoder over the whole GPU is asked for.  At d = 512 the per-XCD one is the faster for any number of
+// rows, and takes them all where the stream has every compute unit and the weights are bf16; whole passes, whole GPU / per XCD, us: 1 row
+// 129 / 113, 6 132 / 116, 22 (two sequences) 142 / 121, 26 (one) 144 / 138, 48 144 / 128, 63 (one a sequence) 173 / 139 (launches: 6 rows 234,
+// 48 246).  At d = 1024 every XCD reads 176 MB of weights: 6 rows 178 / 226, 26 216 / 266, 44 239 / 272, 77 287 / 281, 88 300 / 283, 99 303 /
+// 303, 121 296 / 310, 128 338 / 344 (launches: 6 rows 266, 128 407, 352 497 and per XCD 377).
 constexpr size_t persist_rows(int d) { return d <= 512 ? 63 : 128; }
+static_assert(persist_rows(512) == sd::kXcdFewRows, "beyond, the per-XCD decoder streams a copy of the weights");
 constexpr int kEncT = 12, kDecT = 20;
 int n_weights(const specdec_model_desc* d) { return 1 + kEncT * d->enc_layers + kDecT * d->dec_layers; }
 
@@ -322,12 +328,10 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     // uses neither: the size is asked for without a role.)
     const bool per_xcd = sd::xcd_rows_most((int)Bm, c->lim.k_max + 1) > t.pl_rows;
     const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F);
-    const size_t xcd = per_xcd ? sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F) : 0;
+    const size_t xcd = per_xcd || D == 512 ? sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F) : 0;
     t.pl_exch = cv.take<char>(one > xcd ? one : xcd);
-    if (per_xcd) {
-      t.xcd_stream = cv.take<char>(sd::xcd_stream_bytes(d->dec_layers, (int)D, (int)F));
-      t.xcd_vecs = cv.take<float>(sd::xcd_vec_bytes(d->dec_layers, (int)D) / sizeof(float));
-    }
+    if (per_xcd) t.xcd_stream = cv.take<char>(sd::xcd_stream_bytes(d->dec_layers, (int)D, (int)F));   // (few rows of 512: without it)
+    if (per_xcd || D == 512) t.xcd_vecs = cv.take<float>(sd::xcd_vec_bytes(d->dec_layers, (int)D) / sizeof(float));
   }
   if (d->enc_layers > 0) {
     const size_t Re = Bm * (size_t)c->Scap;
@@ -609,32 +613,28 @@ int stream_cus(hipStream_t st) {
   return n;
 }
 
-// How the decoder layers of a verify pass run: launches a stage; as one kernel over the whole GPU (persist.hip); as one kernel, each XCD
-// on sequences of its own (xcd.hip).
-enum class Way { launches, gpu, xcd };
-
-Way one_kernel_way(const specdec_ctx* c, const Model& m, int B, int T) {
+// cus: compute units the pass's stream has.  few: the E4M3 copies of the weights, if the model has them.
+Way one_kernel_way(const Model& m, int B, int T, bool few, int cus) {
   sd::PlArgs p{};
   p.R = B * T; p.T = T; p.B = B; p.H = m.d.n_heads;
   sd::XcdArgs x{};
   x.R = B * T; x.T = T; x.B = B; x.H = m.d.n_heads;
-  const int D = m.d.d_model, F = m.d.d_ffn, R = B * T;
-  const bool gpu = R <= m.pl_rows && sd::persist_plan(p, D, F) > 0, xcd = m.xcd_stream && R <= sd::kXcdMostRows && !(m.fp8 && R <= 32) && sd::xcd_plan(x, D, F) > 0;
-  return gpu ? Way::gpu : xcd ? Way::xcd : Way::launches;
+  const int D = m.d.d_model, F = m.d.d_ffn, R = B * T, blocks = R <= m.pl_rows ? sd::persist_plan(p, D, F) : 0;
+  const bool xcd = cus >= sd::kPlBlocks && !(m.fp8 && few) && R <= sd::kXcdMostRows && sd::xcd_plan(x, D, F) > 0;
+  if (xcd && D == 512 && m.xcd_vecs && R <= sd::kXcdFewRows) return Way::xcd_few;
+  if (blocks > 0 && cus >= blocks) return Way::gpu;
+  return xcd && m.xcd_stream ? Way::xcd : Way::launches;
 }
 
-bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
+// Whether the pass takes one of them (c->way: which).
+bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, bool few, hipStream_t st) {
   if (!m.pl_exch || T > 32 || c->no_skinny || c->no_ln_fold || c->sliced) return false;
-  const Way way = one_kernel_way(c, m, B, T);
-  if (way == Way::launches) return false;
-  sd::PlArgs a{};
-  a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads;
-  const int blocks = way == Way::xcd ? sd::kPlBlocks : sd::persist_plan(a, m.d.d_model, m.d.d_ffn);   // all of them running at once
   int dev = -1, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < blocks ||
-      stream_cus(st) < blocks)
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return false;
+  c->way = one_kernel_way(m, B, T, few, std::min(cus, stream_cus(st)));   // (all of a way's workgroups run at once)
+  if (c->way == Way::launches) return false;
   if (c->persist_refused || (c->persist_dev >= 0 && c->persist_dev != dev)) return false;
   bool capturing = false;
   if (st && st != hipStreamLegacy) {   // (which cannot be captured)
@@ -658,14 +658,14 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, hipStream_t st) {
   return true;
 }
 
-// The flags of the decoder that runs it.
-unsigned* persist_flags(const specdec_ctx* c, const Model& m, int B, int T) {
-  return reinterpret_cast<unsigned*>(m.pl_err) + (one_kernel_way(c, m, B, T) == Way::xcd ? sd::kPlFlags : 0);
+// The flags of the decoder that runs it: each counts its own passes.
+unsigned* persist_flags(const specdec_ctx* c, const Model& m) {
+  return reinterpret_cast<unsigned*>(m.pl_err) + (c->way == Way::gpu ? 0 : sd::kPlFlags + (c->way == Way::xcd ? 0 : sd::kXcdFlags));
 }
 
 // Bytes of the exchange buffers that the pass's first kernel fills with 0xff.
 size_t persist_clear(const specdec_ctx* c, const Model& m, int B, int T) {
-  if (one_kernel_way(c, m, B, T) == Way::gpu) return sd::persist_exch_bytes(B * T, m.d.dec_layers, m.d.d_model, m.d.d_ffn);
+  if (c->way == Way::gpu) return sd::persist_exch_bytes(B * T, m.d.dec_layers, m.d.d_model, m.d.d_ffn);
   sd::XcdArgs a{};
   a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads;
   return sd::xcd_plan(a, m.d.d_model, m.d.d_ffn);
@@ -673,15 +673,15 @@ size_t persist_clear(const specdec_ctx* c, const Model& m, int B, int T) {
 
 // few: as in decoder_layers (the E4M3 copies of the weights, if the model has them)
 int decoder_layers_persist(specdec_ctx* c, Model& m, int B, int T, bool few, hipStream_t st) {
-  if (one_kernel_way(c, m, B, T) == Way::xcd) {
+  if (c->way != Way::gpu) {
     sd::XcdArgs a{};
     a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads; a.Lcap = c->Lcap; a.Scap = c->Scap; a.n_layers = m.d.dec_layers;
-    a.stream = m.xcd_stream; a.vecs = m.xcd_vecs;
+    a.layers = m.pl_layers; a.stream = c->way == Way::xcd ? m.xcd_stream : nullptr; a.vecs = m.xcd_vecs;
     a.row_b = m.rm.row_b; a.row_pos = m.rm.row_pos; a.src_len = c->st.src_len;
     a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + (size_t)sd::kXcdMostRows * m.d.d_model;
     a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
     if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
-    a.exch = m.pl_exch; a.err = persist_flags(c, m, B, T);
+    a.exch = m.pl_exch; a.err = persist_flags(c, m);
     LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::xcd_decoder(st, a, m.d.d_model, m.d.d_ffn, c->give_up));
     return SPECDEC_OK;
   }
@@ -693,7 +693,7 @@ int decoder_layers_persist(specdec_ctx* c, Model& m, int B, int T, bool few, hip
   a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + persist_rows(m.d.d_model) * m.d.d_model;
   a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
   if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
-  a.exch = m.pl_exch; a.err = persist_flags(c, m, B, T);
+  a.exch = m.pl_exch; a.err = persist_flags(c, m);
   LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::persist_decoder(st, a, m.d.d_model, m.d.d_ffn, c->give_up));
   return SPECDEC_OK;
 }
@@ -932,7 +932,7 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
     if (rcq != SPECDEC_OK) return fail(c, rcq, "FP8 weight quantisation failed: %s", hipGetErrorString(hipGetLastError()));
   }
   {
-    HIPCHK(c, sd::fill_i32(S(stream), m.pl_err, 0, sd::kPlFlags + sd::kXcdFlags));
+    HIPCHK(c, sd::fill_i32(S(stream), m.pl_err, 0, sd::kPlFlags + 2 * sd::kXcdFlags));
     // for the one-kernel decoder: the bf16 matrices, then (FP8 weights) their codes
     std::vector<sd::PlLayer> pl;
     for (int set = 0; set < (m.fp8 ? 2 : 1); ++set)
@@ -945,7 +945,7 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
                                  f.cq.bf, f.w1.cs, f.w1.bf, f.vo, f.vco, f.v2});
       }
     HIPCHK(c, hipMemcpy(m.pl_layers, pl.data(), pl.size() * sizeof(sd::PlLayer), hipMemcpyHostToDevice));
-    if (m.xcd_stream && role == SPECDEC_VERIFIER) HIPCHK(c, sd::xcd_pack(S(stream), m.pl_layers, d->dec_layers, d->d_model, m.xcd_stream, m.xcd_vecs));
+    if (m.xcd_vecs && role == SPECDEC_VERIFIER) HIPCHK(c, sd::xcd_pack(S(stream), m.pl_layers, d->dec_layers, d->d_model, m.xcd_stream, m.xcd_vecs));
   }
   m.bound = true;
   return SPECDEC_OK;
@@ -960,7 +960,7 @@ int specdec_begin(specdec_ctx* c, int32_t B, int32_t max_new, void* stream) {
   const Model& any = c->m[0].bound ? c->m[0] : c->m[1];
   if (max_new > c->lim.max_tgt) max_new = c->lim.max_tgt;   // no stream grows beyond the arena
   HIPCHK(c, sd::begin_state(S(stream), c->st, B, max_new, c->lim.max_tgt, any.d.bos_id));
-  if (c->m[0].bound) HIPCHK(c, sd::fill_i32(S(stream), c->m[0].pl_err, 0, sd::kPlFlags + sd::kXcdFlags));   // a new run clears the one-kernel decoder's flags
+  if (c->m[0].bound) HIPCHK(c, sd::fill_i32(S(stream), c->m[0].pl_err, 0, sd::kPlFlags + 2 * sd::kXcdFlags));   // a new run clears the one-kernel decoder's flags
   c->B = B;
   c->max_new = max_new;
   c->last_T = 0;
@@ -1218,7 +1218,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   // The fused small-batch decoder kernels, whose every block redoes what precedes its product and which embed the rows
   // themselves, where that is little: one sequence of few rows, d = 512 (3 rows 184 against 205 us, 11: 210 / 214, 16: 220 /
   // 218; two sequences of 6 235 / 214; d = 1024: 6 rows 285 / 268, 26 521 / 302).  Otherwise the general ones.
-  const bool one = persist_ok(c, m, B, T, st);
+  const bool one = persist_ok(c, m, B, T, small, st);
   const bool fused = small && !one && (c->no_ln_fold || c->sliced || (B == 1 && R <= 12 && m.d.d_model <= 512));
   VerifyScratch vs{m.part, m.zd, m.row_stats};
   if (ext) {
@@ -1238,7 +1238,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_verify(st, c->st, m.rm, draft, B, k, m.d.vocab, m.embed, m.pe, m.x, m.xb,
                                         m.d.d_model, one ? m.pl_exch : nullptr,
                                         one ? persist_clear(c, m, B, T) : 0));
-  const unsigned* failed = one ? persist_flags(c, m, B, T) + 1 : nullptr;
+  const unsigned* failed = one ? persist_flags(c, m) + 1 : nullptr;
   float* sums = one ? m.skp : m.x;   // the last residual sums (the one-kernel decoder keeps its input rows)
   int n_tiles = (m.d.vocab + 63) / 64;   // per-row partial records of the vocabulary kernel that ran
   if (small && (m.fp8 || m.kv8) && (c->resident || c->sliced))

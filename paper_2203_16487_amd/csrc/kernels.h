@@ -269,7 +269,8 @@ hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F, bool give_up)
 // ---- xcd.hip: the same for more rows, each XCD on sequences of its own ----
 struct XcdArgs {
   int R, T, B, H, Lcap, Scap, n_layers;   // as PlArgs
-  const char* stream;                     // weights and column vectors as xcd_pack lays them out
+  const PlLayer* layers;                  // device array [n_layers]
+  const char* stream;                     // weights and column vectors as xcd_pack lays them out; null (d = 512, kXcdFewRows): the weights as bound
   const float* vecs;
   const int *row_b, *row_pos, *src_len;
   const float* x;
@@ -285,8 +286,10 @@ struct XcdArgs {
                                           // be computed another way); those of that way too (results are void); a counter
   int RP, d, G, wpu;                      // filled by the launcher, as what follows
   unsigned *raised, *ended;
+  unsigned spin_max;
 };
 constexpr int kXcdMostRows = 512;         // rows of a pass at most: 64 on each of 8 XCDs
+constexpr int kXcdFewRows = 63;           // of a pass that reads the weights as bound (no copy of them), 32 on an XCD
 constexpr unsigned kXcdAlonePasses = 16;  // that are computed without waits (7 - 14 ms each) after waits were given up
 // Weights (bf16) of a model's layers (device array) in the order they are used, and their column vectors.
 size_t xcd_stream_bytes(int layers, int d, int F);

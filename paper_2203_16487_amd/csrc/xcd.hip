@@ -18,10 +18,13 @@
 // while they are waited for.  (In waves of their own, the requests held up the barriers instead: a verify pass of 352 rows of d = 512
 // took 244 us so, 227 without them.)
 //
-// What bounds it: instructions in a row, which a wave issues one in four to five cycles, some 2 us a stage of 44 rows, and with
-// the weights of d = 1024 what an XCD takes in.  Whole verify passes, launches / the kernel over the whole GPU (persist.hip) / this one,
-// us: d = 512: 6 rows 234 / 136 / 144, 77 251 / 167 / 154, 176 271 / 217 / 185, 352 315 / - / 212; d = 1024: 6 rows 266 / 177
-// / 253, 128 407 / 374 / 392, 176 391 / - / 345, 352 497 / - / 409.  (The rule is in api.hip.)
+// A pass of at most 63 rows of d = 512 needs no such copy: it reads the matrices as bound, a chunk of 16 rows x 128 bytes at a time (DIRECT;
+// 113.6 us for 6 rows, from a copy 112.7).
+//
+// What bounds it: a hand-over and instructions in a row at every stage (of 11 rows 0.8 - 3.5 us, of 44 1.8 - 3.9), and with the weights of d =
+// 1024 what an XCD takes in.  Whole verify passes, launches / the kernel over the whole GPU (persist.hip) / this one, us: d = 512: 6
+// rows 234 / 125 / 114, 77 251 / 167 / 123, 176 271 / 217 / 151, 352 315 / - / 172; d = 1024: 6 rows 266 / 178 / 226, 128 407 / 338 / 344, 176
+// 391 / - / 317, 352 497 / - / 377.  (The rule is in api.hip.)
 //
 // LayerNorm is folded into the products as in the general kernels (gemm.hip), with statistics per 16 columns; the fp32 residual
 // of a workgroup's columns stays in its LDS.  The exchange buffers of two layers are used in turn.  Those of layer l - 1 are
@@ -66,7 +69,7 @@ __device__ __forceinline__ void pl_again(unsigned& spins, const XcdArgs& a) {
   if ((spins & 63u) == 0) {
     // (the same for the whole wave, and said so: no wait is a loop of single lanes)
     const unsigned raised = __builtin_amdgcn_readfirstlane(__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    if (raised != 0u || spins > kPlSpinMax) {
+    if (raised != 0u || spins > a.spin_max) {
       __hip_atomic_store(a.err, kXcdAlonePasses, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       // (weights on their way to LDS: it may be another workgroup's next)
       asm volatile("s_waitcnt vmcnt(0)\n\ts_endpgm" ::: "memory");
@@ -141,8 +144,9 @@ __device__ __forceinline__ int pl_rounds(const XcdArgs& a, const PlPlace& p) {
 }
 
 // What a wave carries along: its stream of weights (the next chunk to request, how many are left, where it goes in the ring, where the
-// next one to use lies) and the sums so far.
-struct PlTurn { const char* next; int left, slot, use, sums; };
+// next one to use lies) and the sums so far.  Where the weights are read in place (XcdArgs::stream null), at[]: the matrices of which this
+// stage requests chunks.
+struct PlTurn { const char* next; int left, slot, use, sums, w; const char* at[2]; };
 __device__ __forceinline__ unsigned pl_lds_addr(const void* p) {
   return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)SD_LDS_PTR(const_cast<void*>(p)));
 }
@@ -155,14 +159,65 @@ __device__ __forceinline__ void pl_dma(const char* base, unsigned voff, unsigned
 template <int D>
 __device__ __forceinline__ PlTurn pl_turn(const XcdArgs& a, int w, int wave, int l, int c, int n) {
   typedef PlDim<D> Dim;
-  return PlTurn{a.stream + ((size_t)((w * kPlWaves + wave) * a.n_layers + l) * Dim::kPerLayer + c) * Dim::kChunk, n, 0, 0, 0};
+  return PlTurn{a.stream + ((size_t)((w * kPlWaves + wave) * a.n_layers + l) * Dim::kPerLayer + c) * Dim::kChunk, n, 0, 0, 0, w, {nullptr, nullptr}};
+}
+// One chunk of a matrix [columns][K] as it is bound: 16 rows of 128 bytes from `from` on (a workgroup's waves read whole rows), two requests of 8 whole
+// lines.  In the ring 16-byte piece c of row r lies at r * 128 + 16 (c ^ (r / 2 % 8)): 16 rows' same piece meets all banks once.  (As fragments,
+// like a chunk of the copy, a request touches half of each of 16 lines: a pass of 6 rows 122.0 us, so 113.6; from a copy in order of use 112.7.)
+template <int D, int MR>
+__device__ __forceinline__ void pl_request_rows(PlLds<D, MR>& L, PlTurn& t, int wave, const char* from, int pitch) {
+  typedef PlDim<D> Dim;
+  static_assert(D != 512 || (Dim::KW == 64 && Dim::kReq == 2), "rows of a line");
+  const int lane = pl_lane();
+  const unsigned to = pl_lds_addr(L.ring) + wave * (Dim::kRing * Dim::kChunk) + t.slot, voff = (lane >> 3) * pitch + (((lane & 7) ^ (lane >> 4)) << 4);
+  pl_dma<0>(from, voff, to);
+  pl_dma<0>(from + 8 * pitch, voff ^ 64, to + 1024);
+  t.slot = t.slot + Dim::kChunk == Dim::kRing * Dim::kChunk ? 0 : t.slot + Dim::kChunk;
+  --t.left;
+}
+// where workgroup w's first chunk of a matrix lies: of one with N column tiles a workgroup, K = KC * D
+template <int D>
+__device__ __forceinline__ const char* pl_rows_at(const void* W, int w, int wave, int N, int KC) {
+  return static_cast<const char*>(W) + (size_t)w * N * (16 * KC * D * 2) + wave * (PlDim<D>::KW * 2);
+}
+// A layer's pointers, for scalar loads (nothing writes them while the kernel runs).
+typedef const __attribute__((address_space(4))) PlLayer* PlLayerPtr;
+__device__ __forceinline__ PlLayerPtr pl_layer(const XcdArgs& a, int l) { return (PlLayerPtr)(uintptr_t)(a.layers + l); }
+// Requests chunks c .. c + n - 1 of layer l (as many as are left).
+template <int D, int MR>
+__device__ __forceinline__ void pl_ask_rows(const XcdArgs& a, PlLds<D, MR>& L, PlTurn& t, int wave, int l, int c, int n) {
+  typedef PlDim<D> Dim;
+  constexpr int kPitch = D * 2;
+  static_assert(Dim::kTD == 1 || D != 512, "one chunk a square matrix");
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the fragments read from the places that are filled again)
+  const PlLayerPtr Y = pl_layer(a, l);
+  for (int e = c + min(n, t.left); c < e; ++c) {
+    const int f = c - (Dim::kTQ + 3), k = f - Dim::kTF;
+    if (c < Dim::kTQ) pl_request_rows(L, t, wave, pl_rows_at<D>(Y->wqkv.p, t.w, wave, Dim::kTQ, 1) + c * 16 * kPitch, kPitch);
+    else if (f < 0) pl_request_rows(L, t, wave, pl_rows_at<D>(f == -3 ? Y->wo.p : f == -2 ? Y->cwq.p : Y->cwo.p, t.w, wave, 1, 1), kPitch);
+    else if (k < 0) pl_request_rows(L, t, wave, pl_rows_at<D>(Y->w1.p, t.w, wave, Dim::kTF, 1) + f * 16 * kPitch, kPitch);
+    else pl_request_rows(L, t, wave, pl_rows_at<D>(Y->w2.p, t.w, wave, 1, Dim::kKC) + k * kPitch, Dim::kKC * kPitch);
+  }
+}
+// The matrices of which stage S of layer l requests chunks (PlDim::kAsk; the last requests the next layer's): their addresses are there long
+// before the stage's rows are.
+template <int D, int S>
+__device__ __forceinline__ void pl_ask_at(const XcdArgs& a, PlTurn& t, int wave, int l) {
+  typedef PlDim<D> Dim;
+  const PlLayerPtr Y = pl_layer(a, S == 7 ? min(l + 1, a.n_layers - 1) : l);
+  auto square = [&](const void* W) { return pl_rows_at<D>(W, t.w, wave, 1, 1); };
+  if (S == 0) { t.at[0] = square(Y->wo.p); t.at[1] = square(Y->cwq.p); }
+  if (S == 1) { t.at[0] = square(Y->cwo.p); t.at[1] = pl_rows_at<D>(Y->w1.p, t.w, wave, Dim::kTF, 1); }
+  if (S >= 2 && S <= 4) t.at[0] = pl_rows_at<D>(Y->w1.p, t.w, wave, Dim::kTF, 1);
+  if (S == 5 || S == 6) t.at[0] = pl_rows_at<D>(Y->w2.p, t.w, wave, 1, Dim::kKC);
+  if (S == 7) t.at[0] = pl_rows_at<D>(Y->wqkv.p, t.w, wave, Dim::kTQ, 1);
 }
 // Requests the next n chunks there are.
 template <int D, int MR>
-__device__ __forceinline__ void pl_ask(PlLds<D, MR>& L, PlTurn& t, int wave, int n) {
+__device__ __forceinline__ void pl_ask_next(PlLds<D, MR>& L, PlTurn& t, int wave, int n) {
   typedef PlDim<D> Dim;
   const unsigned ring = pl_lds_addr(L.ring) + wave * (Dim::kRing * Dim::kChunk), voff = pl_lane() * 16;
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the fragments read from the places that are filled again)
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (as above)
   for (int i = min(n, t.left); i > 0; --i) {
     pl_dma<0>(t.next, voff, ring + t.slot);
     if constexpr (Dim::kReq > 1) pl_dma<1024>(t.next, voff, ring + t.slot);
@@ -174,6 +229,22 @@ __device__ __forceinline__ void pl_ask(PlLds<D, MR>& L, PlTurn& t, int wave, int
     t.next += Dim::kChunk;
     t.slot = t.slot + Dim::kChunk == Dim::kRing * Dim::kChunk ? 0 : t.slot + Dim::kChunk;
     --t.left;
+  }
+}
+// Requests number FIRST .. FIRST + N - 1 of stage S.
+template <int D, int MR, int S, int FIRST, int N>
+__device__ __forceinline__ void pl_ask(const XcdArgs& a, PlLds<D, MR>& L, PlTurn& t, int wave) {
+  if (D != 512 || a.stream) return pl_ask_next(L, t, wave, N);
+  if (N == 0 || t.left == 0) return;
+  constexpr int kRows = 16 * D * 2;   // to a matrix's next column tile
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int i = FIRST; i < FIRST + N; ++i) {
+    if (S == 0) pl_request_rows(L, t, wave, t.at[i], D * 2);
+    else if (S == 1) pl_request_rows(L, t, wave, t.at[i], D * 2);
+    else if (S <= 4) pl_request_rows(L, t, wave, t.at[0] + (S - 1) * kRows, D * 2);
+    else if (S <= 6) pl_request_rows(L, t, wave, t.at[0] + (S == 5 ? 0 : 1 + i) * (D * 2), PlDim<D>::kKC * D * 2);
+    else pl_request_rows(L, t, wave, t.at[0] + i * kRows, D * 2);
   }
 }
 // Requests the column vectors of layer l (a request each of the first waves).
@@ -189,16 +260,22 @@ __device__ __forceinline__ void pl_ask_vectors(const XcdArgs& a, PlLds<D, MR>& L
 // The fragments of the next chunk, once it is there.  AHEAD: chunks that may have been requested after it
 // (< 0: it was requested before rows that have arrived).
 template <int D, int MR, int AHEAD>
-__device__ __forceinline__ void pl_weights(PlLds<D, MR>& L, PlTurn& t, int wave, int lane, bf16x8 (&wf)[PlDim<D>::KS]) {
+__device__ __forceinline__ void pl_weights(const XcdArgs& a, PlLds<D, MR>& L, PlTurn& t, int wave, int lane, bf16x8 (&wf)[PlDim<D>::KS]) {
   typedef PlDim<D> Dim;
   if constexpr (AHEAD >= 0) {   // (what else is in flight only makes this stricter)
     if (t.left > 0) wait_vmcnt<AHEAD * Dim::kReq>();
     else wait_vmcnt<0>();
     asm volatile("" ::: "memory");
   }
-  const char* c = L.ring[wave] + t.use + lane * 16;
+  const char* c = L.ring[wave] + t.use;
+  if (D != 512 || a.stream) {
 #pragma unroll
-  for (int u = 0; u < Dim::KS; ++u) wf[u] = *reinterpret_cast<const bf16x8*>(c + u * 1024);
+    for (int u = 0; u < Dim::KS; ++u) wf[u] = *reinterpret_cast<const bf16x8*>(c + lane * 16 + u * 1024);
+  } else {   // (see pl_request_rows)
+    const int lq = lane & 15, o = lq * 128 + (((lane >> 4) ^ (lq >> 1)) << 4);
+#pragma unroll
+    for (int u = 0; u < Dim::KS; ++u) wf[u] = *reinterpret_cast<const bf16x8*>(c + (o ^ (u * 64)));
+  }
   t.use = t.use + Dim::kChunk == Dim::kRing * Dim::kChunk ? 0 : t.use + Dim::kChunk;
 }
 
@@ -424,7 +501,7 @@ __device__ __forceinline__ void pl_project(const XcdArgs& a, PlLds<D, MR>& L, Pl
     f32x4 acc[NT][MR];
     auto tile = [&](auto ahead, int i) {
       bf16x8 wf[Dim::KS];
-      pl_weights<D, MR, decltype(ahead)::value>(L, t, wave, lane, wf);
+      pl_weights<D, MR, decltype(ahead)::value>(a, L, t, wave, lane, wf);
 #pragma unroll
       for (int mr = 0; mr < MR; ++mr) acc[i][mr] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -442,7 +519,7 @@ __device__ __forceinline__ void pl_project(const XcdArgs& a, PlLds<D, MR>& L, Pl
     static_assert(NT <= 4 && NT <= Dim::kRing, "a batch");
     struct Have { f32x4 c, b; };
     // (ahead of the sum, so that the next stage's rows are waited for behind less of it: 352 rows of d = 512 188.9 -> 186.7 us)
-    pl_ask<D, MR>(L, t, wave, Dim::kAsk[S] * (CT + NT) / N - Dim::kAsk[S] * CT / N);
+    pl_ask<D, MR, S, Dim::kAsk[S] * CT / N, Dim::kAsk[S] * (CT + NT) / N - Dim::kAsk[S] * CT / N>(a, L, t, wave);
     pl_reduce<D, MR, NT>(L, t, wave, lane, acc,
       [&](int i, int) {
         const float* v = cs + (CT + i) * 16 + 4 * g;
@@ -474,12 +551,13 @@ __device__ __forceinline__ void pl_project(const XcdArgs& a, PlLds<D, MR>& L, Pl
   static_assert(N <= 8 * NB, "batches");
 }
 
-// residual sum on the workgroup's columns: y = LN_prev(x) + A W^T + b; K = KC * D.  vecs: the three column vectors (LDS); resid(mr, ct):
+// residual sum of stage S on the workgroup's columns: y = LN_prev(x) + A W^T + b; K = KC * D.  vecs: the three column vectors (LDS); resid(mr, ct):
 // where lane's part of x is and y goes; out(row, column of the workgroup, y) on live rows.
-template <int D, int MR, int KC, class Resid, class Out>
+template <int D, int MR, int S, class Resid, class Out>
 __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn& t, const char* A, const float* stat, int rows,
                                        const float* vecs, Resid&& resid, Out&& out) {
   typedef PlDim<D> Dim;
+  constexpr int KC = S == 7 ? Dim::kKC : 1;
   const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
   const PlRows<D, MR> R(a, A, false, rows, lane, wave);
   constexpr int SETS = MR * Dim::KS * KC <= 32 ? KC : MR * Dim::KS <= 16 ? 2 : 1, TD = Dim::kTD;   // chunks of K of which rows are held
@@ -510,9 +588,9 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
 #pragma unroll
     for (int ct = 0; ct < TD; ++ct) {
       bf16x8 wf[Dim::KS];
-      if (kc * TD + ct < Dim::kRing) pl_weights<D, MR, -1>(L, t, wave, lane, wf);
-      else if (kc + 1 < KC || ct % GT == 0) pl_weights<D, MR, Dim::kRing - 1>(L, t, wave, lane, wf);
-      else pl_weights<D, MR, Dim::kRing - 2>(L, t, wave, lane, wf);   // (the sum's tiles ask together, behind the last)
+      if (kc * TD + ct < Dim::kRing) pl_weights<D, MR, -1>(a, L, t, wave, lane, wf);
+      else if (kc + 1 < KC || ct % GT == 0) pl_weights<D, MR, Dim::kRing - 1>(a, L, t, wave, lane, wf);
+      else pl_weights<D, MR, Dim::kRing - 2>(a, L, t, wave, lane, wf);   // (the sum's tiles ask together, behind the last)
 #pragma unroll
       for (int u = 0; u < Dim::KS; ++u)
 #pragma unroll
@@ -520,12 +598,13 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
           acc[ct / GT][ct % GT][mr] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[u], __builtin_bit_cast(bf16x8, now[mr][u]),
                                                                               acc[ct / GT][ct % GT][mr], 0, 0, 0);
       if (kc + 1 < KC) {   // (a product of few chunks asks for the next ones at its end, all at once)
-        if (KC * TD > Dim::kRing) pl_ask<D, MR>(L, t, wave, 1);
+        if (KC * TD > Dim::kRing) pl_ask<D, MR, S, 0, 1>(a, L, t, wave);
         continue;
       }
       if ((ct + 1) % GT != 0) continue;
       struct Have { f32x4 v[3], x; };
-      pl_ask<D, MR>(L, t, wave, KC * TD > Dim::kRing ? GT : ct + 1 == TD ? Dim::kAsk[KC == 1 ? 2 : 7] : 0);
+      if (KC * TD > Dim::kRing) pl_ask<D, MR, S, 0, GT>(a, L, t, wave);
+      else if (ct + 1 == TD) pl_ask<D, MR, S, 0, Dim::kAsk[S]>(a, L, t, wave);
       pl_reduce<D, MR, GT>(L, t, wave, lane, acc[ct / GT],
         [&](int i, int mr) {
           const int tile = ct / GT * GT + i;
@@ -808,7 +887,7 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
     lds_barrier();
     // what is requested goes behind all waves' keys and values, and behind the merge on the waves that have a share of it
     auto ask = [&] {
-      if (r + 1 == rounds) pl_ask<D, MR>(L, turn, wave, PlDim<D>::kAsk[SELF ? 1 : 4]);
+      if (r + 1 == rounds) pl_ask<D, MR, SELF ? 1 : 4, 0, PlDim<D>::kAsk[SELF ? 1 : 4]>(a, L, turn, wave);
     };
     if (used <= 1 || kw >= 4) ask();
     auto merge = [&](auto most) {
@@ -852,7 +931,8 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
 // KV8: cross-attention keys / values as E4M3 codes.
 // MR: row tiles of a group.
 // ALONE: see the head of this file; the residual in memory instead of LDS.
-template <bool KV8, int D, int MR, bool ALONE>
+// DIRECT: the weights read in place (d = 512, a few rows).
+template <bool KV8, int D, int MR, bool ALONE, bool DIRECT>
 __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char pl_smem[];
   typedef PlLds<D, MR> Lds;
@@ -861,6 +941,8 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
   Lds& L = *reinterpret_cast<Lds*>(pl_smem);
   if (!ALONE) a.RP = 16 * MR;   // known when compiled: every place in the exchange buffers is then a constant away from the layer's
   a.H = D / kHeadDim;
+  if (DIRECT) a.stream = nullptr; else a.spin_max = kPlSpinMax;   // (as an argument the bound costs 0.1 - 0.6 % of a pass)
+  if (!ALONE && !DIRECT) __builtin_assume(a.stream != nullptr);
   // (one look for all waves: others may raise the flag meanwhile, and none of a workgroup's waves is to go on without the rest)
   if (threadIdx.x == 0) L.row_at[0] = (int)__hip_atomic_load(a.raised, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
@@ -888,6 +970,13 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     // a wave issued 500 instructions a stage, half of them scalar.  Whole verify passes, us, with all that / without: d = 512, 77 rows
     // 149.3 / 133.9, 352 rows 198.4 / 188.9; d = 1024, 352 rows of long sources 544 / 530, 209 rows 422 / 408.
     asm volatile("" : "+s"(l));
+    if constexpr (DIRECT) {
+      if (s == 0) pl_ask_at<D, 0>(a, turn, wave, l);
+      if (s == 1) pl_ask_at<D, 1>(a, turn, wave, l);
+      if (s == 2 || s == 3 || s == 4) pl_ask_at<D, 2>(a, turn, wave, l);
+      if (s == 5 || s == 6) pl_ask_at<D, 5>(a, turn, wave, l);
+      if (s == 7) pl_ask_at<D, 7>(a, turn, wave, l);
+    }
     const PlExch ex(a.exch + (at.g * 2 + (l & 1)) * pl_layer_bytes(a.RP, D, 4 * D), a.RP, D);
     const PlExch before(a.exch + (at.g * 2 + (~l & 1)) * pl_layer_bytes(a.RP, D, 4 * D), a.RP, D);
     const float* vec = L.vec[l & 1];
@@ -959,15 +1048,16 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
                            __builtin_bit_cast(unsigned, fmaxf(ss - sum * sum * (1.0f / 16), 0.f)));
     };
     const float* vecs = vec + Dim::kVecS + i * 3 * Dim::kND;
-    if (s == 7) return pl_sum<D, MR, Dim::kKC>(a, L, turn, ex.hid(), stat, at.rows, vecs, resid, out);
-    pl_sum<D, MR, 1>(a, L, turn, ex.att(i), stat, at.rows, vecs, resid, out);
-    if (!ALONE && s == 2 && l > 0 && l + 1 < a.n_layers) {   // nobody reads the layer before any more
+    if (s == 7) return pl_sum<D, MR, 7>(a, L, turn, ex.hid(), stat, at.rows, vecs, resid, out);
+    if (s == 5) return pl_sum<D, MR, 5>(a, L, turn, ex.att(i), stat, at.rows, vecs, resid, out);
+    pl_sum<D, MR, 2>(a, L, turn, ex.att(i), stat, at.rows, vecs, resid, out);
+    if (!ALONE && l > 0 && l + 1 < a.n_layers) {   // nobody reads the layer before any more
       const u32x4 poison = {kPoison, kPoison, kPoison, kPoison};
       const int bytes = (int)(pl_layer_bytes(a.RP, D, 4 * D) / kPlMembers);
       for (int o = (wave * 64 + pl_lane()) * 16; o < bytes; o += kPlWaves * 1024) *reinterpret_cast<u32x4*>(before.base + at.w * bytes + o) = poison;
     }
     // (what every wave asks for and stores here is done with when it has its rows of stage 3, for the workgroup at the barriers there)
-    if (!ALONE && s == 2 && l + 1 < a.n_layers) pl_ask_vectors<D, MR>(a, L, l + 1, at.w, wave);
+    if (!ALONE && l + 1 < a.n_layers) pl_ask_vectors<D, MR>(a, L, l + 1, at.w, wave);
   };
   if constexpr (!ALONE) {
     for (int i = threadIdx.x; i < Dim::kTD * 16 * MR * 4; i += kPlThreads) {   // the residual: embedded rows
@@ -977,7 +1067,8 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     }
     __syncthreads();
     pl_ask_vectors<D, MR>(a, L, 0, at.w, wave);
-    pl_ask<D, MR>(L, turn, wave, Dim::kAskFirst);
+    if constexpr (DIRECT) pl_ask_rows<D, MR>(a, L, turn, wave, 0, 0, Dim::kAskFirst);
+    else pl_ask_next<D, MR>(L, turn, wave, Dim::kAskFirst);
     wait_vmcnt<Dim::kAskFirst * Dim::kReq>();   // the vectors
     __syncthreads();
     for (int l = 0; l < a.n_layers; ++l) {
@@ -1001,7 +1092,8 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
       for (int e = 0; e < s; ++e) c += pl_chunks<Dim>(e);
       turn = pl_turn<D>(a, at.w, wave, l, c, pl_chunks<Dim>(s));
       pl_ask_vectors<D, MR>(a, L, l, at.w, wave);
-      pl_ask<D, MR>(L, turn, wave, Dim::kRing);
+      if (D == 512 && !a.stream) pl_ask_rows<D, MR>(a, L, turn, wave, l, c, Dim::kRing);
+      else pl_ask_next<D, MR>(L, turn, wave, Dim::kRing);
       wait_vmcnt<0>();
       __syncthreads();
       stage(s, l);
@@ -1058,10 +1150,11 @@ size_t xcd_vec_bytes(int layers, int d) {
 }
 template <int D>
 static hipError_t pack(hipStream_t st, const PlLayer* layers, int n, char* stream, float* vecs) {
-  hipLaunchKernelGGL(xcd::pl_pack_kernel<D>, dim3(xcd::kPlMembers * xcd::kPlWaves * n * xcd::PlDim<D>::kPerLayer), dim3(64), 0, st, layers, n, stream);
+  if (stream) hipLaunchKernelGGL(xcd::pl_pack_kernel<D>, dim3(xcd::kPlMembers * xcd::kPlWaves * n * xcd::PlDim<D>::kPerLayer), dim3(64), 0, st, layers, n, stream);
   hipLaunchKernelGGL(xcd::pl_pack_vectors_kernel<D>, dim3(n * xcd::kPlMembers), dim3(256), 0, st, layers, vecs);
   return hipGetLastError();
 }
+// (stream null: column vectors alone)
 hipError_t xcd_pack(hipStream_t st, const PlLayer* layers, int n, int d, char* stream, float* vecs) {
   return d == 512 ? pack<512>(st, layers, n, stream, vecs) : pack<1024>(st, layers, n, stream, vecs);
 }
@@ -1072,26 +1165,31 @@ static int pl_group_rows(int B, int T) { return ((B + kPlGroups - 1) / kPlGroups
 // Exchange buffers of two layers for every group.
 static size_t pl_exch_bytes(int B, int RP, int d, int F) { return (size_t)(B < kPlGroups ? B : kPlGroups) * 2 * pl_layer_bytes(RP, d, F); }
 
-template <bool KV8, int D, int MR, bool ALONE>
+template <bool KV8, int D, int MR, bool ALONE, bool DIRECT = false>
 static hipError_t pl_launch(hipStream_t st, const XcdArgs& a, int blocks) {
   constexpr int kBytes = (int)sizeof(PlLds<D, MR>);
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pl_decoder_kernel<KV8, D, MR, ALONE>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pl_decoder_kernel<KV8, D, MR, ALONE, DIRECT>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
   if (attr != hipSuccess) return attr;
-  SD_LAUNCH_TIMED((pl_decoder_kernel<KV8, D, MR, ALONE>), dim3(blocks), dim3(kPlThreads), kBytes, st, a);
+  SD_LAUNCH_TIMED((pl_decoder_kernel<KV8, D, MR, ALONE, DIRECT>), dim3(blocks), dim3(kPlThreads), kBytes, st, a);
   return hipGetLastError();
 }
 // the pass, and its second run by a workgroup a group
 template <bool KV8, int D>
 static hipError_t pl_launch_both(hipStream_t st, XcdArgs a, int blocks) {
   hipError_t e = hipErrorInvalidValue;
-  switch (a.RP / 16) {
-    case 1:   // (128 rows at most: with d = 1024 the decoder over the whole GPU takes them)
-      if constexpr (D == 512) e = pl_launch<KV8, D, 1, false>(st, a, blocks);
-      break;
-    case 2: e = pl_launch<KV8, D, 2, false>(st, a, blocks); break;
-    case 3: e = pl_launch<KV8, D, 3, false>(st, a, blocks); break;
-    case 4: e = pl_launch<KV8, D, 4, false>(st, a, blocks); break;
+  if constexpr (D == 512) {
+    if (!a.stream) {   // (63 rows at most: 32 of a group)
+      if (a.RP == 16) e = pl_launch<KV8, D, 1, false, true>(st, a, blocks);
+      if (a.RP == 32) e = pl_launch<KV8, D, 2, false, true>(st, a, blocks);
+    } else if (a.RP == 16) {   // (128 rows at most: with d = 1024 the decoder over the whole GPU takes them)
+      e = pl_launch<KV8, D, 1, false>(st, a, blocks);
+    }
+  }
+  if (a.stream) {
+    if (a.RP == 32) e = pl_launch<KV8, D, 2, false>(st, a, blocks);
+    if (a.RP == 48) e = pl_launch<KV8, D, 3, false>(st, a, blocks);
+    if (a.RP == 64) e = pl_launch<KV8, D, 4, false>(st, a, blocks);
   }
   if (e != hipSuccess) return e;
   a.err += 1;
@@ -1130,6 +1228,7 @@ hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F, bool give_up) {
   // give_up: a place of every group stays empty, as where other kernels hold compute units: the waits for it end at their bound.  (A bound
   // passed as an argument, or where a wait's count starts, cost 0.1 - 0.6 % of every pass.)
   const int blocks = give_up ? kPlBlocks - xcd::kPlGroups : kPlBlocks;
+  a.spin_max = give_up ? 63 : xcd::kPlSpinMax;   // (weights in place; after a look at the flag)
   if (d == 512) return a.xk_scale ? xcd::pl_launch_both<true, 512>(st, a, blocks) : xcd::pl_launch_both<false, 512>(st, a, blocks);
   return a.xk_scale ? xcd::pl_launch_both<true, 1024>(st, a, blocks) : xcd::pl_launch_both<false, 1024>(st, a, blocks);
 }
