@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(AttnArgs a) {
 // are exchanged once per tile, row sums once per pass, masking happens only on tiles a limit cuts, accumulators are rescaled only when some
 // maximum has moved by more than kSlack (at every move, which with 32 rows is nearly every tile: 188 us in place of 177 below).  120 registers,
 // four waves a SIMD; with 140, three of them, 205 us.
-// 32 x 16 heads, 1024 queries on 1024 keys: 177 us in an encoder (776 TFLOP/s), 775 with the kernel above, whose waves fetch keys and values
+// 32 x 16 heads, 1024 queries on 1024 keys: 163 us in an encoder (843 TFLOP/s), 775 with the kernel above, whose waves fetch keys and values
 // one by one.
 constexpr int kTileQ = 128, kTileK = 64;
 
@@ -145,22 +145,36 @@ __global__ __launch_bounds__(256, 3) void attn_tile_kernel(AttnArgs a, int qgrou
 
   const bf16* kbase = a.k + (a.kv_off ? (long)a.kv_off[b] * a.k_row : b * a.k_b) + h * a.k_h;
   const bf16* vbase = a.v + (a.kv_off ? (long)a.kv_off[b] * a.v_row : b * a.v_b) + h * a.v_h;
-  // request i of a wave moves rows 8 (4 wave + i) .. + 7 of the K rows (i < 2) / V rows of a tile
-  const int r0 = wave * 16 + (lane >> 3);
+  // Request i of a wave moves rows 16 wave + 8 i .. + 7 of a tile's keys or values.  A lane's offsets from a tile's first row are the same for
+  // every tile but one that the last key cuts, and the tile's own place is scalar (row strides are whole lines): with an address a lane
+  // and request, 25 instructions more a tile, 168 us in place of 163 below.
+  const int row0 = wave * 16 + (lane >> 3), kpitch = a.k_row * 2, vpitch = a.v_row * 2;
+  const unsigned kpiece = ((lane & 7) ^ (lane >> 4)) << 4, vpiece = ((lane & 7) ^ ((lane >> 2) & 4)) << 4;   // row 8 i on: keys ^ 64, values the same
+  const unsigned koff = row0 * kpitch + kpiece, voff = row0 * vpitch + vpiece;
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)SD_LDS_PTR(&smem[0][0][0])) + wave * 2048;
   auto stage = [&](int c0, int buf) {
+    const bf16* kt = kbase + (long)c0 * a.k_row;
+    const unsigned l = lds0 + buf * (2 * kTileK * 128);
+    const bool whole = c0 + kTileK <= kend;
+    if (whole) {
+      dma16(kt, koff, l);
+      dma16(kt + 8 * a.k_row, koff ^ 64, l + 1024);
+    } else {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int r = r0 + 8 * i, key = min(c0 + r, kend - 1);
-      dma16(kbase + (long)key * a.k_row + (((lane & 7) ^ ((r >> 1) & 7)) << 3), &smem[buf][0][(wave * 16 + 8 * i) * 64]);
+      for (int i = 0; i < 2; ++i) dma16(kt, min(row0 + 8 * i, kend - 1 - c0) * kpitch + (kpiece ^ (i * 64)), l + i * 1024);
     }
+    if constexpr (VBLK) {   // 1 KB = one block of 8 keys
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      if constexpr (VBLK) {   // 1 KB = one block of 8 keys
-        const int blk = min((c0 >> 3) + wave * 2 + i, (a.cap >> 3) - 1);
-        dma16(vbase + (long)blk * (8 * kHeadDim) + lane * 8, &smem[buf][1][(wave * 2 + i) * 512]);
+      for (int i = 0; i < 2; ++i)
+        dma16(vbase + (long)min((c0 >> 3) + wave * 2 + i, (a.cap >> 3) - 1) * (8 * kHeadDim), lane * 16, l + kTileK * 128 + i * 1024);
+    } else {
+      const bf16* vt = vbase + (long)c0 * a.v_row;
+      if (whole) {
+        dma16(vt, voff, l + kTileK * 128);
+        dma16(vt + 8 * a.v_row, voff, l + kTileK * 128 + 1024);
       } else {
-        const int r = r0 + 8 * i, key = min(c0 + r, kend - 1);
-        dma16(vbase + (long)key * a.v_row + (((lane & 7) ^ ((r & 2) << 1)) << 3), &smem[buf][1][(wave * 16 + 8 * i) * 64]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) dma16(vt, min(row0 + 8 * i, kend - 1 - c0) * vpitch + vpiece, l + kTileK * 128 + i * 1024);
       }
     }
   };
