@@ -253,54 +253,114 @@ __global__ __launch_bounds__(kSkThreads) void sk_ffn2_kernel(SkSrc resid, int R,
 }
 
 // ------------------------------------------------------------------------------------ vocabulary
-// Every block first forms the draft logits itself (waves 0 and 1, the sk_draft_logit sequence on
-// its own copy of the hidden rows: the same bits in every block, and the bits its own tile would
-// hold for that column), so the rank counts need no launch of their own before this one.
+// A block of eight waves, one to a CU, takes two tiles of 64 columns.  It normalises all rows (four a wave, one memory round trip) and forms
+// the draft logits itself, on its own copy of the hidden rows, so neither needs a launch of its own: D[i][j] = E[draft of row 16 t + i] . h[16 t + j] on
+// wave t, with the instruction and k order of the projection, hence bit-identical to the element that the projection holds for that
+// (row, column); the diagonal is kept.  Requested in the order of use: draft ids, rows, the drafts' embedding rows (to LDS), then the whole weight
+// tile, which so arrives under the LayerNorm and never waits for registers.
+// With four waves to 64 columns, two blocks a CU, every CU normalised all rows twice, two waves held the drafts' rows in registers that the weights
+// then lacked, and half of d = 1024's were asked for only behind the first products.  Launches, us: 6 rows of d = 512 13.4, now 8.5; 26 rows of d
+// = 1024, 8-bit weights 29.0, now 17.4.
+constexpr int kSkVocabThreads = 512;
 template <int PER, bool TWO, class WT>
-__global__ __launch_bounds__(kSkThreads) void sk_vocab_kernel(SkSrc src, int R, const WT* __restrict__ E,
-                                                              const float* __restrict__ wscale, int V,
-                                                              const int* __restrict__ row_draft,
-                                                              float* __restrict__ zd_out,
-                                                              float* __restrict__ part, int n_tiles,
-                                                              float* __restrict__ logits) {
+struct SkVocabLds {
+  static constexpr int d = 64 * PER, kRows = TWO ? 32 : 16;
+  bf16 hb[kRows][d + kSkPad];
+  WT emb[kRows][d + 16 / sizeof(WT)];       // (16 bytes of padding a row)
+  float zds[kSkRows], red[kSkVocabThreads / 64 * 32 * 4];
+};
+template <int PER, bool TWO, class WT>
+__global__ __launch_bounds__(kSkVocabThreads) void sk_vocab_kernel(SkSrc src, int R, const WT* __restrict__ E,
+                                                                   const float* __restrict__ wscale, int V,
+                                                                   const int* __restrict__ row_draft,
+                                                                   float* __restrict__ zd_out,
+                                                                   float* __restrict__ part, int n_tiles,
+                                                                   float* __restrict__ logits) {
   extern __shared__ __attribute__((aligned(16))) char sk_smem[];
-  SkLds<PER> L(sk_smem);
-  constexpr int d = 64 * PER, pitch = d + kSkPad;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lq = lane & 15;
-  const int n0 = blockIdx.x * 64 + wave * 16;
-  constexpr int steps = d / 32, S1 = steps < kSkW ? steps : kSkW;
-  typename SkFrag<WT>::type wf[S1];
-  const int dtok = sk_draft_tok(R, row_draft);   // first: the draft's embedding row then travels with the tile
-  sk_wload<S1>(E, d, n0, V, 0, wf);
-  SkDraft<PER, WT> dr;
-  sk_draft_fetch<PER, WT>(dr, R, E, V, dtok, wscale);
+  typedef SkVocabLds<PER, TWO, WT> Lds;
+  Lds& L = *reinterpret_cast<Lds*>(sk_smem);
+  constexpr int d = 64 * PER, pitch = d + kSkPad, steps = d / 32, ROWS = Lds::kRows;
+  constexpr int PIECES = d * (int)sizeof(WT) / 16, NE = (ROWS * PIECES + kSkVocabThreads - 1) / kSkVocabThreads;   // 16-byte pieces of a row; a thread's
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
+  const int n0 = blockIdx.x * 128 + wave * 16;
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  int tok[NE];
+#pragma unroll
+  for (int i = 0; i < NE; ++i) tok[i] = row_draft[min((int)(threadIdx.x + i * kSkVocabThreads) / PIECES, R - 1)];
+  const int mine = row_draft[min((wave & 1) * 16 + lq, R - 1)];   // (waves 0 and 1: the draft of the lane's row)
+  SkHidden<PER, ROWS / 8, 8> hs;
+  const bool sum = src.np > 0;   // (same for the whole grid)
+  if (!sum) {
+    hs.params(src);
+    hs.load(src, R, wave);
+  }
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  i32x4 e[NE];
+#pragma unroll
+  for (int i = 0; i < NE; ++i) {
+    const int t = tok[i] >= 0 && tok[i] < V ? tok[i] : 0;
+    e[i] = *reinterpret_cast<const i32x4*>(reinterpret_cast<const char*>(E + (size_t)t * d) + (threadIdx.x + i * kSkVocabThreads) % PIECES * 16);
+  }
+  const bool has = mine >= 0 && mine < V;
+  const float dscale = sk_wscale<WT>(wscale, has ? mine : 0);
   float ws[4];   // this lane's columns n0 + 4 (lane / 16) + r
 #pragma unroll
-  for (int r = 0; r < 4; ++r) ws[r] = sk_wscale<WT>(wscale, min(n0 + 4 * (lane >> 4) + r, V - 1));
-  sk_hidden<PER>(src, R, TWO ? 32 : 16, L.hb, L.hown, -64, true);
-  __syncthreads();
-  float* zds = L.hown;   // [32] (the residual slices are not used by this kernel)
-  sk_draft_logit<PER, WT>(dr, L.hb, R, [&](int row, float v) {
-    zds[row] = v;
-    if (blockIdx.x == 0) zd_out[row] = v;
-  });
+  for (int r = 0; r < 4; ++r) ws[r] = sk_wscale<WT>(wscale, min(n0 + 4 * g + r, V - 1));
+  // (64 registers of them; bf16 at d = 1024: the second half where the rows were)
+  constexpr int S1 = steps * (int)sizeof(typename SkFrag<WT>::type) <= 256 ? steps : steps / 2, S2 = steps - S1;
+  typename SkFrag<WT>::type wf[S1], wf2[S2 > 0 ? S2 : 1];
+  sk_wload<S1>(E, d, n0, V, 0, wf);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  if (sum) sk_hidden_sum<PER, 8, PER>(src, R, ROWS, &L.hb[0][0], nullptr, -64, true, -64);
+  else hs.finish(src, R, ROWS, wave, &L.hb[0][0], nullptr, -64, true, -64);
+#pragma unroll
+  for (int i = 0; i < NE; ++i) {
+    const int p = threadIdx.x + i * kSkVocabThreads;
+    if (p < ROWS * PIECES) *reinterpret_cast<i32x4*>(reinterpret_cast<char*>(&L.emb[p / PIECES][0]) + p % PIECES * 16) = e[i];
+  }
+  if constexpr (S2 > 0) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    sk_wload<S2>(E, d, n0, V, S1 * 32, wf2);
+  }
+  lds_barrier();
+  const bf16* hb = &L.hb[0][0];
+  if (wave < ROWS / 16) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int s = 0; s < steps; ++s) {
+      const bf16x8 hf = *reinterpret_cast<const bf16x8*>(hb + (wave * 16 + lq) * pitch + s * 32 + 8 * g);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sk_frag(*reinterpret_cast<const typename SkFrag<WT>::type*>(&L.emb[wave * 16 + lq][s * 32 + 8 * g])), hf, acc, 0, 0, 0);
+    }
+    mfma_settle(acc);
+    // D[i][j]: this lane holds j = lq, i = 4g + r; diagonal i = j  <=>  g == lq/4, r = lq%4
+    if (g == (lq >> 2) && wave * 16 + lq < R) {
+      float v = 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) if (r == (lq & 3)) v = acc[r];
+      v = has ? v * dscale : kNegInf;   // (the row scale multiplies the sum exactly as the projection does for that column)
+      L.zds[wave * 16 + lq] = v;
+      if (blockIdx.x == 0) zd_out[wave * 16 + lq] = v;
+    }
+  }
   f32x4 acc[2];
   sk_zero(acc);
-  const bf16* hb = L.hb;
   auto getB = [&](int t, int k) { return *reinterpret_cast<const bf16x8*>(hb + (t * 16 + lq) * pitch + k); };
   sk_mma<S1, TWO>(wf, 0, getB, acc);
-  sk_mma_tail<steps, TWO>(E, d, n0, V, 0, getB, acc);
+  if constexpr (S2 > 0) sk_mma<S2, TWO>(wf2, S1 * 32, getB, acc);
   if constexpr (!std::is_same<WT, bf16>::value) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[t][r] *= ws[r];
   }
-  __syncthreads();
+  lds_barrier();
   float zd[2];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) zd[t] = (t * 16 + lq < R) ? zds[t * 16 + lq] : kNegInf;
-  sk_vocab_tile(acc, n0, V, R, zd, L.red, part, n_tiles, blockIdx.x, logits);
+  for (int t = 0; t < 2; ++t) zd[t] = (t * 16 + lq < R) ? L.zds[t * 16 + lq] : kNegInf;
+  sk_vocab_tile(acc, n0, V, R, zd, L.red, part, n_tiles, blockIdx.x * 2, logits);
 }
 
 // ------------------------------------------------------------------------------------ launchers
@@ -346,7 +406,8 @@ static hipError_t sk_init_rows() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)sk_ffn2_lds_bytes<PER, 16, TWO>())) != hipSuccess) return e;
   if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(sk_ffn2_kernel<PER, 32, TWO, WT>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)sk_ffn2_lds_bytes<PER, 32, TWO>())) != hipSuccess) return e;
-  if ((e = sk_attr<PER>(sk_vocab_kernel<PER, TWO, WT>)) != hipSuccess) return e;
+  if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(sk_vocab_kernel<PER, TWO, WT>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)sizeof(SkVocabLds<PER, TWO, WT>))) != hipSuccess) return e;
   return hipSuccess;
 }
 
@@ -409,8 +470,8 @@ hipError_t skinny_vocab(hipStream_t st, const SkSrc& src, int R, int d, SkWeight
                         float* zd_row, float* part, float* logits) {
   const int n_tiles = (V + 63) / 64;
   SK_DISPATCH(d, {
-    SK_ROWS(R, SK_WT(E, hipLaunchKernelGGL((sk_vocab_kernel<PER, TWO, WT>), dim3(n_tiles), dim3(kSkThreads),
-                                           SkLds<PER>::kBytesNoAttn, st, src, R, Wp, E.scale, V, row_draft, zd_row,
+    SK_ROWS(R, SK_WT(E, hipLaunchKernelGGL((sk_vocab_kernel<PER, TWO, WT>), dim3((n_tiles + 1) / 2), dim3(kSkVocabThreads),
+                                           sizeof(SkVocabLds<PER, TWO, WT>), st, src, R, Wp, E.scale, V, row_draft, zd_row,
                                            part, n_tiles, logits)));
   });
   return hipGetLastError();

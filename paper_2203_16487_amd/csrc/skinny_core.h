@@ -412,79 +412,15 @@ __device__ __forceinline__ void sk_reduce(const f32x4 (&acc)[2], float* red, int
   }
 }
 
-// Logit of the draft each row scores: D[i][j] = E[draft of row 16t+i] . h[16t+j] (wave t < 2)
-// with the same instruction and k order as the vocabulary projection, hence bit-identical to
-// the element the projection produces for that (row, column); the diagonal is kept.
-// Two parts: sk_draft_fetch requests the embedding rows of the drafts (first the draft ids,
-// then the rows: two round trips that run while the caller's prologue does), sk_draft_logit
-// multiplies once the hidden rows are in LDS.
-template <int PER, class WT = bf16>
-struct SkDraft {
-  static constexpr int kSteps = 2 * PER;   // d / 32
-  typename SkFrag<WT>::type wf[kSteps];
-  float scale;                             // row scale of the draft's embedding row (1 for bf16 weights)
-  bool has;
-};
-// The draft of this lane's row (waves 0 and 1: row wave*16 + lane%16; others: -1).  Requested on its own,
-// before the block's weight tile, so that waiting for it does not wait for the tile and the draft's
-// embedding row is fetched while the tile streams in.
-__device__ __forceinline__ int sk_draft_tok(int R, const int* __restrict__ row_draft) {
-  const int wave = threadIdx.x >> 6;
-  if (wave >= 2) return -1;
-  return row_draft[min(wave * 16 + (int)(threadIdx.x & 15), R - 1)];
-}
-template <int PER, class WT>
-__device__ __forceinline__ void sk_draft_fetch(SkDraft<PER, WT>& dr, int R, const WT* __restrict__ E, int V, int tok,
-                                               const float* __restrict__ wscale) {
-  constexpr int d = 64 * PER;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lq = lane & 15, g = lane >> 4;
-  dr.has = false;
-  if (wave >= 2) return;
-  const int row = wave * 16 + lq;
-  dr.has = row < R && tok >= 0 && tok < V;
-  dr.scale = wscale ? wscale[dr.has ? tok : 0] : 1.f;
-  const WT* wp = E + (size_t)(dr.has ? tok : 0) * d + 8 * g;
-#pragma unroll
-  for (int s = 0; s < SkDraft<PER, WT>::kSteps; ++s)
-    dr.wf[s] = *reinterpret_cast<const typename SkFrag<WT>::type*>(wp + s * 32);
-}
-template <int PER, class WT>
-__device__ __forceinline__ void sk_draft_fetch(SkDraft<PER, WT>& dr, int R, const WT* __restrict__ E, int V,
-                                               const int* __restrict__ row_draft, const float* __restrict__ wscale) {
-  sk_draft_fetch<PER, WT>(dr, R, E, V, sk_draft_tok(R, row_draft), wscale);
-}
-template <int PER, class WT, class Out>
-__device__ __forceinline__ void sk_draft_logit(const SkDraft<PER, WT>& dr, const bf16* hb, int R, Out&& out) {
-  constexpr int d = 64 * PER, pitch = d + kSkPad;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lq = lane & 15, g = lane >> 4;
-  if (wave >= 2) return;
-  const int row = wave * 16 + lq;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int s = 0; s < SkDraft<PER, WT>::kSteps; ++s) {
-    bf16x8 hf = *reinterpret_cast<const bf16x8*>(hb + row * pitch + s * 32 + 8 * g);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sk_frag(dr.wf[s]), hf, acc, 0, 0, 0);
-  }
-  mfma_settle(acc);
-  // D[i][j]: this lane holds j = lq, i = 4g + r; diagonal i = j  <=>  g == lq/4, r = lq%4
-  if (g == (lq >> 2) && row < R) {
-    float v = 0.f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) if (r == (lq & 3)) v = acc[r];
-    // (the row scale multiplies the sum exactly as the projection does for that column)
-    out(row, dr.has ? v * dr.scale : kNegInf);
-  }
-}
-
-// Row statistics of one 64-column vocabulary tile (16 columns per wave: acc of this wave,
-// first column n0): per row the maximum, its lowest index, sum exp(z - max) and the number of
+// Row statistics of 64-column vocabulary tiles (16 columns per wave, four waves a tile: acc of this wave,
+// first column n0; tile: the first of the block): per row the maximum, its lowest index, sum exp(z - max) and the number of
 // logits above the row's draft logit zd[t] (row t*16 + lane%16); one record per row -> part.
 __device__ __forceinline__ void sk_vocab_tile(const f32x4 (&acc)[2], int n0, int V, int R, const float (&zd_t)[2],
                                               float* red, float* __restrict__ part, int n_tiles, int tile,
                                               float* __restrict__ logits) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lq = lane & 15, g = lane >> 4;
   // this lane: rows m = t*16 + lq, columns n0 + 4g + r
-  // red: [4 waves][32 rows][4]: max, arg-max, sum-exp, count
+  // red: [waves][32 rows][4]: max, arg-max, sum-exp, count
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int m = t * 16 + lq;
@@ -520,24 +456,24 @@ __device__ __forceinline__ void sk_vocab_tile(const f32x4 (&acc)[2], int n0, int
     }
   }
   __syncthreads();
-  if (threadIdx.x < kSkRows && (int)threadIdx.x < R) {
-    const int m = threadIdx.x;
+  const int m = threadIdx.x & (kSkRows - 1), w0 = threadIdx.x / kSkRows * 4;
+  if (w0 * 64 < (int)blockDim.x && m < R && tile + w0 / 4 < n_tiles) {
     float best = kNegInf, tot = 0.f;
     int besti = 0x7fffffff, cnt = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float* p = red + (w * 32 + m) * 4;
+      const float* p = red + ((w0 + w) * 32 + m) * 4;
       const int bi = __float_as_int(p[1]);
       if (p[0] > best || (p[0] == best && bi < besti)) { best = p[0]; besti = bi; }
       cnt += __float_as_int(p[3]);
     }
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float* p = red + (w * 32 + m) * 4;
+      const float* p = red + ((w0 + w) * 32 + m) * 4;
       if (p[0] > kNegInf) tot += p[2] * __expf(p[0] - best);
     }
     f32x4 rec = {best, __int_as_float(besti), tot, __int_as_float(cnt)};
-    *reinterpret_cast<f32x4*>(part + ((size_t)m * n_tiles + tile) * kPartF) = rec;
+    *reinterpret_cast<f32x4*>(part + ((size_t)m * n_tiles + tile + w0 / 4) * kPartF) = rec;
   }
 }
 
