@@ -1634,14 +1634,13 @@ struct VocabTiles {
   __device__ __forceinline__ void finish() const;
 };
 
-template <bool ARGMAX, bool STREAM>
-__device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
-  const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tid = wave * 64 + lane;
-  const int wy = wave >> 2, wx = wave & 3, lcol = lane & 31, lhalf = lane >> 5;
-  float zd[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) zd[i] = zd_row ? zd_rows(flip)[wy * 128 + i * 32 + lcol] : kNegInf;   // -inf on rows that score no draft: count unused
-  f32x4* rec = reinterpret_cast<f32x4*>(smem + Cfg::kSmemBytes);   // [4 wave columns][256 rows]
+// The records of a finished tile of 256 rows; zd: the drafts' logits of the lane's rows (-inf on rows that score no draft: count unused); rec:
+// [wave columns][256 rows].
+template <bool ARGMAX, class Cfg>
+__device__ __forceinline__ void vocab_records(const GemmAcc<Cfg>& acc, const float (&zd)[Cfg::kTM], f32x4* rec, int lane, int wave, int m0, int n0, int M,
+                                              int V, int NT, float* __restrict__ part, float* __restrict__ logits) {
+  static_assert(Cfg::kBM == 256 && Cfg::kWN == 64 && (Cfg::kWavesN == 2 || Cfg::kWavesN == 4) && Cfg::kThreads == 512, "shape");
+  const int tid = wave * 64 + lane, wy = wave / Cfg::kWavesN, wx = wave % Cfg::kWavesN, lcol = lane & 31, lhalf = lane >> 5;
   const int nw = n0 + wx * 64 + 4 * lhalf;        // first column of this lane
   // column of accumulator (j, r) relative to nw: ascending in (j, r), so ">" keeps the lowest index of a tie
   auto col = [](int j, int r) { return j * 32 + 8 * (r >> 2) + (r & 3); };
@@ -1650,7 +1649,7 @@ __device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
     constexpr bool FULL = decltype(full_tag)::value;
     const int nvalid = V - nw;   // columns of this lane inside the matrix (FULL: all of them)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < Cfg::kTM; ++i) {
       float best = kNegInf;
       int bestc = 0x3fffffff, cnt = 0;
 #pragma unroll
@@ -1685,15 +1684,15 @@ __device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
       if (obest > kNegInf) tot += ose * __expf(obest - nb);
       const int nbi = (obest > best || (obest == best && obesti < besti)) ? obesti : besti;
       if (lhalf == 0)
-        rec[wx * 256 + wy * 128 + i * 32 + lcol] = f32x4{nb, __int_as_float(nbi), tot, __int_as_float(cnt + ocnt)};
+        rec[wx * 256 + wy * Cfg::kWM + i * 32 + lcol] = f32x4{nb, __int_as_float(nbi), tot, __int_as_float(cnt + ocnt)};
     }
   };
-  if (n0 + 256 <= V) scan(std::true_type{});
+  if (n0 + Cfg::kBN <= V) scan(std::true_type{});
   else scan(std::false_type{});
   if (logits) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = m0 + wy * 128 + i * 32 + lcol;
+    for (int i = 0; i < Cfg::kTM; ++i) {
+      const int m = m0 + wy * Cfg::kWM + i * 32 + lcol;
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -1707,7 +1706,7 @@ __device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
   // thread (row, 128-column tile): waves 2t and 2t+1 of the row, lower columns first
   const int row = tid & 255, ct = tid >> 8;
   const int m = m0 + row, nt128 = n0 / 128 + ct;
-  if (m < M && nt128 < NT) {
+  if (ct < Cfg::kBN / 128 && m < M && nt128 < NT) {
     const f32x4 a = rec[(2 * ct) * 256 + row], b = rec[(2 * ct + 1) * 256 + row];
     const float nb = fmaxf(a[0], b[0]);
     float tot = 0.f;
@@ -1717,6 +1716,32 @@ __device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
     f32x4 out = {nb, tb ? b[1] : a[1], tot, __int_as_float(__float_as_int(a[3]) + __float_as_int(b[3]))};
     *reinterpret_cast<f32x4*>(part + ((size_t)m * NT + nt128) * kPartF) = out;
   }
+}
+
+template <bool ARGMAX, bool STREAM>
+__device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
+  const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float zd[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) zd[i] = zd_row ? zd_rows(flip)[(wave >> 2) * 128 + i * 32 + (lane & 31)] : kNegInf;
+  vocab_records<ARGMAX>(acc, zd, reinterpret_cast<f32x4*>(smem + Cfg::kSmemBytes), lane, wave, m0, n0, M, V, NT, part, logits);
+}
+
+// 129 - 256 rows: a row tile of 256 x 128 columns, one block to a CU, where the vocabulary is one round of them.
+template <bool ARGMAX>
+__global__ __launch_bounds__(CfgTall::kThreads, 2) void vocab_tall_kernel(const bf16* __restrict__ A, const bf16* __restrict__ E, int M, int V, int K, int NT,
+                                                                          const float* __restrict__ zd_row, float* __restrict__ part,
+                                                                          float* __restrict__ logits) {
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+  int mt, nt;
+  if (!xcd_tile(blockIdx.x, 1, NT, mt, nt)) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float zd[CfgTall::kTM];   // (requested ahead of the products)
+#pragma unroll
+  for (int i = 0; i < CfgTall::kTM; ++i) zd[i] = zd_row ? zd_row[min((wave >> 1) * CfgTall::kWM + i * 32 + (lane & 31), M - 1)] : kNegInf;
+  GemmAcc<CfgTall> acc;
+  gemm_mainloop<CfgTall, true>(A, K, E, K, M, V, 0, K / CfgTall::GK, 0, nt * 128, smem, acc);
+  vocab_records<ARGMAX>(acc, zd, reinterpret_cast<f32x4*>(smem), lane, wave, 0, nt * 128, M, V, NT, part, logits);
 }
 
 template <bool ARGMAX, bool STREAM>
@@ -1747,6 +1772,16 @@ static hipError_t launch_vocab256(hipStream_t st, const bf16* A, const bf16* E, 
   const int MT = (M + 255) / 256, NT = (V + 255) / 256, grid = xcd_grid(MT, NT);
   SD_LAUNCH_TIMED((vocab256_kernel<ARGMAX, STREAM>), dim3(STREAM ? std::min(grid, 256) : grid), dim3(CfgVocab256::kThreads), kBytes, st, A, E, M, V, K,
                   MT, NT, (V + 127) / 128, zd, part, logits);
+  return hipGetLastError();
+}
+
+template <bool ARGMAX>
+static hipError_t launch_vocab_tall(hipStream_t st, const bf16* A, const bf16* E, int M, int V, int K, const float* zd, float* part, float* logits) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab_tall_kernel<ARGMAX>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, CfgTall::kSmemBytes);
+  if (attr != hipSuccess) return attr;
+  const int NT = (V + 127) / 128;
+  SD_LAUNCH_TIMED((vocab_tall_kernel<ARGMAX>), dim3(xcd_grid(1, NT)), dim3(CfgTall::kThreads), CfgTall::kSmemBytes, st, A, E, M, V, K, NT, zd, part, logits);
   return hipGetLastError();
 }
 
@@ -1791,10 +1826,15 @@ hipError_t vocab_stats(hipStream_t st, const bf16* A, const bf16* E, int M, int 
   // 25.3 / 20.9), 704 (384) 68.6 / 62.9.
   const int MT256 = (M + 255) / 256, NT256 = (V + 255) / 256;
   const bool big = force_wide || (long)MT256 * NT256 >= 256;
-  const hipError_t e = big ? launch_draft_logits<true>(st, A, E, M, V, K, row_draft, zd_row, ln)
-                           : launch_draft_logits<false>(st, A, E, M, V, K, row_draft, zd_row, ln);
+  // 129 - 256 rows of a short K, one round of 256 x 128: a launch on 128 x 128 tiles (two to a CU) / so, K = 512: 143 rows 15.7 / 12.4 us, 240 of
+  // a drafter 15.0 / 12.0, 253 16.0 / 13.2.  At K = 1024 a launch by itself is faster, too (209 rows 28.5 / 23.4), but whole passes are not
+  // (209 rows 353.8 / 355.4, 253 356.5 / 360): in those E comes from memory, 16 stages of it one behind the other.
+  const bool tall = !big && MT == 2 && NT <= 256 && K <= 512;
+  const hipError_t e = big || tall ? launch_draft_logits<true>(st, A, E, M, V, K, row_draft, zd_row, ln)
+                                   : launch_draft_logits<false>(st, A, E, M, V, K, row_draft, zd_row, ln);
   if (e != hipSuccess) return e;
   const float* zd = row_draft ? zd_row : nullptr;
+  if (tall) return stats ? launch_vocab_tall<false>(st, A, E, M, V, K, zd, part, logits) : launch_vocab_tall<true>(st, A, E, M, V, K, nullptr, part, logits);
   if (big) {
     const bool stream = K % 128 == 0 && K >= 256 && (long)MT256 * NT256 > 256;
     if (stats) return stream ? launch_vocab256<false, true>(st, A, E, M, V, K, zd, part, logits) : launch_vocab256<false, false>(st, A, E, M, V, K, zd, part, logits);
