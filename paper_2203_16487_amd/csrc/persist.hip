@@ -679,6 +679,9 @@ __global__ __launch_bounds__((64 * NW), 2) void pl_decoder_kernel(PlArgs a) {
   typedef std::integral_constant<int, 1> C1;
   // stage s of layer l, of workgroup w
   auto stage = [&](int s, int l) __attribute__((always_inline)) -> bool {
+    // (what follows from the layer is worked out where it is used: ahead of its stages, where the compiler would have it, it does not fit the
+    // scalar registers; 26 rows of d = 1024, 8-bit weights 206.5 us, so 204.1)
+    asm volatile("" : "+s"(l));
     const int wa = units <= NB ? w - a.att0 : w;
     const PlLayer& Y = reinterpret_cast<const PlLayer*>(L.layers)[l];
     const PlExch ex(a.exch + (size_t)l * pl_layer_bytes(a.RP, d, F), a.RP, d), before(a.exch + (size_t)(l - 1) * pl_layer_bytes(a.RP, d, F), a.RP, d);
