@@ -907,14 +907,18 @@ static hipError_t launch_stream(hipStream_t st, const bf16* A, int lda, const bf
 // 256 x 256 tiles or 128 x 128 ones?  Time of a full round of blocks (256 and 512) as measured over K = 512 .. 4096, us:
 // 10.5 + 1.73 and 3.6 + 1.12 per 64 columns of K; 8.2 + 1.38 where a block takes tile after tile (stream); a last round costs nearly a full one
 // on one block per CU, and on two the better part of one as soon as some CU has a second block.  (Sums of K = 512 take twice as long on both.
-// A streamed last round that is at most half full is charged in full, too, though gemm_stream_kernel computes it as tiles of half the width:
-// the choices were checked before it did.)  Of twelve row counts from 352 to 32768 and nine (N, K) of the two models, the choice was at most
-// 3 % slower than the better of the two wherever it is made.  Where M only bounds the rows in use (bound), the sum over half, three quarters and all of it decides.
+// A streamed last round that is at most half full is computed as tiles of half the width, gemm_stream_kernel, and costs 0.65 of one.)
+// Of twelve row counts from 352 to 32768 and nine (N, K) of the two models, the choice was at most 3 % slower than the better of the two
+// wherever it is made.  Charging that last round in full kept 11264 and 16384 rows of 1536 and 2048 x 512 on 128 x 128 tiles: encoding
+// 128 sources of 128 tokens with 512-wide encoders 3610 us, now 3511; 128 of 16 .. 128 tokens 2769 / 2702; 88 of them 2312 / 2268; with a
+// 1024-wide encoder 3607 / 3580.  Where M only bounds the rows in use (bound), the sum over half, three quarters and all of it decides.
 static float square_minus_wide(int M, int N, int K, bool stream) {
   const float kt = K / 64.f;
   const long sq = (long)((M + 255) / 256) * ((N + 255) / 256), wd = (long)((M + 127) / 128) * ((N + 127) / 128);
   const float round = stream && sq > 256 ? 8.2f + 1.38f * kt : 10.5f + 1.73f * kt;
-  const float t_sq = (float)((sq + 255) / 256) * (sq < 256 ? 0.8f : 1.f) * round;
+  const long last = sq % 256;
+  const float rounds = (float)(sq / 256) + (last == 0 ? 0.f : stream && sq > 256 && last <= 128 ? 0.65f : 1.f);
+  const float t_sq = rounds * (sq < 256 ? 0.8f : 1.f) * round;
   const long rem = wd % 512;
   const float t_wd = ((float)(wd / 512) + (rem == 0 ? 0.f : rem <= 256 ? 0.6f : 1.f)) * (3.6f + 1.12f * kt);
   return t_sq - t_wd;
