@@ -861,6 +861,15 @@ struct StreamTiles {
   }
 };
 
+// The XCD's run of `tiles` tiles, its whole rounds up to `end` and, where the round behind them is at most half full, the number of its
+// tiles, which are computed as two of half the width; 0 if it is not.
+__device__ __forceinline__ int half_round(int tiles, int& end) {
+  const int per = (tiles + 7) >> 3, run = min(per, tiles - (int)(blockIdx.x & 7) * per), cus = gridDim.x >> 3, left = run % cus;
+  const bool halves = run > cus && left != 0 && 2 * left <= cus;
+  end = halves ? run - left : run;
+  return halves ? left : 0;
+}
+
 template <class Epi>
 __global__ __launch_bounds__(CfgSquare::kThreads, 2) void gemm_stream_kernel(const bf16* __restrict__ A, int lda,
                                                                              const bf16* __restrict__ W, int ldw, int M, int N, int K,
@@ -871,10 +880,7 @@ __global__ __launch_bounds__(CfgSquare::kThreads, 2) void gemm_stream_kernel(con
   GemmAcc<Cfg> acc;
   StreamTiles<Epi> t{epi, acc, reinterpret_cast<char*>(smem), M, N, (M + Cfg::kBM - 1) / Cfg::kBM, NT, 0, 0, 0, 0, (int)blockIdx.x >> 3, 0, 0, false, 0};
   if (!t.tile(t.at, t.m0, t.n0)) return;
-  // the XCD's run: whole rounds, and what is left of it
-  const int nb = t.MT * NT, per = (nb + 7) >> 3, run = min(per, nb - (int)(blockIdx.x & 7) * per), cus = gridDim.x >> 3, left = run % cus;
-  const bool halves = run > cus && left != 0 && 2 * left <= cus;
-  t.end = halves ? run - left : run;
+  const int left = half_round(t.MT * NT, t.end);
   gemm_mainloop_square<Cfg>(A, lda, W, ldw, M, N, 0, K / Cfg::GK, t.m0, t.n0, smem, acc, [&] {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     t.vectors(wave, threadIdx.x & 63, t.n0, 0);
@@ -884,8 +890,7 @@ __global__ __launch_bounds__(CfgSquare::kThreads, 2) void gemm_stream_kernel(con
   // a last round at most half full: tiles of 256 x 128, for twice as many CUs (7168 x 3072 x 1024, 336 tiles: 61.7 us, now 56.0; 9216 of 16384
   // rows x 2048 x 512, 288 tiles, 37.7 / 34.4)
   const int i = (int)blockIdx.x >> 3;
-  if (!halves || i >= 2 * left) return;
-  if (!t.tile(t.end + (i >> 1), t.m0, t.n0)) return;
+  if (i >= 2 * left || !t.tile(t.end + (i >> 1), t.m0, t.n0)) return;
   t.n0 += (i & 1) * 128;
   if (t.n0 >= N) return;
   __syncthreads();   // the ring is everybody's again
@@ -1604,6 +1609,7 @@ struct VocabTiles {
   float* __restrict__ part;
   float* __restrict__ logits;
   int m0, n0, m1, n1, at, flip;   // this tile, the next one; which of the XCD's run; half of zd in use
+  int end;                        // of the XCD's run: where tiles of half the width begin
   __device__ __forceinline__ float* zd_rows(int f) const { return reinterpret_cast<float*>(smem + Cfg::kSmemBytes + 4 * 256 * 16) + f * 256; }
   __device__ __forceinline__ bool tile(int at, int& m, int& n) const {
     int mt, nt;
@@ -1622,7 +1628,7 @@ struct VocabTiles {
     at += gridDim.x >> 3;
     m1 = m0;
     n1 = n0;
-    const bool more = tile(at, m1, n1);
+    const bool more = at < end && tile(at, m1, n1);
     if (more) drafts(m1, flip ^ 1);
     m = m1;
     n = n1;
@@ -1731,7 +1737,20 @@ __device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
   vocab_records<ARGMAX>(acc, zd, reinterpret_cast<f32x4*>(smem + Cfg::kSmemBytes), lane, wave, m0, n0, M, V, NT, part, logits);
 }
 
-// 129 - 256 rows: a row tile of 256 x 128 columns, one block to a CU, where the vocabulary is one round of them.
+// A tile of 256 rows x 128 columns.
+template <bool ARGMAX>
+__device__ __forceinline__ void vocab_tall(const bf16* __restrict__ A, const bf16* __restrict__ E, int M, int V, int K, int NT, int m0, int n0,
+                                           const float* __restrict__ zd_row, float* __restrict__ part, float* __restrict__ logits, bf16* smem) {
+  const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float zd[CfgTall::kTM];   // (requested ahead of the products)
+#pragma unroll
+  for (int i = 0; i < CfgTall::kTM; ++i) zd[i] = zd_row ? zd_row[min(m0 + (wave >> 1) * CfgTall::kWM + i * 32 + (lane & 31), M - 1)] : kNegInf;
+  GemmAcc<CfgTall> acc;
+  gemm_mainloop<CfgTall, true>(A, K, E, K, M, V, 0, K / CfgTall::GK, m0, n0, smem, acc);
+  vocab_records<ARGMAX>(acc, zd, reinterpret_cast<f32x4*>(smem), lane, wave, m0, n0, M, V, NT, part, logits);
+}
+
+// 129 - 256 rows: one block to a CU, where the vocabulary is one round of them.
 template <bool ARGMAX>
 __global__ __launch_bounds__(CfgTall::kThreads, 2) void vocab_tall_kernel(const bf16* __restrict__ A, const bf16* __restrict__ E, int M, int V, int K, int NT,
                                                                           const float* __restrict__ zd_row, float* __restrict__ part,
@@ -1739,13 +1758,7 @@ __global__ __launch_bounds__(CfgTall::kThreads, 2) void vocab_tall_kernel(const 
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
   int mt, nt;
   if (!xcd_tile(blockIdx.x, 1, NT, mt, nt)) return;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float zd[CfgTall::kTM];   // (requested ahead of the products)
-#pragma unroll
-  for (int i = 0; i < CfgTall::kTM; ++i) zd[i] = zd_row ? zd_row[min((wave >> 1) * CfgTall::kWM + i * 32 + (lane & 31), M - 1)] : kNegInf;
-  GemmAcc<CfgTall> acc;
-  gemm_mainloop<CfgTall, true>(A, K, E, K, M, V, 0, K / CfgTall::GK, 0, nt * 128, smem, acc);
-  vocab_records<ARGMAX>(acc, zd, reinterpret_cast<f32x4*>(smem), lane, wave, 0, nt * 128, M, V, NT, part, logits);
+  vocab_tall<ARGMAX>(A, E, M, V, K, NT, 0, nt * 128, zd_row, part, logits, smem);
 }
 
 template <bool ARGMAX, bool STREAM>
@@ -1757,11 +1770,20 @@ __global__ __launch_bounds__(CfgVocab256::kThreads, 2) void vocab256_kernel(cons
                                                                             float* __restrict__ logits) {
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
   GemmAcc<CfgVocab256> acc;
-  VocabTiles<ARGMAX, STREAM> t{acc, reinterpret_cast<char*>(smem), M, V, MT, NT256, NT, zd_row, part, logits, 0, 0, 0, 0, (int)blockIdx.x >> 3, 0};
+  VocabTiles<ARGMAX, STREAM> t{acc, reinterpret_cast<char*>(smem), M, V, MT, NT256, NT, zd_row, part, logits, 0, 0, 0, 0, (int)blockIdx.x >> 3, 0, 0};
   if (!t.tile(t.at, t.m0, t.n0)) return;
   auto hook = [&] { t.drafts(t.m0, 0); };
   if constexpr (STREAM) {
+    const int left = half_round(MT * NT256, t.end);
     gemm_mainloop_square<CfgVocab256>(A, K, E, K, M, V, 0, K / CfgVocab256::GK, t.m0, t.n0, smem, acc, hook, t);
+    // a last round at most half full: tiles of 256 x 128, as in gemm_stream_kernel (384 tiles, 704 rows, K = 1024: 58.3 us, now 52.8; 640 of K
+    // = 512, arg-max alone, 32.8 / 30.3; 378 tiles of statistics, 572 rows of 512, 36.9 / 32.8)
+    const int i = (int)blockIdx.x >> 3;
+    if (i >= 2 * left || !t.tile(t.end + (i >> 1), t.m0, t.n0)) return;
+    t.n0 += (i & 1) * 128;
+    if (t.n0 >= V) return;
+    __syncthreads();   // the ring and the records are everybody's again
+    vocab_tall<ARGMAX>(A, E, M, V, K, NT, t.m0, t.n0, zd_row, part, logits, smem);
   } else {
     gemm_mainloop_square<CfgVocab256>(A, K, E, K, M, V, 0, K / CfgVocab256::GK, t.m0, t.n0, smem, acc, hook);
     t.finish();
@@ -1769,7 +1791,7 @@ __global__ __launch_bounds__(CfgVocab256::kThreads, 2) void vocab256_kernel(cons
 }
 template <bool ARGMAX, bool STREAM>
 static hipError_t launch_vocab256(hipStream_t st, const bf16* A, const bf16* E, int M, int V, int K, const float* zd, float* part, float* logits) {
-  constexpr int kBytes = VocabTiles<ARGMAX, STREAM>::kBytes;
+  constexpr int kBytes = STREAM ? std::max(VocabTiles<ARGMAX, STREAM>::kBytes, CfgTall::kSmemBytes) : VocabTiles<ARGMAX, STREAM>::kBytes;
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab256_kernel<ARGMAX, STREAM>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
   if (attr != hipSuccess) return attr;
@@ -1827,7 +1849,7 @@ hipError_t vocab_stats(hipStream_t st, const bf16* A, const bf16* E, int M, int 
   // 256 x 256 tiles once they give every CU one (the batched passes); their product is formed with
   // the operand roles swapped, and the draft logits follow suit.  V = 32768, d = 1024, a launch on 128 x 128 / 256 x 256 tiles: 132 rows
   // (128 of the larger tiles) 25.6 / 32.3 us, 352 (256) 44.8 / 34.7 (d = 512
-  // 25.3 / 20.9), 704 (384) 68.6 / 62.9.
+  // 25.3 / 20.9), 704 (384) 68.6 / 52.8.
   const int MT256 = (M + 255) / 256, NT256 = (V + 255) / 256;
   const bool big = force_wide || (long)MT256 * NT256 >= 256;
   // 129 - 256 rows of a short K, one round of 256 x 128: a launch on 128 x 128 tiles (two to a CU) / so, K = 512: 143 rows 15.7 / 12.4 us, 240 of

@@ -21,8 +21,10 @@ pytestmark = pytest.mark.gpu
     (1024, 9, 6, 1003, {}),                                       # 63 rows
     (1024, 13, 4, 300, {sd.SPECDEC_OPT_WIDE_VOCAB_TILES: 1}),     # 65 rows, 256 x 256 tiles
     (512, 43, 5, 32768, {}),                                      # 258 rows, 256 tiles of 256 x 256: the fewest by themselves
-    (512, 65, 7, 32100, {}),                                      # 520 rows, 378 tiles of 256 x 256: two to some blocks, edges cut
+    (512, 65, 7, 32100, {}),                                      # 520 rows, 378 tiles of 256 x 256: the second round in halves, the last of them cut away
     (256, 65, 7, 33000, {}),                                      # K = 256, the shortest of them
+    (512, 65, 7, 32896, {}),                                      # 387 tiles, a half tile of rows and columns at the end
+    (512, 127, 6, 25600, {}),                                     # 400 tiles: more than half a round, whole tiles
     (192, 65, 7, 32100, {}),                                      # K = 192: a block a tile
     (128, 11, 2, 1003, {}),                                       # another width: two launches
 ])
