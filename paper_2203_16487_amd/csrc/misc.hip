@@ -1,5 +1,7 @@
 // Small kernels around the GEMMs: embedding, LayerNorm, row assembly, the acceptance test
 // (paper Sec. 3.2, Eq. 8-10), commit (Sec. 2, Eq. 3) and state / cache marshalling.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -428,23 +430,29 @@ struct RowMerge {
   float m, lse;
   int arg, cnt;
 };
-__device__ __forceinline__ RowMerge merge_row(const float* __restrict__ pr, int n_tiles, int lane) {
-  constexpr int kHeld = 8;   // records per lane kept in registers: one pass over memory up to 512 tiles
-  const bool held = n_tiles <= 64 * kHeld;
-  f32x4 rec[kHeld];
+constexpr int kHeldRecords = 8;   // per lane, in registers: one pass over memory up to 512 tiles
+struct RowRecords {
+  f32x4 rec[kHeldRecords];
+  __device__ __forceinline__ void request(const float* __restrict__ pr, int n_tiles, int lane) {
+    if (n_tiles > 64 * kHeldRecords) return;
+#pragma unroll
+    for (int i = 0; i < kHeldRecords; ++i)   // (clamped, so that no load sits behind a lane's own branch)
+      rec[i] = *reinterpret_cast<const f32x4*>(pr + (size_t)min(lane + 64 * i, n_tiles - 1) * kPartF);
+  }
+};
+// (held: what was requested of the row)
+__device__ __forceinline__ RowMerge merge_row(const RowRecords& held, const float* __restrict__ pr, int n_tiles, int lane) {
+  const bool all = n_tiles <= 64 * kHeldRecords;
   float m = kNegInf;
   int am = 0x7fffffff, cnt = 0;
-  if (held) {
+  if (all) {
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i)   // (clamped, so that no load sits behind a lane's own branch)
-      rec[i] = *reinterpret_cast<const f32x4*>(pr + (size_t)min(lane + 64 * i, n_tiles - 1) * kPartF);
-#pragma unroll
-    for (int i = 0; i < kHeld; ++i) {
+    for (int i = 0; i < kHeldRecords; ++i) {
       if (lane + 64 * i < n_tiles) {
-        const float tm = rec[i][0];
-        const int ti = __float_as_int(rec[i][1]);
+        const float tm = held.rec[i][0];
+        const int ti = __float_as_int(held.rec[i][1]);
         if (tm > m || (tm == m && ti < am)) { m = tm; am = ti; }
-        cnt += __float_as_int(rec[i][3]);
+        cnt += __float_as_int(held.rec[i][3]);
       }
     }
   } else {
@@ -464,10 +472,10 @@ __device__ __forceinline__ RowMerge merge_row(const float* __restrict__ pr, int 
     cnt += __shfl_xor(cnt, o, 64);
   }
   float se = 0.f;
-  if (held) {
+  if (all) {
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i)
-      if (lane + 64 * i < n_tiles) se += rec[i][2] * __expf(rec[i][0] - gm);
+    for (int i = 0; i < kHeldRecords; ++i)
+      if (lane + 64 * i < n_tiles) se += held.rec[i][2] * __expf(held.rec[i][0] - gm);
   } else {
     for (int t = lane; t < n_tiles; t += 64) {
       const f32x4 p = *reinterpret_cast<const f32x4*>(pr + (size_t)t * kPartF);
@@ -489,8 +497,10 @@ __device__ __forceinline__ void store_row_stats(float* rs, const RowMerge& r, fl
 // beta-th score passes, as ">=" says).  a = number of leading rows that pass; next = arg-max
 // of row a.
 //
-// Both stages in one launch: a block per sequence, its 16 waves merge the k + 1 <= 32 rows (two
-// rounds at most), then one thread scans them.
+// Both stages in one launch: a block per sequence, its 16 waves merge the k + 1 <= 32 rows (two a
+// wave at most), then lane i of the first one takes row i.  All that comes from memory is requested
+// at once, and the block has no wave without a row: bound by round trips (one behind the other and scanned by one thread:
+// whole verify passes of 6 rows of d = 512 112.6 us, now 111.6; of 352 182.9 / 181.6; of 352 of d = 1024 517.5 / 514.6).
 constexpr int kMergeWaves = 16;
 __global__ __launch_bounds__(64 * kMergeWaves) void merge_accept_kernel(const float* __restrict__ part,
                                                            const float* __restrict__ zd_row, int n_tiles,
@@ -501,41 +511,54 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_accept_kernel(const fl
                                                            const unsigned* __restrict__ fail) {
   __shared__ float sm[32], szd[32];
   __shared__ int sarg[32], scnt[32];
-  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int T = k + 1;
-  for (int i = wave; i < T; i += kMergeWaves) {
-    const int r = b * T + i;
-    const RowMerge res = merge_row(part + (size_t)r * n_tiles * kPartF, n_tiles, lane);
-    if (lane == 0) {
-      const float zd = zd_row[r];
-      store_row_stats(row_stats + (size_t)r * kRowStats, res, zd);
-      sm[i] = res.m; szd[i] = zd; sarg[i] = res.arg; scnt[i] = res.cnt;
+  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int T = k + 1, rows = (T - wave + kMergeWaves - 1) / kMergeWaves;   // of this wave: wave, wave + 16
+  const unsigned failed = fail ? *fail : 0u;
+  const int cached = s.cached[0][b], len = s.len[b], finished = s.finished[b];
+  RowRecords held[2];
+  float zd[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (i < rows) {
+      const int r = b * T + wave + i * kMergeWaves;
+      held[i].request(part + (size_t)r * n_tiles * kPartF, n_tiles, lane);
+      zd[i] = zd_row[r];
     }
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  if (fail && *fail) { accept_len[b] = -1; next_token[b] = pad_id; return; }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (i < rows) {
+      const int t = wave + i * kMergeWaves, r = b * T + t;
+      const RowMerge res = merge_row(held[i], part + (size_t)r * n_tiles * kPartF, n_tiles, lane);
+      if (lane == 0) {
+        store_row_stats(row_stats + (size_t)r * kRowStats, res, zd[i]);
+        sm[t] = res.m; szd[t] = zd[i]; sarg[t] = res.arg; scnt[t] = res.cnt;
+      }
+    }
+  lds_barrier();
+  if (wave != 0) return;
   // keys/values of u_0..u_{j-1} must be cached: a cache loaded short of the stream (and not
   // completed by a prefill) would have let this pass attend to rows that were never written
-  if (s.cached[0][b] < s.len[b] && !s.finished[b]) { accept_len[b] = -1; next_token[b] = pad_id; return; }
-  int a = 0;
-  for (; a < k; ++a)
-    if (!(scnt[a] < beta && sm[a] - szd[a] <= tau)) break;
-  const bool fin = s.finished[b] != 0;
-  accept_len[b] = fin ? 0 : a;
-  next_token[b] = fin ? pad_id : sarg[a];
-  if (!fin) {   // rows whose tau test was decided by a margin of at most 1e-2 (up to the bifurcation row)
-    int near = 0;
-    for (int i = 0; i <= a && i < k; ++i) near += fabsf(tau - (sm[i] - szd[i])) <= 1e-2f ? 1 : 0;
-    if (near) atomicAdd(&s.scratch[3], near);
+  if (failed || (cached < len && !finished)) {
+    if (lane == 0) { accept_len[b] = -1; next_token[b] = pad_id; }
+    return;
   }
+  const int i = min(lane, T - 1);
+  const float gap = sm[i] - szd[i];
+  const unsigned long long misses = __builtin_amdgcn_ballot_w64(lane >= k || !(scnt[i] < beta && gap <= tau));   // (k <= 31)
+  const int a = __builtin_ctzll(misses);
+  // rows whose tau test was decided by a margin of at most 1e-2 (up to the bifurcation row)
+  const int near = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane <= a && lane < k && fabsf(tau - gap) <= 1e-2f));
+  if (lane != 0) return;
+  accept_len[b] = finished ? 0 : a;
+  next_token[b] = finished ? pad_id : sarg[a];
+  if (!finished && near) atomicAdd(&s.scratch[3], near);
 }
 hipError_t merge_accept(hipStream_t st, const float* part, const float* zd_row, int n_tiles, float* row_stats,
                         const SeqState& s, int B, int k, int beta, float tau, int pad_id, int* accept_len,
                         int* next_token, const unsigned* fail) {
   if (B <= 0) return hipSuccess;
   if (k + 1 > 32) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(merge_accept_kernel, dim3(B), dim3(64 * kMergeWaves), 0, st, part, zd_row, n_tiles, row_stats, s, k, beta,
+  hipLaunchKernelGGL(merge_accept_kernel, dim3(B), dim3(64 * std::min(k + 1, kMergeWaves)), 0, st, part, zd_row, n_tiles, row_stats, s, k, beta,
                      tau, pad_id, accept_len, next_token, fail);
   return hipGetLastError();
 }
@@ -549,15 +572,16 @@ __global__ __launch_bounds__(64) void merge_drafts_kernel(const float* __restric
                                                           const int* __restrict__ seq_rows,
                                                           int* __restrict__ draft) {
   const int o = blockIdx.x, lane = threadIdx.x;
-  const RowMerge res = merge_row(part + (size_t)o * n_tiles * kPartF, n_tiles, lane);
-  if (lane != 0) return;
-  store_row_stats(row_stats + (size_t)o * kRowStats, res, kNegInf);
   // a sequence whose uncached stream did not fit into this pass got no mask slots (its rows of
   // the pass were all stream rows): what sits at its slot rows belongs to another sequence
-  const int b = o / k;
-  const bool has_slots = seq_rows[b] - new_rows[b] == k;
-  draft[o] = (s.finished[b] || !has_slots) ? pad_id : res.arg;
-  if (o < B) s.cached[1][o] += new_rows[o];
+  const int b = o / k, slots = seq_rows[b] - new_rows[b], finished = s.finished[b], cached = o < B ? s.cached[1][o] + new_rows[o] : 0;
+  RowRecords held;   // (all requests of memory at once, as above)
+  held.request(part + (size_t)o * n_tiles * kPartF, n_tiles, lane);
+  const RowMerge res = merge_row(held, part + (size_t)o * n_tiles * kPartF, n_tiles, lane);
+  if (lane != 0) return;
+  store_row_stats(row_stats + (size_t)o * kRowStats, res, kNegInf);
+  draft[o] = finished || slots != k ? pad_id : res.arg;
+  if (o < B) s.cached[1][o] = cached;
 }
 hipError_t merge_drafts(hipStream_t st, const float* part, int n_tiles, float* row_stats, const SeqState& s, int B,
                         int k, int pad_id, const int* new_rows, const int* seq_rows, int* draft) {
@@ -649,12 +673,14 @@ __global__ __launch_bounds__(64) void merge_head_drafts_kernel(const float* __re
                                                                float* __restrict__ row_stats, SeqState s,
                                                                const int* __restrict__ accept_len, int k, int pad_id,
                                                                int* __restrict__ draft) {
-  const int o = blockIdx.x, lane = threadIdx.x;
-  const RowMerge res = merge_row(part + (size_t)o * n_tiles * kPartF, n_tiles, lane);
+  const int o = blockIdx.x, lane = threadIdx.x, b = o / k;
+  const bool none = s.finished[b] || accept_len[b] < 0;
+  RowRecords held;
+  held.request(part + (size_t)o * n_tiles * kPartF, n_tiles, lane);
+  const RowMerge res = merge_row(held, part + (size_t)o * n_tiles * kPartF, n_tiles, lane);
   if (lane != 0) return;
   store_row_stats(row_stats + (size_t)o * kRowStats, res, kNegInf);
-  const int b = o / k;
-  draft[o] = (s.finished[b] || accept_len[b] < 0) ? pad_id : res.arg;
+  draft[o] = none ? pad_id : res.arg;
 }
 hipError_t merge_head_drafts(hipStream_t st, const float* part, int n_tiles, float* row_stats, const SeqState& s,
                              const int* accept_len, int B, int k, int pad_id, int* draft) {
