@@ -340,7 +340,7 @@ struct SeqState {       // device arrays of the bound state buffer, all [max_bat
   int* cached[2];       // per role: stream positions whose K/V are cached
   int* src_len;
   int* last_draft;      // [max_batch][k_max]
-  int* scratch;         // [8] counters since begin: commits, tokens appended, finished sequences, near-tau rows
+  int* scratch;         // [8] counters since begin: commits, tokens appended, finished sequences, near-tau rows; three words of commit_kernel's
   int tok_pitch, k_max;
 };
 // rows of a verification pass: [u_j, drafts]; also stores the drafts for commit

@@ -695,8 +695,10 @@ hipError_t merge_head_drafts(hipStream_t st, const float* part, int n_tiles, flo
 // sequence stops after its first EOS or when it reaches its cap.  j advances by the number
 // of tokens appended: exactly that many of this pass's cache rows become valid.
 // 32 lanes a sequence, lane i for token i: one memory round trip for everything that is read, whatever it turns out to be, and the length by a
-// ballot.  (With a thread a sequence, which chose and stored its tokens one by one, 8.7 us for 128 sequences; so 5.7.)
-constexpr int kCommitThreads = 1024;
+// ballot.  (With a thread a sequence, which chose and stored its tokens one by one, 8.7 us for 128 sequences; so 5.7.)  Those 32 lanes cost 35 cycles
+// a sequence of one CU's instructions, so a block takes kCommitBatch of them at most, and where there are more the last block to end adds up.
+// (All by one block: 1024 / 4096 sequences of one draft 20.9 / 71 us, a thread a sequence 13.7 / 33; so 7.7 / 8.2.)
+constexpr int kCommitThreads = 1024, kCommitBatch = 128;
 __global__ __launch_bounds__(kCommitThreads) void commit_kernel(SeqState s, const int* __restrict__ accept_len, const int* __restrict__ next_token,
                                                                 int B, int k, int eos_id, int* n_active) {
   __shared__ int active, tokens;
@@ -707,9 +709,10 @@ __global__ __launch_bounds__(kCommitThreads) void commit_kernel(SeqState s, cons
   if (threadIdx.x == 0) { c_commits = s.scratch[0]; c_tokens = s.scratch[1]; }
   const int i = threadIdx.x & 31, shift = threadIdx.x & 32;
   int mine = 0, added = 0;
-  for (int b0 = 0; b0 < B; b0 += (int)blockDim.x >> 5) {
-    const int b = min(b0 + (int)(threadIdx.x >> 5), B - 1);   // (halves of a wave beyond the last sequence: that one, nothing stored)
-    const bool there = b0 + (int)(threadIdx.x >> 5) < B;
+  const int end = min(((int)blockIdx.x + 1) * kCommitBatch, B);
+  for (int b0 = blockIdx.x * kCommitBatch; b0 < end; b0 += (int)blockDim.x >> 5) {
+    const int b = min(b0 + (int)(threadIdx.x >> 5), end - 1);   // (halves of a wave beyond the last sequence: that one, nothing stored)
+    const bool there = b0 + (int)(threadIdx.x >> 5) < end;
     const int fin0 = s.finished[b], a0 = accept_len[b], j0 = s.len[b], cap = s.cap[b], nt = next_token[b];
     const int t = s.last_draft[b * s.k_max + min(i, s.k_max - 1)];
     const bool live = there && !fin0 && a0 >= 0;   // a0 < 0: verification reported a failure, nothing to commit
@@ -733,15 +736,26 @@ __global__ __launch_bounds__(kCommitThreads) void commit_kernel(SeqState s, cons
   if (added) atomicAdd(&tokens, added);
   __syncthreads();
   if (threadIdx.x == 0) {
-    if (n_active) *n_active = active;
-    s.scratch[0] = c_commits + 1;        // commits
-    s.scratch[1] = c_tokens + tokens;    // tokens appended
-    s.scratch[2] = B - active;  // finished sequences
+    int n = active, m = tokens;
+    if (gridDim.x > 1) {   // (the three words are zero between commits: specdec_begin clears them, and the last block does)
+      atomicAdd(&s.scratch[4], n);
+      atomicAdd(&s.scratch[5], m);
+      __threadfence();
+      if (atomicAdd(&s.scratch[6], 1) + 1 != (int)gridDim.x) return;
+      __threadfence();
+      n = atomicExch(&s.scratch[4], 0);
+      m = atomicExch(&s.scratch[5], 0);
+      s.scratch[6] = 0;
+    }
+    if (n_active) *n_active = n;
+    s.scratch[0] = c_commits + 1;   // commits
+    s.scratch[1] = c_tokens + m;    // tokens appended
+    s.scratch[2] = B - n;           // finished sequences
   }
 }
 hipError_t commit_rows(hipStream_t st, const SeqState& s, const int* accept_len, const int* next_token, int B,
                        int k, int eos_id, int* n_active) {
-  hipLaunchKernelGGL(commit_kernel, dim3(1), dim3(std::min((B + 1) / 2 * 64, kCommitThreads)), 0, st, s, accept_len, next_token, B, min(k, s.k_max), eos_id,
+  hipLaunchKernelGGL(commit_kernel, dim3((B + kCommitBatch - 1) / kCommitBatch), dim3(std::min((B + 1) / 2 * 64, kCommitThreads)), 0, st, s, accept_len, next_token, B, min(k, s.k_max), eos_id,
                      n_active);
   return hipGetLastError();
 }

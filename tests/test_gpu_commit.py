@@ -12,7 +12,7 @@ from paper_2203_16487_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,k,max_new", [(1, 0, 3), (1, 5, 40), (2, 31, 17), (31, 3, 6), (33, 7, 9), (70, 4, 12)])
+@pytest.mark.parametrize("B,k,max_new", [(1, 0, 3), (1, 5, 40), (2, 31, 17), (31, 3, 6), (33, 7, 9), (70, 4, 12), (128, 3, 7), (129, 2, 9), (300, 1, 5)])   # (128 sequences a block)
 def test_commit(B, k, max_new):
     desc = synth.ModelDesc(0, 1, 64, 1, 256, 211, 64, 300).resolved()
     case = cases.make_verify_case(desc, seed=B + k, B=B, S=6, k=max(k, 1), beta=3, tau=1.0, len_lo=0, len_hi=9, drafts="random", ragged_src=True)
