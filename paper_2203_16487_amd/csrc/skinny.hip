@@ -261,7 +261,12 @@ __global__ __launch_bounds__(kSkThreads) void sk_ffn2_kernel(SkSrc resid, int R,
 // With four waves to 64 columns, two blocks a CU, every CU normalised all rows twice, two waves held the drafts' rows in registers that the weights
 // then lacked, and half of d = 1024's were asked for only behind the first products.  Launches, us: 6 rows of d = 512 13.4, now 8.5; 26 rows of d
 // = 1024, 8-bit weights 29.0, now 17.4.
+// TILES = 1: a vocabulary that leaves CUs without a block is dealt to twice as many, by tiles of 64 columns (four of the waves; one or two of
+// the others form the draft logits meanwhile), as a block lasts as long as its CU takes in its weights.  Whole passes of one layer, two tiles a
+// block / one, us: 16000 columns, 1 row of d = 1024 44.0 / 41.6, 16 46.7 / 44.9, 32 of d = 512 38.1 / 36.6; 1003 columns, 16 of d = 1024 46.7 /
+// 42.6; but 16448 columns, where some CUs then have two blocks, 1 row of d = 512 35.2 / 37.4, 32 of d = 1024 54.0 / 62.1.
 constexpr int kSkVocabThreads = 512;
+constexpr int kSkVocabSingle = 256;   // tiles up to which a block takes one: the CUs
 template <int PER, bool TWO, class WT>
 struct SkVocabLds {
   static constexpr int d = 64 * PER, kRows = TWO ? 32 : 16;
@@ -269,7 +274,7 @@ struct SkVocabLds {
   WT emb[kRows][d + 16 / sizeof(WT)];       // (16 bytes of padding a row)
   float zds[kSkRows], red[kSkVocabThreads / 64 * 32 * 4];
 };
-template <int PER, bool TWO, class WT>
+template <int PER, bool TWO, class WT, int TILES>
 __global__ __launch_bounds__(kSkVocabThreads) void sk_vocab_kernel(SkSrc src, int R, const WT* __restrict__ E,
                                                                    const float* __restrict__ wscale, int V,
                                                                    const int* __restrict__ row_draft,
@@ -282,12 +287,13 @@ __global__ __launch_bounds__(kSkVocabThreads) void sk_vocab_kernel(SkSrc src, in
   constexpr int d = 64 * PER, pitch = d + kSkPad, steps = d / 32, ROWS = Lds::kRows;
   constexpr int PIECES = d * (int)sizeof(WT) / 16, NE = (ROWS * PIECES + kSkVocabThreads - 1) / kSkVocabThreads;   // 16-byte pieces of a row; a thread's
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
-  const int n0 = blockIdx.x * 128 + wave * 16;
+  const bool cols = TILES == 2 || wave < 4;   // (waves without columns: beyond the last)
+  const int n0 = cols ? (int)blockIdx.x * 64 * TILES + wave * 16 : V, dw = TILES == 2 ? wave : wave - 4;   // dw: row tile whose draft logits the wave forms
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   int tok[NE];
 #pragma unroll
   for (int i = 0; i < NE; ++i) tok[i] = row_draft[min((int)(threadIdx.x + i * kSkVocabThreads) / PIECES, R - 1)];
-  const int mine = row_draft[min((wave & 1) * 16 + lq, R - 1)];   // (waves 0 and 1: the draft of the lane's row)
+  const int mine = row_draft[min((wave & 1) * 16 + lq, R - 1)];   // (of the waves that form draft logits: the draft of the lane's row)
   SkHidden<PER, ROWS / 8, 8> hs;
   const bool sum = src.np > 0;   // (same for the whole grid)
   if (!sum) {
@@ -310,7 +316,7 @@ __global__ __launch_bounds__(kSkVocabThreads) void sk_vocab_kernel(SkSrc src, in
   // (64 registers of them; bf16 at d = 1024: the second half where the rows were)
   constexpr int S1 = steps * (int)sizeof(typename SkFrag<WT>::type) <= 256 ? steps : steps / 2, S2 = steps - S1;
   typename SkFrag<WT>::type wf[S1], wf2[S2 > 0 ? S2 : 1];
-  sk_wload<S1>(E, d, n0, V, 0, wf);
+  if (cols) sk_wload<S1>(E, d, n0, V, 0, wf);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
   if (sum) sk_hidden_sum<PER, 8, PER>(src, R, ROWS, &L.hb[0][0], nullptr, -64, true, -64);
@@ -323,33 +329,35 @@ __global__ __launch_bounds__(kSkVocabThreads) void sk_vocab_kernel(SkSrc src, in
   if constexpr (S2 > 0) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    sk_wload<S2>(E, d, n0, V, S1 * 32, wf2);
+    if (cols) sk_wload<S2>(E, d, n0, V, S1 * 32, wf2);
   }
   lds_barrier();
   const bf16* hb = &L.hb[0][0];
-  if (wave < ROWS / 16) {
+  if (dw >= 0 && dw < ROWS / 16) {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
     for (int s = 0; s < steps; ++s) {
-      const bf16x8 hf = *reinterpret_cast<const bf16x8*>(hb + (wave * 16 + lq) * pitch + s * 32 + 8 * g);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sk_frag(*reinterpret_cast<const typename SkFrag<WT>::type*>(&L.emb[wave * 16 + lq][s * 32 + 8 * g])), hf, acc, 0, 0, 0);
+      const bf16x8 hf = *reinterpret_cast<const bf16x8*>(hb + (dw * 16 + lq) * pitch + s * 32 + 8 * g);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sk_frag(*reinterpret_cast<const typename SkFrag<WT>::type*>(&L.emb[dw * 16 + lq][s * 32 + 8 * g])), hf, acc, 0, 0, 0);
     }
     mfma_settle(acc);
     // D[i][j]: this lane holds j = lq, i = 4g + r; diagonal i = j  <=>  g == lq/4, r = lq%4
-    if (g == (lq >> 2) && wave * 16 + lq < R) {
+    if (g == (lq >> 2) && dw * 16 + lq < R) {
       float v = 0.f;
 #pragma unroll
       for (int r = 0; r < 4; ++r) if (r == (lq & 3)) v = acc[r];
       v = has ? v * dscale : kNegInf;   // (the row scale multiplies the sum exactly as the projection does for that column)
-      L.zds[wave * 16 + lq] = v;
-      if (blockIdx.x == 0) zd_out[wave * 16 + lq] = v;
+      L.zds[dw * 16 + lq] = v;
+      if (blockIdx.x == 0) zd_out[dw * 16 + lq] = v;
     }
   }
   f32x4 acc[2];
   sk_zero(acc);
   auto getB = [&](int t, int k) { return *reinterpret_cast<const bf16x8*>(hb + (t * 16 + lq) * pitch + k); };
-  sk_mma<S1, TWO>(wf, 0, getB, acc);
-  if constexpr (S2 > 0) sk_mma<S2, TWO>(wf2, S1 * 32, getB, acc);
+  if (cols) {
+    sk_mma<S1, TWO>(wf, 0, getB, acc);
+    if constexpr (S2 > 0) sk_mma<S2, TWO>(wf2, S1 * 32, getB, acc);
+  }
   if constexpr (!std::is_same<WT, bf16>::value) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -360,7 +368,7 @@ __global__ __launch_bounds__(kSkVocabThreads) void sk_vocab_kernel(SkSrc src, in
   float zd[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t) zd[t] = (t * 16 + lq < R) ? L.zds[t * 16 + lq] : kNegInf;
-  sk_vocab_tile(acc, n0, V, R, zd, L.red, part, n_tiles, blockIdx.x * 2, logits);
+  sk_vocab_tile<TILES>(acc, n0, V, R, zd, L.red, part, n_tiles, blockIdx.x * TILES, logits);
 }
 
 // ------------------------------------------------------------------------------------ launchers
@@ -406,8 +414,8 @@ static hipError_t sk_init_rows() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)sk_ffn2_lds_bytes<PER, 16, TWO>())) != hipSuccess) return e;
   if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(sk_ffn2_kernel<PER, 32, TWO, WT>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)sk_ffn2_lds_bytes<PER, 32, TWO>())) != hipSuccess) return e;
-  if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(sk_vocab_kernel<PER, TWO, WT>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)sizeof(SkVocabLds<PER, TWO, WT>))) != hipSuccess) return e;
+  for (const void* kernel : {reinterpret_cast<const void*>(sk_vocab_kernel<PER, TWO, WT, 1>), reinterpret_cast<const void*>(sk_vocab_kernel<PER, TWO, WT, 2>)})
+    if ((e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SkVocabLds<PER, TWO, WT>))) != hipSuccess) return e;
   return hipSuccess;
 }
 
@@ -469,10 +477,16 @@ hipError_t skinny_ffn2(hipStream_t st, const SkSrc& resid, int R, int d, const b
 hipError_t skinny_vocab(hipStream_t st, const SkSrc& src, int R, int d, SkWeight E, int V, const int* row_draft,
                         float* zd_row, float* part, float* logits) {
   const int n_tiles = (V + 63) / 64;
+  const bool single = n_tiles <= kSkVocabSingle;
   SK_DISPATCH(d, {
-    SK_ROWS(R, SK_WT(E, hipLaunchKernelGGL((sk_vocab_kernel<PER, TWO, WT>), dim3((n_tiles + 1) / 2), dim3(kSkVocabThreads),
-                                           sizeof(SkVocabLds<PER, TWO, WT>), st, src, R, Wp, E.scale, V, row_draft, zd_row,
-                                           part, n_tiles, logits)));
+    SK_ROWS(R, SK_WT(E, {
+      auto launch = [&](auto kernel, int blocks) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kSkVocabThreads), sizeof(SkVocabLds<PER, TWO, WT>), st, src, R, Wp, E.scale, V, row_draft,
+                           zd_row, part, n_tiles, logits);
+      };
+      if (single) launch(sk_vocab_kernel<PER, TWO, WT, 1>, n_tiles);
+      else launch(sk_vocab_kernel<PER, TWO, WT, 2>, (n_tiles + 1) / 2);
+    }));
   });
   return hipGetLastError();
 }

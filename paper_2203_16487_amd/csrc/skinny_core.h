@@ -412,9 +412,10 @@ __device__ __forceinline__ void sk_reduce(const f32x4 (&acc)[2], float* red, int
   }
 }
 
-// Row statistics of 64-column vocabulary tiles (16 columns per wave, four waves a tile: acc of this wave,
+// Row statistics of TILES 64-column vocabulary tiles (16 columns per wave, four waves a tile: acc of this wave,
 // first column n0; tile: the first of the block): per row the maximum, its lowest index, sum exp(z - max) and the number of
 // logits above the row's draft logit zd[t] (row t*16 + lane%16); one record per row -> part.
+template <int TILES>
 __device__ __forceinline__ void sk_vocab_tile(const f32x4 (&acc)[2], int n0, int V, int R, const float (&zd_t)[2],
                                               float* red, float* __restrict__ part, int n_tiles, int tile,
                                               float* __restrict__ logits) {
@@ -457,7 +458,7 @@ __device__ __forceinline__ void sk_vocab_tile(const f32x4 (&acc)[2], int n0, int
   }
   __syncthreads();
   const int m = threadIdx.x & (kSkRows - 1), w0 = threadIdx.x / kSkRows * 4;
-  if (w0 * 64 < (int)blockDim.x && m < R && tile + w0 / 4 < n_tiles) {
+  if (w0 < 4 * TILES && m < R && tile + w0 / 4 < n_tiles) {
     float best = kNegInf, tot = 0.f;
     int besti = 0x7fffffff, cnt = 0;
 #pragma unroll

@@ -1,6 +1,6 @@
-"""Vocabulary statistics of passes of at most 32 rows: one row tile and two with their remainders, a last block of one tile of 64 columns
-and one that the vocabulary's end cuts, bf16 weights and codes, d = 128, 512 and 1024 (half of the bf16 weights
-requested behind the LayerNorm)."""
+"""Vocabulary statistics of passes of at most 32 rows: one row tile and two with their remainders, a tile of 64 columns to a block and two
+(beyond 256 of them), a last block of one tile and one that the vocabulary's end cuts, bf16 weights and codes, d = 128, 512 and
+1024 (half of the bf16 weights requested behind the LayerNorm)."""
 import numpy as np
 import pytest
 
@@ -15,7 +15,7 @@ FFN = {128: 256, 512: 2048, 1024: 4096}
 
 
 @pytest.mark.parametrize("d,B,k,V,fp8", [
-    (128, 1, 1, 130, False),        # 2 rows; 3 tiles: the last block has one
+    (128, 1, 1, 130, False),        # 2 rows; 3 tiles
     (128, 2, 15, 1003, True),       # 32 rows
     (512, 1, 15, 1003, False),      # 16 rows: one row tile, whole
     (512, 1, 16, 1050, False),      # 17; 17 tiles
@@ -25,6 +25,13 @@ FFN = {128: 256, 512: 2048, 1024: 4096}
     (1024, 2, 15, 1050, False),     # 32
     (1024, 1, 25, 32768, True),     # 26, a block to a CU
     (1024, 1, 5, 200, True),
+    (128, 2, 15, 16384, True),      # 256 tiles: the most of which a block takes one
+    (512, 1, 15, 16384, False),
+    (512, 1, 16, 16385, False),     # 257: the last block has one, of one column
+    (128, 1, 4, 16449, True),       # 258, the last of one column
+    (512, 3, 4, 16500, True),
+    (1024, 1, 15, 16449, False),
+    (1024, 2, 15, 16385, False),
 ])
 def test_few_rows_vocab(d, B, k, V, fp8):
     desc = synth.ModelDesc(0, 1, d, d // 64, FFN[d], V, 16, 64).resolved()
