@@ -629,6 +629,7 @@ Way one_kernel_way(const Model& m, int B, int T, bool few, int cus) {
 // Whether the pass takes one of them (c->way: which).
 bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, bool few, hipStream_t st) {
   if (!m.pl_exch || T > 32 || c->no_skinny || c->no_ln_fold || c->sliced) return false;
+  if (one_kernel_way(m, B, T, few, sd::kPlBlocks) == Way::launches) return false;   // (whatever the GPU and the stream have)
   int dev = -1, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
