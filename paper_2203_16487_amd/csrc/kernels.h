@@ -286,7 +286,6 @@ struct XcdArgs {
                                           // be computed another way); those of that way too (results are void); a counter
   int RP, d, G, wpu;                      // filled by the launcher, as what follows
   unsigned *raised, *ended;
-  unsigned spin_max;
 };
 constexpr int kXcdMostRows = 512;         // rows of a pass at most: 64 on each of 8 XCDs
 constexpr int kXcdFewRows = 63;           // of a pass that reads the weights as bound (no copy of them), 32 on an XCD

@@ -51,7 +51,7 @@
 namespace sd {
 namespace xcd {
 
-constexpr unsigned kPlSpinMax = 3u << 18;   // (0.13 - 0.17 s: 2^17 polls of the L2 take 21 - 28 ms)
+constexpr unsigned kPlSpinMax = 3u << 18;   // (0.13 - 0.3 s: 2^17 polls of the L2 take 21 - 49 ms)
 constexpr int kPlGroups = 8, kPlMembers = 32;          // XCDs; workgroups of each
 constexpr int kPlWaves = 8, kPlThreads = 64 * kPlWaves;
 static_assert(kPlGroups * kPlMembers == kPlBlocks && kPlWaves == 8, "a workgroup per CU; pairs of a row's four lanes");
@@ -69,7 +69,7 @@ __device__ __forceinline__ void pl_again(unsigned& spins, const XcdArgs& a) {
   if ((spins & 63u) == 0) {
     // (the same for the whole wave, and said so: no wait is a loop of single lanes)
     const unsigned raised = __builtin_amdgcn_readfirstlane(__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    if (raised != 0u || spins > a.spin_max) {
+    if (raised != 0u || spins > kPlSpinMax) {
       __hip_atomic_store(a.err, kXcdAlonePasses, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       // (weights on their way to LDS: it may be another workgroup's next)
       asm volatile("s_waitcnt vmcnt(0)\n\ts_endpgm" ::: "memory");
@@ -941,7 +941,7 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
   Lds& L = *reinterpret_cast<Lds*>(pl_smem);
   if (!ALONE) a.RP = 16 * MR;   // known when compiled: every place in the exchange buffers is then a constant away from the layer's
   a.H = D / kHeadDim;
-  if (DIRECT) a.stream = nullptr; else a.spin_max = kPlSpinMax;   // (as an argument the bound costs 0.1 - 0.6 % of a pass)
+  if (DIRECT) a.stream = nullptr;
   if (!ALONE && !DIRECT) __builtin_assume(a.stream != nullptr);
   // (one look for all waves: others may raise the flag meanwhile, and none of a workgroup's waves is to go on without the rest)
   if (threadIdx.x == 0) L.row_at[0] = (int)__hip_atomic_load(a.raised, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1192,6 +1192,7 @@ static hipError_t pl_launch_both(hipStream_t st, XcdArgs a, int blocks) {
     if (a.RP == 64) e = pl_launch<KV8, D, 4, false>(st, a, blocks);
   }
   if (e != hipSuccess) return e;
+  a.raised = a.err;
   a.err += 1;
   return pl_launch<KV8, D, 4, true>(st, a, a.G);
 }
@@ -1226,9 +1227,14 @@ hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F, bool give_up) {
   a.raised = a.err;
   a.ended = a.err + 2;
   // give_up: a place of every group stays empty, as where other kernels hold compute units: the waits for it end at their bound.  (A bound
-  // passed as an argument, or where a wait's count starts, cost 0.1 - 0.6 % of every pass.)
+  // passed as an argument, or where a wait's count starts, cost 0.1 - 0.6 % of every pass.)  Weights in place: at their first look at the flag,
+  // which is raised beforehand; whether it is, the workgroups then ask of the second run's.
   const int blocks = give_up ? kPlBlocks - xcd::kPlGroups : kPlBlocks;
-  a.spin_max = give_up ? 63 : xcd::kPlSpinMax;   // (weights in place; after a look at the flag)
+  if (give_up && !a.stream) {
+    const hipError_t e = fill_i32(st, reinterpret_cast<int*>(a.err), kXcdAlonePasses, 1);
+    if (e != hipSuccess) return e;
+    a.raised = a.err + 1;
+  }
   if (d == 512) return a.xk_scale ? xcd::pl_launch_both<true, 512>(st, a, blocks) : xcd::pl_launch_both<false, 512>(st, a, blocks);
   return a.xk_scale ? xcd::pl_launch_both<true, 1024>(st, a, blocks) : xcd::pl_launch_both<false, 1024>(st, a, blocks);
 }
