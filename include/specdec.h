@@ -344,6 +344,16 @@ typedef enum {
 int specdec_profile_select(specdec_ctx* ctx, int32_t kind);
 int specdec_profile_read(specdec_ctx* ctx, double* total_ms /*host*/, int32_t* launches /*host*/);
 
+/* Which kernels the decoder layers of the latest specdec_verify went to (SPECDEC_WAY_LAUNCHES before the first; -1 without a
+ * context).  Host only.  Where several could take a pass its rows, its stream and the weights decide; they round differently. */
+typedef enum {
+  SPECDEC_WAY_LAUNCHES = 0,      /* launches for every stage of a layer */
+  SPECDEC_WAY_GPU = 1,           /* one kernel, every stage over the whole GPU */
+  SPECDEC_WAY_XCD = 2,           /* one kernel, each XCD on sequences of its own, from a copy of the weights in order of use */
+  SPECDEC_WAY_XCD_IN_PLACE = 3   /* the same from the weights as bound */
+} specdec_way;
+int specdec_decoder_way(const specdec_ctx* ctx);
+
 #ifdef __cplusplus
 }
 #endif

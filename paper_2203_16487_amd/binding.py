@@ -80,6 +80,7 @@ EXPORTS = {
     "specdec_rewind": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p]),
     "specdec_profile_select": (C.c_int, [C.c_void_p, C.c_int32]),
     "specdec_profile_read": (C.c_int, [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_int32)]),
+    "specdec_decoder_way": (C.c_int, [C.c_void_p]),
     "specdec_get_output": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
     "specdec_get_cache": (C.c_int, [C.c_void_p, C.c_int, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p]),
     "specdec_get_row_stats": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p]),
@@ -273,6 +274,13 @@ def specdec_profile_read(ctx):
     ms, n = C.c_double(), C.c_int32()
     _check(ctx, lib().specdec_profile_read(ctx, C.byref(ms), C.byref(n)))
     return ms.value, n.value
+
+
+WAYS = ("launches", "gpu", "xcd", "xcd in place")   # SPECDEC_WAY_*
+
+
+def specdec_decoder_way(ctx) -> str:
+    return WAYS[lib().specdec_decoder_way(ctx)]
 
 
 def specdec_get_output(ctx, tokens, out_len, finished=None):

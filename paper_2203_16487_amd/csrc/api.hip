@@ -48,7 +48,9 @@ struct Fp8Layer {
 
 // How the decoder layers of a verify pass run: launches a stage; as one kernel over the whole GPU (persist.hip); as one kernel, each XCD
 // on sequences of its own (xcd.hip), from a copy of the weights in order of use or, a few rows, from the weights as bound.
-enum class Way { launches, gpu, xcd, xcd_few };
+enum class Way {
+  launches = SPECDEC_WAY_LAUNCHES, gpu = SPECDEC_WAY_GPU, xcd = SPECDEC_WAY_XCD, xcd_few = SPECDEC_WAY_XCD_IN_PLACE
+};
 
 struct Model {
   bool bound = false;
@@ -1220,6 +1222,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   // themselves, where that is little: one sequence of few rows, d = 512 (3 rows 184 against 205 us, 11: 210 / 214, 16: 220 /
   // 218; two sequences of 6 235 / 214; d = 1024: 6 rows 285 / 268, 26 521 / 302).  Otherwise the general ones.
   const bool one = persist_ok(c, m, B, T, small, st);
+  if (!one) c->way = Way::launches;
   const bool fused = small && !one && (c->no_ln_fold || c->sliced || (B == 1 && R <= 12 && m.d.d_model <= 512));
   VerifyScratch vs{m.part, m.zd, m.row_stats};
   if (ext) {
@@ -1463,6 +1466,8 @@ int specdec_quantize_rows(specdec_ctx* c, const void* w, int64_t N, int64_t K, v
                                    static_cast<unsigned char*>(codes), scale));
   return SPECDEC_OK;
 }
+
+int specdec_decoder_way(const specdec_ctx* c) { return c ? static_cast<int>(c->way) : -1; }
 
 int specdec_get_row_stats(specdec_ctx* c, float* stats, void* stream) {
   int rc = check_ready(c, SPECDEC_VERIFIER, false);

@@ -143,7 +143,7 @@ def test_options_and_new_entry_points_validate_their_arguments():
 
 @pytest.mark.parametrize("d,batch,k_max,held", [
     (512, 1, 10, False),
-    (512, 21, 2, False),      # 63 rows: the one-kernel decoder over the whole GPU takes them all
+    (512, 21, 2, False),      # 63 rows: read from the matrices as they are bound
     (512, 32, 1, True),       # 64 rows
     (1024, 1, 25, False),
     (1024, 64, 1, False),     # 128 rows

@@ -28,7 +28,7 @@ def test_few_rows_in_place(B, k, S, lo, hi, opts, half):
     cases.run_oracle(case)
     ses = gh.open_verifier(case, k_max=max(k, 1), options=opts, fill=0xFF)
     n, out = resident_launches(ses, lambda: gh.gpu_verify(ses, case))
-    assert n == 1
+    assert n == 1 and sd.specdec_decoder_way(ses.ctx) == "xcd in place"
     check(case, out)
     assert np.array_equal(gh.gpu_verify(ses, case)["logits"], out["logits"])
     K, V = gh.gpu_cache(ses, case, case.L_max + k + 1)
@@ -43,6 +43,6 @@ def test_few_rows_in_place(B, k, S, lo, hi, opts, half):
         with torch.cuda.stream(stream):
             n, apart = resident_launches(ses, lambda: gh.gpu_verify(ses, case))
         stream.synchronize()
-        assert n == half
+        assert n == half and sd.specdec_decoder_way(ses.ctx) == ("gpu" if half else "launches")
         check(case, apart)
     ses.close()

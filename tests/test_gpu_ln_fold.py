@@ -37,8 +37,8 @@ SHIFT, BOUND = 4.0, 1.1
 
 
 @pytest.mark.parametrize("d,B,k", [
-    (512, 1, 25), (1024, 1, 9), (1024, 9, 8),       # one kernel over the whole GPU; the last on items of 32 rows
-    (512, 12, 10), (512, 30, 10), (1024, 17, 8),    # one kernel, per XCD: two and three row tiles
+    (1024, 1, 9), (1024, 9, 8),                     # one kernel over the whole GPU; the last on items of 32 rows
+    (512, 1, 25), (512, 12, 10), (512, 30, 10), (1024, 17, 8),   # one kernel, per XCD: the first with weights in place
     (512, 48, 10),                                  # 528 rows: launches
 ])
 def test_verify_of_rows_off_zero(d, B, k):

@@ -1,6 +1,7 @@
 """The decoder layers of a pass of few rows as one kernel (d_model 512 / 1024), over the whole GPU or per XCD: row tiles and their
 remainders, queries beyond one tile of 16, key chunks split over the waves and not, a unit of attention per workgroup and per wave,
 E4M3 weights and cross keys / values, against the oracle; waits given up; the path a second context takes; replays of a captured pass."""
+import contextlib
 import ctypes as C
 
 import numpy as np
@@ -30,28 +31,39 @@ def check(case, out):
 FP8_W, FP8_KV = {sd.SPECDEC_OPT_FP8_WEIGHTS: 1}, {sd.SPECDEC_OPT_FP8_CROSS_KV: 1}
 
 
-def way_of(ses, case):
-    """Which of the two kernels a pass takes: waits given up end at once over the whole GPU, and at their bound (0.1 s or more) per XCD."""
-    sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_GIVE_UP_WAITS, 1)
-    sd.specdec_profile_select(ses.ctx, sd.KIND["resident"])
-    gh.gpu_verify(ses, case, want_logits=False)
-    ms, n = sd.specdec_profile_read(ses.ctx)
-    sd.specdec_profile_select(ses.ctx, sd.KIND["none"])
-    sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_GIVE_UP_WAITS, 0)
-    return "launches" if n == 0 else "xcd" if ms > 100 else "gpu"
+def masked_stream(words):
+    """A stream whose kernels may use the compute units of this mask only."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    hip, handle = C.CDLL(path), C.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(C.byref(handle), C.c_uint32(len(words)), (C.c_uint32 * len(words))(*words)) == 0
+    return torch.cuda.ExternalStream(handle.value)
+
+
+@contextlib.contextmanager
+def compute_units(n):
+    """What is inside runs on a stream that may use n compute units (a multiple of 32; None: the default stream)."""
+    if n is None:
+        yield
+        return
+    torch.cuda.synchronize()
+    stream = masked_stream([0xffffffff] * (n // 32) + [0] * (8 - n // 32))
+    with torch.cuda.stream(stream):
+        yield
+    stream.synchronize()
 
 
 @pytest.mark.parametrize("way,d,B,k,S,lo,hi,opts", [
+    # per XCD, weights in place; rows of an XCD, row tiles
+    ("xcd in place", 512, 1, 1, 5, 0, 0, {}),       # two rows, nothing cached
+    ("xcd in place", 512, 1, 16, 40, 31, 31, {}),   # 17, two: a second query tile of one row
+    ("xcd in place", 512, 2, 15, 200, 180, 220, {}),   # every wave has key chunks
+    ("xcd in place", 512, 3, 15, 90, 20, 60, {}),   # 16, one
+    ("xcd in place", 512, 9, 6, 40, 0, 75, {}),     # 14 and 7; 63 rows, the most
+    ("xcd in place", 512, 63, 0, 20, 0, 40, {}),    # 8 and 7: plain steps
+    ("xcd in place", 512, 3, 9, 50, 0, 40, FP8_KV),
+    ("xcd in place", 512, 21, 2, 50, 0, 40, FP8_KV),   # 9 and 6; 63 rows
     # over the whole GPU
-    ("gpu", 512, 1, 1, 5, 0, 0, {}),                # two rows, nothing cached
-    ("gpu", 512, 1, 16, 40, 31, 31, {}),            # 17 rows: a second query tile of one row
-    ("gpu", 512, 2, 15, 200, 180, 220, {}),         # every wave has key chunks
-    ("gpu", 512, 3, 15, 90, 20, 60, {}),            # 48 rows: three row tiles, items of four column tiles
-    ("gpu", 512, 9, 6, 40, 0, 75, {}),              # 63 rows, the most; workgroups with several kinds of items
-    ("gpu", 512, 63, 0, 20, 0, 40, {}),             # plain steps: more units of attention than workgroups
     ("gpu", 512, 3, 9, 50, 0, 40, FP8_W),
-    ("gpu", 512, 3, 9, 50, 0, 40, FP8_KV),
-    ("gpu", 512, 21, 2, 50, 0, 40, FP8_KV),         # 63 rows
     ("gpu", 1024, 1, 25, 90, 57, 57, {}),
     ("gpu", 1024, 16, 3, 30, 0, 40, {}),            # 64 rows, the most on tiles of 16 rows
     ("gpu", 1024, 13, 4, 30, 0, 140, {}),           # 65 rows: tiles of 32, the last of one row
@@ -93,9 +105,8 @@ def test_against_oracle(way, d, B, k, S, lo, hi, opts):
     again = gh.gpu_verify(ses, case)
     L = case.L_max + k + 1
     K, V = gh.gpu_cache(ses, case, L)
-    taken = way_of(ses, case)
+    assert sd.specdec_decoder_way(ses.ctx) == way
     ses.close()
-    assert taken == way
     check(case, out)
     assert np.array_equal(out["logits"], again["logits"])
     for b, st in enumerate(case.states):
@@ -105,7 +116,51 @@ def test_against_oracle(way, d, B, k, S, lo, hi, opts):
             assert np.abs(V[l, b, j:j + k + 1] - st.V[l][j:j + k + 1]).max() <= 3e-2, (b, l)
 
 
-@pytest.mark.parametrize("B,k", [(2, 5), (9, 10)])   # over the whole GPU; 99 rows: per XCD
+@pytest.mark.parametrize("way,cus,B,k,S,lo,hi,opts", [
+    ("gpu", 128, 1, 5, 32, 16, 16, {}),             # 104 workgroups
+    ("gpu", 224, 1, 16, 40, 31, 31, {}),            # 17 rows: a second query tile of one row; 208 workgroups
+    ("gpu", 224, 2, 15, 200, 180, 220, {}),         # every wave has key chunks
+    ("gpu", 224, 3, 15, 90, 20, 60, {}),            # 48 rows, the most: three row tiles, items of four column tiles; 216
+    ("gpu", 224, 2, 16, 60, 0, 75, FP8_KV),         # 34: the last row tile of two rows; 224
+    ("gpu", 224, 4, 7, 50, 0, 40, FP8_KV),          # 32; 224
+    ("gpu", 224, 16, 0, 50, 0, 40, {}),             # plain steps: 16 rows; 224
+    ("launches", 224, 8, 4, 50, 0, 40, {}),         # 40: 256
+    ("launches", 224, 7, 6, 50, 0, 40, {}),         # 49 rows
+    ("launches", 192, 1, 16, 40, 31, 31, {}),
+])
+def test_against_oracle_on_fewer_compute_units(way, cus, B, k, S, lo, hi, opts):
+    """bf16 weights of d_model 512 go over the whole GPU where the stream has fewer compute units than there are, but as many as the kernel has
+    workgroups; given up, the kernel behind it gives the same bits."""
+    case = cases.make_verify_case(desc(512), seed=512 + cus + 10 * B + k, B=B, S=S, k=k, beta=3, tau=1.0, len_lo=lo, len_hi=hi, drafts="random",
+                                  ragged_src=True, fp8_kv=sd.SPECDEC_OPT_FP8_CROSS_KV in opts)
+    cases.run_oracle(case)
+    L = case.L_max + k + 1
+    with compute_units(cus):
+        ses = gh.open_verifier(case, k_max=max(k, 1), options=opts, fill=0xFF)
+        sd.specdec_profile_select(ses.ctx, sd.KIND["resident"])
+        out = gh.gpu_verify(ses, case)
+        ms, n = sd.specdec_profile_read(ses.ctx)
+        assert sd.specdec_decoder_way(ses.ctx) == way and n == (way == "gpu")
+        assert ms < 50                                 # no wait ended at its bound
+        K, V = gh.gpu_cache(ses, case, L)
+        for give_up in (0, 1, 0):
+            sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_GIVE_UP_WAITS, give_up)
+            got = gh.gpu_verify(ses, case)
+            for key in ("logits", "accept", "next", "stats"):
+                assert np.array_equal(got[key], out[key]), (give_up, key)
+            for x, y in zip(gh.gpu_cache(ses, case, L), (K, V)):
+                for b, j in enumerate(case.lens):
+                    assert np.array_equal(x[:, b, :j + k + 1], y[:, b, :j + k + 1])
+        ses.close()
+    check(case, out)
+    for b, st in enumerate(case.states):
+        j = int(case.lens[b])
+        for l in range(case.desc.dec_layers):
+            assert np.abs(K[l, b, j:j + k + 1] - st.K[l][j:j + k + 1]).max() <= 3e-2, (b, l)
+            assert np.abs(V[l, b, j:j + k + 1] - st.V[l][j:j + k + 1]).max() <= 3e-2, (b, l)
+
+
+@pytest.mark.parametrize("B,k", [(2, 5), (9, 10)])   # per XCD: weights in place; 99 rows
 def test_two_contexts_and_replays(B, k):
     case = cases.make_verify_case(desc(512), seed=5, B=B, S=30, k=k, beta=3, tau=1.0, len_lo=3, len_hi=20, drafts="greedy",
                                   ragged_src=True)
@@ -139,11 +194,15 @@ def test_two_contexts_and_replays(B, k):
 
 
 @pytest.mark.parametrize("way,d,B,k,S,lo,hi,opts", [
-    ("gpu", 512, 1, 5, 32, 16, 16, {}),
-    ("gpu", 512, 2, 15, 200, 180, 220, {}),         # a unit of attention per workgroup, every wave with key chunks
-    ("gpu", 512, 9, 6, 40, 0, 75, {}),              # 63 rows
-    ("gpu", 512, 63, 0, 20, 0, 40, {}),             # more units than workgroups
-    ("gpu", 1024, 64, 1, 40, 50, 70, {}),           # the same, items of 32 rows
+    # per XCD, weights in place
+    ("xcd in place", 512, 1, 5, 32, 16, 16, {}),
+    ("xcd in place", 512, 2, 15, 200, 180, 220, {}),   # every wave with key chunks
+    ("xcd in place", 512, 9, 6, 40, 0, 75, {}),     # 63 rows, 14 and 7 of an XCD
+    ("xcd in place", 512, 63, 0, 20, 0, 40, {}),
+    # over the whole GPU
+    ("gpu", 512, 1, 5, 32, 16, 16, FP8_W),
+    ("gpu", 512, 2, 15, 200, 150, 180, FP8_W),      # a unit of attention per workgroup, every wave with key chunks
+    ("gpu", 1024, 64, 1, 40, 50, 70, {}),           # more units than workgroups, items of 32 rows
     ("gpu", 1024, 11, 10, 150, 100, 130, FP8_KV),
     ("gpu", 1024, 1, 30, 33, 9, 9, {**FP8_W, **FP8_KV}),
     # per XCD; rows of an XCD
@@ -157,8 +216,8 @@ def test_two_contexts_and_replays(B, k):
     ("xcd", 1024, 17, 20, 45, 30, 90, FP8_KV),      # 63 and 42; two query tiles a sequence
 ])
 def test_waits_given_up(way, d, B, k, S, lo, hi, opts):
-    """Waits of the kernel given up at once (per XCD: at their bound, as a workgroup of every group is missing; either way it ends with
-    half of its results missing): the kernel behind it computes the pass, to the last bit as the waiting one; so it does the next 63
+    """Waits of the kernel given up at once (per XCD: at their bound, as a workgroup of every group is missing, or with weights in place at
+    their first look at the flag; either way it ends with half of its results missing): the kernel behind it computes the pass, to the last bit as the waiting one; so it does the next 63
     (15), which find the flag raised; then one waits again."""
     case = cases.make_verify_case(desc(d), seed=d + B, B=B, S=S, k=k, beta=3, tau=1.0, len_lo=lo, len_hi=hi, drafts="random",
                                   ragged_src=True, fp8=sd.SPECDEC_OPT_FP8_WEIGHTS in opts, fp8_kv=sd.SPECDEC_OPT_FP8_CROSS_KV in opts)
@@ -166,6 +225,7 @@ def test_waits_given_up(way, d, B, k, S, lo, hi, opts):
     ses = gh.open_verifier(case, k_max=max(k, 1), options=opts, fill=0xFF)
     L = case.L_max + k + 1
     want, cache = gh.gpu_verify(ses, case), gh.gpu_cache(ses, case, L)
+    assert sd.specdec_decoder_way(ses.ctx) == way
     check(case, want)
     sd.specdec_profile_select(ses.ctx, sd.KIND["resident"])
     times = []
@@ -219,8 +279,8 @@ def test_finished_sequences_per_xcd(d, B, k):
 
 
 def test_each_decoder_gives_up_for_itself():
-    """Passes of 9 rows run over the whole GPU, of 99 per XCD: where one kind has given up its waits, the other still waits (its kernel
-    takes some 40 us, 5 where it finds its flag raised)."""
+    """Passes of 9 rows read the weights in place, of 99 a copy of them, both per XCD: where one kind has given up its waits, the other still
+    waits (its kernel takes some 40 us, 5 where it finds its flag raised)."""
     case = cases.make_verify_case(desc(512), seed=95, B=9, S=30, k=10, beta=3, tau=1.0, len_lo=0, len_hi=20, drafts="random", ragged_src=True)
     cases.run_oracle(case)
     ses = gh.open_verifier(case, fill=0xFF)
@@ -233,7 +293,10 @@ def test_each_decoder_gives_up_for_itself():
     def many():
         return gh.gpu_verify(ses, case)["logits"]
 
-    want = {f: f() for f in (few, many)}
+    want = {}
+    for f, way in ((few, "xcd in place"), (many, "xcd")):
+        want[f] = f()
+        assert sd.specdec_decoder_way(ses.ctx) == way
     sd.specdec_profile_select(ses.ctx, sd.KIND["resident"])
     for given_up, other in ((few, many), (many, few)):
         sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_GIVE_UP_WAITS, 1)
@@ -256,14 +319,6 @@ def resident_launches(ses, run):
     n = sd.specdec_profile_read(ses.ctx)[1]
     sd.specdec_profile_select(ses.ctx, sd.KIND["none"])
     return n, out
-
-
-def masked_stream(words):
-    """A stream whose kernels may use the compute units of this mask only."""
-    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
-    hip, handle = C.CDLL(path), C.c_void_p()
-    assert hip.hipExtStreamCreateWithCUMask(C.byref(handle), C.c_uint32(len(words)), (C.c_uint32 * len(words))(*words)) == 0
-    return torch.cuda.ExternalStream(handle.value)
 
 
 def test_stream_with_few_compute_units():
