@@ -241,7 +241,7 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * workgroups that wait for each other; where a
  * kernel of another stream or process keeps some of them from starting for 0.1 s or more, the waits
  * are given up and a second kernel, which needs no more than one free compute unit, computes
- * the pass instead (same bits, 0.5 - 3 ms; in groups 7 - 14); so it does the run's next 63 (15) passes without
+ * the pass instead (same bits, 0.4 - 3 ms); so it does the run's next 63 passes without
  * waiting first.  (SPECDEC_OPT_SMALL_BATCH_KERNELS = 0: separate launches, which share a GPU freely.)
  * One stream of one process at a time runs such passes on a
  * GPU: that of the first context to ask, until it and the others on its stream are destroyed (a

@@ -260,7 +260,7 @@ struct PlArgs {
   struct PlTickets* tickets;
 };
 constexpr int kPlBlocks = 256;            // most workgroups of a pass
-constexpr int kPlFlags = 2, kXcdFlags = 3;   // words of PlArgs::err, XcdArgs::err: each decoder's passes are counted for themselves
+constexpr int kPlFlags = 2, kXcdFlags = 2;   // words of PlArgs::err, XcdArgs::err: each decoder's passes are counted for themselves
 bool persist_supported(int layers, int d, int F);
 size_t persist_exch_bytes(int rows, int layers, int d, int F);
 int persist_plan(PlArgs& a, int d, int F);   // workgroups of a pass of a.R rows, a.B sequences, a.H heads (0: too many rows)
@@ -282,14 +282,14 @@ struct XcdArgs {
   const float *xk_scale, *xv_scale;
   size_t kv_layer, xkv_layer;
   char* exch;                             // xcd_plan bytes of it 0xff when the kernel starts
-  unsigned* err;                          // [3], zero at first and kept from pass to pass: waits were given up (passes yet to
-                                          // be computed another way); those of that way too (results are void); a counter
+  unsigned* err;                          // [2], zero at first and kept from pass to pass: waits were given up (passes yet to
+                                          // be computed another way); those of that way too (results are void)
   int RP, d, G, wpu;                      // filled by the launcher, as what follows
-  unsigned *raised, *ended;
+  unsigned* raised;
+  PlTickets* tickets;
 };
 constexpr int kXcdMostRows = 512;         // rows of a pass at most: 64 on each of 8 XCDs
 constexpr int kXcdFewRows = 63;           // of a pass that reads the weights as bound (no copy of them), 32 on an XCD
-constexpr unsigned kXcdAlonePasses = 16;  // that are computed without waits (7 - 14 ms each) after waits were given up
 // Weights (bf16) of a model's layers (device array) in the order they are used, and their column vectors.
 size_t xcd_stream_bytes(int layers, int d, int F);
 size_t xcd_vec_bytes(int layers, int d);

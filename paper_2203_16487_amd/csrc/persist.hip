@@ -36,9 +36,7 @@
 namespace sd {
 
 constexpr unsigned kPlSpinMax = 1u << 17;   // (0.1 - 0.2 s)
-constexpr unsigned kPlTicketSpinMax = 1u << 24;
 constexpr int kPlTicketBlocks = 64;
-constexpr unsigned kPlTicketPasses = 64;    // (a wait in vain then costs 2 - 3 ms a pass)
 __device__ __forceinline__ bool pl_missing(const u32x4& v) {
   return v[0] == kPoison || v[1] == kPoison || v[2] == kPoison || v[3] == kPoison;
 }
@@ -88,7 +86,6 @@ __device__ __forceinline__ int pl_opaque(int v) {
   return v;
 }
 
-constexpr int kPlLayers = 32;
 constexpr int kPlQPitch = 72;   // (16 rows of 144 bytes: a 16-byte read of every row meets all banks once)
 
 // NP: pairs (row tile, column tile) of the largest item; more than four: one set of partial tiles instead of two in turn
@@ -605,12 +602,6 @@ __device__ __forceinline__ bool pl_attention(const PlArgs& a, const PlExch& ex, 
   lds_barrier();
   return true;
 }
-
-// What the ticket kernel counts with, ahead of the exchange buffers (all words ~0 when a pass starts): tickets drawn, and per
-// stage the virtual workgroups that have finished it.
-constexpr int kPlStages = 8;
-struct PlTickets { unsigned drawn, done[kPlStages * kPlLayers]; };
-constexpr size_t kPlTicketBytes = (sizeof(PlTickets) + 255) & ~size_t(255);
 
 // WT: weights (bf16 or E4M3 codes).  KV8: cross-attention keys / values as E4M3 codes.
 // MR: row tiles of an item.  FBW: column tiles of an item of the wide projections (QKV, first FFN matrix).

@@ -7,6 +7,15 @@ namespace sd {
 
 constexpr unsigned kPoison = 0xffffffffu;   // "not there yet", in every 32-bit word of the exchange buffers when a pass starts
 __device__ __forceinline__ unsigned not_poison(unsigned u) { return u == kPoison ? 0x7fc07fc0u : u; }   // (a NaN for a NaN)
+
+// What the kernels behind them, which run a pass given up by tickets, count with, ahead of the exchange buffers (all words ~0 when a pass
+// starts): tickets drawn, and per stage the virtual workgroups that have finished it.
+constexpr int kPlLayers = 32, kPlStages = 8;
+struct PlTickets { unsigned drawn, done[kPlStages * kPlLayers]; };
+constexpr size_t kPlTicketBytes = (sizeof(PlTickets) + 255) & ~size_t(255);
+constexpr unsigned kPlTicketSpinMax = 1u << 24;
+constexpr unsigned kPlTicketPasses = 64;    // passes that go to it once waits were given up (a wait in vain then costs 2 - 5 ms a pass)
+
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
