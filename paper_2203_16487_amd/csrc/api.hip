@@ -206,13 +206,19 @@ bool desc_ok(const specdec_model_desc* d) {
          d->mask_id >= 0 && d->mask_id < d->vocab;
 }
 constexpr long kPrefillRows = 8192;
-// Most rows of a pass the one-kernel decoder over the whole GPU is asked for.  At d = 512 the per-XCD one is the faster for any number of
-// rows, and takes them all where the stream has every compute unit and the weights are bf16; whole passes, whole GPU / per XCD, us: 1 row
-// 129 / 113, 6 132 / 116, 22 (two sequences) 142 / 121, 26 (one) 144 / 138, 48 144 / 128, 63 (one a sequence) 173 / 139 (launches: 6 rows 234,
-// 48 246).  At d = 1024 every XCD reads 176 MB of weights: 6 rows 178 / 226, 26 216 / 266, 44 239 / 272, 77 287 / 281, 88 300 / 283, 99 303 /
-// 303, 121 296 / 310, 128 338 / 344 (launches: 6 rows 266, 128 407, 352 497 and per XCD 377).
-constexpr size_t persist_rows(int d) { return d <= 512 ? 63 : 128; }
-static_assert(persist_rows(512) == sd::kXcdFewRows, "beyond, the per-XCD decoder streams a copy of the weights");
+// Most rows of a pass the one-kernel decoder over the whole GPU is asked for.
+// At d = 512 the per-XCD one takes all rows where the stream has every compute unit and the weights are bf16.  Whole passes, whole GPU / per XCD,
+// us, 40 source tokens: 1 row 110 / 107, 6 112 / 109, 22 (two sequences) 120 / 111, 48 (three) 128 / 118, (eight) 131 / 125, 63 (one a sequence)
+// 158 / 133, of 1000 source tokens 10 rows 167 / 146, 62 (two) 194 / 167.  One sequence of 17 - 32 rows is the exception while its keys are few: 26
+// rows 124 / 133, on 200 source tokens and 180 cached ones 32 rows 142 / 143, on 1000 175 / 168; two of 17 and 24 are close (131 / 134, on
+// 1000 175 / 163).  How many there are the host does not know, and one kernel for all of a sequence's life gives it the same bits.  (Launches: 6
+// rows 234, 48 246.)  The other one has what comes with codes (32 rows at most), and bf16 weights on a stream that lacks compute units, but has
+// as many as it has workgroups: beyond 48 rows its plan takes all 256.
+// At d = 1024 every XCD reads 176 MB of weights.  64 source tokens: 6 rows 158 / 217, 26 194 / 253, 44 (four sequences) 227 / 268, 64 (one each) 270 /
+// 305, 66 (11 each, as what follows) 264 / 270, 77 266 / 270, 88 277 / 272, 99 281 / 295, 110 282 / 294, 121 282 / 301; one each 80 310 / 314, 128 325
+// / 335; 26 each 78 267 / 260.  512 source tokens: 77 299 / 293, 88 314 / 304, 99 318 / 330, 121 320 / 333; but 64 sequences of two rows 474 /
+// 448, 128 of one 651 / 611, whose attention is most of the pass.  (Launches: 6 rows 266, 128 407; 352 497 and per XCD 363.)
+constexpr size_t persist_rows(int d) { return d <= 512 ? 48 : 128; }
 constexpr int kEncT = 12, kDecT = 20;
 int n_weights(const specdec_model_desc* d) { return 1 + kEncT * d->enc_layers + kDecT * d->dec_layers; }
 
@@ -328,7 +334,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     t.pl_rows = (int)(most < persist_rows((int)D) ? most : persist_rows((int)D));
     // The per-XCD decoder's share only where a pass within the limits can be its (one_kernel_way).  (In a drafter's workspace too, which
     // uses neither: the size is asked for without a role.)
-    const bool per_xcd = sd::xcd_rows_most((int)Bm, c->lim.k_max + 1) > t.pl_rows;
+    const bool per_xcd = sd::xcd_rows_most((int)Bm, c->lim.k_max + 1) > (D == 512 ? sd::kXcdFewRows : (int)persist_rows((int)D));
     const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F);
     const size_t xcd = per_xcd || D == 512 ? sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F) : 0;
     t.pl_exch = cv.take<char>(one > xcd ? one : xcd);
