@@ -16,14 +16,16 @@ pytestmark = pytest.mark.gpu
 def test_round_trip_and_prefix(d, layers, B, L):
     desc = synth.ModelDesc(0, layers, d, d // 64, 4 * d, 1003, 64, 300).resolved()
     case = cases.make_verify_case(desc, seed=d + L, B=B, S=9, k=2, beta=3, tau=1.0, len_lo=L, len_hi=L, drafts="random", ragged_src=True)
-    ses = gh.open_verifier(case, fill=0xFF)
+    ses = gh.open_verifier(case, max_new=2, fill=0xFF)
     gen = torch.Generator(device="cuda").manual_seed(d)
     K, V = (torch.randn((layers, B, L, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
     n = ses.i32(np.arange(B) % (L + 1))                   # (rows beyond the count are stored all the same)
     lens = ses.i32(np.full(B, L) - np.arange(B) % 2)
+    toks, m, fin = (torch.zeros(s, dtype=torch.int32, device="cuda") for s in ((B, 4), B, B))
     got = []
     for prefix in (False, True):
         zeros = torch.zeros_like(K)
+        sd.specdec_set_stream(ses.ctx, ses.i32((case.tokens + 1) % 211), ses.i32(np.arange(B) % 2))   # (whatever is not set below is another stream's)
         sd.specdec_load_cache(ses.ctx, sd.SPECDEC_VERIFIER, zeros, zeros, n)
         if prefix:
             sd.specdec_set_prefix(ses.ctx, sd.SPECDEC_VERIFIER, ses.i32(case.tokens), lens, K, V)
@@ -35,9 +37,19 @@ def test_round_trip_and_prefix(d, layers, B, L):
         assert torch.equal(k2.view(torch.int16), K.view(torch.int16)) and torch.equal(v2.view(torch.int16), V.view(torch.int16))
         acc, nxt = ses.i32(np.zeros(B)), ses.i32(np.zeros(B))
         sd.specdec_verify(ses.ctx, ses.i32(case.drafts), case.k, case.beta, case.tau, acc, nxt)
-        got.append((acc.cpu().tolist(), nxt.cpu().tolist()))
-        assert min(got[-1][0]) >= 0                       # every row below its length counts as cached
+        a, t = acc.cpu().tolist(), nxt.cpu().tolist()
+        assert min(a) >= 0                                # every row below its length counts as cached
+        sd.specdec_commit(ses.ctx, acc, nxt)              # (lengths, starts, caps)
+        sd.specdec_get_output(ses.ctx, toks, m, fin)
+        got.append((a, t, toks.cpu().tolist(), m.cpu().tolist(), fin.cpu().tolist()))
+        for b in range(B):
+            want = (case.drafts[b, :a[b]].tolist() + [t[b]])[:2]
+            if desc.eos_id in want:
+                want = want[:want.index(desc.eos_id) + 1]
+            assert got[-1][3][b] == len(want) and got[-1][2][b][:len(want)] == want, b
+            assert got[-1][4][b] == (len(want) == 2 or desc.eos_id in want), b
     assert got[0] == got[1]
+    sd.specdec_set_stream(ses.ctx, ses.i32(case.tokens), lens)
     sd.specdec_load_cache(ses.ctx, sd.SPECDEC_VERIFIER, K, V, n)
     sd.specdec_verify(ses.ctx, ses.i32(case.drafts), case.k, case.beta, case.tau, acc, nxt)
     short = (n < lens).cpu().tolist()

@@ -217,8 +217,8 @@ def test_two_contexts_and_replays(B, k):
 ])
 def test_waits_given_up(way, d, B, k, S, lo, hi, opts):
     """Waits of the kernel given up at once (per XCD: at their bound, as a workgroup of every group is missing, or with weights in place at
-    their first look at the flag; either way it ends with half of its results missing): the kernel behind it computes the pass, to the last bit as the waiting one; so it does the next 63,
-    which find the flag raised; then one waits again."""
+    their first look at the flag; either way it ends with half of its results missing): the kernel behind it computes the pass, to the
+    last bit as the waiting one; so it does the next 63, which find the flag raised; then one waits again."""
     case = cases.make_verify_case(desc(d), seed=d + B, B=B, S=S, k=k, beta=3, tau=1.0, len_lo=lo, len_hi=hi, drafts="random",
                                   ragged_src=True, fp8=sd.SPECDEC_OPT_FP8_WEIGHTS in opts, fp8_kv=sd.SPECDEC_OPT_FP8_CROSS_KV in opts)
     cases.run_oracle(case)

@@ -6,6 +6,8 @@ import pytest
 
 import cases
 import gpu_harness as gh
+import specdec_oracle as orc
+import test_gpu_parity_extra as extra
 from paper_2203_16487_amd import binding as sd
 from paper_2203_16487_amd import synth
 
@@ -48,3 +50,16 @@ def test_tail_against_oracle(d, B, k, V, opts):
     assert np.array_equal(st[..., 0], z.max(-1)) and np.array_equal(st[..., 1].astype(np.int64), z.argmax(-1))
     assert np.array_equal(bare["stats"], st)
     assert np.array_equal(bare["accept"], out["accept"]) and np.array_equal(bare["next"], out["next"])
+
+
+@pytest.mark.parametrize("d,B,k,V", [
+    (512, 65, 8, 32100),      # 520 rows, 378 tiles of 256 x 256: the second round in halves, the last of them cut away
+    (256, 65, 8, 32896),      # 387, a half tile of rows and columns at the end
+    (512, 26, 10, 32768),     # 260 rows, 256 tiles
+])
+def test_drafter_tail(d, B, k, V):
+    """A drafter's pass: every row's arg-max with the logits asked for and (another kernel) without, two sequences against the oracle."""
+    desc = synth.ModelDesc(1, 1, d, d // 64, 2 * d, V, 16, 64).resolved()
+    bits = synth.make_weights(desc, d + V, tag="drafter")
+    extra.drafter_pass_case(desc, bits, orc.Model(desc, synth.weights_f32(bits)), B=B, S_max=9, k=k, lens=synth.random_lengths(d, "len", B, 0, 12),
+                            seed=d + B, prefill=True, sample=(0, B - 1), max_tgt=40)
