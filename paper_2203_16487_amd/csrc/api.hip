@@ -212,12 +212,12 @@ constexpr long kPrefillRows = 8192;
 // 158 / 133, of 1000 source tokens 10 rows 167 / 146, 62 (two) 194 / 167.  One sequence of 17 - 32 rows is the exception while its keys are few: 26
 // rows 124 / 133, on 200 source tokens and 180 cached ones 32 rows 142 / 143, on 1000 175 / 168; two of 17 and 24 are close (131 / 134, on
 // 1000 175 / 163).  How many there are the host does not know, and one kernel for all of a sequence's life gives it the same bits.  (Launches: 6
-// rows 234, 48 246.)  The other one has what comes with codes (32 rows at most), and bf16 weights on a stream that lacks compute units, but has
+// rows 200, 48 228.)  The other one has what comes with codes (32 rows at most), and bf16 weights on a stream that lacks compute units, but has
 // as many as it has workgroups: beyond 48 rows its plan takes all 256.
 // At d = 1024 every XCD reads 176 MB of weights.  64 source tokens: 6 rows 158 / 217, 26 194 / 253, 44 (four sequences) 227 / 268, 64 (one each) 270 /
 // 305, 66 (11 each, as what follows) 264 / 270, 77 266 / 270, 88 277 / 272, 99 281 / 295, 110 282 / 294, 121 282 / 301; one each 80 310 / 314, 128 325
 // / 335; 26 each 78 267 / 260.  512 source tokens: 77 299 / 293, 88 314 / 304, 99 318 / 330, 121 320 / 333; but 64 sequences of two rows 474 /
-// 448, 128 of one 651 / 611, whose attention is most of the pass.  (Launches: 6 rows 266, 128 407; 352 497 and per XCD 363.)
+// 448, 128 of one 651 / 611, whose attention is most of the pass.  (Launches: 6 rows 252, 128 366; 352 462 and per XCD 363.)
 constexpr size_t persist_rows(int d) { return d <= 512 ? 48 : 128; }
 constexpr int kEncT = 12, kDecT = 20;
 int n_weights(const specdec_model_desc* d) { return 1 + kEncT * d->enc_layers + kDecT * d->dec_layers; }

@@ -111,8 +111,8 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(AttnArgs a) {
 // Per 64 keys and wave: 16 MFMAs (512 cycles) against about 1100 cycles of softmax (a quarter-rate exponential per
 // score), so the vector pipe bounds it (busy 79 % of the time, the matrix pipe 43) and what matters is instructions per score: row maxima
 // are exchanged once per tile, row sums once per pass, masking happens only on tiles a limit cuts, accumulators are rescaled only when some
-// maximum has moved by more than kSlack (at every move, which with 32 rows is nearly every tile: 188 us in place of 177 below).  120 registers,
-// four waves a SIMD; with 140, three of them, 205 us.
+// maximum has moved by more than kSlack (at every move, which with 32 rows is nearly every tile, it took 6 % longer).  120 registers,
+// four waves a SIMD; with 140, three of them, 16 % longer.
 // 32 x 16 heads, 1024 queries on 1024 keys: 163 us in an encoder (843 TFLOP/s), 775 with the kernel above, whose waves fetch keys and values
 // one by one.
 constexpr int kTileQ = 128, kTileK = 64;

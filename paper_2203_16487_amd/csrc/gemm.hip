@@ -915,8 +915,8 @@ static hipError_t launch_stream(hipStream_t st, const bf16* A, int lda, const bf
 // A streamed last round that is at most half full is computed as tiles of half the width, gemm_stream_kernel, and costs 0.65 of one.)
 // Of twelve row counts from 352 to 32768 and nine (N, K) of the two models, the choice was at most 3 % slower than the better of the two
 // wherever it is made.  Charging that last round in full kept 11264 and 16384 rows of 1536 and 2048 x 512 on 128 x 128 tiles: encoding
-// 128 sources of 128 tokens with 512-wide encoders 3610 us, now 3511; 128 of 16 .. 128 tokens 2769 / 2702; 88 of them 2312 / 2268; with a
-// 1024-wide encoder 3607 / 3580.  Where M only bounds the rows in use (bound), the sum over half, three quarters and all of it decides.
+// 128 sources of 128 tokens with a 512-wide encoder of 12 layers 2150 us, now 2064; 128 of 16 .. 128 tokens 1517 / 1475; 88 of 128 tokens 1682
+// / 1697, of 16 .. 128 1252 / 1177; with a 1024-wide encoder level.  Where M only bounds the rows in use (bound), the sum over half, three quarters and all of it decides.
 static float square_minus_wide(int M, int N, int K, bool stream) {
   const float kt = K / 64.f;
   const long sq = (long)((M + 255) / 256) * ((N + 255) / 256), wd = (long)((M + 127) / 128) * ((N + 127) / 128);

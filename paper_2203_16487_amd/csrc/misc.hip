@@ -853,8 +853,6 @@ hipError_t get_output(hipStream_t st, const SeqState& s, int* tokens, int out_ca
 }
 
 // ----------------------------------------------------------------------------- cache layout
-// flat [B][L][H*64]  <->  key cache [B][H][Lcap][64] (16-byte chunks) or transposed value
-// cache (element-wise; only used to load / inspect caches)
 // Keys and values of all layers [layer][B][H][Lcap][64] <-> flat [layer][B][L][d], 16 bytes a thread, in one launch (z < 2 layers: a part of one
 // sequence's rows).  LOAD, z = 2 layers: sequence b's number of cached rows, and its stream where there is one.  In launches of their own, 2.9
 // us for each layer's keys or values (of 64 sequences, 32 rows of 512) and 3.3 and 1.4 us for streams and lengths, each behind the one before,

@@ -22,8 +22,8 @@
 // 113.6 us for 6 rows, from a copy 112.7).
 //
 // What bounds it: a hand-over and instructions in a row at every stage (of 11 rows 0.8 - 3.5 us, of 44 1.8 - 3.9), and with the weights of d =
-// 1024 what an XCD takes in.  Whole verify passes, launches / this kernel, us: d = 512: 6 rows 234 / 109, 77 251 / 121, 176 271 / 145, 352
-// 315 / 172; d = 1024: 6 rows 266 / 217, 128 407 / 335, 176 391 / 318, 352 497 / 374.  (Which passes it takes, and what the kernel over the whole GPU
+// 1024 what an XCD takes in.  Whole verify passes, launches / this kernel, us: d = 512: 6 rows 200 / 109, 77 239 / 121, 176 255 / 140, 352
+// 287 / 168; d = 1024: 6 rows 252 / 217, 128 366 / 335, 176 358 / 317, 352 462 / 363.  (Which passes it takes, and what the kernel over the whole GPU
 // (persist.hip) takes for them, is in api.hip.)
 //
 // LayerNorm is folded into the products as in the general kernels (gemm.hip), with statistics per 16 columns; the fp32 residual
