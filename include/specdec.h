@@ -93,7 +93,8 @@ typedef enum {
                                           infinities) with one fp32 scale per output row, s_n = max_k |w_nk| / 448,
                                           code = nearest-even E4M3 of w_nk / s_n, written by a kernel at bind time.
                                           Passes of at most 32 rows (where weight bytes bound the verification pass
-                                          of Sec. 2) then stream the codes -- half the bytes -- turn them into bf16
+                                          of Sec. 2), with at most 256 source rows and a context made for at most 256
+                                          cached ones (max_tgt + k_max + 1), then stream the codes -- half the bytes -- turn them into bf16
                                           operands in registers and apply s_n to the fp32 sum:
                                           y_n = s_n * sum_k q_nk h_k + b_n.  This changes the model: its results are
                                           those of the model whose matrices are s_n * q_nk, not of the bf16 one.
