@@ -71,8 +71,8 @@ enum { SPECDEC_COUNTERS = 8 };  /* int32 words reported by specdec_get_counters 
 /* Kernel-path switches of a context (specdec_configure), value 0 or 1. */
 typedef enum {
   SPECDEC_OPT_SMALL_BATCH_KERNELS = 0, /* default 1: passes of few rows run their decoder layers as one kernel where that applies
-                                          (specdec_verify); else, of at most 32 rows, one sequence of at most 12 rows with
-                                          d_model <= 512 (and every such pass with LN_FOLD = 0) on the fused small-batch
+                                          (specdec_verify, specdec_draft); else, verification passes
+                                          of at most 32 rows, one sequence of at most 12 rows with d_model <= 512 (and every such pass with LN_FOLD = 0) on the fused small-batch
                                           kernels, others on the general ones; at most 32 rows: the small-batch
                                           vocabulary kernel.  0: none of these                                       */
   SPECDEC_OPT_LN_FOLD = 1,             /* default 1: LayerNorms folded into the projections around them; 0: a pass of their own
@@ -202,6 +202,10 @@ int specdec_prefill(specdec_ctx* ctx, specdec_role role, void* stream);
  * non-autoregressive decoder pass, argmax per slot -> draft device int32 [B, k].  Stream
  * tokens the drafter has not cached yet are processed (causally) in the same pass and
  * cached; mask slots attend to the whole stream and to all k slots.
+ * With d_model 512 / d_ffn 2048 a pass whose places (k and the most stream tokens a sequence can
+ * bring: all that commits since the drafter's latest pass may have appended, one behind a loaded
+ * cache) are few runs its decoder layers as one kernel, each XCD on sequences of its own, under the
+ * rules of specdec_verify; should its second run not complete either, every draft is pad_id.
  * logits_or_null: optional device fp32 [B, k, V] receiving the slots' logits (parity mode; slow). */
 int specdec_draft(specdec_ctx* ctx, int32_t k, int32_t* draft, float* logits_or_null, void* stream);
 

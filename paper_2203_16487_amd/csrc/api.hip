@@ -332,11 +332,11 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   if (sd::persist_supported(d->dec_layers, (int)D, (int)F)) {
     const size_t most = Bm * (c->lim.k_max + 1);
     t.pl_rows = (int)(most < persist_rows((int)D) ? most : persist_rows((int)D));
-    // The per-XCD decoder's share only where a pass within the limits can be its (one_kernel_way).  (In a drafter's workspace too, which
-    // uses neither: the size is asked for without a role.)
+    // The per-XCD decoder's share only where a pass within the limits can be its (one_kernel_way).  (The size is asked for without a role: a
+    // drafter's workspace has the place for the copy of the weights, which it does not use, and a verifier's buffers that a drafter's rows need.)
     const bool per_xcd = sd::xcd_rows_most((int)Bm, c->lim.k_max + 1) > (D == 512 ? sd::kXcdFewRows : (int)persist_rows((int)D));
     const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F);
-    const size_t xcd = per_xcd || D == 512 ? sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F) : 0;
+    const size_t xcd = D == 512 ? sd::xcd_exch_most((int)Bm, c->Tmax, (int)D, (int)F) : per_xcd ? sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F) : 0;
     t.pl_exch = cv.take<char>(one > xcd ? one : xcd);
     if (per_xcd) t.xcd_stream = cv.take<char>(sd::xcd_stream_bytes(d->dec_layers, (int)D, (int)F));   // (few rows of 512: without it)
     if (per_xcd || D == 512) t.xcd_vecs = cv.take<float>(sd::xcd_vec_bytes(d->dec_layers, (int)D) / sizeof(float));
@@ -621,29 +621,33 @@ int stream_cus(hipStream_t st) {
   return n;
 }
 
-// cus: compute units the pass's stream has.  few: the E4M3 copies of the weights, if the model has them.
-Way one_kernel_way(const Model& m, int B, int T, bool few, int cus) {
+// cus: compute units the pass's stream has.  few: the E4M3 copies of the weights, if the model has them.  A drafter's pass (T: the most rows of
+// a sequence) is per XCD, with the matrices as bound, or launches.
+Way one_kernel_way(const Model& m, int B, int T, bool few, bool drafter, int cus) {
   sd::PlArgs p{};
   p.R = B * T; p.T = T; p.B = B; p.H = m.d.n_heads;
   sd::XcdArgs x{};
   x.R = B * T; x.T = T; x.B = B; x.H = m.d.n_heads;
-  const int D = m.d.d_model, F = m.d.d_ffn, R = B * T, blocks = R <= m.pl_rows ? sd::persist_plan(p, D, F) : 0;
+  const int D = m.d.d_model, F = m.d.d_ffn, R = B * T;
+  if (drafter) return D == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && R <= sd::kXcdMostRows && sd::xcd_plan(x, D, F) > 0 ? Way::xcd_few : Way::launches;
+  const int blocks = R <= m.pl_rows ? sd::persist_plan(p, D, F) : 0;
   const bool xcd = cus >= sd::kPlBlocks && !(m.fp8 && few) && R <= sd::kXcdMostRows && sd::xcd_plan(x, D, F) > 0;
   if (xcd && D == 512 && m.xcd_vecs && R <= sd::kXcdFewRows) return Way::xcd_few;
   if (blocks > 0 && cus >= blocks) return Way::gpu;
   return xcd && m.xcd_stream ? Way::xcd : Way::launches;
 }
 
-// Whether the pass takes one of them (c->way: which).
-bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, bool few, hipStream_t st) {
-  if (!m.pl_exch || T > 32 || c->no_skinny || c->no_ln_fold || c->sliced) return false;
-  if (one_kernel_way(m, B, T, few, sd::kPlBlocks) == Way::launches) return false;   // (whatever the GPU and the stream have)
+// Whether the pass takes one of them (way: which).
+bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, bool few, bool drafter, hipStream_t st, Way* way) {
+  *way = Way::launches;
+  if (!m.pl_exch || c->no_skinny || c->no_ln_fold || c->sliced) return false;
+  if (one_kernel_way(m, B, T, few, drafter, sd::kPlBlocks) == Way::launches) return false;   // (whatever the GPU and the stream have)
   int dev = -1, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return false;
-  c->way = one_kernel_way(m, B, T, few, std::min(cus, stream_cus(st)));   // (all of a way's workgroups run at once)
-  if (c->way == Way::launches) return false;
+  const Way found = one_kernel_way(m, B, T, few, drafter, std::min(cus, stream_cus(st)));   // (all of a way's workgroups run at once)
+  if (found == Way::launches) return false;
   if (c->persist_refused || (c->persist_dev >= 0 && c->persist_dev != dev)) return false;
   bool capturing = false;
   if (st && st != hipStreamLegacy) {   // (which cannot be captured)
@@ -664,33 +668,35 @@ bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, bool few, hipStrea
   }
   o.stream = st;
   o.captured |= capturing;
+  *way = found;
   return true;
 }
 
 // The flags of the decoder that runs it: each counts its own passes.
-unsigned* persist_flags(const specdec_ctx* c, const Model& m) {
-  return reinterpret_cast<unsigned*>(m.pl_err) + (c->way == Way::gpu ? 0 : sd::kPlFlags + (c->way == Way::xcd ? 0 : sd::kXcdFlags));
+unsigned* persist_flags(Way way, const Model& m) {
+  return reinterpret_cast<unsigned*>(m.pl_err) + (way == Way::gpu ? 0 : sd::kPlFlags + (way == Way::xcd ? 0 : sd::kXcdFlags));
 }
 
 // Bytes of the exchange buffers that the pass's first kernel fills with 0xff.
-size_t persist_clear(const specdec_ctx* c, const Model& m, int B, int T) {
-  if (c->way == Way::gpu) return sd::persist_exch_bytes(B * T, m.d.dec_layers, m.d.d_model, m.d.d_ffn);
+size_t persist_clear(Way way, const Model& m, int B, int T) {
+  if (way == Way::gpu) return sd::persist_exch_bytes(B * T, m.d.dec_layers, m.d.d_model, m.d.d_ffn);
   sd::XcdArgs a{};
   a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads;
   return sd::xcd_plan(a, m.d.d_model, m.d.d_ffn);
 }
 
 // few: as in decoder_layers (the E4M3 copies of the weights, if the model has them)
-int decoder_layers_persist(specdec_ctx* c, Model& m, int B, int T, bool few, hipStream_t st) {
-  if (c->way != Way::gpu) {
+int decoder_layers_persist(specdec_ctx* c, Model& m, Way way, int B, int T, bool few, bool drafter, hipStream_t st) {
+  if (way != Way::gpu) {
     sd::XcdArgs a{};
     a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads; a.Lcap = c->Lcap; a.Scap = c->Scap; a.n_layers = m.d.dec_layers;
-    a.layers = m.pl_layers; a.stream = c->way == Way::xcd ? m.xcd_stream : nullptr; a.vecs = m.xcd_vecs;
+    a.layers = m.pl_layers; a.stream = way == Way::xcd ? m.xcd_stream : nullptr; a.vecs = m.xcd_vecs;
     a.row_b = m.rm.row_b; a.row_pos = m.rm.row_pos; a.src_len = c->st.src_len;
+    if (drafter) { a.causal = m.new_rows; a.live = m.rm.seq_rows; }
     a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + (size_t)sd::kXcdMostRows * m.d.d_model;
     a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
     if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
-    a.exch = m.pl_exch; a.err = persist_flags(c, m);
+    a.exch = m.pl_exch; a.err = persist_flags(way, m);
     LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::xcd_decoder(st, a, m.d.d_model, m.d.d_ffn, c->give_up));
     return SPECDEC_OK;
   }
@@ -702,7 +708,7 @@ int decoder_layers_persist(specdec_ctx* c, Model& m, int B, int T, bool few, hip
   a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + persist_rows(m.d.d_model) * m.d.d_model;
   a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
   if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
-  a.exch = m.pl_exch; a.err = persist_flags(c, m);
+  a.exch = m.pl_exch; a.err = persist_flags(way, m);
   LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::persist_decoder(st, a, m.d.d_model, m.d.d_ffn, c->give_up));
   return SPECDEC_OK;
 }
@@ -954,7 +960,9 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
                                  f.cq.bf, f.w1.cs, f.w1.bf, f.vo, f.vco, f.v2});
       }
     HIPCHK(c, hipMemcpy(m.pl_layers, pl.data(), pl.size() * sizeof(sd::PlLayer), hipMemcpyHostToDevice));
-    if (m.xcd_vecs && role == SPECDEC_VERIFIER) HIPCHK(c, sd::xcd_pack(S(stream), m.pl_layers, d->dec_layers, d->d_model, m.xcd_stream, m.xcd_vecs));
+    if (role == SPECDEC_DRAFTER) m.xcd_stream = nullptr;   // (reads its matrices as bound)
+    if (m.xcd_vecs && (role == SPECDEC_VERIFIER || d->d_model == 512))
+      HIPCHK(c, sd::xcd_pack(S(stream), m.pl_layers, d->dec_layers, d->d_model, m.xcd_stream, m.xcd_vecs));
   }
   m.bound = true;
   return SPECDEC_OK;
@@ -968,8 +976,9 @@ int specdec_begin(specdec_ctx* c, int32_t B, int32_t max_new, void* stream) {
   if (B > c->lim.max_batch) return fail(c, SPECDEC_ERR_TOO_LARGE, "B = %d exceeds max_batch = %d", B, c->lim.max_batch);
   const Model& any = c->m[0].bound ? c->m[0] : c->m[1];
   if (max_new > c->lim.max_tgt) max_new = c->lim.max_tgt;   // no stream grows beyond the arena
-  HIPCHK(c, sd::begin_state(S(stream), c->st, B, max_new, c->lim.max_tgt, any.d.bos_id));
-  if (c->m[0].bound) HIPCHK(c, sd::fill_i32(S(stream), c->m[0].pl_err, 0, sd::kPlFlags + 2 * sd::kXcdFlags));   // a new run clears the one-kernel decoder's flags
+  // (a new run clears the one-kernel decoders' flags)
+  HIPCHK(c, sd::begin_state(S(stream), c->st, B, max_new, c->lim.max_tgt, any.d.bos_id, c->m[0].bound ? c->m[0].pl_err : nullptr,
+                            c->m[1].bound ? c->m[1].pl_err : nullptr, sd::kPlFlags + 2 * sd::kXcdFlags));
   c->B = B;
   c->max_new = max_new;
   c->last_T = 0;
@@ -1176,15 +1185,21 @@ int specdec_draft(specdec_ctx* c, int32_t k, int32_t* draft, float* logits, void
   const int B = c->B, T = ub + k;
   // rows packed sequence after sequence: a sequence brings 1 .. k_max + 1 new stream rows, the
   // grids are sized for the most (the GEMMs with LayerNorm folded in know how to stop early)
-  const bool packed = !c->no_ln_fold;
+  // The per-XCD decoder takes T places a sequence, those beyond its rows among them.
+  Way way;
+  const bool one = persist_ok(c, m, B, T, false, true, st, &way), packed = !one && !c->no_ln_fold;
   LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_stream(st, c->st, m.rm, SPECDEC_DRAFTER, B, T, k, m.d.mask_id, m.d.pad_id,
-                                      m.d.vocab, m.new_rows, m.embed, m.pe, m.x, m.xb, m.d.d_model, packed));
-  rc = decoder_layers(c, m, B, T, st, true, k, packed);
+                                      m.d.vocab, m.new_rows, m.embed, m.pe, m.x, m.xb, m.d.d_model, packed, one ? m.pl_exch : nullptr,
+                                      one ? persist_clear(way, m, B, T) : 0));
+  const unsigned* failed = one ? persist_flags(way, m) + 1 : nullptr;
+  rc = one ? decoder_layers_persist(c, m, way, B, T, false, true, st) : decoder_layers(c, m, B, T, st, true, k, packed);
   if (rc) return rc;
+  if (one)
+    LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm_slots(st, m.skp, m.dec.back().ln3g, m.dec.back().ln3b, m.slots, m.new_rows, nullptr, B, T, k, m.d.d_model));
   const int R = B * k, tc = sd::vocab_tile_cols(R), n_tiles = (m.d.vocab + tc - 1) / tc;
   LAUNCH(c, SPECDEC_KIND_VOCAB, st, sd::vocab_stats(st, m.slots, m.embed, R, m.d.vocab, m.d.d_model, nullptr, nullptr, m.part, logits, c->wide_vocab));
   LAUNCH(c, SPECDEC_KIND_ACCEPT, st, sd::merge_drafts(st, m.part, n_tiles, m.row_stats, c->st, B, k, m.d.pad_id, m.new_rows,
-                                      m.rm.seq_rows, draft));
+                                      m.rm.seq_rows, draft, failed));
   c->uncached_ub[1] = 0;
   c->trusted[1] = false;
   c->last_k_draft = k;
@@ -1227,8 +1242,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   // The fused small-batch decoder kernels, whose every block redoes what precedes its product and which embed the rows
   // themselves, where that is little: one sequence of few rows, d = 512 (3 rows 184 against 205 us, 11: 210 / 214, 16: 220 /
   // 218; two sequences of 6 235 / 214; d = 1024: 6 rows 285 / 268, 26 521 / 302).  Otherwise the general ones.
-  const bool one = persist_ok(c, m, B, T, small, st);
-  if (!one) c->way = Way::launches;
+  const bool one = persist_ok(c, m, B, T, small, false, st, &c->way);
   const bool fused = small && !one && (c->no_ln_fold || c->sliced || (B == 1 && R <= 12 && m.d.d_model <= 512));
   VerifyScratch vs{m.part, m.zd, m.row_stats};
   if (ext) {
@@ -1247,8 +1261,8 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   else
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_verify(st, c->st, m.rm, draft, B, k, m.d.vocab, m.embed, m.pe, m.x, m.xb,
                                         m.d.d_model, one ? m.pl_exch : nullptr,
-                                        one ? persist_clear(c, m, B, T) : 0));
-  const unsigned* failed = one ? persist_flags(c, m) + 1 : nullptr;
+                                        one ? persist_clear(c->way, m, B, T) : 0));
+  const unsigned* failed = one ? persist_flags(c->way, m) + 1 : nullptr;
   float* sums = one ? m.skp : m.x;   // the last residual sums (the one-kernel decoder keeps its input rows)
   int n_tiles = (m.d.vocab + 63) / 64;   // per-row partial records of the vocabulary kernel that ran
   if (small && (m.fp8 || m.kv8) && (c->resident || c->sliced))
@@ -1256,7 +1270,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   if (small) {
     sd::SkSrc fin{};
     if (!fused) {
-      rc = one ? decoder_layers_persist(c, m, B, T, true, st) : decoder_layers(c, m, B, T, st, true, 0, false, false, true);
+      rc = one ? decoder_layers_persist(c, m, c->way, B, T, true, false, st) : decoder_layers(c, m, B, T, st, true, 0, false, false, true);
       fin = sd::SkSrc{2, sums, m.dec.back().ln3g, m.dec.back().ln3b, nullptr, nullptr, nullptr, nullptr};
     } else if (c->sliced && sd::sk2_supported(m.d.d_model, m.d.d_ffn) && m.d.n_heads <= sd::kSk2MaxParts)
       rc = decoder_layers_sliced(c, m, B, T, st, &fin);
@@ -1267,7 +1281,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     c->fin_x = c->resident ? nullptr : fin.xs; c->fin_g = fin.g; c->fin_b = fin.b;
   } else {
     if (one) {
-      rc = decoder_layers_persist(c, m, B, T, false, st);
+      rc = decoder_layers_persist(c, m, c->way, B, T, false, false, st);
       if (rc) return rc;
     } else {
       rc = decoder_layers(c, m, B, T, st, true, 0, false, false, false, true);
@@ -1365,8 +1379,9 @@ int specdec_commit(specdec_ctx* c, const int32_t* accept_len, const int32_t* nex
   if (!accept_len || !next_token) return fail(c, SPECDEC_ERR_INVALID_ARG, "null accept_len/next_token");
   if (c->last_T <= 0) return fail(c, SPECDEC_ERR_BAD_STATE, "specdec_commit without a preceding specdec_verify");
   HIPCHK(c, sd::commit_rows(S(stream), c->st, accept_len, next_token, c->B, c->last_T - 1, c->m[0].d.eos_id, n_active));
+  const int appended = c->last_T;   // (at most)
   c->last_T = 0;
-  c->uncached_ub[1] += c->lim.k_max + 1;
+  c->uncached_ub[1] += appended;
   return SPECDEC_OK;
 }
 

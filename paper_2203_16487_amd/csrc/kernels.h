@@ -270,9 +270,11 @@ hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F, bool give_up)
 struct XcdArgs {
   int R, T, B, H, Lcap, Scap, n_layers;   // as PlArgs
   const PlLayer* layers;                  // device array [n_layers]
-  const char* stream;                     // weights and column vectors as xcd_pack lays them out; null (d = 512, kXcdFewRows): the weights as bound
+  const char* stream;                     // weights and column vectors as xcd_pack lays them out; null (d = 512; kXcdFewRows, a drafter's): the weights as bound
   const float* vecs;
   const int *row_b, *row_pos, *src_len;
+  const int *causal, *live;               // [B] a drafter's pass: of the T rows of a sequence, the first that see the keys up to their own, and all
+                                          // that there are (those between see all keys); null: T of either
   const float* x;
   const bf16* xb;
   float* y;
@@ -289,7 +291,7 @@ struct XcdArgs {
   PlTickets* tickets;
 };
 constexpr int kXcdMostRows = 512;         // rows of a pass at most: 64 on each of 8 XCDs
-constexpr int kXcdFewRows = 63;           // of a pass that reads the weights as bound (no copy of them), 32 on an XCD
+constexpr int kXcdFewRows = 63;           // of a verification pass that reads the weights as bound (no copy of them), 32 on an XCD
 // Weights (bf16) of a model's layers (device array) in the order they are used, and their column vectors.
 size_t xcd_stream_bytes(int layers, int d, int F);
 size_t xcd_vec_bytes(int layers, int d);
@@ -352,10 +354,10 @@ hipError_t assemble_embed_verify(hipStream_t st, const SeqState& s, const RowMap
                                  size_t clear_bytes = 0);
 // rows of a prefill pass (n_mask = 0) or of a drafter pass (stream rows + n_mask [MASK] slots),
 // embedded in the same launch; new_rows[b] = stream rows of sequence b in this pass;
-// packed: rows of the sequences follow each other without padding (RowMap::row_start is written)
+// packed: rows of the sequences follow each other without padding (RowMap::row_start is written); clear: as above
 hipError_t assemble_embed_stream(hipStream_t st, const SeqState& s, const RowMap& rm, int role, int B, int T,
                                  int n_mask, int mask_id, int pad_id, int V, int* new_rows, const bf16* E,
-                                 const float* pe, float* x, bf16* xb, int d, bool packed);
+                                 const float* pe, float* x, bf16* xb, int d, bool packed, void* clear = nullptr, size_t clear_bytes = 0);
 hipError_t advance_cached(hipStream_t st, const SeqState& s, int role, const int* new_rows, int B);
 hipError_t gather_slots(hipStream_t st, const bf16* xb, bf16* dst, const int* new_rows, const int* row_start, int B,
                         int T, int k, int d);
@@ -377,9 +379,10 @@ hipError_t merge_accept(hipStream_t st, const float* part, const float* zd_row, 
                         int* next_token, const unsigned* fail = nullptr);
 // the same merge for the B*k mask-slot rows of a drafter pass, draft[b][s] = their arg-max (pad
 // for finished sequences), and cached[drafter][b] += new_rows[b]
-// (seq_rows: rows of each sequence in the pass; a sequence without its k slots gets pad drafts)
+// (seq_rows: rows of each sequence in the pass; a sequence without its k slots gets pad drafts; so do all, and nothing counts as cached,
+// where the optional device flag `fail` is set)
 hipError_t merge_drafts(hipStream_t st, const float* part, int n_tiles, float* row_stats, const SeqState& s, int B,
-                        int k, int pad_id, const int* new_rows, const int* seq_rows, int* draft);
+                        int k, int pad_id, const int* new_rows, const int* seq_rows, int* draft, const unsigned* fail = nullptr);
 // k: block size of the pass whose drafts are being committed (accept_len is clamped to it)
 // head-based drafting: input rows of the heads (see misc.hip), fp32 -> bf16 rows, arg-max per head row
 hipError_t head_rows(hipStream_t st, const float* x, const bf16* g, const bf16* beta, const int* accept_len, int B, int T,
@@ -389,8 +392,9 @@ hipError_t merge_head_drafts(hipStream_t st, const float* part, int n_tiles, flo
                              const int* accept_len, int B, int k, int pad_id, int* draft);
 hipError_t commit_rows(hipStream_t st, const SeqState& s, const int* accept_len,
                        const int* next_token, int B, int k, int eos_id, int* n_active);
+// (flags: n_flags words each, cleared in the same launch; null: none)
 hipError_t begin_state(hipStream_t st, const SeqState& s, int B, int max_new, int max_tgt,
-                       int bos_id);
+                       int bos_id, int* flags0, int* flags1, int n_flags);
 hipError_t set_stream(hipStream_t st, const SeqState& s, const int* tokens, const int* len, int B,
                       int L_max, int max_new, int max_tgt);
 hipError_t rewind_state(hipStream_t st, const SeqState& s, const int* len, int B);

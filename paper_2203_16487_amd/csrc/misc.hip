@@ -281,9 +281,14 @@ __global__ __launch_bounds__(128) void assemble_embed_stream_kernel(SeqState s, 
                                                                     const bf16* __restrict__ E,
                                                                     const float* __restrict__ pe,
                                                                     float* __restrict__ x, bf16* __restrict__ xb, int d,
-                                                                    float scale) {
+                                                                    float scale, uint4* __restrict__ clear, long n16) {
   __shared__ int wsum[2];
   __shared__ float red[2];
+  if ((int)blockIdx.x >= B * T) {   // the blocks beyond the rows clear
+    for (long i = (long)((int)blockIdx.x - B * T) * 128 + threadIdx.x; i < n16; i += (long)((int)gridDim.x - B * T) * 128)
+      clear[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    return;
+  }
   const int b = blockIdx.x / T, i = blockIdx.x - b * T;
   const StreamRows me = stream_rows(s, role, b, T, n_mask);
   int first = b * T;
@@ -319,14 +324,16 @@ __global__ __launch_bounds__(128) void assemble_embed_stream_kernel(SeqState s, 
 }
 hipError_t assemble_embed_stream(hipStream_t st, const SeqState& s, const RowMap& rm, int role, int B, int T,
                                  int n_mask, int mask_id, int pad_id, int V, int* new_rows, const bf16* E,
-                                 const float* pe, float* x, bf16* xb, int d, bool packed) {
+                                 const float* pe, float* x, bf16* xb, int d, bool packed, void* clear, size_t clear_bytes) {
   if (B <= 0 || T <= 0) return hipSuccess;
+  const long n16 = (long)(clear_bytes / 16), more = (n16 + 511) / 512;   // four pieces per thread
+  const dim3 grid((unsigned)(B * T + (more < 1024 ? more : 1024)));
   if (packed)
-    hipLaunchKernelGGL(assemble_embed_stream_kernel<true>, dim3(B * T), dim3(128), 0, st, s, rm, role, B, T, n_mask,
-                       mask_id, pad_id, V, new_rows, E, pe, x, xb, d, sqrtf((float)d));
+    hipLaunchKernelGGL(assemble_embed_stream_kernel<true>, grid, dim3(128), 0, st, s, rm, role, B, T, n_mask,
+                       mask_id, pad_id, V, new_rows, E, pe, x, xb, d, sqrtf((float)d), static_cast<uint4*>(clear), n16);
   else
-    hipLaunchKernelGGL(assemble_embed_stream_kernel<false>, dim3(B * T), dim3(128), 0, st, s, rm, role, B, T, n_mask,
-                       mask_id, pad_id, V, new_rows, E, pe, x, xb, d, sqrtf((float)d));
+    hipLaunchKernelGGL(assemble_embed_stream_kernel<false>, grid, dim3(128), 0, st, s, rm, role, B, T, n_mask,
+                       mask_id, pad_id, V, new_rows, E, pe, x, xb, d, sqrtf((float)d), static_cast<uint4*>(clear), n16);
   return hipGetLastError();
 }
 
@@ -570,24 +577,25 @@ __global__ __launch_bounds__(64) void merge_drafts_kernel(const float* __restric
                                                           float* __restrict__ row_stats, SeqState s, int B, int k,
                                                           int pad_id, const int* __restrict__ new_rows,
                                                           const int* __restrict__ seq_rows,
-                                                          int* __restrict__ draft) {
+                                                          int* __restrict__ draft, const unsigned* __restrict__ fail) {
   const int o = blockIdx.x, lane = threadIdx.x;
   // a sequence whose uncached stream did not fit into this pass got no mask slots (its rows of
   // the pass were all stream rows): what sits at its slot rows belongs to another sequence
   const int b = o / k, slots = seq_rows[b] - new_rows[b], finished = s.finished[b], cached = o < B ? s.cached[1][o] + new_rows[o] : 0;
+  const bool failed = fail && *fail != 0u;
   RowRecords held;   // (all requests of memory at once, as above)
   held.request(part + (size_t)o * n_tiles * kPartF, n_tiles, lane);
   const RowMerge res = merge_row(held, part + (size_t)o * n_tiles * kPartF, n_tiles, lane);
   if (lane != 0) return;
   store_row_stats(row_stats + (size_t)o * kRowStats, res, kNegInf);
-  draft[o] = finished || slots != k ? pad_id : res.arg;
-  if (o < B) s.cached[1][o] = cached;
+  draft[o] = finished || slots != k || failed ? pad_id : res.arg;
+  if (o < B && !failed) s.cached[1][o] = cached;
 }
 hipError_t merge_drafts(hipStream_t st, const float* part, int n_tiles, float* row_stats, const SeqState& s, int B,
-                        int k, int pad_id, const int* new_rows, const int* seq_rows, int* draft) {
+                        int k, int pad_id, const int* new_rows, const int* seq_rows, int* draft, const unsigned* fail) {
   if (B <= 0 || k <= 0) return hipSuccess;
   hipLaunchKernelGGL(merge_drafts_kernel, dim3(B * k), dim3(64), 0, st, part, n_tiles, row_stats, s, B, k, pad_id,
-                     new_rows, seq_rows, draft);
+                     new_rows, seq_rows, draft, fail);
   return hipGetLastError();
 }
 
@@ -761,8 +769,10 @@ hipError_t commit_rows(hipStream_t st, const SeqState& s, const int* accept_len,
 }
 
 // ----------------------------------------------------------------------------- state
-__global__ void begin_kernel(SeqState s, int B, int max_new, int max_tgt, int bos_id) {
+__global__ void begin_kernel(SeqState s, int B, int max_new, int max_tgt, int bos_id, int* flags0, int* flags1, int n_flags) {
   int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b < n_flags && flags0) flags0[b] = 0;
+  if (b < n_flags && flags1) flags1[b] = 0;
   if (b < 8) s.scratch[b] = 0;   // counters: commits, tokens appended, finished, near-threshold rows
   if (b >= B) return;
   s.tokens[(size_t)b * s.tok_pitch] = bos_id;
@@ -773,8 +783,9 @@ __global__ void begin_kernel(SeqState s, int B, int max_new, int max_tgt, int bo
   s.cached[0][b] = 0;
   s.cached[1][b] = 0;
 }
-hipError_t begin_state(hipStream_t st, const SeqState& s, int B, int max_new, int max_tgt, int bos_id) {
-  hipLaunchKernelGGL(begin_kernel, blocks_for(B, 128), dim3(128), 0, st, s, B, max_new, max_tgt, bos_id);
+hipError_t begin_state(hipStream_t st, const SeqState& s, int B, int max_new, int max_tgt, int bos_id, int* flags0, int* flags1, int n_flags) {
+  if (n_flags > 128) return hipErrorInvalidValue;   // (the first block's threads)
+  hipLaunchKernelGGL(begin_kernel, blocks_for(B, 128), dim3(128), 0, st, s, B, max_new, max_tgt, bos_id, flags0, flags1, n_flags);
   return hipGetLastError();
 }
 

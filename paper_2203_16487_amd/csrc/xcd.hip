@@ -21,6 +21,11 @@
 // A pass of at most 63 rows of d = 512 needs no such copy: it reads the matrices as bound, a chunk of 16 rows x 128 bytes at a time (DIRECT;
 // 113.6 us for 6 rows, from a copy 112.7).
 //
+// A drafter's pass (d = 512; stream rows and slots of as many places a sequence as it can need) is one of these, its matrices read in place whatever
+// its rows.  Passes behind a loaded cache, statistics read back, launches / this kernel, us: one sequence of 5 + 1 rows 96 / 58, 8 x 11 105 / 63, 32 x 11
+// 124 / 83, on 500 source tokens and 200 cached ones 133 / 100, 64 x 8 123 / 96.  An iteration of the loop with a base verifier, 1 x 11 215 /
+// 185, 24 x 11 (504 places for the drafter, some 340 in use) 291 / 261.
+//
 // What bounds it: a hand-over and instructions in a row at every stage (of 11 rows 0.8 - 3.5 us, of 44 1.8 - 3.9), and with the weights of d =
 // 1024 what an XCD takes in.  Whole verify passes, launches / this kernel, us: d = 512: 6 rows 200 / 109, 77 239 / 121, 176 255 / 140, 352
 // 287 / 168; d = 1024: 6 rows 252 / 217, 128 366 / 335, 176 358 / 317, 352 462 / 363.  (Which passes it takes, and what the kernel over the whole GPU
@@ -103,6 +108,9 @@ struct PlDim {
   static constexpr int kVecs = kVecS + 9 * kND, kVecReq = (kVecs / 4 + 63) / 64, kVecPitch = kVecReq * 256;   // requests of 64 x 16 bytes
 };
 
+// A sequence of the group: the position of its first row, rows that see the keys up to their own, rows of the pass (see pl_attn_wave), source.
+struct alignas(16) PlSeq { int j, causal, live, src_len; };
+
 template <int D, int MR>
 struct PlLds {
   typedef PlDim<D> Dim;
@@ -117,7 +125,8 @@ struct PlLds {
   float resid[Dim::kTD * 16 * MR * 16];           // of the workgroup's columns
   float stat[2][2 * 16 * MR];                     // {rstd, -mean rstd} of the rows, LayerNorms in turn
   float part[kPlWaves][2 * 16 * MR];              // {sum, squared deviations from its mean} of a row's columns, an eighth of them a wave
-  int row_at[kPlRows], row_pos[kPlRows], src_len[kPlRows];   // row_at: of the row in the self-attention cache of head 0 (< 0: none)
+  PlSeq seq[kPlRows];
+  int row_at[kPlRows];                            // of the row in the self-attention cache of head 0 (< 0: none)
   int drawn;                                      // (TICKETS)
   __device__ __forceinline__ bf16* vs(int wave) { return reinterpret_cast<bf16*>(red + wave * 256); }
 };
@@ -639,9 +648,11 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
 // Key chunks kw, kw + kstep, ... of 32 on this wave (see attn_core.h for the operand layouts).  SELF: keys / values below the
 // pass's first row come from the cache, the pass's own from the exchange buffers (waited for); else the cross-attention arenas.
 // KV8 (cross): codes with one fp32 scale per key and per value, as in attn_core.h.
-template <bool SELF, bool KV8>
-__device__ __forceinline__ void pl_attn_wave(const XcdArgs& a, const PlExch& ex, int l, int b0, const PlUnit& t, int kw, int kstep, bf16* Vs,
-                                             float& mrun, float& lrun, f32x4 (&oacc)[4]) {
+// SLOTS: of the a.T row places of a sequence the first `live` hold rows of the pass; the first `causal` of them see the keys up to their own,
+// the others (a drafter's slots) all keys.  Places beyond see none, and nobody reads what becomes of them.  (Else all see the keys up to their own.)
+template <bool SELF, bool KV8, bool SLOTS>
+__device__ __forceinline__ void pl_attn_wave(const XcdArgs& a, const PlExch& ex, int l, int b0, const PlUnit& t, int causal, int live, int kw, int kstep,
+                                             bf16* Vs, float& mrun, float& lrun, f32x4 (&oacc)[4]) {
   const int lane = pl_lane(), lq = lane & 15, g = lane >> 4;
   const int r0 = t.b * a.T;                                // first row of the sequence, in the group
   const int j = t.j, nkey = t.nkey;
@@ -748,7 +759,8 @@ __device__ __forceinline__ void pl_attn_wave(const XcdArgs& a, const PlExch& ex,
     }
   }
   const bf16x8 q0 = __builtin_bit_cast(bf16x8, f[0]), q1 = __builtin_bit_cast(bf16x8, f[1]);
-  const int lim = t.q0 + lq < a.T ? (SELF ? j + t.q0 + lq + 1 : nkey) : 0;
+  const int qrow = t.q0 + lq;
+  const int lim = SELF && SLOTS ? (qrow < causal ? j + qrow + 1 : qrow < live ? j + live : 0) : qrow < a.T ? (SELF ? j + qrow + 1 : nkey) : 0;
   for (int c0 = cfirst; c0 < nkey; c0 += kstep * 32) {
     const int c1 = c0 + kstep * 32;
     if (c1 < nkey && !(SELF && c1 + 32 > j)) fetch(c1, next);
@@ -847,7 +859,7 @@ __device__ __forceinline__ PlPair pl_pair(const XcdArgs& a, const PlPlace& p, in
   return PlPair{__builtin_amdgcn_readfirstlane(b), __builtin_amdgcn_readfirstlane(pair - b * a.H), __builtin_amdgcn_readfirstlane((u - pair * tiles) * 16)};
 }
 // mine: the unit of the first round (there is seldom another)
-template <bool SELF, bool KV8, int D, int MR>
+template <bool SELF, bool KV8, bool SLOTS, int D, int MR>
 __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex, int l, const PlPlace& at, const PlPair& mine, int units, int rounds, PlLds<D, MR>& L,
                                              PlTurn& turn) {
   const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
@@ -858,8 +870,10 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
     const PlPair pair = r == 0 ? mine : pl_pair(a, at, r, wave);
     PlUnit t;
     t.b = pair.b; t.h = pair.h; t.q0 = pair.q0;
-    t.j = SELF ? __builtin_amdgcn_readfirstlane(L.row_pos[t.b * a.T]) : 0;
-    t.nkey = SELF ? t.j + min(a.T, t.q0 + 16) : __builtin_amdgcn_readfirstlane(L.src_len[t.b]);
+    t.j = SELF ? __builtin_amdgcn_readfirstlane(L.seq[t.b].j) : 0;
+    const int causal = SELF && SLOTS ? __builtin_amdgcn_readfirstlane(L.seq[t.b].causal) : 0;
+    const int live = SELF && SLOTS ? __builtin_amdgcn_readfirstlane(L.seq[t.b].live) : 0;
+    t.nkey = !SELF ? __builtin_amdgcn_readfirstlane(L.seq[t.b].src_len) : t.j + (!SLOTS ? min(a.T, t.q0 + 16) : t.q0 + 16 <= causal ? t.q0 + 16 : live);
     const int chunks = (t.nkey + 31) >> 5, used = u < units ? min(max(chunks, 1), wpu) : 0;   // waves with keys (one at least)
     float mrun, lrun;
     f32x4 oacc[4];
@@ -871,7 +885,7 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
       if (t.q0 + lq < a.T) pl_store8(out + pl_at(a.RP, t.b * a.T + t.q0 + lq, t.h * kHeadDim + et * 16 + 4 * g), p[0], p[1]);
     };
     lds_barrier();   // the latest product's partial tiles, or the units' before, are done with
-    if (kw < used) pl_attn_wave<SELF, KV8>(a, ex, l, at.b0, t, kw, wpu, L.vs(wave), mrun, lrun, oacc);
+    if (kw < used) pl_attn_wave<SELF, KV8, SLOTS>(a, ex, l, at.b0, t, causal, live, kw, wpu, L.vs(wave), mrun, lrun, oacc);
     if (used == 1 && kw == 0) {   // nothing to merge
       const float inv = lrun > 0.f ? 1.f / lrun : 0.f;
 #pragma unroll
@@ -933,8 +947,10 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
 // KV8: cross-attention keys / values as E4M3 codes.
 // MR: row tiles of a group.
 // TICKETS: see the head of this file; the residual in memory instead of LDS.
-// DIRECT: the weights read in place (d = 512, a few rows).
-template <bool KV8, int D, int MR, bool TICKETS, bool DIRECT>
+// DIRECT: the weights read in place (d = 512: a few rows, a drafter's).
+// SLOTS: a drafter's rows (XcdArgs::causal); the second run asks for both kinds.  (As what every pass asks, verify passes of d = 512 took 0.5 - 1.6 %
+// longer.)
+template <bool KV8, int D, int MR, bool TICKETS, bool DIRECT, bool SLOTS>
 __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char pl_smem[];
   typedef PlLds<D, MR> Lds;
@@ -959,10 +975,12 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
   auto take_rows = [&] {
     for (int i = threadIdx.x; i < at.rows; i += kPlThreads) {
       const int b = a.row_b[at.row0 + i], pos = a.row_pos[at.row0 + i];
-      L.row_pos[i] = pos;
       L.row_at[i] = b < 0 ? -1 : b * a.H * a.Lcap + pos;
     }
-    for (int i = threadIdx.x; i < at.nb; i += kPlThreads) L.src_len[i] = a.src_len[at.b0 + i];
+    for (int i = threadIdx.x; i < at.nb; i += kPlThreads) {
+      const int b = at.b0 + i;
+      L.seq[i] = PlSeq{a.row_pos[b * a.T], SLOTS && a.causal ? a.causal[b] : a.T, SLOTS && a.causal ? a.live[b] : a.T, a.src_len[b]};
+    }
   };
   if (!TICKETS) take_rows();
   PlTurn turn = pl_turn<D>(a, at.w, wave, 0, 0, a.n_layers * Dim::kPerLayer);
@@ -986,8 +1004,8 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     const PlExch before(a.exch + (at.g * 2 + (~l & 1)) * pl_layer_bytes(a.RP, D, 4 * D), a.RP, D);
     const float* vec = L.vec[l & 1];
     float* stat = L.stat[(3 * l + s / 3) & 1];
-    if (s == 1) return pl_attention<true, false>(a, ex, l, at, mine, units, rounds, L, turn);
-    if (s == 4) return pl_attention<false, KV8>(a, ex, l, at, mine, units, rounds, L, turn);
+    if (s == 1) return pl_attention<true, false, SLOTS>(a, ex, l, at, mine, units, rounds, L, turn);
+    if (s == 4) return pl_attention<false, KV8, SLOTS>(a, ex, l, at, mine, units, rounds, L, turn);
     // the statistics of the LayerNorm pending on the residual
     const char* st = s <= 2 ? (l == 0 ? nullptr : before.st(2)) : s <= 5 ? ex.st(0) : ex.st(1);
     if (s == 0 || s == 3 || s == 6) {
@@ -1196,13 +1214,13 @@ static int pl_group_rows(int B, int T) { return ((B + kPlGroups - 1) / kPlGroups
 // Tickets, and exchange buffers of two layers for every group.
 static size_t pl_exch_bytes(int B, int RP, int d, int F) { return kPlTicketBytes + (size_t)(B < kPlGroups ? B : kPlGroups) * 2 * pl_layer_bytes(RP, d, F); }
 
-template <bool KV8, int D, int MR, bool TICKETS, bool DIRECT = false>
+template <bool KV8, int D, int MR, bool TICKETS, bool DIRECT = false, bool SLOTS = TICKETS>
 static hipError_t pl_launch(hipStream_t st, const XcdArgs& a, int blocks) {
   constexpr int kBytes = (int)sizeof(PlLds<D, MR>);
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pl_decoder_kernel<KV8, D, MR, TICKETS, DIRECT>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pl_decoder_kernel<KV8, D, MR, TICKETS, DIRECT, SLOTS>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
   if (attr != hipSuccess) return attr;
-  SD_LAUNCH_TIMED((pl_decoder_kernel<KV8, D, MR, TICKETS, DIRECT>), dim3(blocks), dim3(kPlThreads), kBytes, st, a);
+  SD_LAUNCH_TIMED((pl_decoder_kernel<KV8, D, MR, TICKETS, DIRECT, SLOTS>), dim3(blocks), dim3(kPlThreads), kBytes, st, a);
   return hipGetLastError();
 }
 // The pass, and its second run by tickets: workgroups for the members of one group, or of two where there are more (a fraction of the chip, so
@@ -1211,7 +1229,12 @@ template <bool KV8, int D>
 static hipError_t pl_launch_both(hipStream_t st, XcdArgs a, int blocks) {
   hipError_t e = hipErrorInvalidValue;
   if constexpr (D == 512) {
-    if (!a.stream) {   // (63 rows at most: 32 of a group)
+    if (a.causal) {
+      if (a.RP == 16) e = pl_launch<KV8, D, 1, false, true, true>(st, a, blocks);
+      if (a.RP == 32) e = pl_launch<KV8, D, 2, false, true, true>(st, a, blocks);
+      if (a.RP == 48) e = pl_launch<KV8, D, 3, false, true, true>(st, a, blocks);
+      if (a.RP == 64) e = pl_launch<KV8, D, 4, false, true, true>(st, a, blocks);
+    } else if (!a.stream) {   // (63 rows at most: 32 of a group)
       if (a.RP == 16) e = pl_launch<KV8, D, 1, false, true>(st, a, blocks);
       if (a.RP == 32) e = pl_launch<KV8, D, 2, false, true>(st, a, blocks);
     } else if (a.RP == 16) {   // (128 rows at most: with d = 1024 the decoder over the whole GPU takes them)
@@ -1232,7 +1255,7 @@ static hipError_t pl_launch_both(hipStream_t st, XcdArgs a, int blocks) {
 
 int xcd_rows_most(int max_batch, int max_T) {
   int most = 0;
-  for (int T = 1; T <= max_T && T <= 32; ++T) {
+  for (int T = 1; T <= max_T && T <= xcd::kPlRows; ++T) {
     const int B = std::min(max_batch, xcd::kPlGroups * (xcd::kPlRows / T));
     most = std::max(most, B * T);
   }
@@ -1254,7 +1277,7 @@ size_t xcd_plan(XcdArgs& a, int d, int F) {
   return xcd::pl_exch_bytes(a.B, a.RP, d, F);
 }
 hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F, bool give_up) {
-  if (a.R < 1 || a.T < 1 || a.T > 32 || a.R != a.B * a.T || !persist_supported(a.n_layers, d, F)) return hipErrorInvalidValue;
+  if (a.R < 1 || a.T < 1 || a.T > xcd::kPlRows || a.R != a.B * a.T || !persist_supported(a.n_layers, d, F)) return hipErrorInvalidValue;
   if (xcd_plan(a, d, F) == 0) return hipErrorInvalidValue;
   a.tickets = reinterpret_cast<PlTickets*>(a.exch);
   a.exch += kPlTicketBytes;
