@@ -239,9 +239,9 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * Finished sequences report accept_len 0 and next_token pad_id.
  * k = 0 (draft may be null) is one plain autoregressive step: accept_len = 0 and next_token is
  * the verifier's greedy token (the baseline of Sec. 2 on the same kernels).
- * Passes of few rows (d_model 512 / d_ffn 2048 or 1024 / 4096, 32 layers; at most 512 rows, and at most
- * 64 to each of eight groups that the sequences are dealt to evenly; of those beyond 128 rows, and at d_model 512 of
- * all that read bf16 weights, every XCD takes one group; where the stream has fewer than 256 compute units, one of at
+ * Passes of few rows (d_model 512 / d_ffn 2048 or 1024 / 4096, 32 layers; at most 64
+ * rows, d_model 512: 112, to each of eight groups that the sequences are dealt to evenly; of those beyond 128 rows, and at
+ * d_model 512 of all that read bf16 weights, every XCD takes one group; where the stream has fewer than 256 compute units, one of at
  * most 48 (1024: 128) rows may still run over those it has) run their decoder layers as one kernel of up to 256
  * workgroups that wait for each other; where a
  * kernel of another stream or process keeps some of them from starting for 0.1 s or more, the waits

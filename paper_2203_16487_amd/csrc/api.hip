@@ -83,6 +83,7 @@ struct Model {
   int* pl_err = nullptr;              // its flags (PlArgs::err), behind them the per-XCD one's (XcdArgs::err)
   char* pl_exch = nullptr;            // exchange buffers, its or the per-XCD one's (xcd.hip); null: dimensions they do not support
   int pl_rows = 0;                    // rows they are sized for, its
+  int xcd_rows = 0;                   // rows that skp holds twice for the other one
   char* xcd_stream = nullptr;         // the layers' weights as the per-XCD decoder streams them (null: no pass of more than a few rows of 512)
   float* xcd_vecs = nullptr;          // and their column vectors
   bf16* xb = nullptr;        // [Rpass][d]
@@ -294,8 +295,9 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   t.xv = cv.take<bf16>(t.xkv_layer * d->dec_layers);
   t.x = cv.take<float>(Rpass * D);
   t.x2 = cv.take<float>(32 * D);
-  t.skp = cv.take<float>((size_t)2 * sd::kSk2MaxParts * 32 * D);   // (or the one-kernel decoder's sum and its residual)
-  static_assert(2 * persist_rows(512) <= 2 * sd::kSk2MaxParts * 32 && 2 * sd::kXcdMostRows <= 2 * sd::kSk2MaxParts * 32, "both fit");
+  t.xcd_rows = D == 512 && sd::xcd_rows_most((int)Bm, c->Tmax, 512) > 512 ? 896 : 512;
+  t.skp = cv.take<float>((size_t)2 * t.xcd_rows * D);   // (or the one-kernel decoder's sum and its residual)
+  static_assert(2 * sd::kSk2MaxParts * 32 <= 2 * 512 && persist_rows(512) <= 512 && persist_rows(1024) <= 512, "both fit");
   t.hx = cv.take<float>(Bm * (size_t)c->lim.k_max * D);
   if (c->fp8_kv) {
     t.xk8 = cv.take<unsigned char>(t.xkv_layer * d->dec_layers);
@@ -334,7 +336,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     t.pl_rows = (int)(most < persist_rows((int)D) ? most : persist_rows((int)D));
     // The per-XCD decoder's share only where a pass within the limits can be its (one_kernel_way).  (The size is asked for without a role: a
     // drafter's workspace has the place for the copy of the weights, which it does not use, and a verifier's buffers that a drafter's rows need.)
-    const bool per_xcd = sd::xcd_rows_most((int)Bm, c->lim.k_max + 1) > (D == 512 ? sd::kXcdFewRows : (int)persist_rows((int)D));
+    const bool per_xcd = sd::xcd_copy_rows_most((int)Bm, c->lim.k_max + 1) > (D == 512 ? sd::kXcdFewRows : (int)persist_rows((int)D));
     const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F);
     const size_t xcd = D == 512 ? sd::xcd_exch_most((int)Bm, c->Tmax, (int)D, (int)F) : per_xcd ? sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F) : 0;
     t.pl_exch = cv.take<char>(one > xcd ? one : xcd);
@@ -363,7 +365,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     m->x = t.x; m->x2 = t.x2; m->skp = t.skp; m->hx = t.hx; m->w8 = t.w8; m->w8s = t.w8s; m->fold8 = t.fold8; m->xk8 = t.xk8; m->xv8 = t.xv8; m->xks = t.xks; m->xvs = t.xvs; m->xb = t.xb; m->q = t.q; m->att = t.att; m->hid = t.hid;
     m->part = t.part; m->row_stats = t.row_stats; m->zd = t.zd; m->rm = t.rm;
     m->slots = t.slots; m->new_rows = t.new_rows; m->pl_err = t.pl_err;
-    m->pl_layers = t.pl_layers; m->pl_exch = t.pl_exch; m->pl_rows = t.pl_rows;
+    m->pl_layers = t.pl_layers; m->pl_exch = t.pl_exch; m->pl_rows = t.pl_rows; m->xcd_rows = t.xcd_rows;
     m->xcd_stream = t.xcd_stream; m->xcd_vecs = t.xcd_vecs;
     m->ex = t.ex; m->exb = t.exb; m->eqkv = t.eqkv; m->eatt = t.eatt; m->ehid = t.ehid;
     m->elnp[0] = t.elnp[0]; m->elnp[1] = t.elnp[1]; m->efold = t.efold; m->epos = t.epos; m->erow_b = t.erow_b; m->erow_start = t.erow_start; m->en_rows = t.en_rows;
@@ -629,12 +631,12 @@ Way one_kernel_way(const Model& m, int B, int T, bool few, bool drafter, int cus
   sd::XcdArgs x{};
   x.R = B * T; x.T = T; x.B = B; x.H = m.d.n_heads;
   const int D = m.d.d_model, F = m.d.d_ffn, R = B * T;
-  if (drafter) return D == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && R <= sd::kXcdMostRows && sd::xcd_plan(x, D, F) > 0 ? Way::xcd_few : Way::launches;
+  if (drafter) return D == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && R <= m.xcd_rows && sd::xcd_plan(x, D, F) > 0 ? Way::xcd_few : Way::launches;
   const int blocks = R <= m.pl_rows ? sd::persist_plan(p, D, F) : 0;
-  const bool xcd = cus >= sd::kPlBlocks && !(m.fp8 && few) && R <= sd::kXcdMostRows && sd::xcd_plan(x, D, F) > 0;
-  if (xcd && D == 512 && m.xcd_vecs && R <= sd::kXcdFewRows) return Way::xcd_few;
+  const bool xcd = cus >= sd::kPlBlocks && !(m.fp8 && few) && R <= m.xcd_rows && sd::xcd_plan(x, D, F) > 0;
+  if (xcd && D == 512 && m.xcd_vecs && (R <= sd::kXcdFewRows || !x.copy)) return Way::xcd_few;
   if (blocks > 0 && cus >= blocks) return Way::gpu;
-  return xcd && m.xcd_stream ? Way::xcd : Way::launches;
+  return xcd && x.copy && m.xcd_stream ? Way::xcd : Way::launches;
 }
 
 // Whether the pass takes one of them (way: which).
@@ -693,7 +695,7 @@ int decoder_layers_persist(specdec_ctx* c, Model& m, Way way, int B, int T, bool
     a.layers = m.pl_layers; a.stream = way == Way::xcd ? m.xcd_stream : nullptr; a.vecs = m.xcd_vecs;
     a.row_b = m.rm.row_b; a.row_pos = m.rm.row_pos; a.src_len = c->st.src_len;
     if (drafter) { a.causal = m.new_rows; a.live = m.rm.seq_rows; }
-    a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + (size_t)sd::kXcdMostRows * m.d.d_model;
+    a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + (size_t)m.xcd_rows * m.d.d_model;
     a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
     if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
     a.exch = m.pl_exch; a.err = persist_flags(way, m);

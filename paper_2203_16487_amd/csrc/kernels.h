@@ -278,7 +278,7 @@ struct XcdArgs {
   const float* x;
   const bf16* xb;
   float* y;
-  float* resid;                           // [kXcdMostRows][d], scratch
+  float* resid;                           // [xcd_rows_most, of each of eight groups rounded up to 16 times 4 or 7][d], scratch
   bf16 *kc, *vc;
   const void *xk, *xv;
   const float *xk_scale, *xv_scale;
@@ -287,17 +287,18 @@ struct XcdArgs {
   unsigned* err;                          // [2], zero at first and kept from pass to pass: waits were given up (passes yet to
                                           // be computed another way); those of that way too (results are void)
   int RP, d, G, wpu;                      // filled by the launcher, as what follows
+  bool copy;                              // few enough rows to a group for the kernels that stream the copy
   unsigned* raised;
   PlTickets* tickets;
 };
-constexpr int kXcdMostRows = 512;         // rows of a pass at most: 64 on each of 8 XCDs
 constexpr int kXcdFewRows = 63;           // of a verification pass that reads the weights as bound (no copy of them), 32 on an XCD
 // Weights (bf16) of a model's layers (device array) in the order they are used, and their column vectors.
 size_t xcd_stream_bytes(int layers, int d, int F);
 size_t xcd_vec_bytes(int layers, int d);
 hipError_t xcd_pack(hipStream_t st, const PlLayer* layers, int n, int d, char* stream, float* vecs);
-// rows of the largest pass of up to max_batch sequences of up to max_T rows each that it takes
-int xcd_rows_most(int max_batch, int max_T);
+// rows of the largest pass of up to max_batch sequences of up to max_T rows each that it takes; from the copy of the weights
+int xcd_rows_most(int max_batch, int max_T, int d);
+int xcd_copy_rows_most(int max_batch, int max_T);
 // bytes of exch for passes of up to max_batch sequences of up to max_T rows
 size_t xcd_exch_most(int max_batch, int max_T, int d, int F);
 // bytes of exch that a pass of a.B sequences of a.T rows uses (0: too many rows)

@@ -2,7 +2,7 @@
 //
 // With few rows a decoder layer is eight dependent products and attentions of a microsecond each, and as separate kernels
 // every hand-over costs a launch (about 4 us from one kernel's operands to the next one's).  Here 32 workgroups on the 32 CUs
-// of an XCD stay resident for all layers and carry up to 64 rows (whole sequences, dealt over the XCDs; sequences do not meet)
+// of an XCD stay resident for all layers and carry up to 64 rows (d = 512: 112; whole sequences, dealt over the XCDs; sequences do not meet)
 // through them.  A product's columns are dealt over the 32 workgroups, whose eight computing waves split K.  What one workgroup
 // produces for another goes to an exchange buffer that holds kPoison in every 32-bit word beforehand; the consumers load the
 // words they need past their L1, straight into MFMA operand registers, until none of them is kPoison any more.  The value is
@@ -25,6 +25,10 @@
 // its rows.  Passes behind a loaded cache, statistics read back, launches / this kernel, us: one sequence of 5 + 1 rows 96 / 58, 8 x 11 105 / 63, 32 x 11
 // 124 / 83, on 500 source tokens and 200 cached ones 133 / 100, 64 x 8 123 / 96.  An iteration of the loop with a base verifier, 1 x 11 215 /
 // 185, 24 x 11 (504 places for the drafter, some 340 in use) 291 / 261.
+//
+// Five to seven row tiles (65 - 112 rows of an XCD, d = 512; one column tile is summed at a time, the matrices are read in place): a tile more costs
+// 0.4 us a stage where the launches of a pass beyond 512 rows cost 6 each.  Whole passes, launches / this kernel, us: verification of 48 x 11 rows 337
+// / 241, 64 x 11 350 / 267, 80 x 11 368 / 309; drafting 48 x 11 133 / 105, 64 x 11 150 / 126, 80 x 11 157 / 141.
 //
 // What bounds it: a hand-over and instructions in a row at every stage (of 11 rows 0.8 - 3.5 us, of 44 1.8 - 3.9), and with the weights of d =
 // 1024 what an XCD takes in.  Whole verify passes, launches / this kernel, us: d = 512: 6 rows 200 / 109, 77 239 / 121, 176 255 / 140, 352
@@ -86,14 +90,15 @@ __device__ __forceinline__ void pl_again(unsigned& spins, const XcdArgs& a) {
   asm volatile("" ::: "memory");
 }
 
-constexpr int kPlRows = 64;   // rows of a group
+constexpr int kPlRows = 64;   // rows of a group, of the passes that stream a copy of the weights
+constexpr int pl_rows_most(int d) { return d == 512 ? 112 : kPlRows; }   // of any: what registers and LDS hold
 
 // What depends on the dimensions and the type of the weights alone.  A chunk of weights: 16 rows (output columns) x an eighth of D of K,
 // as MFMA fragments: [K / 32][lane][8 values], lane = row + 16 (K / 8 % 4).
 template <int D>
 struct PlDim {
   static constexpr int KW = D / kPlWaves, KS = KW / 32, kChunk = 32 * KW, kReq = kChunk / 1024;
-  static constexpr int kRing = D == 512 ? 5 : 3, kRedTiles = D == 512 ? 8 : 4;   // (what LDS has room for)
+  static constexpr int kRing = D == 512 ? 5 : 3;   // (what LDS has room for)
   static_assert(kReq >= 1 && kRing * kReq <= 56, "whole requests, as many as a wave can have in flight");
   // columns and column tiles of a workgroup: QKV, the square ones, first FFN matrix; chunks of K of the second; all chunks of a layer
   static constexpr int kNQ = 3 * D / kPlMembers, kND = D / kPlMembers, kNF = 4 * D / kPlMembers;
@@ -115,18 +120,19 @@ template <int D, int MR>
 struct PlLds {
   typedef PlDim<D> Dim;
   // column tiles summed together: as many as their partial tiles have room for, and as leave some of the ring
-  static constexpr int kBatch = D == 1024 ? 1 : MR <= 2 ? 4 : 2;
-  static constexpr int kFlips = 2 * kBatch * MR <= Dim::kRedTiles ? 2 : 1;
+  static constexpr int kBatch = D == 1024 || MR > 4 ? 1 : MR <= 2 ? 4 : 2;
+  static constexpr int kRedTiles = D == 1024 ? 4 : MR > 4 ? MR : 8;   // (what LDS has room for)
+  static constexpr int kFlips = 2 * kBatch * MR <= kRedTiles ? 2 : 1;
   char ring[kPlWaves][Dim::kRing * Dim::kChunk];
-  f32x4 red[kPlWaves * Dim::kRedTiles * 64];      // partial tiles, kFlips sets; attention: value tiles of the waves ([32 keys][64],
+  f32x4 red[kPlWaves * kRedTiles * 64];           // partial tiles, kFlips sets; attention: value tiles of the waves ([32 keys][64],
                                                   // swizzled like the tile kernel's), then partial results, 4 KB a wave either way
   float vec[2][Dim::kVecPitch];                   // column vectors, layers in turn
   float ml[kPlWaves * 32];
   float resid[Dim::kTD * 16 * MR * 16];           // of the workgroup's columns
   float stat[2][2 * 16 * MR];                     // {rstd, -mean rstd} of the rows, LayerNorms in turn
   float part[kPlWaves][2 * 16 * MR];              // {sum, squared deviations from its mean} of a row's columns, an eighth of them a wave
-  PlSeq seq[kPlRows];
-  int row_at[kPlRows];                            // of the row in the self-attention cache of head 0 (< 0: none)
+  PlSeq seq[16 * MR];
+  int row_at[16 * MR];                            // of the row in the self-attention cache of head 0 (< 0: none)
   int drawn;                                      // (TICKETS)
   __device__ __forceinline__ bf16* vs(int wave) { return reinterpret_cast<bf16*>(red + wave * 256); }
 };
@@ -468,10 +474,10 @@ __device__ __forceinline__ f32x2 pl_row_stat(const float* part, int pitch, int r
 template <int D, int MR, int NT, class Pre, class Done>
 __device__ __forceinline__ void pl_reduce(PlLds<D, MR>& L, PlTurn& t, int wave, int lane, f32x4 (&acc)[NT][MR], Pre&& pre, Done&& done) {
   constexpr int P = NT * MR;
-  static_assert(PlLds<D, MR>::kFlips * P <= PlDim<D>::kRedTiles && P <= kPlWaves, "room for the partial tiles");
+  static_assert(PlLds<D, MR>::kFlips * P <= PlLds<D, MR>::kRedTiles && P <= kPlWaves, "room for the partial tiles");
   f32x4* red = L.red;
   if (PlLds<D, MR>::kFlips == 1) lds_barrier();   // the tiles before have been summed
-  else red += (t.sums & 1) * (kPlWaves * PlDim<D>::kRedTiles / 2 * 64);
+  else red += (t.sums & 1) * (kPlWaves * PlLds<D, MR>::kRedTiles / 2 * 64);
   const int p = P <= 4 ? (wave + 4 * t.sums) & (kPlWaves - 1) : wave, q0 = min(p, P - 1);
   ++t.sums;
   const auto have = pre(q0 / MR, q0 % MR);
@@ -1048,7 +1054,7 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     }
     auto resid = [&](int mr, int ct) {
       const int lane = pl_lane(), lq = lane & 15, g = lane >> 4;
-      if (TICKETS) return a.resid + (size_t)(at.g * kPlRows + 16 * mr + lq) * D + (at.w * Dim::kTD + ct) * 16 + 4 * g;
+      if (TICKETS) return a.resid + (size_t)(at.g * 16 * MR + 16 * mr + lq) * D + (at.w * Dim::kTD + ct) * 16 + 4 * g;
       return L.resid + ((ct * MR + mr) * 16 + lq) * 16 + 4 * g;
     };
     auto out = [&](int row, int c, const f32x4& y, const f32x4& gx) {
@@ -1144,7 +1150,7 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
       if (st == 0) {   // the residual of the member's columns: embedded rows (those beyond the group's: read, never used)
         for (int i = threadIdx.x; i < 16 * MR * (Dim::kND / 4); i += kPlThreads) {
           const int row = i / (Dim::kND / 4), col = at.w * Dim::kND + i % (Dim::kND / 4) * 4;
-          *reinterpret_cast<f32x4*>(a.resid + (size_t)(g * kPlRows + row) * D + col) =
+          *reinterpret_cast<f32x4*>(a.resid + (size_t)(g * 16 * MR + row) * D + col) =
               *reinterpret_cast<const f32x4*>(a.x + (size_t)(at.row0 + min(row, at.rows - 1)) * D + col);
         }
       }
@@ -1229,7 +1235,11 @@ template <bool KV8, int D>
 static hipError_t pl_launch_both(hipStream_t st, XcdArgs a, int blocks) {
   hipError_t e = hipErrorInvalidValue;
   if constexpr (D == 512) {
-    if (a.causal) {
+    if (a.RP > kPlRows) {   // (a verification pass from the copy: within 1 %)
+      if (a.RP == 80) e = pl_launch<KV8, D, 5, false, true, true>(st, a, blocks);
+      if (a.RP == 96) e = pl_launch<KV8, D, 6, false, true, true>(st, a, blocks);
+      if (a.RP == 112) e = pl_launch<KV8, D, 7, false, true, true>(st, a, blocks);
+    } else if (a.causal) {
       if (a.RP == 16) e = pl_launch<KV8, D, 1, false, true, true>(st, a, blocks);
       if (a.RP == 32) e = pl_launch<KV8, D, 2, false, true, true>(st, a, blocks);
       if (a.RP == 48) e = pl_launch<KV8, D, 3, false, true, true>(st, a, blocks);
@@ -1249,27 +1259,31 @@ static hipError_t pl_launch_both(hipStream_t st, XcdArgs a, int blocks) {
   if (e != hipSuccess) return e;
   a.raised = a.err;
   a.err += 1;
+  if constexpr (D == 512) if (a.RP > kPlRows) return pl_launch<KV8, D, 7, true>(st, a, kPlMembers * std::min(a.G, 2));
   return pl_launch<KV8, D, 4, true>(st, a, kPlMembers * std::min(a.G, 2));
 }
 }  // namespace xcd
 
-int xcd_rows_most(int max_batch, int max_T) {
+static int rows_most(int max_batch, int max_T, int of_group) {
   int most = 0;
-  for (int T = 1; T <= max_T && T <= xcd::kPlRows; ++T) {
-    const int B = std::min(max_batch, xcd::kPlGroups * (xcd::kPlRows / T));
+  for (int T = 1; T <= max_T && T <= of_group; ++T) {
+    const int B = std::min(max_batch, xcd::kPlGroups * (of_group / T));
     most = std::max(most, B * T);
   }
   return most;
 }
+int xcd_copy_rows_most(int max_batch, int max_T) { return rows_most(max_batch, max_T, xcd::kPlRows); }
+int xcd_rows_most(int max_batch, int max_T, int d) { return rows_most(max_batch, max_T, xcd::pl_rows_most(d)); }
 size_t xcd_exch_most(int max_batch, int max_T, int d, int F) {
   const int rows = xcd::pl_group_rows(max_batch, max_T);
-  return xcd::pl_exch_bytes(max_batch, rows < xcd::kPlRows ? rows : xcd::kPlRows, d, F);
+  return xcd::pl_exch_bytes(max_batch, std::min(rows, xcd::pl_rows_most(d)), d, F);
 }
 size_t xcd_plan(XcdArgs& a, int d, int F) {
   a.RP = xcd::pl_group_rows(a.B, a.T);
   a.d = d;
   a.G = a.B < xcd::kPlGroups ? a.B : xcd::kPlGroups;
-  if (a.RP > xcd::kPlRows) return 0;
+  if (a.RP > xcd::pl_rows_most(d)) return 0;
+  a.copy = a.RP <= xcd::kPlRows;
   // waves to a unit of attention: as many as leave every unit its own
   const int units = (a.B + a.G - 1) / a.G * a.H * ((a.T + 15) >> 4);
   a.wpu = xcd::kPlWaves;
@@ -1277,8 +1291,8 @@ size_t xcd_plan(XcdArgs& a, int d, int F) {
   return xcd::pl_exch_bytes(a.B, a.RP, d, F);
 }
 hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F, bool give_up) {
-  if (a.R < 1 || a.T < 1 || a.T > xcd::kPlRows || a.R != a.B * a.T || !persist_supported(a.n_layers, d, F)) return hipErrorInvalidValue;
-  if (xcd_plan(a, d, F) == 0) return hipErrorInvalidValue;
+  if (a.R < 1 || a.T < 1 || a.T > xcd::pl_rows_most(d) || a.R != a.B * a.T || !persist_supported(a.n_layers, d, F)) return hipErrorInvalidValue;
+  if (xcd_plan(a, d, F) == 0 || (a.stream && !a.copy)) return hipErrorInvalidValue;
   a.tickets = reinterpret_cast<PlTickets*>(a.exch);
   a.exch += kPlTicketBytes;
   a.raised = a.err;
