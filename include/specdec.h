@@ -204,7 +204,7 @@ int specdec_prefill(specdec_ctx* ctx, specdec_role role, void* stream);
  * cached; mask slots attend to the whole stream and to all k slots.
  * With d_model 512 / d_ffn 2048 a pass whose places (k and the most stream tokens a sequence can
  * bring: all that commits since the drafter's latest pass may have appended, one behind a loaded
- * cache) are few runs its decoder layers as one kernel, each XCD on sequences of its own, under the
+ * cache) are few (at most 144 to a group, 128 where a sequence can bring several) runs its decoder layers as one kernel, each XCD on sequences of its own, under the
  * rules of specdec_verify; should its second run not complete either, every draft is pad_id.
  * logits_or_null: optional device fp32 [B, k, V] receiving the slots' logits (parity mode; slow). */
 int specdec_draft(specdec_ctx* ctx, int32_t k, int32_t* draft, float* logits_or_null, void* stream);
@@ -239,8 +239,8 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * Finished sequences report accept_len 0 and next_token pad_id.
  * k = 0 (draft may be null) is one plain autoregressive step: accept_len = 0 and next_token is
  * the verifier's greedy token (the baseline of Sec. 2 on the same kernels).
- * Passes of few rows (d_model 512 / d_ffn 2048 or 1024 / 4096, 32 layers; at most 64
- * rows, d_model 512: 112, to each of eight groups that the sequences are dealt to evenly; of those beyond 128 rows, and at
+ * Passes of few rows (d_model 512 / d_ffn 2048 or 1024 / 4096, 32 layers; at most 96
+ * rows, d_model 512: 160, to each of eight groups that the sequences are dealt to evenly; of those beyond 128 rows, and at
  * d_model 512 of all that read bf16 weights, every XCD takes one group; where the stream has fewer than 256 compute units, one of at
  * most 48 (1024: 128) rows may still run over those it has) run their decoder layers as one kernel of up to 256
  * workgroups that wait for each other; where a

@@ -295,7 +295,8 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   t.xv = cv.take<bf16>(t.xkv_layer * d->dec_layers);
   t.x = cv.take<float>(Rpass * D);
   t.x2 = cv.take<float>(32 * D);
-  t.xcd_rows = D == 512 && sd::xcd_rows_most((int)Bm, c->Tmax, 512) > 512 ? 896 : 512;
+  t.xcd_rows = sd::persist_supported(d->dec_layers, (int)D, (int)F) &&
+                       sd::xcd_rows_most((int)Bm, D == 512 ? c->Tmax : c->lim.k_max + 1, (int)D) > 512 ? 8 * sd::xcd_group_rows_most((int)D) : 512;
   t.skp = cv.take<float>((size_t)2 * t.xcd_rows * D);   // (or the one-kernel decoder's sum and its residual)
   static_assert(2 * sd::kSk2MaxParts * 32 <= 2 * 512 && persist_rows(512) <= 512 && persist_rows(1024) <= 512, "both fit");
   t.hx = cv.take<float>(Bm * (size_t)c->lim.k_max * D);
@@ -336,7 +337,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     t.pl_rows = (int)(most < persist_rows((int)D) ? most : persist_rows((int)D));
     // The per-XCD decoder's share only where a pass within the limits can be its (one_kernel_way).  (The size is asked for without a role: a
     // drafter's workspace has the place for the copy of the weights, which it does not use, and a verifier's buffers that a drafter's rows need.)
-    const bool per_xcd = sd::xcd_copy_rows_most((int)Bm, c->lim.k_max + 1) > (D == 512 ? sd::kXcdFewRows : (int)persist_rows((int)D));
+    const bool per_xcd = sd::xcd_copy_rows_most((int)Bm, c->lim.k_max + 1, (int)D) > (D == 512 ? sd::kXcdFewRows : (int)persist_rows((int)D));
     const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F);
     const size_t xcd = D == 512 ? sd::xcd_exch_most((int)Bm, c->Tmax, (int)D, (int)F) : per_xcd ? sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F) : 0;
     t.pl_exch = cv.take<char>(one > xcd ? one : xcd);
@@ -623,15 +624,13 @@ int stream_cus(hipStream_t st) {
   return n;
 }
 
-// cus: compute units the pass's stream has.  few: the E4M3 copies of the weights, if the model has them.  A drafter's pass (T: the most rows of
-// a sequence) is per XCD, with the matrices as bound, or launches.
-Way one_kernel_way(const Model& m, int B, int T, bool few, bool drafter, int cus) {
+// cus: compute units the pass's stream has.  few: the E4M3 copies of the weights, if the model has them.
+Way one_kernel_way(const Model& m, int B, int T, bool few, int cus) {
   sd::PlArgs p{};
   p.R = B * T; p.T = T; p.B = B; p.H = m.d.n_heads;
   sd::XcdArgs x{};
   x.R = B * T; x.T = T; x.B = B; x.H = m.d.n_heads;
   const int D = m.d.d_model, F = m.d.d_ffn, R = B * T;
-  if (drafter) return D == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && R <= m.xcd_rows && sd::xcd_plan(x, D, F) > 0 ? Way::xcd_few : Way::launches;
   const int blocks = R <= m.pl_rows ? sd::persist_plan(p, D, F) : 0;
   const bool xcd = cus >= sd::kPlBlocks && !(m.fp8 && few) && R <= m.xcd_rows && sd::xcd_plan(x, D, F) > 0;
   if (xcd && D == 512 && m.xcd_vecs && (R <= sd::kXcdFewRows || !x.copy)) return Way::xcd_few;
@@ -639,16 +638,28 @@ Way one_kernel_way(const Model& m, int B, int T, bool few, bool drafter, int cus
   return xcd && x.copy && m.xcd_stream ? Way::xcd : Way::launches;
 }
 
-// Whether the pass takes one of them (way: which).
-bool persist_ok(specdec_ctx* c, const Model& m, int B, int T, bool few, bool drafter, hipStream_t st, Way* way) {
+// The same for a drafter's pass of `fresh` stream rows a sequence at most and k slots: per XCD with the matrices as bound, or launches.
+// The launches compute the rows there are, this one the places for the most there can be.  Launches / this one, us, rows of an XCD: places all in
+// use 132 (96 x 11) 172 / 157, 143 184 / 174, 154 188 / 194, 156 (48 x 26) 196 / 191; iterations of the loop with a base verifier, two thirds of them
+// in use, 126 397 / 385, 147 430 / 434, 168 465 / 478.
+Way draft_way(const Model& m, int B, int fresh, int k, int cus) {
+  sd::XcdArgs x{};
+  x.R = B * (fresh + k); x.T = fresh + k; x.B = B; x.H = m.d.n_heads;
+  const bool xcd = m.d.d_model == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && x.R <= m.xcd_rows && sd::xcd_plan(x, 512, m.d.d_ffn) > 0;
+  return xcd && x.RP <= (fresh > 1 ? 128 : 144) ? Way::xcd_few : Way::launches;
+}
+
+// Whether the pass takes one of them (way: which); way_of(cus): the way it takes with as many compute units.
+template <class F>
+bool persist_ok(specdec_ctx* c, const Model& m, hipStream_t st, F way_of, Way* way) {
   *way = Way::launches;
   if (!m.pl_exch || c->no_skinny || c->no_ln_fold || c->sliced) return false;
-  if (one_kernel_way(m, B, T, few, drafter, sd::kPlBlocks) == Way::launches) return false;   // (whatever the GPU and the stream have)
+  if (way_of(sd::kPlBlocks) == Way::launches) return false;   // (whatever the GPU and the stream have)
   int dev = -1, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return false;
-  const Way found = one_kernel_way(m, B, T, few, drafter, std::min(cus, stream_cus(st)));   // (all of a way's workgroups run at once)
+  const Way found = way_of(std::min(cus, stream_cus(st)));   // (all of a way's workgroups run at once)
   if (found == Way::launches) return false;
   if (c->persist_refused || (c->persist_dev >= 0 && c->persist_dev != dev)) return false;
   bool capturing = false;
@@ -1189,7 +1200,7 @@ int specdec_draft(specdec_ctx* c, int32_t k, int32_t* draft, float* logits, void
   // grids are sized for the most (the GEMMs with LayerNorm folded in know how to stop early)
   // The per-XCD decoder takes T places a sequence, those beyond its rows among them.
   Way way;
-  const bool one = persist_ok(c, m, B, T, false, true, st, &way), packed = !one && !c->no_ln_fold;
+  const bool one = persist_ok(c, m, st, [&](int cus) { return draft_way(m, B, ub, k, cus); }, &way), packed = !one && !c->no_ln_fold;
   LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_stream(st, c->st, m.rm, SPECDEC_DRAFTER, B, T, k, m.d.mask_id, m.d.pad_id,
                                       m.d.vocab, m.new_rows, m.embed, m.pe, m.x, m.xb, m.d.d_model, packed, one ? m.pl_exch : nullptr,
                                       one ? persist_clear(way, m, B, T) : 0));
@@ -1244,7 +1255,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   // The fused small-batch decoder kernels, whose every block redoes what precedes its product and which embed the rows
   // themselves, where that is little: one sequence of few rows, d = 512 (3 rows 184 against 205 us, 11: 210 / 214, 16: 220 /
   // 218; two sequences of 6 235 / 214; d = 1024: 6 rows 285 / 268, 26 521 / 302).  Otherwise the general ones.
-  const bool one = persist_ok(c, m, B, T, small, false, st, &c->way);
+  const bool one = persist_ok(c, m, st, [&](int cus) { return one_kernel_way(m, B, T, small, cus); }, &c->way);
   const bool fused = small && !one && (c->no_ln_fold || c->sliced || (B == 1 && R <= 12 && m.d.d_model <= 512));
   VerifyScratch vs{m.part, m.zd, m.row_stats};
   if (ext) {

@@ -278,7 +278,7 @@ struct XcdArgs {
   const float* x;
   const bf16* xb;
   float* y;
-  float* resid;                           // [xcd_rows_most, of each of eight groups rounded up to 16 times 4 or 7][d], scratch
+  float* resid;                           // [8 * 64, beyond 64 rows of a group 8 * xcd_group_rows_most][d], scratch
   bf16 *kc, *vc;
   const void *xk, *xv;
   const float *xk_scale, *xv_scale;
@@ -298,7 +298,8 @@ size_t xcd_vec_bytes(int layers, int d);
 hipError_t xcd_pack(hipStream_t st, const PlLayer* layers, int n, int d, char* stream, float* vecs);
 // rows of the largest pass of up to max_batch sequences of up to max_T rows each that it takes; from the copy of the weights
 int xcd_rows_most(int max_batch, int max_T, int d);
-int xcd_copy_rows_most(int max_batch, int max_T);
+int xcd_copy_rows_most(int max_batch, int max_T, int d);
+int xcd_group_rows_most(int d);   // rows of a group at most
 // bytes of exch for passes of up to max_batch sequences of up to max_T rows
 size_t xcd_exch_most(int max_batch, int max_T, int d, int F);
 // bytes of exch that a pass of a.B sequences of a.T rows uses (0: too many rows)

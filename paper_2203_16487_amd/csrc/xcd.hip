@@ -2,7 +2,7 @@
 //
 // With few rows a decoder layer is eight dependent products and attentions of a microsecond each, and as separate kernels
 // every hand-over costs a launch (about 4 us from one kernel's operands to the next one's).  Here 32 workgroups on the 32 CUs
-// of an XCD stay resident for all layers and carry up to 64 rows (d = 512: 112; whole sequences, dealt over the XCDs; sequences do not meet)
+// of an XCD stay resident for all layers and carry up to 96 rows (d = 512: 160; whole sequences, dealt over the XCDs; sequences do not meet)
 // through them.  A product's columns are dealt over the 32 workgroups, whose eight computing waves split K.  What one workgroup
 // produces for another goes to an exchange buffer that holds kPoison in every 32-bit word beforehand; the consumers load the
 // words they need past their L1, straight into MFMA operand registers, until none of them is kPoison any more.  The value is
@@ -26,9 +26,11 @@
 // 124 / 83, on 500 source tokens and 200 cached ones 133 / 100, 64 x 8 123 / 96.  An iteration of the loop with a base verifier, 1 x 11 215 /
 // 185, 24 x 11 (504 places for the drafter, some 340 in use) 291 / 261.
 //
-// Five to seven row tiles (65 - 112 rows of an XCD, d = 512; one column tile is summed at a time, the matrices are read in place): a tile more costs
-// 0.4 us a stage where the launches of a pass beyond 512 rows cost 6 each.  Whole passes, launches / this kernel, us: verification of 48 x 11 rows 337
-// / 241, 64 x 11 350 / 267, 80 x 11 368 / 309; drafting 48 x 11 133 / 105, 64 x 11 150 / 126, 80 x 11 157 / 141.
+// More than four row tiles (65 rows and more of an XCD; one column tile is summed at a time and, where LDS has no room for its row tiles, these in two
+// parts; of d = 512 the matrices are read in place): a tile more costs 0.4 us a stage where the launches of a pass beyond 512 rows cost 6 each.
+// Whole passes, launches / this kernel, us: verification, d = 512: 48 x 11 rows 337 / 241, 64 x 11 350 / 267, 80 x 11 368 / 309, 96 x 11 421 / 360, 112 x
+// 11 441 / 436 (eleven tiles, 128 x 11: 471 / 496), on 250 source tokens 128 x 9 565 / 483; d = 1024: 48 x 11 560 / 506, 64 x 11 589 / 555, on 512
+// source tokens 753 / 724; drafting 48 x 11 133 / 105, 64 x 11 150 / 126, 80 x 11 157 / 141.
 //
 // What bounds it: a hand-over and instructions in a row at every stage (of 11 rows 0.8 - 3.5 us, of 44 1.8 - 3.9), and with the weights of d =
 // 1024 what an XCD takes in.  Whole verify passes, launches / this kernel, us: d = 512: 6 rows 200 / 109, 77 239 / 121, 176 255 / 140, 352
@@ -90,8 +92,11 @@ __device__ __forceinline__ void pl_again(unsigned& spins, const XcdArgs& a) {
   asm volatile("" ::: "memory");
 }
 
-constexpr int kPlRows = 64;   // rows of a group, of the passes that stream a copy of the weights
-constexpr int pl_rows_most(int d) { return d == 512 ? 112 : kPlRows; }   // of any: what registers and LDS hold
+// Rows of a group: what registers and LDS hold; of d = 512 from a copy of the weights (more are read in place); what the second run's smaller
+// kernel takes.
+constexpr int pl_rows_most(int d) { return d == 512 ? 160 : 96; }
+constexpr int pl_copy_rows_most(int d) { return d == 512 ? 64 : 96; }
+constexpr int kPlRows = 64;
 
 // What depends on the dimensions and the type of the weights alone.  A chunk of weights: 16 rows (output columns) x an eighth of D of K,
 // as MFMA fragments: [K / 32][lane][8 values], lane = row + 16 (K / 8 % 4).
@@ -121,8 +126,10 @@ struct PlLds {
   typedef PlDim<D> Dim;
   // column tiles summed together: as many as their partial tiles have room for, and as leave some of the ring
   static constexpr int kBatch = D == 1024 || MR > 4 ? 1 : MR <= 2 ? 4 : 2;
-  static constexpr int kRedTiles = D == 1024 ? 4 : MR > 4 ? MR : 8;   // (what LDS has room for)
-  static constexpr int kFlips = 2 * kBatch * MR <= kRedTiles ? 2 : 1;
+  // row tiles summed together, and tiles there is room for
+  static constexpr int kSub = D == 1024 ? (MR <= 4 ? MR : 3) : MR <= 7 ? MR : MR == 8 ? 4 : 5;
+  static constexpr int kRedTiles = D == 1024 || kSub < MR ? (kSub > 4 ? kSub : 4) : MR > 4 ? MR : 8;
+  static constexpr int kFlips = 2 * kBatch * kSub <= kRedTiles ? 2 : 1;
   char ring[kPlWaves][Dim::kRing * Dim::kChunk];
   f32x4 red[kPlWaves * kRedTiles * 64];           // partial tiles, kFlips sets; attention: value tiles of the waves ([32 keys][64],
                                                   // swizzled like the tile kernel's), then partial results, 4 KB a wave either way
@@ -471,23 +478,23 @@ __device__ __forceinline__ f32x2 pl_row_stat(const float* part, int pitch, int r
 // The partial tiles of NT column tiles: stored, met at the barrier, summed in wave order, each by one wave (not the ones that
 // summed last where there are enough).  There pre(i, mr) reads what the epilogue needs ahead of the barrier and done(i, mr, v, pre's)
 // finishes: row 16 mr + lq, columns 4 g .. + 3 of tile i.
-template <int D, int MR, int NT, class Pre, class Done>
-__device__ __forceinline__ void pl_reduce(PlLds<D, MR>& L, PlTurn& t, int wave, int lane, f32x4 (&acc)[NT][MR], Pre&& pre, Done&& done) {
-  constexpr int P = NT * MR;
+template <int D, int MR, int NT, int M0, int MS, class Pre, class Done>
+__device__ __forceinline__ void pl_reduce_some(PlLds<D, MR>& L, PlTurn& t, int wave, int lane, f32x4 (&acc)[NT][MR], Pre&& pre, Done&& done) {
+  constexpr int P = NT * MS;
   static_assert(PlLds<D, MR>::kFlips * P <= PlLds<D, MR>::kRedTiles && P <= kPlWaves, "room for the partial tiles");
   f32x4* red = L.red;
   if (PlLds<D, MR>::kFlips == 1) lds_barrier();   // the tiles before have been summed
   else red += (t.sums & 1) * (kPlWaves * PlLds<D, MR>::kRedTiles / 2 * 64);
   const int p = P <= 4 ? (wave + 4 * t.sums) & (kPlWaves - 1) : wave, q0 = min(p, P - 1);
   ++t.sums;
-  const auto have = pre(q0 / MR, q0 % MR);
+  const auto have = pre(q0 / MS, M0 + q0 % MS);
   asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc[NT - 1][MR - 1]));   // (the last of the products; see mfma_settle)
 #pragma unroll
   for (int i = 0; i < NT; ++i)
 #pragma unroll
-    for (int mr = 0; mr < MR; ++mr) {
-      asm volatile("" : "+v"(acc[i][mr]));   // (not ahead of it)
-      red[((i * MR + mr) * kPlWaves + wave) * 64 + lane] = acc[i][mr];
+    for (int mr = 0; mr < MS; ++mr) {
+      asm volatile("" : "+v"(acc[i][M0 + mr]));   // (not ahead of it)
+      red[((i * MS + mr) * kPlWaves + wave) * 64 + lane] = acc[i][M0 + mr];
     }
   lds_barrier();
   if (p >= P) return;
@@ -500,7 +507,15 @@ __device__ __forceinline__ void pl_reduce(PlLds<D, MR>& L, PlTurn& t, int wave, 
 #pragma unroll
     for (int w = 1; w < kPlWaves; ++w) v[e] += q[w][e];
   }
-  done(p / MR, p % MR, v, have);
+  done(p / MS, M0 + p % MS, v, have);
+}
+// (row tiles a few at a time, where the partial tiles of all have no room)
+template <int D, int MR, int NT, class Pre, class Done>
+__device__ __forceinline__ void pl_reduce(PlLds<D, MR>& L, PlTurn& t, int wave, int lane, f32x4 (&acc)[NT][MR], Pre&& pre, Done&& done) {
+  constexpr int SUB = PlLds<D, MR>::kSub;
+  static_assert(MR <= 2 * SUB, "twice at most");
+  pl_reduce_some<D, MR, NT, 0, SUB>(L, t, wave, lane, acc, pre, done);
+  if constexpr (MR > SUB) pl_reduce_some<D, MR, NT, SUB, MR - SUB>(L, t, wave, lane, acc, pre, done);
 }
 
 // hidden (LayerNorm folded) W^T + b on N column tiles, the workgroup's; cs: their cs, behind them bf (LDS); epi(row of the group,
@@ -1047,8 +1062,8 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
       u32x4 none[MR][Dim::KS];
       PlRows<D, MR>(a, s == 7 ? ex.hid() : ex.att(i), false, at.rows, pl_lane(), wave).first(none, st, L.part[wave]);
       lds_barrier();
-      if (wave < MR) {
-        const int row = 16 * wave + (pl_lane() & 15);
+      for (int mr = wave; mr < MR; mr += kPlWaves) {
+        const int row = 16 * mr + (pl_lane() & 15);
         *reinterpret_cast<f32x2*>(stat + 2 * row) = st ? pl_row_stat<D>(&L.part[0][0], 2 * 16 * MR, row, pl_lane() >> 4) : f32x2{1.f, 0.f};
       }
     }
@@ -1235,10 +1250,13 @@ template <bool KV8, int D>
 static hipError_t pl_launch_both(hipStream_t st, XcdArgs a, int blocks) {
   hipError_t e = hipErrorInvalidValue;
   if constexpr (D == 512) {
-    if (a.RP > kPlRows) {   // (a verification pass from the copy: within 1 %)
+    if (!a.copy) {   // (a verification pass from the copy: within 1 %)
       if (a.RP == 80) e = pl_launch<KV8, D, 5, false, true, true>(st, a, blocks);
       if (a.RP == 96) e = pl_launch<KV8, D, 6, false, true, true>(st, a, blocks);
       if (a.RP == 112) e = pl_launch<KV8, D, 7, false, true, true>(st, a, blocks);
+      if (a.RP == 128) e = pl_launch<KV8, D, 8, false, true, true>(st, a, blocks);
+      if (a.RP == 144) e = pl_launch<KV8, D, 9, false, true, true>(st, a, blocks);
+      if (a.RP == 160) e = pl_launch<KV8, D, 10, false, true, true>(st, a, blocks);
     } else if (a.causal) {
       if (a.RP == 16) e = pl_launch<KV8, D, 1, false, true, true>(st, a, blocks);
       if (a.RP == 32) e = pl_launch<KV8, D, 2, false, true, true>(st, a, blocks);
@@ -1255,11 +1273,15 @@ static hipError_t pl_launch_both(hipStream_t st, XcdArgs a, int blocks) {
     if (a.RP == 32) e = pl_launch<KV8, D, 2, false>(st, a, blocks);
     if (a.RP == 48) e = pl_launch<KV8, D, 3, false>(st, a, blocks);
     if (a.RP == 64) e = pl_launch<KV8, D, 4, false>(st, a, blocks);
+    if constexpr (D == 1024) {
+      if (a.RP == 80) e = pl_launch<KV8, D, 5, false>(st, a, blocks);
+      if (a.RP == 96) e = pl_launch<KV8, D, 6, false>(st, a, blocks);
+    }
   }
   if (e != hipSuccess) return e;
   a.raised = a.err;
   a.err += 1;
-  if constexpr (D == 512) if (a.RP > kPlRows) return pl_launch<KV8, D, 7, true>(st, a, kPlMembers * std::min(a.G, 2));
+  if (a.RP > kPlRows) return pl_launch<KV8, D, pl_rows_most(D) / 16, true>(st, a, kPlMembers * std::min(a.G, 2));
   return pl_launch<KV8, D, 4, true>(st, a, kPlMembers * std::min(a.G, 2));
 }
 }  // namespace xcd
@@ -1272,7 +1294,8 @@ static int rows_most(int max_batch, int max_T, int of_group) {
   }
   return most;
 }
-int xcd_copy_rows_most(int max_batch, int max_T) { return rows_most(max_batch, max_T, xcd::kPlRows); }
+int xcd_copy_rows_most(int max_batch, int max_T, int d) { return rows_most(max_batch, max_T, xcd::pl_copy_rows_most(d)); }
+int xcd_group_rows_most(int d) { return xcd::pl_rows_most(d); }
 int xcd_rows_most(int max_batch, int max_T, int d) { return rows_most(max_batch, max_T, xcd::pl_rows_most(d)); }
 size_t xcd_exch_most(int max_batch, int max_T, int d, int F) {
   const int rows = xcd::pl_group_rows(max_batch, max_T);
@@ -1283,7 +1306,7 @@ size_t xcd_plan(XcdArgs& a, int d, int F) {
   a.d = d;
   a.G = a.B < xcd::kPlGroups ? a.B : xcd::kPlGroups;
   if (a.RP > xcd::pl_rows_most(d)) return 0;
-  a.copy = a.RP <= xcd::kPlRows;
+  a.copy = a.RP <= xcd::pl_copy_rows_most(d);
   // waves to a unit of attention: as many as leave every unit its own
   const int units = (a.B + a.G - 1) / a.G * a.H * ((a.T + 15) >> 4);
   a.wpu = xcd::kPlWaves;

@@ -1,5 +1,5 @@
-"""Passes of 65 - 112 rows to an XCD (d_model 512): verification and drafting as one kernel, five to seven row tiles and their remainders,
-against the oracle; waits given up; one row more than it takes."""
+"""Passes of more than 64 rows to an XCD (d_model 512: up to 160, 1024: up to 96): verification and drafting as one kernel, five to ten row
+tiles and their remainders, summed all at once and a few at a time, against the oracle; waits given up; more rows than it takes."""
 import numpy as np
 import pytest
 
@@ -14,17 +14,26 @@ from test_gpu_one_kernel_draft import draft, model, open_pass
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("way,B,k,S,lo,hi,opts", [
-    ("xcd in place", 34, 12, 20, 0, 40, {}),       # 65 and 52 rows, five tiles: the last of one row
-    ("xcd in place", 40, 15, 30, 0, 60, FP8_KV),   # 80, five
-    ("xcd in place", 64, 10, 64, 0, 64, {}),       # 88, six
-    ("xcd in place", 43, 15, 300, 0, 200, {}),     # 96 and 80, six; several chunks of keys
-    ("xcd in place", 97, 7, 30, 0, 75, FP8_KV),    # 104 and 96, seven
-    ("xcd in place", 32, 27, 20, 0, 40, {}),       # 112, seven: 896 rows, the most; two query tiles a sequence
-    ("launches", 33, 27, 20, 0, 40, {}),           # 140 and 112
+@pytest.mark.parametrize("way,d,B,k,S,lo,hi,opts", [
+    ("xcd in place", 512, 34, 12, 20, 0, 40, {}),       # 65 and 52 rows, five tiles: the last of one row
+    ("xcd in place", 512, 40, 15, 30, 0, 60, FP8_KV),   # 80, five
+    ("xcd in place", 512, 64, 10, 64, 0, 64, {}),       # 88, six
+    ("xcd in place", 512, 43, 15, 300, 0, 200, {}),     # 96 and 80, six; several chunks of keys
+    ("xcd in place", 512, 97, 7, 30, 0, 75, FP8_KV),    # 104 and 96, seven
+    ("xcd in place", 512, 32, 27, 20, 0, 40, {}),  # 112, seven; two query tiles a sequence
+    ("xcd in place", 512, 81, 10, 20, 0, 40, {}),  # 121 and 110, eight
+    ("xcd in place", 512, 43, 21, 20, 0, 40, FP8_KV),   # 132 and 110, nine
+    ("xcd in place", 512, 112, 10, 64, 0, 64, {}), # 154, ten
+    ("xcd in place", 512, 80, 15, 20, 0, 40, {}),  # 160, ten: 1280 rows, the most
+    ("launches", 512, 121, 10, 20, 0, 40, {}),     # 176 and 165
+    ("xcd", 1024, 34, 12, 20, 0, 40, {}),          # 65 and 52, five
+    ("xcd", 1024, 40, 15, 200, 0, 140, FP8_KV),    # 80, five
+    ("xcd", 1024, 64, 10, 40, 0, 64, {}),          # 88, six
+    ("xcd", 1024, 24, 31, 40, 0, 64, {}),          # 96, six: 768 rows, the most; two query tiles a sequence
+    ("launches", 1024, 33, 21, 20, 0, 40, {}),     # 110 and 88
 ])
-def test_verification_against_oracle(way, B, k, S, lo, hi, opts):
-    case = cases.make_verify_case(desc(512), seed=600 + B, B=B, S=S, k=k, beta=3, tau=1.0, len_lo=lo, len_hi=hi, drafts="random", ragged_src=True,
+def test_verification_against_oracle(way, d, B, k, S, lo, hi, opts):
+    case = cases.make_verify_case(desc(d), seed=600 + B, B=B, S=S, k=k, beta=3, tau=1.0, len_lo=lo, len_hi=hi, drafts="random", ragged_src=True,
                                   fp8_kv=sd.SPECDEC_OPT_FP8_CROSS_KV in opts)
     cases.run_oracle(case)
     ses = gh.open_verifier(case, k_max=k, options=opts, fill=0xFF)
@@ -50,6 +59,8 @@ def test_verification_against_oracle(way, B, k, S, lo, hi, opts):
     (16, 25, 30, (0, 25), False),       # up to 102, seven; half of them without rows
     (40, 7, 20, (0, 7), False),         # up to 75, five
     (33, 15, 260, (200, 290), True),    # 80 and 64, five
+    (41, 10, 20, (0, 10), False),       # up to 126 and 105, eight
+    (97, 10, 20, (0, 30), True),        # 143 and 132, nine: the most
 ])
 def test_drafting_against_oracle(B, k, S, j, prefill):
     dd, db, dm = model()
