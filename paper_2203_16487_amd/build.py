@@ -16,7 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspecdec.so")
-SOURCES = ["api.hip", "gemm.hip", "attn.hip", "misc.hip", "skinny.hip", "skinny2.hip", "persist.hip", "xcd.hip"]
+SOURCES = ["api.hip", "gemm.hip", "attn.hip", "misc.hip", "skinny.hip", "skinny2.hip", "persist.hip", "xcd.hip",
+           "xcd_512.hip", "xcd_512_kv8.hip", "xcd_1024.hip", "xcd_1024_kv8.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", *os.environ.get("SD_EXTRA_FLAGS", "").split(), "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-parameter",
          # packed-fp32 instruction selection off (device pass only; the host pass
@@ -38,7 +39,7 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(_compile, SOURCES))
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
                        capture_output=True, text=True)

@@ -47,7 +47,7 @@ struct Fp8Layer {
 };
 
 // How the decoder layers of a verify pass run: launches a stage; as one kernel over the whole GPU (persist.hip); as one kernel, each XCD
-// on sequences of its own (xcd.hip), from a copy of the weights in order of use or, a few rows, from the weights as bound.
+// on sequences of its own (xcd_core.h), from a copy of the weights in order of use or, a few rows, from the weights as bound.
 enum class Way {
   launches = SPECDEC_WAY_LAUNCHES, gpu = SPECDEC_WAY_GPU, xcd = SPECDEC_WAY_XCD, xcd_few = SPECDEC_WAY_XCD_IN_PLACE
 };
@@ -81,7 +81,7 @@ struct Model {
   bool skinny_ready = false;
   sd::PlLayer* pl_layers = nullptr;   // device copy of the decoder layers' pointers (one-kernel decoder, persist.hip)
   int* pl_err = nullptr;              // its flags (PlArgs::err), behind them the per-XCD one's (XcdArgs::err)
-  char* pl_exch = nullptr;            // exchange buffers, its or the per-XCD one's (xcd.hip); null: dimensions they do not support
+  char* pl_exch = nullptr;            // exchange buffers, its or the per-XCD one's (xcd_core.h); null: dimensions they do not support
   int pl_rows = 0;                    // rows they are sized for, its
   int xcd_rows = 0;                   // rows that skp holds twice for the other one
   char* xcd_stream = nullptr;         // the layers' weights as the per-XCD decoder streams them (null: no pass of more than a few rows of 512)

@@ -266,7 +266,7 @@ size_t persist_exch_bytes(int rows, int layers, int d, int F);
 int persist_plan(PlArgs& a, int d, int F);   // workgroups of a pass of a.R rows, a.B sequences, a.H heads (0: too many rows)
 // give_up: every wait that does not end at once is given up
 hipError_t persist_decoder(hipStream_t st, PlArgs a, int d, int F, bool give_up);
-// ---- xcd.hip: the same for more rows, each XCD on sequences of its own ----
+// ---- xcd.hip, xcd_core.h: the same for more rows, each XCD on sequences of its own ----
 struct XcdArgs {
   int R, T, B, H, Lcap, Scap, n_layers;   // as PlArgs
   const PlLayer* layers;                  // device array [n_layers]
@@ -302,7 +302,7 @@ int xcd_copy_rows_most(int max_batch, int max_T, int d);
 int xcd_group_rows_most(int d);   // rows of a group at most
 // bytes of exch for passes of up to max_batch sequences of up to max_T rows
 size_t xcd_exch_most(int max_batch, int max_T, int d, int F);
-// bytes of exch that a pass of a.B sequences of a.T rows uses (0: too many rows)
+// bytes of exch that are 0xff when a pass of a.B sequences of a.T rows starts (0: too many rows)
 size_t xcd_plan(XcdArgs& a, int d, int F);
 hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F, bool give_up);   // give_up: so that waits have to be given up
 // ---- skinny2.hip: the same passes with sub-layers owned by head / by FFN slice (three kernels per layer) ----

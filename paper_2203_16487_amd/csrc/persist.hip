@@ -19,7 +19,7 @@
 // What bounds it: the chain of 7 hand-overs a layer.  A whole verify pass of 6 layers, separate launches -> this kernel: d = 512, 6 rows
 // 200 -> 112 us, 48 228 -> 131; d = 1024, 6 rows 252 -> 159, 26 293 -> 193, with E4M3 weights 285 -> 200.  Beyond 64 rows
 // of d = 1024, items of 32 rows: 121 rows 323 -> 283.  More rows (from 129 of d = 1024 on), and at d = 512 all passes with bf16 weights on a
-// stream that has every compute unit, are the per-XCD decoder's (xcd.hip).  Larger items were tried (48 x 64, 352 rows) and are level with separate launches: every item fetches its rows and weights at the 60 - 75 GB/s one CU takes in,
+// stream that has every compute unit, are the per-XCD decoder's (xcd_core.h).  Larger items were tried (48 x 64, 352 rows) and are level with separate launches: every item fetches its rows and weights at the 60 - 75 GB/s one CU takes in,
 // whether the rows come through the L2 (counters instead of kPoison) or not, and whether or not the next weights are requested ahead.
 //
 // The workgroups wait for each other, so all of them have to be running.  There are no more of them than the stream has CUs and

@@ -1,4 +1,4 @@
-// What the two decoders that run as one kernel share (persist.hip: over the whole GPU; xcd.hip: each XCD on sequences of its own):
+// What the two decoders that run as one kernel share (persist.hip: over the whole GPU; xcd_core.h: each XCD on sequences of its own):
 // words that are their own flags, and the buffers workgroups exchange them through.
 #pragma once
 #include "attn_core.h"

@@ -1,0 +1,8 @@
+// The per-XCD decoder's kernels, d = 1024, cross-attention keys / values in bf16.
+#include "xcd_core.h"
+
+namespace sd {
+namespace xcd {
+template hipError_t pl_launch_both<false, 1024>(hipStream_t, XcdArgs, int);
+}  // namespace xcd
+}  // namespace sd
