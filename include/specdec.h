@@ -161,7 +161,11 @@ int specdec_begin(specdec_ctx* ctx, int32_t B, int32_t max_new, void* stream);
 
 /* Encoder pass of every bound model over src (device int32 [B, S_max], right-padded;
  * src_len device int32 [B], 1 <= src_len <= S_max <= max_src), then the cross-attention
- * keys/values of every decoder layer.  Runs once per input, not per iteration (Sec. 3.1.2). */
+ * keys/values of every decoder layer.  Runs once per input, not per iteration (Sec. 3.1.2).
+ * With both models bound the drafter's encoder runs beside the verifier's, on a stream of the
+ * context's own that starts behind what `stream` holds and that `stream` then waits for (also under
+ * capture); one after the other on a stream that may not use every compute unit, and while launches
+ * are timed.  Same results. */
 int specdec_encode(specdec_ctx* ctx, const int32_t* src, const int32_t* src_len, int32_t S_max,
                    void* stream);
 

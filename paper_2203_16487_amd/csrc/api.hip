@@ -149,6 +149,10 @@ struct specdec_ctx {
   bool fp8 = false;         // SPECDEC_OPT_FP8_WEIGHTS = 1: models bound from now on keep E4M3 copies for small batches
   bool fp8_kv = false;      // SPECDEC_OPT_FP8_CROSS_KV = 1: models bound from now on keep E4M3 cross keys / values
   bool wide_vocab = false;  // SPECDEC_OPT_WIDE_VOCAB_TILES = 1: 256 x 256 vocabulary tiles in every pass of more than 32 rows
+  // the drafter's encoder beside the verifier's (specdec_encode): made when the second of two models with encoders is bound
+  hipStream_t side = nullptr;
+  int side_dev = -1;
+  hipEvent_t side_ev[2] = {nullptr, nullptr};   // what the caller's stream held, the end
   char err[512] = {0};
 };
 
@@ -785,6 +789,15 @@ int specdec_create(specdec_ctx** out, const specdec_limits* lim) {
 void specdec_destroy(specdec_ctx* c) {
   if (!c) return;
   for (hipEvent_t e : c->prof_ev) (void)hipEventDestroy(e);
+  if (c->side) {   // (what it still holds is finished first; another thread's capture is not to mind)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipStreamSynchronize(c->side);
+    (void)hipStreamDestroy(c->side);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  for (hipEvent_t e : c->side_ev)
+    if (e) (void)hipEventDestroy(e);
   persist_release(c);
   delete c;
 }
@@ -978,6 +991,12 @@ int specdec_bind_model(specdec_ctx* c, specdec_role role, const specdec_model_de
       HIPCHK(c, sd::xcd_pack(S(stream), m.pl_layers, d->dec_layers, d->d_model, m.xcd_stream, m.xcd_vecs));
   }
   m.bound = true;
+  if (!c->side && other.bound && other.d.enc_layers > 0 && d->enc_layers > 0) {
+    HIPCHK(c, hipGetDevice(&c->side_dev));
+    for (hipEvent_t& e : c->side_ev)
+      if (!e) HIPCHK(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    HIPCHK(c, hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+  }
   return SPECDEC_OK;
 }
 
@@ -1018,53 +1037,76 @@ int specdec_set_memory(specdec_ctx* c, specdec_role role, const void* memory, co
 }
 
 // Encoder of one model over the sources' rows without padding (sequence b owns rows erow_start[b] ..
-// + src_len[b] - 1; grids are sized for B*S_max rows, row tiles beyond the real count return at once);
-// leaves the memory (bf16, packed) in m.exb.
-static int encoder_pass(specdec_ctx* c, Model& m, const int32_t* src, int B, int S_max, hipStream_t st) {
-  const int R = B * S_max, D = m.d.d_model, F = m.d.d_ffn, H = m.d.n_heads;
+// + src_len[b] - 1; grids are sized for B*S_max rows, row tiles beyond the real count return at once), in steps: its rows,
+// layer after layer, then the memory (bf16, packed) in m.exb and the cross-attention keys / values.
+struct EncoderRun {
+  Model* m;
+  hipStream_t st;
+  sd::LnPairs pend{nullptr, 0};   // LayerNorm folded into the projections, as in decoder_layers: m.ex holds un-normalised sums, m.exb them times the gain
+  int flip = 1, step = 0;
+  int steps() const { return m->d.enc_layers + 2; }
+};
+static int encoder_step(specdec_ctx* c, EncoderRun& run, const int32_t* src, int B, int S_max) {
+  Model& m = *run.m;
+  hipStream_t st = run.st;
+  const int R = B * S_max, D = m.d.d_model, F = m.d.d_ffn, H = m.d.n_heads, l = run.step++ - 1;
   const int* nr = m.en_rows;
-  LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::encoder_rows_embed(st, src, c->st.src_len, m.epos, m.erow_b, m.erow_start, m.en_rows, B,
-                                                           S_max, m.d.vocab, m.embed, m.pe, m.ex, m.exb, D));
-  // LayerNorm folded into the projections, as in decoder_layers: m.ex holds un-normalised sums, m.exb them times the gain
   const bool fold = !c->no_ln_fold;
-  sd::LnPairs pend{m.elnp[0], 0};
-  int flip = 1;
+  if (l < 0) {
+    run.pend = sd::LnPairs{m.elnp[0], 0};
+    LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::encoder_rows_embed(st, src, c->st.src_len, m.epos, m.erow_b, m.erow_start, m.en_rows, B,
+                                                             S_max, m.d.vocab, m.embed, m.pe, m.ex, m.exb, D));
+    return SPECDEC_OK;
+  }
+  if (l == m.d.enc_layers) {
+    const EncLayer& last = m.enc[l - 1];
+    LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, last.ln2g, last.ln2b, m.exb, R, D, nr, false));
+    m.enc_packed = true;
+    return cross_kv_from(c, m, m.exb, B, S_max, st, true);
+  }
   auto sum = [&](const bf16* A, int K, const bf16* W, const float* vecs) {
-    float* out = m.elnp[flip];
-    hipError_t e = sd::gemm_ln_sum(st, A, K, W, R, D, K, vecs, pend, m.ex, m.exb, out, nr);
-    pend = sd::LnPairs{out, sd::ln_sum_chunks(R, D)};
-    flip ^= 1;
+    float* out = m.elnp[run.flip];
+    hipError_t e = sd::gemm_ln_sum(st, A, K, W, R, D, K, vecs, run.pend, m.ex, m.exb, out, nr);
+    run.pend = sd::LnPairs{out, sd::ln_sum_chunks(R, D)};
+    run.flip ^= 1;
     return e;
   };
-  for (int l = 0; l < m.d.enc_layers; ++l) {
-    const EncLayer& L = m.enc[l];
-    const EncFolds& f = m.efolds[l];
-    if (fold) LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_ln_bf16(st, m.exb, L.wqkv, R, 3 * D, D, f.qkv, pend, m.eqkv, 3 * D, false, nr));
-    else LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_bf16(st, m.exb, D, L.wqkv, R, 3 * D, D, L.bqkv, m.eqkv, 3 * D, false, nr));
-    sd::AttnArgs a{};
-    a.q = m.eqkv; a.q_row = 3 * D;
-    a.k = m.eqkv + D; a.k_h = 64; a.k_row = 3 * D;
-    a.v = m.eqkv + 2 * D; a.v_h = 64; a.v_row = 3 * D; a.v_blocked = 0;
-    a.o = m.eatt; a.o_row = D;
-    a.q_count = c->st.src_len; a.q_off = m.erow_start; a.kv_off = m.erow_start; a.lim_row = nullptr; a.lim_seq = c->st.src_len;
-    a.T = S_max; a.H = H; a.B = B; a.cap = c->Scap;
-    LAUNCH(c, SPECDEC_KIND_ATTN, st, sd::attention(st, a));
-    if (fold) {
-      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.eatt, D, L.wo, f.vo));
-      LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_ln_bf16(st, m.exb, L.w1, R, F, D, f.w1, pend, m.ehid, F, true, nr));
-      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.ehid, F, L.w2, f.v2));
-    } else {
-      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sd::gemm_f32(st, m.eatt, D, L.wo, R, D, D, L.bo, m.ex, m.ex, D, nr));
-      LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, L.ln1g, L.ln1b, m.exb, R, D, nr));
-      LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_bf16(st, m.exb, D, L.w1, R, F, D, L.b1, m.ehid, F, true, nr));
-      LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sd::gemm_f32(st, m.ehid, F, L.w2, R, D, F, L.b2, m.ex, m.ex, D, nr));
-      if (l + 1 < m.d.enc_layers) LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, L.ln2g, L.ln2b, m.exb, R, D, nr));
-    }
+  const EncLayer& L = m.enc[l];
+  const EncFolds& f = m.efolds[l];
+  if (fold) LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_ln_bf16(st, m.exb, L.wqkv, R, 3 * D, D, f.qkv, run.pend, m.eqkv, 3 * D, false, nr));
+  else LAUNCH(c, SPECDEC_KIND_GEMM_QKV, st, sd::gemm_bf16(st, m.exb, D, L.wqkv, R, 3 * D, D, L.bqkv, m.eqkv, 3 * D, false, nr));
+  sd::AttnArgs a{};
+  a.q = m.eqkv; a.q_row = 3 * D;
+  a.k = m.eqkv + D; a.k_h = 64; a.k_row = 3 * D;
+  a.v = m.eqkv + 2 * D; a.v_h = 64; a.v_row = 3 * D; a.v_blocked = 0;
+  a.o = m.eatt; a.o_row = D;
+  a.q_count = c->st.src_len; a.q_off = m.erow_start; a.kv_off = m.erow_start; a.lim_row = nullptr; a.lim_seq = c->st.src_len;
+  a.T = S_max; a.H = H; a.B = B; a.cap = c->Scap;
+  LAUNCH(c, SPECDEC_KIND_ATTN, st, sd::attention(st, a));
+  if (fold) {
+    LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.eatt, D, L.wo, f.vo));
+    LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_ln_bf16(st, m.exb, L.w1, R, F, D, f.w1, run.pend, m.ehid, F, true, nr));
+    LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sum(m.ehid, F, L.w2, f.v2));
+  } else {
+    LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sd::gemm_f32(st, m.eatt, D, L.wo, R, D, D, L.bo, m.ex, m.ex, D, nr));
+    LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, L.ln1g, L.ln1b, m.exb, R, D, nr));
+    LAUNCH(c, SPECDEC_KIND_GEMM_BF16, st, sd::gemm_bf16(st, m.exb, D, L.w1, R, F, D, L.b1, m.ehid, F, true, nr));
+    LAUNCH(c, SPECDEC_KIND_GEMM_F32, st, sd::gemm_f32(st, m.ehid, F, L.w2, R, D, F, L.b2, m.ex, m.ex, D, nr));
+    if (l + 1 < m.d.enc_layers) LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, L.ln2g, L.ln2b, m.exb, R, D, nr));
   }
-  const EncLayer& last = m.enc[m.d.enc_layers - 1];
-  LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm(st, m.ex, last.ln2g, last.ln2b, m.exb, R, D, nr, false));
-  m.enc_packed = true;
   return SPECDEC_OK;
+}
+
+// The encoders of the two models do not meet, and the launches of either leave compute units without work (a last round of tiles,
+// epilogues that wait for memory, launches of few rows): they run beside each other, the drafter's on a stream of the context that starts
+// behind what the caller's holds and that the caller's waits for.  Encoding with a big / base verifier and the drafter, one after the other / so,
+// us: one source of 30 tokens 698 / 561, 531 / 456; 16 of 16 .. 128 1441 / 1077, 986 / 803; 128 of 16 .. 128 3871 / 3317, 2532 / 2195; 12 of
+// 500 .. 1000 4255 / 3737, 2865 / 2516; 32 of 1024 level.  Not where the caller's stream has not all compute units (this one has), where
+// launches are timed, or on another GPU.
+static bool encoders_apart(const specdec_ctx* c, hipStream_t st) {
+  int dev = -1, cus = 0;
+  return c->side && c->prof_kind == SPECDEC_KIND_NONE && hipGetDevice(&dev) == hipSuccess && dev == c->side_dev &&
+         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && stream_cus(st) >= cus;
 }
 
 int specdec_encode(specdec_ctx* c, const int32_t* src, const int32_t* src_len, int32_t S_max, void* stream) {
@@ -1079,15 +1121,27 @@ int specdec_encode(specdec_ctx* c, const int32_t* src, const int32_t* src_len, i
   hipStream_t st = S(stream);
   HIPCHK(c, sd::set_src_len(st, c->st, src_len, c->B, S_max));
   c->S_cur = S_max;
-  for (int r = 0; r < 2; ++r) {
-    Model& m = c->m[r];
-    if (!m.bound || m.d.enc_layers == 0) continue;
-    int rc = encoder_pass(c, m, src, c->B, S_max, st);
-    if (rc) return rc;
-    rc = cross_kv_from(c, m, m.exb, c->B, S_max, st, true);
-    if (rc) return rc;
+  const bool apart = n == 2 && encoders_apart(c, st);
+  std::vector<EncoderRun> runs;
+  for (int r = 0; r < 2; ++r)
+    if (c->m[r].bound && c->m[r].d.enc_layers > 0) runs.push_back(EncoderRun{&c->m[r], apart && r == SPECDEC_DRAFTER ? c->side : st});
+  if (apart) {
+    HIPCHK(c, hipEventRecord(c->side_ev[0], st));
+    HIPCHK(c, hipStreamWaitEvent(c->side, c->side_ev[0], 0));
   }
-  return SPECDEC_OK;
+  int rc = SPECDEC_OK;
+  while (!rc) {   // launched in turn, the one that is less far; or one after the other
+    EncoderRun* next = nullptr;
+    for (EncoderRun& run : runs)
+      if (run.step < run.steps() && (!next || (apart && run.step * next->steps() < next->step * run.steps()))) next = &run;
+    if (!next) break;
+    rc = encoder_step(c, *next, src, c->B, S_max);
+  }
+  if (apart) {   // (whatever became of it)
+    HIPCHK(c, hipEventRecord(c->side_ev[1], c->side));
+    HIPCHK(c, hipStreamWaitEvent(st, c->side_ev[1], 0));
+  }
+  return rc;
 }
 
 // tokens: set_stream in the same launch (null: not)
