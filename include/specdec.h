@@ -71,7 +71,7 @@ enum { SPECDEC_COUNTERS = 8 };  /* int32 words reported by specdec_get_counters 
 /* Kernel-path switches of a context (specdec_configure), value 0 or 1. */
 typedef enum {
   SPECDEC_OPT_SMALL_BATCH_KERNELS = 0, /* default 1: passes of few rows run their decoder layers as one kernel where that applies
-                                          (specdec_verify, specdec_draft); else, verification passes
+                                          (specdec_verify, specdec_draft, specdec_prefill); else, verification passes
                                           of at most 32 rows, one sequence of at most 12 rows with d_model <= 512 (and every such pass with LN_FOLD = 0) on the fused small-batch
                                           kernels, others on the general ones; at most 32 rows: the small-batch
                                           vocabulary kernel.  0: none of these                                       */
@@ -198,7 +198,10 @@ int specdec_set_prefix(specdec_ctx* ctx, specdec_role role, const int32_t* token
 
 /* Cache the keys/values of every stream token a model has not cached yet (u_0..u_{j-1} for
  * the verifier, u_0..u_j for the drafter) with causal decoder passes, as few as the workspace's
- * activation buffers allow.  Needed after specdec_set_stream unless a cache is loaded. */
+ * activation buffers allow.  Needed after specdec_set_stream unless a cache is loaded.  With
+ * d_model 512 / d_ffn 2048 passes of few rows (of a group at most 112, 80 of up to three sequences)
+ * run as one kernel, under the rules of specdec_verify; should its second run not complete either,
+ * nothing counts as cached. */
 int specdec_prefill(specdec_ctx* ctx, specdec_role role, void* stream);
 
 /* ---- the hot path -------------------------------------------------------------------- */

@@ -2,6 +2,7 @@
 // of every entry point declared in include/specdec.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstddef>
@@ -299,8 +300,10 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   t.xv = cv.take<bf16>(t.xkv_layer * d->dec_layers);
   t.x = cv.take<float>(Rpass * D);
   t.x2 = cv.take<float>(32 * D);
+  // (places of a sequence in its passes: at d = 512 the drafter's and prefill's too)
+  const int xcd_T = D == 512 ? std::max(c->Tmax, std::min(c->lim.max_tgt + 1, sd::xcd_group_rows_most(512))) : c->lim.k_max + 1;
   t.xcd_rows = sd::persist_supported(d->dec_layers, (int)D, (int)F) &&
-                       sd::xcd_rows_most((int)Bm, D == 512 ? c->Tmax : c->lim.k_max + 1, (int)D) > 512 ? 8 * sd::xcd_group_rows_most((int)D) : 512;
+                       sd::xcd_rows_most((int)Bm, xcd_T, (int)D) > 512 ? 8 * sd::xcd_group_rows_most((int)D) : 512;
   t.skp = cv.take<float>((size_t)2 * t.xcd_rows * D);   // (or the one-kernel decoder's sum and its residual)
   static_assert(2 * sd::kSk2MaxParts * 32 <= 2 * 512 && persist_rows(512) <= 512 && persist_rows(1024) <= 512, "both fit");
   t.hx = cv.take<float>(Bm * (size_t)c->lim.k_max * D);
@@ -343,7 +346,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     // drafter's workspace has the place for the copy of the weights, which it does not use, and a verifier's buffers that a drafter's rows need.)
     const bool per_xcd = sd::xcd_copy_rows_most((int)Bm, c->lim.k_max + 1, (int)D) > (D == 512 ? sd::kXcdFewRows : (int)persist_rows((int)D));
     const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F);
-    const size_t xcd = D == 512 ? sd::xcd_exch_most((int)Bm, c->Tmax, (int)D, (int)F) : per_xcd ? sd::xcd_exch_most((int)Bm, c->lim.k_max + 1, (int)D, (int)F) : 0;
+    const size_t xcd = D == 512 || per_xcd ? sd::xcd_exch_most((int)Bm, xcd_T, (int)D, (int)F) : 0;
     t.pl_exch = cv.take<char>(one > xcd ? one : xcd);
     if (per_xcd) t.xcd_stream = cv.take<char>(sd::xcd_stream_bytes(d->dec_layers, (int)D, (int)F));   // (few rows of 512: without it)
     if (per_xcd || D == 512) t.xcd_vecs = cv.take<float>(sd::xcd_vec_bytes(d->dec_layers, (int)D) / sizeof(float));
@@ -653,6 +656,16 @@ Way draft_way(const Model& m, int B, int fresh, int k, int cus) {
   return xcd && x.RP <= (fresh > 1 ? 128 : 144) ? Way::xcd_few : Way::launches;
 }
 
+// The same for a prefill pass of at most T rows a sequence.  Prefill and a verification pass of 6 rows a sequence, base verifier, launches / this one for the
+// prefill, us: 1 x 5 rows 283 / 204, 1 x 50 295 / 254, 1 x 100 321 / 328, 1 x 150 332 / 436; 4 x 100 374 / 348, of 0 .. 100 362 / 344; 8 x 20 344 /
+// 244, 8 x 100 421 / 354, of 0 .. 100 398 / 350, 8 x 150 475 / 465, of 0 .. 150 446 / 458; 16 x 50 410 / 355; 64 x 20 534 / 512, of 0 .. 20 508 / 511.
+Way prefill_way(const Model& m, int B, int T, int cus) {
+  sd::XcdArgs x{};
+  x.R = B * T; x.T = T; x.B = B; x.H = m.d.n_heads;
+  const bool xcd = m.d.d_model == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && x.R <= m.xcd_rows && sd::xcd_plan(x, 512, m.d.d_ffn) > 0;
+  return xcd && x.RP <= (B < 4 ? 80 : 112) ? Way::xcd_few : Way::launches;
+}
+
 // Whether the pass takes one of them (way: which); way_of(cus): the way it takes with as many compute units.
 template <class F>
 bool persist_ok(specdec_ctx* c, const Model& m, hipStream_t st, F way_of, Way* way) {
@@ -702,14 +715,15 @@ size_t persist_clear(Way way, const Model& m, int B, int T) {
   return sd::xcd_plan(a, m.d.d_model, m.d.d_ffn);
 }
 
-// few: as in decoder_layers (the E4M3 copies of the weights, if the model has them)
-int decoder_layers_persist(specdec_ctx* c, Model& m, Way way, int B, int T, bool few, bool drafter, hipStream_t st) {
+// few: as in decoder_layers (the E4M3 copies of the weights, if the model has them).  stream: rows of assemble_embed_stream; kv_only: as there.
+int decoder_layers_persist(specdec_ctx* c, Model& m, Way way, int B, int T, bool few, bool stream, bool kv_only, hipStream_t st) {
   if (way != Way::gpu) {
     sd::XcdArgs a{};
     a.R = B * T; a.T = T; a.B = B; a.H = m.d.n_heads; a.Lcap = c->Lcap; a.Scap = c->Scap; a.n_layers = m.d.dec_layers;
     a.layers = m.pl_layers; a.stream = way == Way::xcd ? m.xcd_stream : nullptr; a.vecs = m.xcd_vecs;
     a.row_b = m.rm.row_b; a.row_pos = m.rm.row_pos; a.src_len = c->st.src_len;
-    if (drafter) { a.causal = m.new_rows; a.live = m.rm.seq_rows; }
+    if (stream) { a.causal = m.new_rows; a.live = m.rm.seq_rows; }
+    a.kv_only = kv_only;
     a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + (size_t)m.xcd_rows * m.d.d_model;
     a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
     if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
@@ -1221,11 +1235,14 @@ int specdec_prefill(specdec_ctx* c, specdec_role role, void* stream) {
   const int most = (int)(c->pass_rows / c->B), passes = (c->uncached_ub[role] + most - 1) / most;
   const int T = passes > 0 ? (c->uncached_ub[role] + passes - 1) / passes : 0;
   while (c->uncached_ub[role] > 0) {
+    Way way;
+    const bool one = persist_ok(c, m, st, [&](int cus) { return prefill_way(m, c->B, T, cus); }, &way);
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_stream(st, c->st, m.rm, role, c->B, T, 0, m.d.mask_id, m.d.pad_id, m.d.vocab,
-                                        m.new_rows, m.embed, m.pe, m.x, m.xb, m.d.d_model, packed));
-    rc = decoder_layers(c, m, c->B, T, st, true, 0, packed, true);
+                                        m.new_rows, m.embed, m.pe, m.x, m.xb, m.d.d_model, packed && !one, one ? m.pl_exch : nullptr,
+                                        one ? persist_clear(way, m, c->B, T) : 0));
+    rc = one ? decoder_layers_persist(c, m, way, c->B, T, false, true, true, st) : decoder_layers(c, m, c->B, T, st, true, 0, packed, true);
     if (rc) return rc;
-    HIPCHK(c, sd::advance_cached(st, c->st, role, m.new_rows, c->B));
+    HIPCHK(c, sd::advance_cached(st, c->st, role, m.new_rows, c->B, one ? persist_flags(way, m) + 1 : nullptr));
     c->uncached_ub[role] -= T;
   }
   c->uncached_ub[role] = 0;
@@ -1259,7 +1276,7 @@ int specdec_draft(specdec_ctx* c, int32_t k, int32_t* draft, float* logits, void
                                       m.d.vocab, m.new_rows, m.embed, m.pe, m.x, m.xb, m.d.d_model, packed, one ? m.pl_exch : nullptr,
                                       one ? persist_clear(way, m, B, T) : 0));
   const unsigned* failed = one ? persist_flags(way, m) + 1 : nullptr;
-  rc = one ? decoder_layers_persist(c, m, way, B, T, false, true, st) : decoder_layers(c, m, B, T, st, true, k, packed);
+  rc = one ? decoder_layers_persist(c, m, way, B, T, false, true, false, st) : decoder_layers(c, m, B, T, st, true, k, packed);
   if (rc) return rc;
   if (one)
     LAUNCH(c, SPECDEC_KIND_LN, st, sd::layer_norm_slots(st, m.skp, m.dec.back().ln3g, m.dec.back().ln3b, m.slots, m.new_rows, nullptr, B, T, k, m.d.d_model));
@@ -1337,7 +1354,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   if (small) {
     sd::SkSrc fin{};
     if (!fused) {
-      rc = one ? decoder_layers_persist(c, m, c->way, B, T, true, false, st) : decoder_layers(c, m, B, T, st, true, 0, false, false, true);
+      rc = one ? decoder_layers_persist(c, m, c->way, B, T, true, false, false, st) : decoder_layers(c, m, B, T, st, true, 0, false, false, true);
       fin = sd::SkSrc{2, sums, m.dec.back().ln3g, m.dec.back().ln3b, nullptr, nullptr, nullptr, nullptr};
     } else if (c->sliced && sd::sk2_supported(m.d.d_model, m.d.d_ffn) && m.d.n_heads <= sd::kSk2MaxParts)
       rc = decoder_layers_sliced(c, m, B, T, st, &fin);
@@ -1348,7 +1365,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
     c->fin_x = c->resident ? nullptr : fin.xs; c->fin_g = fin.g; c->fin_b = fin.b;
   } else {
     if (one) {
-      rc = decoder_layers_persist(c, m, c->way, B, T, false, false, st);
+      rc = decoder_layers_persist(c, m, c->way, B, T, false, false, false, st);
       if (rc) return rc;
     } else {
       rc = decoder_layers(c, m, B, T, st, true, 0, false, false, false, true);

@@ -275,6 +275,7 @@ struct XcdArgs {
   const int *row_b, *row_pos, *src_len;
   const int *causal, *live;               // [B] a drafter's pass: of the T rows of a sequence, the first that see the keys up to their own, and all
                                           // that there are (those between see all keys); null: T of either
+  int kv_only;                            // (with causal) ends where the last layer's keys and values are stored
   const float* x;
   const bf16* xb;
   float* y;
@@ -360,7 +361,8 @@ hipError_t assemble_embed_verify(hipStream_t st, const SeqState& s, const RowMap
 hipError_t assemble_embed_stream(hipStream_t st, const SeqState& s, const RowMap& rm, int role, int B, int T,
                                  int n_mask, int mask_id, int pad_id, int V, int* new_rows, const bf16* E,
                                  const float* pe, float* x, bf16* xb, int d, bool packed, void* clear = nullptr, size_t clear_bytes = 0);
-hipError_t advance_cached(hipStream_t st, const SeqState& s, int role, const int* new_rows, int B);
+// (fail: optional device flag; where it is set nothing counts as cached)
+hipError_t advance_cached(hipStream_t st, const SeqState& s, int role, const int* new_rows, int B, const unsigned* fail = nullptr);
 hipError_t gather_slots(hipStream_t st, const bf16* xb, bf16* dst, const int* new_rows, const int* row_start, int B,
                         int T, int k, int d);
 // Encoder rows without padding: sequence b owns rows row_start[b] .. + src_len[b] - 1 (running sum, batch order; row_start

@@ -337,12 +337,12 @@ hipError_t assemble_embed_stream(hipStream_t st, const SeqState& s, const RowMap
   return hipGetLastError();
 }
 
-__global__ void advance_cached_kernel(SeqState s, int role, const int* __restrict__ new_rows, int B) {
+__global__ void advance_cached_kernel(SeqState s, int role, const int* __restrict__ new_rows, int B, const unsigned* __restrict__ fail) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < B) s.cached[role][b] += new_rows[b];
+  if (b < B && !(fail && *fail != 0u)) s.cached[role][b] += new_rows[b];
 }
-hipError_t advance_cached(hipStream_t st, const SeqState& s, int role, const int* new_rows, int B) {
-  hipLaunchKernelGGL(advance_cached_kernel, blocks_for(B, 64), dim3(64), 0, st, s, role, new_rows, B);
+hipError_t advance_cached(hipStream_t st, const SeqState& s, int role, const int* new_rows, int B, const unsigned* fail) {
+  hipLaunchKernelGGL(advance_cached_kernel, blocks_for(B, 64), dim3(64), 0, st, s, role, new_rows, B, fail);
   return hipGetLastError();
 }
 

@@ -32,6 +32,8 @@
 // 11 441 / 436 (eleven tiles, 128 x 11: 471 / 496), on 250 source tokens 128 x 9 565 / 483; d = 1024: 48 x 11 560 / 506, 64 x 11 589 / 555, on 512
 // source tokens 753 / 724; drafting 48 x 11 133 / 105, 64 x 11 150 / 126, 80 x 11 157 / 141.
 //
+// A prefill pass is one of these as well (all of its rows see the keys up to their own); it ends where the last layer's keys and values are stored.
+//
 // What bounds it: a hand-over and instructions in a row at every stage (of 11 rows 0.8 - 3.5 us, of 44 1.8 - 3.9), and with the weights of d =
 // 1024 what an XCD takes in.  Whole verify passes, launches / this kernel, us: d = 512: 6 rows 200 / 109, 77 239 / 121, 176 255 / 140, 352
 // 287 / 168; d = 1024: 6 rows 252 / 217, 128 366 / 335, 176 358 / 317, 352 462 / 363.  (Which passes it takes, and what the kernel over the whole GPU
@@ -1120,10 +1122,15 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     wait_vmcnt<Dim::kAskFirst * Dim::kReq>();   // the vectors
     __syncthreads();
     for (int l = 0; l < a.n_layers; ++l) {
-      stage(0, l); stage(1, l); stage(2, l); stage(3, l); stage(4, l); stage(5, l); stage(6, l); stage(7, l);
+      stage(0, l);
+      if (SLOTS && a.kv_only && l + 1 == a.n_layers) {
+        wait_vmcnt<0>();   // (weights on their way to LDS, as in pl_again)
+        return;
+      }
+      stage(1, l); stage(2, l); stage(3, l); stage(4, l); stage(5, l); stage(6, l); stage(7, l);
     }
   } else {
-    const int per = a.G * kPlMembers, total = a.n_layers * kPlStages * per;   // tickets of a stage; of the pass: below 2^17
+    const int per = a.G * kPlMembers, total = (a.n_layers * kPlStages - (a.kv_only ? kPlStages - 1 : 0)) * per;   // tickets of a stage; of the pass: below 2^17
     int st = -1, group = -1;
     while (true) {
       // (In one block: see persist.hip)
