@@ -288,6 +288,7 @@ struct XcdArgs {
   unsigned* err;                          // [2], zero at first and kept from pass to pass: waits were given up (passes yet to
                                           // be computed another way); those of that way too (results are void)
   int RP, d, G, wpu;                      // filled by the launcher, as what follows
+  bool form;                              // units of cross-attention form their queries
   bool copy;                              // few enough rows to a group for the kernels that stream the copy
   unsigned* raised;
   PlTickets* tickets;

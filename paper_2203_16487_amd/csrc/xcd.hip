@@ -38,15 +38,29 @@ __global__ __launch_bounds__(256) void pl_pack_vectors_kernel(const PlLayer* __r
   for (int k = 0; k < 3; ++k)
     for (int i = 0; i < 3; ++i) put(sums[k] + i * D, Dim::kND);
 }
+// The cross-attention's query matrix as operands of its 16-column tiles (PlOwnQueries): [layer][tile][wave], a chunk each.  One block a chunk.
+template <int D>
+__global__ __launch_bounds__(64) void pl_pack_queries_kernel(const PlLayer* __restrict__ layers, char* __restrict__ out) {
+  typedef PlDim<D> Dim;
+  const int chunk = blockIdx.x, wave = chunk % kPlWaves, tile = chunk / kPlWaves % (D / 16), l = chunk / (kPlWaves * (D / 16)), lane = threadIdx.x;
+  const bf16* src = static_cast<const bf16*>(layers[l].cwq.p) + (size_t)(tile * 16 + (lane & 15)) * D + wave * Dim::KW + 8 * (lane >> 4);
+#pragma unroll
+  for (int u = 0; u < Dim::KS; ++u)
+    *reinterpret_cast<bf16x8*>(out + (size_t)chunk * Dim::kChunk + u * 1024 + lane * 16) = *reinterpret_cast<const bf16x8*>(src + u * 32);
+}
 }  // namespace xcd
 size_t xcd_stream_bytes(int layers, int d, int F) { return (size_t)layers * (6 * (size_t)d * d + 2 * (size_t)d * F) * sizeof(bf16); }
 size_t xcd_vec_bytes(int layers, int d) {
-  return (size_t)layers * xcd::kPlMembers * (d == 512 ? xcd::PlDim<512>::kVecPitch : xcd::PlDim<1024>::kVecPitch) * sizeof(float);
+  return (size_t)layers * xcd::kPlMembers * (d == 512 ? xcd::PlDim<512>::kVecPitch : xcd::PlDim<1024>::kVecPitch) * sizeof(float) +
+         (d == 512 ? (size_t)layers * d * d * sizeof(bf16) : 0);   // (the query matrix, see PlOwnQueries)
 }
 template <int D>
 static hipError_t pack(hipStream_t st, const PlLayer* layers, int n, char* stream, float* vecs) {
   if (stream) hipLaunchKernelGGL(xcd::pl_pack_kernel<D>, dim3(xcd::kPlMembers * xcd::kPlWaves * n * xcd::PlDim<D>::kPerLayer), dim3(64), 0, st, layers, n, stream);
   hipLaunchKernelGGL(xcd::pl_pack_vectors_kernel<D>, dim3(n * xcd::kPlMembers), dim3(256), 0, st, layers, vecs);
+  if constexpr (D == 512)
+    hipLaunchKernelGGL(xcd::pl_pack_queries_kernel<D>, dim3(n * (D / 16) * xcd::kPlWaves), dim3(64), 0, st, layers,
+                       reinterpret_cast<char*>(vecs + (size_t)n * xcd::kPlMembers * xcd::PlDim<D>::kVecPitch));
   return hipGetLastError();
 }
 // (stream null: column vectors alone)
@@ -92,6 +106,7 @@ size_t xcd_plan(XcdArgs& a, int d, int F) {
   const int units = (a.B + a.G - 1) / a.G * a.H * ((a.T + 15) >> 4);
   a.wpu = xcd::kPlWaves;
   while (a.wpu > 1 && units > xcd::kPlMembers * (xcd::kPlWaves / a.wpu)) a.wpu >>= 1;
+  a.form = 2 * units <= xcd::kPlMembers;
   return xcd::pl_exch_bytes(a.B, a.RP, d, F, a.RP > xcd::kPlRows ? 1 : 2);
 }
 hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F, bool give_up) {

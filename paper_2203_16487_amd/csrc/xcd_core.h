@@ -147,6 +147,9 @@ struct PlLds {
   int row_at[16 * MR];                            // of the row in the self-attention cache of head 0 (< 0: none)
   int drawn;                                      // (TICKETS)
   __device__ __forceinline__ bf16* vs(int wave) { return reinterpret_cast<bf16*>(red + wave * 256); }
+  // Where units of attention can form their queries (see PlOwnQueries): these, behind the first 32 KB of red.
+  static constexpr bool kForm = D == 512 && MR <= 2;
+  __device__ __forceinline__ bf16* queries() { static_assert(!kForm || kRedTiles == 8, "64 KB"); return reinterpret_cast<bf16*>(red + 2048); }
 };
 
 // A workgroup's place: group g carries sequences b0 .. b0 + nb - 1, rows row0 .. row0 + rows - 1 of the pass.
@@ -440,27 +443,38 @@ struct PlRows {
       const LateStats late{*this, pl_buf(stats), st};
       late.request();
       arrive(af, late);
-#pragma unroll
-      for (int mr = 0; mr < MR; ++mr) {
-        f32x2 p[NS];
-        float s = 0.f, q = 0.f;
-#pragma unroll
-        for (int i = 0; i < NS; ++i) {
-          p[i] = __builtin_bit_cast(f32x2, st[mr][i]);
-          s += p[i][0];
-        }
-        s = pl_row_sum(s);
-#pragma unroll
-        for (int i = 0; i < NS; ++i) {
-          const float dv = (p[i][0] - s * (16.f / KW)) * (1.f / 16);
-          q += __builtin_fmaf(16.f * dv, dv, p[i][1]);
-        }
-        q = pl_row_sum(q);
-        if (g == 0) *reinterpret_cast<f32x2*>(part + 2 * (16 * mr + lq)) = f32x2{s, q};
-      }
+      merge(st, lq, g, part);
     } else {
       arrive(af);
     }
+  }
+  static __device__ __forceinline__ void merge(const u32x2 (&st)[MR][NS], int lq, int g, float* part) {
+#pragma unroll
+    for (int mr = 0; mr < MR; ++mr) {
+      f32x2 p[NS];
+      float s = 0.f, q = 0.f;
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        p[i] = __builtin_bit_cast(f32x2, st[mr][i]);
+        s += p[i][0];
+      }
+      s = pl_row_sum(s);
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        const float dv = (p[i][0] - s * (16.f / KW)) * (1.f / 16);
+        q += __builtin_fmaf(16.f * dv, dv, p[i][1]);
+      }
+      q = pl_row_sum(q);
+      if (g == 0) *reinterpret_cast<f32x2*>(part + 2 * (16 * mr + lq)) = f32x2{s, q};
+    }
+  }
+  // The statistics alone.
+  __device__ __forceinline__ void statistics(const char* stats, float* part) const {
+    u32x2 st[MR][NS];
+    const LateStats late{*this, pl_buf(stats), st};
+    late.request();
+    for (unsigned spins = 0; late.missing(); late.request()) pl_again(spins, a);
+    merge(st, lane & 15, lane >> 4, part);
   }
 };
 // {rstd, -mean rstd} of row 16 mr + lq from the waves' pairs, two of them a lane of the row's four
@@ -671,14 +685,86 @@ __device__ __forceinline__ void pl_sum(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
   }
 }
 
+// The queries of a workgroup's unit of cross-attention, formed by the workgroup itself: a product of a head's 64 columns in place of a stage
+// of its own and its hand-over, where the units of self-attention and of cross-attention have workgroups of their own (PlPlace::w from below
+// and from above).  The weights and the first chunk of keys and values are requested while the others are at self-attention and held until the
+// rows are there; the queries pass through LDS.  Same products, sums and statistics as in that stage: the same bits.
+template <int D>
+struct PlOwnQueries {
+  typedef PlDim<D> Dim;
+  static constexpr int kPitch = 72;   // (16 rows of 144 bytes: a 16-byte read of every row meets all banks once)
+  bf16x8 wf[4][Dim::KS];
+  f32x4 c, b;
+  PlChunk chunk;
+  __device__ __forceinline__ void request(const XcdArgs& a, PlLayerPtr Y, int l, int h, int lane, int wave) {
+    const int g = lane >> 4;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const int tile = h * 4 + f;
+      // (operands in order, from a copy of this matrix behind the column vectors.  As bound, half of each of 16 lines a request: 6 rows 112.7 us,
+      // so 108.8.)
+      const char* p = reinterpret_cast<const char*>(a.vecs) + ((size_t)a.n_layers * kPlMembers * Dim::kVecPitch * 4 + ((size_t)(l * (D / 16) + tile) * kPlWaves + wave) * Dim::kChunk);
+#pragma unroll
+      for (int u = 0; u < Dim::KS; ++u) wf[f][u] = *reinterpret_cast<const bf16x8*>(p + lane * 16 + u * 1024);
+    }
+    const int n = h * kHeadDim + (wave & 3) * 16 + 4 * g;   // (the first four waves' column tiles)
+    c = *reinterpret_cast<const f32x4*>(Y->cq_cs + n);
+    b = *reinterpret_cast<const f32x4*>(Y->cq_bf + n);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // the unit's queries as operands f
+  template <int MR>
+  __device__ __forceinline__ void form(const XcdArgs& a, PlLds<D, MR>& L, const PlExch& ex, const PlUnit& t, int lane, int wave, u32x4 (&f)[2]) const {
+    const int lq = lane & 15, g = lane >> 4, row0 = t.b * a.T + t.q0;
+    u32x4 af[1][Dim::KS];
+    PlRows<D, 1>(a, ex.xg(0) + row0 * 32, false, min(16, a.T - t.q0), lane, wave).first(af, ex.st(0) + row0 * 8, L.part[wave]);
+    f32x4* red = L.red;
+    bf16* q = L.queries();
+    f32x4 acc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < Dim::KS; ++u)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i][u], __builtin_bit_cast(bf16x8, af[0][u]), acc[i], 0, 0, 0);
+    }
+    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc[3]));   // (the last of the products; see mfma_settle)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      asm volatile("" : "+v"(acc[i]));   // (not ahead of it)
+      red[(i * kPlWaves + wave) * 64 + lane] = acc[i];
+    }
+    lds_barrier();
+    if (wave < 4) {
+      f32x4 p[kPlWaves];
+#pragma unroll
+      for (int w = 0; w < kPlWaves; ++w) p[w] = red[(wave * kPlWaves + w) * 64 + lane];
+      const f32x2 st = pl_row_stat<D>(&L.part[0][0], 2 * 16 * MR, lq, g);
+      float o[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float v = p[0][e];
+#pragma unroll
+        for (int w = 1; w < kPlWaves; ++w) v += p[w][e];
+        o[e] = __builtin_fmaf(v, st[0], __builtin_fmaf(st[1], c[e], b[e]));
+      }
+      *reinterpret_cast<u32x2*>(q + lq * kPitch + wave * 16 + 4 * g) = pl_pack4(o);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) f[i] = *reinterpret_cast<const u32x4*>(q + lq * kPitch + i * 32 + 8 * g);
+  }
+};
 // Key chunks kw, kw + kstep, ... of 32 on this wave (see attn_core.h for the operand layouts).  SELF: keys / values below the
 // pass's first row come from the cache, the pass's own from the exchange buffers (waited for); else the cross-attention arenas.
 // KV8 (cross): codes with one fp32 scale per key and per value, as in attn_core.h.
 // SLOTS: of the a.T row places of a sequence the first `live` hold rows of the pass; the first `causal` of them see the keys up to their own,
 // the others (a drafter's slots) all keys.  Places beyond see none, and nobody reads what becomes of them.  (Else all see the keys up to their own.)
-template <bool SELF, bool KV8, bool SLOTS>
+// PHASE 1: requests the first chunk of cross-attention alone; 2: that chunk and the queries f are there.
+template <bool SELF, bool KV8, bool SLOTS, int PHASE>
 __device__ __forceinline__ void pl_attn_wave(const XcdArgs& a, const PlExch& ex, int l, int b0, const PlUnit& t, int causal, int live, int kw, int kstep,
-                                             bf16* Vs, float& mrun, float& lrun, f32x4 (&oacc)[4]) {
+                                             bf16* Vs, PlChunk& now, u32x4 (&f)[2], float& mrun, float& lrun, f32x4 (&oacc)[4]) {
   const int lane = pl_lane(), lq = lane & 15, g = lane >> 4;
   const int r0 = t.b * a.T;                                // first row of the sequence, in the group
   const int j = t.j, nkey = t.nkey;
@@ -694,8 +780,7 @@ __device__ __forceinline__ void pl_attn_wave(const XcdArgs& a, const PlExch& ex,
   for (int et = 0; et < 4; ++et) oacc[et] = f32x4{0.f, 0.f, 0.f, 0.f};
   // K operands: tile i, row lq  <->  key c0 + 8*(lq/4) + 4*i + lq%4; values as whole rows (lane -> row 8*i + lane/8, dims
   // 8*(lane%8) .. + 7) or, key-blocked, as operands.  A chunk without rows of the pass is requested ahead.
-  PlChunk now, next;
-  u32x4 f[2];
+  PlChunk next;
   auto key_k = [&](int c0, int i) { return c0 + 8 * (lq >> 2) + 4 * i + (lq & 3); };
   auto key_v = [&](int c0, int i) { return c0 + 8 * i + (lane >> 3); };
   auto fetch = [&](int c0, PlChunk& t) {
@@ -771,9 +856,15 @@ __device__ __forceinline__ void pl_attn_wave(const XcdArgs& a, const PlExch& ex,
       for (int e = 0; e < 4; ++e) t_.vf[i][e] = key_v(c0, i) >= nkey ? 0u : t_.vf[i][e];
   };
   const int cfirst = kw * 32;
+  if (PHASE == 1) {
+    fetch(cfirst, now);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    return;
+  }
   if (SELF && cfirst + 32 > j) {
     own(cfirst, now);
-  } else {
+  } else if (PHASE == 0) {
     fetch(cfirst, now);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -885,14 +976,15 @@ __device__ __forceinline__ PlPair pl_pair(const XcdArgs& a, const PlPlace& p, in
   return PlPair{__builtin_amdgcn_readfirstlane(b), __builtin_amdgcn_readfirstlane(pair - b * a.H), __builtin_amdgcn_readfirstlane((u - pair * tiles) * 16)};
 }
 // mine: the unit of the first round (there is seldom another)
-template <bool SELF, bool KV8, bool SLOTS, int D, int MR>
+// FORM: the units' queries may be formed here (form: they are, and units come from above); own: what is held of it
+template <bool SELF, bool KV8, bool SLOTS, bool FORM, int D, int MR>
 __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex, int l, const PlPlace& at, const PlPair& mine, int units, int rounds, PlLds<D, MR>& L,
-                                             PlTurn& turn) {
+                                             PlTurn& turn, bool form, PlOwnQueries<D>& own) {
   const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
   char* out = ex.att(SELF ? 0 : 1);
   const int wpu = a.wpu, per = kPlWaves / wpu, kw = wave & (wpu - 1);   // waves of a unit, units at a time
   for (int r = 0; r < rounds; ++r) {
-    const int u = (r * kPlMembers + at.w) * per + wave / wpu;
+    const int u = FORM && form ? kPlMembers - 1 - at.w : (r * kPlMembers + at.w) * per + wave / wpu;
     const PlPair pair = r == 0 ? mine : pl_pair(a, at, r, wave);
     PlUnit t;
     t.b = pair.b; t.h = pair.h; t.q0 = pair.q0;
@@ -911,7 +1003,15 @@ __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex,
       if (t.q0 + lq < a.T) pl_store8(out + pl_at(a.RP, t.b * a.T + t.q0 + lq, t.h * kHeadDim + et * 16 + 4 * g), p[0], p[1]);
     };
     lds_barrier();   // the latest product's partial tiles, or the units' before, are done with
-    if (kw < used) pl_attn_wave<SELF, KV8, SLOTS>(a, ex, l, at.b0, t, causal, live, kw, wpu, L.vs(wave), mrun, lrun, oacc);
+    if (FORM && form) {   // (every wave takes part in forming the queries)
+      u32x4 f[2];
+      if (used > 0) own.form(a, L, ex, t, lane, wave, f);
+      if (kw < used) pl_attn_wave<SELF, KV8, SLOTS, FORM ? 2 : 0>(a, ex, l, at.b0, t, causal, live, kw, wpu, L.vs(wave), own.chunk, f, mrun, lrun, oacc);
+    } else if (kw < used) {
+      PlChunk chunk;
+      u32x4 f[2];
+      pl_attn_wave<SELF, KV8, SLOTS, 0>(a, ex, l, at.b0, t, causal, live, kw, wpu, L.vs(wave), chunk, f, mrun, lrun, oacc);
+    }
     if (used == 1 && kw == 0) {   // nothing to merge
       const float inv = lrun > 0.f ? 1.f / lrun : 0.f;
 #pragma unroll
@@ -1013,6 +1113,10 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
   PlTurn turn = pl_turn<D>(a, at.w, wave, 0, 0, a.n_layers * Dim::kPerLayer);
   int units = pl_units(a, at), rounds = pl_rounds(a, at);
   PlPair mine = pl_pair(a, at, 0, wave);
+  PlPlace from_above = at;
+  from_above.w = kPlMembers - 1 - at.w;
+  const PlPair above = pl_pair(a, from_above, 0, wave);
+  PlOwnQueries<D> own;
   // stage s of layer l
   auto stage = [&](int s, int l) __attribute__((always_inline)) {
     // What follows from the layer is worked out where it is used.  Ahead of the layer's stages, where the compiler would have it, it does not fit
@@ -1031,8 +1135,25 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     const PlExch before(a.exch + (kHalf ? (~l & 1) * a.G + at.g : at.g * 2 + (~l & 1)) * pl_layer_bytes(a.RP, D, 4 * D), a.RP, D);
     const float* vec = L.vec[l & 1];
     float* stat = L.stat[(3 * l + s / 3) & 1];
-    if (s == 1) return pl_attention<true, false, SLOTS>(a, ex, l, at, mine, units, rounds, L, turn);
-    if (s == 4) return pl_attention<false, KV8, SLOTS>(a, ex, l, at, mine, units, rounds, L, turn);
+    // (see PlOwnQueries)
+    constexpr bool FORM = !TICKETS && Lds::kForm;
+    const bool form = FORM && a.form;
+    if (s == 1) {
+      pl_attention<true, false, SLOTS, false>(a, ex, l, at, mine, units, rounds, L, turn, false, own);
+      if (FORM && form && kPlMembers - 1 - at.w < units) {
+        const int lane = pl_lane();
+        PlUnit t;
+        t.b = above.b; t.h = above.h; t.q0 = above.q0; t.j = 0;
+        t.nkey = __builtin_amdgcn_readfirstlane(L.seq[t.b].src_len);
+        own.request(a, pl_layer(a, l), l, above.h, lane, wave);
+        float m;
+        f32x4 o[4];
+        u32x4 f[2];
+        if (wave * 32 < t.nkey) pl_attn_wave<false, KV8, SLOTS, 1>(a, ex, l, at.b0, t, 0, 0, wave, kPlWaves, L.vs(wave), own.chunk, f, m, m, o);
+      }
+      return;
+    }
+    if (s == 4) return pl_attention<false, KV8, SLOTS, FORM>(a, ex, l, at, FORM && form ? above : mine, units, rounds, L, turn, form, own);
     // the statistics of the LayerNorm pending on the residual
     const char* st = s <= 2 ? (l == 0 ? nullptr : before.st(2)) : s <= 5 ? ex.st(0) : ex.st(1);
     if (s == 0 || s == 3 || s == 6) {
@@ -1048,6 +1169,9 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
           bf16* cache = (part == 1 ? a.kc : a.vc) + a.kv_layer * l;
           *reinterpret_cast<u32x2*>(cache + (size_t)(to + (cc >> 6) * a.Lcap) * kHeadDim + (cc & 63)) = p;
         });
+      } else if (s == 3 && form) {   // (its weights are passed over)
+        for (int i = 0; i < Dim::kTD; ++i) turn.use = turn.use + Dim::kChunk == Dim::kRing * Dim::kChunk ? 0 : turn.use + Dim::kChunk;
+        pl_ask<D, MR, 3, 0, Dim::kAsk[3]>(a, L, turn, wave);
       } else if (s == 3) {
         pl_project<D, MR, 3, Dim::kTD>(a, L, turn, A, false, st, stat, at.rows, vec + Dim::kVecC, [&](int row, int c, const float (&v)[4]) {
           const u32x2 p = pl_pack4(v);
@@ -1071,6 +1195,14 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
       for (int mr = wave; mr < MR; mr += kPlWaves) {
         const int row = 16 * mr + (pl_lane() & 15);
         *reinterpret_cast<f32x2*>(stat + 2 * row) = st ? pl_row_stat<D>(&L.part[0][0], 2 * 16 * MR, row, pl_lane() >> 4) : f32x2{1.f, 0.f};
+      }
+    }
+    if (s == 5 && form) {   // the statistics, which stage 3 has not formed
+      PlRows<D, MR>(a, ex.xg(0), false, at.rows, pl_lane(), wave).statistics(st, L.part[wave]);
+      lds_barrier();
+      if (wave < MR) {
+        const int row = 16 * wave + (pl_lane() & 15);
+        *reinterpret_cast<f32x2*>(stat + 2 * row) = pl_row_stat<D>(&L.part[0][0], 2 * 16 * MR, row, pl_lane() >> 4);
       }
     }
     auto resid = [&](int mr, int ct) {
