@@ -49,6 +49,13 @@ __device__ __forceinline__ int pl_lane() {
   return t;
 }
 
+// The wave, likewise (the same for all of its lanes).
+__device__ __forceinline__ int pl_wave() {
+  int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  asm volatile("" : "+s"(w));
+  return w;
+}
+
 // Exchange buffers of one layer (and group), all in tiles of 16 columns, [column / 16][RP][16]: what one item produces lies together and
 // shares no line with another workgroup's stores (with rows of all columns side by side the 8- and 32-byte pieces of up to 16
 // workgroups met in every line, and a residual sum took 3 us to become visible through memory instead of 1).  Statistics likewise,

@@ -231,18 +231,17 @@ __device__ __forceinline__ void pl_ask_rows(const XcdArgs& a, PlLds<D, MR>& L, P
     else pl_request_rows(L, t, wave, pl_rows_at<D>(Y->w2.p, t.w, wave, 1, Dim::kKC) + k * kPitch, Dim::kKC * kPitch);
   }
 }
-// The matrices of which stage S of layer l requests chunks (PlDim::kAsk; the last requests the next layer's): their addresses are there long
-// before the stage's rows are.
+// The matrices of which stage S of layer l requests chunks (PlDim::kAsk; the last requests the next layer's): as they are bound, so that nothing
+// waits for them before they are used.
 template <int D, int S>
-__device__ __forceinline__ void pl_ask_at(const XcdArgs& a, PlTurn& t, int wave, int l) {
-  typedef PlDim<D> Dim;
+__device__ __forceinline__ void pl_ask_at(const XcdArgs& a, PlTurn& t, int l) {
   const PlLayerPtr Y = pl_layer(a, S == 7 ? min(l + 1, a.n_layers - 1) : l);
-  auto square = [&](const void* W) { return pl_rows_at<D>(W, t.w, wave, 1, 1); };
-  if (S == 0) { t.at[0] = square(Y->wo.p); t.at[1] = square(Y->cwq.p); }
-  if (S == 1) { t.at[0] = square(Y->cwo.p); t.at[1] = pl_rows_at<D>(Y->w1.p, t.w, wave, Dim::kTF, 1); }
-  if (S >= 2 && S <= 4) t.at[0] = pl_rows_at<D>(Y->w1.p, t.w, wave, Dim::kTF, 1);
-  if (S == 5 || S == 6) t.at[0] = pl_rows_at<D>(Y->w2.p, t.w, wave, 1, Dim::kKC);
-  if (S == 7) t.at[0] = pl_rows_at<D>(Y->wqkv.p, t.w, wave, Dim::kTQ, 1);
+  auto set = [&](int i, const void* W) { t.at[i] = static_cast<const char*>(W); };
+  if (S == 0) { set(0, Y->wo.p); set(1, Y->cwq.p); }
+  if (S == 1) { set(0, Y->cwo.p); set(1, Y->w1.p); }
+  if (S >= 2 && S <= 4) set(0, Y->w1.p);
+  if (S == 5 || S == 6) set(0, Y->w2.p);
+  if (S == 7) set(0, Y->wqkv.p);
 }
 // Requests the next n chunks there are.
 template <int D, int MR>
@@ -272,11 +271,12 @@ __device__ __forceinline__ void pl_ask(const XcdArgs& a, PlLds<D, MR>& L, PlTurn
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
   for (int i = FIRST; i < FIRST + N; ++i) {
-    if (S == 0) pl_request_rows(L, t, wave, t.at[i], D * 2);
-    else if (S == 1) pl_request_rows(L, t, wave, t.at[i], D * 2);
-    else if (S <= 4) pl_request_rows(L, t, wave, t.at[0] + (S - 1) * kRows, D * 2);
-    else if (S <= 6) pl_request_rows(L, t, wave, t.at[0] + (S == 5 ? 0 : 1 + i) * (D * 2), PlDim<D>::kKC * D * 2);
-    else pl_request_rows(L, t, wave, t.at[0] + i * kRows, D * 2);
+    typedef PlDim<D> Dim;
+    const char* W = t.at[S <= 1 ? i : 0];
+    if (S == 0 || (S == 1 && i == 0)) pl_request_rows(L, t, wave, pl_rows_at<D>(W, t.w, wave, 1, 1), D * 2);
+    else if (S <= 4) pl_request_rows(L, t, wave, pl_rows_at<D>(W, t.w, wave, Dim::kTF, 1) + (S - 1) * kRows, D * 2);
+    else if (S <= 6) pl_request_rows(L, t, wave, pl_rows_at<D>(W, t.w, wave, 1, Dim::kKC) + (S == 5 ? 0 : 1 + i) * (D * 2), Dim::kKC * D * 2);
+    else pl_request_rows(L, t, wave, pl_rows_at<D>(W, t.w, wave, Dim::kTQ, 1) + i * kRows, D * 2);
   }
 }
 // Requests the column vectors of layer l (a request each of the first waves).
@@ -980,11 +980,13 @@ __device__ __forceinline__ PlPair pl_pair(const XcdArgs& a, const PlPlace& p, in
 template <bool SELF, bool KV8, bool SLOTS, bool FORM, int D, int MR>
 __device__ __forceinline__ void pl_attention(const XcdArgs& a, const PlExch& ex, int l, const PlPlace& at, const PlPair& mine, int units, int rounds, PlLds<D, MR>& L,
                                              PlTurn& turn, bool form, PlOwnQueries<D>& own) {
-  const int lane = pl_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lq = lane & 15, g = lane >> 4;
   char* out = ex.att(SELF ? 0 : 1);
-  const int wpu = a.wpu, per = kPlWaves / wpu, kw = wave & (wpu - 1);   // waves of a unit, units at a time
+  const int wpu = a.wpu, log = 31 - __builtin_clz(wpu), per = kPlWaves >> log;   // waves of a unit, units at a time
   for (int r = 0; r < rounds; ++r) {
-    const int u = FORM && form ? kPlMembers - 1 - at.w : (r * kPlMembers + at.w) * per + wave / wpu;
+    // (What follows from the lane and the wave is worked out in the round, where it is used: ahead of the loop, where the compiler would have it,
+    // the merge's share of it comes before the keys' and values' requests.)
+    const int lane = pl_lane(), wave = pl_wave(), lq = lane & 15, g = lane >> 4, kw = wave & (wpu - 1);
+    const int u = FORM && form ? kPlMembers - 1 - at.w : (r * kPlMembers + at.w) * per + (wave >> log);
     const PlPair pair = r == 0 ? mine : pl_pair(a, at, r, wave);
     PlUnit t;
     t.b = pair.b; t.h = pair.h; t.q0 = pair.q0;
@@ -1125,11 +1127,11 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
     // 149.3 / 133.9, 352 rows 198.4 / 188.9; d = 1024, 352 rows of long sources 544 / 530, 209 rows 422 / 408.
     asm volatile("" : "+s"(l));
     if constexpr (DIRECT) {
-      if (s == 0) pl_ask_at<D, 0>(a, turn, wave, l);
-      if (s == 1) pl_ask_at<D, 1>(a, turn, wave, l);
-      if (s == 2 || s == 3 || s == 4) pl_ask_at<D, 2>(a, turn, wave, l);
-      if (s == 5 || s == 6) pl_ask_at<D, 5>(a, turn, wave, l);
-      if (s == 7) pl_ask_at<D, 7>(a, turn, wave, l);
+      if (s == 0) pl_ask_at<D, 0>(a, turn, l);
+      if (s == 1) pl_ask_at<D, 1>(a, turn, l);
+      if (s == 2 || s == 3 || s == 4) pl_ask_at<D, 2>(a, turn, l);
+      if (s == 5 || s == 6) pl_ask_at<D, 5>(a, turn, l);
+      if (s == 7) pl_ask_at<D, 7>(a, turn, l);
     }
     const PlExch ex(a.exch + (kHalf ? (l & 1) * a.G + at.g : at.g * 2 + (l & 1)) * pl_layer_bytes(a.RP, D, 4 * D), a.RP, D);
     const PlExch before(a.exch + (kHalf ? (~l & 1) * a.G + at.g : at.g * 2 + (~l & 1)) * pl_layer_bytes(a.RP, D, 4 * D), a.RP, D);
