@@ -1050,12 +1050,16 @@ struct KsplitCfg {
   static constexpr int kStageElems = (BM + BN) * 64;
   static constexpr int kIPW = (BM + BN) / 8;                       // requests per wave and stage
   static constexpr int kRingBytes = NW * STAGES * kStageElems * 2;
-  static constexpr int kSmemBytes = kRingBytes + BM * 8;           // + rowstat
+  // rows' statistics: behind the rings, or where these take all of the LDS, in what a wave's partial tile leaves of its own
+  static constexpr bool kStatInRing = kRingBytes + BM * 8 > 160 * 1024;
+  static constexpr int kSmemBytes = kRingBytes + (kStatInRing ? 0 : BM * 8);
   static constexpr int kV = BN / 16, kLPR = 16;                    // columns per lane, lanes per row in the epilogue
   static constexpr int kRowsPerPass = kThreads / kLPR < BM ? kThreads / kLPR : BM;
   static constexpr int kIter = BM / kRowsPerPass;
   static constexpr int kTPR = kThreads / BM >= 16 ? 16 : kThreads / BM >= 8 ? 8 : kThreads / BM >= 4 ? 4 : 2;   // statistics: threads per row
-  static_assert(BM * BN * 4 <= STAGES * kStageElems * 2, "a wave's partial tile fits its ring");
+  static constexpr int kWaveRows = 64 / kTPR, kWaveF = STAGES * kStageElems / 2;   // rows whose statistics a wave forms; floats of a ring
+  __device__ __forceinline__ static int stat_off(int r) { return kStatInRing ? r / kWaveRows * kWaveF + BM * BN + r % kWaveRows * 2 : kRingBytes / 4 + r * 2; }
+  static_assert(BM * BN * 4 + (kStatInRing ? kWaveRows * 8 : 0) <= STAGES * kStageElems * 2, "a wave's partial tile fits its ring");
   static_assert((BN == 32 || BN == 64) && BM % 16 == 0 && BM % kRowsPerPass == 0, "tile shape");
   static_assert(kSmemBytes <= 160 * 1024, "LDS of a CU");
   // partial tile in LDS: [BM][BN] floats, 16-byte chunk c of row r at chunk c ^ (r mod chunks)
@@ -1073,7 +1077,6 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ksplit_kernel(const bf16* 
   const bf16* __restrict__ W = static_cast<const bf16*>(Wv);
   constexpr int BM = Cfg::kBM, BN = Cfg::kBN, NW = Cfg::kWaves, S = Cfg::kStages, IPW = W8 ? BM / 8 + BN / 16 : Cfg::kIPW;
   constexpr int FA = BM / 16, FB = BN / 16, V = Cfg::kV, LPR = Cfg::kLPR, ITER = Cfg::kIter, RPP = Cfg::kRowsPerPass;
-  float* rowstat = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Cfg::kRingBytes);   // [BM][2]
   int mt, nt;
   if (!xcd_tile(blockIdx.x, MT, NT, mt, nt)) return;
   const int m0 = mt * BM, n0 = nt * BN;
@@ -1176,13 +1179,13 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ksplit_kernel(const bf16* 
   M = min(M, mr);
   // D[n][m]: this lane holds row i*16 + lq, columns j*16 + 4g .. + 3; the wave's own ring takes its partial tile
   float* red = reinterpret_cast<float*>(smem);
-  constexpr int kWaveF = S * Cfg::kStageElems / 2;
+  constexpr int kWaveF = Cfg::kWaveF;
 #pragma unroll
   for (int i = 0; i < FA; ++i)
 #pragma unroll
     for (int j = 0; j < FB; ++j)
       *reinterpret_cast<f32x4*>(red + wave * kWaveF + Cfg::red_off(i * 16 + lq, j * 16 + 4 * g)) = acc[i][j];
-  ln_row_stats<TPR, NL>(pr, sj, epi.d_ln(), epi.chunks, epi.identity(), tid < BM * TPR, rowstat + 2 * sr);
+  ln_row_stats<TPR, NL>(pr, sj, epi.d_ln(), epi.chunks, epi.identity(), tid < BM * TPR, red + Cfg::stat_off(sr));
   lds_barrier();
   if (RPP * LPR < Cfg::kThreads && tid >= RPP * LPR) return;
 #pragma unroll
@@ -1202,7 +1205,7 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_ksplit_kernel(const bf16* 
 #pragma unroll
       for (int e = 0; e < V; ++e) v[e] *= wsc[e];
     }
-    const f32x2 rs = *reinterpret_cast<const f32x2*>(rowstat + 2 * r);
+    const f32x2 rs = *reinterpret_cast<const f32x2*>(red + Cfg::stat_off(r));
     epi.template store<V, BN>(m, n, m < M && n < N, v, pre[it], rs[0], rs[1], cv);
   }
 }
@@ -1239,10 +1242,12 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeig
   if (one_round(M, N, 32, 64)) return launch_ksplit<KsplitCfg<32, 64, 8, 1>>(st, A, lda, W, M, N, K, epi, m_real);
   if (one_round(M, N, 48, 64)) return launch_ksplit<KsplitCfg<48, 64, 4, 2>>(st, A, lda, W, M, N, K, epi, m_real);
   // a long K pays for a larger tile where the ring's tiles are more than one to a CU (FFN2 of the big model at 1408 rows: 64 x 64 ring
-  // 28.0 us, 24.2; but at 1024 rows 19.2 and 22.9); at K <= 2048 the ring is level or better, and so it is where M is only a bound on the
-  // rows in use
+  // 28.0 us, with three waves 24.2; but at 1024 rows 19.2 and 22.9); at K <= 2048 the ring is level or better, and so it is where M is only a
+  // bound on the rows in use.  Four waves, one to a SIMD, whose rings take all of the LDS: a verify pass of 128 x 11 rows 885 us with three, now 876 (x 1024 x
+  // 1024 so as well, in place of the 64 x 64 ring: 890).  What a CU takes in bounds it, some 64 B/ns: fragments of a slab read under the products of the one
+  // before it were slower (886).
   if constexpr (Epi::kVec == 3) {
-    if (K >= 4096 && !m_real && !one_round(M, N, 64, 64) && one_round(M, N, 96, 64)) return launch_ksplit<KsplitCfg<96, 64, 3, 2>>(st, A, lda, W, M, N, K, epi, m_real);
+    if (K >= 4096 && !m_real && !one_round(M, N, 64, 64) && one_round(M, N, 96, 64)) return launch_ksplit<KsplitCfg<96, 64, 4, 2>>(st, A, lda, W, M, N, K, epi, m_real);
   }
   // From 512 tiles of 128 x 128 on: two of them a CU, or 256 x 256.  Below: 256 x 128 while those are at most one to a CU, 128 x 128 with a
   // ring of four, one to a CU, while these are, and 64 x 64, two to a CU, while those are.  us on 64 x 64 / 128 x 128 ring of four /
