@@ -1654,7 +1654,7 @@ struct VocabTiles {
 template <bool ARGMAX, class Cfg>
 __device__ __forceinline__ void vocab_records(const GemmAcc<Cfg>& acc, const float (&zd)[Cfg::kTM], f32x4* rec, int lane, int wave, int m0, int n0, int M,
                                               int V, int NT, float* __restrict__ part, float* __restrict__ logits) {
-  static_assert(Cfg::kBM == 256 && Cfg::kWN == 64 && (Cfg::kWavesN == 2 || Cfg::kWavesN == 4) && Cfg::kThreads == 512, "shape");
+  static_assert((Cfg::kBM == 256 || Cfg::kBM == 192) && Cfg::kWN == 64 && (Cfg::kWavesN == 2 || Cfg::kWavesN == 4) && Cfg::kThreads == 512, "shape");
   const int tid = wave * 64 + lane, wy = wave / Cfg::kWavesN, wx = wave % Cfg::kWavesN, lcol = lane & 31, lhalf = lane >> 5;
   const int nw = n0 + wx * 64 + 4 * lhalf;        // first column of this lane
   // column of accumulator (j, r) relative to nw: ascending in (j, r), so ">" keeps the lowest index of a tie
@@ -1721,7 +1721,7 @@ __device__ __forceinline__ void vocab_records(const GemmAcc<Cfg>& acc, const flo
   // thread (row, 128-column tile): waves 2t and 2t+1 of the row, lower columns first
   const int row = tid & 255, ct = tid >> 8;
   const int m = m0 + row, nt128 = n0 / 128 + ct;
-  if (ct < Cfg::kBN / 128 && m < M && nt128 < NT) {
+  if (ct < Cfg::kBN / 128 && (Cfg::kBM == 256 || row < Cfg::kBM) && m < M && nt128 < NT) {
     const f32x4 a = rec[(2 * ct) * 256 + row], b = rec[(2 * ct + 1) * 256 + row];
     const float nb = fmaxf(a[0], b[0]);
     float tot = 0.f;
@@ -1742,16 +1742,16 @@ __device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
   vocab_records<ARGMAX>(acc, zd, reinterpret_cast<f32x4*>(smem + Cfg::kSmemBytes), lane, wave, m0, n0, M, V, NT, part, logits);
 }
 
-// A tile of 256 rows x 128 columns.
-template <bool ARGMAX>
-__device__ __forceinline__ void vocab_tall(const bf16* __restrict__ A, const bf16* __restrict__ E, int M, int V, int K, int NT, int m0, int n0,
+// A tile of 256 rows x 128 columns, or 192 x 256.
+template <bool ARGMAX, class Cfg>
+__device__ __forceinline__ void vocab_tile(const bf16* __restrict__ A, const bf16* __restrict__ E, int M, int V, int K, int NT, int m0, int n0,
                                            const float* __restrict__ zd_row, float* __restrict__ part, float* __restrict__ logits, bf16* smem) {
   const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float zd[CfgTall::kTM];   // (requested ahead of the products)
+  float zd[Cfg::kTM];   // (requested ahead of the products)
 #pragma unroll
-  for (int i = 0; i < CfgTall::kTM; ++i) zd[i] = zd_row ? zd_row[min(m0 + (wave >> 1) * CfgTall::kWM + i * 32 + (lane & 31), M - 1)] : kNegInf;
-  GemmAcc<CfgTall> acc;
-  gemm_mainloop<CfgTall, true>(A, K, E, K, M, V, 0, K / CfgTall::GK, m0, n0, smem, acc);
+  for (int i = 0; i < Cfg::kTM; ++i) zd[i] = zd_row ? zd_row[min(m0 + wave / Cfg::kWavesN * Cfg::kWM + i * 32 + (lane & 31), M - 1)] : kNegInf;
+  GemmAcc<Cfg> acc;
+  gemm_mainloop<Cfg, true>(A, K, E, K, M, V, 0, K / Cfg::GK, m0, n0, smem, acc);
   vocab_records<ARGMAX>(acc, zd, reinterpret_cast<f32x4*>(smem), lane, wave, m0, n0, M, V, NT, part, logits);
 }
 
@@ -1763,7 +1763,19 @@ __global__ __launch_bounds__(CfgTall::kThreads, 2) void vocab_tall_kernel(const 
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
   int mt, nt;
   if (!xcd_tile(blockIdx.x, 1, NT, mt, nt)) return;
-  vocab_tall<ARGMAX>(A, E, M, V, K, NT, 0, nt * 128, zd_row, part, logits, smem);
+  vocab_tile<ARGMAX, CfgTall>(A, E, M, V, K, NT, 0, nt * 128, zd_row, part, logits, smem);
+}
+
+// 257 - 384 rows, likewise.
+typedef GemmCfg<192, 256, 2, 2, 4> CfgVocabMid;
+template <bool ARGMAX>
+__global__ __launch_bounds__(CfgVocabMid::kThreads, 2) void vocab_mid_kernel(const bf16* __restrict__ A, const bf16* __restrict__ E, int M, int V, int K, int NT,
+                                                                             const float* __restrict__ zd_row, float* __restrict__ part,
+                                                                             float* __restrict__ logits) {
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+  int mt, nt;
+  if (!xcd_tile(blockIdx.x, 2, (V + 255) / 256, mt, nt)) return;
+  vocab_tile<ARGMAX, CfgVocabMid>(A, E, M, V, K, NT, mt * 192, nt * 256, zd_row, part, logits, smem);
 }
 
 template <bool ARGMAX, bool STREAM>
@@ -1788,7 +1800,7 @@ __global__ __launch_bounds__(CfgVocab256::kThreads, 2) void vocab256_kernel(cons
     t.n0 += (i & 1) * 128;
     if (t.n0 >= V) return;
     __syncthreads();   // the ring and the records are everybody's again
-    vocab_tall<ARGMAX>(A, E, M, V, K, NT, t.m0, t.n0, zd_row, part, logits, smem);
+    vocab_tile<ARGMAX, CfgTall>(A, E, M, V, K, NT, t.m0, t.n0, zd_row, part, logits, smem);
   } else {
     gemm_mainloop_square<CfgVocab256>(A, K, E, K, M, V, 0, K / CfgVocab256::GK, t.m0, t.n0, smem, acc, hook);
     t.finish();
@@ -1813,6 +1825,16 @@ static hipError_t launch_vocab_tall(hipStream_t st, const bf16* A, const bf16* E
   if (attr != hipSuccess) return attr;
   const int NT = (V + 127) / 128;
   SD_LAUNCH_TIMED((vocab_tall_kernel<ARGMAX>), dim3(xcd_grid(1, NT)), dim3(CfgTall::kThreads), CfgTall::kSmemBytes, st, A, E, M, V, K, NT, zd, part, logits);
+  return hipGetLastError();
+}
+
+template <bool ARGMAX>
+static hipError_t launch_vocab_mid(hipStream_t st, const bf16* A, const bf16* E, int M, int V, int K, const float* zd, float* part, float* logits) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab_mid_kernel<ARGMAX>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, CfgVocabMid::kSmemBytes);
+  if (attr != hipSuccess) return attr;
+  SD_LAUNCH_TIMED((vocab_mid_kernel<ARGMAX>), dim3(xcd_grid(2, (V + 255) / 256)), dim3(CfgVocabMid::kThreads), CfgVocabMid::kSmemBytes, st, A, E, M, V, K,
+                  (V + 127) / 128, zd, part, logits);
   return hipGetLastError();
 }
 
@@ -1856,22 +1878,32 @@ hipError_t vocab_stats(hipStream_t st, const bf16* A, const bf16* E, int M, int 
   // (128 of the larger tiles) 25.6 / 32.3 us, 352 (256) 44.8 / 34.7 (d = 512
   // 25.3 / 20.9), 704 (384) 68.6 / 52.8.
   const int MT256 = (M + 255) / 256, NT256 = (V + 255) / 256;
-  const bool big = force_wide || (long)MT256 * NT256 >= 256;
+  // ... or where those of 128 x 128, two to a CU, are one round and some of a second, up to three quarters of it.  Whole verify passes on 128 x 128 / 256 x 256,
+  // us, tiles of 128 x 128: 506 rows, d = 512, 440 of them 207.8 / 209.2, 532 219.3 / 210.2, 752 222.6 / 215.5, 1004 226.3 / 225.4; d = 1024 438.4 / 438.7,
+  // 455.9 / 439.1, 461.2 / 445.1, 465.6 / 468.4; 704 rows, d = 512, 474 236.3 / 233.3, 660 247.5 / 234.6, 942 249.8 / 246.8; d = 1024 485.5 / 487.4,
+  // 506.5 / 488.2, 508.4 / 509.7.
+  const long tiles = (long)MT * NT;
+  const bool big = force_wide || (long)MT256 * NT256 >= 256 || (M > 256 && tiles > 512 && tiles <= 896);
   // 129 - 256 rows of a short K, one round of 256 x 128: a launch on 128 x 128 tiles (two to a CU) / so, K = 512: 143 rows 15.7 / 12.4 us, 240 of
   // a drafter 15.0 / 12.0, 253 16.0 / 13.2.  At K = 1024 a launch by itself is faster, too (209 rows 28.5 / 23.4), but whole passes are not
   // (209 rows 353.8 / 355.4, 253 356.5 / 360): in those E comes from memory, 16 stages of it one behind the other.
   const bool tall = !big && MT == 2 && NT <= 256 && K <= 512;
-  const hipError_t e = big || tall ? launch_draft_logits<true>(st, A, E, M, V, K, row_draft, zd_row, ln)
+  // 257 - 384 rows, one round of 192 x 256: two row tiles of 256 would be a third empty.  Whole verify passes of 352 rows on 128 x 128 tiles / so, us, by
+  // vocabulary: d = 512, 14000 166.0 / 167.3, 17000 168.0 / 169.0, 20000 168.5 / 170.1, 22000 176.1 / 168.0, 28000 182.2 / 172.8, 32003 182.8 / 177.2; d = 1024
+  // 349.6 / 352.5, 352.0 / 354.5, 357.9 / 354.6, 366.3 / 354.5, 372.3 / 358.5, 373.6 / 364.3; of 32768, on 256 x 256 tiles before, d = 512 185.0 / 183.2.
+  const bool mid = MT == 3 && 2 * NT256 <= 256 && (force_wide || tiles > 512);
+  const hipError_t e = big || tall || mid ? launch_draft_logits<true>(st, A, E, M, V, K, row_draft, zd_row, ln)
                                    : launch_draft_logits<false>(st, A, E, M, V, K, row_draft, zd_row, ln);
   if (e != hipSuccess) return e;
   const float* zd = row_draft ? zd_row : nullptr;
   if (tall) return stats ? launch_vocab_tall<false>(st, A, E, M, V, K, zd, part, logits) : launch_vocab_tall<true>(st, A, E, M, V, K, nullptr, part, logits);
+  if (mid) return stats ? launch_vocab_mid<false>(st, A, E, M, V, K, zd, part, logits) : launch_vocab_mid<true>(st, A, E, M, V, K, nullptr, part, logits);
   if (big) {
     const bool stream = K % 128 == 0 && K >= 256 && (long)MT256 * NT256 > 256;
     if (stats) return stream ? launch_vocab256<false, true>(st, A, E, M, V, K, zd, part, logits) : launch_vocab256<false, false>(st, A, E, M, V, K, zd, part, logits);
     return stream ? launch_vocab256<true, true>(st, A, E, M, V, K, nullptr, part, logits) : launch_vocab256<true, false>(st, A, E, M, V, K, nullptr, part, logits);
   }
-  const bool deep = (long)MT * NT <= 256;   // V = 32768, d = 1024, 128 rows (256 blocks): short ring 24.2 us, deep 21.1; more blocks share CUs
+  const bool deep = tiles <= 256;   // V = 32768, d = 1024, 128 rows (256 blocks): short ring 24.2 us, deep 21.1; more blocks share CUs
   if (stats) return deep ? launch_vocab<false, CfgVocabDeep>(st, A, E, M, V, K, MT, NT, zd, part, logits) : launch_vocab<false, CfgVocab>(st, A, E, M, V, K, MT, NT, zd, part, logits);
   return deep ? launch_vocab<true, CfgVocabDeep>(st, A, E, M, V, K, MT, NT, nullptr, part, logits) : launch_vocab<true, CfgVocab>(st, A, E, M, V, K, MT, NT, nullptr, part, logits);
 }
