@@ -1766,7 +1766,7 @@ __global__ __launch_bounds__(CfgTall::kThreads, 2) void vocab_tall_kernel(const 
   vocab_tile<ARGMAX, CfgTall>(A, E, M, V, K, NT, 0, nt * 128, zd_row, part, logits, smem);
 }
 
-// 257 - 384 rows, likewise.
+// 257 - 384 rows in two row tiles of 192, likewise.  513 - 640: those behind the first 256, and of these a tile of 256 x 128 a CU ahead.
 typedef GemmCfg<192, 256, 2, 2, 4> CfgVocabMid;
 template <bool ARGMAX>
 __global__ __launch_bounds__(CfgVocabMid::kThreads, 2) void vocab_mid_kernel(const bf16* __restrict__ A, const bf16* __restrict__ E, int M, int V, int K, int NT,
@@ -1775,7 +1775,11 @@ __global__ __launch_bounds__(CfgVocabMid::kThreads, 2) void vocab_mid_kernel(con
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
   int mt, nt;
   if (!xcd_tile(blockIdx.x, 2, (V + 255) / 256, mt, nt)) return;
-  vocab_tile<ARGMAX, CfgVocabMid>(A, E, M, V, K, NT, mt * 192, nt * 256, zd_row, part, logits, smem);
+  if (M > 384) {
+    if (nt * 256 + mt * 128 < V) vocab_tile<ARGMAX, CfgTall>(A, E, M, V, K, NT, 0, nt * 256 + mt * 128, zd_row, part, logits, smem);
+    __syncthreads();
+  }
+  vocab_tile<ARGMAX, CfgVocabMid>(A, E, M, V, K, NT, (M > 384 ? 256 : 0) + mt * 192, nt * 256, zd_row, part, logits, smem);
 }
 
 template <bool ARGMAX, bool STREAM>
@@ -1830,10 +1834,11 @@ static hipError_t launch_vocab_tall(hipStream_t st, const bf16* A, const bf16* E
 
 template <bool ARGMAX>
 static hipError_t launch_vocab_mid(hipStream_t st, const bf16* A, const bf16* E, int M, int V, int K, const float* zd, float* part, float* logits) {
+  constexpr int kBytes = std::max(CfgVocabMid::kSmemBytes, CfgTall::kSmemBytes);
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab_mid_kernel<ARGMAX>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, CfgVocabMid::kSmemBytes);
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
   if (attr != hipSuccess) return attr;
-  SD_LAUNCH_TIMED((vocab_mid_kernel<ARGMAX>), dim3(xcd_grid(2, (V + 255) / 256)), dim3(CfgVocabMid::kThreads), CfgVocabMid::kSmemBytes, st, A, E, M, V, K,
+  SD_LAUNCH_TIMED((vocab_mid_kernel<ARGMAX>), dim3(xcd_grid(2, (V + 255) / 256)), dim3(CfgVocabMid::kThreads), kBytes, st, A, E, M, V, K,
                   (V + 127) / 128, zd, part, logits);
   return hipGetLastError();
 }
@@ -1891,7 +1896,10 @@ hipError_t vocab_stats(hipStream_t st, const bf16* A, const bf16* E, int M, int 
   // 257 - 384 rows, one round of 192 x 256: two row tiles of 256 would be a third empty.  Whole verify passes of 352 rows on 128 x 128 tiles / so, us, by
   // vocabulary: d = 512, 14000 166.0 / 167.3, 17000 168.0 / 169.0, 20000 168.5 / 170.1, 22000 176.1 / 168.0, 28000 182.2 / 172.8, 32003 182.8 / 177.2; d = 1024
   // 349.6 / 352.5, 352.0 / 354.5, 357.9 / 354.6, 366.3 / 354.5, 372.3 / 358.5, 373.6 / 364.3; of 32768, on 256 x 256 tiles before, d = 512 185.0 / 183.2.
-  const bool mid = MT == 3 && 2 * NT256 <= 256 && (force_wide || tiles > 512);
+  // 513 - 640 rows, one round of these behind one of 256 x 128, where 256 x 256 would be one and a half: a drafter's 640 with the pass around them 127.5 / 123.4;
+  // whole verify passes, d = 512, 528 rows 225.2 / 221.4, 638 244.5 / 240.8; d = 1024 459.6 / 456.3, 501.0 / 497.0.  (770 rows as two rounds of 192 x 256, and the last
+  // 384 rows of 825, 1056 and 1408 as one: level or up to 3 % slower.)
+  const bool mid = 2 * NT256 <= 256 && ((MT == 3 && (force_wide || tiles > 512)) || (MT == 5 && 3 * NT256 > 256));
   const hipError_t e = big || tall || mid ? launch_draft_logits<true>(st, A, E, M, V, K, row_draft, zd_row, ln)
                                    : launch_draft_logits<false>(st, A, E, M, V, K, row_draft, zd_row, ln);
   if (e != hipSuccess) return e;
