@@ -16,7 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspecdec.so")
-SOURCES = ["api.hip", "gemm.hip", "attn.hip", "misc.hip", "skinny.hip", "skinny2.hip", "persist.hip", "xcd.hip",
+SOURCES = ["api.hip", "gemm.hip", "vocab_mid.hip", "attn.hip", "misc.hip", "skinny.hip", "skinny2.hip", "persist.hip", "xcd.hip",
            "xcd_512.hip", "xcd_512_kv8.hip", "xcd_1024.hip", "xcd_1024_kv8.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", *os.environ.get("SD_EXTRA_FLAGS", "").split(), "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-parameter",

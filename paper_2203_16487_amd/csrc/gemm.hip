@@ -1,6 +1,7 @@
 // MFMA GEMM kernels of the decoder / encoder blocks and the fused vocabulary kernel.
 #include "gemm_core.h"
 #include "kernels.h"
+#include "vocab_tiles.h"
 #include <type_traits>
 
 namespace sd {
@@ -9,20 +10,7 @@ static thread_local KernelTimer* g_kernel_timer = nullptr;
 void set_kernel_timer(KernelTimer* t) { g_kernel_timer = t; }
 KernelTimer* kernel_timer() { return g_kernel_timer; }
 
-// Workgroup ids are dealt round-robin to the 8 XCDs (id % 8), each with its own L2.  Tiles are
-// numbered n-major (m fastest) and XCD x takes the contiguous run [x*per, (x+1)*per): the
-// tiles that run together on one XCD then share a few weight column-panels and the
-// activation rows, which stay in that XCD's L2.  Returns false for the padding blocks.
-__device__ __forceinline__ bool xcd_tile(int id, int MT, int NT, int& mt, int& nt) {
-  const int nb = MT * NT;
-  const int per = (nb + 7) >> 3;
-  const int t = (id & 7) * per + (id >> 3);
-  if ((id >> 3) >= per || t >= nb) return false;
-  nt = t / MT;
-  mt = t - nt * MT;
-  return true;
-}
-// The same for many row tiles: groups of 8 row tiles, inside a group n-major, so that what runs together on an XCD shares
+// xcd_tile for many row tiles: groups of 8 row tiles, inside a group n-major, so that what runs together on an XCD shares
 // both a few weight panels and a few row panels (one long n-major run streams all rows past each weight panel: 32768 x 3072
 // x 1024 on 128 x 128 tiles 276 us, grouped 247; on 256 x 256 231, grouped 212).
 __device__ __forceinline__ bool xcd_tile_grouped(int id, int MT, int NT, int& mt, int& nt) {
@@ -36,7 +24,6 @@ __device__ __forceinline__ bool xcd_tile_grouped(int id, int MT, int NT, int& mt
   mt = g * G + r - nt * rows;
   return true;
 }
-static inline int xcd_grid(int MT, int NT) { return 8 * ((MT * NT + 7) / 8); }
 
 // fp32 staging tile in LDS, [BM][BN]; rows r and r+4 come from the two lane halves of one
 // MFMA register, so bit 5 of the column is flipped for every other group of 4 rows.
@@ -177,7 +164,6 @@ __global__ __launch_bounds__(Cfg::kThreads) void gemm_kernel(const bf16* __restr
 
 typedef GemmCfg<128, 128, 2> CfgWide;      // 64 KB LDS: two blocks per CU
 typedef GemmCfg<64, 64, 4> CfgSmall;       // 64 KB LDS; many tiles for narrow outputs
-typedef GemmCfg<256, 128, 3, 4, 2> CfgTall;   // 144 KB LDS, eight waves: one block per CU
 
 template <class Cfg, class Epi>
 static hipError_t launch_cfg(hipStream_t st, const bf16* A, int lda, const bf16* W, int M, int N, int K,
@@ -1649,90 +1635,6 @@ struct VocabTiles {
   __device__ __forceinline__ void finish() const;
 };
 
-// The records of a finished tile of 256 rows; zd: the drafts' logits of the lane's rows (-inf on rows that score no draft: count unused); rec:
-// [wave columns][256 rows].
-template <bool ARGMAX, class Cfg>
-__device__ __forceinline__ void vocab_records(const GemmAcc<Cfg>& acc, const float (&zd)[Cfg::kTM], f32x4* rec, int lane, int wave, int m0, int n0, int M,
-                                              int V, int NT, float* __restrict__ part, float* __restrict__ logits) {
-  static_assert((Cfg::kBM == 256 || Cfg::kBM == 192) && Cfg::kWN == 64 && (Cfg::kWavesN == 2 || Cfg::kWavesN == 4) && Cfg::kThreads == 512, "shape");
-  const int tid = wave * 64 + lane, wy = wave / Cfg::kWavesN, wx = wave % Cfg::kWavesN, lcol = lane & 31, lhalf = lane >> 5;
-  const int nw = n0 + wx * 64 + 4 * lhalf;        // first column of this lane
-  // column of accumulator (j, r) relative to nw: ascending in (j, r), so ">" keeps the lowest index of a tie
-  auto col = [](int j, int r) { return j * 32 + 8 * (r >> 2) + (r & 3); };
-  constexpr float kLog2e = 1.44269504088896341f;
-  auto scan = [&](auto full_tag) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    const int nvalid = V - nw;   // columns of this lane inside the matrix (FULL: all of them)
-#pragma unroll
-    for (int i = 0; i < Cfg::kTM; ++i) {
-      float best = kNegInf;
-      int bestc = 0x3fffffff, cnt = 0;
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float v = acc.c[i][j][r];
-          if (FULL || col(j, r) < nvalid) {
-            if (v > best) { best = v; bestc = col(j, r); }
-            if (!ARGMAX) cnt += (v > zd[i]) ? 1 : 0;
-          }
-        }
-      float se = 0.f;
-      if (!ARGMAX) {
-        const float nb2 = -best * kLog2e;   // exp(v - best) = 2^(v log2e - best log2e)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (FULL || col(j, r) < nvalid) se += __builtin_amdgcn_exp2f(__builtin_fmaf(acc.c[i][j][r], kLog2e, nb2));
-        if (!(best > kNegInf)) se = 0.f;    // no valid column (or all -inf): nothing to sum
-      }
-      const int besti = nw + bestc;
-      // the other lane half holds the interleaved groups of 4 columns of the same row
-      const float obest = __shfl_xor(best, 32, 64);
-      const int obesti = __shfl_xor(besti, 32, 64);
-      const float ose = __shfl_xor(se, 32, 64);
-      const int ocnt = __shfl_xor(cnt, 32, 64);
-      const float nb = fmaxf(best, obest);
-      float tot = 0.f;
-      if (best > kNegInf) tot += se * __expf(best - nb);
-      if (obest > kNegInf) tot += ose * __expf(obest - nb);
-      const int nbi = (obest > best || (obest == best && obesti < besti)) ? obesti : besti;
-      if (lhalf == 0)
-        rec[wx * 256 + wy * Cfg::kWM + i * 32 + lcol] = f32x4{nb, __int_as_float(nbi), tot, __int_as_float(cnt + ocnt)};
-    }
-  };
-  if (n0 + Cfg::kBN <= V) scan(std::true_type{});
-  else scan(std::false_type{});
-  if (logits) {
-#pragma unroll
-    for (int i = 0; i < Cfg::kTM; ++i) {
-      const int m = m0 + wy * Cfg::kWM + i * 32 + lcol;
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int n = nw + j * 32 + 8 * (r >> 2) + (r & 3);
-          if (m < M && n < V) logits[(size_t)m * V + n] = acc.c[i][j][r];
-        }
-    }
-  }
-  lds_barrier();
-  // thread (row, 128-column tile): waves 2t and 2t+1 of the row, lower columns first
-  const int row = tid & 255, ct = tid >> 8;
-  const int m = m0 + row, nt128 = n0 / 128 + ct;
-  if (ct < Cfg::kBN / 128 && (Cfg::kBM == 256 || row < Cfg::kBM) && m < M && nt128 < NT) {
-    const f32x4 a = rec[(2 * ct) * 256 + row], b = rec[(2 * ct + 1) * 256 + row];
-    const float nb = fmaxf(a[0], b[0]);
-    float tot = 0.f;
-    if (a[0] > kNegInf) tot += a[2] * __expf(a[0] - nb);
-    if (b[0] > kNegInf) tot += b[2] * __expf(b[0] - nb);
-    const bool tb = b[0] > a[0];   // equal maxima: the lower columns (a) win
-    f32x4 out = {nb, tb ? b[1] : a[1], tot, __int_as_float(__float_as_int(a[3]) + __float_as_int(b[3]))};
-    *reinterpret_cast<f32x4*>(part + ((size_t)m * NT + nt128) * kPartF) = out;
-  }
-}
-
 template <bool ARGMAX, bool STREAM>
 __device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
   const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1740,19 +1642,6 @@ __device__ __forceinline__ void VocabTiles<ARGMAX, STREAM>::finish() const {
 #pragma unroll
   for (int i = 0; i < 4; ++i) zd[i] = zd_row ? zd_rows(flip)[(wave >> 2) * 128 + i * 32 + (lane & 31)] : kNegInf;
   vocab_records<ARGMAX>(acc, zd, reinterpret_cast<f32x4*>(smem + Cfg::kSmemBytes), lane, wave, m0, n0, M, V, NT, part, logits);
-}
-
-// A tile of 256 rows x 128 columns, or 192 x 256.
-template <bool ARGMAX, class Cfg>
-__device__ __forceinline__ void vocab_tile(const bf16* __restrict__ A, const bf16* __restrict__ E, int M, int V, int K, int NT, int m0, int n0,
-                                           const float* __restrict__ zd_row, float* __restrict__ part, float* __restrict__ logits, bf16* smem) {
-  const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float zd[Cfg::kTM];   // (requested ahead of the products)
-#pragma unroll
-  for (int i = 0; i < Cfg::kTM; ++i) zd[i] = zd_row ? zd_row[min(m0 + wave / Cfg::kWavesN * Cfg::kWM + i * 32 + (lane & 31), M - 1)] : kNegInf;
-  GemmAcc<Cfg> acc;
-  gemm_mainloop<Cfg, true>(A, K, E, K, M, V, 0, K / Cfg::GK, m0, n0, smem, acc);
-  vocab_records<ARGMAX>(acc, zd, reinterpret_cast<f32x4*>(smem), lane, wave, m0, n0, M, V, NT, part, logits);
 }
 
 // 129 - 256 rows: one block to a CU, where the vocabulary is one round of them.
@@ -1764,22 +1653,6 @@ __global__ __launch_bounds__(CfgTall::kThreads, 2) void vocab_tall_kernel(const 
   int mt, nt;
   if (!xcd_tile(blockIdx.x, 1, NT, mt, nt)) return;
   vocab_tile<ARGMAX, CfgTall>(A, E, M, V, K, NT, 0, nt * 128, zd_row, part, logits, smem);
-}
-
-// 257 - 384 rows in two row tiles of 192, likewise.  513 - 640: those behind the first 256, and of these a tile of 256 x 128 a CU ahead.
-typedef GemmCfg<192, 256, 2, 2, 4> CfgVocabMid;
-template <bool ARGMAX>
-__global__ __launch_bounds__(CfgVocabMid::kThreads, 2) void vocab_mid_kernel(const bf16* __restrict__ A, const bf16* __restrict__ E, int M, int V, int K, int NT,
-                                                                             const float* __restrict__ zd_row, float* __restrict__ part,
-                                                                             float* __restrict__ logits) {
-  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
-  int mt, nt;
-  if (!xcd_tile(blockIdx.x, 2, (V + 255) / 256, mt, nt)) return;
-  if (M > 384) {
-    if (nt * 256 + mt * 128 < V) vocab_tile<ARGMAX, CfgTall>(A, E, M, V, K, NT, 0, nt * 256 + mt * 128, zd_row, part, logits, smem);
-    __syncthreads();
-  }
-  vocab_tile<ARGMAX, CfgVocabMid>(A, E, M, V, K, NT, (M > 384 ? 256 : 0) + mt * 192, nt * 256, zd_row, part, logits, smem);
 }
 
 template <bool ARGMAX, bool STREAM>
@@ -1829,17 +1702,6 @@ static hipError_t launch_vocab_tall(hipStream_t st, const bf16* A, const bf16* E
   if (attr != hipSuccess) return attr;
   const int NT = (V + 127) / 128;
   SD_LAUNCH_TIMED((vocab_tall_kernel<ARGMAX>), dim3(xcd_grid(1, NT)), dim3(CfgTall::kThreads), CfgTall::kSmemBytes, st, A, E, M, V, K, NT, zd, part, logits);
-  return hipGetLastError();
-}
-
-template <bool ARGMAX>
-static hipError_t launch_vocab_mid(hipStream_t st, const bf16* A, const bf16* E, int M, int V, int K, const float* zd, float* part, float* logits) {
-  constexpr int kBytes = std::max(CfgVocabMid::kSmemBytes, CfgTall::kSmemBytes);
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(vocab_mid_kernel<ARGMAX>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
-  if (attr != hipSuccess) return attr;
-  SD_LAUNCH_TIMED((vocab_mid_kernel<ARGMAX>), dim3(xcd_grid(2, (V + 255) / 256)), dim3(CfgVocabMid::kThreads), kBytes, st, A, E, M, V, K,
-                  (V + 127) / 128, zd, part, logits);
   return hipGetLastError();
 }
 
@@ -1905,7 +1767,7 @@ hipError_t vocab_stats(hipStream_t st, const bf16* A, const bf16* E, int M, int 
   if (e != hipSuccess) return e;
   const float* zd = row_draft ? zd_row : nullptr;
   if (tall) return stats ? launch_vocab_tall<false>(st, A, E, M, V, K, zd, part, logits) : launch_vocab_tall<true>(st, A, E, M, V, K, nullptr, part, logits);
-  if (mid) return stats ? launch_vocab_mid<false>(st, A, E, M, V, K, zd, part, logits) : launch_vocab_mid<true>(st, A, E, M, V, K, nullptr, part, logits);
+  if (mid) return vocab_mid(st, A, E, M, V, K, stats, zd, part, logits);
   if (big) {
     const bool stream = K % 128 == 0 && K >= 256 && (long)MT256 * NT256 > 256;
     if (stats) return stream ? launch_vocab256<false, true>(st, A, E, M, V, K, zd, part, logits) : launch_vocab256<false, false>(st, A, E, M, V, K, zd, part, logits);
