@@ -21,7 +21,7 @@
 // A pass of at most 63 rows of d = 512 needs no such copy: it reads the matrices as bound, a chunk of 16 rows x 128 bytes at a time (DIRECT;
 // 113.6 us for 6 rows, from a copy 112.7).
 //
-// A drafter's pass (d = 512; stream rows and slots of as many places a sequence as it can need) is one of these, its matrices read in place whatever
+// A drafter's pass of at least 200 drafts (d = 512; stream rows and slots of as many places a sequence as it can need) is one of these, its matrices read in place whatever
 // its rows.  Passes behind a loaded cache, statistics read back, launches / this kernel, us: one sequence of 5 + 1 rows 96 / 58, 8 x 11 105 / 63, 32 x 11
 // 124 / 83, on 500 source tokens and 200 cached ones 133 / 100, 64 x 8 123 / 96.  An iteration of the loop with a base verifier, 1 x 11 215 /
 // 185, 24 x 11 (504 places for the drafter, some 340 in use) 291 / 261.

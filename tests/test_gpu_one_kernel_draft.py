@@ -1,4 +1,4 @@
-"""A drafter's pass of few rows (d_model 512) as one kernel, each XCD on sequences of its own: row tiles and their remainders, stream rows of
+"""A drafter's pass of few rows (d_model 512, at least 200 drafts) as one kernel, each XCD on sequences of its own: row tiles and their remainders, stream rows of
 different numbers a sequence, slots beyond one tile of 16 queries and beyond a chunk of keys, against the oracle; caches loaded short of the
 stream, waits given up, replays of a captured pass, and the launches it takes with the kernels for small batches off."""
 import numpy as np
@@ -23,7 +23,7 @@ def model(seed=31):
 
 
 @pytest.mark.parametrize("B,k,S,j,prefill", [
-    # j: stream lengths; without a prefill all j + 1 rows are the pass's own.  Rows of an XCD, row tiles
+    # (from 200 drafts on: one kernel)  j: stream lengths; without a prefill all j + 1 rows are the pass's own.  Rows of an XCD, row tiles
     (1, 1, 5, (0, 0), False),           # one stream row, one slot
     (1, 15, 40, (31, 31), True),        # 16, one
     (1, 16, 40, (15, 15), False),       # 16 + 16, two; the slots are the second query tile
@@ -34,6 +34,9 @@ def model(seed=31):
     (24, 10, 30, (0, 10), False),       # up to 63, four
     (40, 10, 64, (20, 140), True),      # 55, four
     (64, 7, 70, (0, 60), True),         # 64: 512 rows, the most
+    (7, 29, 90, (0, 12), False),        # up to 42, three; one sequence to an XCD
+    (8, 31, 33, (31, 31), False),       # 32 + 31, four: the most a sequence can have
+    (17, 12, 260, (250, 290), True),    # several chunks of keys a wave
     (2, 12, 260, (250, 290), True),     # several chunks of keys a wave
 ])
 def test_against_oracle(B, k, S, j, prefill):
@@ -67,7 +70,7 @@ def draft(ses, dd, B, k, lens, fresh):
     return dr.cpu().numpy(), z.cpu().numpy()
 
 
-@pytest.mark.parametrize("B,k,j,options", [(1, 5, (3, 3), {}), (11, 10, (0, 10), {}), (24, 10, (0, 10), {}), (7, 9, (0, 9), FP8_KV)])
+@pytest.mark.parametrize("B,k,j,options", [(8, 25, (3, 3), {}), (20, 10, (0, 10), {}), (24, 10, (0, 10), {}), (23, 9, (0, 9), FP8_KV)])
 def test_one_launch_and_waits_given_up(B, k, j, options):
     """One launch of the decoder; the same bits from its second run; with the option off separate launches, the same but for the order of sums."""
     ses, dd, toks, lens = open_pass(B, k, j, 200 + B, options)
@@ -87,9 +90,17 @@ def test_one_launch_and_waits_given_up(B, k, j, options):
         assert np.abs(z - other[1]).max() <= px.LOGIT_TOL
 
 
+@pytest.mark.parametrize("B,k,one", [(1, 5, 0), (19, 10, 0), (22, 9, 0), (20, 10, 1)])
+def test_fewer_than_200_drafts_keep_the_launches(B, k, one):
+    ses, dd, _, lens = open_pass(B, k, (0, 9), 300 + B)
+    n, _ = resident_launches(ses, lambda: draft(ses, dd, B, k, lens, False))
+    ses.close()
+    assert n == one
+
+
 def test_short_cache_gives_pad_drafts():
     """A cache loaded more than a row short of the stream: no place for that sequence's slots; the others' are what they were."""
-    B, k = 4, 5
+    B, k = 20, 10
     ses, dd, toks, lens = open_pass(B, k, (6, 9), 77)
     sd.specdec_prefill(ses.ctx, sd.SPECDEC_DRAFTER)
     L = int(lens.max()) + 1
@@ -112,7 +123,7 @@ def test_short_cache_gives_pad_drafts():
 
 def test_replays_of_a_captured_pass():
     """set_prefix, draft and its statistics as a graph: every replay, other work between them, has the eager pass's bits."""
-    B, k = 9, 10
+    B, k = 20, 10
     ses, dd, toks, lens = open_pass(B, k, (12, 40), 78)
     sd.specdec_prefill(ses.ctx, sd.SPECDEC_DRAFTER)
     L = int(lens.max())
