@@ -84,7 +84,7 @@ struct Model {
   int* pl_err = nullptr;              // its flags (PlArgs::err), behind them the per-XCD one's (XcdArgs::err)
   char* pl_exch = nullptr;            // exchange buffers, its or the per-XCD one's (xcd_core.h); null: dimensions they do not support
   int pl_rows = 0;                    // rows they are sized for, its
-  int xcd_rows = 0;                   // rows that skp holds twice for the other one
+  int xcd_rows = 0;                   // rows that skp holds twice for the other one (xcd_needs)
   char* xcd_stream = nullptr;         // the layers' weights as the per-XCD decoder streams them (null: no pass of more than a few rows of 512)
   float* xcd_vecs = nullptr;          // and their column vectors
   bf16* xb = nullptr;        // [Rpass][d]
@@ -300,10 +300,8 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   t.xv = cv.take<bf16>(t.xkv_layer * d->dec_layers);
   t.x = cv.take<float>(Rpass * D);
   t.x2 = cv.take<float>(32 * D);
-  // (places of a sequence in its passes: at d = 512 the drafter's and prefill's too)
-  const int xcd_T = D == 512 ? std::max(c->Tmax, std::min(c->lim.max_tgt + 1, sd::xcd_group_rows_most(512))) : c->lim.k_max + 1;
-  t.xcd_rows = sd::persist_supported(d->dec_layers, (int)D, (int)F) &&
-                       sd::xcd_rows_most((int)Bm, xcd_T, (int)D) > 512 ? 8 * sd::xcd_group_rows_most((int)D) : 512;
+  const sd::XcdRoom room = sd::xcd_room((int)Bm, c->lim.k_max, c->lim.max_tgt, (int)D, (int)F);
+  t.xcd_rows = sd::persist_supported(d->dec_layers, (int)D, (int)F) ? std::max(room.rows, 512) : 512;
   t.skp = cv.take<float>((size_t)2 * t.xcd_rows * D);   // (or the one-kernel decoder's sum and its residual)
   static_assert(2 * sd::kSk2MaxParts * 32 <= 2 * 512 && persist_rows(512) <= 512 && persist_rows(1024) <= 512, "both fit");
   t.hx = cv.take<float>(Bm * (size_t)c->lim.k_max * D);
@@ -346,7 +344,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     // drafter's workspace has the place for the copy of the weights, which it does not use, and a verifier's buffers that a drafter's rows need.)
     const bool per_xcd = sd::xcd_copy_rows_most((int)Bm, c->lim.k_max + 1, (int)D) > (D == 512 ? sd::kXcdFewRows : (int)persist_rows((int)D));
     const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F);
-    const size_t xcd = D == 512 || per_xcd ? sd::xcd_exch_most((int)Bm, xcd_T, (int)D, (int)F) : 0;
+    const size_t xcd = D == 512 || per_xcd ? room.exch : 0;
     t.pl_exch = cv.take<char>(one > xcd ? one : xcd);
     if (per_xcd) t.xcd_stream = cv.take<char>(sd::xcd_stream_bytes(d->dec_layers, (int)D, (int)F));   // (few rows of 512: without it)
     if (per_xcd || D == 512) t.xcd_vecs = cv.take<float>(sd::xcd_vec_bytes(d->dec_layers, (int)D) / sizeof(float));
@@ -631,6 +629,12 @@ int stream_cus(hipStream_t st) {
   return n;
 }
 
+// Whether the pass is planned (here) and the model's workspace has room for it.
+bool xcd_takes(const Model& m, sd::XcdArgs& x) {
+  const sd::XcdRoom n = sd::xcd_needs(x.B, x.T, m.d.d_model, m.d.d_ffn);
+  return n.rows > 0 && n.rows <= m.xcd_rows && sd::xcd_plan(x, m.d.d_model, m.d.d_ffn) > 0;
+}
+
 // cus: compute units the pass's stream has.  few: the E4M3 copies of the weights, if the model has them.
 Way one_kernel_way(const Model& m, int B, int T, bool few, int cus) {
   sd::PlArgs p{};
@@ -639,7 +643,7 @@ Way one_kernel_way(const Model& m, int B, int T, bool few, int cus) {
   x.R = B * T; x.T = T; x.B = B; x.H = m.d.n_heads;
   const int D = m.d.d_model, F = m.d.d_ffn, R = B * T;
   const int blocks = R <= m.pl_rows ? sd::persist_plan(p, D, F) : 0;
-  const bool xcd = cus >= sd::kPlBlocks && !(m.fp8 && few) && R <= m.xcd_rows && sd::xcd_plan(x, D, F) > 0;
+  const bool xcd = cus >= sd::kPlBlocks && !(m.fp8 && few) && xcd_takes(m, x);
   if (xcd && D == 512 && m.xcd_vecs && (R <= sd::kXcdFewRows || !x.copy)) return Way::xcd_few;
   if (blocks > 0 && cus >= blocks) return Way::gpu;
   return xcd && x.copy && m.xcd_stream ? Way::xcd : Way::launches;
@@ -655,7 +659,7 @@ Way draft_way(const Model& m, int B, int fresh, int k, int cus) {
   // Sums are added in another order than by the launches, so a draft between two logits as good as equal may be the other one: 4 of 2400, whose
   // logits were within 1.1e-3 of 1.7.  Passes of fewer than 200 drafts, where one such is a share that shows, keep the launches and their bits.
   if (B * k < 200) return Way::launches;
-  const bool xcd = m.d.d_model == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && x.R <= m.xcd_rows && sd::xcd_plan(x, 512, m.d.d_ffn) > 0;
+  const bool xcd = m.d.d_model == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && xcd_takes(m, x);
   return xcd && x.RP <= (fresh > 1 ? 128 : 144) ? Way::xcd_few : Way::launches;
 }
 
@@ -665,7 +669,7 @@ Way draft_way(const Model& m, int B, int fresh, int k, int cus) {
 Way prefill_way(const Model& m, int B, int T, int cus) {
   sd::XcdArgs x{};
   x.R = B * T; x.T = T; x.B = B; x.H = m.d.n_heads;
-  const bool xcd = m.d.d_model == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && x.R <= m.xcd_rows && sd::xcd_plan(x, 512, m.d.d_ffn) > 0;
+  const bool xcd = m.d.d_model == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && xcd_takes(m, x);
   return xcd && x.RP <= (B < 4 ? 80 : 112) ? Way::xcd_few : Way::launches;
 }
 
@@ -731,7 +735,7 @@ int decoder_layers_persist(specdec_ctx* c, Model& m, Way way, int B, int T, bool
     a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
     if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
     a.exch = m.pl_exch; a.err = persist_flags(way, m);
-    LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::xcd_decoder(st, a, m.d.d_model, m.d.d_ffn, c->give_up));
+    LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::xcd_decoder(st, a, m.xcd_rows, m.d.d_model, m.d.d_ffn, c->give_up));
     return SPECDEC_OK;
   }
   sd::PlArgs a{};

@@ -6,6 +6,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include "xcd_room.h"
+
 namespace sd {
 
 typedef __bf16 bf16;
@@ -279,7 +281,7 @@ struct XcdArgs {
   const float* x;
   const bf16* xb;
   float* y;
-  float* resid;                           // [8 * 64, beyond 64 rows of a group 8 * xcd_group_rows_most][d], scratch
+  float* resid;                           // [xcd_needs rows][d], scratch
   bf16 *kc, *vc;
   const void *xk, *xv;
   const float *xk_scale, *xv_scale;
@@ -298,15 +300,12 @@ constexpr int kXcdFewRows = 63;           // of a verification pass that reads t
 size_t xcd_stream_bytes(int layers, int d, int F);
 size_t xcd_vec_bytes(int layers, int d);
 hipError_t xcd_pack(hipStream_t st, const PlLayer* layers, int n, int d, char* stream, float* vecs);
-// rows of the largest pass of up to max_batch sequences of up to max_T rows each that it takes; from the copy of the weights
-int xcd_rows_most(int max_batch, int max_T, int d);
+// rows of the largest pass of up to max_batch sequences of up to max_T rows each that it takes from the copy of the weights
 int xcd_copy_rows_most(int max_batch, int max_T, int d);
-int xcd_group_rows_most(int d);   // rows of a group at most
-// bytes of exch for passes of up to max_batch sequences of up to max_T rows
-size_t xcd_exch_most(int max_batch, int max_T, int d, int F);
 // bytes of exch that are 0xff when a pass of a.B sequences of a.T rows starts (0: too many rows)
 size_t xcd_plan(XcdArgs& a, int d, int F);
-hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F, bool give_up);   // give_up: so that waits have to be given up
+// rows: that a.y and a.resid have room for, each (refused if xcd_needs more); give_up: so that waits have to be given up
+hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int rows, int d, int F, bool give_up);
 // ---- skinny2.hip: the same passes with sub-layers owned by head / by FFN slice (three kernels per layer) ----
 bool sk2_supported(int d, int F);
 int sk2_ffn_slices(int F);             // partial results the FFN kernel leaves (at most 16)

@@ -2,17 +2,14 @@
 // words that are their own flags, and the buffers workgroups exchange them through.
 #pragma once
 #include "attn_core.h"
+#include "xcd_room.h"
 
 namespace sd {
 
 constexpr unsigned kPoison = 0xffffffffu;   // "not there yet", in every 32-bit word of the exchange buffers when a pass starts
 __device__ __forceinline__ unsigned not_poison(unsigned u) { return u == kPoison ? 0x7fc07fc0u : u; }   // (a NaN for a NaN)
 
-// What the kernels behind them, which run a pass given up by tickets, count with, ahead of the exchange buffers (all words ~0 when a pass
-// starts): tickets drawn, and per stage the virtual workgroups that have finished it.
-constexpr int kPlLayers = 32, kPlStages = 8;
-struct PlTickets { unsigned drawn, done[kPlStages * kPlLayers]; };
-constexpr size_t kPlTicketBytes = (sizeof(PlTickets) + 255) & ~size_t(255);
+// The kernels behind them, which run a pass given up by tickets (PlTickets).
 constexpr unsigned kPlTicketSpinMax = 1u << 24;
 constexpr unsigned kPlTicketPasses = 64;    // passes that go to it once waits were given up (a wait in vain then costs 2 - 5 ms a pass)
 
@@ -59,10 +56,7 @@ __device__ __forceinline__ int pl_wave() {
 // Exchange buffers of one layer (and group), all in tiles of 16 columns, [column / 16][RP][16]: what one item produces lies together and
 // shares no line with another workgroup's stores (with rows of all columns side by side the 8- and 32-byte pieces of up to 16
 // workgroups met in every line, and a residual sum took 3 us to become visible through memory instead of 1).  Statistics likewise,
-// [chunk][RP] pairs.
-__host__ __device__ inline size_t pl_layer_bytes(int RP, int d, int F) {
-  return (size_t)RP * (3 * (2 * d + d / 2) + 6 * 2 * d + 2 * F);
-}
+// [chunk][RP] pairs.  (pl_layer_bytes of them.)
 struct PlExch {   // (only the layer's base stays in registers)
   char* base;
   int row;        // bytes of a buffer of RP rows of d

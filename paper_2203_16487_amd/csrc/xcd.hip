@@ -70,10 +70,6 @@ hipError_t xcd_pack(hipStream_t st, const PlLayer* layers, int n, int d, char* s
 
 namespace xcd {
 // ---- launcher ------------------------------------------------------------------------------
-static int pl_group_rows(int B, int T) { return ((B + kPlGroups - 1) / kPlGroups * T + 15) & ~15; }
-// Tickets, and exchange buffers of two layers for every group.
-static size_t pl_exch_bytes(int B, int RP, int d, int F, int layers) { return kPlTicketBytes + (size_t)(B < kPlGroups ? B : kPlGroups) * layers * pl_layer_bytes(RP, d, F); }
-
 // (each in a file of its own: they take a minute to compile)
 extern template hipError_t pl_launch_both<false, 512>(hipStream_t, XcdArgs, int);
 extern template hipError_t pl_launch_both<true, 512>(hipStream_t, XcdArgs, int);
@@ -81,20 +77,14 @@ extern template hipError_t pl_launch_both<false, 1024>(hipStream_t, XcdArgs, int
 extern template hipError_t pl_launch_both<true, 1024>(hipStream_t, XcdArgs, int);
 }  // namespace xcd
 
-static int rows_most(int max_batch, int max_T, int of_group) {
+int xcd_copy_rows_most(int max_batch, int max_T, int d) {
+  const int of_group = xcd::pl_copy_rows_most(d);
   int most = 0;
   for (int T = 1; T <= max_T && T <= of_group; ++T) {
     const int B = std::min(max_batch, xcd::kPlGroups * (of_group / T));
     most = std::max(most, B * T);
   }
   return most;
-}
-int xcd_copy_rows_most(int max_batch, int max_T, int d) { return rows_most(max_batch, max_T, xcd::pl_copy_rows_most(d)); }
-int xcd_group_rows_most(int d) { return xcd::pl_rows_most(d); }
-int xcd_rows_most(int max_batch, int max_T, int d) { return rows_most(max_batch, max_T, xcd::pl_rows_most(d)); }
-size_t xcd_exch_most(int max_batch, int max_T, int d, int F) {
-  const int rows = xcd::pl_group_rows(max_batch, max_T);
-  return xcd::pl_exch_bytes(max_batch, std::min(rows, xcd::pl_rows_most(d)), d, F, 2);
 }
 size_t xcd_plan(XcdArgs& a, int d, int F) {
   a.RP = xcd::pl_group_rows(a.B, a.T);
@@ -109,9 +99,9 @@ size_t xcd_plan(XcdArgs& a, int d, int F) {
   a.form = 2 * units <= xcd::kPlMembers;
   return xcd::pl_exch_bytes(a.B, a.RP, d, F, a.RP > xcd::kPlRows ? 1 : 2);
 }
-hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int d, int F, bool give_up) {
+hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int rows, int d, int F, bool give_up) {
   if (a.R < 1 || a.T < 1 || a.T > xcd::pl_rows_most(d) || a.R != a.B * a.T || !persist_supported(a.n_layers, d, F)) return hipErrorInvalidValue;
-  if (xcd_plan(a, d, F) == 0 || (a.stream && !a.copy)) return hipErrorInvalidValue;
+  if (xcd_plan(a, d, F) == 0 || (a.stream && !a.copy) || xcd_needs(a.B, a.T, d, F).rows > rows) return hipErrorInvalidValue;
   a.tickets = reinterpret_cast<PlTickets*>(a.exch);
   a.exch += kPlTicketBytes;
   a.raised = a.err;

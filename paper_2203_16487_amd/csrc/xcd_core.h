@@ -70,7 +70,7 @@ namespace sd {
 namespace xcd {
 
 constexpr unsigned kPlSpinMax = 3u << 18;   // (0.13 - 0.3 s: 2^17 polls of the L2 take 21 - 49 ms)
-constexpr int kPlGroups = 8, kPlMembers = 32;          // XCDs; workgroups of each
+constexpr int kPlMembers = 32;          // workgroups of each XCD
 constexpr int kPlWaves = 8, kPlThreads = 64 * kPlWaves;
 static_assert(kPlGroups * kPlMembers == kPlBlocks && kPlWaves == 8, "a workgroup per CU; pairs of a row's four lanes");
 // (a word of each 8 bytes: results are stored 8 bytes at a time)
@@ -96,12 +96,6 @@ __device__ __forceinline__ void pl_again(unsigned& spins, const XcdArgs& a) {
   __builtin_amdgcn_s_sleep(1);
   asm volatile("" ::: "memory");
 }
-
-// Rows of a group: what registers and LDS hold; of d = 512 from a copy of the weights (more are read in place); what the second run's smaller
-// kernel takes.
-constexpr int pl_rows_most(int d) { return d == 512 ? 160 : 96; }
-constexpr int pl_copy_rows_most(int d) { return d == 512 ? 64 : 96; }
-constexpr int kPlRows = 64;
 
 // What depends on the dimensions and the type of the weights alone.  A chunk of weights: 16 rows (output columns) x an eighth of D of K,
 // as MFMA fragments: [K / 32][lane][8 values], lane = row + 16 (K / 8 % 4).
@@ -1369,8 +1363,10 @@ hipError_t pl_launch_both(hipStream_t st, XcdArgs a, int blocks) {
   if (e != hipSuccess) return e;
   a.raised = a.err;
   a.err += 1;
-  if (a.RP > kPlRows) return pl_launch<KV8, D, pl_rows_most(D) / 16, true>(st, a, kPlMembers * std::min(a.G, 2));
-  return pl_launch<KV8, D, 4, true>(st, a, kPlMembers * std::min(a.G, 2));
+  // (either kernel writes all of its row tiles of the residual, pl_resid_rows of them a group)
+  constexpr int kTall = pl_resid_rows(pl_rows_most(D), D), kShort = pl_resid_rows(kPlRows, D);
+  if (pl_resid_rows(a.RP, D) == kTall) return pl_launch<KV8, D, kTall / 16, true>(st, a, kPlMembers * std::min(a.G, 2));
+  return pl_launch<KV8, D, kShort / 16, true>(st, a, kPlMembers * std::min(a.G, 2));
 }
 }  // namespace xcd
 }  // namespace sd
