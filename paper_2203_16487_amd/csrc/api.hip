@@ -84,7 +84,7 @@ struct Model {
   int* pl_err = nullptr;              // its flags (PlArgs::err), behind them the per-XCD one's (XcdArgs::err)
   char* pl_exch = nullptr;            // exchange buffers, its or the per-XCD one's (xcd_core.h); null: dimensions they do not support
   int pl_rows = 0;                    // rows they are sized for, its
-  int xcd_rows = 0;                   // rows that skp holds twice for the other one (xcd_needs)
+  sd::XcdRoom room{0, 0, 0};          // bytes there are of them, rows that skp holds twice, for the other one
   char* xcd_stream = nullptr;         // the layers' weights as the per-XCD decoder streams them (null: no pass of more than a few rows of 512)
   float* xcd_vecs = nullptr;          // and their column vectors
   bf16* xb = nullptr;        // [Rpass][d]
@@ -211,7 +211,6 @@ bool desc_ok(const specdec_model_desc* d) {
          d->eos_id >= 0 && d->eos_id < d->vocab && d->pad_id >= 0 && d->pad_id < d->vocab &&
          d->mask_id >= 0 && d->mask_id < d->vocab;
 }
-constexpr long kPrefillRows = 8192;
 // Most rows of a pass the one-kernel decoder over the whole GPU is asked for.
 // At d = 512 the per-XCD one takes all rows where the stream has every compute unit and the weights are bf16.  Whole passes, whole GPU / per XCD,
 // us, 40 source tokens: 1 row 110 / 107, 6 112 / 109, 22 (two sequences) 120 / 111, 48 (three) 128 / 118, (eight) 131 / 125, 63 (one a sequence)
@@ -301,8 +300,8 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
   t.x = cv.take<float>(Rpass * D);
   t.x2 = cv.take<float>(32 * D);
   const sd::XcdRoom room = sd::xcd_room((int)Bm, c->lim.k_max, c->lim.max_tgt, (int)D, (int)F);
-  t.xcd_rows = sd::persist_supported(d->dec_layers, (int)D, (int)F) ? std::max(room.rows, 512) : 512;
-  t.skp = cv.take<float>((size_t)2 * t.xcd_rows * D);   // (or the one-kernel decoder's sum and its residual)
+  t.room.rows = sd::persist_supported(d->dec_layers, (int)D, (int)F) ? std::max(room.rows, 512) : 512;
+  t.skp = cv.take<float>((size_t)2 * t.room.rows * D);   // (or the one-kernel decoder's sum and its residual)
   static_assert(2 * sd::kSk2MaxParts * 32 <= 2 * 512 && persist_rows(512) <= 512 && persist_rows(1024) <= 512, "both fit");
   t.hx = cv.take<float>(Bm * (size_t)c->lim.k_max * D);
   if (c->fp8_kv) {
@@ -345,7 +344,8 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     const bool per_xcd = sd::xcd_copy_rows_most((int)Bm, c->lim.k_max + 1, (int)D) > (D == 512 ? sd::kXcdFewRows : (int)persist_rows((int)D));
     const size_t one = sd::persist_exch_bytes(t.pl_rows, d->dec_layers, (int)D, (int)F);
     const size_t xcd = D == 512 || per_xcd ? room.exch : 0;
-    t.pl_exch = cv.take<char>(one > xcd ? one : xcd);
+    t.room.exch = std::max(one, xcd);
+    t.pl_exch = cv.take<char>(t.room.exch);
     if (per_xcd) t.xcd_stream = cv.take<char>(sd::xcd_stream_bytes(d->dec_layers, (int)D, (int)F));   // (few rows of 512: without it)
     if (per_xcd || D == 512) t.xcd_vecs = cv.take<float>(sd::xcd_vec_bytes(d->dec_layers, (int)D) / sizeof(float));
   }
@@ -371,7 +371,7 @@ size_t carve_model(const specdec_ctx* c, const specdec_model_desc* d, void* base
     m->x = t.x; m->x2 = t.x2; m->skp = t.skp; m->hx = t.hx; m->w8 = t.w8; m->w8s = t.w8s; m->fold8 = t.fold8; m->xk8 = t.xk8; m->xv8 = t.xv8; m->xks = t.xks; m->xvs = t.xvs; m->xb = t.xb; m->q = t.q; m->att = t.att; m->hid = t.hid;
     m->part = t.part; m->row_stats = t.row_stats; m->zd = t.zd; m->rm = t.rm;
     m->slots = t.slots; m->new_rows = t.new_rows; m->pl_err = t.pl_err;
-    m->pl_layers = t.pl_layers; m->pl_exch = t.pl_exch; m->pl_rows = t.pl_rows; m->xcd_rows = t.xcd_rows;
+    m->pl_layers = t.pl_layers; m->pl_exch = t.pl_exch; m->pl_rows = t.pl_rows; m->room = t.room;
     m->xcd_stream = t.xcd_stream; m->xcd_vecs = t.xcd_vecs;
     m->ex = t.ex; m->exb = t.exb; m->eqkv = t.eqkv; m->eatt = t.eatt; m->ehid = t.ehid;
     m->elnp[0] = t.elnp[0]; m->elnp[1] = t.elnp[1]; m->efold = t.efold; m->epos = t.epos; m->erow_b = t.erow_b; m->erow_start = t.erow_start; m->en_rows = t.en_rows;
@@ -632,7 +632,7 @@ int stream_cus(hipStream_t st) {
 // Whether the pass is planned (here) and the model's workspace has room for it.
 bool xcd_takes(const Model& m, sd::XcdArgs& x) {
   const sd::XcdRoom n = sd::xcd_needs(x.B, x.T, m.d.d_model, m.d.d_ffn);
-  return n.rows > 0 && n.rows <= m.xcd_rows && sd::xcd_plan(x, m.d.d_model, m.d.d_ffn) > 0;
+  return n.rows > 0 && n.rows <= m.room.rows && n.exch <= m.room.exch && sd::xcd_plan(x, m.d.d_model, m.d.d_ffn) > 0;
 }
 
 // cus: compute units the pass's stream has.  few: the E4M3 copies of the weights, if the model has them.
@@ -731,11 +731,11 @@ int decoder_layers_persist(specdec_ctx* c, Model& m, Way way, int B, int T, bool
     a.row_b = m.rm.row_b; a.row_pos = m.rm.row_pos; a.src_len = c->st.src_len;
     if (stream) { a.causal = m.new_rows; a.live = m.rm.seq_rows; }
     a.kv_only = kv_only;
-    a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + (size_t)m.xcd_rows * m.d.d_model;
+    a.x = m.x; a.xb = m.xb; a.y = m.skp; a.resid = m.skp + (size_t)m.room.rows * m.d.d_model;
     a.kc = m.kc; a.vc = m.vc; a.xk = m.xk; a.xv = m.xv; a.kv_layer = m.kv_layer; a.xkv_layer = m.xkv_layer;
     if (m.kv8) { a.xk = m.xk8; a.xv = m.xv8; a.xk_scale = m.xks; a.xv_scale = m.xvs; }
     a.exch = m.pl_exch; a.err = persist_flags(way, m);
-    LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::xcd_decoder(st, a, m.xcd_rows, m.d.d_model, m.d.d_ffn, c->give_up));
+    LAUNCH(c, SPECDEC_KIND_RESIDENT, st, sd::xcd_decoder(st, a, m.room, m.d.d_model, m.d.d_ffn, c->give_up));
     return SPECDEC_OK;
   }
   sd::PlArgs a{};
@@ -798,11 +798,7 @@ int specdec_create(specdec_ctx** out, const specdec_limits* lim) {
   c->Lcap = (lim->max_tgt + lim->k_max + 1 + 31) & ~31;   // rows of the KV arenas (32-key chunks)
   c->Scap = (lim->max_src + 31) & ~31;
   c->n_pos = c->Lcap > c->Scap ? c->Lcap : c->Scap;
-  // A prefill pass takes as many rows as make its products large (8192 rows: 150 MB of activations for the big model),
-  // never more than the streams can hold and never fewer than a verify / draft pass needs.
-  const long pre = lim->max_batch * (long)(lim->max_tgt + 1), most = pre < kPrefillRows ? pre : kPrefillRows;
-  const long least = (long)lim->max_batch * c->Tmax;
-  c->pass_rows = most > least ? most : least;
+  c->pass_rows = sd::decoder_pass_rows(lim->max_batch, lim->k_max, lim->max_tgt);
   *out = c;
   return SPECDEC_OK;
 }
@@ -1235,13 +1231,13 @@ int specdec_prefill(specdec_ctx* c, specdec_role role, void* stream) {
   if (rc) return rc;
   Model& m = c->m[role];
   hipStream_t st = S(stream);
-  // As few passes as the activation buffers allow, all of the same size: a pass of a few rows per sequence is a chain of
+  // As few passes as the activation buffers allow: a pass of a few rows per sequence is a chain of
   // small launches that reads every weight again (32 sequences of up to 224 tokens, big model: 11 passes of 21 positions
   // 7.4 ms, 1.8 ms in one).  Rows are packed: short streams bring no padding.
   const bool packed = !c->no_ln_fold;
-  const int most = (int)(c->pass_rows / c->B), passes = (c->uncached_ub[role] + most - 1) / most;
-  const int T = passes > 0 ? (c->uncached_ub[role] + passes - 1) / passes : 0;
-  while (c->uncached_ub[role] > 0) {
+  const sd::PrefillPasses pass = sd::prefill_passes(c->uncached_ub[role], c->pass_rows, c->B, c->lim.max_tgt);
+  const int T = pass.T;
+  for (int i = 0; i < pass.passes; ++i) {
     Way way;
     const bool one = persist_ok(c, m, st, [&](int cus) { return prefill_way(m, c->B, T, cus); }, &way);
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_stream(st, c->st, m.rm, role, c->B, T, 0, m.d.mask_id, m.d.pad_id, m.d.vocab,
@@ -1250,7 +1246,6 @@ int specdec_prefill(specdec_ctx* c, specdec_role role, void* stream) {
     rc = one ? decoder_layers_persist(c, m, way, c->B, T, false, true, true, st) : decoder_layers(c, m, c->B, T, st, true, 0, packed, true);
     if (rc) return rc;
     HIPCHK(c, sd::advance_cached(st, c->st, role, m.new_rows, c->B, one ? persist_flags(way, m) + 1 : nullptr));
-    c->uncached_ub[role] -= T;
   }
   c->uncached_ub[role] = 0;
   c->trusted[role] = false;

@@ -304,8 +304,8 @@ hipError_t xcd_pack(hipStream_t st, const PlLayer* layers, int n, int d, char* s
 int xcd_copy_rows_most(int max_batch, int max_T, int d);
 // bytes of exch that are 0xff when a pass of a.B sequences of a.T rows starts (0: too many rows)
 size_t xcd_plan(XcdArgs& a, int d, int F);
-// rows: that a.y and a.resid have room for, each (refused if xcd_needs more); give_up: so that waits have to be given up
-hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int rows, int d, int F, bool give_up);
+// room: bytes of a.exch, rows of a.y and of a.resid (refused if xcd_needs more); give_up: so that waits have to be given up
+hipError_t xcd_decoder(hipStream_t st, XcdArgs a, const XcdRoom& room, int d, int F, bool give_up);
 // ---- skinny2.hip: the same passes with sub-layers owned by head / by FFN slice (three kernels per layer) ----
 bool sk2_supported(int d, int F);
 int sk2_ffn_slices(int F);             // partial results the FFN kernel leaves (at most 16)

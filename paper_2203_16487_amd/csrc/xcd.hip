@@ -99,9 +99,10 @@ size_t xcd_plan(XcdArgs& a, int d, int F) {
   a.form = 2 * units <= xcd::kPlMembers;
   return xcd::pl_exch_bytes(a.B, a.RP, d, F, a.RP > xcd::kPlRows ? 1 : 2);
 }
-hipError_t xcd_decoder(hipStream_t st, XcdArgs a, int rows, int d, int F, bool give_up) {
+hipError_t xcd_decoder(hipStream_t st, XcdArgs a, const XcdRoom& room, int d, int F, bool give_up) {
   if (a.R < 1 || a.T < 1 || a.T > xcd::pl_rows_most(d) || a.R != a.B * a.T || !persist_supported(a.n_layers, d, F)) return hipErrorInvalidValue;
-  if (xcd_plan(a, d, F) == 0 || (a.stream && !a.copy) || xcd_needs(a.B, a.T, d, F).rows > rows) return hipErrorInvalidValue;
+  const XcdRoom need = xcd_needs(a.B, a.T, d, F);
+  if (xcd_plan(a, d, F) == 0 || (a.stream && !a.copy) || need.rows > room.rows || need.exch > room.exch) return hipErrorInvalidValue;
   a.tickets = reinterpret_cast<PlTickets*>(a.exch);
   a.exch += kPlTicketBytes;
   a.raised = a.err;

@@ -53,4 +53,20 @@ inline XcdRoom xcd_room(int max_batch, int k_max, int max_tgt, int d, int F) {
   return r;
 }
 
+// Rows that the activation buffers of a decoder pass hold.  A prefill pass takes as many rows as make its products large (8192 rows: 150 MB of
+// activations for the big model), never more than the streams can hold and never fewer than a verify / draft pass needs.
+inline long decoder_pass_rows(int max_batch, int k_max, int max_tgt) {
+  return std::max(std::min(max_batch * (long)(max_tgt + 1), 8192L), max_batch * (long)(2 * k_max + 1));
+}
+
+// Prefill of B streams of which at most `uncached` tokens each (no stream has more than max_tgt + 1, whatever the bound) are not cached: as few
+// passes as the buffers allow, all of the same number of places.
+struct PrefillPasses { int passes, T; };
+inline PrefillPasses prefill_passes(int uncached, long pass_rows, int B, int max_tgt) {
+  const int rows = std::min(uncached, max_tgt + 1), most = (int)(pass_rows / B);
+  if (rows <= 0) return PrefillPasses{0, 0};
+  const int passes = (rows + most - 1) / most;
+  return PrefillPasses{passes, (rows + passes - 1) / passes};
+}
+
 }  // namespace sd

@@ -7,6 +7,7 @@ import torch
 import cases
 import gpu_harness as gh
 from paper_2203_16487_amd import binding as sd
+from paper_2203_16487_amd import synth
 from test_gpu_one_kernel import check, desc, resident_launches
 
 pytestmark = pytest.mark.gpu
@@ -65,3 +66,42 @@ def test_behind_a_cache():
     assert launches == 1
     check(case, gh.gpu_verify(ses, case))
     ses.close()
+
+
+def test_bound_beyond_what_a_stream_can_have():
+    """Four commits without a draft between them: the bound on what the drafter has not cached is 45 tokens, a stream has 34 at most.  The prefill that
+    the draft begins with has places for these, and caches what one after set_stream does."""
+    B, k, max_tgt, seed = 9, 10, 33, 860
+    vd, dd = (synth.ModelDesc(0, layers, 512, 8, 2048, 1003, 20, 64).resolved() for layers in (1, 2))
+    ses = sd.Session(16, k, 20, max_tgt, fill=0xFF)
+    ses.bind_model(sd.SPECDEC_VERIFIER, vd, ses.upload_weights(synth.make_weights(vd, seed, std=0.02)))
+    ses.bind_model(sd.SPECDEC_DRAFTER, dd, ses.upload_weights(synth.make_weights(dd, seed, tag="drafter", std=0.02)))
+    dev = ses.device
+    sd.specdec_begin(ses.ctx, B, 30)
+    for role, tag in ((sd.SPECDEC_VERIFIER, 1), (sd.SPECDEC_DRAFTER, 2)):
+        sd.specdec_set_memory(ses.ctx, role, ses.bf16(synth.make_memory(seed + tag, B, 20, 512)), ses.i32(np.full(B, 20)))
+    acc, nxt, out_len = (torch.zeros(B, dtype=torch.int32, device=dev) for _ in range(3))
+    for i in range(4):
+        sd.specdec_verify(ses.ctx, ses.i32(synth.random_tokens(seed + i, "drafts", (B, k), vd, full_vocab=True)), k, 3, 1.0, acc, nxt)
+        sd.specdec_commit(ses.ctx, acc, nxt)
+    toks = torch.zeros((B, max_tgt), dtype=torch.int32, device=dev)
+    sd.specdec_get_output(ses.ctx, toks, out_len)
+    dr = torch.zeros((B, k), dtype=torch.int32, device=dev)
+    z = torch.zeros((B, k, dd.vocab), dtype=torch.float32, device=dev)
+    L = int(out_len.max()) + 1
+    K, V = (torch.zeros((2, B, L, 512), dtype=torch.bfloat16, device=dev) for _ in range(2))
+    got = []
+    for again in (False, True):
+        if again:
+            stream = torch.cat([torch.full((B, 1), dd.bos_id, dtype=torch.int32, device=dev), toks[:, :L - 1]], 1).contiguous()
+            sd.specdec_set_stream(ses.ctx, stream, out_len)
+            sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_SMALL_BATCH_KERNELS, 0)
+            sd.specdec_prefill(ses.ctx, sd.SPECDEC_DRAFTER)
+        n, _ = resident_launches(ses, lambda: sd.specdec_draft(ses.ctx, k, dr, z))
+        assert n == (0 if again else 1)
+        sd.specdec_get_cache(ses.ctx, sd.SPECDEC_DRAFTER, K, V)
+        live = (torch.arange(L, device=dev)[None, :] <= out_len[:, None])[None, :, :, None]
+        got.append([(t.float() * live).cpu().numpy() for t in (K, V)] + [z.cpu().numpy()])
+    ses.close()
+    for a, b in zip(*got):
+        assert np.isfinite(a).all() and np.abs(a - b).max() <= 3e-2

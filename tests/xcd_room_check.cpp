@@ -36,7 +36,16 @@ int main() {
             for (int T = 1; T <= k_max + 1; ++T) check("verify", room, max_batch, k_max, max_tgt, B, T, d, 4 * d);
             if (d != 512) continue;
             for (int T = k_max + 2; T <= 2 * k_max + 1; ++T) check("draft", room, max_batch, k_max, max_tgt, B, T, d, 4 * d);
-            for (int T = 1; T <= max_tgt + 1 && T <= 160; ++T) check("prefill", room, max_batch, k_max, max_tgt, B, T, d, 4 * d);
+            // (the bound on what is not cached grows with every commit, beyond what a stream can have)
+            const long pass_rows = sd::decoder_pass_rows(max_batch, k_max, max_tgt);
+            for (int uncached = 1; uncached <= 2 * max_tgt + 160; uncached += uncached < 200 ? 1 : 37) {
+              const sd::PrefillPasses p = sd::prefill_passes(uncached, pass_rows, B, max_tgt);
+              if (p.T < 1 || (long)p.T * B > pass_rows || p.T > max_tgt + 1 || p.T * p.passes < (uncached < max_tgt + 1 ? uncached : max_tgt + 1)) {
+                printf("prefill of %d, limits (%d, %d, %d), %d sequences: %d passes of %d\n", uncached, max_batch, k_max, max_tgt, B, p.passes, p.T);
+                exit(1);
+              }
+              check("prefill", room, max_batch, k_max, max_tgt, B, p.T, d, 4 * d);
+            }
           }
         }
   printf("%ld passes\n", checked);
