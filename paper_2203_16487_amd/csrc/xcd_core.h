@@ -42,7 +42,10 @@
 // LayerNorm is folded into the products as in the general kernels (gemm.hip), with statistics per 16 columns; the fp32 residual
 // of a workgroup's columns stays in its LDS.  The exchange buffers of two layers are used in turn.  Those of layer l - 1 are
 // filled with kPoison again once the output product of layer l's self-attention has all its rows: every workgroup has then
-// stored its queries, keys and values of layer l, after the last it read of layer l - 1; and whoever waits for a word of
+// stored its queries, keys and values of layer l, after the last it read of layer l - 1 (the units of a sequence's eight heads wait for all
+// columns of one key and value of the pass at least: of a sequence without rows, which a prefill pass may have, those of its first place, which
+// nothing else needs; before, a group of such sequences alone left the workgroups behind that make keys and values alone, and one of them
+// could find what it was still to read filled again); and whoever waits for a word of
 // layer l + 1 has had rows of layer l from every workgroup, stored after the refill was acknowledged.  The pass's first kernel fills both layers'; of
 // more than 64 rows of a group the first layer's alone, the other half in the first layer as in later ones (d = 1024, launches / both / one: 48 x 11
 // rows 560 / 506 / 490, 64 x 11 589 / 555 / 541; 6 rows of d = 512 both 110.4, one 111.3).
@@ -835,11 +838,14 @@ __device__ __forceinline__ void pl_attn_wave(const XcdArgs& a, const PlExch& ex,
                      "=&v"(t_.vf[2]), "=&v"(t_.vf[3]), "=&v"(f[0]), "=&v"(f[1])
                    : "v"(pk[0]), "v"(pk[1]), "v"(pk[2]), "v"(pk[3]), "v"(pv[0]), "v"(pv[1]), "v"(pv[2]), "v"(pv[3]), "v"(pq[0]), "v"(pq[1])
                    : "memory");
-      bool bad = pl_missing(f[0]) || pl_missing(f[1]);   // (keys at and beyond nkey are masked later: not waited for)
+      // (keys at and beyond nkey are masked later: not waited for, but the first place's of a sequence without rows is, for the sake of the
+      // refill)
+      const int end = SLOTS ? max(nkey, j + 1) : nkey;
+      bool bad = pl_missing(f[0]) || pl_missing(f[1]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) bad |= key_k(c0, i >> 1) >= j && key_k(c0, i >> 1) < nkey && pl_missing(t_.kf[i]);
+      for (int i = 0; i < 4; ++i) bad |= key_k(c0, i >> 1) >= j && key_k(c0, i >> 1) < end && pl_missing(t_.kf[i]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) bad |= key_v(c0, i) >= j && key_v(c0, i) < nkey && pl_missing(t_.vf[i]);
+      for (int i = 0; i < 4; ++i) bad |= key_v(c0, i) >= j && key_v(c0, i) < end && pl_missing(t_.vf[i]);
       if (!__builtin_amdgcn_ballot_w64(bad)) break;
       pl_again(spins, a);
     }

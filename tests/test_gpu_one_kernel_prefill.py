@@ -1,5 +1,7 @@
 """Prefill passes of few rows (d_model 512) as one kernel, each XCD on sequences of its own, which ends where the last layer's keys and values are
 stored: what it caches against the oracle, for streams of different lengths, empty ones among them; waits given up; more rows than it takes."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -105,3 +107,35 @@ def test_bound_beyond_what_a_stream_can_have():
     ses.close()
     for a, b in zip(*got):
         assert np.isfinite(a).all() and np.abs(a - b).max() <= 3e-2
+
+
+@pytest.mark.parametrize("lens,T", [
+    ([0, 12, 5], 12),                     # an XCD's only stream is empty; eight units of attention
+    ([0] * 8, 16),
+    ([0, 0, 7, 16, 0, 3, 1, 0, 9], 16),   # two empty ones to an XCD, and one
+    ([0], 80),                            # places of five query tiles
+])
+def test_streams_without_rows(lens, T):
+    """No row of the pass to an XCD, in a model of six layers, whose exchange buffers are used in turn: waits end (one in vain takes 0.1 s), and what is
+    cached and verified for the others is what launches give."""
+    B, lens = len(lens), np.array(lens, np.int32)
+    case = cases.make_verify_case(desc(512, 6), seed=870 + B, B=B, S=20, k=4, beta=3, tau=1.0, len_lo=T, len_hi=T, ragged_src=True)
+    ses = gh.open_verifier(case, fill=0xFF)
+    outs = []
+    for small in (0, 1):
+        sd.specdec_configure(ses.ctx, sd.SPECDEC_OPT_SMALL_BATCH_KERNELS, small)
+        for n in [case.lens] + [lens] * 20:   # (first with rows everywhere: kernels loaded)
+            sd.specdec_set_stream(ses.ctx, ses.i32(case.tokens), ses.i32(n))
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            launches, _ = resident_launches(ses, lambda: sd.specdec_prefill(ses.ctx, sd.SPECDEC_VERIFIER))
+            torch.cuda.synchronize()
+            assert launches == small
+            if n is lens:
+                assert time.perf_counter() - t < 0.05
+        K, V = gh.gpu_cache(ses, case, T)
+        live = (np.arange(T)[None, :] < lens[:, None])[None, :, :, None]
+        outs.append((K * live, V * live, gh.gpu_verify(ses, case)["logits"]))
+    ses.close()
+    for a, b, tol in zip(*outs, (3e-2, 3e-2, 2 * max(2e-2, 0.04 * float(outs[0][2].std())))):   # (logits: either within half of it of the oracle's)
+        assert np.isfinite(a).all() and np.abs(a - b).max() <= tol
