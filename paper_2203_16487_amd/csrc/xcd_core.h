@@ -1240,7 +1240,10 @@ __global__ __launch_bounds__(kPlThreads) void pl_decoder_kernel(XcdArgs a) {
       const int bytes = (int)(pl_layer_bytes(a.RP, D, 4 * D) / kPlMembers);
       for (int o = (wave * 64 + pl_lane()) * 16; o < bytes; o += kPlWaves * 1024) *reinterpret_cast<u32x4*>(before.base + at.w * bytes + o) = poison;
     }
-    // (what every wave asks for and stores here is done with when it has its rows of stage 3, for the workgroup at the barriers there)
+    // (what every wave asks for and stores here is done with when it has its rows of stage 3, for the workgroup at the barriers there.  Where units
+    // form their queries nothing is waited for in stage 3, and in stage 4 by the workgroups of units alone: there it is done with in stage 5 when the
+    // wave has its statistics, which it requests behind all this, and at the barrier behind them, ahead of all that the workgroup stores in that stage.
+    // Nobody can be in the next layer before: its first product takes rows of stage 7 from every workgroup.)
     if (!TICKETS && l + 1 < a.n_layers) pl_ask_vectors<D, MR>(a, L, l + 1, at.w, wave);
   };
   if constexpr (!TICKETS) {
