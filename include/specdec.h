@@ -201,7 +201,7 @@ int specdec_set_prefix(specdec_ctx* ctx, specdec_role role, const int32_t* token
  * activation buffers allow.  Needed after specdec_set_stream unless a cache is loaded.  With
  * d_model 512 / d_ffn 2048 passes of few rows (of a group at most 112, 80 of up to three sequences)
  * run as one kernel, under the rules of specdec_verify; should its second run not complete either,
- * nothing counts as cached. */
+ * nothing counts as cached: specdec_verify then reports it, and specdec_set_stream starts anew. */
 int specdec_prefill(specdec_ctx* ctx, specdec_role role, void* stream);
 
 /* ---- the hot path -------------------------------------------------------------------- */
@@ -210,9 +210,11 @@ int specdec_prefill(specdec_ctx* ctx, specdec_role role, void* stream);
  * tokens the drafter has not cached yet are processed (causally) in the same pass and
  * cached; mask slots attend to the whole stream and to all k slots.
  * With d_model 512 / d_ffn 2048 a pass whose places (k and the most stream tokens a sequence can
- * bring: all that commits since the drafter's latest pass may have appended, one behind a loaded
+ * bring: all that commits since the drafter's latest pass may have appended, each its block's k + 1, but k_max + 1 behind
+ * specdec_load_cache and from the first captured pass or commit of the context on; one in the first pass behind a loaded
  * cache) are few (at most 144 to a group, 128 where a sequence can bring several) runs its decoder layers as one kernel, each XCD on sequences of its own, under the
- * rules of specdec_verify; should its second run not complete either, every draft is pad_id.
+ * rules of specdec_verify; should its second run not complete either, every draft is pad_id.  (The stream tokens that a
+ * sequence with pad drafts brought are taken up by later passes.)
  * logits_or_null: optional device fp32 [B, k, V] receiving the slots' logits (parity mode; slow). */
 int specdec_draft(specdec_ctx* ctx, int32_t k, int32_t* draft, float* logits_or_null, void* stream);
 

@@ -133,8 +133,12 @@ struct specdec_ctx {
   const bf16 *hw1 = nullptr, *hb1 = nullptr, *hw2 = nullptr, *hb2 = nullptr;
   bool last_draft_by_heads = false;
   int S_cur = 0;      // S_max of the current memory
-  int uncached_ub[2] = {0, 0};
+  // Stream tokens a model has not cached, at most: every commit adds k_max + 1 of them.  uncached_block: the drafter's where it is known what was
+  // cached and committed since, a commit's own block (drafter_uncached).
+  int uncached_ub[2] = {0, 0}, uncached_block = 0;
   bool trusted[2] = {false, false};
+  bool short_cache = false;   // the drafter's loaded cache may be short of the stream, and its passes since may still be catching up
+  bool replays = false;       // a drafter's pass or a commit was captured: the host does not see what runs
   // event timing of one kernel kind
   int prof_kind = SPECDEC_KIND_NONE;
   std::vector<hipEvent_t> prof_ev;
@@ -635,6 +639,26 @@ bool xcd_takes(const Model& m, sd::XcdArgs& x) {
   return n.rows > 0 && n.rows <= m.room.rows && n.exch <= m.room.exch && sd::xcd_plan(x, m.d.d_model, m.d.d_ffn) > 0;
 }
 
+// Whether what is issued on this stream is captured (result false: the HIP runtime will not say, and it is taken for captured).
+bool capture_state(hipStream_t st, bool* capturing) {
+  *capturing = false;
+  if (!st || st == hipStreamLegacy) return true;   // (which cannot be)
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  const bool known = hipStreamIsCapturing(st, &status) == hipSuccess;
+  *capturing = !known || status != hipStreamCaptureStatusNone;
+  return known;
+}
+
+// Stream tokens of a sequence that the drafter has not cached, at most.  A commit appends no more than its block, k + 1 tokens, and the drafter's pass
+// has a place for each, few of them for small blocks; but what a captured pass meets when it is replayed is not what the host has seen at its
+// capture, and a pass behind a cache that was loaded short of the stream takes up what it has places for: there every commit counts for the largest block.
+int drafter_uncached(specdec_ctx* c, hipStream_t st) {
+  bool captures;
+  (void)capture_state(st, &captures);
+  c->replays |= captures;
+  return c->short_cache || c->replays ? c->uncached_ub[1] : c->uncached_block;
+}
+
 // cus: compute units the pass's stream has.  few: the E4M3 copies of the weights, if the model has them.
 Way one_kernel_way(const Model& m, int B, int T, bool few, int cus) {
   sd::PlArgs p{};
@@ -686,17 +710,13 @@ bool persist_ok(specdec_ctx* c, const Model& m, hipStream_t st, F way_of, Way* w
   const Way found = way_of(std::min(cus, stream_cus(st)));   // (all of a way's workgroups run at once)
   if (found == Way::launches) return false;
   if (c->persist_refused || (c->persist_dev >= 0 && c->persist_dev != dev)) return false;
-  bool capturing = false;
-  if (st && st != hipStreamLegacy) {   // (which cannot be captured)
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &status) != hipSuccess) return false;
-    capturing = status != hipStreamCaptureStatusNone;
-  }
+  bool captures;
+  if (!capture_state(st, &captures)) return false;
   std::lock_guard<std::mutex> guard(persist_mutex);
   PersistGpu& o = persist_gpu[dev];
   const bool user = c->persist_dev == dev;
   // (for the whole run: the two ways add in different orders, and which one a pass takes is not to change with the life of others)
-  c->persist_refused = (o.users > (user ? 1 : 0) && (o.captured || capturing || st != o.stream || st == hipStreamPerThread)) ||
+  c->persist_refused = (o.users > (user ? 1 : 0) && (o.captured || captures || st != o.stream || st == hipStreamPerThread)) ||
                        (!o.users && !persist_open(o, dev));
   if (c->persist_refused) return false;
   if (!user) {
@@ -704,7 +724,7 @@ bool persist_ok(specdec_ctx* c, const Model& m, hipStream_t st, F way_of, Way* w
     c->persist_dev = dev;
   }
   o.stream = st;
-  o.captured |= capturing;
+  o.captured |= captures;
   *way = found;
   return true;
 }
@@ -1033,7 +1053,8 @@ int specdec_begin(specdec_ctx* c, int32_t B, int32_t max_new, void* stream) {
   c->last_T = 0;
   c->last_k_draft = 0;
   c->uncached_ub[0] = 0;
-  c->uncached_ub[1] = 1;
+  c->uncached_ub[1] = c->uncached_block = 1;
+  c->short_cache = false;
   c->trusted[0] = c->trusted[1] = false;
   c->persist_refused = false;
   c->m[0].has_memory = c->m[1].has_memory = false;
@@ -1170,6 +1191,7 @@ static int load_cache(specdec_ctx* c, specdec_role role, const void* k_cache, co
                            static_cast<bf16*>(const_cast<void*>(v_cache)), m.kv_layer, m.d.dec_layers, m.d.n_heads, c->Lcap, L_max, n, role,
                            tokens, c->max_new, c->lim.max_tgt}, c->B));
   c->trusted[role] = true;
+  if (role == SPECDEC_DRAFTER) c->short_cache = true;
   return SPECDEC_OK;
 }
 
@@ -1192,7 +1214,8 @@ static int check_stream(specdec_ctx* c, const int32_t* tokens, const int32_t* le
 }
 static void stream_replaced(specdec_ctx* c, int32_t L_max) {
   c->uncached_ub[0] = L_max;
-  c->uncached_ub[1] = L_max + 1;
+  c->uncached_ub[1] = c->uncached_block = L_max + 1;
+  c->short_cache = false;
   c->trusted[0] = c->trusted[1] = false;
   c->last_T = 0;
 }
@@ -1235,7 +1258,8 @@ int specdec_prefill(specdec_ctx* c, specdec_role role, void* stream) {
   // small launches that reads every weight again (32 sequences of up to 224 tokens, big model: 11 passes of 21 positions
   // 7.4 ms, 1.8 ms in one).  Rows are packed: short streams bring no padding.
   const bool packed = !c->no_ln_fold;
-  const sd::PrefillPasses pass = sd::prefill_passes(c->uncached_ub[role], c->pass_rows, c->B, c->lim.max_tgt);
+  const int uncached = role == SPECDEC_DRAFTER ? drafter_uncached(c, st) : c->uncached_ub[role];
+  const sd::PrefillPasses pass = sd::prefill_passes(uncached, c->pass_rows, c->B, c->lim.max_tgt);
   const int T = pass.T;
   for (int i = 0; i < pass.passes; ++i) {
     Way way;
@@ -1248,6 +1272,10 @@ int specdec_prefill(specdec_ctx* c, specdec_role role, void* stream) {
     HIPCHK(c, sd::advance_cached(st, c->st, role, m.new_rows, c->B, one ? persist_flags(way, m) + 1 : nullptr));
   }
   c->uncached_ub[role] = 0;
+  if (role == SPECDEC_DRAFTER) {
+    c->uncached_block = 0;
+    c->short_cache = false;
+  }
   c->trusted[role] = false;
   return SPECDEC_OK;
 }
@@ -1261,7 +1289,8 @@ int specdec_draft(specdec_ctx* c, int32_t k, int32_t* draft, float* logits, void
   Model& m = c->m[SPECDEC_DRAFTER];
   hipStream_t st = S(stream);
   // stream tokens the drafter has not ingested yet: at most k_max + 1 fit beside the k slots
-  int ub = c->trusted[1] ? 1 : c->uncached_ub[1];
+  const int uncached = drafter_uncached(c, st);
+  int ub = c->trusted[1] ? 1 : uncached;
   if (ub < 1) ub = 1;
   if (ub > c->lim.k_max + 1) {
     rc = specdec_prefill(c, SPECDEC_DRAFTER, stream);
@@ -1286,7 +1315,7 @@ int specdec_draft(specdec_ctx* c, int32_t k, int32_t* draft, float* logits, void
   LAUNCH(c, SPECDEC_KIND_VOCAB, st, sd::vocab_stats(st, m.slots, m.embed, R, m.d.vocab, m.d.d_model, nullptr, nullptr, m.part, logits, c->wide_vocab));
   LAUNCH(c, SPECDEC_KIND_ACCEPT, st, sd::merge_drafts(st, m.part, n_tiles, m.row_stats, c->st, B, k, m.d.pad_id, m.new_rows,
                                       m.rm.seq_rows, draft, failed));
-  c->uncached_ub[1] = 0;
+  c->uncached_ub[1] = c->uncached_block = 0;
   c->trusted[1] = false;
   c->last_k_draft = k;
   return SPECDEC_OK;
@@ -1465,9 +1494,11 @@ int specdec_commit(specdec_ctx* c, const int32_t* accept_len, const int32_t* nex
   if (!accept_len || !next_token) return fail(c, SPECDEC_ERR_INVALID_ARG, "null accept_len/next_token");
   if (c->last_T <= 0) return fail(c, SPECDEC_ERR_BAD_STATE, "specdec_commit without a preceding specdec_verify");
   HIPCHK(c, sd::commit_rows(S(stream), c->st, accept_len, next_token, c->B, c->last_T - 1, c->m[0].d.eos_id, n_active));
-  const int appended = c->last_T;   // (at most)
+  // (two at least: a drafter's pass that came to nothing leaves a sequence behind, and a place more than plain steps need lets it catch up)
+  c->uncached_block += std::max(c->last_T, 2);
   c->last_T = 0;
-  c->uncached_ub[1] += appended;
+  c->uncached_ub[1] += c->lim.k_max + 1;
+  (void)drafter_uncached(c, S(stream));   // (captured?)
   return SPECDEC_OK;
 }
 
