@@ -257,14 +257,17 @@ int specdec_draft_heads(specdec_ctx* ctx, const int32_t* accept_len, int32_t k, 
  * are given up and a second kernel, which needs no more than one free compute unit, computes
  * the pass instead (same bits, 0.4 - 3 ms); so it does the run's next 63 passes without
  * waiting first.  (SPECDEC_OPT_SMALL_BATCH_KERNELS = 0: separate launches, which share a GPU freely.)
- * One stream of one process at a time runs such passes on a
+ * One stream of one process at a time runs such verification passes on a
  * GPU: that of the first context to ask, until it and the others on its stream are destroyed (a
  * context that captures one: until it is destroyed, whatever the stream).  A context on another
  * stream or in another process runs its passes as separate launches, from the first pass refused to its
  * next specdec_begin.  So does a stream with fewer compute units than the pass has workgroups.  The
- * two ways add in different orders: their logits differ in the last bits.  Processes in different
+ * two ways add in different orders: their logits differ in the last bits.  Drafting and prefill take the
+ * GPU from no verification: while a context has it, they run as one kernel on its stream alone (captured
+ * ones only in a context that has captured verification), else as separate launches; while none of any process has it, those on one stream of
+ * one process do, and not captured, until a verification pass comes.  Processes in different
  * network name spaces (containers) do not see each other, nor is a pass seen that a destroyed context
- * has left in flight: such passes may meet, and are then completed as above.
+ * has left in flight, or, by verification, a drafting or prefill pass in flight elsewhere: such passes may meet, and are then completed as above.
  * logits_or_null: optional device fp32 [B, k+1, V] receiving every row's logits (parity
  * mode; slow).  Does not change any length: calling it twice, on the same stream and within one run
  * (not captured in between), gives the same result. */

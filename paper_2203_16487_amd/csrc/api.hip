@@ -148,6 +148,8 @@ struct specdec_ctx {
   bool resident = false;    // SPECDEC_OPT_RESIDENT = 1: refuses what a pass of at most 32 rows as one kernel once did not support
   int persist_dev = -1;     // GPU on which this context is among the users of the one-kernel decoder
   bool persist_refused = false;   // another user was found on it in this run: separate launches until the next specdec_begin
+  int guest_dev = -1;       // the same for drafting and prefill while nobody verifies (PersistGpu)
+  bool guest_refused = false;
   Way way = Way::launches;  // of the latest pass
   bool give_up = false;     // SPECDEC_OPT_GIVE_UP_WAITS = 1: the one-kernel decoder's waits are given up at once
   bool sliced = false;      // SPECDEC_OPT_SLICED_SUBLAYERS = 1: small-batch sub-layers owned by head / FFN slice
@@ -597,29 +599,52 @@ int decoder_layers_sliced(specdec_ctx* c, Model& m, int B, int T, hipStream_t st
 // is alone with its GPU until it is destroyed (or, where it is not alone, captures the kernel-per-stage path).  Among processes
 // the user is the one that holds the lock named after the GPU's PCI address.  (`stream` is compared, never used: it may be gone.  So a
 // pass of a destroyed context that is still in flight is not seen, and one of the next context on another stream may meet it.)
+// It is verification that has the GPU so.  Drafting and prefill passes take nothing from it: they run so on the stream that verification has, in turn
+// with it, and as guests, by the same rules among themselves, while no context of any process verifies; a captured one, which could not give way, only
+// where its context has captured verification and is alone for that.  (A guest's pass in flight when verification begins may meet it, as above.)
 constexpr int kMaxDevices = 64;
-struct PersistGpu {
+struct PersistTurn {
   hipStream_t stream = nullptr;
   int users = 0;             // contexts
   bool captured = false;     // by the only one
   sd::ProcessLock lock;
+  char name[64] = {0};
+
+  // Whether a pass of a context (user: one of the users) has to be launches; where it has not, nobody else's may be otherwise until it has entered.
+  bool refuses(bool user, hipStream_t st, bool captures) {
+    if (users > (user ? 1 : 0)) return captured || captures || st != stream || st == hipStreamPerThread;
+    return !users && !lock.take(name);
+  }
+  void enter(int& dev_of_user, int dev, hipStream_t st, bool captures) {
+    if (dev_of_user < 0) {
+      ++users;
+      dev_of_user = dev;
+    }
+    stream = st;
+    captured |= captures;
+  }
+  void leave() {
+    if (--users) return;
+    captured = false;
+    lock.drop();
+  }
 };
+struct PersistGpu { PersistTurn verify, guests; };
 PersistGpu persist_gpu[kMaxDevices];
 std::mutex persist_mutex;
 
-bool persist_open(PersistGpu& o, int dev) {
-  char bus[32], name[64];
+bool persist_named(PersistGpu& gpu, int dev) {
+  char bus[32];
+  if (gpu.verify.name[0]) return true;
   if (hipDeviceGetPCIBusId(bus, sizeof bus, dev) != hipSuccess) return false;
-  snprintf(name, sizeof name, "specdec-%s", bus);
-  return o.lock.take(name);
+  snprintf(gpu.guests.name, sizeof gpu.guests.name, "specdec-guests-%s", bus);
+  snprintf(gpu.verify.name, sizeof gpu.verify.name, "specdec-%s", bus);
+  return true;
 }
 void persist_release(specdec_ctx* c) {
-  if (c->persist_dev < 0) return;
   std::lock_guard<std::mutex> guard(persist_mutex);
-  PersistGpu& o = persist_gpu[c->persist_dev];
-  if (--o.users) return;
-  o.captured = false;
-  o.lock.drop();
+  if (c->persist_dev >= 0) persist_gpu[c->persist_dev].verify.leave();
+  if (c->guest_dev >= 0) persist_gpu[c->guest_dev].guests.leave();
 }
 
 // Compute units a kernel on this stream may use: a stream can be made with a mask of them, and the environment can set one for
@@ -697,9 +722,9 @@ Way prefill_way(const Model& m, int B, int T, int cus) {
   return xcd && x.RP <= (B < 4 ? 80 : 112) ? Way::xcd_few : Way::launches;
 }
 
-// Whether the pass takes one of them (way: which); way_of(cus): the way it takes with as many compute units.
+// Whether the pass takes one of them (way: which); way_of(cus): the way it takes with as many compute units; verifies: else drafting or prefill.
 template <class F>
-bool persist_ok(specdec_ctx* c, const Model& m, hipStream_t st, F way_of, Way* way) {
+bool persist_ok(specdec_ctx* c, const Model& m, bool verifies, hipStream_t st, F way_of, Way* way) {
   *way = Way::launches;
   if (!m.pl_exch || c->no_skinny || c->no_ln_fold || c->sliced) return false;
   if (way_of(sd::kPlBlocks) == Way::launches) return false;   // (whatever the GPU and the stream have)
@@ -709,22 +734,36 @@ bool persist_ok(specdec_ctx* c, const Model& m, hipStream_t st, F way_of, Way* w
     return false;
   const Way found = way_of(std::min(cus, stream_cus(st)));   // (all of a way's workgroups run at once)
   if (found == Way::launches) return false;
-  if (c->persist_refused || (c->persist_dev >= 0 && c->persist_dev != dev)) return false;
+  if (c->persist_refused || (c->persist_dev >= 0 && c->persist_dev != dev) || (c->guest_dev >= 0 && c->guest_dev != dev)) return false;
   bool captures;
   if (!capture_state(st, &captures)) return false;
   std::lock_guard<std::mutex> guard(persist_mutex);
-  PersistGpu& o = persist_gpu[dev];
+  PersistGpu& gpu = persist_gpu[dev];
+  PersistTurn& o = gpu.verify;
   const bool user = c->persist_dev == dev;
-  // (for the whole run: the two ways add in different orders, and which one a pass takes is not to change with the life of others)
-  c->persist_refused = (o.users > (user ? 1 : 0) && (o.captured || captures || st != o.stream || st == hipStreamPerThread)) ||
-                       (!o.users && !persist_open(o, dev));
-  if (c->persist_refused) return false;
-  if (!user) {
-    ++o.users;
-    c->persist_dev = dev;
+  // (a refusal is for the whole run: the two ways add in different orders, and which one a pass takes is not to change with the life of others)
+  if (verifies) {
+    c->persist_refused = !persist_named(gpu, dev) || o.refuses(user, st, captures);
+    if (c->persist_refused) return false;
+    o.enter(c->persist_dev, dev, st, captures);
+  } else if (o.users > 0) {   // behind what verification has on its stream
+    const bool alone = user && o.users == 1;
+    if (st != o.stream || (!alone && (o.captured || captures || st == hipStreamPerThread)) || (captures && !o.captured) || (!user && c->guest_refused)) {
+      if (!user) c->guest_refused = true;
+      return false;
+    }
+  } else {
+    if (captures || c->guest_refused) return false;
+    PersistTurn& g = gpu.guests;
+    c->guest_refused = !persist_named(gpu, dev) || g.refuses(c->guest_dev == dev, st, false);
+    if (c->guest_refused) return false;
+    if (g.lock.held(o.name)) {   // (verification of another process)
+      c->guest_refused = true;
+      if (!g.users) g.lock.drop();
+      return false;
+    }
+    g.enter(c->guest_dev, dev, st, false);
   }
-  o.stream = st;
-  o.captured |= captures;
   *way = found;
   return true;
 }
@@ -1056,7 +1095,7 @@ int specdec_begin(specdec_ctx* c, int32_t B, int32_t max_new, void* stream) {
   c->uncached_ub[1] = c->uncached_block = 1;
   c->short_cache = false;
   c->trusted[0] = c->trusted[1] = false;
-  c->persist_refused = false;
+  c->persist_refused = c->guest_refused = false;
   c->m[0].has_memory = c->m[1].has_memory = false;
   return SPECDEC_OK;
 }
@@ -1263,7 +1302,7 @@ int specdec_prefill(specdec_ctx* c, specdec_role role, void* stream) {
   const int T = pass.T;
   for (int i = 0; i < pass.passes; ++i) {
     Way way;
-    const bool one = persist_ok(c, m, st, [&](int cus) { return prefill_way(m, c->B, T, cus); }, &way);
+    const bool one = persist_ok(c, m, false, st, [&](int cus) { return prefill_way(m, c->B, T, cus); }, &way);
     LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_stream(st, c->st, m.rm, role, c->B, T, 0, m.d.mask_id, m.d.pad_id, m.d.vocab,
                                         m.new_rows, m.embed, m.pe, m.x, m.xb, m.d.d_model, packed && !one, one ? m.pl_exch : nullptr,
                                         one ? persist_clear(way, m, c->B, T) : 0));
@@ -1302,7 +1341,7 @@ int specdec_draft(specdec_ctx* c, int32_t k, int32_t* draft, float* logits, void
   // grids are sized for the most (the GEMMs with LayerNorm folded in know how to stop early)
   // The per-XCD decoder takes T places a sequence, those beyond its rows among them.
   Way way;
-  const bool one = persist_ok(c, m, st, [&](int cus) { return draft_way(m, B, ub, k, cus); }, &way), packed = !one && !c->no_ln_fold;
+  const bool one = persist_ok(c, m, false, st, [&](int cus) { return draft_way(m, B, ub, k, cus); }, &way), packed = !one && !c->no_ln_fold;
   LAUNCH(c, SPECDEC_KIND_OTHER, st, sd::assemble_embed_stream(st, c->st, m.rm, SPECDEC_DRAFTER, B, T, k, m.d.mask_id, m.d.pad_id,
                                       m.d.vocab, m.new_rows, m.embed, m.pe, m.x, m.xb, m.d.d_model, packed, one ? m.pl_exch : nullptr,
                                       one ? persist_clear(way, m, B, T) : 0));
@@ -1357,7 +1396,7 @@ int verify_impl(specdec_ctx* c, const int32_t* draft, int32_t k, int32_t beta, f
   // The fused small-batch decoder kernels, whose every block redoes what precedes its product and which embed the rows
   // themselves, where that is little: one sequence of few rows, d = 512 (3 rows 184 against 205 us, 11: 210 / 214, 16: 220 /
   // 218; two sequences of 6 235 / 214; d = 1024: 6 rows 285 / 268, 26 521 / 302).  Otherwise the general ones.
-  const bool one = persist_ok(c, m, st, [&](int cus) { return one_kernel_way(m, B, T, small, cus); }, &c->way);
+  const bool one = persist_ok(c, m, true, st, [&](int cus) { return one_kernel_way(m, B, T, small, cus); }, &c->way);
   const bool fused = small && !one && (c->no_ln_fold || c->sliced || (B == 1 && R <= 12 && m.d.d_model <= 512));
   VerifyScratch vs{m.part, m.zd, m.row_stats};
   if (ext) {

@@ -8,6 +8,7 @@
 #include <sys/un.h>
 #include <unistd.h>
 
+#include <cerrno>
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
@@ -20,19 +21,24 @@ class ProcessLock {
   bool take(const char* name) {
     static const int registered = pthread_atfork(nullptr, nullptr, close_all);
     if (registered != 0 || fd_ >= 0 || count_ >= kMost) return false;
-    sockaddr_un address{};
-    address.sun_family = AF_UNIX;
-    const int n = snprintf(address.sun_path + 1, sizeof address.sun_path - 1, "%s", name);
-    if (n < 1 || n >= (int)sizeof address.sun_path - 1) return false;
+    sockaddr_un address;
+    const socklen_t n = named(address, name);
+    if (n == 0) return false;
     const int fd = socket(AF_UNIX, SOCK_DGRAM | SOCK_CLOEXEC, 0);
     if (fd < 0) return false;
-    if (bind(fd, reinterpret_cast<sockaddr*>(&address), (socklen_t)(offsetof(sockaddr_un, sun_path) + 1 + n)) != 0) {
+    if (bind(fd, reinterpret_cast<sockaddr*>(&address), n) != 0) {
       close(fd);
       return false;
     }
     fd_ = fd;
     held_[count_++] = this;
     return true;
+  }
+  // whether another lock holds that name, or it is not known that none does (asked through this one's socket: one that is not held does not know)
+  bool held(const char* name) const {
+    sockaddr_un address;
+    const socklen_t n = named(address, name);
+    return n == 0 || connect(fd_, reinterpret_cast<sockaddr*>(&address), n) == 0 || errno != ECONNREFUSED;
   }
   void drop() {
     if (fd_ < 0) return;
@@ -43,6 +49,13 @@ class ProcessLock {
   }
 
  private:
+  // the name's address and its length (0: no such name)
+  static socklen_t named(sockaddr_un& address, const char* name) {
+    address = sockaddr_un{};
+    address.sun_family = AF_UNIX;
+    const int n = snprintf(address.sun_path + 1, sizeof address.sun_path - 1, "%s", name);
+    return n < 1 || n >= (int)sizeof address.sun_path - 1 ? 0 : (socklen_t)(offsetof(sockaddr_un, sun_path) + 1 + n);
+  }
   // (callers hold a mutex of their own around take and drop)
   static void close_all() {
     for (int i = 0; i < count_; ++i) { close(held_[i]->fd_); held_[i]->fd_ = -1; }

@@ -39,6 +39,36 @@ int main(int, char** argv) {
   close(go[1]);
   CHECK(waitpid(child, nullptr, 0) == child);
   a.drop();
+  // asked, not taken: by a lock of another name, of this process and of others
+  char second[256];
+  snprintf(second, sizeof second, "%s-second", name);
+  CHECK(a.held(name));          // (no socket of its own to ask through)
+  CHECK(a.take(second));
+  CHECK(!a.held(name));
+  CHECK(b.take(name));
+  for (int i = 0; i < 3; ++i) CHECK(a.held(name));
+  CHECK(!other_takes(name));
+  b.drop();
+  CHECK(!a.held(name));         // (having asked does not keep it)
+  CHECK(other_takes(name));
+  int up[2], down[2];
+  CHECK(pipe(up) == 0 && pipe(down) == 0);
+  const pid_t holder = fork();
+  if (holder == 0) {
+    sd::ProcessLock l;
+    char c = l.take(name) ? 'y' : 'n';
+    (void)!write(up[1], &c, 1);
+    close(down[1]);
+    (void)!read(down[0], &c, 1);
+    _exit(0);
+  }
+  char c = 0;
+  CHECK(read(up[0], &c, 1) == 1 && c == 'y');
+  CHECK(a.held(name));
+  close(down[1]);
+  CHECK(waitpid(holder, nullptr, 0) == holder);
+  CHECK(!a.held(name));         // (gone with its process)
+  a.drop();
   // no socket to be had, or no such name: not the holder
   char longer[256];
   memset(longer, 'x', sizeof longer - 1);

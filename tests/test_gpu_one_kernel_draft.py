@@ -47,12 +47,12 @@ def test_against_oracle(B, k, S, j, prefill):
                          sample=sorted({0, B // 2, B - 1}) if B > 3 else None)
 
 
-def open_pass(B, k, j, seed, options=None, S=30):
+def open_pass(B, k, j, seed, options=None, S=30, ver=None):
     dd, db, dm = model()
     lens = synth.random_lengths(seed, "len", B, *j)
     toks = synth.random_tokens(seed, "stream", (B, int(lens.max()) + 1), dd)
     toks[:, 0] = dd.bos_id
-    ses = dl.open_session(B, k, S, 330, dr=(dd, db), options=options)
+    ses = dl.open_session(B, k, S, 330, ver=ver, dr=(dd, db), options=options)
     sd.specdec_begin(ses.ctx, B, 100)
     sd.specdec_encode(ses.ctx, ses.i32(synth.random_tokens(seed, "src", (B, S), dd)), ses.i32(synth.random_lengths(seed, "src_len", B, 2, S)))
     sd.specdec_set_stream(ses.ctx, ses.i32(toks), ses.i32(lens))
@@ -122,9 +122,13 @@ def test_short_cache_gives_pad_drafts():
 
 
 def test_replays_of_a_captured_pass():
-    """set_prefix, draft and its statistics as a graph: every replay, other work between them, has the eager pass's bits."""
+    """set_prefix, draft and its statistics as a graph: every replay, other work between them, has the eager pass's bits.  (One kernel in a context
+    that has captured verification.)"""
     B, k = 20, 10
-    ses, dd, toks, lens = open_pass(B, k, (12, 40), 78)
+    vd = synth.ModelDesc(1, 1, 512, 8, 2048, 1003, 300, 330).resolved()
+    ses, dd, toks, lens = open_pass(B, k, (12, 40), 78, ver=(vd, synth.make_weights(vd, 32, std=STD)))
+    sd.specdec_prefill(ses.ctx, sd.SPECDEC_VERIFIER)
+    acc, nxt = ses.i32(np.zeros(B)), ses.i32(np.zeros(B))
     sd.specdec_prefill(ses.ctx, sd.SPECDEC_DRAFTER)
     L = int(lens.max())
     K = torch.zeros((dd.dec_layers, B, L, dd.d_model), dtype=torch.bfloat16, device=ses.device)
@@ -141,6 +145,11 @@ def test_replays_of_a_captured_pass():
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):
+        verifies = torch.cuda.CUDAGraph()
+        sd.specdec_verify(ses.ctx, None, 0, 1, 0.0, acc, nxt)
+        side.synchronize()
+        with torch.cuda.graph(verifies, stream=side):
+            sd.specdec_verify(ses.ctx, None, 0, 1, 0.0, acc, nxt)
         launches, _ = resident_launches(ses, call)
         assert launches == 1
         side.synchronize()
