@@ -209,7 +209,8 @@ int specdec_prefill(specdec_ctx* ctx, specdec_role role, void* stream);
  * non-autoregressive decoder pass, argmax per slot -> draft device int32 [B, k].  Stream
  * tokens the drafter has not cached yet are processed (causally) in the same pass and
  * cached; mask slots attend to the whole stream and to all k slots.
- * With d_model 512 / d_ffn 2048 a pass whose places (k and the most stream tokens a sequence can
+ * With d_model 512 / d_ffn 2048 a pass of at least 200 drafts (of fewer the order of sums stays what it was: two logits as good
+ * as equal decide a draft now and then) whose places (k and the most stream tokens a sequence can
  * bring: all that commits since the drafter's latest pass may have appended, each its block's k + 1, but k_max + 1 behind
  * specdec_load_cache and from the first captured pass or commit of the context on; one in the first pass behind a loaded
  * cache) are few (at most 144 to a group, 128 where a sequence can bring several) runs its decoder layers as one kernel, each XCD on sequences of its own, under the

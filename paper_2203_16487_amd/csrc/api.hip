@@ -705,8 +705,11 @@ Way one_kernel_way(const Model& m, int B, int T, bool few, int cus) {
 Way draft_way(const Model& m, int B, int fresh, int k, int cus) {
   sd::XcdArgs x{};
   x.R = B * (fresh + k); x.T = fresh + k; x.B = B; x.H = m.d.n_heads;
-  // Sums are added in another order than by the launches, so a draft between two logits as good as equal may be the other one: 4 of 2400, whose
-  // logits were within 1.1e-3 of 1.7.  Passes of fewer than 200 drafts, where one such is a share that shows, keep the launches and their bits.
+  // Time has no line here: of fewer drafts this one is ahead by most (6 rows 96 / 58, 8 x 11 105 / 63).  But it adds in another order than the launches,
+  // and a draft whose two largest logits lie within that may be the other one: 9 of 4080, whose largest lie within 3e-3 of each other.  Neither order is
+  // the better one: the largest logits of 200 - 640 drafts are off those in 64 bits by 4.2e-4 - 4.7e-4 (2-norm, relative) either way, and of 1680 drafts 7
+  // and 10 are not the 64-bit ones.  The measured cases (perf/cases.py) allow one whole value in a hundred to differ, for ties, which one draft of fewer
+  // than 100 exceeds and two of 200 meet: passes of fewer than 200 keep the launches and their bits.
   if (B * k < 200) return Way::launches;
   const bool xcd = m.d.d_model == 512 && m.xcd_vecs && cus >= sd::kPlBlocks && xcd_takes(m, x);
   return xcd && x.RP <= (fresh > 1 ? 128 : 144) ? Way::xcd_few : Way::launches;

@@ -22,9 +22,9 @@
 // 113.6 us for 6 rows, from a copy 112.7).
 //
 // A drafter's pass of at least 200 drafts (d = 512; stream rows and slots of as many places a sequence as it can need) is one of these, its matrices read in place whatever
-// its rows.  Passes behind a loaded cache, statistics read back, launches / this kernel, us: one sequence of 5 + 1 rows 96 / 58, 8 x 11 105 / 63, 32 x 11
-// 124 / 83, on 500 source tokens and 200 cached ones 133 / 100, 64 x 8 123 / 96.  An iteration of the loop with a base verifier, 1 x 11 215 /
-// 185, 24 x 11 (504 places for the drafter, some 340 in use) 291 / 261.
+// its rows (fewer drafts are launches, see draft_way).  Passes behind a loaded cache, statistics read back, launches / this kernel, us: 32 x 11
+// 124 / 83, on 500 source tokens and 200 cached ones 133 / 100, 64 x 8 123 / 96.  An iteration of the loop with a base verifier, 24 x 11 (504 places
+// for the drafter, some 340 in use) 291 / 261.
 //
 // More than four row tiles (65 rows and more of an XCD; one column tile is summed at a time and, where LDS has no room for its row tiles, these in two
 // parts; of d = 512 the matrices are read in place): a tile more costs 0.4 us a stage where the launches of a pass beyond 512 rows cost 6 each.

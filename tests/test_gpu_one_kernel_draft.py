@@ -1,6 +1,6 @@
 """A drafter's pass of few rows (d_model 512, at least 200 drafts) as one kernel, each XCD on sequences of its own: row tiles and their remainders, stream rows of
-different numbers a sequence, slots beyond one tile of 16 queries and beyond a chunk of keys, against the oracle; caches loaded short of the
-stream, waits given up, replays of a captured pass, and the launches it takes with the kernels for small batches off."""
+different numbers a sequence, slots beyond one tile of 16 queries and beyond a chunk of keys, against the oracle, and the launches of passes of fewer
+drafts; caches loaded short of the stream, waits given up, replays of a captured pass, and the launches it takes with the kernels for small batches off."""
 import numpy as np
 import pytest
 import torch
@@ -22,29 +22,37 @@ def model(seed=31):
     return dd, db, orc.Model(dd, synth.weights_f32(db))
 
 
-@pytest.mark.parametrize("B,k,S,j,prefill", [
-    # (from 200 drafts on: one kernel)  j: stream lengths; without a prefill all j + 1 rows are the pass's own.  Rows of an XCD, row tiles
-    (1, 1, 5, (0, 0), False),           # one stream row, one slot
-    (1, 15, 40, (31, 31), True),        # 16, one
-    (1, 16, 40, (15, 15), False),       # 16 + 16, two; the slots are the second query tile
-    (3, 20, 90, (0, 12), False),        # up to 33, three
-    (1, 31, 33, (31, 31), False),       # 32 + 31, four: the most a sequence can have
-    (9, 10, 40, (0, 75), True),         # 22 and 11
-    (8, 25, 20, (0, 25), False),        # up to 51, four; places of two query tiles without rows
-    (24, 10, 30, (0, 10), False),       # up to 63, four
-    (40, 10, 64, (20, 140), True),      # 55, four
-    (64, 7, 70, (0, 60), True),         # 64: 512 rows, the most
-    (7, 29, 90, (0, 12), False),        # up to 42, three; one sequence to an XCD
-    (8, 31, 33, (31, 31), False),       # 32 + 31, four: the most a sequence can have
-    (17, 12, 260, (250, 290), True),    # several chunks of keys a wave
-    (2, 12, 260, (250, 290), True),     # several chunks of keys a wave
+@pytest.mark.parametrize("one,B,k,S,j,prefill", [
+    # j: stream lengths; without a prefill all j + 1 rows are the pass's own.
+    # launches: fewer than 200 drafts
+    (0, 1, 1, 5, (0, 0), False),        # one stream row, one slot
+    (0, 1, 15, 40, (31, 31), True),
+    (0, 1, 16, 40, (15, 15), False),    # 16 + 16: the slots are the second query tile
+    (0, 3, 20, 90, (0, 12), False),
+    (0, 1, 31, 33, (31, 31), False),    # 32 + 31: the most a sequence can have
+    (0, 9, 10, 40, (0, 75), True),
+    (0, 2, 12, 260, (250, 290), True),
+    # one kernel: rows of an XCD, row tiles
+    (1, 7, 31, 5, (0, 0), False),       # 1 + 31, two; one sequence to an XCD
+    (1, 40, 5, 20, (31, 31), True),     # 30, two
+    (1, 16, 15, 40, (0, 31), True),     # 32, two: a sequence's places are a query tile
+    (1, 25, 8, 40, (0, 75), True),      # 36 and 27, three and two
+    (1, 7, 29, 90, (0, 12), False),     # up to 42, three; one sequence to an XCD
+    (1, 8, 25, 20, (0, 25), False),     # up to 51, four; places of two query tiles without rows
+    (1, 24, 10, 30, (0, 10), False),    # up to 63, four
+    (1, 40, 10, 64, (20, 140), True),   # 55, four
+    (1, 64, 7, 70, (0, 60), True),      # 64, four
+    (1, 8, 31, 33, (31, 31), False),    # 32 + 31, four: the most a sequence can have
+    (1, 16, 16, 40, (15, 15), False),   # 2 x (16 + 16), four: the slots are the second query tile
+    (1, 11, 20, 90, (0, 12), False),    # up to 66, five
+    (1, 17, 12, 260, (250, 290), True), # several chunks of keys a wave
 ])
-def test_against_oracle(B, k, S, j, prefill):
+def test_against_oracle(one, B, k, S, j, prefill):
     dd, db, dm = model()
     lens = synth.random_lengths(100 + B + k, "len", B, *j)
     lens[0] = j[1]
     px.drafter_pass_case(dd, db, dm, B=B, S_max=S, k=k, lens=lens, seed=100 + B, prefill=prefill, max_tgt=330,
-                         sample=sorted({0, B // 2, B - 1}) if B > 3 else None)
+                         sample=sorted({0, B // 2, B - 1}) if B > 3 else None, one=one)
 
 
 def open_pass(B, k, j, seed, options=None, S=30, ver=None):

@@ -66,7 +66,7 @@ def test_drafting_against_oracle(B, k, S, j, prefill):
     dd, db, dm = model()
     lens = synth.random_lengths(700 + B, "len", B, *j)
     lens[0] = j[1]
-    px.drafter_pass_case(dd, db, dm, B=B, S_max=S, k=k, lens=lens, seed=700 + B, prefill=prefill, max_tgt=330, sample=(0, B // 2, B - 1))
+    px.drafter_pass_case(dd, db, dm, B=B, S_max=S, k=k, lens=lens, seed=700 + B, prefill=prefill, max_tgt=330, sample=(0, B // 2, B - 1), one=1)
 
 
 def test_drafting_given_up():

@@ -26,9 +26,10 @@ REL_TOL = 0.04          # of the oracle's logit standard deviation
 
 
 def drafter_pass_case(dd, db, dm, B, S_max, k, lens, seed, prefill, sample=None, max_tgt=64, fixed_src=False,
-                      options=None):
+                      options=None, one=None):
     """One Spec-Drafter pass of the whole batch on the GPU; the oracle recomputes `sample` (all
-    by default).  Returns the worst logit / key-value errors seen."""
+    by default).  Returns the worst logit / key-value errors seen.  one: whether its layers have to run as one kernel, or not
+    (None: as they may)."""
     src_len = np.full(B, S_max, np.int32) if fixed_src else synth.random_lengths(seed, "src_len", B, 2, S_max)
     src = synth.random_tokens(seed, "src", (B, S_max), dd)
     L_max = int(lens.max())
@@ -43,7 +44,11 @@ def drafter_pass_case(dd, db, dm, B, S_max, k, lens, seed, prefill, sample=None,
         sd.specdec_prefill(ses.ctx, sd.SPECDEC_DRAFTER)
     dr = torch.full((B, k), -1, dtype=torch.int32, device=dev)
     logits = torch.full((B, k, dd.vocab), float("nan"), dtype=torch.float32, device=dev)
+    sd.specdec_profile_select(ses.ctx, sd.KIND["resident"])
     sd.specdec_draft(ses.ctx, k, dr, logits)
+    launches = sd.specdec_profile_read(ses.ctx)[1]
+    sd.specdec_profile_select(ses.ctx, sd.KIND["none"])
+    assert one is None or launches == int(one)
     stats = torch.zeros((B, k, sd.ROW_STATS), dtype=torch.float32, device=dev)
     sd.specdec_get_draft_stats(ses.ctx, stats)
     L = L_max + 1
