@@ -1120,8 +1120,8 @@ int specdec_set_memory(specdec_ctx* c, specdec_role role, const void* memory, co
 // + src_len[b] - 1; grids are sized for B*S_max rows, row tiles beyond the real count return at once), in steps: its rows,
 // layer after layer, then the memory (bf16, packed) in m.exb and the cross-attention keys / values.
 struct EncoderRun {
-  Model* m;
-  hipStream_t st;
+  Model* m = nullptr;
+  hipStream_t st = nullptr;
   sd::LnPairs pend{nullptr, 0};   // LayerNorm folded into the projections, as in decoder_layers: m.ex holds un-normalised sums, m.exb them times the gain
   int flip = 1, step = 0;
   int steps() const { return m->d.enc_layers + 2; }
@@ -1202,9 +1202,10 @@ int specdec_encode(specdec_ctx* c, const int32_t* src, const int32_t* src_len, i
   HIPCHK(c, sd::set_src_len(st, c->st, src_len, c->B, S_max));
   c->S_cur = S_max;
   const bool apart = n == 2 && encoders_apart(c, st);
-  std::vector<EncoderRun> runs;
+  EncoderRun runs[2];
+  int used = 0;
   for (int r = 0; r < 2; ++r)
-    if (c->m[r].bound && c->m[r].d.enc_layers > 0) runs.push_back(EncoderRun{&c->m[r], apart && r == SPECDEC_DRAFTER ? c->side : st});
+    if (c->m[r].bound && c->m[r].d.enc_layers > 0) runs[used++] = EncoderRun{&c->m[r], apart && r == SPECDEC_DRAFTER ? c->side : st};
   if (apart) {
     HIPCHK(c, hipEventRecord(c->side_ev[0], st));
     HIPCHK(c, hipStreamWaitEvent(c->side, c->side_ev[0], 0));
@@ -1212,8 +1213,8 @@ int specdec_encode(specdec_ctx* c, const int32_t* src, const int32_t* src_len, i
   int rc = SPECDEC_OK;
   while (!rc) {   // launched in turn, the one that is less far; or one after the other
     EncoderRun* next = nullptr;
-    for (EncoderRun& run : runs)
-      if (run.step < run.steps() && (!next || (apart && run.step * next->steps() < next->step * run.steps()))) next = &run;
+    for (EncoderRun* run = runs; run < runs + used; ++run)
+      if (run->step < run->steps() && (!next || (apart && run->step * next->steps() < next->step * run->steps()))) next = run;
     if (!next) break;
     rc = encoder_step(c, *next, src, c->B, S_max);
   }
