@@ -1230,7 +1230,9 @@ static hipError_t launch_ln(hipStream_t st, const bf16* A, int lda, const SkWeig
   // a long K pays for a larger tile where the ring's tiles are more than one to a CU (FFN2 of the big model at 1408 rows: 64 x 64 ring
   // 28.0 us, with three waves 24.2; but at 1024 rows 19.2 and 22.9); at K <= 2048 the ring is level or better, and so it is where M is only a
   // bound on the rows in use.  Four waves, one to a SIMD, whose rings take all of the LDS: a verify pass of 128 x 11 rows 885 us with three, now 876 (x 1024 x
-  // 1024 so as well, in place of the 64 x 64 ring: 890).  What a CU takes in bounds it, some 64 B/ns: fragments of a slab read under the products of the one
+  // 1024 so as well, in place of the 64 x 64 ring: 890).  The four partial sums, of other slabs than the three, are added in another order: statistics of a
+  // pass of 1408 rows move by 7e-5 - 1.6e-4 (2-norm, relative), as far as they are from those in 64 bits (8.5e-5 - 1.8e-4 with three, 8.2e-5 - 1.8e-4
+  // with four).  What a CU takes in bounds it, some 64 B/ns: fragments of a slab read under the products of the one
   // before it were slower (886).
   if constexpr (Epi::kVec == 3) {
     if (K >= 4096 && !m_real && !one_round(M, N, 64, 64) && one_round(M, N, 96, 64)) return launch_ksplit<KsplitCfg<96, 64, 4, 2>>(st, A, lda, W, M, N, K, epi, m_real);
