@@ -112,9 +112,11 @@ typedef enum {
                                           out += (p * v_scale) * codes.  Changes the model like FP8_WEIGHTS does;
                                           the two options are independent.  Refused by RESIDENT / SLICED_SUBLAYERS. */
   SPECDEC_OPT_WIDE_VOCAB_TILES = 6,    /* default 0: the vocabulary projection of a pass of more than 32 rows takes
-                                          its 256 x 256 tiles only where they give every compute unit one or more
-                                          (the batched passes), else 128 x 128 tiles.  1: 256 x 256 tiles in every
-                                          such pass (so that the wide kernel can be checked on small shapes).     */
+                                          256 x 256 tiles only where they give every compute unit one or more (the batched
+                                          passes) or tiles of 128 x 128 would begin a second round, others of 256 rows or of
+                                          192 where these fit its rows better, else 128 x 128 tiles.  1: 256 x 256 tiles (of
+                                          257 - 384 rows 192 x 256) in every such pass, so that the wide kernels can be checked
+                                          on small shapes.                                                        */
   SPECDEC_OPT_GIVE_UP_WAITS = 7        /* default 0.  1: every wait of the one-kernel decoder that does not end at once is
                                           given up (in groups: one workgroup of each is left out, and waits end at their
                                           bound, of at most 63 rows after 64 polls), and the pass completed by the kernel behind it
