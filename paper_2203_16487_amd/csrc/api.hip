@@ -610,7 +610,8 @@ struct PersistTurn {
   sd::ProcessLock lock;
   char name[64] = {0};
 
-  // Whether a pass of a context (user: one of the users) has to be launches; where it has not, nobody else's may be otherwise until it has entered.
+  // Whether a pass of a context (user: it is one of the users) has to be launches.  If not, the lock is held: by the users, or taken here for the first one
+  // (enter() follows, or lock.drop()).
   bool refuses(bool user, hipStream_t st, bool captures) {
     if (users > (user ? 1 : 0)) return captured || captures || st != stream || st == hipStreamPerThread;
     return !users && !lock.take(name);
